@@ -4,9 +4,9 @@
 //   mode spectrum      eigenvalues (and eigenvectors) of G = A_m A_m^T, the squared singular values and
 //                      left singular vectors of the mode-m unfolding (App. A.2): k_mode_gram accumulates
 //                      G in fp64 on the MFMA, split over column ranges; k_gram_reduce adds the ranges in a
-//                      fixed order; a cyclic one-sided Jacobi iteration (k_jacobi_round, one launch per
-//                      round of disjoint row pairs, one wave per pair) orthogonalises the rows of W = G,
-//                      after which row k is lambda_k v_k^T; k_spectrum_finish sorts.
+//                      fixed order; k_chol_panel factors it (G = R^T R), a cyclic one-sided Jacobi iteration
+//                      (k_jacobi_small, k_jacobi_block) orthogonalises the rows of W = R, after which row k
+//                      is sqrt(lambda_k) v_k^T; k_spectrum_finish sorts.
 //   explained variance ranks per threshold (Sec. 3.3, Step 1): k_ev_ranks.
 //   perplexity         Frobenius norm of the difference of two weight gradients (Eq. 7): k_frob_partial,
 //                      k_frob_final.
@@ -16,6 +16,7 @@
 // asi_weight_grad_* on the truncated eigenvectors).
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
@@ -132,18 +133,21 @@ __global__ __launch_bounds__(256) void k_mode_gram(GramJob jb) {
         }
 }
 
-// G[e] = sum over the column ranges, in their order
+// G[e] = sum over the column ranges, in their order, 32 of them in flight; the first workgroup clears the iteration's counters
 __global__ __launch_bounds__(256) void k_gram_reduce(const double* __restrict__ part, int nsplit, long long cnt,
-                                                     double* __restrict__ G) {
+                                                     double* __restrict__ G, int32_t* __restrict__ zero, int nzero) {
+    if (blockIdx.x == 0 && (int)threadIdx.x < nzero) zero[threadIdx.x] = 0;
     const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
     if (e >= cnt) return;
     double s = 0.0;
-    for (int z = 0; z < nsplit; ++z) s += part[(long long)z * cnt + e];
+    for (int z0 = 0; z0 < nsplit; z0 += 32) {
+        double t[32];
+#pragma unroll
+        for (int u = 0; u < 32; ++u) t[u] = part[(long long)(z0 + u < nsplit ? z0 + u : nsplit - 1) * cnt + e];
+#pragma unroll
+        for (int u = 0; u < 32; ++u) s += z0 + u < nsplit ? t[u] : 0.0;
+    }
     G[e] = s;
-}
-
-__global__ void k_set_i32(int32_t* p, int32_t v) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *p = v;
 }
 
 __device__ __forceinline__ double wave_sum(double x) {
@@ -152,75 +156,393 @@ __device__ __forceinline__ double wave_sum(double x) {
     return x;
 }
 
-// One round of the cyclic one-sided Jacobi iteration on the rows of W (n x n, row-major): workgroup p (one
-// wave) takes the p-th pair of the round-robin schedule on n2 = n rounded up to even players, and rotates its
-// two rows so that they become orthogonal.  The pairs of a round are disjoint, so the waves touch disjoint
-// rows; rounds are ordered by the stream.  `rotations` counts the pairs that were not yet orthogonal.
-__global__ __launch_bounds__(64) void k_jacobi_round(double* __restrict__ W, int n, int round, double tol,
-                                                     int32_t* __restrict__ rotations) {
-    constexpr int NE = RK_NMAX / 64;
-    const int n2 = (n + 1) & ~1, m = n2 - 1, p = blockIdx.x, lane = threadIdx.x;
-    int a = p == 0 ? m : (round + p) % m;
-    int b = p == 0 ? round : (round - p + m) % m;
-    if (a > b) { const int t = a; a = b; b = t; }
-    if (b >= n) return;                                  // the bye of an odd n
-    double* ra = W + (long long)a * n;
-    double* rb = W + (long long)b * n;
-    double x[NE], y[NE];
-    double al = 0.0, be = 0.0, ga = 0.0;
+// ---- Cholesky factor of the Gram matrix --------------------------------------------------------------------
+// G + s I = R^T R (R upper triangular); the iteration below runs on the rows of R, whose singular values are the square
+// roots of G's eigenvalues, and not on G itself: half the spread, and a factor is already half way to orthogonal rows
+// (18 sweeps become 12 on a 160-long mode whose spectrum falls over six decades and ends in noise; simulated for
+// several spectra before it was built).  The shift s = 4 n eps trace(G) keeps every pivot positive whatever G's rank
+// and is subtracted from the eigenvalues again, so it costs no accuracy beyond the rounding of G itself.  G is also
+// scaled by a power of two (exact) so that its trace is near 1: the iteration squares squares.
+// One launch per panel of 32 rows: workgroup (I, J) factors the 32 x 32 diagonal block (redundantly: 32 dependent steps,
+// 3 us, less than a launch of its own), solves the panel's blocks above I and J and updates the trailing block (I, J).
+constexpr int RK_CB = 32;
+struct CholScale { double scale, shift; };               // what the factorisation applied: W^T W = scale (G + shift / scale I)
+
+__global__ __launch_bounds__(256) void k_chol_scale(const double* __restrict__ G, int n, double shift_factor, CholScale* out) {
+    __shared__ double red[4];
+    const int tid = threadIdx.x;
+    double s = 0.0;
 #pragma unroll
-    for (int k = 0; k < NE; ++k) {
-        const int i = lane + 64 * k;
-        x[k] = i < n ? ra[i] : 0.0;
-        y[k] = i < n ? rb[i] : 0.0;
-        al += x[k] * x[k]; be += y[k] * y[k]; ga += x[k] * y[k];
+    for (int u = 0; u < RK_NMAX / 256; ++u) {
+        const int k = tid + 256 * u;
+        const double g = G[(long long)(k < n ? k : 0) * (n + 1)];
+        s += k < n ? g : 0.0;
     }
-    al = wave_sum(al); be = wave_sum(be); ga = wave_sum(ga);
-    if (!(fabs(ga) > tol * sqrt(al * be))) return;       // orthogonal already (or a zero row)
-    const double zeta = (be - al) / (2.0 * ga);
-    const double t = (zeta >= 0.0 ? 1.0 : -1.0) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
-    const double c = 1.0 / sqrt(1.0 + t * t), s = c * t;
-#pragma unroll
-    for (int k = 0; k < NE; ++k) {
-        const int i = lane + 64 * k;
-        if (i < n) {
-            ra[i] = c * x[k] - s * y[k];
-            rb[i] = s * x[k] + c * y[k];
-        }
+    s = wave_sum(s);
+    if ((tid & 63) == 0) red[tid >> 6] = s;
+    __syncthreads();
+    if (tid == 0) {
+        const double tr = (red[0] + red[1]) + (red[2] + red[3]);
+        int e = 0;
+        const bool ok = tr > 0.0 && tr < 1e300;          // (a zero tensor: the factor is sqrt(shift) I)
+        if (ok) (void)frexp(tr, &e);
+        out->scale = ldexp(1.0, -e);
+        out->shift = ok ? shift_factor * ldexp(tr, -e) : 1.0;
     }
-    if (lane == 0) atomicAdd(rotations, 1);
 }
 
-// After convergence row k of W is lambda_k v_k^T.  Eigenvalues in descending order (ties by row index),
+__global__ __launch_bounds__(256) void k_chol_panel(double* __restrict__ G, double* __restrict__ W, int n, int P,
+                                                    const CholScale* __restrict__ sc) {
+    constexpr int B = RK_CB, LD = B + 1;
+    __shared__ double D[B * LD], Xi[B * LD], Xj[B * LD], dinv[B];
+    const int tid = threadIdx.x, nb = (n + B - 1) / B, rest = nb - P - 1;
+    // workgroup 0 writes the diagonal block of R; the others are the tiles I <= J of the trailing matrix
+    int I = P, J = P;
+    if (rest > 0) {
+        int q = blockIdx.x, i = 0;
+        while (q >= rest - i) { q -= rest - i; ++i; }
+        I = P + 1 + i; J = I + q;
+    }
+    const double scale = P == 0 ? sc->scale : 1.0, shift = P == 0 ? sc->shift : 0.0;   // applied when G is first read
+    auto ld = [&](int row, int col) {                    // G is symmetric; only blocks on or above the diagonal stay valid
+        const bool in = row < n && col < n;
+        const double g = G[(long long)(in ? row : 0) * n + (in ? col : 0)];
+        return in ? g * scale + (row == col ? shift : 0.0) : (row == col ? 1.0 : 0.0);
+    };
+    double td[4], ti[4], tj[4], tg[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int e = tid + 256 * u, r = e >> 5, c = e & 31;
+        td[u] = ld(P * B + r, P * B + c);
+        ti[u] = ld(P * B + r, I * B + c);
+        tj[u] = ld(P * B + r, J * B + c);
+        tg[u] = ld(I * B + r, J * B + c);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int e = tid + 256 * u, r = e >> 5, c = e & 31;
+        D[r * LD + c] = td[u]; Xi[r * LD + c] = ti[u]; Xj[r * LD + c] = tj[u];
+    }
+    __syncthreads();
+    // D = R_PP^T R_PP, rows left unscaled (row k holds R_kk R_kj) and the pivots' reciprocals kept: one barrier per step
+    const int r0 = tid >> 5, c0 = tid & 31;
+    for (int k = 0; k < B; ++k) {
+        const double pk = 1.0 / D[k * LD + k], dk = D[k * LD + c0] * pk;
+        double v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = D[(r0 + 8 * u) * LD + c0] - D[k * LD + r0 + 8 * u] * dk;
+        if (tid == 0) dinv[k] = pk;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (r0 + 8 * u > k && c0 >= r0 + 8 * u) D[(r0 + 8 * u) * LD + c0] = v[u];
+        __syncthreads();
+    }
+    if (rest > 0 && tid < 2 * B) {
+        // forward substitution down one column of the panel (unscaled rows: x_k = g_k, later rows lose R_kr R_kk x_k / R_kk^2)
+        double* x = tid < B ? Xi : Xj;
+        const int c = tid & 31;
+        double t[B];
+#pragma unroll
+        for (int k = 0; k < B; ++k) t[k] = x[k * LD + c];
+#pragma unroll
+        for (int k = 0; k < B; ++k) {
+            const double f = t[k] * dinv[k];
+#pragma unroll
+            for (int r = k + 1; r < B; ++r) t[r] = fma(-D[k * LD + r], f, t[r]);
+        }
+#pragma unroll
+        for (int k = 0; k < B; ++k) x[k * LD + c] = t[k];
+    }
+    __syncthreads();
+    if (rest > 0) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int r = r0 + 8 * u;
+            double s = tg[u];
+#pragma unroll
+            for (int k = 0; k < B; ++k) s = fma(-Xi[k * LD + r] * dinv[k], Xj[k * LD + c0], s);
+            const int row = I * B + r, col = J * B + c0;
+            if (row < n && col < n) G[(long long)row * n + col] = s;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int r = r0 + 8 * u, row = P * B + r;
+        const double rs = sqrt(dinv[r]);
+        if (rest > 0 && I == J) {                        // R's rows right of the diagonal block, zeros below it
+            if (row < n && I * B + c0 < n) W[(long long)row * n + I * B + c0] = Xi[r * LD + c0] * rs;
+            if (I * B + r < n && P * B + c0 < n) W[(long long)(I * B + r) * n + P * B + c0] = 0.0;
+        }
+        if (blockIdx.x == 0 && row < n && P * B + c0 < n)
+            W[(long long)row * n + P * B + c0] = c0 >= r ? D[r * LD + c0] * rs : 0.0;
+    }
+}
+
+// ---- cyclic one-sided Jacobi iteration on the rows of W (n x n, row-major) -------------------------------------
+// A rotation of two rows makes them orthogonal; a sweep visits every pair once.  The iteration is a chain of n - 1
+// dependent rounds of disjoint pairs per sweep and some ten sweeps: what bounds it is the length of a round, not
+// arithmetic.  One launch per round cost ~5 us a round (32 ms for a 512-long mode, 7 ms for 160); here the rounds of a
+// launch run inside workgroups that hold their rows in LDS, 16 lanes to a pair (1.8 ms for 160, 8.9 ms for 512, factor and
+// all; a round of cross pairs is 0.6 us, of which the LDS traffic of the rows is about a third).
+//   n <= 64: one workgroup holds all rows and runs the whole iteration to convergence in one launch.
+//   n > 64:  rows in blocks of 16.  A launch pairs the blocks (round-robin over blocks), a workgroup takes two blocks and
+//            visits their 16 x 16 cross pairs in 16 rounds; the first launch of a sweep also visits the pairs inside the
+//            blocks (31 rounds over the 32 rows).  A sweep is ceil(n/16) - 1 launches instead of n - 1.
+// Every pair of a sweep is visited exactly once; the squared norms of the rows are computed when a launch starts
+// and carried through its rotations.
+constexpr int RK_JB = 16;               // rows of a block
+constexpr int RK_JL = 16;               // lanes of a pair
+
+// sum over the 16 lanes of a pair: four rotations inside the row of 16 lanes; every lane gets the same bits
+// (each step adds the same two numbers in both lanes)
+template <int ROR>
+__device__ __forceinline__ double row_ror(double x) {
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), 0x120 + ROR, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), 0x120 + ROR, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double row16_sum(double x) {
+    x += row_ror<8>(x);
+    x += row_ror<4>(x);
+    x += row_ror<2>(x);
+    x += row_ror<1>(x);
+    return x;
+}
+// 1 / sqrt(x) for positive normal x: the hardware's estimate and two Newton steps (x e^2 = 1 + d, e <- e (1 - d/2 + 3 d^2/8))
+__device__ __forceinline__ double rsqrt64(double x) {
+    double e = __builtin_amdgcn_rsq(x);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const double d = fma(-x * e, e, 1.0);
+        e = fma(e * d, fma(d, 0.375, 0.5), e);
+    }
+    return e;
+}
+
+// The rotation (c, s) that makes rows with squared norms al, be and product ga orthogonal: x' = c x - s y, y' = s x + c y.
+// With d = be - al, g = 2 ga, h = sqrt(d^2 + g^2):  c = sqrt((1 + |d| / h) / 2),  s = sign(d) g / (2 h c), the smaller of
+// the two angles.  Returns false (c = 1, s = 0) where the rows are orthogonal to the rounding of their product already.
+__device__ __forceinline__ bool rotation(double& al, double& be, double ga, double tol2, double* c, double* s) {
+    *c = 1.0; *s = 0.0;
+    if (!(ga * ga > tol2 * (al * be))) return false;
+    const double d = be - al, g = 2.0 * ga;
+    const double ih = rsqrt64(fma(d, d, g * g));
+    const double c2 = fma(0.5 * fabs(d), ih, 0.5), rc = rsqrt64(c2);
+    *c = c2 * rc;
+    *s = (d >= 0.0 ? 0.5 : -0.5) * g * ih * rc;
+    const double tg = *s * rc * ga;                      // tan(angle) ga, rc = 1 / c
+    al -= tg; be += tg;
+    return true;
+}
+
+// pair p of round `round` of the round-robin schedule over m + 1 players (m odd)
+__device__ __forceinline__ void round_robin(int m, int round, int p, int* a, int* b) {
+    int u = p == 0 ? m : round + p, v = p == 0 ? round : round - p;
+    if (p != 0 && u >= m) u -= m;
+    if (v < 0) v += m;
+    *a = u < v ? u : v;
+    *b = u < v ? v : u;
+}
+
+// Rotates the rows ra, rb in LDS (16 NE elements, zero padded) with squared norms in na, nb; returns whether it did.
+template <int NE>
+__device__ __forceinline__ bool jacobi_pair(double* ra, double* rb, double* na, double* nb, int lane, double tol2) {
+    double x[NE], y[NE], al = *na, be = *nb, ga = 0.0, g2 = 0.0;
+#pragma unroll
+    for (int k = 0; k < NE; ++k) { x[k] = ra[lane + RK_JL * k]; y[k] = rb[lane + RK_JL * k]; }
+#pragma unroll
+    for (int k = 0; k < NE; k += 2) { ga = fma(x[k], y[k], ga); g2 = fma(x[k + 1], y[k + 1], g2); }
+    ga = row16_sum(ga + g2);
+    double c, s;
+    if (!rotation(al, be, ga, tol2, &c, &s)) return false;
+#pragma unroll
+    for (int k = 0; k < NE; ++k) {
+        ra[lane + RK_JL * k] = fma(c, x[k], -s * y[k]);
+        rb[lane + RK_JL * k] = fma(s, x[k], c * y[k]);
+    }
+    if (lane == 0) { *na = al; *nb = be; }
+    return true;
+}
+// squared norm of an LDS row by its 16 lanes
+template <int NE>
+__device__ __forceinline__ void row_norm2(const double* r, double* out, int lane) {
+    double q = 0.0;
+#pragma unroll
+    for (int k = 0; k < NE; ++k) { const double v = r[lane + RK_JL * k]; q = fma(v, v, q); }
+    q = row16_sum(q);
+    if (lane == 0) *out = q;
+}
+
+// n <= 64: the whole iteration.  32 pairs x 16 lanes; rot[0] = sweeps used if converged, else 0.
+__global__ __launch_bounds__(512) void k_jacobi_small(double* __restrict__ W, int n, double tol2, int max_sweeps,
+                                                      int32_t* __restrict__ rot) {
+    constexpr int NE = 4, LD = 64 + 16;                  // pitch 16 mod 32 doubles: two rows on disjoint banks
+    __shared__ double w[64 * LD], nrm[64];
+    __shared__ int s_rot;
+    const int tid = threadIdx.x, lane = tid & (RK_JL - 1), p = tid / RK_JL;
+    const int n2 = (n + 1) & ~1, m = n2 - 1;
+    for (int e = tid; e < 64 * 64; e += 512) {
+        const int i = e >> 6, j = e & 63;
+        w[i * LD + j] = (i < n && j < n) ? W[i * n + j] : 0.0;
+    }
+    int used = 0;
+    for (int sweep = 0; sweep < max_sweeps; ++sweep) {
+        __syncthreads();
+        if (tid == 0) s_rot = 0;
+        row_norm2<NE>(w + p * LD, nrm + p, lane);
+        row_norm2<NE>(w + (p + 32) * LD, nrm + p + 32, lane);
+        __syncthreads();
+        int mine = 0;
+        for (int round = 0; round < m; ++round) {
+            int a, b;
+            round_robin(m, round, p, &a, &b);
+            if (2 * p < n2 && b < n) mine += jacobi_pair<NE>(w + a * LD, w + b * LD, nrm + a, nrm + b, lane, tol2) ? 1 : 0;
+            __syncthreads();                             // a row is written by one pair and read by another in the next round
+        }
+        if (lane == 0 && mine) atomicAdd(&s_rot, mine);
+        __syncthreads();
+        if (s_rot == 0) { used = sweep + 1; break; }     // the same for all threads
+    }
+    for (int e = tid; e < n * n; e += 512) {
+        const int i = e / n, j = e - i * n;
+        W[e] = w[i * LD + j];
+    }
+    if (tid == 0) rot[0] = used;
+}
+
+// One launch of a sweep for n > 64: workgroup q takes the q-th pair of blocks of `round`.  prev / cur: rotations of the
+// sweep before (null in the first; zero there means converged, nothing is done) and of this one.
+extern __shared__ double jac_dyn[];
+template <int NE>
+__global__ __launch_bounds__(256) void k_jacobi_block(double* __restrict__ W, int n, int nblk2, int round, double tol2,
+                                                      const int32_t* __restrict__ prev, int32_t* __restrict__ cur) {
+    constexpr int LD = RK_JL * NE + ((RK_JL * NE) % 32 == 0 ? 16 : 0);
+    if (prev && *prev == 0) return;
+    __shared__ int s_rot;
+    __shared__ double nrm[2 * RK_JB];
+    double* w = jac_dyn;                                 // 32 rows of LD
+    const int tid = threadIdx.x, lane = tid & (RK_JL - 1), p = tid / RK_JL;
+    int bi, bj;
+    round_robin(nblk2 - 1, round, blockIdx.x, &bi, &bj);
+    if (tid == 0) s_rot = 0;
+    // this thread group's two rows; rows past the end are zeros and never rotate.  All loads are in flight together.
+    const int gi = bi * RK_JB + p, gj = bj * RK_JB + p;
+    double x[NE], y[NE];
+#pragma unroll
+    for (int k = 0; k < NE; ++k) {
+        const int i = lane + RK_JL * k, ic = i < n ? i : n - 1;
+        x[k] = W[(long long)(gi < n ? gi : n - 1) * n + ic];
+        y[k] = W[(long long)(gj < n ? gj : n - 1) * n + ic];
+    }
+#pragma unroll
+    for (int k = 0; k < NE; ++k) {
+        const bool in = lane + RK_JL * k < n;
+        x[k] = in && gi < n ? x[k] : 0.0;
+        y[k] = in && gj < n ? y[k] : 0.0;
+    }
+    double* ri = w + p * LD + lane;
+    double* rj = w + (RK_JB + p) * LD + lane;
+    double qx = 0.0, qy = 0.0;
+#pragma unroll
+    for (int k = 0; k < NE; ++k) {
+        ri[RK_JL * k] = x[k]; rj[RK_JL * k] = y[k];
+        qx = fma(x[k], x[k], qx); qy = fma(y[k], y[k], qy);
+    }
+    qx = row16_sum(qx); qy = row16_sum(qy);
+    if (lane == 0) { nrm[p] = qx; nrm[RK_JB + p] = qy; }
+    __syncthreads();
+    int mine = 0;
+    if (round == 0) {                                    // the pairs inside the blocks and across them
+        for (int q = 0; q < 2 * RK_JB - 1; ++q) {
+            int a, b;
+            round_robin(2 * RK_JB - 1, q, p, &a, &b);
+            mine += jacobi_pair<NE>(w + a * LD, w + b * LD, nrm + a, nrm + b, lane, tol2) ? 1 : 0;
+            __syncthreads();
+        }
+#pragma unroll
+        for (int k = 0; k < NE; ++k) x[k] = ri[RK_JL * k];
+    } else {
+        // a row of block I stays in the registers of its lanes, the rows of block J go round through LDS
+        double al = qx;
+        for (int q = 0; q < RK_JB; ++q) {
+            const int b = RK_JB + ((p + q) & (RK_JB - 1));
+            double* rb = w + b * LD + lane;
+            double be = nrm[b], ga = 0.0, g2 = 0.0;
+#pragma unroll
+            for (int k = 0; k < NE; ++k) y[k] = rb[RK_JL * k];
+#pragma unroll
+            for (int k = 0; k < NE; k += 2) { ga = fma(x[k], y[k], ga); g2 = fma(x[k + 1], y[k + 1], g2); }
+            ga = row16_sum(ga + g2);
+            double c, s;
+            if (rotation(al, be, ga, tol2, &c, &s)) {
+#pragma unroll
+                for (int k = 0; k < NE; ++k) {
+                    const double v = fma(c, x[k], -s * y[k]);
+                    rb[RK_JL * k] = fma(s, x[k], c * y[k]);
+                    x[k] = v;
+                }
+                if (lane == 0) nrm[b] = be;
+                ++mine;
+            }
+            __syncthreads();
+        }
+    }
+    if (lane == 0 && mine) atomicAdd(&s_rot, mine);
+#pragma unroll
+    for (int k = 0; k < NE; ++k) {
+        const int i = lane + RK_JL * k;
+        y[k] = rj[RK_JL * k];
+        if (i < n && gi < n) W[(long long)gi * n + i] = x[k];
+        if (i < n && gj < n) W[(long long)gj * n + i] = y[k];
+    }
+    __syncthreads();
+    if (tid == 0 && s_rot) atomicAdd(cur, s_rot);
+}
+
+// After convergence row k of W is sqrt(lambda_k) v_k^T, lambda_k an eigenvalue of the scaled and shifted G.  Eigenvalues in descending order (ties by row index),
 // eigenvectors as the columns of an n x n row-major fp32 matrix; a column whose eigenvalue is below
 // 1e-12 of the largest (a null direction, whose row carries no direction any more) is returned as zeros.
-__global__ __launch_bounds__(256) void k_spectrum_finish(const double* __restrict__ W, int n, double* __restrict__ lam_out,
-                                                         float* __restrict__ vec_out) {
-    __shared__ double lam[RK_NMAX];
-    __shared__ int order[RK_NMAX];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    for (int k = wave; k < n; k += 4) {
-        double s = 0.0;
-        for (int i = lane; i < n; i += 64) { const double w = W[(long long)k * n + i]; s += w * w; }
-        s = wave_sum(s);
-        if (lane == 0) lam[k] = sqrt(s);
+__global__ __launch_bounds__(64) void k_row_norms(const double* __restrict__ W, int n, double* __restrict__ norms, const CholScale* __restrict__ sc) {
+    constexpr int NE = RK_NMAX / 64;
+    const int k = blockIdx.x, lane = threadIdx.x;
+    double t[NE];
+#pragma unroll
+    for (int u = 0; u < NE; ++u) t[u] = W[(long long)k * n + (lane + 64 * u < n ? lane + 64 * u : 0)];
+    double s = 0.0;
+#pragma unroll
+    for (int u = 0; u < NE; ++u) s += lane + 64 * u < n ? t[u] * t[u] : 0.0;
+    s = wave_sum(s);
+    if (lane == 0) norms[k] = s > sc->shift ? (s - sc->shift) / sc->scale : 0.0;       // the eigenvalue of G itself
+}
+// workgroup k places row k: its rank among the eigenvalues by counting, then its column of the eigenvector matrix
+__global__ __launch_bounds__(256) void k_spectrum_finish(const double* __restrict__ W, int n, const double* __restrict__ norms, const CholScale* __restrict__ sc,
+                                                         double* __restrict__ lam_out, float* __restrict__ vec_out) {
+    __shared__ int s_pos[4];
+    __shared__ double s_max[4];
+    const int tid = threadIdx.x, k = blockIdx.x;
+    const double l = norms[k];
+    int pos = 0;
+    double lmax = 0.0;
+#pragma unroll
+    for (int u = 0; u < RK_NMAX / 256; ++u) {
+        const int j = tid + 256 * u;
+        const double lj = norms[j < n ? j : 0];
+        if (j < n) {
+            pos += (lj > l || (lj == l && j < k)) ? 1 : 0;
+            lmax = fmax(lmax, lj);
+        }
     }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) { pos += __shfl_xor(pos, d, 64); lmax = fmax(lmax, __shfl_xor(lmax, d, 64)); }
+    if ((tid & 63) == 0) { s_pos[tid >> 6] = pos; s_max[tid >> 6] = lmax; }
     __syncthreads();
-    for (int k = tid; k < n; k += 256) {
-        int pos = 0;
-        for (int j = 0; j < n; ++j) pos += (lam[j] > lam[k] || (lam[j] == lam[k] && j < k)) ? 1 : 0;
-        order[pos] = k;
-        lam_out[pos] = lam[k];
-    }
-    __syncthreads();
+    pos = s_pos[0] + s_pos[1] + s_pos[2] + s_pos[3];
+    lmax = fmax(fmax(s_max[0], s_max[1]), fmax(s_max[2], s_max[3]));
+    if (tid == 0) lam_out[pos] = l;
     if (!vec_out) return;
-    const double lmax = lam[order[0]];
-    for (long long e = tid; e < (long long)n * n; e += 256) {
-        const int i = (int)(e / n), k = (int)(e - (long long)i * n);
-        const int row = order[k];
-        const double l = lam[row];
-        vec_out[e] = (l > 1e-12 * lmax && l > 0.0) ? (float)(W[(long long)row * n + i] / l) : 0.f;
-    }
+    const bool live = l > 1e-12 * lmax && l > 0.0;
+    const double inv = live ? 1.0 / sqrt(l * sc->scale + sc->shift) : 0.0;       // the row's norm
+    for (int i = tid; i < n; i += 256) vec_out[(long long)i * n + pos] = (float)(W[(long long)k * n + i] * inv);
 }
 
 struct EpsList { double eps[16]; int count; };
@@ -280,7 +602,8 @@ bool parse_mode(const asi_tensor_desc* desc, int mode, ModeShape* ms, asi_status
     ms->bf16 = desc->dtype == ASI_BF16;
     return true;
 }
-struct GramPlan { int tiles, nchunks, nsplit; size_t part_bytes, w_bytes, bytes; };
+constexpr int RK_SWEEPS = 60;
+struct GramPlan { int tiles, nchunks, nsplit; size_t part_bytes, w_bytes, norm_bytes, bytes; };
 GramPlan plan_gram(const ModeShape& ms) {
     GramPlan p;
     p.tiles = (ms.n + RK_T - 1) / RK_T;
@@ -293,8 +616,35 @@ GramPlan plan_gram(const ModeShape& ms) {
     p.nsplit = (int)want;
     p.part_bytes = align_up(sizeof(double) * (size_t)p.nsplit * ms.n * ms.n);
     p.w_bytes = align_up(sizeof(double) * (size_t)ms.n * ms.n);
-    p.bytes = p.part_bytes + p.w_bytes + RK_ALIGN;      // partial Gram matrices, W, the rotation counter
+    p.norm_bytes = align_up(sizeof(double) * (size_t)ms.n);
+    // partial Gram matrices, G, W, the eigenvalues in row order, scale and shift, a rotation counter per sweep
+    p.bytes = p.part_bytes + 2 * p.w_bytes + p.norm_bytes + align_up(sizeof(CholScale)) + align_up(sizeof(int32_t) * RK_SWEEPS);
     return p;
+}
+
+// the launches of one sweep for n > 64: every pair of blocks once
+template <int NE>
+hipError_t jacobi_sweep(double* W, int n, double tol2, const int32_t* prev, int32_t* cur, hipStream_t st) {
+    constexpr size_t lds = sizeof(double) * 2 * RK_JB * (RK_JL * NE + ((RK_JL * NE) % 32 == 0 ? 16 : 0));
+    if (lds > 65536) {
+        static std::atomic<bool> allowed{false};
+        if (!allowed.load()) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_jacobi_block<NE>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            if (e != hipSuccess) return e;
+            allowed.store(true);
+        }
+    }
+    const int nblk2 = ((n + RK_JB - 1) / RK_JB + 1) & ~1;
+    for (int round = 0; round < nblk2 - 1; ++round)
+        hipLaunchKernelGGL(k_jacobi_block<NE>, dim3((unsigned)(nblk2 / 2)), 256, lds, st, W, n, nblk2, round, tol2, prev, cur);
+    return hipGetLastError();
+}
+hipError_t launch_jacobi_sweep(double* W, int n, double tol2, const int32_t* prev, int32_t* cur, hipStream_t st) {
+    if (n <= 128) return jacobi_sweep<8>(W, n, tol2, prev, cur, st);
+    if (n <= 192) return jacobi_sweep<12>(W, n, tol2, prev, cur, st);
+    if (n <= 256) return jacobi_sweep<16>(W, n, tol2, prev, cur, st);
+    return jacobi_sweep<32>(W, n, tol2, prev, cur, st);
 }
 
 struct Search {
@@ -357,8 +707,12 @@ asi_status asi_mode_spectrum(const asi_tensor_desc* desc, const void* A, int32_t
     hipStream_t st = static_cast<hipStream_t>(stream);
     char* base = static_cast<char*>(ws);
     double* part = reinterpret_cast<double*>(base);
-    double* W = reinterpret_cast<double*>(base + p.part_bytes);
-    int32_t* rot = reinterpret_cast<int32_t*>(base + p.part_bytes + p.w_bytes);
+    base += p.part_bytes;
+    double* G = reinterpret_cast<double*>(base); base += p.w_bytes;
+    double* W = reinterpret_cast<double*>(base); base += p.w_bytes;
+    double* norms = reinterpret_cast<double*>(base); base += p.norm_bytes;
+    CholScale* sc = reinterpret_cast<CholScale*>(base); base += align_up(sizeof(CholScale));
+    int32_t* rot = reinterpret_cast<int32_t*>(base);
     const int n = ms.n;
 
     GramJob jb;
@@ -368,28 +722,46 @@ asi_status asi_mode_spectrum(const asi_tensor_desc* desc, const void* A, int32_t
     if (ms.bf16) hipLaunchKernelGGL(k_mode_gram<bf16_t>, grid, 256, 0, st, jb);
     else hipLaunchKernelGGL(k_mode_gram<float>, grid, 256, 0, st, jb);
     const long long cnt = (long long)n * n;
-    hipLaunchKernelGGL(k_gram_reduce, dim3((unsigned)((cnt + 255) / 256)), 256, 0, st, part, p.nsplit, cnt, W);
+    hipLaunchKernelGGL(k_gram_reduce, dim3((unsigned)((cnt + 255) / 256)), 256, 0, st, part, p.nsplit, cnt, G, rot, RK_SWEEPS);
+    hipLaunchKernelGGL(k_chol_scale, dim3(1), 256, 0, st, G, n, 4.0 * n * 1.1102230246251565e-16, sc);
+    for (int P = 0, nb = (n + RK_CB - 1) / RK_CB; P < nb; ++P) {
+        const int rest = nb - P - 1;
+        hipLaunchKernelGGL(k_chol_panel, dim3((unsigned)(rest > 0 ? rest * (rest + 1) / 2 : 1)), 256, 0, st, G, W, n, P, sc);
+    }
     if (hipGetLastError() != hipSuccess) return ASI_ERR_HIP;
 
-    // sweeps of n2 - 1 rounds until a whole sweep rotates nothing; the count comes back to the host after
-    // every sweep (this entry point iterates to convergence and therefore waits for the stream)
-    const int n2 = (n + 1) & ~1, npairs = n2 / 2;
+    // sweeps until a whole one rotates nothing; the counts come back to the host (this entry point iterates to
+    // convergence and therefore waits for the stream)
     const double tol = 4.0 * n * 2.220446049250313e-16;     // two rows count as orthogonal below the rounding of their dot product
     int used = 0;
     bool converged = n == 1;
-    for (int sweep = 0; sweep < 60 && !converged; ++sweep) {
-        hipLaunchKernelGGL(k_set_i32, dim3(1), 64, 0, st, rot, 0);
-        for (int round = 0; round < n2 - 1; ++round)
-            hipLaunchKernelGGL(k_jacobi_round, dim3((unsigned)npairs), 64, 0, st, W, n, round, tol, rot);
-        if (hipGetLastError() != hipSuccess) return ASI_ERR_HIP;
-        int32_t h = -1;
-        if (hipMemcpyAsync(&h, rot, sizeof(int32_t), hipMemcpyDeviceToHost, st) != hipSuccess) return ASI_ERR_HIP;
-        if (hipStreamSynchronize(st) != hipSuccess) return ASI_ERR_HIP;
-        used = sweep + 1;
-        converged = h == 0;
+    int32_t h[RK_SWEEPS];
+    auto read_counts = [&](int count) {
+        return hipMemcpyAsync(h, rot, sizeof(int32_t) * count, hipMemcpyDeviceToHost, st) == hipSuccess &&
+               hipStreamSynchronize(st) == hipSuccess;
+    };
+    if (n > 1 && n <= 64) {
+        hipLaunchKernelGGL(k_jacobi_small, dim3(1), 512, 0, st, W, n, tol * tol, RK_SWEEPS, rot);
+        if (hipGetLastError() != hipSuccess || !read_counts(1)) return ASI_ERR_HIP;
+        used = h[0];
+        converged = used > 0;
+    } else if (n > 64) {
+        // Sweeps are handed over several at a time (a sweep that follows a converged one returns at once), so that the
+        // host's wait for a count does not stand between every two of them.
+        for (int done = 0; done < RK_SWEEPS && !converged;) {
+            int upto = done + (done == 0 ? 6 : 2);
+            if (upto > RK_SWEEPS) upto = RK_SWEEPS;
+            for (int sweep = done; sweep < upto; ++sweep)
+                if (launch_jacobi_sweep(W, n, tol * tol, sweep ? rot + sweep - 1 : nullptr, rot + sweep, st) != hipSuccess) return ASI_ERR_HIP;
+            if (!read_counts(upto)) return ASI_ERR_HIP;
+            for (int sweep = done; sweep < upto && !converged; ++sweep)
+                if (h[sweep] == 0) { converged = true; used = sweep + 1; }
+            done = upto;
+        }
     }
     if (sweeps) *sweeps = converged ? used : -1;
-    hipLaunchKernelGGL(k_spectrum_finish, dim3(1), 256, 0, st, W, n, eigenvalues, eigenvectors);
+    hipLaunchKernelGGL(k_row_norms, dim3((unsigned)n), 64, 0, st, W, n, norms, sc);
+    hipLaunchKernelGGL(k_spectrum_finish, dim3((unsigned)n), 256, 0, st, W, n, norms, sc, eigenvalues, eigenvectors);
     if (hipGetLastError() != hipSuccess) return ASI_ERR_HIP;
     return converged ? ASI_OK : ASI_ERR_NUMERIC;
 }

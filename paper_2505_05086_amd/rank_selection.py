@@ -85,23 +85,25 @@ def perplexity_row(A: torch.Tensor, grad_out: torch.Tensor, dW_exact: torch.Tens
     rank_rows = explained_variance_ranks(spectra, eps)
     f32 = dict(dtype=torch.float32, device=A.device)
     fws = torch.empty(B.FROBENIUS_WS_BYTES, dtype=torch.uint8, device=A.device)
-    out = torch.empty(1, dtype=torch.float64, device=A.device)
+    distinct = list(dict.fromkeys(rank_rows))
+    out = torch.empty(len(distinct), dtype=torch.float64, device=A.device)
+    dW = torch.empty(dW_exact.shape, **f32)
+    memory = []
+    for k, ranks in enumerate(distinct):        # nothing waits between the thresholds: the distances are read once, below
+        desc = B.make_desc(tuple(A.shape), ranks, _dtype_name(A))
+        ws = B.alloc_workspace(desc, conv, dout, device=A.device)
+        U = hosvd_factors(spectra, ranks)
+        S = torch.empty(ranks, **f32)
+        B.asi_core_project(desc, A, U, S, ws)
+        if conv is not None:
+            B.asi_weight_grad_conv2d(desc, S, U, grad_out, conv, dW, False, ws)
+        else:
+            B.asi_weight_grad_linear(desc, S, U, grad_out, dout, dW, False, ws)
+        B.asi_frobenius_diff(dW_exact, dW, out[k:k + 1], fws)
+        memory.append(B.asi_activation_memory(desc))
+    done = dict(zip(distinct, zip(memory, out.tolist())))
     table = LayerTable([], [], [])
-    done = {}
     for ranks in rank_rows:
-        if ranks not in done:
-            desc = B.make_desc(tuple(A.shape), ranks, _dtype_name(A))
-            ws = B.alloc_workspace(desc, conv, dout, device=A.device)
-            U = hosvd_factors(spectra, ranks)
-            S = torch.empty(ranks, **f32)
-            B.asi_core_project(desc, A, U, S, ws)
-            dW = torch.empty(dW_exact.shape, **f32)
-            if conv is not None:
-                B.asi_weight_grad_conv2d(desc, S, U, grad_out, conv, dW, False, ws)
-            else:
-                B.asi_weight_grad_linear(desc, S, U, grad_out, dout, dW, False, ws)
-            B.asi_frobenius_diff(dW_exact, dW, out, fws)
-            done[ranks] = (B.asi_activation_memory(desc), float(out.item()))
         mem, ppl = done[ranks]
         table.ranks.append(ranks)
         table.memory.append(mem)

@@ -70,6 +70,30 @@ def test_mode_spectra_against_library_svd(case):
         assert O.max_rel_err(O.projector(U), O.projector(Uo)) <= 1e-5, m
 
 
+@pytest.mark.parametrize("n", [2, 63, 64, 65, 97, 128, 129, 192, 193, 257, 512])
+@pytest.mark.parametrize("thin", [False, True])
+def test_mode_spectrum_at_the_edges_of_the_iteration(n, thin):
+    """One workgroup up to 64 rows, blocks of 16 rows beyond (register shapes to 128, 192, 256, 512), panels of 32 in the
+    factorisation; thin: fewer columns than rows, so that the Gram matrix is singular and only the shift keeps it definite.
+    Eigenvalues to n eps of the trace (the rounding of the Gram matrix and of its factor), at most 1e-12 of the largest x 10."""
+    B, RS = _mods()
+    rng = np.random.default_rng(n + 7 * thin)
+    dims = (3, n, 5) if thin else (4, n, 160)
+    A = rng.standard_normal(dims).astype(np.float32) * (0.9 ** np.arange(n, dtype=np.float32))[None, :, None]
+    sp = RS.mode_spectrum(torch.from_numpy(A).cuda(), 1)
+    want = R.mode_spectrum(A.astype(F64), 1)
+    lam = sp.eigenvalues.cpu().numpy()
+    assert sp.sweeps >= 1 and np.all(np.diff(lam) <= 0)
+    assert np.max(np.abs(lam - want)) <= 4 * n * np.finfo(F64).eps * want.sum()
+    live = int(np.sum(want > 1e-10 * want[0]))
+    U = sp.eigenvectors.double().cpu().numpy()
+    # fp32 columns: rounding 6e-8 each, summed over the n entries of a dot product of unit vectors
+    assert np.max(np.abs(U[:, :live].T @ U[:, :live] - np.eye(live))) <= 1e-6
+    A1 = np.moveaxis(A.astype(F64), 1, 0).reshape(n, -1)
+    res = A1.T @ U[:, :live]                      # column norms are the singular values
+    assert np.max(np.abs((res * res).sum(0) - want[:live])) <= 1e-6 * want[0]
+
+
 def test_explained_variance_ranks_match_the_oracle_on_planted_spectra():
     B, RS = _mods()
     rng = np.random.default_rng(7)
