@@ -93,7 +93,7 @@ struct CompressPlan {
     bool longm[4] = {};              // long fibres: V and P from one LDS tile of complete fibres (asi_long.hip)
     bool paired = false;             // the last two modes of a 4-mode tensor share one kernel
     bool tiny = false;               // ... the vector-ALU kernel for tiny planes
-    bool planes = false;             // ... the kernel for large planes (asi_planes.hip)
+    bool planes = false;             // ... the Gram-matrix kernel for planes of up to 64 x 64 (asi_planes.hip)
     bool fast_orth[4] = {};
     bool wide_orth[4] = {};
     size_t bytes = 0;
@@ -128,14 +128,13 @@ CompressPlan plan_compress(const Shape& s, void* ws, bool cold = false) {
     p.Vpart = c.take<float>(vpmax);
     p.ctr8 = c.take<int32_t>(8);
     p.tiny = !cold && s.d == 4 && subspace_tiny_supported((int)s.n[2], (int)s.n[3], s.r[2], s.r[3]);
-    p.planes = !cold && s.d == 4 && subspace_planes_supported(s.n[0] * s.n[1], (int)s.n[2], (int)s.n[3], s.r[2], s.r[3]);
-    p.paired = p.tiny || p.planes || (!cold && s.d == 4 && subspace_pair_supported((int)s.n[2], (int)s.n[3], s.r[2], s.r[3]));
+    p.planes = !cold && s.d == 4 && !p.tiny && subspace_planes_supported(s.n[0] * s.n[1], (int)s.n[2], (int)s.n[3], s.r[2], s.r[3]);
+    p.paired = p.tiny || p.planes;
     for (int m = 0; m < s.d; ++m) {
         const size_t n = (size_t)s.n[m], r = (size_t)s.r[m];
         if (p.tiny && m >= 2) p.nsplit[m] = subspace_tiny_nwg(s.n[0] * s.n[1]);
-        else if (p.planes && m >= 2) p.nsplit[m] = subspace_planes_nwg(s.n[0] * s.n[1]);
-        else if (p.paired && m >= 2) p.nsplit[m] = subspace_pair_nwg(s.n[0] * s.n[1], (int)s.n[2], (int)s.n[3]);
-        else if (p.gramm[m]) p.nsplit[m] = subspace_gram_nwg(s.outer(m), (int)n, s.inner(m));
+        else if (p.planes && m >= 2) p.nsplit[m] = subspace_planes_nwg(s.dt, s.n[0] * s.n[1], (int)s.n[2], (int)s.n[3]);
+        else if (p.gramm[m]) p.nsplit[m] = subspace_gram_nwg(s.dt, s.outer(m), (int)n, s.inner(m));
         else if (p.longm[m]) p.nsplit[m] = subspace_long_splits(s.outer(m), (int)n, s.inner(m), (int)r);
         else p.nsplit[m] = p.fused[m] ? subspace_small_nwg(s.outer(m), (int)n, s.inner(m))
                                       : pair_splits(s.outer(m), (int)n, s.inner(m), (int)r);
@@ -511,13 +510,9 @@ asi_status build_compress(const asi_tensor_desc* desc, const void* A, const floa
                 ASI_ADD(pg, "", tot * esize(s.dt) + 8.0 * (n * r + (double)s.n[3] * s.r[3]) * p.nsplit[m], 4.0 * tot * (r + s.r[3]),
                         make_subspace_planes(s.dt, A, s.n[0] * s.n[1], n, (int)s.n[3], U_prev[2], r, p.part[2], U_prev[3], s.r[3],
                                              p.part[3], p.nsplit[m], nullptr, 0, it__));
-            else if (p.tiny)
-                ASI_ADD(pg, "", tot * esize(s.dt) + 8.0 * (n * r + (double)s.n[3] * s.r[3]) * p.nsplit[m], 4.0 * tot * (r + s.r[3]),
-                        make_subspace_tiny(s.dt, A, s.n[0] * s.n[1], n, (int)s.n[3], U_prev[2], r, p.part[2], U_prev[3], s.r[3],
-                                           p.part[3], p.nsplit[m], it__));
             else
                 ASI_ADD(pg, "", tot * esize(s.dt) + 8.0 * (n * r + (double)s.n[3] * s.r[3]) * p.nsplit[m], 4.0 * tot * (r + s.r[3]),
-                        make_subspace_pair(s.dt, A, s.n[0] * s.n[1], n, (int)s.n[3], U_prev[2], r, p.part[2], U_prev[3], s.r[3],
+                        make_subspace_tiny(s.dt, A, s.n[0] * s.n[1], n, (int)s.n[3], U_prev[2], r, p.part[2], U_prev[3], s.r[3],
                                            p.part[3], p.nsplit[m], it__));
         } else if (p.paired && m == 3) {
             // done together with mode 3

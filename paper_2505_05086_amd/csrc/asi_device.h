@@ -29,6 +29,25 @@ __device__ __forceinline__ double ldg_f64(const double* __restrict__ p, long lon
     return ok ? v : 0.0;
 }
 
+// Memory-to-LDS copy without registers: every active lane of the wave moves 16 bytes from src + off (off below `bytes`, the
+// extent of src) to lds + 16 * lane, lds being the same for the whole wave.  Waited for like any load (a workgroup barrier
+// does).  The builtins exist in the device pass only.
+__device__ __forceinline__ void copy16_to_lds(const void* src, int bytes, int off, void* lds) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(src), 0, bytes, 0x00027000),
+                                             (__attribute__((address_space(3))) void*)lds, 16, off, 0, 0, 0);
+#endif
+}
+
+// Waits until at most N of this wave's copies (or other vector loads) are outstanding, then for the workgroup: a barrier that
+// leaves the newest copies on their way.  LDS reads before it must have been consumed, as they are when they feed products.
+template <int N>
+__device__ __forceinline__ void wait_copies_and_sync() {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(N) : "memory");
+#endif
+}
+
 // A tensor seen from one mode: X[o, i, j], o < outer, i < n (the mode), j < inner.
 // Column c of the mode unfolding (Sec. 3.2) is the pair (o, j) = (c / inner, c % inner).
 struct ModeView {

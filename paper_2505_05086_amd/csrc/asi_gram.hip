@@ -5,263 +5,273 @@
 // n x n matrix G = A_m A_m^T is tiny, so the step is one pass over the activation that accumulates G
 // and a product G U_prev at the end; V (columns x r) is never formed, not even in registers:
 //     G[i][i'] = sum_c X[i][c] X[i'][c]      fp64 MFMA 16x16x4, both operands from ONE LDS read
-//     P        = G U_prev                    n * n * r multiply-adds per workgroup, fp64
+//     P        = G U_prev                    fp64 MFMA, once per workgroup
 // Products of fp32 (or bf16) values are exact in fp64 and the sums are carried in fp64, so P is at least
 // as accurate as the two-product form (which rounds V to fp32 in between).
 //
-// A lane reads 16 bytes of one LDS row: columns c0 + 4 (lane / 16) .. + 3 of row lane % 16.  Element s of
-// those four is the lane's operand of K step s, for the row block as A operand and as B operand alike
-// (A[i][k] and B[k][j] of the instruction both come from lane (k, i) resp. (k, j)), so which column a K
-// slot stands for does not matter.  Per 16 columns and row block a wave issues one LDS read and four
-// conversions for 4 * (blocks on or above the diagonal) MFMAs: the matrix pipe is the only busy unit.
+// A tile is the n rows of a range of columns, 16 or 32 KB.  The pass is bound by memory up to two row blocks (n <= 32), so
+// what counts is how much of it is on its way: the tiles travel straight from memory to LDS, 16 bytes per lane and
+// instruction, without registers or vector instructions, into a ring of buffers (16 KB each, six; 32 KB each, four) of
+// which all but two are in flight while one is multiplied and one is being freed; one workgroup of eight waves per CU.
+// What lies past the tensor's rows or past the columns of a slice is given an offset beyond the buffer descriptor's
+// extent: the copy then writes zeros, so neither the copy nor the products have a test for it.  In LDS the 16-byte pieces
+// of row i are permuted (piece p of the row sits at p ^ (i % 16)), which spreads the 16 rows an operand read touches over
+// the banks.
+//
+// 32 entries over 401 K columns (51 MB) 24.4 -> 20.4 us, 64 over 605 K in bf16 (77 MB, bound by the fp64 MFMA: 40 us of
+// products) 82 -> 71, 8 entries over 32 K columns 7.7 -> 5.3 (against tiles through registers, two workgroups per CU).
+//
+// A lane reads four consecutive columns c0 + 4 (lane / 16) .. + 3 of row lane % 16.  Element s of those four is the
+// lane's operand of K step s, for the row block as A operand and as B operand alike (A[i][k] and B[k][j] of the instruction
+// both come from lane (k, i) resp. (k, j)), so which column a K slot stands for does not matter.
 //
 // A mode of at most 8 indices would leave half of the 16 x 16 result unused.  Its tile holds S = 2 (4 for
 // n <= 4) ranges of columns stacked in the 16 rows (row s n + i = index i of range s); the diagonal
 // n x n sub-blocks of the result are the Gram matrices of the ranges (the rest mixes ranges and is
 // dropped), so each instruction covers S times the columns.
-#include "asi_device.h"
+#include "asi_gram_device.h"
 #include "asi_kernels.h"
 
+#include <atomic>
 #include <cstdio>
 #include <cstring>
 
 namespace asi {
 
-typedef double v4d __attribute__((ext_vector_type(4)));
-typedef float v4f __attribute__((ext_vector_type(4)));
-
-constexpr int SG_NT = 256;
-constexpr int SG_MAX_WG = 512;             // two resident workgroups per CU, each walking several tiles
-template <int NBM>
-constexpr int sg_tc() { return NBM == 1 ? 512 : (NBM == 2 ? 256 : 128); }      // columns per tile: ~33 KB of LDS
+constexpr int SG_NT = 512, SG_NW = SG_NT / 64;
+constexpr int SG_MAX_WG = 256;             // one workgroup per CU, each walking several tiles
+template <int NB> constexpr int sg_row_bytes() { return NB == 1 ? 1024 : 512; }
+template <int NB> constexpr int sg_buf_bytes() { return 16 * (NB <= 2 ? NB : 4) * sg_row_bytes<NB>(); }     // 16, 16, 32, 32 KB
+template <int NB> constexpr int sg_nbuf() { return NB <= 2 ? 6 : 4; }
 
 struct GramJob {
     const void* X;       // (outer, n, inner)
     const float* U;      // (n, r) previous factor
     double* part;        // (nwg, n, r) partial sums of P
     long long outer, inner;
-    long long tiles_per_o, ntiles;
+    int tiles_per_o, ntiles;
     int n, r, nwg;
     int S;               // n <= 8: S = 2 (n <= 4: 4) column ranges of a tile are stacked in the 16 LDS rows
     int32_t* zero;       // nullable: `nzero` int32 to clear
     int nzero;
 };
 
-template <typename T> struct Vec4;
-template <> struct Vec4<float> { typedef v4f type; };
-template <> struct Vec4<bf16_t> { typedef uint2 type; };
-__device__ __forceinline__ v4f widen4(v4f x) { return x; }
-__device__ __forceinline__ v4f widen4(uint2 x) {
-    v4f o;
-    o[0] = __uint_as_float(x.x << 16); o[1] = __uint_as_float(x.x & 0xffff0000u);
-    o[2] = __uint_as_float(x.y << 16); o[3] = __uint_as_float(x.y & 0xffff0000u);
-    return o;
-}
+extern __shared__ __align__(16) unsigned char sg_raw[];
 
-// VEC: rows of X start 16-byte (fp32) / 8-byte (bf16) aligned and inner is a multiple of 4, so a thread
-// moves four consecutive columns at a time; otherwise single elements.
-template <typename T, int NBM, bool VEC>
+// DMA: X starts 16-byte aligned, rows are a multiple of 16 bytes long and a slice is below 2 GiB; otherwise single elements
+// through registers.
+template <typename T, int NB, bool DMA>
 __global__ __launch_bounds__(SG_NT, 2) void k_subspace_gram(Batch<GramJob> bt) {
-    constexpr int TC = sg_tc<NBM>(), PITCH = TC + 4, ROWS = 16 * NBM;
-    constexpr int NPAIR = NBM * (NBM + 1) / 2;
-    __shared__ __align__(16) float Xs[ROWS * PITCH];
-    static_assert(sizeof(float) * ROWS * PITCH >= sizeof(double) * ROWS * ROWS, "the Gram matrix fits the tile buffer");
+    constexpr int RB = sg_row_bytes<NB>(), TC = RB / (int)sizeof(T), BUF = sg_buf_bytes<NB>(), NBUF = sg_nbuf<NB>();
+    constexpr int PPR = RB / 16, NP = gram_blocks<NB>();
+    constexpr int NL = BUF / 16 / SG_NT;                   // copies per thread and tile
     int lb;
     const GramJob& jb = bt.job[locate(bt, &lb)];
     const T* __restrict__ X = static_cast<const T*>(jb.X);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lg = lane >> 4, ll = lane & 15;
-    const int n = jb.n, r = jb.r;
-    const int S = NBM == 1 ? jb.S : 1;
-    const float inv_n = 1.0f / (float)n;
+    const int tid = threadIdx.x, lane = tid & 63, lg = lane >> 4, ll = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = jb.n, r = jb.r, S = NB == 1 ? jb.S : 1, rows = S * n;
     const long long inner = jb.inner;
     if (jb.zero && lb == 0 && tid < jb.nzero) jb.zero[tid] = 0;
-    for (int e = tid; e < ROWS * PITCH; e += SG_NT) Xs[e] = 0.f;      // rows >= n stay zero for good
-    // U_prev for the product at the end: fetched now (all loads of the workgroup together, addresses valid for
-    // every lane), so that the last step reads it from LDS instead of one word at a time from memory
-    __shared__ float Us[ROWS * 64];
-    {
-        constexpr int NU = ROWS * 64 / SG_NT;
-        float ut[NU];
+
+    auto origin = [&](int tile, int* o, long long* j0, int* vc) __attribute__((always_inline)) {
+        *o = (unsigned)tile / (unsigned)jb.tiles_per_o;
+        *j0 = (long long)(tile - *o * jb.tiles_per_o) * (TC * S);
+        *vc = (int)(inner - *j0 < TC * S ? inner - *j0 : TC * S);
+    };
+    // ---- copies: piece u * SG_NT + tid of a tile is LDS slot (row, slot) = global piece slot ^ (row % 16) of the row
+    constexpr int FAR = 0x7ffffff0;                        // past any descriptor's extent: the copy writes zeros
+    int goff[DMA ? NL : 1], gcol[DMA ? NL : 1];            // byte offset from the tile's first element; its column range
+    if constexpr (DMA) {
 #pragma unroll
-        for (int u = 0; u < NU; ++u) {
-            const int e = tid + SG_NT * u;
-            ut[u] = jb.U[e < n * r ? e : 0];
+        for (int u = 0; u < NL; ++u) {
+            const int pc = u * SG_NT + tid, row = pc / PPR, cp = (pc % PPR) ^ (row & 15);
+            const int sidx = S > 1 ? row / n : 0, i = row - sidx * n;
+            gcol[u] = row < rows ? (sidx * TC) * (int)sizeof(T) + 16 * cp : FAR;
+            goff[u] = (int)(i * inner * (int)sizeof(T)) + (sidx * TC) * (int)sizeof(T) + 16 * cp;
         }
-#pragma unroll
-        for (int u = 0; u < NU; ++u) Us[tid + SG_NT * u] = ut[u];
     }
-
-    // a thread's share of a tile: NL pieces (VEC: of four columns) in rows (piece / pieces per row)
-    constexpr int W = VEC ? 4 : 1, PPR = TC / W, NL = ROWS * PPR / SG_NT;
-    static_assert(ROWS * PPR % SG_NT == 0, "whole pieces per thread");
-    typename Vec4<T>::type pv[VEC ? NL : 1];
-    T ps[VEC ? 1 : NL];
-    auto origin = [&](long long tile, long long* base, int* vc) {
-        const long long o = tile / jb.tiles_per_o, j0 = (tile - o * jb.tiles_per_o) * (TC * S);
-        *vc = (int)(inner - j0 < TC * S ? inner - j0 : TC * S);
-        *base = o * n * inner + j0;
-    };
-    // LDS row -> (column range, mode index); the rounded float quotient is exact for these small integers
-    auto split_row = [&](int row, int* sidx, int* i) {
-        if (NBM == 1) { *sidx = (int)(((float)row + 0.5f) * inv_n); *i = row - *sidx * n; }
-        else { *sidx = row < n ? 0 : 1; *i = row; }
-    };
-    // Loads go to clamped addresses (always inside X) rather than behind branches, so that all of a
-    // tile's loads are in flight together, and are issued while the previous tile is multiplied.
-    auto issue = [&](long long tile) {
-        long long base;
-        int vc;
-        origin(tile, &base, &vc);
+    auto copy = [&](int tile, int b) __attribute__((always_inline)) {
+        int o = 0, vc = 0;
+        long long j0 = 0;
+        if (tile < jb.ntiles) origin(tile, &o, &j0, &vc);  // (past the last tile: nothing is valid, zeros)
+        const T* base = X + (long long)o * n * inner + j0;
+        const int extent = (int)((n * inner - j0) * (long long)sizeof(T));
 #pragma unroll
-        for (int u = 0; u < NL; ++u) {
-            const int e = u * SG_NT + tid, row = e / PPR, c = (e - row * PPR) * W;
-            int sidx, i;
-            split_row(row, &sidx, &i);
-            const bool ok = sidx < S && sidx * TC + c < vc;
-            const long long idx = ok ? base + (long long)i * inner + sidx * TC + c : 0;
-            if constexpr (VEC) pv[u] = *reinterpret_cast<const typename Vec4<T>::type*>(X + idx);
-            else ps[u] = X[idx];
+        for (int u = 0; u < NL; ++u)
+            copy16_to_lds(base, extent, gcol[u] < vc * (int)sizeof(T) ? goff[u] : FAR, sg_raw + b * BUF + (u * SG_NT + 64 * wave) * 16);
+    };
+    // ---- element-wise form: a tile waits in registers while the one before it is multiplied
+    constexpr int NE = BUF / (int)sizeof(T) / SG_NT;
+    T pre[DMA ? 1 : NE];
+    auto fetch = [&](int tile) __attribute__((always_inline)) {
+        int o, vc;
+        long long j0;
+        origin(tile, &o, &j0, &vc);
+        const T* base = X + (long long)o * n * inner + j0;
+#pragma unroll
+        for (int u = 0; u < NE; ++u) {
+            const int e = u * SG_NT + tid, row = e / TC, c = e % TC;
+            const int sidx = S > 1 ? row / n : 0, i = row - sidx * n;
+            const bool ok = row < rows && sidx * TC + c < vc;
+            pre[DMA ? 0 : u] = base[ok ? i * inner + sidx * TC + c : 0];
         }
     };
-    auto commit = [&](long long tile) -> int {
-        long long base;
-        int vc;
-        origin(tile, &base, &vc);
+    auto store = [&](int tile, int b) __attribute__((always_inline)) {
+        int o, vc;
+        long long j0;
+        origin(tile, &o, &j0, &vc);
 #pragma unroll
-        for (int u = 0; u < NL; ++u) {
-            const int e = u * SG_NT + tid, row = e / PPR, c = (e - row * PPR) * W;
-            int sidx, i;
-            split_row(row, &sidx, &i);
-            if (sidx < S) {
-                const bool in = sidx * TC + c < vc;
-                if constexpr (VEC) {
-                    const v4f z = {0.f, 0.f, 0.f, 0.f};
-                    *reinterpret_cast<v4f*>(&Xs[row * PITCH + c]) = in ? widen4(pv[u]) : z;
-                } else {
-                    Xs[row * PITCH + c] = in ? to_f32(ps[u]) : 0.f;
-                }
-            }
+        for (int u = 0; u < NE; ++u) {
+            const int e = u * SG_NT + tid, row = e / TC, c = e % TC, cb = c * (int)sizeof(T);
+            const int sidx = S > 1 ? row / n : 0;
+            const bool ok = row < rows && sidx * TC + c < vc;
+            T z;
+            memset(&z, 0, sizeof(z));
+            *reinterpret_cast<T*>(sg_raw + b * BUF + row * RB + (((cb >> 4) ^ (row & 15)) << 4) + (cb & 15)) = ok ? pre[DMA ? 0 : u] : z;
         }
-        return vc;
     };
 
-    v4d acc[NPAIR];
+    v4d acc[NP];
 #pragma unroll
-    for (int p = 0; p < NPAIR; ++p) acc[p] = (v4d){0.0, 0.0, 0.0, 0.0};
-    if (lb < jb.ntiles) issue(lb);
-    for (long long tile = lb; tile < jb.ntiles; tile += jb.nwg) {
-        __syncthreads();                                   // the previous tile is no longer read
-        const int vc = commit(tile);
-        __syncthreads();
-        if (tile + jb.nwg < jb.ntiles) issue(tile + jb.nwg);
-        const int nch = ((vc < TC ? vc : TC) + 15) >> 4;   // columns past vc are zero in LDS
-        for (int ch = wave; ch < nch; ch += 4) {
-            double d[NBM][4];
+    for (int p = 0; p < NP; ++p) acc[p] = (v4d){0.0, 0.0, 0.0, 0.0};
+    if constexpr (DMA) {
 #pragma unroll
-            for (int mb = 0; mb < NBM; ++mb) {
-                const v4f x = *reinterpret_cast<const v4f*>(&Xs[(16 * mb + ll) * PITCH + 16 * ch + 4 * lg]);
+        for (int b = 0; b < NBUF - 1; ++b) copy(lb + b * jb.nwg, b);
+    } else {
+        if (lb < jb.ntiles) fetch(lb);
+    }
+    int b = 0;
+    for (int tile = lb; tile < jb.ntiles; tile += jb.nwg) {
+        if constexpr (DMA) {
+            // this wave's copies of `tile` have landed (those of the NBUF - 2 tiles after it may be on their way), then
+            // everybody's have; nobody reads the buffer of the tile before any more, which takes the next copy
+            wait_copies_and_sync<NL * (NBUF - 2)>();
+            copy(tile + (NBUF - 1) * jb.nwg, b == 0 ? NBUF - 1 : b - 1);
+        } else {
+            store(tile, b);
+            __syncthreads();
+            if (tile + jb.nwg < jb.ntiles) fetch(tile + jb.nwg);
+        }
+        const unsigned char* xs = sg_raw + b * BUF + ll * RB;
+        for (int ch = wave; ch < TC / 16; ch += SG_NW) {
+            double d[NB][4];
+            const int off = sizeof(T) == 4 ? ((4 * ch + lg) ^ ll) * 16 : ((2 * ch + (lg >> 1)) ^ ll) * 16 + (lg & 1) * 8;
+#pragma unroll
+            for (int mb = 0; mb < NB; ++mb) {
+                float x[4];
+                read4(reinterpret_cast<const T*>(xs + 16 * mb * RB + off), true, x);
 #pragma unroll
                 for (int s = 0; s < 4; ++s) d[mb][s] = (double)x[s];
             }
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                int p = 0;
-#pragma unroll
-                for (int mb = 0; mb < NBM; ++mb)
-#pragma unroll
-                    for (int nb = mb; nb < NBM; ++nb, ++p)
-                        acc[p] = __builtin_amdgcn_mfma_f64_16x16x4f64(d[mb][s], d[nb][s], acc[p], 0, 0, 0);
-            }
+            for (int s = 0; s < 4; ++s) gram_step<NB>(d, s, acc);
         }
+        b = b + 1 == NBUF ? 0 : b + 1;
     }
-    // G = sum of the four waves' accumulators, wave after wave (fixed order); blocks on or above the diagonal
-    double* G = reinterpret_cast<double*>(Xs);             // [ROWS][ROWS]
-    for (int w = 0; w < 4; ++w) {
-        __syncthreads();
-        if (wave == w) {
-            int p = 0;
-#pragma unroll
-            for (int mb = 0; mb < NBM; ++mb)
-#pragma unroll
-                for (int nb = mb; nb < NBM; ++nb, ++p)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        double* g = G + (16 * mb + lg + 4 * v) * ROWS + 16 * nb + ll;      // fp64 MFMA result layout
-                        *g = (w == 0) ? acc[p][v] : *g + acc[p][v];
-                    }
-        }
+    // G = sum over the eight waves (a tree, fixed order) in LDS, left in the first wave's place; then P = G U_prev
+    float u[NB][4];
+    gram_load_u<NB>(jb.U, n, r, wave, lane, u);            // on its way during the sums
+    double* red = reinterpret_cast<double*>(sg_raw);       // [4][NP][256]
+    double* mine = red + (wave & 3) * NP * 256;
+    wait_copies_and_sync<0>();                             // the tiles are no longer read, the copies past the last one have landed
+    __syncthreads();
+    if (wave >= 4) gram_put<NB>(acc, mine, lane);
+    __syncthreads();
+    if (wave < 4) gram_add<NB>(acc, mine, lane);
+    if (wave == 2 || wave == 3) gram_put<NB>(acc, mine, lane);
+    __syncthreads();
+    if (wave < 2) gram_add<NB>(acc, mine + 2 * NP * 256, lane);
+    if (wave == 1) gram_put<NB>(acc, mine, lane);
+    __syncthreads();
+    if (wave == 0) {
+        gram_add<NB>(acc, mine + NP * 256, lane);
+        gram_put<NB>(acc, mine, lane);
     }
     __syncthreads();
-    // P = G U_prev for this workgroup's columns; a block below the diagonal is its mirror image's transpose
-    double* out = jb.part + (long long)lb * n * r;
-    for (int e = tid; e < n * r; e += SG_NT) {
-        const int i = e / r, q = e - i * r;
-        double sum = 0.0;
-        for (int k = 0; k < n; ++k) {
-            double g;
-            if (NBM == 1) {
-                g = G[i * ROWS + k];
-                for (int sidx = 1; sidx < S; ++sidx) g += G[(sidx * n + i) * ROWS + sidx * n + k];
-            } else {
-                g = ((i >> 4) <= (k >> 4)) ? G[i * ROWS + k] : G[k * ROWS + i];
+    if (NB == 1 && S > 1) {                                // the ranges' Gram matrices lie along the diagonal of the block
+        double g = 0.0;
+        const int i = tid >> 4, k = tid & 15;
+        if (i < n && k < n)
+            for (int s = 0; s < S; ++s) {
+                const int ii = s * n + i;
+                g += red[(ii >> 2) * 64 + (ii & 3) * 16 + s * n + k];
             }
-            sum = fma(g, (double)Us[k * r + q], sum);
-        }
-        out[e] = sum;
+        __syncthreads();
+        if (i < n && k < n) red[(i >> 2) * 64 + (i & 3) * 16 + k] = g;
+        __syncthreads();
     }
+    gram_times_u<NB, SG_NW>(red, jb.U, n, r, jb.part + (long long)lb * n * r, wave, lane, u);
 }
 
 // ---- host side ---------------------------------------------------------------------
 bool subspace_gram_supported(long long outer, int n, long long inner, int r) {
     if (n < 1 || n > 64 || r < 1 || r > 64 || outer < 1) return false;
-    // The Gram matrix costs n (n + 16) / 2 multiply-adds per column in fp64 against 2 n r for the two
-    // products (one of them fp32): with four row blocks and a rank of at most 16 the products are cheaper.
+    // With four row blocks and one block of ranks the two products of Alg. 1 cost 6 MFMA units per four columns against 10
+    // here, and the sums over the waves (80 KB of LDS) are long for the few tiles a workgroup then walks: three 64 x 512 x 7 x 7
+    // layers in one launch 29 us here against 22 us on the kernel for short fibres (asi_subspace.hip), one alone the same.
     if (n > 48 && r <= 16) return false;
     return inner >= 128;                  // a long inner extent: tiles of consecutive columns
 }
-static int gram_nbm(int n) { return (n + 15) / 16; }
+static int gram_nb(int n) { return (n + 15) / 16; }
 static int gram_stack(int n) { return n <= 4 ? 4 : (n <= 8 ? 2 : 1); }
 // columns per tile
-static int gram_tc(int n) { const int b = gram_nbm(n); return b == 1 ? 512 * gram_stack(n) : (b == 2 ? 256 : 128); }
-int subspace_gram_nwg(long long outer, int n, long long inner) {
-    const long long tiles = outer * ((inner + gram_tc(n) - 1) / gram_tc(n));
-    return (int)(tiles < SG_MAX_WG ? tiles : SG_MAX_WG);
+static int gram_tc(DType xt, int n) { return (n <= 16 ? 1024 * gram_stack(n) : 512) / (xt == F32 ? 4 : 2); }
+int subspace_gram_nwg(DType xt, long long outer, int n, long long inner) {
+    const long long tc = gram_tc(xt, n), tiles = outer * ((inner + tc - 1) / tc);
+    const long long per = (tiles + SG_MAX_WG - 1) / SG_MAX_WG;       // every workgroup walks the same number of tiles
+    return (int)((tiles + per - 1) / per);
 }
 
-// key: [0] bf16, [1] vector loads, [4..6] NBM
+// key: [0] bf16, [1] memory-to-LDS copies, [4..6] NB
 bool make_subspace_gram(DType xt, const void* X, long long outer, int n, long long inner, const float* U, int r, double* part,
                         int nwg, int32_t* zero, int nzero, Item* out) {
     if (!subspace_gram_supported(outer, n, inner, r) || !X || !U || !part || nzero < 0 || nzero > 256) return false;
-    if (nwg != subspace_gram_nwg(outer, n, inner)) return false;
+    if (nwg != subspace_gram_nwg(xt, outer, n, inner)) return false;
     GramJob jb;
     std::memset(&jb, 0, sizeof(jb));
     jb.X = X; jb.U = U; jb.part = part; jb.outer = outer; jb.inner = inner; jb.n = n; jb.r = r; jb.nwg = nwg;
-    jb.tiles_per_o = (inner + gram_tc(n) - 1) / gram_tc(n);
-    jb.ntiles = outer * jb.tiles_per_o;
+    const long long tiles_per_o = (inner + gram_tc(xt, n) - 1) / gram_tc(xt, n), ntiles = outer * tiles_per_o;
+    if (ntiles + 8LL * SG_MAX_WG > 0x7fffffffLL) return false;
+    jb.tiles_per_o = (int)tiles_per_o; jb.ntiles = (int)ntiles;
     jb.S = gram_stack(n);
     jb.zero = zero; jb.nzero = zero ? nzero : 0;
-    const size_t esz = xt == F32 ? 4 : 2;
-    const bool vec = inner % 4 == 0 && reinterpret_cast<uintptr_t>(X) % (4 * esz) == 0;
-    const int nbm = gram_nbm(n);
+    const long long esz = xt == F32 ? 4 : 2;
+    const bool dma = inner * esz % 16 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0 && n * inner * esz < 0x7fff0000LL;
+    const int nb = gram_nb(n);
     *out = Item();
     out->kind = IT_GRAM_MODE;
-    out->key = (xt == BF16 ? 1u : 0u) | (vec ? 2u : 0u) | ((unsigned)nbm << 4);
+    out->key = (xt == BF16 ? 1u : 0u) | (dma ? 2u : 0u) | ((unsigned)nb << 4);
     out->nblocks = nwg;
-    std::snprintf(out->label, sizeof(out->label), "k_subspace_gram<%s, %d, %s>", xt == F32 ? "float" : "asi::bf16_t", nbm,
-                  vec ? "true" : "false");
+    std::snprintf(out->label, sizeof(out->label), "k_subspace_gram<%s, %d, %s>", xt == F32 ? "float" : "asi::bf16_t", nb,
+                  dma ? "true" : "false");
     static_assert(sizeof(GramJob) <= kItemArgMax, "argument block");
     std::memcpy(out->arg, &jb, sizeof(jb));
     return true;
 }
 
-template <typename T, bool VEC>
-static void launch_gram_nbm(int nbm, dim3 grid, hipStream_t st, const Batch<GramJob>& b) {
-    switch (nbm) {
-        case 1: hipLaunchKernelGGL((k_subspace_gram<T, 1, VEC>), grid, SG_NT, 0, st, b); break;
-        case 2: hipLaunchKernelGGL((k_subspace_gram<T, 2, VEC>), grid, SG_NT, 0, st, b); break;
-        case 3: hipLaunchKernelGGL((k_subspace_gram<T, 3, VEC>), grid, SG_NT, 0, st, b); break;
-        default: hipLaunchKernelGGL((k_subspace_gram<T, 4, VEC>), grid, SG_NT, 0, st, b); break;
+template <typename T, int NB, bool DMA>
+static hipError_t launch_gram_t(dim3 grid, hipStream_t st, const Batch<GramJob>& b) {
+    constexpr int ring = sg_nbuf<NB>() * sg_buf_bytes<NB>(), sums = 4 * gram_blocks<NB>() * 256 * 8, lds = ring > sums ? ring : sums;
+    static std::atomic<bool> allowed{false};
+    if (!allowed.load()) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_subspace_gram<T, NB, DMA>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e != hipSuccess) return e;
+        allowed.store(true);
     }
+    hipLaunchKernelGGL((k_subspace_gram<T, NB, DMA>), grid, SG_NT, lds, st, b);
+    return hipGetLastError();
+}
+template <typename T, bool DMA>
+static hipError_t launch_gram_nb(int nb, dim3 grid, hipStream_t st, const Batch<GramJob>& b) {
+    switch (nb) {
+        case 1: return launch_gram_t<T, 1, DMA>(grid, st, b);
+        case 2: return launch_gram_t<T, 2, DMA>(grid, st, b);
+        case 3: return launch_gram_t<T, 3, DMA>(grid, st, b);
+        case 4: return launch_gram_t<T, 4, DMA>(grid, st, b);
+    }
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_gram_items(const Item* const* items, int n, hipStream_t st) {
@@ -269,16 +279,9 @@ hipError_t launch_gram_items(const Item* const* items, int n, hipStream_t st) {
     dim3 grid;
     if (!gather(items, n, &b, &grid)) return hipErrorInvalidValue;
     const unsigned key = items[0]->key;
-    const int nbm = (int)((key >> 4) & 7u);
-    if (nbm < 1 || nbm > 4) return hipErrorInvalidValue;
-    if (key & 1u) {
-        if (key & 2u) launch_gram_nbm<bf16_t, true>(nbm, grid, st, b);
-        else          launch_gram_nbm<bf16_t, false>(nbm, grid, st, b);
-    } else {
-        if (key & 2u) launch_gram_nbm<float, true>(nbm, grid, st, b);
-        else          launch_gram_nbm<float, false>(nbm, grid, st, b);
-    }
-    return hipGetLastError();
+    const int nb = (int)((key >> 4) & 7u);
+    if (key & 1u) return (key & 2u) ? launch_gram_nb<bf16_t, true>(nb, grid, st, b) : launch_gram_nb<bf16_t, false>(nb, grid, st, b);
+    return (key & 2u) ? launch_gram_nb<float, true>(nb, grid, st, b) : launch_gram_nb<float, false>(nb, grid, st, b);
 }
 
 }  // namespace asi

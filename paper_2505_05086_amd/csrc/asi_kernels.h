@@ -217,7 +217,7 @@ bool make_sum_partials_f64(const double* part, int nsplit, long long count, floa
 // ---- short mode with a long inner extent through its Gram matrix (asi_gram.hip): part is (nwg, n, r) fp64 ----
 // P = (A_m A_m^T) U_prev: one pass accumulates the n x n Gram matrix in fp64, V is never formed
 bool subspace_gram_supported(long long outer, int n, long long inner, int r);
-int subspace_gram_nwg(long long outer, int n, long long inner);
+int subspace_gram_nwg(DType xt, long long outer, int n, long long inner);
 bool make_subspace_gram(DType xt, const void* X, long long outer, int n, long long inner, const float* U, int r, double* part,
                         int nwg, int32_t* zero, int nzero, Item* out);
 hipError_t launch_gram_items(const Item* const* items, int n, hipStream_t st);
@@ -227,22 +227,16 @@ bool subspace_small_supported(int n, int r);
 int subspace_small_nwg(long long outer, int n, long long inner);
 bool make_subspace_small(DType xt, const void* X, long long outer, int n, long long inner, const float* U, int r,
                          double* part, int nwg, int32_t* zero, int nzero, Item* out);
-// The last two modes of X seen as (planes, rows, cols), both from one read of X.
-bool subspace_pair_supported(int rows, int cols, int r_rows, int r_cols);
-int subspace_pair_nwg(long long planes, int rows, int cols);
-bool make_subspace_pair(DType xt, const void* X, long long planes, int rows, int cols, const float* U_rows, int r_rows,
-                        double* part_rows, const float* U_cols, int r_cols, double* part_cols, int nwg, Item* out);
-
 // ---- fused V/P step for modes with 64 < n <= 512 and r <= 64 (asi_long.hip): part is (nsplit, n, r) fp64 -------
 bool subspace_long_supported(long long outer, int n, long long inner, int r);
 int subspace_long_splits(long long outer, int n, long long inner, int r);
 bool make_subspace_long(DType xt, const void* X, long long outer, int n, long long inner, const float* U, int r,
                         double* part, int nsplit, int32_t* zero, int nzero, Item* out);
 
-// The last two modes of large planes (33..64 rows and columns, ranks up to 32, at least 1024 planes; asi_planes.hip):
+// The last two modes of X seen as (planes, rows, cols), planes of up to 64 x 64, both from one read of X (asi_planes.hip):
 // part_rows is (nwg, rows, r_rows), part_cols (nwg, cols, r_cols).
 bool subspace_planes_supported(long long planes, int rows, int cols, int r_rows, int r_cols);
-int subspace_planes_nwg(long long planes);
+int subspace_planes_nwg(DType xt, long long planes, int rows, int cols);
 bool make_subspace_planes(DType xt, const void* X, long long planes, int rows, int cols, const float* U_rows, int r_rows,
                           double* part_rows, const float* U_cols, int r_cols, double* part_cols, int nwg, int32_t* zero,
                           int nzero, Item* out);

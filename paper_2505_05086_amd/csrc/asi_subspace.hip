@@ -1,5 +1,5 @@
-// Fused subspace-iteration step for modes with a short fibre (n <= 64): B, H, W of a
-// conv activation, the batch mode of a token tensor.
+// Fused subspace-iteration step for modes with a short fibre (n <= 64) over few columns: what the Gram-matrix
+// kernels (asi_gram.hip, asi_planes.hip) leave.
 //
 // For such a mode the two products of Alg. 1, V = A_m^T U_prev and P = A_m V, are done
 // on the same LDS tile of complete mode-m fibres, so V never exists in memory and the
@@ -12,8 +12,7 @@
 // P is summed in fp64: the columns of U_prev need not be aligned with singular vectors, so
 // P holds components (sigma_r/sigma_1)^2 below its largest ones that fp32 sums would lose.
 //
-// A tile is either a run of complete outer slices (contiguous memory; the H and W modes,
-// which then share one tile as two "views" of the same planes) or, for a long inner
+// A tile is either a run of complete outer slices (contiguous memory) or, for a long inner
 // extent, n rows of 128 consecutive elements.  All loads of a tile are issued before the
 // first is stored (one memory latency per tile); two or more workgroups per CU overlap one
 // tile's loads with another's MFMAs.
@@ -29,7 +28,7 @@ namespace asi {
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef double v4d __attribute__((ext_vector_type(4)));
 
-constexpr int SS_TC = 128;                 // fibres (unfolding columns) per tile and view
+constexpr int SS_TC = 128;                 // fibres (unfolding columns) per tile
 constexpr int SS_PAD = 4;
 constexpr int SS_LDS_FLOATS = 64 * (SS_TC + SS_PAD);   // 33 KB
 constexpr int SS_PRE = (SS_LDS_FLOATS + 255) / 256;    // prefetch registers per thread
@@ -52,20 +51,19 @@ struct SmallJob {
     int whole_o, To;     // To: outer slices per tile (whole_o), else column groups per tile
     long long tiles_per_o;
     long long ntiles;
-    int nviews;
     int nwg;             // workgroups of this job; each walks tiles nwg apart
     int32_t* zero;       // nullable: `nzero` int32 to clear (arrival counters of the orth launches that follow)
     int nzero;
-    SmallView v[2];
+    SmallView v;
 };
 
 
-template <typename T, int NBM, int NBR, int NV, bool WHOLE_O, bool STACK = false>   // STACK: several column groups per tile
+template <typename T, int NBM, int NBR, bool WHOLE_O, bool STACK = false>   // STACK: several column groups per tile
 __global__ __launch_bounds__(256, 2) void k_subspace_small(Batch<SmallJob> bt) {
     int lb;
     const SmallJob& jb = bt.job[locate(bt, &lb)];
     __shared__ float smem[SS_LDS_FLOATS];
-    __shared__ float Us[NV][NBM * 16][NBR * 16];
+    __shared__ float Us[NBM * 16][NBR * 16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int lg = lane >> 4, ll = lane & 15;
     const T* __restrict__ X = static_cast<const T*>(jb.X);
@@ -76,34 +74,29 @@ __global__ __launch_bounds__(256, 2) void k_subspace_small(Batch<SmallJob> bt) {
     {
         constexpr int PV = NBM * 16 * NBR * 16, NU = PV / 256;
         static_assert(NU * 256 == PV, "whole passes");
-        float ut[NV][NU];
-        bool uok[NV][NU];
-#pragma unroll
-        for (int vi = 0; vi < NV; ++vi) {
-            const float* Uv = jb.v[vi].U;
-            const int nv = jb.v[vi].n, rv = jb.v[vi].r;
+        float ut[NU];
+        bool uok[NU];
+        {
+            const float* Uv = jb.v.U;
+            const int nv = jb.v.n, rv = jb.v.r;
 #pragma unroll
             for (int u = 0; u < NU; ++u) {
                 const int rem = tid + 256 * u, i = rem / (NBR * 16), q = rem - i * (NBR * 16);
-                uok[vi][u] = i < nv && q < rv;
-                ut[vi][u] = Uv[uok[vi][u] ? (long long)i * rv + q : 0LL];
+                uok[u] = i < nv && q < rv;
+                ut[u] = Uv[uok[u] ? (long long)i * rv + q : 0LL];
             }
         }
 #pragma unroll
-        for (int vi = 0; vi < NV; ++vi)
-#pragma unroll
-            for (int u = 0; u < NU; ++u) (&Us[vi][0][0])[tid + 256 * u] = uok[vi][u] ? ut[vi][u] : 0.f;
+            for (int u = 0; u < NU; ++u) (&Us[0][0])[tid + 256 * u] = uok[u] ? ut[u] : 0.f;
     }
 
-    v4d pacc[NV][NBM][NBR];
-#pragma unroll
-    for (int vi = 0; vi < NV; ++vi)
+    v4d pacc[NBM][NBR];
 #pragma unroll
         for (int mb = 0; mb < NBM; ++mb)
 #pragma unroll
-            for (int nb = 0; nb < NBR; ++nb) pacc[vi][mb][nb] = (v4d){0.0, 0.0, 0.0, 0.0};
+            for (int nb = 0; nb < NBR; ++nb) pacc[mb][nb] = (v4d){0.0, 0.0, 0.0, 0.0};
 
-    const int n0 = jb.v[0].n;
+    const int n0 = jb.v.n;
     const int rowI = SS_TC + SS_PAD;
     // Tiles of a long inner extent (!WHOLE_O): a short mode leaves most of the 64 LDS rows empty, so a tile
     // takes To groups of 128 columns and stacks them: LDS row g * n + i holds mode index i of columns
@@ -182,9 +175,8 @@ __global__ __launch_bounds__(256, 2) void k_subspace_small(Batch<SmallJob> bt) {
         if constexpr (!WHOLE_O) {
             if (tile + jb.nwg < jb.ntiles) issue(tile + jb.nwg);
         }
-#pragma unroll
-        for (int vi = 0; vi < NV; ++vi) {
-            const SmallView& sv = jb.v[vi];
+        {
+            const SmallView& sv = jb.v;
             const int n = sv.n, sI = sv.sI;
             const int valid_cols = WHOLE_O ? no_or_vc * sv.cols_per_o : no_or_vc;
             // The loop body is free of branches and every group of LDS reads is issued before the
@@ -194,7 +186,7 @@ __global__ __launch_bounds__(256, 2) void k_subspace_small(Batch<SmallJob> bt) {
 #pragma unroll
             for (int ks = 0; ks < NBM * 4; ++ks)
 #pragma unroll
-                for (int nb = 0; nb < NBR; ++nb) ub[ks][nb] = Us[vi][4 * ks + lg][16 * nb + ll];
+                for (int nb = 0; nb < NBR; ++nb) ub[ks][nb] = Us[4 * ks + lg][16 * nb + ll];
             for (int cb = wave; cb * 16 < valid_cols; cb += 4) {
                 // step A: V for 16 fibres
                 const int cA = cb * 16 + ll;
@@ -239,15 +231,14 @@ __global__ __launch_bounds__(256, 2) void k_subspace_small(Batch<SmallJob> bt) {
                     for (int mb = 0; mb < NBM; ++mb)
 #pragma unroll
                         for (int nb = 0; nb < NBR; ++nb)
-                            pacc[vi][mb][nb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a2[v][mb], (double)vacc[nb][v],
-                                                                                    pacc[vi][mb][nb], 0, 0, 0);
+                            pacc[mb][nb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a2[v][mb], (double)vacc[nb][v],
+                                                                                    pacc[mb][nb], 0, 0, 0);
             }
         }
     }
     // sum the four waves' accumulators through LDS, wave after wave (fixed order)
     double* red = reinterpret_cast<double*>(smem);   // (NBM*16) x (NBR*16) doubles <= 32 KB
-#pragma unroll
-    for (int vi = 0; vi < NV; ++vi) {
+        {
         __syncthreads();
         for (int w = 0; w < 4; ++w) {
             if (wave == w) {
@@ -259,13 +250,13 @@ __global__ __launch_bounds__(256, 2) void k_subspace_small(Batch<SmallJob> bt) {
                         for (int v = 0; v < 4; ++v) {
                             const int i = 16 * mb + lg + 4 * v, q = 16 * nb + ll;   // fp64 MFMA result layout
                             double* p = red + i * (NBR * 16) + q;
-                            *p = (w == 0) ? pacc[vi][mb][nb][v] : *p + pacc[vi][mb][nb][v];
+                            *p = (w == 0) ? pacc[mb][nb][v] : *p + pacc[mb][nb][v];
                         }
             }
             __syncthreads();
         }
-        const int n = jb.v[vi].n, r = jb.v[vi].r;
-        double* out = jb.v[vi].part + (long long)lb * n * r;
+        const int n = jb.v.n, r = jb.v.r;
+        double* out = jb.v.part + (long long)lb * n * r;
         for (int e = tid; e < n * r; e += 256) {
             const int i = e / r, q = e - i * r;
             out[e] = red[i * (NBR * 16) + q];
@@ -313,38 +304,17 @@ int subspace_small_nwg(long long outer, int n, long long inner) {
     return (int)(jb.ntiles < cap ? jb.ntiles : cap);
 }
 
-// The last two modes of a tensor (planes, rows, cols) can share tiles of whole planes.
-bool subspace_pair_supported(int rows, int cols, int r_rows, int r_cols) {
-    if (!subspace_small_supported(rows, r_rows) || !subspace_small_supported(cols, r_cols)) return false;
-    if ((rows + 15) / 16 != (cols + 15) / 16) return false;           // one register shape for both views
-    const int nbr = std::max((r_rows + 15) / 16, (r_cols + 15) / 16);
-    if (nbr > 2) return false;
-    return (long long)rows * cols <= SS_LDS_FLOATS;
-}
-static int pair_To(long long planes, int rows, int cols) { return (int)whole_To(planes, (long long)rows * cols); }
-int subspace_pair_nwg(long long planes, int rows, int cols) {
-    const int To = pair_To(planes, rows, cols);
-    const long long ntiles = (planes + To - 1) / To;
-    return (int)(ntiles < SS_MAX_WG ? ntiles : SS_MAX_WG);
-}
-
-// key: [0] bf16, [1] two views, [2] whole_o, [3] stacked column groups (n <= 32), [4..6] NBM, [8..10] NBR
-static bool small_key_ok(int nbm, int nbr, int nv) {
-    if (nbm < 1 || nbm > 4 || nbr < 1 || nbr > nbm) return false;
-    return nv == 1 || nbr <= 2;
-}
 static bool finish_small(DType xt, SmallJob& jb, int nbm, int nbr, int nwg, Item* out) {
-    if (!small_key_ok(nbm, nbr, jb.nviews) || nwg <= 0 || nwg > jb.ntiles) return false;
-    if (jb.nviews == 2 && !jb.whole_o) return false;
+    if (nbm < 1 || nbm > 4 || nbr < 1 || nbr > nbm || nwg <= 0 || nwg > jb.ntiles) return false;
     jb.nwg = nwg;
     *out = Item();
     out->kind = IT_SMALL;
     const bool stack = !jb.whole_o && jb.To > 1;
-    out->key = (xt == BF16 ? 1u : 0u) | (jb.nviews == 2 ? 2u : 0u) | (jb.whole_o ? 4u : 0u) | (stack ? 8u : 0u) |
+    out->key = (xt == BF16 ? 1u : 0u) | (jb.whole_o ? 4u : 0u) | (stack ? 8u : 0u) |
                ((unsigned)nbm << 4) | ((unsigned)nbr << 8);
     out->nblocks = nwg;
-    std::snprintf(out->label, sizeof(out->label), "k_subspace_small<%s, %d, %d, %d, %s, %s>", xt == F32 ? "float" : "asi::bf16_t",
-                  nbm, nbr, jb.nviews, jb.whole_o ? "true" : "false", stack ? "true" : "false");
+    std::snprintf(out->label, sizeof(out->label), "k_subspace_small<%s, %d, %d, %s, %s>", xt == F32 ? "float" : "asi::bf16_t",
+                  nbm, nbr, jb.whole_o ? "true" : "false", stack ? "true" : "false");
     static_assert(sizeof(SmallJob) <= kItemArgMax, "argument block");
     std::memcpy(out->arg, &jb, sizeof(jb));
     return true;
@@ -357,8 +327,7 @@ bool make_subspace_small(DType xt, const void* X, long long outer, int n, long l
     std::memset(&jb, 0, sizeof(jb));
     jb.X = X; jb.zero = zero; jb.nzero = zero ? nzero : 0;
     single_geometry(outer, n, inner, &jb);
-    jb.nviews = 1;
-    SmallView& v = jb.v[0];
+    SmallView& v = jb.v;
     v.U = U; v.part = part; v.n = n; v.r = r;
     if (jb.whole_o) {
         v.sI = (int)inner; v.div = (int)inner; v.mulA = n * (int)inner; v.mulB = 1; v.cols_per_o = (int)inner;
@@ -366,30 +335,7 @@ bool make_subspace_small(DType xt, const void* X, long long outer, int n, long l
         v.sI = SS_TC + SS_PAD; v.div = SS_TC; v.mulA = n * (SS_TC + SS_PAD); v.mulB = 1; v.cols_per_o = 0;   // group g starts n rows further down
     }
     v.inv_div = 1.0f / (float)v.div;
-    jb.v[1] = jb.v[0];
     return finish_small(xt, jb, (n + 15) / 16, (r + 15) / 16, nwg, out);
-}
-
-// Modes "rows" and "cols" of X seen as (planes, rows, cols), both from one read of X.
-bool make_subspace_pair(DType xt, const void* X, long long planes, int rows, int cols, const float* U_rows, int r_rows,
-                        double* part_rows, const float* U_cols, int r_cols, double* part_cols, int nwg, Item* out) {
-    if (!subspace_pair_supported(rows, cols, r_rows, r_cols) || !X || !U_rows || !U_cols || !part_rows || !part_cols)
-        return false;
-    SmallJob jb;
-    std::memset(&jb, 0, sizeof(jb));
-    jb.X = X; jb.outer = planes; jb.inner = cols; jb.o_elems = (long long)rows * cols;
-    jb.whole_o = 1; jb.To = pair_To(planes, rows, cols); jb.tiles_per_o = 0;
-    jb.ntiles = (planes + jb.To - 1) / jb.To;
-    jb.nviews = 2;
-    SmallView& a = jb.v[0];      // fibres run along rows: element (i, c = (plane, col)) at plane*rows*cols + i*cols + col
-    a.U = U_rows; a.part = part_rows; a.n = rows; a.r = r_rows;
-    a.sI = cols; a.div = cols; a.mulA = rows * cols; a.mulB = 1; a.cols_per_o = cols;
-    a.inv_div = 1.0f / (float)cols;
-    SmallView& b = jb.v[1];      // fibres run along cols: element (i, c = (plane, row)) at plane*rows*cols + row*cols + i
-    b.U = U_cols; b.part = part_cols; b.n = cols; b.r = r_cols;
-    b.sI = 1; b.div = rows; b.mulA = rows * cols; b.mulB = cols; b.cols_per_o = rows;
-    b.inv_div = 1.0f / (float)rows;
-    return finish_small(xt, jb, (rows + 15) / 16, std::max((r_rows + 15) / 16, (r_cols + 15) / 16), nwg, out);
 }
 
 // ---- the last two modes when both are tiny (rows, cols <= 8, ranks <= 8) ------------------------------
@@ -625,31 +571,24 @@ hipError_t launch_tiny_items(const Item* const* items, int n, hipStream_t st) {
     return hipErrorInvalidValue;
 }
 
-template <typename T, int NV>
+template <typename T>
 static bool launch_small_t(const Batch<SmallJob>& b, dim3 grid, int nbm, int nbr, bool whole_o, bool stack, hipStream_t st) {
-    if constexpr (NV == 1) {
-        if (stack) {
-            if (whole_o || nbm > 2) return false;
-            if (nbm == 1 && nbr == 1) hipLaunchKernelGGL((k_subspace_small<T, 1, 1, 1, false, true>), grid, 256, 0, st, b);
-            else if (nbm == 2 && nbr == 1) hipLaunchKernelGGL((k_subspace_small<T, 2, 1, 1, false, true>), grid, 256, 0, st, b);
-            else if (nbm == 2 && nbr == 2) hipLaunchKernelGGL((k_subspace_small<T, 2, 2, 1, false, true>), grid, 256, 0, st, b);
-            else return false;
-            return true;
-        }
-    } else if (stack) {
-        return false;
+    if (stack) {
+        if (whole_o || nbm > 2) return false;
+        if (nbm == 1 && nbr == 1) hipLaunchKernelGGL((k_subspace_small<T, 1, 1, false, true>), grid, 256, 0, st, b);
+        else if (nbm == 2 && nbr == 1) hipLaunchKernelGGL((k_subspace_small<T, 2, 1, false, true>), grid, 256, 0, st, b);
+        else if (nbm == 2 && nbr == 2) hipLaunchKernelGGL((k_subspace_small<T, 2, 2, false, true>), grid, 256, 0, st, b);
+        else return false;
+        return true;
     }
 #define ASI_SS_CASE(M, R)                                                                                \
     if (nbm == M && nbr == R) {                                                                          \
-        if (whole_o) hipLaunchKernelGGL((k_subspace_small<T, M, R, NV, true>), grid, 256, 0, st, b);     \
-        else if constexpr (NV == 1) hipLaunchKernelGGL((k_subspace_small<T, M, R, NV, false>), grid, 256, 0, st, b); \
+        if (whole_o) hipLaunchKernelGGL((k_subspace_small<T, M, R, true>), grid, 256, 0, st, b);         \
+        else hipLaunchKernelGGL((k_subspace_small<T, M, R, false>), grid, 256, 0, st, b);                \
         return true;                                                                                     \
     }
     ASI_SS_CASE(1, 1) ASI_SS_CASE(2, 1) ASI_SS_CASE(2, 2) ASI_SS_CASE(3, 1) ASI_SS_CASE(3, 2)
-    ASI_SS_CASE(4, 1) ASI_SS_CASE(4, 2)
-    if constexpr (NV == 1) {
-        ASI_SS_CASE(3, 3) ASI_SS_CASE(4, 3) ASI_SS_CASE(4, 4)
-    }
+    ASI_SS_CASE(3, 3) ASI_SS_CASE(4, 1) ASI_SS_CASE(4, 2) ASI_SS_CASE(4, 3) ASI_SS_CASE(4, 4)
 #undef ASI_SS_CASE
     return false;
 }
@@ -659,11 +598,9 @@ hipError_t launch_small_items(const Item* const* items, int n, hipStream_t st) {
     dim3 grid;
     if (!gather(items, n, &b, &grid)) return hipErrorInvalidValue;
     const unsigned key = items[0]->key;
-    const bool bf16 = key & 1u, two = key & 2u, whole_o = key & 4u, stack = key & 8u;
+    const bool bf16 = key & 1u, whole_o = key & 4u, stack = key & 8u;
     const int nbm = (int)((key >> 4) & 7u), nbr = (int)((key >> 8) & 7u);
-    bool ok;
-    if (!bf16) ok = two ? launch_small_t<float, 2>(b, grid, nbm, nbr, whole_o, stack, st) : launch_small_t<float, 1>(b, grid, nbm, nbr, whole_o, stack, st);
-    else ok = two ? launch_small_t<bf16_t, 2>(b, grid, nbm, nbr, whole_o, stack, st) : launch_small_t<bf16_t, 1>(b, grid, nbm, nbr, whole_o, stack, st);
+    const bool ok = bf16 ? launch_small_t<bf16_t>(b, grid, nbm, nbr, whole_o, stack, st) : launch_small_t<float>(b, grid, nbm, nbr, whole_o, stack, st);
     return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
 

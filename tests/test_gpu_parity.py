@@ -568,3 +568,44 @@ def test_ill_conditioned_wide_rank_many_slices(ratio):
     by a tree level before the factorisation; both passes and the shifted retry read the summed ones."""
     lay = Layer("illcond", (8, 20, 2100), (6, 16, 90), "f32", "linear", 12)
     _check_orthonormal_basis(lay, _graded_tensor(lay, ratio), 10, f"wide, many slices, ratio {ratio}")
+
+
+# (planes, rows, cols) one above and below every block of 16, blocks that differ between the two modes, more planes than a
+# round of workgroups takes, fewer than a tile; batch modes of one to four row blocks over ragged column ranges.
+GRAM_CASES = [
+    ((3, 5, 9, 16), (2, 3, 5, 9)), ((2, 3, 17, 9), (2, 3, 11, 4)), ((1, 3, 16, 33), (1, 2, 3, 16)),
+    ((5, 7, 32, 31), (3, 4, 20, 17)), ((2, 9, 48, 49), (2, 3, 33, 12)), ((3, 3, 64, 64), (2, 2, 40, 64)), ((2, 2, 63, 10), (2, 2, 9, 7)),
+    ((36, 150, 15, 11), (8, 9, 6, 5)), ((50, 90, 20, 13), (18, 9, 6, 5)), ((64, 12, 31, 20), (33, 5, 9, 6)), ((20, 260, 9, 10), (7, 8, 5, 5)),
+    ((7, 40, 34, 20), (5, 6, 8, 8)), ((3, 60, 24, 24), (3, 6, 8, 8)),
+]
+
+
+@pytest.mark.parametrize("dims,ranks", GRAM_CASES)
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_subspace_steps_through_the_gram_matrix(dims, ranks, dtype, shift):
+    """Short modes and planes of up to 64 x 64, from an activation aligned to 16 bytes (copied straight to LDS) and from one
+    aligned to its element only (loaded through registers), against the oracle."""
+    from paper_2505_05086_amd import binding as B
+    lay = Layer("gram", dims, ranks, dtype, "conv2d", 3, k=1, alpha=0.7, noise=1e-2)
+    st = LayerStream(9, 11, lay)
+    run = _runner(lay)
+    A_np, U0 = st.activation(0), st.u_prev0()
+    U_or = O.compress(A_np.astype(F64), [u.astype(F64) for u in U0])
+    A = run.upload(A_np)
+    buf = torch.empty(A.numel() + 8, dtype=A.dtype, device=A.device)
+    A_t = buf[shift:shift + A.numel()].view(A.shape)
+    A_t.copy_(A)
+    run.set_factors(U0)
+    B.asi_profile_enable(True)
+    try:
+        U = [_np(u) for u in run.compress(A_t)]
+        torch.cuda.synchronize()
+        sites = list(B.asi_profile_report())
+    finally:
+        B.asi_profile_enable(False)
+    assert int(run.info.item()) == 0
+    assert any("k_subspace_planes" in s_ for s_ in sites), sites
+    for m, (ug, uo) in enumerate(zip(U, U_or)):
+        assert np.max(np.abs(ug.T @ ug - np.eye(ug.shape[1]))) < 1e-5, m
+        assert O.max_rel_err(O.projector(ug), O.projector(uo)) <= TOL[dtype], (m, sites)
