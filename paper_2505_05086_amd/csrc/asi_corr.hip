@@ -75,9 +75,12 @@ static bool corr_plan(const CorrGeom& g, CorrPlan* p) {
         zmax = big ? CR_ZMAX_BIG : CR_ZMAX_SMALL;
         p->ry = p->kc / g.Wo;
         if (p->ry > g.Ho) p->ry = g.Ho;
+        p->wp = (g.Wo - 1) * g.sw + (g.kw - 1) * g.dw + 1;
+        // fewer rows per chunk where a stride or a dilation makes the slab of Z that goes with them too large for LDS (a 45 x 37
+        // map at stride 2, 101 channels, fell to the one-thread-per-output kernel: 117 us, 16 with chunks of two rows)
+        while (!big && p->ry > 1 && (long long)((p->ry - 1) * g.sh + (g.kh - 1) * g.dh + 1) * p->wp * 16 > zmax) --p->ry;
         p->nyc = (g.Ho + p->ry - 1) / p->ry;
         p->rows_in = (p->ry - 1) * g.sh + (g.kh - 1) * g.dh + 1;
-        p->wp = (g.Wo - 1) * g.sw + (g.kw - 1) * g.dw + 1;
         p->slab = p->rows_in * p->wp;
         if ((long long)p->slab * 16 <= zmax && (!big || ((p->rows_in == 4 || p->rows_in == 6) && p->wp <= 128 && g.Wo % 4 == 0 && g.sw == 1))) break;
         if (!big) return false;
@@ -92,10 +95,10 @@ static bool corr_plan(const CorrGeom& g, CorrPlan* p) {
     p->nchunks = g.r1 * p->nyc;
     const long long base = (long long)((g.cout + CR_TO - 1) / CR_TO) * ((g.r2 + 15) / 16);
     long long target = 256;
-    long long want = (target + base - 1) / base;
-    // With the large chunks a CU holds one workgroup (LDS), so a workgroup beyond the 256th waits for a whole
-    // round: round the split count down, not up.
-    if (p->kc == CR_KC_BIG) want = target / base;
+    // A CU holds one workgroup (registers; the large chunks: LDS, too), so a workgroup beyond the 256th waits for a whole
+    // round: the split count is rounded down (960 x 40 x 9 over 24 x 7 x 7: 270 workgroups 46 us, 225 with a fifth chunk each
+    // 29; two workgroups per CU, forced to 128 registers, 34).
+    long long want = target / base;
     if (want > p->nchunks) want = p->nchunks;
     if (want < 1) want = 1;
     p->cps = (int)((p->nchunks + want - 1) / want);
