@@ -611,9 +611,9 @@ def test_subspace_steps_through_the_gram_matrix(dims, ranks, dtype, shift):
         assert O.max_rel_err(O.projector(ug), O.projector(uo)) <= TOL[dtype], (m, sites)
 
 
-@pytest.mark.parametrize("dims,ranks,cout,stride,dil", [((3, 20, 45, 37), (3, 18, 6, 5), 70, 2, 1), ((2, 9, 41, 43), (2, 7, 6, 5), 9, 1, 3)])
+@pytest.mark.parametrize("dims,ranks,cout,stride,dil", [((3, 20, 45, 37), (3, 18, 6, 5), 70, 2, 1), ((2, 9, 41, 20), (2, 7, 6, 5), 9, 1, 4)])
 def test_correlation_takes_fewer_rows_per_chunk_where_the_slab_is_large(dims, ranks, cout, stride, dil):
-    """Stride 2 and dilation 3: the rows of Z that a full chunk of 64 output positions touches do not fit in LDS, two or one
+    """Stride 2 and dilation 4: the rows of Z that a full chunk of 64 output positions touches do not fit in LDS, two or three
     output rows do; the MFMA kernel runs, in chunks of fewer rows."""
     from paper_2505_05086_amd import binding as B
     lay = Layer("edge", dims, ranks, "f32", "conv2d", cout, k=3, stride=stride, pad=1, dil=dil, alpha=0.7, noise=1e-2)
