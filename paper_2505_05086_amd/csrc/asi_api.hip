@@ -83,9 +83,10 @@ struct CompressPlan {
     double* Gsum[4] = {};           // wide path, many slices: the slice Grams added up by a tree level
     int ngsum[4] = {};
     double* R[4] = {};
+    double* Rinv[4] = {};
     double* Dinv[4] = {};
     double* scal[4] = {};
-    int32_t* ctr8 = nullptr;         // arrival counters, two per mode
+    int32_t* ctr8 = nullptr;         // arrival counters, kOrthCtrs per mode
     int nsplit[4] = {};
     int nblk[4] = {};
     bool fused[4] = {};
@@ -126,7 +127,7 @@ CompressPlan plan_compress(const Shape& s, void* ws, bool cold = false) {
         if (p.bfks[m] > 1) vpmax = std::max(vpmax, (size_t)p.bfks[m] * (size_t)(s.numel / s.n[m]) * s.r[m]);
     }
     p.Vpart = c.take<float>(vpmax);
-    p.ctr8 = c.take<int32_t>(8);
+    p.ctr8 = c.take<int32_t>(4 * kOrthCtrs);
     p.tiny = !cold && s.d == 4 && subspace_tiny_supported((int)s.n[2], (int)s.n[3], s.r[2], s.r[3]);
     p.planes = !cold && s.d == 4 && !p.tiny && subspace_planes_supported(s.n[0] * s.n[1], (int)s.n[2], (int)s.n[3], s.r[2], s.r[3]);
     p.paired = p.tiny || p.planes;
@@ -147,8 +148,9 @@ CompressPlan plan_compress(const Shape& s, void* ws, bool cold = false) {
         p.fast_orth[m] = orth_fast_supported((int)r);
         if (p.fast_orth[m]) {
             p.nblk[m] = orth_slices((int)n);
-            p.Gpart[m] = c.take<double>((size_t)p.nblk[m] * r * r);
+            p.Gpart[m] = c.take<double>((size_t)(orth_gram_slices((int)n) + orth_groups((int)n)) * r * (r + 1) / 2);
             p.R[m] = c.take<double>(r * r);
+            p.Rinv[m] = c.take<double>(orth_rinv_elems((int)r));
             p.Dinv[m] = c.take<double>(((r + 15) / 16) * 256);
             p.scal[m] = c.take<double>(68);
         } else if (orth_wide_supported((int)r)) {
@@ -522,7 +524,7 @@ asi_status build_compress(const asi_tensor_desc* desc, const void* A, const floa
             zero_given = true;
             const double cols = (double)outer * (double)inner;
             ASI_ADD(pg, "", cols * n * esize(s.dt) + 4.0 * n * r + 8.0 * n * r * p.nsplit[m], 4.0 * cols * n * r,
-                    make_subspace_long(s.dt, A, outer, n, inner, U_prev[m], r, p.part[m], p.nsplit[m], zero, 8, it__));
+                    make_subspace_long(s.dt, A, outer, n, inner, U_prev[m], r, p.part[m], p.nsplit[m], zero, 4 * kOrthCtrs, it__));
         } else if (p.gramm[m]) {
             // short mode, long inner extent: the Gram matrix of the unfolding in one pass, then G U_prev
             int32_t* zero = zero_given ? nullptr : p.ctr8;
@@ -530,14 +532,14 @@ asi_status build_compress(const asi_tensor_desc* desc, const void* A, const floa
             const double cols = (double)outer * (double)inner;
             // flops by the step's definition (two products of 2 cols n r), not the Gram matrix's own count
             ASI_ADD(pg, "", cols * n * esize(s.dt) + 4.0 * n * r + 8.0 * n * r * p.nsplit[m], 4.0 * cols * n * r,
-                    make_subspace_gram(s.dt, A, outer, n, inner, U_prev[m], r, p.part[m], p.nsplit[m], zero, 8, it__));
+                    make_subspace_gram(s.dt, A, outer, n, inner, U_prev[m], r, p.part[m], p.nsplit[m], zero, 4 * kOrthCtrs, it__));
         } else if (p.fused[m]) {
             // short fibres: V and P from one LDS tile of complete fibres, V never stored
             int32_t* zero = zero_given ? nullptr : p.ctr8;       // one early kernel clears the arrival counters
             zero_given = true;
             const double cols = (double)outer * (double)inner;
             ASI_ADD(pg, "", cols * n * esize(s.dt) + 4.0 * n * r + 8.0 * n * r * p.nsplit[m], 4.0 * cols * n * r,
-                    make_subspace_small(s.dt, A, outer, n, inner, U_prev[m], r, p.part[m], p.nsplit[m], zero, 8, it__));
+                    make_subspace_small(s.dt, A, outer, n, inner, U_prev[m], r, p.part[m], p.nsplit[m], zero, 4 * kOrthCtrs, it__));
         } else {
             int32_t* zero = zero_given ? nullptr : p.ctr8;
             zero_given = true;
@@ -569,10 +571,10 @@ asi_status build_compress(const asi_tensor_desc* desc, const void* A, const floa
                     preneed[m2] = false;
                 }
             if (cold)
-                ASI_TRYS(add_pair_gauss(pg, "P", s.dt, A, outer, n, inner, *seed, m, r, p.part[m], p.nsplit[m], zero, 8,
+                ASI_TRYS(add_pair_gauss(pg, "P", s.dt, A, outer, n, inner, *seed, m, r, p.part[m], p.nsplit[m], zero, 4 * kOrthCtrs,
                                         ride.njobs ? &ride : nullptr, ride_b));
             else
-                ASI_TRYS(add_pair(pg, "P", s.dt, A, outer, n, inner, p.V, r, p.part[m], p.nsplit[m], zero, 8,
+                ASI_TRYS(add_pair(pg, "P", s.dt, A, outer, n, inner, p.V, r, p.part[m], p.nsplit[m], zero, 4 * kOrthCtrs,
                                   ride.njobs ? &ride : nullptr, ride_b));
         }
     }
@@ -588,8 +590,9 @@ asi_status build_compress(const asi_tensor_desc* desc, const void* A, const floa
         j.part = p.part[m]; j.nsplit = p.nsplit[m]; j.n = n; j.r = r;
         if (p.part2[m]) { j.part = p.part2[m]; j.nsplit = p.nsplit2[m]; }     // the tree's first level has run
         j.P64 = p.P64[m]; j.Uout = U_out[m]; j.mode1 = m + 1; j.info = info;
-        j.nblk = p.nblk[m]; j.Gpart = p.Gpart[m]; j.R = p.R[m]; j.Dinv = p.Dinv[m]; j.scal = p.scal[m];
-        j.ctr = p.ctr8 + 2 * m;
+        j.nblk = p.nblk[m]; j.Gpart = p.Gpart[m]; j.R = p.R[m]; j.Rinv = p.Rinv[m]; j.Dinv = p.Dinv[m]; j.scal = p.scal[m];
+        j.ctr = p.ctr8 + kOrthCtrs * m;
+        if (p.fast_orth[m]) j.gsz = orth_group_size(n);
         if (p.wide_orth[m] && p.Gsum[m]) {
             GsumJob& gj = gsum.job[gsum.njobs++];
             gj.in = p.Gpart[m]; gj.out = p.Gsum[m]; gj.nblk = p.nblk[m]; gj.r = r;

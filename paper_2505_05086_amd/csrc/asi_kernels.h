@@ -248,22 +248,25 @@ bool make_subspace_tiny(DType xt, const void* X, long long planes, int rows, int
                         double* part_rows, const float* U_cols, int r_cols, double* part_cols, int nwg, Item* out);
 
 // ---- Orthogonalize (asi_orth.hip) ---------------------------------------------------------------------------
+constexpr int kOrthGroups = 32;          // groups of slices of a mode, at most
+constexpr int kOrthCtrs = 2 + kOrthGroups;
 struct OrthJob {
     const double* part;  // (nsplit, n, r) partial sums of P
     double* P64;         // (n, r) scratch
     float* Uout;         // (n, r)
     int32_t* info;       // nullable
     // fast path (r <= 64) and wide path
-    double* Gpart;       // (nblk, r (r+1) / 2) packed slice Gram matrices; slow path: (r, r) Gram matrix
+    double* Gpart;       // fast path: (orth_gram_slices(n) + groups of them, r (r+1) / 2) packed Gram matrices; slow path: (r, r)
     double* R;           // (r, r)
+    double* Rinv;        // fast path: blocks of R^-1 on and above the diagonal, orth_rinv_elems(r) elements
     double* Dinv;        // (ceil(r/16), 16, 16) inverses of R's diagonal blocks
     double* scal;        // 68 doubles of bookkeeping (wide path: 2 + 192)
-    int32_t* ctr;        // 2 arrival counters, zero before the first orth launch of a call
+    int32_t* ctr;        // 2 + kOrthGroups arrival counters, zero before the first orth launch of a call
     int nsplit;
     int n, r;
     int mode1;           // 1-based mode number for *info
     int nblk;            // row slices = orth_slices(n) (wide path: orth_wide_gram_blocks(n))
-    int pad_;
+    int gsz;             // fast path: slices of gram0 per group
     unsigned long long* devbits;   // wide path with a summed Gram matrix (make_orthw_gsum): bits of max |G - I|; else null
 };
 struct OrthArgs {        // the modes of one tensor that share a path
@@ -286,11 +289,14 @@ struct GsumArgs {
 };
 bool make_orthw_gsum(const GsumArgs& a, Item* out);
 bool orth_fast_supported(int r);
+inline size_t orth_rinv_elems(int r) { const size_t nb = (size_t)(r + 15) / 16; return nb * (nb + 1) / 2 * 256; }
 int orth_slices(int n);
-// gram0: sums the partial sums of P, slice Grams; the last workgroup of a mode factors (shifted pass)
-//        and clears *info.
-// apply(0): Q0 = P R0^-1, slice Grams of Q0; the last workgroup of a mode factors again.
-// apply(1): U = Q0 R1^-1 in fp32.
+int orth_gram_slices(int n);
+int orth_group_size(int n);
+inline int orth_groups(int n) { return (orth_gram_slices(n) + orth_group_size(n) - 1) / orth_group_size(n); }
+// gram0: sums the partial sums of P, slice Grams; the last workgroup of a mode factors (shifted if need be), inverts the
+//        factor, certifies the first pass where it can, and clears *info.
+// apply: U = P R^-1; where the first pass is not certified, slice Grams of the result and, if they say so, a second pass.
 bool make_orth_gram0(const OrthArgs& a, Item* out);
 bool make_orth_apply(const OrthArgs& a, Item* out);
 // wide path, 64 < r <= 192: nblk = orth_wide_gram_blocks(n), scal holds 2 + 192 doubles,

@@ -13,11 +13,18 @@
 // Fast path (r <= 64), two launches that serve all modes of a tensor at once:
 //   gram0 : row slices of 32 rows sum the split partial sums of P -> P64 and write their slice Gram
 //           (fp64 MFMA); the workgroup that arrives last at the mode's counter sums the slice Grams and
-//           factors: blocked Cholesky in LDS without a shift, with the shift only if a pivot is lost;
-//           it also inverts the 16x16 diagonal blocks of R
-//   apply : row slices: Q0 = P R^-1 by block forward substitution (fp64 MFMA), written in fp64 and as
+//           factors: blocked Cholesky in LDS without a shift, with the shift only if a pivot is lost.
+//           It then inverts R and bounds what one pass leaves of |Q^T Q - I|: with X = R^-1 and
+//           c = max_j sum_i sqrt(G_ii) |X_ij|  (the column-scaled condition number), rounding of G, of the factor and of
+//           the products gives  |Q^T Q - I| <= u ((18 + slices of a group + groups + 2 r) c^2 + 4 r c).  Below OP_DONE_TOL - the steady
+//           state of a warm-started basis, c is 10..300 there and 2000 would do - the first pass is certified.
+//   apply : certified: Q = P X, a wave per 16 x 16 block of Q, all its operands in one round of loads; nothing else.
+//           Otherwise: Q0 = P R^-1 by block forward substitution (fp64 MFMA), written in fp64 and as
 //           the fp32 result, plus the slice Gram of Q0; the last-arriving workgroup measures
 //           |Q0^T Q0 - I| and only if that exceeds OP_DONE_TOL runs the second pass by itself
+// The two launches are a chain of dependent round trips to memory and of pivots; 512 threads keep up to 48 loads each in
+// flight.  960 x 40 (30 slices) and three short modes: gram0 30.9 -> 27.2, apply 21.0 -> 4.7 us; measuring the result instead of
+// certifying it (slice Grams, hand-over, sum, comparison) was half of apply.
 // Wide path (64 < r <= 192): separate Gram / Cholesky / apply launches on the packed triangle.
 // Slow path (r > 192): one workgroup per mode, everything in global memory.
 #include "asi_device.h"
@@ -32,10 +39,12 @@ namespace asi {
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 
-constexpr int OP_RS = 32;              // rows per slice
+constexpr int OP_RS = 32;              // rows per slice of apply
+constexpr int OP_GS = 16;              // rows per slice of gram0
 constexpr int OP_RMAX = 64;
 constexpr int OP_LD = OP_RMAX + 1;
 constexpr double OP_EPS = 1.1102230246251565e-16;
+constexpr int OP_NT = 512, OP_NW = OP_NT / 64;
 constexpr double OP_DONE_TOL = 1e-7;   // |Q0^T Q0 - I| below which the first pass is the result
 
 
@@ -46,8 +55,9 @@ __device__ __forceinline__ void flag_info(int32_t* info, int mode1, int col1) {
 // the modes of all layers of one launch
 constexpr int kMaxOrthJobs = 4 * kMaxBatch;
 struct OrthBatch {
-    OrthJob job[kMaxOrthJobs];
     int njobs;
+    int first[kMaxOrthJobs + 1];       // workgroups before job j (filled for the launches that walk slices)
+    OrthJob job[kMaxOrthJobs];
 };
 struct PresumBatch {
     PresumJob job[kMaxOrthJobs];
@@ -56,16 +66,28 @@ struct PresumBatch {
 static_assert(sizeof(OrthBatch) <= 4096, "kernel argument limit");
 
 __device__ __forceinline__ void find_job(const OrthBatch& a, int* ji, int* blk) {
-    int j = 0, b = blockIdx.x;
-    while (j + 1 < a.njobs && b >= a.job[j].nblk) { b -= a.job[j].nblk; ++j; }
-    *ji = j; *blk = b;
+    int j = 0;
+    const int b = blockIdx.x;
+    while (j + 1 < a.njobs && b >= a.first[j + 1]) ++j;
+    *ji = j; *blk = b - a.first[j];
 }
 
 // Packed upper triangle: element (ga <= gb) of an r x r symmetric matrix
 __device__ __forceinline__ int tri_idx(int r, int ga, int gb) { return ga * r - (ga * (ga - 1)) / 2 + (gb - ga); }
 
-// Gram of the 32 rows held in Ps (zero padded to 64 columns) -> packed upper triangle Gout (r (r+1) / 2)
-__device__ void gram_from_lds(const double (*Ps)[OP_LD], int r, double* __restrict__ Gout) {
+// What one workgroup writes for another of the same launch: stores and loads that go past the XCD's L2 (agent scope), so that
+// the hand-over needs no write-back and no invalidation of whole caches.
+__device__ __forceinline__ void publish(double* p, double v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double published(const double* p, long long idx, bool ok) {
+    const double v = __hip_atomic_load(p + (ok ? idx : 0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return ok ? v : 0.0;
+}
+
+// Gram of the ROWS rows held in Ps (zero padded to 64 columns) -> packed upper triangle Gout (r (r+1) / 2)
+template <int ROWS>
+__device__ void gram_from_lds(const double (*Ps)[OP_LD], int r, double* Gout) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lg = lane >> 4, ll = lane & 15;
     const int nb = (r + 15) / 16, npairs = nb * (nb + 1) / 2;
     const int nwaves = blockDim.x >> 6;
@@ -75,13 +97,13 @@ __device__ void gram_from_lds(const double (*Ps)[OP_LD], int r, double* __restri
         const int bb = ab + rem;
         v4d acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int ks = 0; ks < OP_RS / 4; ++ks)
+        for (int ks = 0; ks < ROWS / 4; ++ks)
             acc = __builtin_amdgcn_mfma_f64_16x16x4f64(Ps[4 * ks + lg][16 * ab + ll], Ps[4 * ks + lg][16 * bb + ll], acc,
                                                        0, 0, 0);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int ga = 16 * ab + lg + 4 * v, gb = 16 * bb + ll;
-            if (ga < r && gb < r && ga <= gb) Gout[tri_idx(r, ga, gb)] = acc[v];
+            if (ga < r && gb < r && ga <= gb) publish(Gout + tri_idx(r, ga, gb), acc[v]);
         }
     }
 }
@@ -98,19 +120,6 @@ __device__ __forceinline__ double bcast_lane(double x, int src) {      // src un
     return __hiloint2double(hi, lo);
 }
 
-// Cholesky of the 16x16 diagonal block of Gs at `base` by ONE wave, four pivots per round.
-// Lane j < 16 keeps column j of the (symmetric) trailing block in registers, so row k of the
-// trailing block is lane k's column.  A round eliminates its four pivots inside the 4-row
-// panel, fetching the few values it needs from their lanes; every lane then publishes its four
-// finished row entries in `rowbuf` (LDS serves one wave's accesses in order, so no barrier is
-// needed) and applies the rank-4 update to its rows below the panel.  The rows of the next
-// panel are updated first, so that the next panel's chain of reciprocals is independent of the
-// rest of the update and the two are interleaved.  The code is branch free; a non-positive
-// pivot is replaced by 1 and reported through `bad` (1-based index, first one wins).
-// Rows are left unscaled: on return Gs[base+k][base+j], k <= j, holds R[k][j] * R[k][k], the
-// diagonal the pivots R[k][k]^2, and pinvs[base+k] their reciprocals.
-// Lanes 48..63 carry the columns of an identity block through the same row operations, which
-// leaves the inverse of the block's unit lower triangular factor in Xb[i][j] = (L^-1)[j][i].
 // e / r for 0 <= e < 2^16 and 1 <= r <= 64 without an integer division: the rounded float quotient
 // of (e + 0.5) is exact in that range (the same device as in the product kernels).
 __device__ __forceinline__ int small_div(int e, float inv_r) { return (int)(((float)e + 0.5f) * inv_r); }
@@ -135,226 +144,262 @@ struct GramPacked {                      // row-wise packed upper triangle of an
         if (row <= col && col < r) Gp[idx(row, col)] = v;
     }
 };
+// Cholesky on the fp64 MFMA by ONE wave, four pivots per round.  A 16 x 16 block sits in the MFMA's result layout: register v
+// of lane (lg, ll) is element (4 v + lg, ll), so panel p of four rows is register p of every lane, and as it is both the A
+// operand (element (k, i) of the panel, k = lg) and the B operand of a rank-4 update.  A round fetches the panel's 4x4
+// diagonal block D = L4 diag(q) L4^T with v_readlane and factors it redundantly in every lane; the panel's rows become
+// W = L4^-1 G_panel (one product per block), the rows below lose W^T diag(1/q) W (another).  An identity block that goes through
+// the same row operations becomes the inverse of the block's unit lower triangular factor.
+// Rows are left unscaled: row k holds R[k][j] * R[k][k], the diagonal the pivots R[k][k]^2.
+// A non-positive pivot is replaced (by a number in [1, 2)) and reported through `bad` (1-based index, first one wins).
+struct Panel4 {
+    double li;           // lane (lg, ll): element [ll][lg] of L4^-1 (zero for ll > 3)
+    double pl;           // 1 / q of row lg of the panel
+};
+// g: the panel's register of the diagonal block; p: the panel's number in the block; col1: 1-based index of its first pivot
+__device__ __forceinline__ Panel4 factor_panel(double g, int p, int col1, int lg, int ll, int* bad) {
+    double a[4][4], pi[4], m[4][4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int k2 = k; k2 < 4; ++k2) a[k][k2] = bcast_lane(g, 16 * k + 4 * p + k2);
+    // column lg of L4^-1 by forward substitution, beside the pivots
+    double x[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[k] = lg == k ? 1.0 : 0.0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        double q = a[k][k];
+        const bool okp = q > 0.0;                        // false for zero, negative, NaN
+        *bad = (!okp && *bad == 0) ? col1 + k : *bad;
+        q = __hiloint2double(okp ? __double2hiint(q) : 0x3ff00000, __double2loint(q));
+        double inv = __builtin_amdgcn_rcp(q);
+        const double e = fma(-q, inv, 1.0);              // r (1 + e + e^2): full accuracy from the estimate's 2^-20 and better
+        inv = fma(inv * e, 1.0 + e, inv);
+        pi[k] = inv;
+#pragma unroll
+        for (int k2 = k + 1; k2 < 4; ++k2) m[k][k2] = a[k][k2] * inv;                // L4[k2][k]
+#pragma unroll
+        for (int k2 = k + 1; k2 < 4; ++k2) {
+#pragma unroll
+            for (int k3 = k2; k3 < 4; ++k3) a[k2][k3] = fma(-m[k][k2], a[k][k3], a[k2][k3]);
+            x[k2] = fma(-m[k][k2], x[k], x[k2]);
+        }
+    }
+    // (pinned: left alone the compiler turns the selects into a ladder of branches around the arithmetic)
+    asm volatile("" : "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(pi[0]), "+v"(pi[1]), "+v"(pi[2]), "+v"(pi[3]));
+    Panel4 o;
+    o.li = ll == 0 ? x[0] : (ll == 1 ? x[1] : (ll == 2 ? x[2] : (ll == 3 ? x[3] : 0.0)));
+    o.pl = lg == 0 ? pi[0] : (lg == 1 ? pi[1] : (lg == 2 ? pi[2] : pi[3]));
+    return o;
+}
+__device__ __forceinline__ v4d mfma64(double a, double b, v4d c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+
+// One diagonal block of a matrix in LDS behind an accessor (wide ranks): U in place, pinvs[base+k] the pivots' reciprocals,
+// Xb[i][j] = (L^-1)[j][i].
 template <class GA>
-__device__ void chol_block16(const GA G, double (*rowbuf)[64][4], double (*Xb)[17], double* pinvs, int base,
-                             int* bad_io) {
-    const int j = threadIdx.x;          // 0..63
-    const bool xl = j >= 48;            // identity lane
-    double col[16];
-    {
-        // All 16 reads are issued before any is used.  Left to itself the compiler sinks each read
-        // into the branch that selects it (only lanes 0..15 keep the value) and waits for one LDS
-        // round trip per row; the empty asm pins the reads in front of the selects.
-        double g[16];
+__device__ void chol_block16(const GA G, double (*Xb)[17], double* pinvs, int base, int* bad_io) {
+    const int lane = threadIdx.x & 63, lg = lane >> 4, ll = lane & 15;
+    const v4d zero = {0.0, 0.0, 0.0, 0.0};
+    v4d g, x;
 #pragma unroll
-        for (int a2 = 0; a2 < 16; ++a2) g[a2] = G.ld(base + a2, base + (j & 15));
-#pragma unroll
-        for (int a2 = 0; a2 < 16; ++a2) asm volatile("" : "+v"(g[a2]));
-#pragma unroll
-        for (int a2 = 0; a2 < 16; ++a2) col[a2] = xl ? ((a2 == j - 48) ? 1.0 : 0.0) : (j < 16 ? g[a2] : 0.0);
+    for (int v = 0; v < 4; ++v) {
+        const int i = 4 * v + lg;
+        g[v] = G.ld(base + (i < ll ? i : ll), base + (i < ll ? ll : i));
+        x[v] = i == ll ? 1.0 : 0.0;
     }
     int bad = *bad_io;
-    double f[4];
-    // Panel K0..K0+3.  Its 4x4 diagonal block (10 values, fetched from their lanes in one go) is
-    // factored redundantly by every lane, which keeps the cross-lane traffic off the chain of
-    // reciprocals; each lane then applies the multipliers to its own four row entries.
-    // F[kk] = (row K0+kk of this lane's column) / pivot.
-#define ASI_CHOL_PANEL(K0, F)                                                                       \
-    {                                                                                               \
-        double a_[4][4], pi_[4], m_[4][4];                                                          \
-        _Pragma("unroll") for (int kk = 0; kk < 4; ++kk)                                            \
-            _Pragma("unroll") for (int k2 = kk; k2 < 4; ++k2) a_[kk][k2] = bcast_lane(col[(K0) + kk], (K0) + k2); \
-        _Pragma("unroll") for (int kk = 0; kk < 4; ++kk) {                                          \
-            double p = a_[kk][kk];                                                                  \
-            const bool okp = p > 0.0;                /* false for zero, negative, NaN */            \
-            bad = (!okp && bad == 0) ? base + (K0) + kk + 1 : bad;                                  \
-            p = okp ? p : 1.0;                                                                      \
-            double pinv = __builtin_amdgcn_rcp(p);                                                  \
-            pinv = fma(fma(-p, pinv, 1.0), pinv, pinv);   /* two Newton steps: full accuracy */     \
-            pinv = fma(fma(-p, pinv, 1.0), pinv, pinv);                                             \
-            pi_[kk] = pinv;                                                                         \
-            a_[kk][kk] = p;                          /* the pivot actually used */                  \
-            _Pragma("unroll") for (int k2 = kk + 1; k2 < 4; ++k2) m_[kk][k2] = a_[kk][k2] * pinv;   \
-            _Pragma("unroll") for (int k2 = kk + 1; k2 < 4; ++k2)                                   \
-                _Pragma("unroll") for (int k3 = k2; k3 < 4; ++k3) a_[k2][k3] = fma(-m_[kk][k2], a_[kk][k3], a_[k2][k3]); \
-        }                                                                                           \
-        _Pragma("unroll") for (int k2 = 1; k2 < 4; ++k2)                                            \
-            _Pragma("unroll") for (int kk = 0; kk < k2; ++kk)                                       \
-                col[(K0) + k2] = fma(-m_[kk][k2], col[(K0) + kk], col[(K0) + k2]);                  \
-        _Pragma("unroll") for (int kk = 0; kk < 4; ++kk) {                                          \
-            F[kk] = col[(K0) + kk] * pi_[kk];                                                       \
-            if (j == (K0) + kk) { col[(K0) + kk] = a_[kk][kk]; pinvs[base + (K0) + kk] = pi_[kk]; } \
-        }                                                                                           \
-    }
-#define ASI_CHOL_UPDATE(A_LO, A_HI, RB)                                                             \
-    {                                                                                               \
-        _Pragma("unroll") for (int a0 = (A_LO); a0 < (A_HI); a0 += 4) {                             \
-            double w[4][4];                                                                         \
-            _Pragma("unroll") for (int g = 0; g < 4; ++g)                                           \
-                _Pragma("unroll") for (int kk = 0; kk < 4; ++kk) w[g][kk] = RB[a0 + g][kk];         \
-            _Pragma("unroll") for (int kk = 0; kk < 4; ++kk)                                        \
-                _Pragma("unroll") for (int g = 0; g < 4; ++g)                                       \
-                    col[a0 + g] = fma(-w[g][kk], f[kk], col[a0 + g]);                               \
-        }                                                                                           \
-    }
-    ASI_CHOL_PANEL(0, f)
 #pragma unroll
-    for (int k0 = 0; k0 + 4 < 16; k0 += 4) {
-        double (*rb)[4] = rowbuf[(k0 >> 2) & 1];
-        rb[j][0] = col[k0]; rb[j][1] = col[k0 + 1]; rb[j][2] = col[k0 + 2]; rb[j][3] = col[k0 + 3];
-        ASI_CHOL_UPDATE(k0 + 4, k0 + 8, rb)
-        double fn[4];
-        ASI_CHOL_PANEL(k0 + 4, fn)
-        ASI_CHOL_UPDATE(k0 + 8, 16, rb)
+    for (int p = 0; p < 4; ++p) {
+        const Panel4 f = factor_panel(g[p], p, base + 4 * p + 1, lg, ll, &bad);
+        const double w = mfma64(f.li, g[p], zero)[0], wx = mfma64(f.li, x[p], zero)[0];
+        if (p < 3) {
+            const v4d gn = mfma64(-w, w * f.pl, g), xn = mfma64(-w, wx * f.pl, x);
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) f[kk] = fn[kk];
+            for (int v = p + 1; v < 4; ++v) { g[v] = gn[v]; x[v] = xn[v]; }
+        }
+        g[p] = w;
+        x[p] = wx;
+        if (ll == 0) pinvs[base + 4 * p + lg] = f.pl;
     }
-#undef ASI_CHOL_PANEL
-#undef ASI_CHOL_UPDATE
     *bad_io = bad;
-    // lanes 0..15 write their column of the block (entries below the diagonal are never read again),
-    // lanes 48..63 their row of the inverse factor: one run of stores for both
-    if (xl) {
 #pragma unroll
-        for (int k = 0; k < 16; ++k) Xb[j - 48][k] = col[k];
-    } else if (j < 16) {
-#pragma unroll
-        for (int k = 0; k < 16; ++k) G.st(base + k, base + j, col[k]);
+    for (int v = 0; v < 4; ++v) {
+        const int i = 4 * v + lg;
+        if (i <= ll) G.st(base + i, base + ll, g[v]);
+        Xb[ll][i] = x[v];
     }
 }
 
-// One workgroup (256 threads): sums the slice Grams of a mode, adds the shift (first pass) and
-// factors the matrix, identity padded to a multiple of 16, by blocked right-looking Cholesky:
-// wave 0 factors a diagonal block, then the four waves solve that block row and update the
-// trailing blocks with fp64 MFMA.  Writes R, the inverses of R's diagonal blocks and the
-// bookkeeping in scal; with `last` it reports a rank-deficient P through *info.  scal[0] = trace(P^T P), scal[1 + k] = running product of the
-// R diagonals, scal[65] = first bad pivot, scal[66] = 1 when the first pass needed no second.
+// A matrix of nb <= NB blocks a side (r <= 64), whole, in the registers of the wave: no LDS round trip and no barrier between
+// panels.  In: Gs (symmetric, identity beyond r); out: U in the upper blocks of Gs, Xs[b][i][j] = (L_bb^-1)[j][i].
+// Per panel the chain is fetch, four reciprocals, two products (~700 cycles); the products of the other blocks fill its gaps.
+// 48 columns: 9.5 us as blocks of 16 with the block row and the trailing blocks dealt to all waves behind barriers, 7.6 so.
+template <int NB>
+__device__ __forceinline__ void chol_wave(double (*Gs)[OP_LD], double (*Xs)[16][17], int nb, int* bad_io) {
+    const int lane = threadIdx.x & 63, lg = lane >> 4, ll = lane & 15;
+    const v4d zero = {0.0, 0.0, 0.0, 0.0};
+    v4d g[NB][NB];
+#pragma unroll
+    for (int I = 0; I < NB; ++I)
+#pragma unroll
+        for (int J = I; J < NB; ++J)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) g[I][J][v] = Gs[16 * I + 4 * v + lg][16 * J + ll];
+    int bad = 0;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        if (b < nb) {                                    // uniform
+            v4d x;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) x[v] = 4 * v + lg == ll ? 1.0 : 0.0;
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                const Panel4 f = factor_panel(g[b][b][p], p, 16 * b + 4 * p + 1, lg, ll, &bad);
+                double w[NB], mw[NB];
+                w[b] = mfma64(f.li, g[b][b][p], zero)[0];
+                mw[b] = w[b] * f.pl;
+                if (p < 3) {
+                    const v4d gn = mfma64(-w[b], mw[b], g[b][b]);
+#pragma unroll
+                    for (int v = p + 1; v < 4; ++v) g[b][b][v] = gn[v];
+                }
+                g[b][b][p] = w[b];
+                const double wx = mfma64(f.li, x[p], zero)[0];
+                if (p < 3) {
+                    const v4d xn = mfma64(-w[b], wx * f.pl, x);
+#pragma unroll
+                    for (int v = p + 1; v < 4; ++v) x[v] = xn[v];
+                }
+                x[p] = wx;
+#pragma unroll
+                for (int J = b + 1; J < NB; ++J) {
+                    w[J] = mfma64(f.li, g[b][J][p], zero)[0];
+                    mw[J] = w[J] * f.pl;
+                    if (p < 3) {
+                        const v4d gn = mfma64(-w[b], mw[J], g[b][J]);
+#pragma unroll
+                        for (int v = p + 1; v < 4; ++v) g[b][J][v] = gn[v];
+                    }
+                    g[b][J][p] = w[J];
+                }
+#pragma unroll
+                for (int I = b + 1; I < NB; ++I)
+#pragma unroll
+                    for (int J = I; J < NB; ++J) g[I][J] = mfma64(-w[I], mw[J], g[I][J]);
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                Xs[b][ll][4 * v + lg] = x[v];
+#pragma unroll
+                for (int J = b; J < NB; ++J)
+                    if (J > b || 4 * v + lg <= ll) Gs[16 * b + 4 * v + lg][16 * J + ll] = g[b][J][v];
+            }
+        }
+    }
+    *bad_io = bad;
+}
+
+// One workgroup: sums the slice Grams of a mode, adds the shift (first pass) and
+// factors the matrix, identity padded to a multiple of 16 (wave 0).  Writes R, the inverses of R's diagonal blocks and the
+// bookkeeping in scal; the first pass also inverts R and certifies itself where it can (see above); with `last` it reports a rank-deficient P through *info.  scal[0] = trace(P^T P), scal[1 + k] = running product of the
+// R diagonals, scal[65] = first bad pivot, scal[66] = 1 when the first pass needed no second (apply's
+// check), 2 when it is certified.
 struct CholSmem {
     double Gs[OP_RMAX][OP_LD];
     double dinv[OP_RMAX];
     double rdiag[OP_RMAX];
     double pinvs[OP_RMAX];
-    double rowbuf[2][64][4];
+    double gsq[OP_RMAX];
     double Xs[OP_RMAX / 16][16][17];
+    double colmax[OP_NW];
     double s_trace;
     int s_bad;
 };
 
+// Sum of `count` packed matrices of T elements, in their order: element tid + OP_NT it in sum[it].  A round keeps up to 48
+// loads per thread in flight (a round is one dependent trip to memory).
 template <int RM>
-__device__ bool chol_job(const OrthJob& jb, int pass, int last, int32_t* info, CholSmem& sm) {
+constexpr int packed_its() { return (RM * (RM + 1) / 2 + OP_NT - 1) / OP_NT; }
+template <int RM>
+__device__ __forceinline__ void sum_packed(const double* src, int count, int T, double (&sum)[packed_its<RM>()]) {
+    constexpr int ITS = packed_its<RM>(), SB = 48 / ITS > 24 ? 24 : 48 / ITS;
+    const int tid = threadIdx.x;
+#pragma unroll
+    for (int it = 0; it < ITS; ++it) sum[it] = 0.0;
+#pragma unroll 1
+    for (int b0 = 0; b0 < count; b0 += SB) {
+        double t[SB][ITS];
+#pragma unroll
+        for (int u = 0; u < SB; ++u) {
+            const double* m = src + (long long)(b0 + u < count ? b0 + u : count - 1) * T;       // uniform
+#pragma unroll
+            for (int it = 0; it < ITS; ++it)
+                t[u][it] = published(m, (unsigned)(tid + OP_NT * it < T ? tid + OP_NT * it : 0), true);
+        }
+#pragma unroll
+        for (int u = 0; u < SB; ++u)
+#pragma unroll
+            for (int it = 0; it < ITS; ++it) sum[it] += b0 + u < count ? t[u][it] : 0.0;
+    }
+}
+
+// slices, nslices: the packed matrices whose sum is factored (groups of slices in the first pass, slices in the second)
+template <int RM>
+__device__ bool chol_job(const OrthJob& jb, int pass, int last, const double* slices, int nslices, int32_t* info, CholSmem& sm) {
     double (*Gs)[OP_LD] = sm.Gs;
     double* dinv = sm.dinv;
     double* rdiag = sm.rdiag;
     double* pinvs = sm.pinvs;
-    double (*rowbuf)[64][4] = sm.rowbuf;
+    double* gsq = sm.gsq;
     double (*Xs)[16][17] = sm.Xs;
     double& s_trace = sm.s_trace;
     int& s_bad = sm.s_bad;
     const int n = jb.n, r = jb.r, tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6, lg = lane >> 4, ll = lane & 15;
     const int nb = (r + 15) / 16;
-    // sum of the slice Grams (packed upper triangles), slice after slice in their order: a round keeps up
-    // to 48 loads per thread in flight (a round is one dependent trip to memory, and a long mode has a
-    // hundred slices and more): IA elements per thread x SBX slices, IA = what the rank needs of the ITS
-    // elements the launch's largest rank would
-    constexpr int ITS = (RM * (RM + 1) / 2 + 255) / 256;
+    // sum of the slice Grams (packed upper triangles); IA elements per thread
+    constexpr int ITS = packed_its<RM>();
     const int T = (r * (r + 1)) / 2;
     double sum[ITS];
-#pragma unroll
-    for (int it = 0; it < ITS; ++it) sum[it] = 0.0;
-    auto sum_slices = [&](auto ia_c, auto sb_c) __attribute__((always_inline)) {
-        constexpr int IA = decltype(ia_c)::value, SBX = decltype(sb_c)::value;
-        for (int b0 = 0; b0 < jb.nblk; b0 += SBX) {
-            double t[SBX][IA];
-#pragma unroll
-            for (int u = 0; u < SBX; ++u)
-#pragma unroll
-                for (int it = 0; it < IA; ++it) {
-                    const int e = tid + 256 * it;
-                    t[u][it] = ldg_f64(jb.Gpart, (long long)(b0 + u) * T + e, e < T && b0 + u < jb.nblk);
-                }
-#pragma unroll
-            for (int u = 0; u < SBX; ++u)
-#pragma unroll
-                for (int it = 0; it < IA; ++it) sum[it] += t[u][it];
-        }
+    // where the thread's elements lie in the matrix (worked out while the loads are on their way): row ga of the packed
+    // triangle is the largest with tri_idx(r, ga, ga) <= e; the square root is off by one at most
+    int gpos[ITS];
+    auto decode = [&](int e) __attribute__((always_inline)) {
+        const float d = (float)(2 * r + 1);
+        int ga = (int)((d - sqrtf(d * d - 8.0f * (float)e)) * 0.5f);
+        ga = ga < 0 ? 0 : (ga > r - 1 ? r - 1 : ga);
+        ga += (ga + 1 < r && tri_idx(r, ga + 1, ga + 1) <= e) ? 1 : 0;
+        ga -= tri_idx(r, ga, ga) > e ? 1 : 0;
+        return ga * OP_LD + ga + (e - tri_idx(r, ga, ga));
     };
-    {
-        const int ia = (T + 255) / 256;
-        constexpr int SB = (96 / ITS) > 16 ? 16 : (96 / ITS);
-        if (ia == 1) sum_slices(std::integral_constant<int, 1>{}, std::integral_constant<int, 48>{});
-        else if (ITS >= 2 && ia == 2) sum_slices(std::integral_constant<int, (ITS >= 2 ? 2 : 1)>{}, std::integral_constant<int, 24>{});
-        else sum_slices(std::integral_constant<int, ITS>{}, std::integral_constant<int, SB>{});
-    }
+#pragma unroll
+    for (int it = 0; it < ITS; ++it) gpos[it] = tid + OP_NT * it < T ? decode(tid + OP_NT * it) : 0;
+    sum_packed<RM>(slices, nslices, T, sum);
     // Gs = the summed Gram matrix, padded with the identity up to a multiple of 16
     auto scatter = [&]() {
         __syncthreads();
-        for (int e = tid; e < OP_RMAX * 64; e += 256) Gs[e >> 6][e & 63] = ((e >> 6) == (e & 63)) ? 1.0 : 0.0;
+        for (int e = tid; e < OP_RMAX * 64; e += OP_NT) Gs[e >> 6][e & 63] = ((e >> 6) == (e & 63)) ? 1.0 : 0.0;
         __syncthreads();
 #pragma unroll
-        for (int it = 0; it < ITS; ++it) {
-            const int e = tid + 256 * it;
-            if (e < T) {
-                // row ga of the packed triangle: largest ga with tri_idx(r, ga, ga) <= e
-                int ga = (int)(((2 * r + 1) - sqrtf((float)((2 * r + 1) * (2 * r + 1) - 8 * e))) * 0.5f);
-                ga = ga < 0 ? 0 : (ga > r - 1 ? r - 1 : ga);
-                while (ga > 0 && tri_idx(r, ga, ga) > e) --ga;
-                while (ga + 1 < r && tri_idx(r, ga + 1, ga + 1) <= e) ++ga;
-                const int gb = ga + (e - tri_idx(r, ga, ga));
-                Gs[ga][gb] = sum[it];
-                Gs[gb][ga] = sum[it];
+        for (int it = 0; it < ITS; ++it)
+            if (tid + OP_NT * it < T) {
+                const int row = gpos[it] / OP_LD, col = gpos[it] - row * OP_LD;
+                Gs[row][col] = sum[it];
+                Gs[col][row] = sum[it];
             }
-        }
         __syncthreads();
     };
     scatter();
     int bad = 0;
-    // blocked right-looking factorisation of Gs in place
-    auto factor = [&]() {
-        for (int P = 0; P < nb; ++P) {
-            if (wave == 0) chol_block16(GramSquare{Gs}, rowbuf, Xs[P], pinvs, 16 * P, &bad);
-            __syncthreads();
-            if (P + 1 < nb) {
-                // block row P right of the diagonal:  U_PJ = L_PP^-1 G_PJ   (unscaled rows, like the diagonal block)
-                for (int J = P + 1 + wave; J < nb; J += 4) {
-                    double bv[4];
-    #pragma unroll
-                    for (int ks = 0; ks < 4; ++ks) bv[ks] = Gs[16 * P + 4 * ks + lg][16 * J + ll];
-                    v4d acc = {0.0, 0.0, 0.0, 0.0};
-    #pragma unroll
-                    for (int ks = 0; ks < 4; ++ks)      // A[i][k] = (L^-1)[i][k] = Xs[P][k][i]
-                        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(Xs[P][4 * ks + lg][ll], bv[ks], acc, 0, 0, 0);
-    #pragma unroll
-                    for (int v = 0; v < 4; ++v) Gs[16 * P + lg + 4 * v][16 * J + ll] = acc[v];
-                }
-                __syncthreads();
-                // trailing blocks:  G_IJ -= U_PI^T diag(1/pivot) U_PJ,  P < I <= J
-                int cnt = 0;
-                for (int I = P + 1; I < nb; ++I)
-                    for (int J = I; J < nb; ++J, ++cnt) {
-                        if ((cnt & 3) != wave) continue;
-                        v4d acc;
-    #pragma unroll
-                        for (int v = 0; v < 4; ++v) acc[v] = Gs[16 * I + lg + 4 * v][16 * J + ll];
-    #pragma unroll
-                        for (int ks = 0; ks < 4; ++ks) {
-                            const int k = 16 * P + 4 * ks + lg;
-                            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-Gs[k][16 * I + ll], Gs[k][16 * J + ll] * pinvs[k], acc, 0, 0, 0);
-                        }
-    #pragma unroll
-                        for (int v = 0; v < 4; ++v) Gs[16 * I + lg + 4 * v][16 * J + ll] = acc[v];
-                    }
-                __syncthreads();
-            }
-        }
-    };
+    bool shifted = false;
     if (pass == 1) {
         // Q0 may already be orthonormal to working accuracy (a warm-started, well-conditioned P): then
         // the second pass would only reproduce the identity, and the fp32 copy of Q0 that the solve
         // has written is the result.
         double dev = 0.0;
         const float inv_r1 = 1.0f / (float)r;
-        for (int e = tid; e < r * r; e += 256) {
+        for (int e = tid; e < r * r; e += OP_NT) {
             const int ga = small_div(e, inv_r1), gb = e - ga * r;
             dev = fmax(dev, fabs(Gs[ga][gb] - (ga == gb ? 1.0 : 0.0)));
         }
@@ -362,7 +407,9 @@ __device__ bool chol_job(const OrthJob& jb, int pass, int last, int32_t* info, C
         for (int m = 32; m >= 1; m >>= 1) dev = fmax(dev, __shfl_xor(dev, m));
         if (lane == 0) rdiag[wave] = dev;
         __syncthreads();
-        dev = fmax(fmax(rdiag[0], rdiag[1]), fmax(rdiag[2], rdiag[3]));
+        dev = 0.0;
+#pragma unroll
+        for (int w = 0; w < OP_NW; ++w) dev = fmax(dev, rdiag[w]);
         __syncthreads();
         const bool done = dev <= OP_DONE_TOL;
         if (tid == 0) jb.scal[66] = done ? 1.0 : 0.0;
@@ -380,68 +427,131 @@ __device__ bool chol_job(const OrthJob& jb, int pass, int last, int32_t* info, C
             return false;
         }
         if (tid == 0) s_trace = jb.scal[0];
-        factor();
-    } else {
-        // First pass.  Plain Cholesky first; if a pivot is lost (non-positive, or below 1e-12 of its
-        // diagonal entry: cond(P) beyond ~1e6) the factorisation is redone with the diagonal shift
-        // that makes it safe up to cond(P) ~ 1e9.
-        double tr = 0.0;
-        if (wave == 0) {
-            const double g = (lane < r) ? Gs[lane][lane] : 0.0;
-            tr = g;
+    } else if (wave == 0) {
+        const double g = (lane < r) ? Gs[lane][lane] : 0.0;
+        double tr = g;
 #pragma unroll
-            for (int m = 32; m >= 1; m >>= 1) tr += __shfl_xor(tr, m);
-            if (lane == 0) { s_trace = tr; jb.scal[0] = tr; }
-            if (lane < r) rdiag[lane] = g;                  // the diagonal before elimination
-        }
-        factor();
+        for (int m = 32; m >= 1; m >>= 1) tr += __shfl_xor(tr, m);
+        if (lane == 0) { s_trace = tr; jb.scal[0] = tr; }
+        if (lane < r) rdiag[lane] = g;                      // the diagonal before elimination
+    }
+    // First pass: plain Cholesky first; if a pivot is lost (non-positive, or below 1e-12 of its
+    // diagonal entry: cond(P) beyond ~1e6) the factorisation is redone with the diagonal shift
+    // that makes it safe up to cond(P) ~ 1e9.  The second pass factors once.
+    for (int attempt = 0;; ++attempt) {
         if (wave == 0) {
-            const bool lost = lane < r && !(Gs[lane][lane] > 1e-12 * rdiag[lane]);
+            chol_wave<RM / 16>(Gs, Xs, nb, &bad);
+            const bool lost = pass == 0 && lane < r && !(Gs[lane][lane] > 1e-12 * rdiag[lane]);
             const unsigned long long mask = __ballot(lost);
             if (lane == 0) s_bad = (bad != 0 || mask != 0) ? 1 : 0;
         }
         __syncthreads();
-        if (s_bad) {
-            scatter();
-            bad = 0;
-            if (wave == 0) {
-                const double shift = 11.0 * ((double)n * r + (double)r * (r + 1)) * OP_EPS * tr;
-                if (lane < r) Gs[lane][lane] += shift;
-            }
-            factor();
-        }
+        if (pass != 0 || attempt != 0 || !s_bad) break;
+        shifted = true;
+        scatter();
+        if (tid < r) Gs[tid][tid] += 11.0 * ((double)n * r + (double)r * (r + 1)) * OP_EPS * s_trace;
         __syncthreads();
     }
+    __syncthreads();
     if (tid == 0) s_bad = bad;
+    double gdiag = 0.0;                      // the column's diagonal before elimination
     if (tid < r) {
         double p = Gs[tid][tid];
         if (!(p > 0.0)) p = 1.0;
         const double d = sqrt(p);
         dinv[tid] = 1.0 / d;
-        pinvs[tid] = d;                     // the pivots' reciprocals are not needed any more
+        pinvs[tid] = d;
+        gdiag = rdiag[tid];
         const double rd = (pass == 0 ? 1.0 : jb.scal[1 + tid]) * d;
         rdiag[tid] = rd;
         jb.scal[1 + tid] = rd;
+    } else if (tid < OP_RMAX) {
+        dinv[tid] = 1.0; pinvs[tid] = 1.0;
     }
+    if (tid < OP_RMAX) gsq[tid] = tid < r ? sqrt(gdiag) : 0.0;
     __syncthreads();
+    if (pass == 0 && !shifted) {
+        // X = R^-1, wave J its block column J from the diagonal block up:  X_IJ = -X_II sum_{I < K <= J} R_IK X_KJ.  A result
+        // block (lane: rows lg + 4 v, column ll) is the B operand of the next product as it is, K slot (v, lg) being row
+        // lg + 4 v, so the chain stays in registers.  Stored in that order for apply: block (I, J) of the upper triangle at
+        // J (J + 1) / 2 + I, element [v][lane].
+        double cs = 0.0;                     // this lane's share of its column's sum_i sqrt(G_ii) |X_ij|
+        if (wave < nb) {
+            const int J = wave;
+            v4d X[RM / 16];
+#pragma unroll
+            for (int I = RM / 16 - 1; I >= 0; --I) {
+                if (I > J) continue;         // uniform
+                if (I == J) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int i = lg + 4 * v;
+                        X[I][v] = (ll >= i && 16 * J + ll < r) ? Xs[I][i][ll] * dinv[16 * J + ll] : 0.0;
+                    }
+                } else {
+                    v4d acc = {0.0, 0.0, 0.0, 0.0};
+                    const double di = dinv[16 * I + ll];
+#pragma unroll
+                    for (int K = I + 1; K < RM / 16; ++K)
+                        if (K <= J)          // uniform
+#pragma unroll
+                            for (int v = 0; v < 4; ++v)
+                                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(Gs[16 * I + ll][16 * K + lg + 4 * v] * di, X[K][v], acc, 0, 0, 0);
+                    v4d o = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int k = lg + 4 * v;
+                        o = __builtin_amdgcn_mfma_f64_16x16x4f64(k >= ll ? -Xs[I][ll][k] * dinv[16 * I + k] : 0.0, acc[v], o, 0, 0, 0);
+                    }
+                    X[I] = o;
+                }
+                double* xo = jb.Rinv + (J * (J + 1) / 2 + I) * 256 + lane;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    xo[64 * v] = X[I][v];
+                    cs += gsq[16 * I + lg + 4 * v] * fabs(X[I][v]);
+                }
+            }
+            cs += __shfl_xor(cs, 16);
+            cs += __shfl_xor(cs, 32);
+#pragma unroll
+            for (int m = 8; m >= 1; m >>= 1) cs = fmax(cs, __shfl_xor(cs, m));
+        }
+        if (lane == 0) sm.colmax[wave] = cs;
+        __syncthreads();
+        double c = 0.0;
+#pragma unroll
+        for (int w = 0; w < OP_NW; ++w) c = fmax(c, sm.colmax[w]);
+        // (16 products in a chain per slice, the slices of a group, the groups; then factor, inverse and product)
+        const double bound = OP_EPS * ((18.0 + jb.gsz + nslices + 2.0 * r) * c * c + 4.0 * r * c);
+        if (s_bad == 0 && bound <= OP_DONE_TOL) {            // (false for NaN)
+            if (tid == 0) jb.scal[66] = 2.0;
+            if (tid < 64) {
+                const unsigned long long mask = __ballot(tid < r && !(rdiag[tid] > 1e-12 * sqrt(s_trace)));
+                if (tid == 0 && info && mask) flag_info(info, jb.mode1, __ffsll((long long)mask));
+            }
+            return false;
+        }
+    }
+    if (pass == 0 && tid == 0) jb.scal[66] = 0.0;
     {   // R = rows scaled by 1 / R[k][k], zeros below the diagonal (reads first, selects after)
         const int gb = tid & 63;
-        double gv[RM / 4], dv[RM / 4], iv[RM / 4];
+        double gv[RM / OP_NW], dv[RM / OP_NW], iv[RM / OP_NW];
 #pragma unroll
-        for (int it = 0; it < RM / 4; ++it) {
-            const int ga = (tid >> 6) + 4 * it;
+        for (int it = 0; it < RM / OP_NW; ++it) {
+            const int ga = (tid >> 6) + OP_NW * it;
             gv[it] = Gs[ga][gb]; dv[it] = pinvs[ga]; iv[it] = dinv[ga];
         }
 #pragma unroll
-        for (int it = 0; it < RM / 4; ++it) asm volatile("" : "+v"(gv[it]), "+v"(dv[it]), "+v"(iv[it]));
+        for (int it = 0; it < RM / OP_NW; ++it) asm volatile("" : "+v"(gv[it]), "+v"(dv[it]), "+v"(iv[it]));
 #pragma unroll
-        for (int it = 0; it < RM / 4; ++it) {
-            const int ga = (tid >> 6) + 4 * it;
+        for (int it = 0; it < RM / OP_NW; ++it) {
+            const int ga = (tid >> 6) + OP_NW * it;
             if (ga < r && gb < r) jb.R[ga * r + gb] = (ga < gb) ? gv[it] * iv[it] : (ga == gb ? dv[it] : 0.0);
         }
     }
     // inverse of each 16x16 diagonal block of R:  (R_bb^-1)[i][j] = (L_bb^-1)[j][i] / R[j][j]
-    for (int e = tid; e < nb * 256; e += 256) {
+    for (int e = tid; e < nb * 256; e += OP_NT) {
         const int b = e >> 8, i = (e >> 4) & 15, jj = e & 15, base = 16 * b;
         const bool in = base + i < r && base + jj < r && jj >= i;
         jb.Dinv[e] = in ? Xs[b][i][jj] * dinv[base + jj] : 0.0;
@@ -466,10 +576,13 @@ __device__ bool chol_job(const OrthJob& jb, int pass, int last, int32_t* info, C
 
 // ---- hand-over from the slices of a mode to its factorisation ------------------------------
 // Every workgroup of a mode calls this after its global writes.  Returns true in exactly one of
-// them, the one that arrives last; by then the writes of all the others are visible to it.  The
-// counter must be zero before the launch and is zero again afterwards.
+// them, the one that arrives last; by then the writes of all the others are visible to it: what was published to loads of
+// the same kind, and with FENCE everything to everything.  The counter must be zero before the launch and is zero again
+// afterwards.
+template <bool FENCE>
 __device__ bool last_arrival(int32_t* ctr, int nblk, int* s_flag) {
-    __threadfence();                       // this thread's writes are visible device-wide ...
+    if (FENCE) __threadfence();            // this thread's writes are visible device-wide ...
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // (published ones once they are acknowledged)
     __syncthreads();                       // ... for every thread of the workgroup
     if (threadIdx.x == 0) {
         const int ticket = atomicAdd(ctr, 1);
@@ -478,87 +591,82 @@ __device__ bool last_arrival(int32_t* ctr, int nblk, int* s_flag) {
     }
     __syncthreads();
     const bool last = *s_flag != 0;
-    if (last) __threadfence();             // order the reads below after the other workgroups' arrivals
+    if (FENCE && last) __threadfence();    // order the reads below after the other workgroups' arrivals
     return last;
 }
 
 // ---- gram0 ----------------------------------------------------------------------------------
-// RM bounds the ranks of the launch's modes: a slice has at most 32 * RM elements, ITS per thread.
+// A slice is 16 rows, so that the partial sums of P (10 MB for 32 splits of 960 x 40) are read by as many CUs as there are
+// slices; the slice Grams are then added in two levels, groups of gsz slices by the workgroup of a group that arrives last,
+// the groups by the one of the mode that does, because what one CU can read past its L2 is 25 bytes a cycle (30 slices of
+// 32 rows summed by one workgroup: 8.5 us for the partial sums and 6.8 for the Grams; 60 slices in 8 groups 3.6 and 6.3).
+// RM bounds the ranks of the launch's modes: a slice has at most 16 * RM elements, ITS per thread.
 template <int RM>
-__global__ __launch_bounds__(256) void k_orth_gram0(OrthBatch a) {
+__global__ __launch_bounds__(OP_NT, RM <= 32 ? 4 : 2) void k_orth_gram0(OrthBatch a) {
     __shared__ __align__(16) unsigned char raw[sizeof(CholSmem)];
     __shared__ int s_last;
-    double (*Ps)[OP_LD] = reinterpret_cast<double (*)[OP_LD]>(raw);                 // [OP_RS][OP_LD]
-    double* red = reinterpret_cast<double*>(raw) + OP_RS * OP_LD;                     // [256]
-    static_assert(sizeof(CholSmem) >= (OP_RS * OP_LD + 256) * sizeof(double), "slice buffers fit");
+    double (*Ps)[OP_LD] = reinterpret_cast<double (*)[OP_LD]>(raw);                 // [OP_GS][OP_LD]
+    static_assert(sizeof(CholSmem) >= OP_GS * OP_LD * sizeof(double), "the slice fits");
     int ji, blk;
     find_job(a, &ji, &blk);
-    const OrthJob jb = a.job[ji];
-    const int n = jb.n, r = jb.r, tid = threadIdx.x;
+    const OrthJob& jb = a.job[ji];
+    const int n = jb.n, r = jb.r, ns = jb.nsplit, tid = threadIdx.x;
     if (blk == 0 && tid == 0 && jb.info) *jb.info = 0;            // nothing has reported yet
-    const int i0 = blk * OP_RS;
-    const int nrows = (n - i0 < OP_RS) ? n - i0 : OP_RS;
+    const int i0 = blk * OP_GS;
+    const int nrows = (n - i0 < OP_GS) ? n - i0 : OP_GS;
     const long long cnt = (long long)n * r;
     const int E = nrows * r;
-    for (int e = tid; e < OP_RS * OP_LD; e += 256) (&Ps[0][0])[e] = 0.0;
-    // Sum of the split partial sums.  A slice of 256 or more elements gives every thread ITS
-    // elements and SB splits per round; a smaller one shares its splits among `nsg` thread
-    // groups whose results are added in group order.  All loads of a round are in flight together.
-    constexpr int ITS = RM / 8, SB = 32 / ITS;
-    const bool small = E < 256;
-    const int nsg = small ? 256 / E : 1;
-    const int sg = small ? tid / E : 0;
-    const int idx0 = small ? tid - sg * E : tid;
-    const bool act0 = sg < nsg;
+    // Sum of the split partial sums, in their order; up to 32 loads per thread in flight
+    constexpr int ITS = (OP_GS * RM + OP_NT - 1) / OP_NT, SB = 32 / ITS;
     double sum[ITS];
 #pragma unroll
     for (int it = 0; it < ITS; ++it) sum[it] = 0.0;
-    for (int sp0 = sg; sp0 < jb.nsplit; sp0 += SB * nsg) {
+#pragma unroll 1
+    for (int sp0 = 0; sp0 < ns; sp0 += SB) {
         double t[SB][ITS];
 #pragma unroll
-        for (int u = 0; u < SB; ++u)
+        for (int u = 0; u < SB; ++u) {
+            const double* src = jb.part + (long long)(sp0 + u < ns ? sp0 + u : ns - 1) * cnt + (long long)i0 * r;    // uniform
 #pragma unroll
-            for (int it = 0; it < ITS; ++it) {
-                const int sp = sp0 + u * nsg, idx = idx0 + 256 * it;
-                const bool ok = act0 && idx < E && (it == 0 || !small) && sp < jb.nsplit;
-                t[u][it] = ldg_f64(jb.part, (long long)sp * cnt + (long long)i0 * r + idx, ok);
-            }
-#pragma unroll
-        for (int u = 0; u < SB; ++u)
-#pragma unroll
-            for (int it = 0; it < ITS; ++it) sum[it] += t[u][it];
-    }
-    if (small && nsg > 1) {
-        if (act0) red[sg * E + idx0] = sum[0];
-        __syncthreads();
-        if (act0 && sg == 0) {
-            double s2 = 0.0;
-            for (int g2 = 0; g2 < nsg; ++g2) s2 += red[g2 * E + idx0];
-            sum[0] = s2;
+            for (int it = 0; it < ITS; ++it) t[u][it] = src[(unsigned)(tid + OP_NT * it < E ? tid + OP_NT * it : 0)];
         }
-    } else {
-        __syncthreads();      // the zero fill above is complete
-    }
-    if (act0 && sg == 0) {
 #pragma unroll
-        for (int it = 0; it < ITS; ++it) {
-            const int idx = idx0 + 256 * it;
-            if (idx < E && (it == 0 || !small)) {
-                jb.P64[(long long)i0 * r + idx] = sum[it];
-                const int pi = small_div(idx, 1.0f / (float)r);
-                Ps[pi][idx - pi * r] = sum[it];
-            }
+        for (int u = 0; u < SB; ++u)
+#pragma unroll
+            for (int it = 0; it < ITS; ++it) sum[it] += sp0 + u < ns ? t[u][it] : 0.0;
+    }
+    for (int e = tid; e < OP_GS * OP_LD; e += OP_NT) (&Ps[0][0])[e] = 0.0;
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < ITS; ++it) {
+        const int idx = tid + OP_NT * it;
+        if (idx < E) {
+            jb.P64[(long long)i0 * r + idx] = sum[it];
+            const int pi = small_div(idx, 1.0f / (float)r);
+            Ps[pi][idx - pi * r] = sum[it];
         }
     }
     __syncthreads();
-    gram_from_lds(Ps, r, jb.Gpart + (long long)blk * ((r * (r + 1)) / 2));
-    // the workgroup that finishes a mode's last slice goes on to factor its Gram matrix
-    if (!last_arrival(jb.ctr + 0, jb.nblk, &s_last)) return;
-    chol_job<RM>(jb, 0, 0, jb.info, *reinterpret_cast<CholSmem*>(raw));
+    const int T = (r * (r + 1)) / 2, nsl = (n + OP_GS - 1) / OP_GS, gsz = jb.gsz, ngrp = (nsl + gsz - 1) / gsz;
+    const int grp = blk / gsz, in_grp = nsl - grp * gsz < gsz ? nsl - grp * gsz : gsz;
+    gram_from_lds<OP_GS>(Ps, r, jb.Gpart + (long long)blk * T);
+    // the workgroup that finishes a group's last slice adds the group up, the one that finishes the last group factors
+    if (!last_arrival<false>(jb.ctr + 2 + grp, in_grp, &s_last)) return;
+    double* sums = jb.Gpart;
+    if (ngrp > 1) {
+        sums += (long long)nsl * T;
+        double gs[packed_its<RM>()];
+        sum_packed<RM>(jb.Gpart + (long long)grp * gsz * T, in_grp, T, gs);
+#pragma unroll
+        for (int it = 0; it < packed_its<RM>(); ++it)
+            if (tid + OP_NT * it < T) publish(sums + (long long)grp * T + tid + OP_NT * it, gs[it]);
+        if (!last_arrival<false>(jb.ctr + 0, ngrp, &s_last)) return;
+    }
+    chol_job<RM>(jb, 0, 0, sums, ngrp > 1 ? ngrp : nsl, jb.info, *reinterpret_cast<CholSmem*>(raw));
 }
 
 // ---- apply ----------------------------------------------------------------------------------
-// 256 threads load the slice, R and the diagonal-block inverses in one round of loads; waves 0 and 1
+// Not certified: all threads load the slice, R and the diagonal-block inverses in one round of loads; waves 0 and 1
 // then solve 16 rows each.
 struct ApplySmem {
     double Ps[OP_RS][OP_LD];
@@ -583,42 +691,42 @@ __device__ void apply_slice(const OrthJob& jb, int blk, int final_pass, ApplySme
     const int nb = (r + 15) / 16;
     const int i0 = blk * OP_RS;
     const int nrows = (n - i0 < OP_RS) ? n - i0 : OP_RS;
-    constexpr int PI = RM / 8, RI = RM * RM / 256, DI = RM / 16;
+    constexpr int PI = OP_RS * RM / OP_NT, RI = (RM * RM + OP_NT - 1) / OP_NT, DI = (RM * 16 + OP_NT - 1) / OP_NT;
     const float inv_r = 1.0f / (float)r;
     double tp[PI], tr[RI], td[DI];
 #pragma unroll
     for (int u = 0; u < PI; ++u) {
-        const int idx = u * 256 + tid;
+        const int idx = u * OP_NT + tid;
         tp[u] = ldg_f64(jb.P64, (long long)i0 * r + idx, idx < nrows * r);
     }
 #pragma unroll
     for (int u = 0; u < RI; ++u) {
-        const int e = u * 256 + tid;
+        const int e = u * OP_NT + tid;
         tr[u] = ldg_f64(jb.R, e, e < r * r);
     }
 #pragma unroll
     for (int u = 0; u < DI; ++u) {
-        const int e = u * 256 + tid;
+        const int e = u * OP_NT + tid;
         td[u] = ldg_f64(jb.Dinv, e, e < nb * 256);
     }
-    for (int e = tid; e < OP_RS * OP_LD; e += 256) (&Ps[0][0])[e] = 0.0;
-    for (int e = tid; e < OP_RMAX * OP_LD; e += 256) (&Rs[0][0])[e] = 0.0;
+    for (int e = tid; e < OP_RS * OP_LD; e += OP_NT) (&Ps[0][0])[e] = 0.0;
+    for (int e = tid; e < OP_RMAX * OP_LD; e += OP_NT) (&Rs[0][0])[e] = 0.0;
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < PI; ++u) {
-        const int idx = u * 256 + tid;
+        const int idx = u * OP_NT + tid;
         const int pi = small_div(idx, inv_r);
         if (idx < nrows * r) Ps[pi][idx - pi * r] = tp[u];
     }
 #pragma unroll
     for (int u = 0; u < RI; ++u) {
-        const int e = u * 256 + tid;
+        const int e = u * OP_NT + tid;
         const int ri = small_div(e, inv_r);
         if (e < r * r) Rs[ri][e - ri * r] = tr[u];
     }
 #pragma unroll
     for (int u = 0; u < DI; ++u) {
-        const int e = u * 256 + tid;
+        const int e = u * OP_NT + tid;
         if (e < nb * 256) Ds[e >> 8][(e >> 4) & 15][e & 15] = td[u];
     }
     __syncthreads();
@@ -652,18 +760,18 @@ __device__ void apply_slice(const OrthJob& jb, int blk, int final_pass, ApplySme
         __syncthreads();
     }
     if (final_pass) {
-        for (int idx = tid; idx < nrows * r; idx += 256) {
+        for (int idx = tid; idx < nrows * r; idx += OP_NT) {
             const int pi = small_div(idx, inv_r);
             jb.Uout[(long long)i0 * r + idx] = (float)Ps[pi][idx - pi * r];
         }
     } else {
-        for (int idx = tid; idx < nrows * r; idx += 256) {
+        for (int idx = tid; idx < nrows * r; idx += OP_NT) {
             const int pi = small_div(idx, inv_r);
             const double q0 = Ps[pi][idx - pi * r];
             jb.P64[(long long)i0 * r + idx] = q0;
             jb.Uout[(long long)i0 * r + idx] = (float)q0;
         }
-        gram_from_lds(Ps, r, jb.Gpart + (long long)blk * ((r * (r + 1)) / 2));
+        gram_from_lds<OP_RS>(Ps, r, jb.Gpart + (long long)blk * ((r * (r + 1)) / 2));
     }
 }
 
@@ -672,16 +780,53 @@ __device__ void apply_slice(const OrthJob& jb, int blk, int final_pass, ApplySme
 // and, only if that fails, factors it and solves all slices of the mode once more by itself (a
 // rare, slow path: it trades a launch per call for serial work on ill-conditioned inputs).
 template <int RM>
-__global__ __launch_bounds__(256) void k_orth_apply(OrthBatch a) {
+__global__ __launch_bounds__(OP_NT) void k_orth_apply(OrthBatch a) {
     __shared__ __align__(16) unsigned char raw[sizeof(ApplyOrChol)];
     __shared__ int s_last;
     ApplySmem& ap = *reinterpret_cast<ApplySmem*>(raw);
     int ji, blk;
     find_job(a, &ji, &blk);
     const OrthJob jb = a.job[ji];
+    {
+        // Certified: wave (half h, block column J) multiplies 16 rows by the block column of X, operands straight from memory
+        // (K slot (v, lg) of a block is index lg + 4 v for both sides); they are requested together with the flag that says
+        // whether they are of use.
+        const int n = jb.n, r = jb.r, nb = (r + 15) / 16;
+        const int lane = threadIdx.x & 63, lg = lane >> 4, ll = lane & 15;
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const int h = wave & 1, J = wave >> 1;
+        const int row = blk * OP_RS + 16 * h + ll;
+        double av[RM / 16][4], bv[RM / 16][4];
+#pragma unroll
+        for (int I = 0; I < RM / 16; ++I)
+            if (I <= J && J < nb) {          // uniform
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int k = 16 * I + lg + 4 * v;
+                    av[I][v] = jb.P64[(row < n && k < r) ? (long long)row * r + k : 0];
+                    bv[I][v] = jb.Rinv[(J * (J + 1) / 2 + I) * 256 + 64 * v + lane];
+                }
+            }
+        if (jb.scal[66] == 2.0) {
+            if (J >= nb) return;
+            v4d q = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int I = 0; I < RM / 16; ++I)
+                if (I <= J)                  // uniform
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        q = __builtin_amdgcn_mfma_f64_16x16x4f64((row < n && 16 * I + lg + 4 * v < r) ? av[I][v] : 0.0, bv[I][v], q, 0, 0, 0);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int i = blk * OP_RS + 16 * h + lg + 4 * v, c = 16 * J + ll;
+                if (i < n && c < r) jb.Uout[(long long)i * r + c] = (float)q[v];
+            }
+            return;
+        }
+    }
     apply_slice<RM>(jb, blk, 0, ap);
-    if (!last_arrival(jb.ctr + 1, jb.nblk, &s_last)) return;
-    const bool again = chol_job<RM>(jb, 1, 1, jb.info, *reinterpret_cast<CholSmem*>(raw));
+    if (!last_arrival<true>(jb.ctr + 1, jb.nblk, &s_last)) return;
+    const bool again = chol_job<RM>(jb, 1, 1, jb.Gpart, jb.nblk, jb.info, *reinterpret_cast<CholSmem*>(raw));
     if (!again) return;
     for (int b2 = 0; b2 < jb.nblk; ++b2) {
         __threadfence();                   // R, Dinv (and every slice of Q0) are read back from memory
@@ -863,7 +1008,6 @@ __global__ __launch_bounds__(OWC_NT) void k_orthw_chol(OrthBatch a, int pass, in
     const int nb = (r + 15) / 16;
     double* pinvs = rdiag + r;                               // nb * 16
     double (*Xs)[17] = reinterpret_cast<double (*)[17]>(pinvs + nb * 16);
-    double (*rowbuf)[64][4] = reinterpret_cast<double (*)[64][4]>(pinvs + nb * 16 + 16 * 17);
     const GramPacked G{Gp, r};
     const int lane = tid & 63, wave = tid >> 6, lg = lane >> 4, ll = lane & 15;
     // Second pass with a summed Gram matrix: its distance from the identity has been measured by the launch that
@@ -936,7 +1080,7 @@ __global__ __launch_bounds__(OWC_NT) void k_orthw_chol(OrthBatch a, int pass, in
     for (int attempt = 0;; ++attempt) {
         int bad = 0;
         for (int P = 0; P < nb; ++P) {
-            if (wave == 0) chol_block16(G, rowbuf, Xs, pinvs, 16 * P, &bad);
+            if (wave == 0) chol_block16(G, Xs, pinvs, 16 * P, &bad);
             __syncthreads();
             if (tid < 16 && 16 * P + tid < r) {
                 const double p = G.ld(16 * P + tid, 16 * P + tid);          // the pivot actually used
@@ -1236,6 +1380,16 @@ __global__ __launch_bounds__(ORTH_NT) void k_orth_big(OrthBatch a) {
 // ---- host side -------------------------------------------------------------------------------
 bool orth_fast_supported(int r) { return r <= OP_RMAX; }
 int orth_slices(int n) { return (n + OP_RS - 1) / OP_RS; }
+int orth_gram_slices(int n) { return (n + OP_GS - 1) / OP_GS; }
+// slices per group: about the square root, no more than kOrthGroups groups
+int orth_group_size(int n) {
+    const int s = orth_gram_slices(n);
+    int g = 1;
+    while (g * g < s) ++g;
+    if (s <= 12) g = s;                                  // one group: the second level only copies
+    while ((s + g - 1) / g > kOrthGroups) ++g;
+    return g;
+}
 bool orth_wide_supported(int r) { return r > OP_RMAX && r <= OW_RMAX; }
 int orth_wide_gram_blocks(int n) { return (n + OW_ROWS - 1) / OW_ROWS; }
 
@@ -1258,7 +1412,8 @@ static bool fast_args_ok(const OrthArgs& a) {
     for (int j = 0; j < a.njobs; ++j) {
         const OrthJob& jb = a.job[j];
         if (jb.n <= 0 || jb.r <= 0 || jb.r > OP_RMAX || jb.nblk != orth_slices(jb.n)) return false;
-        if (!jb.Gpart || !jb.R || !jb.Dinv || !jb.scal || !jb.P64 || !jb.Uout || !jb.part || !jb.ctr) return false;
+        if (jb.gsz != orth_group_size(jb.n) || orth_groups(jb.n) > kOrthGroups) return false;
+        if (!jb.Gpart || !jb.R || !jb.Rinv || !jb.Dinv || !jb.scal || !jb.P64 || !jb.Uout || !jb.part || !jb.ctr) return false;
     }
     return true;
 }
@@ -1300,7 +1455,10 @@ bool make_orthw_gsum(const GsumArgs& a, Item* out) {
     return true;
 }
 bool make_orth_gram0(const OrthArgs& a, Item* out) {
-    return fast_args_ok(a) && put_orth(IT_GRAM0, 0, "k_orth_gram0", a, total_blocks(a), out);
+    if (!fast_args_ok(a)) return false;
+    int blocks = 0;
+    for (int j = 0; j < a.njobs; ++j) blocks += orth_gram_slices(a.job[j].n);
+    return put_orth(IT_GRAM0, 0, "k_orth_gram0", a, blocks, out);
 }
 bool make_orth_apply(const OrthArgs& a, Item* out) {
     return fast_args_ok(a) && put_orth(IT_APPLY, 0, "k_orth_apply", a, total_blocks(a), out);
@@ -1388,29 +1546,31 @@ hipError_t launch_orth_items(const Item* const* items, int n, hipStream_t st, ch
             rmax = a.job[k].r > rmax ? a.job[k].r : rmax;
         }
     }
+    b.first[0] = 0;
+    for (int j = 0; j < b.njobs; ++j) b.first[j + 1] = b.first[j] + (kind == IT_GRAM0 ? orth_gram_slices(b.job[j].n) : b.job[j].nblk);
     const int rm = rmax <= 16 ? 16 : (rmax <= 32 ? 32 : (rmax <= 48 ? 48 : 64));   // register shape of the fast kernels
     if (label_out && (kind == IT_GRAM0 || kind == IT_APPLY))
         std::snprintf(label_out, 96, "%s<%d>", kind == IT_GRAM0 ? "k_orth_gram0" : "k_orth_apply", rm);
     switch (kind) {
         case IT_GRAM0:
-            if (rm == 16) hipLaunchKernelGGL(k_orth_gram0<16>, grid, 256, 0, st, b);
-            else if (rm == 32) hipLaunchKernelGGL(k_orth_gram0<32>, grid, 256, 0, st, b);
-            else if (rm == 48) hipLaunchKernelGGL(k_orth_gram0<48>, grid, 256, 0, st, b);
-            else hipLaunchKernelGGL(k_orth_gram0<64>, grid, 256, 0, st, b);
+            if (rm == 16) hipLaunchKernelGGL(k_orth_gram0<16>, grid, OP_NT, 0, st, b);
+            else if (rm == 32) hipLaunchKernelGGL(k_orth_gram0<32>, grid, OP_NT, 0, st, b);
+            else if (rm == 48) hipLaunchKernelGGL(k_orth_gram0<48>, grid, OP_NT, 0, st, b);
+            else hipLaunchKernelGGL(k_orth_gram0<64>, grid, OP_NT, 0, st, b);
             break;
         case IT_APPLY:
-            if (rm == 16) hipLaunchKernelGGL(k_orth_apply<16>, grid, 256, 0, st, b);
-            else if (rm == 32) hipLaunchKernelGGL(k_orth_apply<32>, grid, 256, 0, st, b);
-            else if (rm == 48) hipLaunchKernelGGL(k_orth_apply<48>, grid, 256, 0, st, b);
-            else hipLaunchKernelGGL(k_orth_apply<64>, grid, 256, 0, st, b);
+            if (rm == 16) hipLaunchKernelGGL(k_orth_apply<16>, grid, OP_NT, 0, st, b);
+            else if (rm == 32) hipLaunchKernelGGL(k_orth_apply<32>, grid, OP_NT, 0, st, b);
+            else if (rm == 48) hipLaunchKernelGGL(k_orth_apply<48>, grid, OP_NT, 0, st, b);
+            else hipLaunchKernelGGL(k_orth_apply<64>, grid, OP_NT, 0, st, b);
             break;
         case IT_ORTHW_GRAM:
             hipLaunchKernelGGL(k_orthw_gram, grid, 256, 0, st, b);
             break;
         case IT_ORTHW_CHOL: {
-            // packed triangle, dinv, rdiag, pivot reciprocals, inverse block factor, row exchange buffer
+            // packed triangle, dinv, rdiag, pivot reciprocals, inverse block factor
             const size_t nb16 = (size_t)((rmax + 15) / 16) * 16;
-            const size_t lds = sizeof(double) * ((size_t)rmax * (rmax + 1) / 2 + 2 * (size_t)rmax + nb16 + 16 * 17 + 2 * 64 * 4);
+            const size_t lds = sizeof(double) * ((size_t)rmax * (rmax + 1) / 2 + 2 * (size_t)rmax + nb16 + 16 * 17);
             static std::atomic<size_t> lds_allowed{0};     // the attribute only ever needs to grow
             if (lds > lds_allowed.load()) {
                 hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_orthw_chol),

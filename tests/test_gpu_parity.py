@@ -627,3 +627,13 @@ def test_correlation_takes_fewer_rows_per_chunk_where_the_slab_is_large(dims, ra
     finally:
         B.asi_profile_enable(False)
     assert any("k_corr_mfma" in s_ for s_ in sites), sites
+
+
+@pytest.mark.parametrize("ratio", [0.9, 0.2])
+@pytest.mark.parametrize("dims,ranks", [((15, 192, 193), (15, 16, 17)), ((33, 208, 50), (32, 33, 49)), ((64, 70, 1000), (64, 63, 48))])
+def test_orthogonalisation_at_block_and_slice_edges(dims, ranks, ratio):
+    """Ranks one around every block of 16 up to 64, modes of one ragged slice of 16 rows, of 12 and 13 slices (added directly
+    and in groups) and of 63; graded mildly (the first pass is certified from its factor) and strongly (it is checked and
+    repeated)."""
+    lay = Layer("orth", dims, ranks, "f32", "linear", 12)
+    _check_orthonormal_basis(lay, _graded_tensor(lay, ratio), 13, f"{dims} ratio {ratio}")
