@@ -298,7 +298,8 @@ struct ConvPlan {
     size_t bytes = 0;
 };
 
-ConvPlan plan_conv(const Shape& s, const ConvGeom& cg, void* ws) {
+// layers: how many layers of a batch share the launches; the workspace is that of one alone, which has the most splits
+ConvPlan plan_conv(const Shape& s, const ConvGeom& cg, void* ws, int layers = 1) {
     ConvPlan p;
     const CorrGeom& g = cg.g;
     Carver c(ws);
@@ -307,11 +308,15 @@ ConvPlan plan_conv(const Shape& s, const ConvGeom& cg, void* ws) {
     if ((long long)s.r[2] * s.r[3] > kKronMaxN || (long long)g.H * g.W > kKronMaxOut)
         p.Z1 = c.take<float>((size_t)g.r1 * g.r2 * g.H * s.r[3]);      // else Z comes from one merged pass
     p.Z = c.take<float>((size_t)g.r1 * g.r2 * g.H * g.W);
-    p.nsplit = corr_splits(g);
+    p.nsplit = corr_splits(g, 1);
     const size_t tsz = (size_t)g.cout * g.r2 * g.kh * g.kw;
     p.T = c.take<float>(tsz);
     p.Tpart = p.nsplit > 1 ? c.take<float>(tsz * p.nsplit) : p.T;
     p.bytes = c.off;
+    if (layers > 1) {
+        p.nsplit = corr_splits(g, layers);
+        if (p.nsplit == 1) p.Tpart = p.T;
+    }
     return p;
 }
 
@@ -711,7 +716,7 @@ asi_status build_core(const asi_tensor_desc* desc, const void* A, const float* c
 }
 
 asi_status build_conv(const asi_tensor_desc* desc, const float* S, const float* const* U, const void* grad_out,
-                      const asi_conv2d_desc* conv, float* dW, int accumulate, void* ws, size_t ws_bytes, Program& pg) {
+                      const asi_conv2d_desc* conv, float* dW, int accumulate, void* ws, size_t ws_bytes, int layers, Program& pg) {
     Shape s;
     asi_status why;
     if (!parse_desc(desc, &s, &why)) return why;
@@ -721,7 +726,7 @@ asi_status build_conv(const asi_tensor_desc* desc, const float* S, const float* 
     if (!S || !U || !grad_out || !dW) return ASI_ERR_INVALID_ARG;
     for (int m = 0; m < 4; ++m)
         if (!U[m]) return ASI_ERR_INVALID_ARG;
-    ConvPlan p = plan_conv(s, cg, ws);
+    ConvPlan p = plan_conv(s, cg, ws, layers);
     if (!ws_ok(ws, ws_bytes, p.bytes)) return ASI_ERR_WORKSPACE;
     const CorrGeom& g = cg.g;
     const int r3 = s.r[2], r4 = s.r[3];
@@ -771,7 +776,7 @@ asi_status build_conv(const asi_tensor_desc* desc, const float* S, const float* 
     // 4. T = correlation of Zpad with G1 over (r1, Ho, Wo)        (cout, r2, kh, kw)
     const double tsz = (double)g.cout * g.r2 * taps;
     ASI_ADD(pg, "", 4.0 * ((double)g.r1 * g.cout * g.Ho * g.Wo + (double)g.r1 * g.r2 * g.H * g.W + tsz * p.nsplit),
-            2.0 * g.r1 * g.Ho * g.Wo * tsz, make_corr(G1, p.Z, p.Tpart, g, p.nsplit, it__));
+            2.0 * g.r1 * g.Ho * g.Wo * tsz, make_corr(G1, p.Z, p.Tpart, g, p.nsplit, layers, it__));
     // 5. dW = T x_(r2) U2, per group                              (cout, C/groups, kh, kw)
     // An ungrouped convolution with 1 or 9 taps and r2 <= 64 sums the partial T's and expands the result in one
     // launch (T itself is then never written); anything else sums first and multiplies in a second launch.
@@ -1005,7 +1010,7 @@ asi_status asi_weight_grad_conv2d_batch(int32_t count, const asi_tensor_desc* de
     std::vector<Program> progs(count);
     for (int l = 0; l < count; ++l)
         ASI_TRYS(build_conv(&descs[l], S[l], U[l], grad_out[l], &convs[l], dW[l], accumulate ? accumulate[l] : 0, ws[l],
-                            ws_bytes[l], progs[l]));
+                            ws_bytes[l], count, progs[l]));
     return flush(progs, static_cast<hipStream_t>(stream), "dW");
 }
 

@@ -22,14 +22,16 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int CR_TO = 64;            // output channels per workgroup
 // Output positions per chunk and the floats of LDS for the Z slab that goes with them.  Small output maps
-// (a few hundred positions) take chunks of 64 in one LDS buffer: load -> barrier -> store -> barrier -> multiply.
-// On large maps that order leaves the matrix pipe idle a third of the time (measured with device
+// (a few hundred positions) take chunks of 64.  One LDS buffer (load -> barrier -> store -> barrier -> multiply)
+// leaves the matrix pipe of a large map idle a third of the time (measured with device
 // timestamps: per chunk 1.0-1.3 us of LDS stores and 1.3-2.7 us of load issue in which no wave multiplies,
-// against 6-8 us of products), so they take chunks of 128 positions (whole output rows) in TWO buffers:
+// against 6-8 us of products), so large maps take chunks of 128 positions (whole output rows), and both forms use TWO buffers:
 // half of the waves store the next chunk and issue the loads of the one after it BEFORE they multiply the
 // current chunk, the other half AFTER, so that on every SIMD one wave multiplies while the other moves
 // data, and a chunk costs one barrier.
-constexpr int CR_KC_SMALL = 64, CR_ZMAX_SMALL = 4096;
+// Small maps: slabs of up to CR_ZMAX_SHORT floats (7 x 7 with a halo: 16 x 81) have an instantiation of their own, whose
+// loader takes half the loads.
+constexpr int CR_KC_SMALL = 64, CR_ZMAX_SMALL = 4096, CR_ZMAX_SHORT = 2048;
 constexpr int CR_KC_BIG = 128, CR_ZMAX_BIG = 5120;
 constexpr int CR_BIG_MIN_POSITIONS = 1024;      // Ho * Wo from which the large chunks are used
 // Waves per workgroup: 4 own 16 output channels each; with 8 the second four take every other
@@ -63,7 +65,8 @@ struct CorrJob {
     int ips;             // fallback kernel: core channels i per split
 };
 
-static bool corr_plan(const CorrGeom& g, CorrPlan* p) {
+// layers: how many layers of a batch share the launch
+static bool corr_plan(const CorrGeom& g, int layers, CorrPlan* p) {
     const int taps = g.kh * g.kw;
     if (g.Wo > CR_KC_SMALL || taps > 25) return false;
     // the kernel indexes G1 and Z with 32-bit offsets
@@ -110,6 +113,17 @@ static bool corr_plan(const CorrGeom& g, CorrPlan* p) {
         want = (3 * target + base - 1) / base;
         if (want > p->nchunks) want = p->nchunks;
         p->cps = (int)((p->nchunks + want - 1) / want);
+    } else if (layers > 1) {
+        // The other layers of a batch take their share of the CUs, and a workgroup costs about four chunks beside its own
+        // (first loads, result through LDS): the count with the fewest rounds x (chunks + 4), never more than alone (three
+        // layers of 512 x 48 x 9 over 16 x 7 x 7: 576 workgroups of two chunks 46 us, 216 of six 32).
+        long long best = -1;
+        const int alone = (int)((p->nchunks + p->cps - 1) / p->cps);
+        for (int ns = 1; ns <= alone; ++ns) {
+            const int cps = (p->nchunks + ns - 1) / ns;
+            const long long wgs = base * layers * ((p->nchunks + cps - 1) / cps), cost = ((wgs + target - 1) / target) * (cps + 4);
+            if (best < 0 || cost < best) { best = cost; p->cps = cps; }
+        }
     }
     p->nsplit = (p->nchunks + p->cps - 1) / p->cps;
     return true;
@@ -120,9 +134,10 @@ extern __shared__ float cr_dyn[];
 
 template <int MAXT>
 constexpr int corr_lds_floats(int kc, int zmax) {
-    // the G1 tile, the Z slabs and the table of window origins; afterwards the result tile
-    return (CR_TO * (16 * (MAXT < 9 ? MAXT : 9) + 1) > kc * (CR_TO + 2) + zmax) ? CR_TO * (16 * (MAXT < 9 ? MAXT : 9) + 1)
-                                                                                   : kc * (CR_TO + 2) + zmax;
+    // two buffers of (G1 tile, Z slabs), then the table of window origins; afterwards the result tile
+    return (CR_TO * (16 * (MAXT < 9 ? MAXT : 9) + 1) > 2 * (kc * (CR_TO + 1) + zmax) + kc)
+               ? CR_TO * (16 * (MAXT < 9 ? MAXT : 9) + 1)
+               : 2 * (kc * (CR_TO + 1) + zmax) + kc;
 }
 // large chunks: two buffers of (channel-major G1 tile with a pitch of kc + 4, Z slabs), then the table
 constexpr int corr_big_buf_floats() { return CR_TO * (CR_KC_BIG + 4) + CR_ZMAX_BIG; }
@@ -135,16 +150,16 @@ constexpr int corr_big_lds_floats() { return 2 * corr_big_buf_floats() + CR_KC_B
 // so the loop carries as little else as possible: per K step one table read for the window origin,
 // three address additions (one per kernel row; the three taps of a row are immediate offsets), two A
 // reads and nine B reads feed eighteen products.
-// BIGV: 0 = chunks of 64 in one buffer; 1..4 = the large-chunk form for slabs of ZR = 4 (1, 2) or 6 (3, 4) rows
+// BIGV: 0 = chunks of 64, 5 = the same for short slabs; 1..4 = the large-chunk form for slabs of ZR = 4 (1, 2) or 6 (3, 4) rows
 // with a row in 64 lanes (1, 3) or 128 lanes (2, 4): the loader's loop bounds are compile-time constants, so
 // it has no branches (as uniform run-time tests they cost 200 scalar branches and 1000 scalar instructions
 // per chunk and wave, 1.4 us of the 3.3 us a wave spent on a chunk).
 template <int MAXT, bool EXACT, int BIGV>
 __global__ __launch_bounds__(CR_NT) void k_corr_mfma(Batch<CorrJob> bt) {
-    constexpr bool BIG = BIGV != 0;
+    constexpr bool BIG = BIGV >= 1 && BIGV <= 4;
     constexpr int ZR = BIGV >= 3 ? 6 : 4;                // BIG: rows of a slab
     constexpr bool ZW64 = (BIGV & 1) != 0;               // BIG: a slab row fits 64 lanes
-    constexpr int CR_KC = BIG ? CR_KC_BIG : CR_KC_SMALL, CR_ZMAX = BIG ? CR_ZMAX_BIG : CR_ZMAX_SMALL;
+    constexpr int CR_KC = BIG ? CR_KC_BIG : CR_KC_SMALL, CR_ZMAX = BIG ? CR_ZMAX_BIG : (BIGV == 5 ? CR_ZMAX_SHORT : CR_ZMAX_SMALL);
     constexpr int OB = BIG ? 2 : 1;                      // blocks of 16 output channels per wave
     constexpr int NWO = 4 / OB;                          // waves side by side along the output channels
     constexpr int KG = CR_NW / NWO;                      // K groups: waves that share channels and split the K steps
@@ -153,8 +168,6 @@ __global__ __launch_bounds__(CR_NT) void k_corr_mfma(Batch<CorrJob> bt) {
     constexpr int CR_TG = MAXT < 9 ? MAXT : 9;           // taps per pass of the result through LDS
     constexpr int CR_TS_LD = 16 * CR_TG + 1;
     float* lds_raw = cr_dyn;                             // corr_lds_floats<MAXT>(CR_KC, CR_ZMAX) floats (BIG: corr_big_lds_floats())
-    float (*As)[CR_TO + 1] = reinterpret_cast<float (*)[CR_TO + 1]>(lds_raw);
-    float* Zs = lds_raw + CR_KC * (CR_TO + 1);
     int lb;
     const CorrJob& jb = bt.job[locate_xcd(bt, &lb)];     // the tiles of one split share its G1 rows and Z slabs
     const float* __restrict__ G1 = jb.G1;
@@ -213,7 +226,7 @@ __global__ __launch_bounds__(CR_NT) void k_corr_mfma(Batch<CorrJob> bt) {
     // depends on the slab or its row is the same for a whole wave and lives in scalar registers.
     constexpr int AP = CR_KC + 4;                                         // BIG: pitch of the channel-major G1 tile
     constexpr int NA4 = CR_TO * CR_KC / 4 / CR_NT;                        // BIG: 16-byte loads of G1 per thread
-    constexpr int BUF = BIG ? corr_big_buf_floats() : 0;                  // BIG: floats of one buffer
+    constexpr int BUF = BIG ? corr_big_buf_floats() : CR_KC * (CR_TO + 1) + CR_ZMAX;   // floats of one buffer
     constexpr int SPG = ZW64 ? 2 : 4;                                     // BIG: slabs per lane group
     constexpr int NZB = SPG * ZR;                                         // BIG: Z loads per thread and chunk
     const int rgz = __builtin_amdgcn_readfirstlane(ZW64 ? (tid >> 6) : (tid >> 7));
@@ -293,44 +306,72 @@ __global__ __launch_bounds__(CR_NT) void k_corr_mfma(Batch<CorrJob> bt) {
             }
         }
     };
+    // Small form.  What a thread's Z loads depend on is fixed but for the core channel i and the chunk's first row: the slab row
+    // (row_z), the offset of (core channel j, column) inside core channel i's planes, the LDS address.  Row, column and core
+    // channel are clamped one by one (no select between two address expressions, no 64-bit multiply-add: both make the
+    // compiler wait for earlier loads).
+    const int nzu = BIG ? 0 : (ztotal + CR_NT - 1) / CR_NT;               // loads a thread needs (uniform)
+    int off_z[NZ], row_z[NZ], dst_z[NZ];
+    unsigned fix_z = 0;                // the loads that belong to the tile, whatever the chunk's rows
+    if constexpr (!BIG) {
+#pragma unroll
+        for (int u = 0; u < NZ; ++u) {
+            const int e = u * CR_NT + tid;
+            // e < 4096, slab <= 256: the rounded float quotient is exact, no integer division needed
+            const int jl = (int)(((float)e + 0.5f) * inv_slab), rem = e - __mul24(jl, pl.slab);
+            const int rr = (int)(((float)rem + 0.5f) * inv_wp), col = rem - __mul24(rr, pl.wp) - g.pw, j = j0 + jl;
+            fix_z |= ((e < ztotal) & (j < g.r2) & (col >= 0) & (col < g.W)) ? (1u << u) : 0u;
+            off_z[u] = min(j, g.r2 - 1) * g.H * g.W + min(max(col, 0), g.W - 1);
+            row_z[u] = rr;
+            dst_z[u] = e < ztotal ? e + jl * (pl.zld - pl.slab) : -1;
+        }
+    }
+    const int k_a = tid & (CR_KC - 1);
+    int off_a[NA];
+#pragma unroll
+    for (int u = 0; u < (BIG ? 0 : NA); ++u) {
+        const int o = o0 + tid / CR_KC + (CR_NT / CR_KC) * u;
+        off_a[u] = (o < g.cout ? o : o0) * HoWo;
+    }
     auto fetch = [&](int ch) __attribute__((always_inline)) {
         const int i = ch / pl.nyc, yc = ch - i * pl.nyc;
         const int y0 = yc * pl.ry;
         const int rows = (g.Ho - y0 < pl.ry) ? g.Ho - y0 : pl.ry;
         const int kcv = rows * g.Wo;
-        // Z slab first.  Row, column and core channel are clamped one by one (no select between two
-        // address expressions, no 64-bit multiply-add: both make the compiler wait for earlier loads).
         const int ylo = y0 * g.sh - g.ph;
-        const int zbase = i * g.r2;
+        const float* __restrict__ Zi = Z + (unsigned)(i * g.r2) * (unsigned)(g.H * g.W);       // uniform
         zmask = 0;
 #pragma unroll
         for (int u = 0; u < NZ; ++u) {
-            const int e = u * CR_NT + tid;
-            // e < 8192, slab <= 512: the rounded float quotient is exact, no integer division needed
-            const int jl = (int)(((float)e + 0.5f) * inv_slab), rem = e - __mul24(jl, pl.slab);
-            const int rr = (int)(((float)rem + 0.5f) * inv_wp), cc = rem - __mul24(rr, pl.wp);
-            const int row = ylo + rr, col = cc - g.pw, j = j0 + jl;
-            const bool ok = (e < ztotal) & (j < g.r2) & (row >= 0) & (row < g.H) & (col >= 0) & (col < g.W);
-            const int jc = min(j, g.r2 - 1), rowc = min(max(row, 0), g.H - 1), colc = min(max(col, 0), g.W - 1);
-            z_t[u] = Z[__mul24(__mul24(zbase + jc, g.H) + rowc, g.W) + colc];
-            zmask |= ok ? (1u << u) : 0u;
+            if (u < nzu) {             // uniform
+                const int row = ylo + row_z[u], rowc = min(max(row, 0), g.H - 1);
+                z_t[u] = Zi[(unsigned)(off_z[u] + __mul24(rowc, g.W))];
+                zmask |= row == rowc ? (1u << u) : 0u;
+            }
         }
+        zmask &= fix_z;
         // G1 tile: lane k of a wave walks the positions, the rows (channels) are CR_NT / CR_KC apart
-        const int k = tid & (CR_KC - 1);
-        const bool kin = k < kcv;
-        const int abase = __mul24(i, g.cout) * HoWo + y0 * g.Wo + (kin ? k : 0);
+        const bool kin = k_a < kcv;
+        const float* __restrict__ Gi = G1 + ((unsigned)(i * g.cout) * (unsigned)HoWo + (unsigned)(y0 * g.Wo));     // uniform
         amask = 0;
 #pragma unroll
         for (int u = 0; u < NA; ++u) {
-            const int o = o0 + tid / CR_KC + (CR_NT / CR_KC) * u;
-            const bool oin = o < g.cout;
-            a_t[u] = G1[abase + __mul24(oin ? o : o0, HoWo)];
-            amask |= (kin & oin) ? (1u << u) : 0u;
+            a_t[u] = Gi[(unsigned)(off_a[u] + (kin ? k_a : 0))];
+            amask |= (kin & (o0 + tid / CR_KC + (CR_NT / CR_KC) * u < g.cout)) ? (1u << u) : 0u;
         }
+    };
+    auto store = [&](float* buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < NA; ++u)
+            buf[k_a * (CR_TO + 1) + tid / CR_KC + (CR_NT / CR_KC) * u] = ((amask >> u) & 1u) ? a_t[u] : 0.f;
+        float* zb = buf + CR_KC * (CR_TO + 1);
+#pragma unroll
+        for (int u = 0; u < NZ; ++u)
+            if (u < nzu && dst_z[u] >= 0) zb[dst_z[u]] = ((zmask >> u) & 1u) ? z_t[u] : 0.f;
     };
     // korg[k]: offset of the window origin of output position k inside a slab, (k / Wo) * sh * wp + (k % Wo) * sw
     // (0 for positions beyond the rows of a chunk; their A values are zero).  The same for every chunk.
-    int* korg = reinterpret_cast<int*>(lds_raw + (BIG ? 2 * BUF : CR_KC * (CR_TO + 1) + CR_ZMAX));
+    int* korg = reinterpret_cast<int*>(lds_raw + 2 * BUF);
     for (int k = tid; k < CR_KC; k += CR_NT) {
         const int yl = (int)(((float)k + 0.5f) * inv_wo), x = k - yl * g.Wo;     // k < 2^14: exact
         korg[k] = (yl < pl.ry) ? yl * row_step + x * g.sw : 0;
@@ -485,21 +526,23 @@ __global__ __launch_bounds__(CR_NT) void k_corr_mfma(Batch<CorrJob> bt) {
             __syncthreads();
         }
     } else {
-        if (ch_beg < ch_end) fetch(ch_beg);
+        // two buffers here, too: one barrier per chunk, and the loads of a chunk have the products of the one before to arrive
+        // (one buffer, and the slab's index arithmetic done anew for every load and chunk: 30.0 us for 960 x 40 x 9 over
+        // 24 x 7 x 7, 27.7 so)
+        if (ch_beg < ch_end) {
+            fetch(ch_beg);
+            store(lds_raw);
+        }
+        if (ch_beg + 1 < ch_end) fetch(ch_beg + 1);
+        __syncthreads();
+#pragma unroll 1
         for (int ch = ch_beg; ch < ch_end; ++ch) {
-            __syncthreads();                               // previous chunk consumed
-#pragma unroll
-            for (int u = 0; u < NA; ++u)
-                As[tid & (CR_KC - 1)][tid / CR_KC + (CR_NT / CR_KC) * u] = ((amask >> u) & 1u) ? a_t[u] : 0.f;
-#pragma unroll
-            for (int u = 0; u < NZ; ++u) {
-                const int e = u * CR_NT + tid;
-                const int jl = (int)(((float)e + 0.5f) * inv_slab);
-                if (e < ztotal) Zs[e + jl * (pl.zld - pl.slab)] = ((zmask >> u) & 1u) ? z_t[u] : 0.f;
-            }
+            const int cur = (ch - ch_beg) & 1;
+            const float* bcur = lds_raw + cur * BUF;
+            if (ch + 1 < ch_end) store(lds_raw + (cur ^ 1) * BUF);
+            if (ch + 2 < ch_end) fetch(ch + 2);
+            multiply(chunk_positions(ch), bcur, bcur + CR_KC * (CR_TO + 1));
             __syncthreads();
-            if (ch + 1 < ch_end) fetch(ch + 1);            // in flight while this chunk is multiplied
-            multiply(chunk_positions(ch), lds_raw, Zs);
         }
     }
     // lane holds o = o0 + 16 (OB wo + ob) + 4*lg + v, j = j0 + ll
@@ -592,9 +635,9 @@ __global__ __launch_bounds__(256) void k_corr(Batch<CorrJob> bt) {
     Tpart[(long long)bsplit * total + e] = acc;
 }
 
-int corr_splits(const CorrGeom& g) {
+int corr_splits(const CorrGeom& g, int layers) {
     CorrPlan pl;
-    if (corr_plan(g, &pl)) return pl.nsplit;
+    if (corr_plan(g, layers, &pl)) return pl.nsplit;
     const long long total = (long long)g.cout * g.r2 * g.kh * g.kw;
     const long long blocks = (total + 255) / 256;
     long long want = (2048 + blocks - 1) / blocks;
@@ -604,22 +647,23 @@ int corr_splits(const CorrGeom& g) {
     return (g.r1 + ips - 1) / ips;
 }
 
-// key: low nibble 0 = k_corr_mfma<1,true,0>, 1 = <9,true,0>, 2 = <9,false,0>, 3 = <25,false,0>; high nibble = BIGV of <9,true,BIGV> (large chunks);
+// key: low nibble 0 = k_corr_mfma<1,true,V>, 1 = <9,true,V>, 2 = <9,false,V>, 3 = <25,false,V>; high nibble = V (BIGV);
 // the fallback kernel has kind IT_CORR
-bool make_corr(const float* G1, const float* Z, float* Tpart, const CorrGeom& g, int nsplit, Item* out) {
+bool make_corr(const float* G1, const float* Z, float* Tpart, const CorrGeom& g, int nsplit, int layers, Item* out) {
     const long long total = (long long)g.cout * g.r2 * g.kh * g.kw;
     if (total <= 0 || nsplit <= 0 || !G1 || !Z || !Tpart) return false;
     CorrJob jb;
     std::memset(&jb, 0, sizeof(jb));
     jb.G1 = G1; jb.Z = Z; jb.Tpart = Tpart; jb.g = g;
     *out = Item();
-    if (corr_plan(g, &jb.pl)) {
+    if (corr_plan(g, layers, &jb.pl)) {
         if (nsplit != jb.pl.nsplit) return false;
         jb.gx = (g.cout + CR_TO - 1) / CR_TO; jb.gy = (g.r2 + 15) / 16; jb.gz = jb.pl.nsplit;
         const int taps = g.kh * g.kw;
         out->kind = IT_CORR_MFMA;
-        // large chunks: instantiation by slab rows (4 or 6) and lanes per slab row (64 or 128)
-        const int bigv = jb.pl.kc == CR_KC_BIG ? (jb.pl.rows_in == 4 ? 1 : 3) + (jb.pl.wp <= 64 ? 0 : 1) : 0;
+        // large chunks: instantiation by slab rows (4 or 6) and lanes per slab row (64 or 128); small ones: by the slab's length
+        const int bigv = jb.pl.kc == CR_KC_BIG ? (jb.pl.rows_in == 4 ? 1 : 3) + (jb.pl.wp <= 64 ? 0 : 1)
+                                               : (jb.pl.zld * 16 <= CR_ZMAX_SHORT ? 5 : 0);
         out->key = (taps == 1 ? 0u : (taps == 9 ? 1u : (taps < 9 ? 2u : 3u))) | ((unsigned)bigv << 4);
         std::snprintf(out->label, sizeof(out->label), "k_corr_mfma<%d, %s, %d>", taps == 1 ? 1 : (taps <= 9 ? 9 : 25),
                       (taps == 1 || taps == 9) ? "true" : "false", bigv);
@@ -649,8 +693,9 @@ hipError_t launch_corr_items(const Item* const* items, int n, hipStream_t st) {
     // which has to be allowed once per kernel (the flags are only ever set, so a race between threads is harmless)
 #define ASI_CORR_LAUNCH(MAXT, EXACT, BIG)                                                                          \
     do {                                                                                                           \
-        constexpr size_t lds = sizeof(float) * (BIG ? corr_big_lds_floats()                                        \
-                                                    : corr_lds_floats<MAXT>(CR_KC_SMALL, CR_ZMAX_SMALL));          \
+        constexpr int ZMAX = BIG == 5 ? CR_ZMAX_SHORT : CR_ZMAX_SMALL;                                             \
+        constexpr size_t lds = sizeof(float) * (BIG >= 1 && BIG <= 4 ? corr_big_lds_floats()                                        \
+                                                    : corr_lds_floats<MAXT>(CR_KC_SMALL, ZMAX));                   \
         if (lds > 65536) {                                                                                         \
             static std::atomic<bool> allowed{false};                                                               \
             if (!allowed.load()) {                                                                                 \
@@ -667,6 +712,10 @@ hipError_t launch_corr_items(const Item* const* items, int n, hipStream_t st) {
         case 1: ASI_CORR_LAUNCH(9, true, 0); break;
         case 2: ASI_CORR_LAUNCH(9, false, 0); break;
         case 3: ASI_CORR_LAUNCH(25, false, 0); break;
+        case 0x50: ASI_CORR_LAUNCH(1, true, 5); break;
+        case 0x51: ASI_CORR_LAUNCH(9, true, 5); break;
+        case 0x52: ASI_CORR_LAUNCH(9, false, 5); break;
+        case 0x53: ASI_CORR_LAUNCH(25, false, 5); break;
         case 0x11: ASI_CORR_LAUNCH(9, true, 1); break;
         case 0x21: ASI_CORR_LAUNCH(9, true, 2); break;
         case 0x31: ASI_CORR_LAUNCH(9, true, 3); break;

@@ -314,8 +314,9 @@ bool make_init_ctrl(int32_t* info, Item* out);   // *info = 0
 struct CorrGeom {
     int r1, r2, cout, H, W, Ho, Wo, kh, kw, sh, sw, ph, pw, dh, dw;
 };
-int corr_splits(const CorrGeom& g);
-bool make_corr(const float* G1, const float* Z, float* Tpart, const CorrGeom& g, int nsplit, Item* out);
+// layers: how many layers of a batch share the launch (1 gives the most splits)
+int corr_splits(const CorrGeom& g, int layers);
+bool make_corr(const float* G1, const float* Z, float* Tpart, const CorrGeom& g, int nsplit, int layers, Item* out);
 
 // ---- step 5 of Eq. 14 with groups: dW[o,c,t] (+)= sum_j T[o,j,t] * U2[(o/og)*cg + c, j] -----------------------
 struct ExpandJob {

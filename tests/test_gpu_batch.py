@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 import torch
 
-from asi_inputs import CONFIGS, LayerStream
+from asi_inputs import CONFIGS, Layer, LayerStream
 from paper_2505_05086_amd.runner import BatchRunner, LayerRunner
 
 pytestmark = pytest.mark.gpu
@@ -14,8 +14,11 @@ pytestmark = pytest.mark.gpu
 
 def _run_pair(cfg_index, layer_ids, steps=2):
     cfg = CONFIGS[cfg_index]
-    layers = [cfg.layers[i] for i in layer_ids]
-    streams = [LayerStream(cfg.index, i, cfg.layers[i], cfg.theta) for i in layer_ids]
+    _run_layers(cfg_index, layer_ids, [cfg.layers[i] for i in layer_ids],
+                [LayerStream(cfg.index, i, cfg.layers[i], cfg.theta) for i in layer_ids], steps)
+
+
+def _run_layers(cfg_index, layer_ids, layers, streams, steps):
     singles = [LayerRunner(lay) for lay in layers]
     batch = BatchRunner(layers)
     for r, b, st in zip(singles, batch.runs, streams):
@@ -47,6 +50,14 @@ def test_batch_equals_single_config3_mixed_shapes_and_groups():
 
 def test_batch_equals_single_config5_linear_bf16():
     _run_pair(5, list(range(len(CONFIGS[5].layers))), steps=1)
+
+
+@pytest.mark.parametrize("hw,k,r1,cout", [((7, 8), 3, 5, 130), ((8, 8), 3, 7, 130), ((7, 7), 5, 3, 64), ((14, 13), 3, 5, 70), ((7, 7), 1, 4, 33)])
+def test_batch_of_equal_layers_shares_the_correlation(hw, k, r1, cout):
+    """Three equal layers: the correlation's K is split into fewer parts than for one (the single layer's is the reference that
+    the parity tests hold against the oracle); slabs of Z one step below and above the short form's, a partial last split."""
+    lay = Layer("share", (9, 40, *hw), (r1, 18, 5, 5), "f32", "conv2d", cout, k=k, pad=(k - 1) // 2, alpha=0.7, noise=1e-2)
+    _run_layers(9, [21, 22, 23], [lay] * 3, [LayerStream(9, 21 + i, lay) for i in range(3)], 1)
 
 
 def test_batch_of_one_and_repeated_layer():
