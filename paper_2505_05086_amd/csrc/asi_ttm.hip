@@ -442,34 +442,48 @@ __global__ __launch_bounds__(256) void k_ttm_thin(Batch<TtmJob> bt) {
             }
 }
 
-// ---- a short last mode expanded to many outputs, on the vector ALU ------------------------------
+// ---- a short last mode expanded to many outputs ------------------------------------------------
 // Y[c, q] (+)= sum_k X[c, k] M(k, q) with at most 32 terms and 256 or more outputs per column: the last
 // step of the linear weight gradient (dW = T U_3^T: rank 20, thousands of features).  The output is the
-// only large tensor, so the kernel is built around its stores: a workgroup owns 32 columns x 256 outputs,
-// lane l holds the four consecutive outputs 4 l .. 4 l + 3 of eight columns, and every store instruction of
-// a wave writes 1 KB of one output row.  M's tile sits in LDS as Ms[k][q] (one 16-byte read per term), X's
-// tile as Xs[c][k] (every lane of a wave reads the same word).
-constexpr int EX_C = 32, EX_Q = 256, EX_K = 32;
+// only large tensor, so the kernel is built around its stores: a workgroup owns 256 outputs and walks `tile_cols` columns in
+// passes of 32; M's tile is staged once, the next pass's X tile is requested before the products of this one.  Products run
+// on the fp32 MFMA, rows = outputs (a lane then holds four consecutive ones), a wave 64 outputs x 32 columns; the tile goes
+// through LDS so that a store instruction writes 1 KB of one output row.  On the vector ALU (a thread per four outputs of
+// eight columns) every multiply-add needed its share of nine LDS reads per term: 22.8 -> 19.5 us for 5632 x 2048 outputs of
+// rank 20 (46 MB written).
+constexpr int EX_C = 32, EX_Q = 256, EX_K = 32, EX_YP = EX_Q + 4;
 __global__ __launch_bounds__(256) void k_ttm_expand(Batch<TtmJob> bt) {
-    __shared__ __align__(16) float Ms[EX_K][EX_Q + 4];
+    constexpr int MP = EX_Q + 16;                    // pitch 16 mod 32: the two row groups of a half wave lie on other banks
+    __shared__ __align__(16) float ex_tile[EX_K * MP];       // M's tile, then the result tile of a pass
     __shared__ float Xs[EX_C][EX_K + 1];
+    static_assert(EX_C * EX_YP <= EX_K * MP, "the result tile takes the place of M's");
+    float (*Ms)[MP] = reinterpret_cast<float (*)[MP]>(ex_tile);
+    float (*Ys)[EX_YP] = reinterpret_cast<float (*)[EX_YP]>(ex_tile);
     int lb;
     const TtmJob& jb = bt.job[locate(bt, &lb)];
     const float* __restrict__ X = static_cast<const float*>(jb.X);
     const float* __restrict__ Mp = jb.Mp;
     float* __restrict__ Y = jb.Y;
     const long long ncols = jb.outer, ms_i = jb.ms_i, ms_q = jb.ms_q;
-    const int n = jb.n, r = jb.r, beta = jb.beta;
+    const int n = jb.n, r = jb.r, beta = jb.beta, n4 = (n + 3) & ~3;
     const int bx = lb / jb.gy, by = lb - bx * jb.gy;
-    const long long c0 = (long long)bx * EX_C;
+    const long long c0 = (long long)bx * jb.tile_cols;
     const int q0 = by * EX_Q;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lg = lane >> 4, ll = lane & 15;
     if (jb.zero && lb == 0 && tid < jb.nzero) jb.zero[tid] = 0;
     // tiles: consecutive threads along the index that is contiguous in memory; every load of the workgroup is
     // issued before the first is stored (clamped addresses, masks at the store: nothing waits in between)
     const bool k_fast = ms_i == 1;
     const float inv_n = 1.0f / (float)n;             // e < 2^13: the rounded float quotients are exact
     float mt[EX_K], xt[EX_C * EX_K / 256];
+    auto x_load = [&](long long cb) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < EX_C * EX_K / 256; ++u) {
+            const int e = tid + 256 * u;
+            const int c = (int)(((float)e + 0.5f) * inv_n);
+            xt[u] = X[e < EX_C * n && cb + c < ncols ? cb * n + e : 0LL];
+        }
+    };
 #pragma unroll
     for (int u = 0; u < EX_K; ++u) {
         const int e = tid + 256 * u;
@@ -478,13 +492,9 @@ __global__ __launch_bounds__(256) void k_ttm_expand(Batch<TtmJob> bt) {
         const bool ok = e < EX_Q * n && q0 + q < r;
         mt[u] = Mp[ok ? (long long)k * ms_i + (long long)(q0 + q) * ms_q : 0LL];
     }
-#pragma unroll
-    for (int u = 0; u < EX_C * EX_K / 256; ++u) {
-        const int e = tid + 256 * u;
-        const int c = (int)(((float)e + 0.5f) * inv_n), k = e - c * n;
-        const bool ok = e < EX_C * n && c0 + c < ncols;
-        xt[u] = X[ok ? (c0 + c) * n + k : 0LL];
-    }
+    x_load(c0);
+    for (int e = tid; e < (n4 - n) * EX_Q; e += 256) Ms[n + (e >> 8)][e & 255] = 0.f;        // terms up to a multiple of four
+    for (int e = tid; e < (n4 - n) * EX_C; e += 256) Xs[e & 31][n + (e >> 5)] = 0.f;
 #pragma unroll
     for (int u = 0; u < EX_K; ++u) {
         const int e = tid + 256 * u;
@@ -492,35 +502,56 @@ __global__ __launch_bounds__(256) void k_ttm_expand(Batch<TtmJob> bt) {
         const int k = k_fast ? e - eq * n : u, q = k_fast ? eq : tid;
         if (e < EX_Q * n) Ms[k][q] = (q0 + q < r) ? mt[u] : 0.f;
     }
-#pragma unroll
-    for (int u = 0; u < EX_C * EX_K / 256; ++u) {
-        const int e = tid + 256 * u;
-        const int c = (int)(((float)e + 0.5f) * inv_n), k = e - c * n;
-        if (e < EX_C * n) Xs[c][k] = (c0 + c < ncols) ? xt[u] : 0.f;
-    }
     __syncthreads();
-    v4f acc[8];
+    float a[EX_K / 4][4];                            // the wave's A operands: 64 outputs, all terms
 #pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j] = (v4f){0.f, 0.f, 0.f, 0.f};
-    for (int k = 0; k < n; ++k) {
-        const v4f m = *reinterpret_cast<const v4f*>(&Ms[k][4 * lane]);
+    for (int ks = 0; ks < EX_K / 4; ++ks)
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const float x = Xs[8 * wave + j][k];
-            acc[j][0] = fmaf(x, m[0], acc[j][0]); acc[j][1] = fmaf(x, m[1], acc[j][1]);
-            acc[j][2] = fmaf(x, m[2], acc[j][2]); acc[j][3] = fmaf(x, m[3], acc[j][3]);
+        for (int t = 0; t < 4; ++t) a[ks][t] = 4 * ks < n4 ? Ms[4 * ks + lg][64 * wave + 16 * t + ll] : 0.f;
+    const int np = jb.tile_cols / EX_C;
+    for (int p = 0; p < np; ++p) {
+        const long long cb = c0 + p * EX_C;
+        if (cb >= ncols) break;
+#pragma unroll
+        for (int u = 0; u < EX_C * EX_K / 256; ++u) {
+            const int e = tid + 256 * u;
+            const int c = (int)(((float)e + 0.5f) * inv_n), k = e - c * n;
+            if (e < EX_C * n) Xs[c][k] = (cb + c < ncols) ? xt[u] : 0.f;
         }
-    }
-    const int q = q0 + 4 * lane;
-    if (q < r) {                                      // r is a multiple of four (host check): a piece is whole
+        __syncthreads();                             // (also: M's tile and the last pass's result tile have been read)
+        if (p + 1 < np) x_load(cb + EX_C);
+        v4f acc[4][2];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const long long c = c0 + 8 * wave + j;
-            if (c < ncols) {
-                v4f* yp = reinterpret_cast<v4f*>(Y + c * r + q);
-                v4f out = acc[j];
-                if (beta) out += *yp;
-                *yp = out;
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) acc[t][h] = (v4f){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < EX_K / 4; ++ks)
+            if (4 * ks < n4) {
+                float b[2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) b[h] = Xs[16 * h + ll][4 * ks + lg];
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) acc[t][h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[ks][t], b[h], acc[t][h], 0, 0, 0);
+            }
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) *reinterpret_cast<v4f*>(&Ys[16 * h + ll][64 * wave + 16 * t + 4 * lg]) = acc[t][h];
+        __syncthreads();
+        const int q = q0 + 4 * lane;
+        if (q < r) {                                 // r is a multiple of four (host check): a piece is whole
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const long long c = cb + 8 * wave + j;
+                if (c < ncols) {
+                    v4f* yp = reinterpret_cast<v4f*>(Y + c * r + q);
+                    v4f out = *reinterpret_cast<const v4f*>(&Ys[8 * wave + j][4 * lane]);
+                    if (beta) out += *yp;
+                    *yp = out;
+                }
             }
         }
     }
@@ -558,7 +589,10 @@ static bool fill_ttm(DType xt, const void* X, long long outer, int n, long long 
     const char* tn = xt == F32 ? "float" : "asi::bf16_t";
     *out = Item();
     if (!kron && ttm_expand_supported(xt, inner, n, r, Y)) {
-        const long long gx = (ncols + EX_C - 1) / EX_C;
+        // two passes per workgroup once that still leaves two workgroups per CU: M's tile is then staged half as often
+        const long long tiles = (ncols + EX_C - 1) / EX_C * ((r + EX_Q - 1) / EX_Q);
+        jb.tile_cols = tiles >= 1024 ? 2 * EX_C : EX_C;
+        const long long gx = (ncols + jb.tile_cols - 1) / jb.tile_cols;
         jb.gx = (int)gx; jb.gy = (r + EX_Q - 1) / EX_Q;
         if (gx * jb.gy > 0x3fffffffLL) return false;
         out->kind = IT_TTM_EXPAND; out->key = 0;

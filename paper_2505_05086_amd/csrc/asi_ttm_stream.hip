@@ -288,6 +288,176 @@ __global__ __launch_bounds__(256, NBR <= 2 ? 4 : 2) void k_ttm_stream_short(Batc
     }
 }
 
+// bf16 tensors along a mode of 128 or more entries: the same span, loads and epilogue on the bf16 MFMA.
+// A lane loads, per K step of 32 rows, the eight rows 32 S + 8 lg .. + 7 of its four columns (8 bytes each) and
+// turns them with byte permutes into the A operands of a 16x16x32 MFMA for the four column blocks {4 l + v}.  The
+// matrix is cut into three bf16 terms when it is staged (top 8 significant bits, the next 8, the rest: every fp32 value is
+// their exact sum, and a product with a bf16 value is exact in fp32), so that nothing is lost against the fp32 MFMA:
+// 3 x 16 cycles per 16 x 16 x 32 block instead of 8 x 32.  LDS holds the r rows of a term only (a lane beyond r reads row
+// r - 1, its outputs are dropped), Ms[term][q][i], pitch KP + 8 (16-byte reads of 16 rows then meet every bank once).
+// KW of the 8 waves share a span; a wave has two K steps in flight, i.e. its whole share of a mode of up to 512.
+// The fp32 form needed 10 us of MFMA time for the (8, 512, 5632) grad_out of a language model's widest layer, after its
+// loads and before the next ones: 28.6 -> 14.5 us (46 MB read).
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+constexpr int TSB_NT = 512, TSB_MIN_N = 128;
+
+template <int NBR, int KW>
+__global__ __launch_bounds__(TSB_NT, NBR <= 2 ? 4 : 2) void k_ttm_stream_bf16(Batch<TtmJob> bt) {
+    constexpr int SPANS = 8 / KW, QP = 16 * NBR, HK = KW / 2;
+    int lb;
+    const TtmJob& jb = bt.job[locate_xcd(bt, &lb)];
+    const bf16_t* __restrict__ X = static_cast<const bf16_t*>(jb.X);
+    const float* __restrict__ Mp = jb.Mp;
+    float* __restrict__ Y = jb.Y;
+    const unsigned inner = (unsigned)jb.inner, ncols = (unsigned)(jb.outer * jb.inner);   // below 2^31 (host check)
+    const int n = jb.n, r = jb.r, beta = jb.beta;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lg = lane >> 4, ll = lane & 15;
+    const int span = wave / KW, kp = wave % KW;
+    if (jb.zero && lb == 0 && tid < jb.nzero) jb.zero[tid] = 0;
+
+    const int NR = (n + 31) >> 5, MP = 32 * NR + 8;      // K steps; pitch of a matrix row
+    unsigned short* Ms = reinterpret_cast<unsigned short*>(ts_dyn);
+    const unsigned cs = ((unsigned)lb * SPANS + span) * 64u, c = cs + 4u * ll;
+    const unsigned cc = c < ncols ? c : 0u;              // past the end: the first piece (valid), dropped at the store
+    const unsigned o = cc / inner, j = cc - o * inner;
+    const bf16_t* __restrict__ xp = X + ((size_t)o * n * inner + j);
+
+    // A staging task: four rows of M times four outputs; two tasks per thread are requested before X.
+    const long long ms_i = jb.ms_i;
+    const int r4 = r >> 2, ntask = 8 * NR * r4;
+    constexpr int MU = 2;
+    v4f mreg[MU][4];
+    auto m_load = [&](int e0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < MU; ++u) {
+            const int e = e0 + tid + TSB_NT * u, i4 = e / r4, q = 4 * (e - i4 * r4);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int i = 4 * i4 + t;
+                mreg[u][t] = *reinterpret_cast<const v4f*>(Mp + (i < n ? i * ms_i + q : 0LL));
+            }
+        }
+    };
+    auto m_store = [&](int e0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < MU; ++u) {
+            const int e = e0 + tid + TSB_NT * u, i4 = e / r4, q = 4 * (e - i4 * r4);
+            if (e < ntask) {
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    unsigned w[3][4];                    // the terms' bits, in the upper half of the word
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const float x = 4 * i4 + t < n ? mreg[u][t][s] : 0.f;
+                        w[0][t] = __float_as_uint(x) & 0xffff0000u;
+                        const float x1 = x - __uint_as_float(w[0][t]);
+                        w[1][t] = __float_as_uint(x1) & 0xffff0000u;
+                        w[2][t] = __float_as_uint(x1 - __uint_as_float(w[1][t]));
+                    }
+#pragma unroll
+                    for (int p = 0; p < 3; ++p) {
+                        const uint2 out = {__builtin_amdgcn_perm(w[p][1], w[p][0], 0x07060302u),
+                                           __builtin_amdgcn_perm(w[p][3], w[p][2], 0x07060302u)};
+                        *reinterpret_cast<uint2*>(Ms + (p * r + q + s) * MP + 4 * i4) = out;
+                    }
+                }
+            }
+        }
+    };
+    m_load(0);
+
+    uint2 x[2][8];
+    auto fetch = [&](int S0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            if (S0 + KW * u < NR) {
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {            // a row past n is read as row n - 1 and meets zeros
+                    const int i = 32 * (S0 + KW * u) + 8 * lg + t;
+                    x[u][t] = *reinterpret_cast<const uint2*>(xp + (unsigned)(i < n ? i : n - 1) * inner);
+                }
+            }
+    };
+    fetch(kp);
+
+    m_store(0);
+    for (int e0 = TSB_NT * MU; e0 < ntask; e0 += TSB_NT * MU) {
+        m_load(e0);
+        m_store(e0);
+    }
+    __syncthreads();
+
+    v4f acc[4][NBR];
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int nb = 0; nb < NBR; ++nb) acc[v][nb] = (v4f){0.f, 0.f, 0.f, 0.f};
+    for (int S0 = kp; S0 < NR; S0 += 2 * KW) {
+        if (S0 != kp) fetch(S0);
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            if (S0 + KW * u < NR) {
+                v8bf b[3][NBR];
+#pragma unroll
+                for (int nb = 0; nb < NBR; ++nb) {
+                    const int q = 16 * nb + ll < r ? 16 * nb + ll : r - 1;
+#pragma unroll
+                    for (int p = 0; p < 3; ++p)
+                        b[p][nb] = *reinterpret_cast<const v8bf*>(Ms + (p * r + q) * MP + 32 * (S0 + KW * u) + 8 * lg);
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    v4u w;
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const unsigned lo = v < 2 ? x[u][2 * t].x : x[u][2 * t].y, hi = v < 2 ? x[u][2 * t + 1].x : x[u][2 * t + 1].y;
+                        w[t] = __builtin_amdgcn_perm(hi, lo, (v & 1) ? 0x07060302u : 0x05040100u);
+                    }
+                    const v8bf a = __builtin_bit_cast(v8bf, w);
+#pragma unroll
+                    for (int p = 2; p >= 0; --p)
+#pragma unroll
+                        for (int nb = 0; nb < NBR; ++nb)
+                            acc[v][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[p][nb], acc[v][nb], 0, 0, 0);
+                }
+            }
+    }
+
+    // the tiles meet in LDS as in k_ttm_stream, in two steps: the upper half of a span's waves hands its tiles to the lower
+    float* red = ts_dyn;                                 // [4][QP][TS_RP]
+    float* mine = red + (size_t)((span * HK + kp % HK) * QP) * TS_RP;
+    __syncthreads();                                     // every wave has read its last matrix operand
+#pragma unroll
+    for (int half = 1; half >= 0; --half) {
+        if (kp / HK == half) {
+#pragma unroll
+            for (int nb = 0; nb < NBR; ++nb)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    v4f* tp = reinterpret_cast<v4f*>(mine + (16 * nb + ll) * TS_RP + 16 * lg + 4 * e);
+                    v4f out = {acc[0][nb][e], acc[1][nb][e], acc[2][nb][e], acc[3][nb][e]};
+                    if (half == 0) out += *tp;           // the same lane of the wave HK further on wrote it
+                    *tp = out;
+                }
+        }
+        __syncthreads();
+    }
+    const int pc = tid & 15, sp = (tid >> 4) % SPANS, q0 = tid / (16 * SPANS);
+    const unsigned ce = ((unsigned)lb * SPANS + sp) * 64u + 4u * pc;
+    if (ce < ncols) {
+        const unsigned oe = ce / inner, je = ce - oe * inner;
+        for (int q = q0; q < r; q += TSB_NT / 16 / SPANS) {
+            v4f out = *reinterpret_cast<const v4f*>(red + ((sp * HK * QP + q) * TS_RP + 4 * pc));
+#pragma unroll
+            for (int k = 1; k < HK; ++k) out += *reinterpret_cast<const v4f*>(red + (((sp * HK + k) * QP + q) * TS_RP + 4 * pc));
+            v4f* yp = reinterpret_cast<v4f*>(Y + (((size_t)oe * r + q) * inner + je));
+            if (beta) out += *yp;
+            *yp = out;
+        }
+    }
+}
+
 // ---- host side -----------------------------------------------------------------------------------
 static size_t stream_lds(int n, int nbr, int kw) {
     const size_t ms = sizeof(float) * (size_t)(16 * nbr) * (size_t)(16 * ((n + 15) / 16) + 4);
@@ -295,6 +465,16 @@ static size_t stream_lds(int n, int nbr, int kw) {
     (void)kw;
     return ms > rd ? ms : rd;
 }
+
+static size_t stream_bf16_lds(int n, int r) {
+    const size_t ms = sizeof(unsigned short) * 3u * (size_t)r * (size_t)(32 * ((n + 31) / 32) + 8);
+    const size_t rd = sizeof(float) * 4u * (size_t)(16 * ((r + 15) / 16)) * TS_RP;
+    return ms > rd ? ms : rd;
+}
+// The bf16 form stages three terms per workgroup of 8 waves: below 128 entries the fp32 form's matrix time is short
+// against its loads (64 entries and 32 outputs over 151296 columns run at 2.6 TB/s), and beyond 80 KB of LDS a CU would hold
+// one workgroup.
+static bool stream_bf16_ok(DType xt, int n, int r) { return xt == BF16 && n >= TSB_MIN_N && stream_bf16_lds(n, r) <= 80 * 1024; }
 
 // waves per span: the fewest that still give every CU two workgroups, and every wave a round
 static int stream_kw(long long ncols, int n) {
@@ -314,7 +494,7 @@ bool ttm_stream_supported(DType xt, const void* X, long long outer, int n, long 
     return stream_lds(n, nbr, 4) <= TS_LDS_MAX;
 }
 
-// key: [0] bf16, [4..6] NBR - 1, [8..10] KW, [12] k_ttm_stream_short
+// key: [0] bf16, [4..6] NBR - 1, [8..11] KW, [12] k_ttm_stream_short, [13] k_ttm_stream_bf16
 bool make_ttm_stream(DType xt, const void* X, long long outer, int n, long long inner, const float* Mp, long long ms_i,
                      long long ms_q, int r, float* Y, int beta, Item* out) {
     if (!X || !Mp || !Y || !ttm_stream_supported(xt, X, outer, n, inner, Mp, ms_i, ms_q, r, Y)) return false;
@@ -323,15 +503,17 @@ bool make_ttm_stream(DType xt, const void* X, long long outer, int n, long long 
     jb.X = X; jb.outer = outer; jb.inner = inner; jb.Mp = Mp; jb.ms_i = ms_i; jb.ms_q = ms_q; jb.Y = Y;
     jb.n = n; jb.r = r; jb.beta = beta;
     const long long ncols = outer * inner;
-    const int nbr = (r + 15) / 16, kw = stream_kw(ncols, n);
-    const long long wcols = 64LL * (4 / kw);
+    const bool wide = stream_bf16_ok(xt, n, r);          // modes of up to 256: four waves per span have two K steps each
+    const int nbr = (r + 15) / 16, kw = wide ? (n <= 256 ? 4 : 8) : stream_kw(ncols, n);
+    const long long wcols = 64LL * ((wide ? 8 : 4) / kw);
     jb.gx = (int)((ncols + wcols - 1) / wcols); jb.gy = 1;
     *out = Item();
     out->kind = IT_TTM_STREAM;
-    const bool shrt = kw == 1 && n > 16 && n <= 32 && ms_i < (1LL << 25);
-    out->key = (xt == BF16 ? 1u : 0u) | ((unsigned)(nbr - 1) << 4) | ((unsigned)kw << 8) | (shrt ? 1u << 12 : 0u);
+    const bool shrt = !wide && kw == 1 && n > 16 && n <= 32 && ms_i < (1LL << 25);
+    out->key = (xt == BF16 ? 1u : 0u) | ((unsigned)(nbr - 1) << 4) | ((unsigned)kw << 8) | (shrt ? 1u << 12 : 0u) | (wide ? 1u << 13 : 0u);
     out->nblocks = jb.gx;
-    if (shrt) std::snprintf(out->label, sizeof(out->label), "k_ttm_stream_short<%s, %d>", xt == F32 ? "float" : "asi::bf16_t", nbr);
+    if (wide) std::snprintf(out->label, sizeof(out->label), "k_ttm_stream_bf16<%d, %d>", nbr, kw);
+    else if (shrt) std::snprintf(out->label, sizeof(out->label), "k_ttm_stream_short<%s, %d>", xt == F32 ? "float" : "asi::bf16_t", nbr);
     else std::snprintf(out->label, sizeof(out->label), "k_ttm_stream<%s, %d, %d>", xt == F32 ? "float" : "asi::bf16_t", nbr, kw);
     static_assert(sizeof(TtmJob) <= kItemArgMax, "argument block");
     std::memcpy(out->arg, &jb, sizeof(jb));
@@ -378,12 +560,31 @@ static hipError_t launch_stream_t(int nbr, int kw, const Batch<TtmJob>& b, dim3 
     }
 }
 
+template <int NBR, int KW>
+static hipError_t launch_stream_bf16_one(const Batch<TtmJob>& b, dim3 grid, size_t lds, hipStream_t st) {
+    if (lds > 65536) {
+        static std::atomic<bool> allowed{false};
+        if (!allowed.load()) {
+            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_ttm_stream_bf16<NBR, KW>),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)TS_LDS_MAX);
+            if (e != hipSuccess) return e;
+            allowed.store(true);
+        }
+    }
+    hipLaunchKernelGGL((k_ttm_stream_bf16<NBR, KW>), grid, TSB_NT, lds, st, b);
+    return hipGetLastError();
+}
+template <int NBR>
+static hipError_t launch_stream_bf16(int kw, const Batch<TtmJob>& b, dim3 grid, size_t lds, hipStream_t st) {
+    return kw == 4 ? launch_stream_bf16_one<NBR, 4>(b, grid, lds, st) : launch_stream_bf16_one<NBR, 8>(b, grid, lds, st);
+}
+
 hipError_t launch_ttm_stream_items(const Item* const* items, int n, hipStream_t st) {
     Batch<TtmJob> b;
     dim3 grid;
     if (!gather(items, n, &b, &grid)) return hipErrorInvalidValue;
     const unsigned key = items[0]->key;
-    const int nbr = (int)((key >> 4) & 7u) + 1, kw = (int)((key >> 8) & 7u);
+    const int nbr = (int)((key >> 4) & 7u) + 1, kw = (int)((key >> 8) & 15u);
     if ((key >> 12) & 1u) {                             // the short form holds exactly two rounds of a mode
         for (int j = 0; j < n; ++j) {
             TtmJob tj;
@@ -392,6 +593,23 @@ hipError_t launch_ttm_stream_items(const Item* const* items, int n, hipStream_t 
         }
         if (key & 1u) return launch_stream_short_t<bf16_t>(nbr, b, grid, st);
         return launch_stream_short_t<float>(nbr, b, grid, st);
+    }
+    if ((key >> 13) & 1u) {
+        size_t lds = 0;
+        for (int j = 0; j < n; ++j) {
+            TtmJob tj;
+            std::memcpy(&tj, items[j]->arg, sizeof(tj));
+            if (tj.r > 16 * nbr) return hipErrorInvalidValue;
+            const size_t l = stream_bf16_lds(tj.n, tj.r);
+            lds = l > lds ? l : lds;
+        }
+        if (lds > TS_LDS_MAX) return hipErrorInvalidValue;
+        switch (nbr) {
+            case 1: return launch_stream_bf16<1>(kw, b, grid, lds, st);
+            case 2: return launch_stream_bf16<2>(kw, b, grid, lds, st);
+            case 3: return launch_stream_bf16<3>(kw, b, grid, lds, st);
+            default: return launch_stream_bf16<4>(kw, b, grid, lds, st);
+        }
     }
     size_t lds = 0;
     for (int j = 0; j < n; ++j) {                       // items of one launch share the instantiation; the largest matrix sizes the LDS

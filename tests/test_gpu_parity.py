@@ -263,6 +263,32 @@ def test_streaming_mode_product(case, dtype):
     assert any(w in s_ for s_ in sites for w in want), (want, [s_ for s_ in sites if "ttm" in s_])
 
 
+# bf16 tensors of 128 or more entries along a mode that is not the last: the streaming product on the bf16 MFMA, <NBR, KW>
+STREAM_BF16 = [
+    ((5, 133, 96), (5, 4, 24), 3380, "1, 4"),        # five K steps, the last of 5 rows; one block of four outputs; ragged last span
+    ((4, 256, 96), (4, 20, 24), 4108, "2, 4"),       # two full K steps per wave
+    ((3, 270, 96), (3, 36, 30), 5464, "3, 8"),       # nine K steps over eight waves, the last ragged; 256.1 spans of 64 columns
+    ((2, 600, 96), (2, 8, 12), 8200, "1, 8"),        # more than two K steps per wave
+]
+
+
+@pytest.mark.parametrize("case", STREAM_BF16)
+def test_streaming_mode_product_bf16(case):
+    from paper_2505_05086_amd import binding as B
+    dims, ranks, dout, variant = case
+    lay = Layer("stream", dims, ranks, "bf16", "linear", dout, alpha=0.5, noise=1e-2)
+    st = LayerStream(9, 5, lay)
+    run = _runner(lay)
+    A_t, A64, U_or = check_compress(run, lay, st.activation(0), st.u_prev0(), TOL["bf16"], f"stream {case}")
+    B.asi_profile_enable(True)
+    try:
+        check_core_and_dw(run, lay, A_t, A64, U_or, st.grad_out(0), TOL["bf16"], f"stream {case}")
+        sites = list(B.asi_profile_report())
+    finally:
+        B.asi_profile_enable(False)
+    assert any("k_ttm_stream_bf16<%s>" % variant in s_ for s_ in sites), [s_ for s_ in sites if "ttm" in s_]
+
+
 EDGE_LINEAR = [((3, 5, 7), (2, 3, 4), 6), ((4, 9, 30), (4, 9, 30), 3), ((2, 33, 130), (1, 7, 20), 70),
                ((64, 1, 5), (3, 1, 2), 1), ((6, 50, 300), (3, 34, 100), 40),     # a rank above 64
                ((3, 20, 600), (2, 8, 24), 50),                                   # a last mode of 512 or more
@@ -289,6 +315,27 @@ def test_edge_linear_shapes(case, dtype):
     tol = TOL[dtype]
     A_t, A64, U_or = check_compress(run, lay, st.activation(0), st.u_prev0(), tol, f"edge {case}")
     check_core_and_dw(run, lay, A_t, A64, U_or, st.grad_out(0), tol, f"edge {case}")
+
+
+# 1024 or more tiles of 32 x 256 outputs: a workgroup of the expansion kernel walks two column blocks (the last one ragged or
+# missing); ranks that fill no, part of and all of the last group of four terms
+@pytest.mark.parametrize("cout,feat,r3", [(8207, 1028, 7), (8225, 1024, 32), (2061, 260, 1)])
+def test_expansion_kernel_passes(cout, feat, r3):
+    dims, ranks = (3, 20, feat), (3, 12, r3)
+    lay = Layer("edge", dims, ranks, "f32", "linear", cout, alpha=0.5, noise=1e-2)
+    st = LayerStream(9, 4, lay)
+    run = _runner(lay)
+    A_t, A64, U_or = check_compress(run, lay, st.activation(0), st.u_prev0(), TOL["f32"], "expand")
+    check_core_and_dw(run, lay, A_t, A64, U_or, st.grad_out(0), TOL["f32"], "expand")
+
+
+# the wide orthogonalisation at its edges: one column past the short path, ranks that fill blocks of 16 and do not, a last
+# slice of a few rows, one slice only
+@pytest.mark.parametrize("n,r", [(200, 65), (129, 96), (400, 177), (192, 192)])
+def test_wide_orthogonalisation_edges(n, r):
+    lay = Layer("edge", (14, 15, n), (14, 15, r), "f32", "linear", 20, alpha=0.1, noise=1e-2)
+    st = LayerStream(9, 6, lay)
+    check_compress(_runner(lay), lay, st.activation(0), st.u_prev0(), TOL["f32"], f"wide {n} {r}")
 
 
 def test_full_rank_batch_mode_and_the_expansion_kernel_are_taken():
