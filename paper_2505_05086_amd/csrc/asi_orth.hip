@@ -844,64 +844,73 @@ __global__ __launch_bounds__(OP_NT) void k_orth_apply(OrthBatch a) {
 constexpr int OW_RMAX = 192;
 constexpr int OW_LD = OW_RMAX + 1;
 constexpr int OW_ROWS = 64;             // rows per gramw block
-constexpr int OW_MAXPAIR = 20;          // block pairs per wave: ceil(78 / 4)
+constexpr int OW_PARTS = 4;             // workgroups (blockIdx.y) that share the block pairs of a slice
+constexpr int OW_MAXPAIR = 5;           // block pairs per wave: ceil(78 / (4 OW_PARTS))
 
+// 64-row slices of a 3072-row mode are 48 workgroups with 78 block pairs each: 20 us of matrix time per wave behind three rounds
+// of loads.  The pairs of a slice are dealt to four workgroups instead, each of which reads the whole slice (100 KB, from
+// L2) with every load of 32 rows in flight; there are no more partial matrices to add than before.  36 -> 11 us.
 __global__ __launch_bounds__(256) void k_orthw_gram(OrthBatch a) {
     __shared__ double Ps[OP_RS][OW_LD];
     int ji, blk;
     find_job(a, &ji, &blk);
-    const OrthJob jb = a.job[ji];
+    const OrthJob& jb = a.job[ji];
     const int n = jb.n, r = jb.r, tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6, lg = lane >> 4, ll = lane & 15;
     const int nb = (r + 15) / 16, npairs = nb * (nb + 1) / 2;
+    const int first = blockIdx.y + OW_PARTS * wave;         // this wave's pairs: first + 4 OW_PARTS s
+    const double* __restrict__ P64 = jb.P64;
+    int ab[OW_MAXPAIR], bb[OW_MAXPAIR];
+#pragma unroll
+    for (int s = 0; s < OW_MAXPAIR; ++s) {
+        const int pr = first + 4 * OW_PARTS * s;
+        int i = 0, rem = pr < npairs ? pr : 0;
+        while (rem >= nb - i) { rem -= nb - i; ++i; }
+        ab[s] = i; bb[s] = i + rem;
+    }
     v4d acc[OW_MAXPAIR];
 #pragma unroll
     for (int s = 0; s < OW_MAXPAIR; ++s) acc[s] = (v4d){0.0, 0.0, 0.0, 0.0};
-    for (int e = tid; e < OP_RS * OW_LD; e += 256) (&Ps[0][0])[e] = 0.0;
+    const float inv_rf = 1.0f / (float)r;
+    for (int e = tid; e < OP_RS * (16 * nb - r); e += 256) Ps[e & (OP_RS - 1)][r + e / OP_RS] = 0.0;
     const int row_beg = blk * OW_ROWS;
     const int row_end = (row_beg + OW_ROWS < n) ? row_beg + OW_ROWS : n;
     for (int i0 = row_beg; i0 < row_end; i0 += OP_RS) {
         const int nrows = (row_end - i0 < OP_RS) ? row_end - i0 : OP_RS;
+        double t[OP_RS * OW_RMAX / 256];
+#pragma unroll
+        for (int u = 0; u < OP_RS * OW_RMAX / 256; ++u) {
+            const int idx = u * 256 + tid;
+            t[u] = P64[(long long)i0 * r + (idx < nrows * r ? idx : 0)];
+        }
         __syncthreads();
-        for (int idx0 = 0; idx0 < OP_RS * r; idx0 += 256 * 8) {
-            double t[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int idx = idx0 + u * 256 + tid;
-                t[u] = ldg_f64(jb.P64, (long long)i0 * r + idx, idx < nrows * r);
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int idx = idx0 + u * 256 + tid;
-                if (idx < OP_RS * r) Ps[idx / r][idx % r] = t[u];      // rows past nrows become zero
-            }
+        for (int u = 0; u < OP_RS * OW_RMAX / 256; ++u) {
+            const int idx = u * 256 + tid, row = small_div(idx, inv_rf);
+            if (idx < OP_RS * r) Ps[row][idx - row * r] = idx < nrows * r ? t[u] : 0.0;      // rows past nrows become zero
         }
         __syncthreads();
 #pragma unroll
         for (int s = 0; s < OW_MAXPAIR; ++s) {
-            const int pr = wave + 4 * s;
-            if (pr < npairs) {
-                int ab = 0, rem = pr;
-                while (rem >= nb - ab) { rem -= nb - ab; ++ab; }
-                const int bb = ab + rem;
+            if (first + 4 * OW_PARTS * s < npairs) {
+                double av[OP_RS / 4], bv[OP_RS / 4];
 #pragma unroll
-                for (int ks = 0; ks < OP_RS / 4; ++ks)
-                    acc[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(Ps[4 * ks + lg][16 * ab + ll], Ps[4 * ks + lg][16 * bb + ll],
-                                                                  acc[s], 0, 0, 0);
+                for (int ks = 0; ks < OP_RS / 4; ++ks) {
+                    av[ks] = Ps[4 * ks + lg][16 * ab[s] + ll];
+                    bv[ks] = Ps[4 * ks + lg][16 * bb[s] + ll];
+                }
+#pragma unroll
+                for (int ks = 0; ks < OP_RS / 4; ++ks) acc[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[ks], bv[ks], acc[s], 0, 0, 0);
             }
         }
     }
     double* Gout = jb.Gpart + (long long)blk * r * r;
 #pragma unroll
     for (int s = 0; s < OW_MAXPAIR; ++s) {
-        const int pr = wave + 4 * s;
-        if (pr < npairs) {
-            int ab = 0, rem = pr;
-            while (rem >= nb - ab) { rem -= nb - ab; ++ab; }
-            const int bb = ab + rem;
+        if (first + 4 * OW_PARTS * s < npairs) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int ga = 16 * ab + lg + 4 * v, gb = 16 * bb + ll;
+                const int ga = 16 * ab[s] + lg + 4 * v, gb = 16 * bb[s] + ll;
                 if (ga < r && gb < r && ga <= gb) Gout[ga * r + gb] = acc[s][v];
             }
         }
@@ -1079,9 +1088,9 @@ __global__ __launch_bounds__(OWC_NT) void k_orthw_chol(OrthBatch a, int pass, in
     // went through scratch memory and every LDS access in it became a flat access.
     for (int attempt = 0;; ++attempt) {
         int bad = 0;
+        if (wave == 0) chol_block16(G, Xs, pinvs, 0, &bad);
+        __syncthreads();
         for (int P = 0; P < nb; ++P) {
-            if (wave == 0) chol_block16(G, Xs, pinvs, 16 * P, &bad);
-            __syncthreads();
             if (tid < 16 && 16 * P + tid < r) {
                 const double p = G.ld(16 * P + tid, 16 * P + tid);          // the pivot actually used
                 if (!(p > 1e-12 * rdiag[16 * P + tid])) s_lost = 1;
@@ -1112,40 +1121,62 @@ __global__ __launch_bounds__(OWC_NT) void k_orthw_chol(OrthBatch a, int pass, in
                     roff[ks] = k * r - (k * (k + 1)) / 2;
                     pv[ks] = pinvs[k];
                 }
-                int cnt = 0;
-                for (int I = P + 1; I < nb; ++I)
-                    for (int J = I; J < nb; ++J, ++cnt) {
-                        if ((cnt & (OWC_NW - 1)) != wave) continue;
+                // Wave 0 takes the next diagonal block and factors it at once (nothing it reads is still being written, and the
+                // inverse Xs of this panel has been used); the other waves share the remaining pairs, three at a
+                // time, so that the reads of one run under the products of another.  192 wide: 113 -> 102 us.
+                const int m = nb - P - 1, npairs = m * (m + 1) / 2;
+                constexpr int NP = 3;
+                for (int c0 = wave; c0 < npairs; c0 += NP * (OWC_NW - 1)) {
+                    double av[NP][4], bv[NP][4], cv[NP][4];
+                    int cidx[NP][4];
+                    bool cin[NP][4], iin[NP], jin[NP];
+#pragma unroll
+                    for (int t = 0; t < NP; ++t) {
+                        const int c = c0 + t * (OWC_NW - 1);
+                        const bool have = c < npairs && (t == 0 || wave != 0);
+                        int I = 0, rem = have ? c : 0;
+                        while (rem >= m - I) { rem -= m - I; ++I; }
+                        const int J = P + 1 + I + rem;
+                        I += P + 1;
                         const int ci = 16 * I + ll, cj = 16 * J + ll;
-                        const bool iin = ci < r, jin = cj < r;
-                        double av[4], bv[4], cv[4];
-                        int cidx[4];
-                        bool cin[4];
+                        iin[t] = ci < r; jin[t] = cj < r;
 #pragma unroll
                         for (int ks = 0; ks < 4; ++ks) {
                             const int k = 16 * P + 4 * ks + lg;
-                            av[ks] = Gp[roff[ks] + (iin ? ci : k)];
-                            bv[ks] = Gp[roff[ks] + (jin ? cj : k)];
+                            av[t][ks] = Gp[roff[ks] + (iin[t] ? ci : k)];
+                            bv[t][ks] = Gp[roff[ks] + (jin[t] ? cj : k)];
                         }
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
                             const int rw = 16 * I + lg + 4 * v;
-                            cin[v] = rw <= cj && jin;
-                            cidx[v] = cin[v] ? rw * r - (rw * (rw + 1)) / 2 + cj : 0;
-                            cv[v] = Gp[cidx[v]];
+                            cin[t][v] = have && rw <= cj && jin[t];
+                            cidx[t][v] = cin[t][v] ? rw * r - (rw * (rw + 1)) / 2 + cj : 0;
+                            cv[t][v] = Gp[cidx[t][v]];
                         }
+                    }
 #pragma unroll
-                        for (int ks = 0; ks < 4; ++ks) asm volatile("" : "+v"(av[ks]), "+v"(bv[ks]), "+v"(cv[ks]));
-                        v4d acc;
+                    for (int t = 0; t < NP; ++t)
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) acc[v] = cin[v] ? cv[v] : 0.0;
+                        for (int ks = 0; ks < 4; ++ks) asm volatile("" : "+v"(av[t][ks]), "+v"(bv[t][ks]), "+v"(cv[t][ks]));
+                    v4d acc[NP];
 #pragma unroll
-                        for (int ks = 0; ks < 4; ++ks)
-                            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(iin ? -av[ks] : 0.0, jin ? bv[ks] * pv[ks] : 0.0, acc, 0, 0, 0);
+                    for (int t = 0; t < NP; ++t)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) acc[t][v] = cin[t][v] ? cv[t][v] : 0.0;
+#pragma unroll
+                    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                        for (int t = 0; t < NP; ++t)
+                            acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(iin[t] ? -av[t][ks] : 0.0, jin[t] ? bv[t][ks] * pv[ks] : 0.0,
+                                                                          acc[t], 0, 0, 0);
+#pragma unroll
+                    for (int t = 0; t < NP; ++t)
 #pragma unroll
                         for (int v = 0; v < 4; ++v)
-                            if (cin[v]) Gp[cidx[v]] = acc[v];
-                    }
+                            if (cin[t][v]) Gp[cidx[t][v]] = acc[t][v];
+                    if (wave == 0) break;
+                }
+                if (wave == 0) chol_block16(G, Xs, pinvs, 16 * (P + 1), &bad);
                 __syncthreads();
             }
         }
@@ -1223,51 +1254,62 @@ __global__ __launch_bounds__(128) void k_orthw_apply(OrthBatch a, int final_pass
     const int nb = (r + 15) / 16;
     const int i0 = blk * OP_RS;
     const int nrows = (n - i0 < OP_RS) ? n - i0 : OP_RS;
-    for (int idx0 = 0; idx0 < OP_RS * OW_LD; idx0 += 128) {
-        const int e = idx0 + tid;
-        if (e < OP_RS * OW_LD) (&Ps[0][0])[e] = 0.0;
-    }
-    __syncthreads();
-    for (int idx0 = 0; idx0 < nrows * r; idx0 += 128 * 8) {
-        double t[8];
+    const float inv_rf = 1.0f / (float)r;
+    {                                                 // the slice, every load of it in flight; zero beyond its rows and columns
+        double t[OP_RS * OW_RMAX / 128];
+        const double* __restrict__ src = jb.P64 + (long long)i0 * r;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int idx = idx0 + u * 128 + tid;
-            t[u] = ldg_f64(jb.P64, (long long)i0 * r + idx, idx < nrows * r);
+        for (int u = 0; u < OP_RS * OW_RMAX / 128; ++u) {
+            const int idx = u * 128 + tid;
+            t[u] = src[idx < nrows * r ? idx : 0];
         }
+        for (int e = tid; e < OP_RS * (16 * nb - r); e += 128) Ps[e & (OP_RS - 1)][r + e / OP_RS] = 0.0;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int idx = idx0 + u * 128 + tid;
-            if (idx < nrows * r) Ps[idx / r][idx % r] = t[u];
+        for (int u = 0; u < OP_RS * OW_RMAX / 128; ++u) {
+            const int idx = u * 128 + tid, row = small_div(idx, inv_rf);
+            if (idx < OP_RS * r) Ps[row][idx - row * r] = idx < nrows * r ? t[u] : 0.0;
         }
     }
     __syncthreads();
     const int rw = 16 * wave;
     const double* __restrict__ R = jb.R;
+    const double* __restrict__ Di = jb.Dinv;
+    // A block column of R needs all block columns of Q before it, and its loads nothing: the operands of column b + 1 (up to
+    // 44 + 4 per lane) travel while column b is multiplied.  Loaded four block rows at a time just before their
+    // products, twelve columns were 30 dependent round trips to L2: 42 us for 3072 x 192, 29 so (with the slice in one round).
+    constexpr int NB = OW_RMAX / 16;
+    double rv[NB - 1][4], dv[4], rn[NB - 1][4], dn[4];
+    auto r_load = [&](int b) __attribute__((always_inline)) {
+        const int cb = 16 * b + ll < r ? 16 * b + ll : 0;           // a column past r: masked below
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) dn[ks] = Di[(b * 16 + 4 * ks + lg) * 16 + ll];
+#pragma unroll
+        for (int u = 0; u < NB - 1; ++u)
+            if (u < b) {
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks) rn[u][ks] = R[(long long)(16 * u + 4 * ks + lg) * r + cb];
+            }
+    };
+    r_load(0);
     for (int b = 0; b < nb; ++b) {
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) dv[ks] = dn[ks];
+#pragma unroll
+        for (int u = 0; u < NB - 1; ++u)
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) rv[u][ks] = rn[u][ks];
+        if (b + 1 < nb) r_load(b + 1);
         v4d acc = {0.0, 0.0, 0.0, 0.0};
-        const int cb = 16 * b + ll;
-        double dv[4];                                   // B operands of R_bb^-1
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) dv[ks] = jb.Dinv[(b * 16 + 4 * ks + lg) * 16 + ll];
-        for (int ab0 = 0; ab0 < b; ab0 += 4) {          // 16 global loads in flight
-            double rv[4][4];
+        for (int u = 0; u < NB - 1; ++u)
+            if (u < b) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
+                for (int ks = 0; ks < 4; ++ks)
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(Ps[rw + ll][16 * u + 4 * ks + lg], rv[u][ks], acc, 0, 0, 0);
+            }
+        const bool in = 16 * b + ll < r;
 #pragma unroll
-                for (int ks = 0; ks < 4; ++ks) {
-                    const int row = 16 * (ab0 + u) + 4 * ks + lg;
-                    rv[u][ks] = ldg_f64(R, (long long)row * r + cb, ab0 + u < b && cb < r);
-                }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (ab0 + u < b)
-#pragma unroll
-                    for (int ks = 0; ks < 4; ++ks)
-                        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(Ps[rw + ll][16 * (ab0 + u) + 4 * ks + lg], rv[u][ks], acc, 0, 0, 0);
-        }
-#pragma unroll
-        for (int v = 0; v < 4; ++v) Ps[rw + lg + 4 * v][16 * b + ll] -= acc[v];
+        for (int v = 0; v < 4; ++v) Ps[rw + lg + 4 * v][16 * b + ll] -= in ? acc[v] : 0.0;
         __syncthreads();
         v4d q = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -1278,14 +1320,11 @@ __global__ __launch_bounds__(128) void k_orthw_apply(OrthBatch a, int final_pass
         for (int v = 0; v < 4; ++v) Ps[rw + lg + 4 * v][16 * b + ll] = q[v];
         __syncthreads();
     }
-    if (final_pass) {
-        for (int idx = tid; idx < nrows * r; idx += 128) jb.Uout[(long long)i0 * r + idx] = (float)Ps[idx / r][idx % r];
-    } else {
-        for (int idx = tid; idx < nrows * r; idx += 128) {
-            const double q0 = Ps[idx / r][idx % r];
-            jb.P64[(long long)i0 * r + idx] = q0;
-            jb.Uout[(long long)i0 * r + idx] = (float)q0;
-        }
+    for (int idx = tid; idx < nrows * r; idx += 128) {
+        const int row = small_div(idx, inv_rf);
+        const double q0 = Ps[row][idx - row * r];
+        if (!final_pass) jb.P64[(long long)i0 * r + idx] = q0;
+        jb.Uout[(long long)i0 * r + idx] = (float)q0;
     }
 }
 
@@ -1565,7 +1604,7 @@ hipError_t launch_orth_items(const Item* const* items, int n, hipStream_t st, ch
             else hipLaunchKernelGGL(k_orth_apply<64>, grid, OP_NT, 0, st, b);
             break;
         case IT_ORTHW_GRAM:
-            hipLaunchKernelGGL(k_orthw_gram, grid, 256, 0, st, b);
+            hipLaunchKernelGGL(k_orthw_gram, dim3(grid.x, OW_PARTS), 256, 0, st, b);
             break;
         case IT_ORTHW_CHOL: {
             // packed triangle, dinv, rdiag, pivot reciprocals, inverse block factor
