@@ -144,8 +144,11 @@ CompressPlan plan_compress(const Shape& s, void* ws, bool cold = false) {
             p.nsplit2[m] = (p.nsplit[m] + 31) / 32;
             p.part2[m] = c.take<double>((size_t)p.nsplit2[m] * n * r);
         }
-        p.P64[m] = c.take<double>(n * r);
         p.fast_orth[m] = orth_fast_supported((int)r);
+        // gram0 leaves the sum in the place of the first of the partial sums that it adds up: a workgroup has read all of its
+        // rows before it writes them, and no other reads those rows.  Pays for the Gram matrices of 16-row slices, so that no
+        // layer needs more scratch for them.
+        p.P64[m] = !p.fast_orth[m] ? c.take<double>(n * r) : p.part2[m] ? p.part2[m] : p.part[m];
         if (p.fast_orth[m]) {
             p.nblk[m] = orth_slices((int)n);
             p.Gpart[m] = c.take<double>((size_t)(orth_gram_slices((int)n) + orth_groups((int)n)) * r * (r + 1) / 2);

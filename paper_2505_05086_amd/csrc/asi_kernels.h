@@ -252,7 +252,7 @@ constexpr int kOrthGroups = 32;          // groups of slices of a mode, at most
 constexpr int kOrthCtrs = 2 + kOrthGroups;
 struct OrthJob {
     const double* part;  // (nsplit, n, r) partial sums of P
-    double* P64;         // (n, r) scratch
+    double* P64;         // (n, r) scratch; up to rank 64 it may be the first of the partial sums
     float* Uout;         // (n, r)
     int32_t* info;       // nullable
     // fast path (r <= 64) and wide path

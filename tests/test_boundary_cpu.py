@@ -53,6 +53,12 @@ def test_workspace_query():
     assert asi.asi_workspace_bytes(asi.make_desc((4, 20, 2100), (3, 8, 90)), None, 12) == 0
 
 
+def test_layers_that_just_fit_the_static_scratch():
+    # long modes of rank 64 in few columns: what grows with the 16-row Gram slices must not push them over the limit
+    for dims, ranks in (((3, 214, 3423), (1, 64, 64)), ((3, 299, 2618), (2, 64, 64)), ((6, 94, 3614), (1, 58, 64))):
+        assert 0 < asi.asi_workspace_bytes(asi.make_desc(dims, ranks)) <= B.STATIC_SCRATCH_BYTES, dims
+
+
 def _arr(n=4):
     a = (C.c_void_p * 4)()
     for i in range(n):
