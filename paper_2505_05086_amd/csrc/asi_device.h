@@ -39,12 +39,12 @@ __device__ __forceinline__ void copy16_to_lds(const void* src, int bytes, int of
 #endif
 }
 
-// Waits until at most N of this wave's copies (or other vector loads) are outstanding, then for the workgroup: a barrier that
-// leaves the newest copies on their way.  LDS reads before it must have been consumed, as they are when they feed products.
+// Waits until at most N of this wave's copies (or other vector loads) are outstanding and its LDS reads have returned, then for
+// the workgroup: a barrier that leaves the newest copies on their way, after which a buffer read before it may be overwritten.
 template <int N>
 __device__ __forceinline__ void wait_copies_and_sync() {
 #if defined(__HIP_DEVICE_COMPILE__)
-    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(N) : "memory");
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 #endif
 }
 
