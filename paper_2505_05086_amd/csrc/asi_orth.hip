@@ -302,9 +302,11 @@ __device__ __forceinline__ void chol_wave(double (*Gs)[OP_LD], double (*Xs)[16][
 
 // One workgroup: sums the slice Grams of a mode, adds the shift (first pass) and
 // factors the matrix, identity padded to a multiple of 16 (wave 0).  Writes R, the inverses of R's diagonal blocks and the
-// bookkeeping in scal; the first pass also inverts R and certifies itself where it can (see above); with `last` it reports a rank-deficient P through *info.  scal[0] = trace(P^T P), scal[1 + k] = running product of the
-// R diagonals, scal[65] = first bad pivot, scal[66] = 1 when the first pass needed no second (apply's
-// check), 2 when it is certified.
+// bookkeeping in scal; the first pass also inverts R and certifies itself where it can (see above); with `last` it reports a
+// rank-deficient P through *info.  The first pass never does: its launch clears *info, which the modes of a layer share, and
+// nothing orders one workgroup's report after another's clearing.  scal[0] = trace(P^T P), scal[1 + k] = running product of
+// the R diagonals, scal[65] = first bad pivot (certified: first column at the noise floor), scal[66] = 1 when the first
+// pass needed no second (apply's check), 2 when it is certified.
 struct CholSmem {
     double Gs[OP_RMAX][OP_LD];
     double dinv[OP_RMAX];
@@ -525,10 +527,13 @@ __device__ bool chol_job(const OrthJob& jb, int pass, int last, const double* sl
         // (16 products in a chain per slice, the slices of a group, the groups; then factor, inverse and product)
         const double bound = OP_EPS * ((18.0 + jb.gsz + nslices + 2.0 * r) * c * c + 4.0 * r * c);
         if (s_bad == 0 && bound <= OP_DONE_TOL) {            // (false for NaN)
-            if (tid == 0) jb.scal[66] = 2.0;
             if (tid < 64) {
+                // a column at the noise floor is left for apply to report: this launch is the one that clears *info
                 const unsigned long long mask = __ballot(tid < r && !(rdiag[tid] > 1e-12 * sqrt(s_trace)));
-                if (tid == 0 && info && mask) flag_info(info, jb.mode1, __ffsll((long long)mask));
+                if (tid == 0) {
+                    jb.scal[65] = mask ? (double)__ffsll((long long)mask) : 0.0;
+                    jb.scal[66] = 2.0;
+                }
             }
             return false;
         }
@@ -807,7 +812,9 @@ __global__ __launch_bounds__(OP_NT) void k_orth_apply(OrthBatch a) {
                     bv[I][v] = jb.Rinv[(J * (J + 1) / 2 + I) * 256 + 64 * v + lane];
                 }
             }
-        if (jb.scal[66] == 2.0) {
+        const double state = jb.scal[66], low = jb.scal[65];
+        if (state == 2.0) {
+            if (blk == 0 && threadIdx.x == 0 && low != 0.0) flag_info(jb.info, jb.mode1, (int)low);
             if (J >= nb) return;
             v4d q = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll

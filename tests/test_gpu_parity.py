@@ -684,3 +684,64 @@ def test_orthogonalisation_at_block_and_slice_edges(dims, ranks, ratio):
     repeated)."""
     lay = Layer("orth", dims, ranks, "f32", "linear", 12)
     _check_orthonormal_basis(lay, _graded_tensor(lay, ratio), 13, f"{dims} ratio {ratio}")
+
+
+def _orth_path(ws, A64, U_prev, m):
+    """Which path the orthogonalisation of mode m (rank up to 64) took in the compress call that last used the workspace:
+    2 = first pass certified from its factor, 1 = measured and found enough, 0 = second pass.  The bookkeeping is found by what
+    it holds: trace(P^T P), then the diagonal of R, the path at 66 doubles from the first."""
+    n, r = A64.shape[m], U_prev.shape[1]
+    Am = np.moveaxis(A64, m, 0).reshape(n, -1)
+    P = Am @ (Am.T @ U_prev)
+    diag = np.abs(np.diag(np.linalg.qr(P)[1]))
+    tr = np.sum(P * P)
+    w = ws[:ws.numel() // 8 * 8].cpu().numpy().view(F64)
+    k = min(r, 4)
+    hits = [i for i in np.flatnonzero(np.abs(w - tr) <= 1e-4 * tr) if i % 32 == 0 and i + 67 <= w.size
+            and np.all(np.abs(w[i + 1:i + 1 + k] - diag[:k]) <= 1e-2 * diag[:k])]
+    assert len(hits) == 1, (m, hits)
+    return int(w[hits[0] + 66])
+
+
+def _tensor_with_a_low_direction(rng, dims, m):
+    """Mode m: orthogonal directions of singular values 0.95^i, the last at 6e-7, so that P = A A^T U has orthogonal columns
+    (any factor of it is well conditioned column by column) of which the last keeps 3.6e-13 < 1e-12 ||P||."""
+    n, b = dims[m], int(np.prod(dims)) // dims[m]
+    s = 0.95 ** np.arange(n)
+    s[-1] = 6e-7
+    Q = np.linalg.qr(rng.standard_normal((b, n)))[0]
+    rest = [d for k, d in enumerate(dims) if k != m]
+    return np.ascontiguousarray(np.moveaxis((s[:, None] * Q.T).reshape([n] + rest), 0, m), dtype=np.float32)
+
+
+@pytest.mark.parametrize("mode", [0, 1, 2, 3])
+@pytest.mark.parametrize("batched", [False, True])
+def test_low_column_of_a_certified_factor_is_reported_past_the_other_modes(mode, batched):
+    """A mode whose first pass is certified AND has a column at the noise floor, beside three good modes that share its info
+    word; the word holds an old report when the call starts.  Batched: a good layer before and after it."""
+    from paper_2505_05086_amd import binding as B
+    rng = np.random.default_rng(40 + mode)
+    dims = (16, 24, 12, 10)
+    ranks = tuple(n if m == mode else n // 2 for m, n in enumerate(dims))
+    bad = _tensor_with_a_low_direction(rng, dims, mode)
+    good = rng.standard_normal(dims).astype(np.float32)
+    tensors = [good, bad, good] if batched else [bad]
+    desc = B.make_desc(dims, ranks, "f32")
+    A, U, out, ws, info = [], [], [], [], []
+    for x in tensors:
+        u = [np.linalg.svd(np.moveaxis(x.astype(F64), m, 0).reshape(n, -1), full_matrices=False)[0][:, :r] for m, (n, r) in enumerate(zip(dims, ranks))]
+        if x is bad:
+            u[mode] = np.eye(dims[mode])
+        U.append([_dev(v) for v in u])
+        A.append(torch.from_numpy(x).cuda())
+        out.append([torch.empty(n, r, device="cuda") for n, r in zip(dims, ranks)])
+        ws.append(torch.zeros_like(B.alloc_workspace(desc, None, 0)))
+        info.append(torch.full((1,), 7777, dtype=torch.int32, device="cuda"))
+    if batched:
+        B.asi_compress_batch([desc] * 3, A, U, out, ws, info)
+    else:
+        B.asi_compress(desc, A[0], U[0], out[0], ws[0], info[0])
+    torch.cuda.synchronize()
+    k = len(tensors) // 2
+    assert _orth_path(ws[k], bad.astype(F64), _np(U[k][mode]), mode) == 2
+    assert [int(i.item()) for i in info] == [((mode + 1) * 1000 + dims[mode]) if x is bad else 0 for x in tensors]
