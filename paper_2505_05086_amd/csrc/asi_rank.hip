@@ -166,11 +166,16 @@ __device__ __forceinline__ double wave_sum(double x) {
 // One launch per panel of 32 rows: workgroup (I, J) factors the 32 x 32 diagonal block (redundantly: 32 dependent steps,
 // 3 us, less than a launch of its own), solves the panel's blocks above I and J and updates the trailing block (I, J).
 constexpr int RK_CB = 32;
-struct CholScale { double scale, shift; };               // what the factorisation applied: W^T W = scale (G + shift / scale I)
+struct CholScale {
+    double scale, shift;                                 // what the factorisation applied: W^T W = scale (G + shift / scale I)
+    double bad;                                          // 0; G not finite: what every eigenvalue is returned as, NaN or Inf
+};
 
 __global__ __launch_bounds__(256) void k_chol_scale(const double* __restrict__ G, int n, double shift_factor, CholScale* out) {
     __shared__ double red[4];
+    __shared__ int s_nan;
     const int tid = threadIdx.x;
+    if (tid == 0) s_nan = 0;
     double s = 0.0;
 #pragma unroll
     for (int u = 0; u < RK_NMAX / 256; ++u) {
@@ -181,13 +186,20 @@ __global__ __launch_bounds__(256) void k_chol_scale(const double* __restrict__ G
     s = wave_sum(s);
     if ((tid & 63) == 0) red[tid >> 6] = s;
     __syncthreads();
+    const double tr = (red[0] + red[1]) + (red[2] + red[3]);
+    const bool finite = tr < INFINITY;                   // (the trace of squares: finite if every entry of G is)
+    if (!finite) {                                       // the same for all threads
+        for (int e = tid; e < n * n; e += 256)
+            if (isnan(G[e])) s_nan = 1;
+        __syncthreads();
+    }
     if (tid == 0) {
-        const double tr = (red[0] + red[1]) + (red[2] + red[3]);
         int e = 0;
         const bool ok = tr > 0.0 && tr < 1e300;          // (a zero tensor: the factor is sqrt(shift) I)
         if (ok) (void)frexp(tr, &e);
         out->scale = ldexp(1.0, -e);
         out->shift = ok ? shift_factor * ldexp(tr, -e) : 1.0;
+        out->bad = finite ? 0.0 : (s_nan ? NAN : INFINITY);
     }
 }
 
@@ -501,7 +513,8 @@ __global__ __launch_bounds__(256) void k_jacobi_block(double* __restrict__ W, in
 
 // After convergence row k of W is sqrt(lambda_k) v_k^T, lambda_k an eigenvalue of the scaled and shifted G.  Eigenvalues in descending order (ties by row index),
 // eigenvectors as the columns of an n x n row-major fp32 matrix; a column whose eigenvalue is below
-// 1e-12 of the largest (a null direction, whose row carries no direction any more) is returned as zeros.
+// 1e-12 of the largest (a null direction, whose row carries no direction any more) is returned as zeros.  A G that is not finite
+// has no spectrum: every eigenvalue is NaN (Inf if no entry of G is NaN), every column zeros.
 __global__ __launch_bounds__(64) void k_row_norms(const double* __restrict__ W, int n, double* __restrict__ norms, const CholScale* __restrict__ sc) {
     constexpr int NE = RK_NMAX / 64;
     const int k = blockIdx.x, lane = threadIdx.x;
@@ -512,7 +525,7 @@ __global__ __launch_bounds__(64) void k_row_norms(const double* __restrict__ W, 
 #pragma unroll
     for (int u = 0; u < NE; ++u) s += lane + 64 * u < n ? t[u] * t[u] : 0.0;
     s = wave_sum(s);
-    if (lane == 0) norms[k] = s > sc->shift ? (s - sc->shift) / sc->scale : 0.0;       // the eigenvalue of G itself
+    if (lane == 0) norms[k] = sc->bad != 0.0 ? sc->bad : s > sc->shift ? (s - sc->shift) / sc->scale : 0.0;   // the eigenvalue of G itself
 }
 // workgroup k places row k: its rank among the eigenvalues by counting, then its column of the eigenvector matrix
 __global__ __launch_bounds__(256) void k_spectrum_finish(const double* __restrict__ W, int n, const double* __restrict__ norms, const CholScale* __restrict__ sc,
@@ -538,11 +551,12 @@ __global__ __launch_bounds__(256) void k_spectrum_finish(const double* __restric
     __syncthreads();
     pos = s_pos[0] + s_pos[1] + s_pos[2] + s_pos[3];
     lmax = fmax(fmax(s_max[0], s_max[1]), fmax(s_max[2], s_max[3]));
+    if (sc->bad != 0.0) pos = k;                         // (nothing to order by)
     if (tid == 0) lam_out[pos] = l;
     if (!vec_out) return;
     const bool live = l > 1e-12 * lmax && l > 0.0;
     const double inv = live ? 1.0 / sqrt(l * sc->scale + sc->shift) : 0.0;       // the row's norm
-    for (int i = tid; i < n; i += 256) vec_out[(long long)i * n + pos] = (float)(W[(long long)k * n + i] * inv);
+    for (int i = tid; i < n; i += 256) vec_out[(long long)i * n + pos] = live ? (float)(W[(long long)k * n + i] * inv) : 0.f;
 }
 
 struct EpsList { double eps[16]; int count; };

@@ -230,3 +230,21 @@ def test_spectrum_of_a_full_sized_layer_sums_to_the_energy(dims):
         v = sp.eigenvectors.double()
         assert float((v.T @ v - torch.eye(v.shape[0], device="cuda", dtype=torch.float64)).abs().max().item()) <= 1e-5
         print(f"mode {m}: n = {A.shape[m]}, {sp.sweeps} sweeps, {ms:.1f} ms")
+
+
+@pytest.mark.parametrize("n", [12, 64, 65, 200])
+@pytest.mark.parametrize("what", ["nan", "inf", "inf beside zeros"])
+def test_spectrum_of_a_tensor_that_is_not_finite(n, what):
+    """No eigenvalue of a tensor that holds a NaN or an Inf may look like a number (0 did: rank 1 was enough for any threshold).
+    Inf among nonzero entries gives an infinite Gram matrix; Inf times 0 is NaN."""
+    B, RS = _mods()
+    A = np.random.default_rng(n).standard_normal((3, n, 40)).astype(np.float32) + 5.0
+    A[1, n // 2, 17] = np.nan if what == "nan" else np.inf
+    if what == "inf beside zeros":
+        A[1, 0, 17] = 0.0
+    sp = RS.mode_spectrum(torch.from_numpy(A).cuda(), 1)
+    lam = sp.eigenvalues.cpu().numpy()
+    assert np.all(np.isinf(lam) if what == "inf" else np.isnan(lam)), lam[:4]
+    assert not torch.any(sp.eigenvectors)
+    if what != "inf":
+        assert RS.explained_variance_ranks([sp], (0.5, 0.9)) == [(n,), (n,)]
