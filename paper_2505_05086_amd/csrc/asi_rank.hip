@@ -160,8 +160,12 @@ __device__ __forceinline__ double wave_sum(double x) {
 // G + s I = R^T R (R upper triangular); the iteration below runs on the rows of R, whose singular values are the square
 // roots of G's eigenvalues, and not on G itself: half the spread, and a factor is already half way to orthogonal rows
 // (18 sweeps become 12 on a 160-long mode whose spectrum falls over six decades and ends in noise; simulated for
-// several spectra before it was built).  The shift s = 4 n eps trace(G) keeps every pivot positive whatever G's rank
-// and is subtracted from the eigenvalues again, so it costs no accuracy beyond the rounding of G itself.  G is also
+// several spectra before it was built).  The shift s = (4 n + adds) u trace(G), u = 2^-53, keeps every pivot positive whatever
+// G's rank: adds is the longest chain of additions behind an entry of G (the products themselves are exact), so the rounding
+// of G is at most adds u sqrt(G_ii G_jj) an entry and adds u trace(G) in norm, and 4 n u trace(G) covers the
+// factorisation's own.  (With 4 n u trace(G) alone, pivots of constant samples went negative: an eigenvalue of 8 samples of
+// 1 M equal values each was off by 4.5e-12 of the trace, of 32 of 4 M by 2.3e-10; 5e-14 and 1.4e-13 so.)
+// It is subtracted from the eigenvalues again, so it costs no accuracy beyond the rounding of G itself.  G is also
 // scaled by a power of two (exact) so that its trace is near 1: the iteration squares squares.
 // One launch per panel of 32 rows: workgroup (I, J) factors the 32 x 32 diagonal block (redundantly: 32 dependent steps,
 // 3 us, less than a launch of its own), solves the panel's blocks above I and J and updates the trailing block (I, J).
@@ -737,7 +741,9 @@ asi_status asi_mode_spectrum(const asi_tensor_desc* desc, const void* A, int32_t
     else hipLaunchKernelGGL(k_mode_gram<float>, grid, 256, 0, st, jb);
     const long long cnt = (long long)n * n;
     hipLaunchKernelGGL(k_gram_reduce, dim3((unsigned)((cnt + 255) / 256)), 256, 0, st, part, p.nsplit, cnt, G, rot, RK_SWEEPS);
-    hipLaunchKernelGGL(k_chol_scale, dim3(1), 256, 0, st, G, n, 4.0 * n * 1.1102230246251565e-16, sc);
+    // additions behind an entry of G: the columns of a range (64 a chunk), then the ranges
+    const double adds = (double)RK_T * ((p.nchunks + p.nsplit - 1) / p.nsplit) + p.nsplit;
+    hipLaunchKernelGGL(k_chol_scale, dim3(1), 256, 0, st, G, n, (4.0 * n + adds) * 1.1102230246251565e-16, sc);
     for (int P = 0, nb = (n + RK_CB - 1) / RK_CB; P < nb; ++P) {
         const int rest = nb - P - 1;
         hipLaunchKernelGGL(k_chol_panel, dim3((unsigned)(rest > 0 ? rest * (rest + 1) / 2 : 1)), 256, 0, st, G, W, n, P, sc);

@@ -232,6 +232,27 @@ def test_spectrum_of_a_full_sized_layer_sums_to_the_energy(dims):
         print(f"mode {m}: n = {A.shape[m]}, {sp.sweeps} sweeps, {ms:.1f} ms")
 
 
+@pytest.mark.parametrize("n,hw", [(4, 1024), (8, 1024), (32, 512)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_spectrum_of_constant_samples(n, hw, dtype):
+    """A batch of samples that each hold one value: rank one, and every column of the unfolding rounds the sums of the Gram
+    matrix the same way, so its rounding is as far from definite as it gets (adds u trace, adds = the additions behind an entry).
+    Sums of 64 ceil(chunks / ranges) columns and of the ranges, u = 2^-53, and 4 n for the factor: eigenvalues to that bound."""
+    B, RS = _mods()
+    for seed in range(12):
+        a = torch.from_numpy(np.random.default_rng(seed).standard_normal(n).astype(np.float32)).cuda()
+        At = a.to(torch.bfloat16 if dtype == "bf16" else torch.float32)[:, None, None].expand(n, hw, hw).contiguous()
+        a64 = At[:, 0, 0].double().cpu().numpy()
+        sp = RS.mode_spectrum(At, 0)
+        lam = sp.eigenvalues.cpu().numpy()
+        trace = hw * hw * np.sum(a64 * a64)
+        bound = (64 * -(-(hw * hw // 64) // 256) + 256 + 4 * n) * 2.0 ** -53 * trace
+        assert abs(lam[0] - trace) <= bound and np.all(lam[1:] <= bound) and np.all(lam[1:] >= 0), (seed, lam[:3] / trace)
+        v = sp.eigenvectors[:, 0].double().cpu().numpy()
+        assert abs(abs(v @ a64) - np.linalg.norm(a64)) <= 1e-6 * np.linalg.norm(a64)
+        assert RS.explained_variance_ranks([sp], (0.9, 0.999)) == [(1,), (1,)]
+
+
 @pytest.mark.parametrize("n", [12, 64, 65, 200])
 @pytest.mark.parametrize("what", ["nan", "inf", "inf beside zeros"])
 def test_spectrum_of_a_tensor_that_is_not_finite(n, what):
