@@ -301,8 +301,8 @@ struct ConvPlan {
     size_t bytes = 0;
 };
 
-// layers: how many layers of a batch share the launches; the workspace is that of one alone, which has the most splits
-ConvPlan plan_conv(const Shape& s, const ConvGeom& cg, void* ws, int layers = 1) {
+// (the splits of a layer alone, which are the most: a batch may take fewer, see build_conv_grad)
+ConvPlan plan_conv(const Shape& s, const ConvGeom& cg, void* ws) {
     ConvPlan p;
     const CorrGeom& g = cg.g;
     Carver c(ws);
@@ -311,15 +311,13 @@ ConvPlan plan_conv(const Shape& s, const ConvGeom& cg, void* ws, int layers = 1)
     if ((long long)s.r[2] * s.r[3] > kKronMaxN || (long long)g.H * g.W > kKronMaxOut)
         p.Z1 = c.take<float>((size_t)g.r1 * g.r2 * g.H * s.r[3]);      // else Z comes from one merged pass
     p.Z = c.take<float>((size_t)g.r1 * g.r2 * g.H * g.W);
-    p.nsplit = corr_splits(g, 1);
+    CorrGroup alone;
+    alone.n = 1; alone.g[0] = &g;
+    p.nsplit = corr_splits(alone, 0);
     const size_t tsz = (size_t)g.cout * g.r2 * g.kh * g.kw;
     p.T = c.take<float>(tsz);
     p.Tpart = p.nsplit > 1 ? c.take<float>(tsz * p.nsplit) : p.T;
     p.bytes = c.off;
-    if (layers > 1) {
-        p.nsplit = corr_splits(g, layers);
-        if (p.nsplit == 1) p.Tpart = p.T;
-    }
     return p;
 }
 
@@ -718,22 +716,31 @@ asi_status build_core(const asi_tensor_desc* desc, const void* A, const float* c
     return ASI_OK;
 }
 
-asi_status build_conv(const asi_tensor_desc* desc, const float* S, const float* const* U, const void* grad_out,
-                      const asi_conv2d_desc* conv, float* dW, int accumulate, void* ws, size_t ws_bytes, int layers, Program& pg) {
+// A convolution's launches in two parts, because how far the correlation (step 4) is split depends on the layers it shares a
+// launch with, i.e. on where the first parts of the others' programs end.
+struct ConvBuild {
+    ConvGeom cg;
+    ConvPlan p;
+    const float* G1 = nullptr;       // what the correlation reads: p.G1 or grad_out itself
+};
+
+// validation and steps 1 to 3
+asi_status build_conv_maps(const asi_tensor_desc* desc, const float* S, const float* const* U, const void* grad_out,
+                           const asi_conv2d_desc* conv, const float* dW, void* ws, size_t ws_bytes, ConvBuild* cb, Program& pg) {
     Shape s;
     asi_status why;
     if (!parse_desc(desc, &s, &why)) return why;
     if (s.d != 4 || !conv) return ASI_ERR_INVALID_ARG;
-    ConvGeom cg;
+    ConvGeom& cg = cb->cg;
     if (!parse_conv(s, conv, &cg)) return ASI_ERR_INVALID_ARG;
     if (!S || !U || !grad_out || !dW) return ASI_ERR_INVALID_ARG;
     for (int m = 0; m < 4; ++m)
         if (!U[m]) return ASI_ERR_INVALID_ARG;
-    ConvPlan p = plan_conv(s, cg, ws, layers);
+    cb->p = plan_conv(s, cg, ws);
+    const ConvPlan& p = cb->p;
     if (!ws_ok(ws, ws_bytes, p.bytes)) return ASI_ERR_WORKSPACE;
     const CorrGeom& g = cg.g;
     const int r3 = s.r[2], r4 = s.r[3];
-    const int taps = g.kh * g.kw;
 
     // With r1 = B the batch factor is square: G1 would be as large as grad_out, and forming it saves the
     // correlation nothing.  The same sum with the parentheses moved expands the small core instead,
@@ -741,12 +748,12 @@ asi_status build_conv(const asi_tensor_desc* desc, const float* S, const float* 
     // and the correlation reads grad_out itself (fp32 data, aligned for its 16-byte loads).
     const bool expand_core = p.S1 && s.dt == F32 && reinterpret_cast<uintptr_t>(grad_out) % 16 == 0;
     const float* Sz = S;
-    const float* G1 = p.G1;
+    cb->G1 = p.G1;
     if (expand_core) {
         // 1'. S1[b,...] = sum_i U1[b,i] S[i,...]
         ASI_TRYS(add_ttm(pg, "S1", F32, S, 1, g.r1, (long long)g.r2 * r3 * r4, U[0], 1, g.r1, cg.B, p.S1, 0));
         Sz = p.S1;
-        G1 = static_cast<const float*>(grad_out);
+        cb->G1 = static_cast<const float*>(grad_out);
     } else {
         // 1. G1 = grad_out x_1 U1^T                                   (r1, cout, Ho, Wo)
         // (where Z comes from one merged product it can share G1's launch: G1 then stays on the tiled kernel)
@@ -776,10 +783,23 @@ asi_status build_conv(const asi_tensor_desc* desc, const float* S, const float* 
         // 3. Z = Z1 x_4 U4                                        (r1, r2, H, W)
         ASI_TRYS(add_ttm(pg, "Z", F32, p.Z1, (long long)g.r1 * g.r2 * g.H, r4, 1, U[3], 1, r4, g.W, p.Z, 0));
     }
+    return ASI_OK;
+}
+
+// Steps 4 and 5.  grp: the correlations of the launch, this one at `self`.
+asi_status build_conv_grad(const ConvBuild& cb, const float* const* U, float* dW, int accumulate, const CorrGroup& grp, int self,
+                           Program& pg) {
+    const ConvGeom& cg = cb.cg;
+    const CorrGeom& g = cg.g;
+    const int taps = g.kh * g.kw;
+    ConvPlan p = cb.p;
+    p.nsplit = corr_splits(grp, self);
+    if (p.nsplit > cb.p.nsplit) return ASI_ERR_UNSUPPORTED;        // (cannot be: the workspace holds those of the layer alone)
+    if (p.nsplit == 1) p.Tpart = p.T;
     // 4. T = correlation of Zpad with G1 over (r1, Ho, Wo)        (cout, r2, kh, kw)
     const double tsz = (double)g.cout * g.r2 * taps;
     ASI_ADD(pg, "", 4.0 * ((double)g.r1 * g.cout * g.Ho * g.Wo + (double)g.r1 * g.r2 * g.H * g.W + tsz * p.nsplit),
-            2.0 * g.r1 * g.Ho * g.Wo * tsz, make_corr(G1, p.Z, p.Tpart, g, p.nsplit, layers, it__));
+            2.0 * g.r1 * g.Ho * g.Wo * tsz, make_corr(cb.G1, p.Z, p.Tpart, grp, self, p.nsplit, it__));
     // 5. dW = T x_(r2) U2, per group                              (cout, C/groups, kh, kw)
     // An ungrouped convolution with 1 or 9 taps and r2 <= 64 sums the partial T's and expands the result in one
     // launch (T itself is then never written); anything else sums first and multiplies in a second launch.
@@ -1011,9 +1031,22 @@ asi_status asi_weight_grad_conv2d_batch(int32_t count, const asi_tensor_desc* de
     if (!batch_count_ok(count)) return ASI_ERR_UNSUPPORTED;
     if (!descs || !S || !U || !grad_out || !convs || !dW || !ws || !ws_bytes) return ASI_ERR_INVALID_ARG;
     std::vector<Program> progs(count);
+    std::vector<ConvBuild> cb(count);
     for (int l = 0; l < count; ++l)
-        ASI_TRYS(build_conv(&descs[l], S[l], U[l], grad_out[l], &convs[l], dW[l], accumulate ? accumulate[l] : 0, ws[l],
-                            ws_bytes[l], count, progs[l]));
+        ASI_TRYS(build_conv_maps(&descs[l], S[l], U[l], grad_out[l], &convs[l], dW[l], ws[l], ws_bytes[l], &cb[l], progs[l]));
+    // Correlations at the same place of their programs and on the same kernel go out together and share the CUs; the others of a
+    // batch run by themselves, one after the other, and are split like layers alone (a 3x3, a 1x1, a 5x5 and a 14x14
+    // layer in one batch, all split as if they shared one launch: 174 us for the weight gradients instead of 137).
+    std::vector<CorrGroup> grp(count);
+    std::vector<int> self(count, 0);
+    for (int l = 0; l < count; ++l)
+        for (int k = 0; k < count; ++k)
+            if (k == l || (progs[k].items.size() == progs[l].items.size() && corr_shares(cb[k].cg.g, cb[l].cg.g))) {
+                if (k == l) self[l] = grp[l].n;
+                grp[l].g[grp[l].n++] = &cb[k].cg.g;
+            }
+    for (int l = 0; l < count; ++l)
+        ASI_TRYS(build_conv_grad(cb[l], U[l], dW[l], accumulate ? accumulate[l] : 0, grp[l], self[l], progs[l]));
     return flush(progs, static_cast<hipStream_t>(stream), "dW");
 }
 

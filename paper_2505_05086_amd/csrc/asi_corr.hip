@@ -65,8 +65,17 @@ struct CorrJob {
     int ips;             // fallback kernel: core channels i per split
 };
 
-// layers: how many layers of a batch share the launch
-static bool corr_plan(const CorrGeom& g, int layers, CorrPlan* p) {
+// instantiation of k_corr_mfma for a plan: low nibble 0 = <1,true,V>, 1 = <9,true,V>, 2 = <9,false,V>, 3 = <25,false,V>;
+// high nibble = V.  Large chunks: by slab rows (4 or 6) and lanes per slab row (64 or 128); small ones: by the slab's length.
+static unsigned corr_plan_key(const CorrGeom& g, const CorrPlan& p) {
+    const int taps = g.kh * g.kw;
+    const int bigv = p.kc == CR_KC_BIG ? (p.rows_in == 4 ? 1 : 3) + (p.wp <= 64 ? 0 : 1) : (p.zld * 16 <= CR_ZMAX_SHORT ? 5 : 0);
+    return (taps == 1 ? 0u : (taps == 9 ? 1u : (taps < 9 ? 2u : 3u))) | ((unsigned)bigv << 4);
+}
+static long long corr_plan_tiles(const CorrGeom& g) { return (long long)((g.cout + CR_TO - 1) / CR_TO) * ((g.r2 + 15) / 16); }
+
+// The plan of a layer that has the launch to itself.  cut: its chunks are dealt out by the rule for long walks.
+static bool corr_plan(const CorrGeom& g, CorrPlan* p, bool* cut) {
     const int taps = g.kh * g.kw;
     if (g.Wo > CR_KC_SMALL || taps > 25) return false;
     // the kernel indexes G1 and Z with 32-bit offsets
@@ -96,7 +105,7 @@ static bool corr_plan(const CorrGeom& g, int layers, CorrPlan* p) {
     while (g.sw == 1 ? (p->zld % 32 != 2) : (p->zld % 2 == 0)) ++p->zld;
     if ((long long)p->zld * 16 > zmax) p->zld = p->slab;
     p->nchunks = g.r1 * p->nyc;
-    const long long base = (long long)((g.cout + CR_TO - 1) / CR_TO) * ((g.r2 + 15) / 16);
+    const long long base = corr_plan_tiles(g);
     long long target = 256;
     // A CU holds one workgroup (registers; the large chunks: LDS, too), so a workgroup beyond the 256th waits for a whole
     // round: the split count is rounded down (960 x 40 x 9 over 24 x 7 x 7: 270 workgroups 46 us, 225 with a fifth chunk each
@@ -109,21 +118,41 @@ static bool corr_plan(const CorrGeom& g, int layers, CorrPlan* p) {
     // thousand output positions or more this way is better cut in three, so that three workgroups
     // per CU hide each other's rounds (measured on 64 x 64 planes: 252 -> 144 us; below that the extra
     // partial sums cost more than the overlap gains: 83 -> 96 us on 56 x 56 planes with twice the channels' splits).
-    if (p->kc == CR_KC_SMALL && (long long)p->cps * p->ry * g.Wo >= 1024) {
+    *cut = p->kc == CR_KC_SMALL && (long long)p->cps * p->ry * g.Wo >= 1024;
+    if (*cut) {
         want = (3 * target + base - 1) / base;
         if (want > p->nchunks) want = p->nchunks;
         p->cps = (int)((p->nchunks + want - 1) / want);
-    } else if (layers > 1) {
-        // The other layers of a batch take their share of the CUs, and a workgroup costs about four chunks beside its own
-        // (first loads, result through LDS): the count with the fewest rounds x (chunks + 4), never more than alone (three
-        // layers of 512 x 48 x 9 over 16 x 7 x 7: 576 workgroups of two chunks 46 us, 216 of six 32).
-        long long best = -1;
-        const int alone = (int)((p->nchunks + p->cps - 1) / p->cps);
-        for (int ns = 1; ns <= alone; ++ns) {
-            const int cps = (p->nchunks + ns - 1) / ns;
-            const long long wgs = base * layers * ((p->nchunks + cps - 1) / cps), cost = ((wgs + target - 1) / target) * (cps + 4);
-            if (best < 0 || cost < best) { best = cost; p->cps = cps; }
+    }
+    p->nsplit = (p->nchunks + p->cps - 1) / p->cps;
+    return true;
+}
+
+// The plan of layer `self` of a launch.  The layers share the CUs, and a workgroup costs about four chunks beside its own (first
+// loads, result through LDS): every layer takes as many chunks per workgroup as give the fewest rounds x (chunks + 4) over
+// the whole launch, never more splits than alone (three layers of 512 x 48 x 9 over 16 x 7 x 7: 576 workgroups of two chunks
+// 46 us, 216 of six 32; one of them beside 256 x 32 x 9 over 16 x 14 x 14: 448 workgroups of two chunks 34, 224 of four 26).
+static bool corr_plan_shared(const CorrGroup& grp, int self, CorrPlan* p) {
+    bool cut;
+    if (!corr_plan(*grp.g[self], p, &cut)) return false;
+    if (grp.n <= 1 || cut) return true;
+    CorrPlan pl[kMaxBatch];
+    bool fixed[kMaxBatch];
+    for (int k = 0; k < grp.n; ++k)
+        if (!corr_plan(*grp.g[k], &pl[k], &fixed[k])) return false;
+    long long best = -1;
+    const int alone = p->nsplit;
+    for (int ns = 1, last = 0; ns <= alone; ++ns) {
+        const int cps = (p->nchunks + ns - 1) / ns;
+        if (cps == last) continue;
+        last = cps;
+        long long wgs = 0;
+        for (int k = 0; k < grp.n; ++k) {
+            const int splits = (pl[k].nchunks + cps - 1) / cps;
+            wgs += corr_plan_tiles(*grp.g[k]) * (fixed[k] || splits > pl[k].nsplit ? pl[k].nsplit : splits);
         }
+        const long long cost = (wgs + 255) / 256 * (cps + 4);
+        if (best < 0 || cost < best) { best = cost; p->cps = cps; }
     }
     p->nsplit = (p->nchunks + p->cps - 1) / p->cps;
     return true;
@@ -635,9 +664,16 @@ __global__ __launch_bounds__(256) void k_corr(Batch<CorrJob> bt) {
     Tpart[(long long)bsplit * total + e] = acc;
 }
 
-int corr_splits(const CorrGeom& g, int layers) {
+bool corr_shares(const CorrGeom& a, const CorrGeom& b) {
+    CorrPlan pa, pb;
+    bool cut;
+    return corr_plan(a, &pa, &cut) && corr_plan(b, &pb, &cut) && corr_plan_key(a, pa) == corr_plan_key(b, pb);
+}
+
+int corr_splits(const CorrGroup& grp, int self) {
+    const CorrGeom& g = *grp.g[self];
     CorrPlan pl;
-    if (corr_plan(g, layers, &pl)) return pl.nsplit;
+    if (corr_plan_shared(grp, self, &pl)) return pl.nsplit;
     const long long total = (long long)g.cout * g.r2 * g.kh * g.kw;
     const long long blocks = (total + 255) / 256;
     long long want = (2048 + blocks - 1) / blocks;
@@ -647,26 +683,23 @@ int corr_splits(const CorrGeom& g, int layers) {
     return (g.r1 + ips - 1) / ips;
 }
 
-// key: low nibble 0 = k_corr_mfma<1,true,V>, 1 = <9,true,V>, 2 = <9,false,V>, 3 = <25,false,V>; high nibble = V (BIGV);
-// the fallback kernel has kind IT_CORR
-bool make_corr(const float* G1, const float* Z, float* Tpart, const CorrGeom& g, int nsplit, int layers, Item* out) {
+// key: see corr_plan_key; the fallback kernel has kind IT_CORR
+bool make_corr(const float* G1, const float* Z, float* Tpart, const CorrGroup& grp, int self, int nsplit, Item* out) {
+    const CorrGeom& g = *grp.g[self];
     const long long total = (long long)g.cout * g.r2 * g.kh * g.kw;
     if (total <= 0 || nsplit <= 0 || !G1 || !Z || !Tpart) return false;
     CorrJob jb;
     std::memset(&jb, 0, sizeof(jb));
     jb.G1 = G1; jb.Z = Z; jb.Tpart = Tpart; jb.g = g;
     *out = Item();
-    if (corr_plan(g, layers, &jb.pl)) {
+    if (corr_plan_shared(grp, self, &jb.pl)) {
         if (nsplit != jb.pl.nsplit) return false;
         jb.gx = (g.cout + CR_TO - 1) / CR_TO; jb.gy = (g.r2 + 15) / 16; jb.gz = jb.pl.nsplit;
         const int taps = g.kh * g.kw;
         out->kind = IT_CORR_MFMA;
-        // large chunks: instantiation by slab rows (4 or 6) and lanes per slab row (64 or 128); small ones: by the slab's length
-        const int bigv = jb.pl.kc == CR_KC_BIG ? (jb.pl.rows_in == 4 ? 1 : 3) + (jb.pl.wp <= 64 ? 0 : 1)
-                                               : (jb.pl.zld * 16 <= CR_ZMAX_SHORT ? 5 : 0);
-        out->key = (taps == 1 ? 0u : (taps == 9 ? 1u : (taps < 9 ? 2u : 3u))) | ((unsigned)bigv << 4);
+        out->key = corr_plan_key(g, jb.pl);
         std::snprintf(out->label, sizeof(out->label), "k_corr_mfma<%d, %s, %d>", taps == 1 ? 1 : (taps <= 9 ? 9 : 25),
-                      (taps == 1 || taps == 9) ? "true" : "false", bigv);
+                      (taps == 1 || taps == 9) ? "true" : "false", (int)(out->key >> 4));
     } else {
         jb.ips = (g.r1 + nsplit - 1) / nsplit;
         if ((total + 255) / 256 > 0x3fffffLL) return false;

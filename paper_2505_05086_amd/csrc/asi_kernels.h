@@ -314,9 +314,14 @@ bool make_init_ctrl(int32_t* info, Item* out);   // *info = 0
 struct CorrGeom {
     int r1, r2, cout, H, W, Ho, Wo, kh, kw, sh, sw, ph, pw, dh, dw;
 };
-// layers: how many layers of a batch share the launch (1 gives the most splits)
-int corr_splits(const CorrGeom& g, int layers);
-bool make_corr(const float* G1, const float* Z, float* Tpart, const CorrGeom& g, int nsplit, int layers, Item* out);
+// corr_shares: the two layers' correlations run on the same kernel, so that a batch can launch them together
+struct CorrGroup {       // the correlations of one launch; how far each is split depends on all of them (alone gives the most splits)
+    int n = 0;
+    const CorrGeom* g[kMaxBatch] = {};
+};
+bool corr_shares(const CorrGeom& a, const CorrGeom& b);
+int corr_splits(const CorrGroup& grp, int self);
+bool make_corr(const float* G1, const float* Z, float* Tpart, const CorrGroup& grp, int self, int nsplit, Item* out);
 
 // ---- step 5 of Eq. 14 with groups: dW[o,c,t] (+)= sum_j T[o,j,t] * U2[(o/og)*cg + c, j] -----------------------
 struct ExpandJob {

@@ -69,3 +69,45 @@ def test_batch_of_eight_layers():
     """The largest batch the ABI takes: every launch serves eight argument blocks."""
     _run_pair(2, [0, 1, 2, 3, 3, 2, 1, 0], steps=1)
     _run_pair(3, [0, 3, 0, 3, 1, 2, 0, 3], steps=1)
+
+
+def test_correlations_that_share_no_launch_are_split_like_layers_alone():
+    """3x3, 1x1 and 5x5 kernels over the same map: the correlations of such a batch run one after the other, and each must fill
+    the chip by itself.  A second 3x3 layer shares its launch, and the two take fewer splits together than two alone."""
+    from paper_2505_05086_amd import binding as B
+
+    def corr_workgroups(step):
+        torch.cuda.synchronize()
+        B.asi_profile_enable(True)
+        try:
+            step()
+            torch.cuda.synchronize()
+            return {s: v["workgroups"] for s, v in B.asi_profile_report().items() if "k_corr" in s}
+        finally:
+            B.asi_profile_enable(False)
+
+    layers = [Layer("mix", (16, 128, 7, 7), (12, 48, 5, 5), "f32", "conv2d", 512, k=k, pad=(k - 1) // 2, alpha=0.7, noise=1e-2)
+              for k in (3, 1, 5)]
+    streams = [LayerStream(9, 31 + i, lay) for i, lay in enumerate(layers)]
+    _run_layers(9, [31, 32, 33], layers, streams, 1)
+    alone = {}
+    for lay, st in zip(layers, streams):
+        r = LayerRunner(lay)
+        r.set_factors(st.u_prev0())
+        a, g = r.upload(st.activation(0)), r.upload(st.grad_out(0))
+        alone.update(corr_workgroups(lambda: r.step(a, g)))
+    assert len(alone) == 3
+
+    def together(idx):
+        batch = BatchRunner([layers[i] for i in idx])
+        for r, i in zip(batch.runs, idx):
+            r.set_factors(streams[i].u_prev0())
+        A = [r.upload(streams[i].activation(0)) for r, i in zip(batch.runs, idx)]
+        dY = [r.upload(streams[i].grad_out(0)) for r, i in zip(batch.runs, idx)]
+        return corr_workgroups(lambda: batch.step(A, dY))
+
+    assert together([0, 1, 2]) == alone
+    four = together([0, 1, 2, 0])
+    pair = [s for s in alone if "<9, " in s][0]
+    assert {s: w for s, w in four.items() if s != pair} == {s: w for s, w in alone.items() if s != pair}
+    assert alone[pair] <= four[pair] <= 2 * alone[pair]
