@@ -293,7 +293,9 @@ __global__ __launch_bounds__(256, NBR <= 2 ? 4 : 2) void k_ttm_stream_short(Batc
 // turns them with byte permutes into the A operands of a 16x16x32 MFMA for the four column blocks {4 l + v}.  The
 // matrix is cut into three bf16 terms when it is staged (top 8 significant bits, the next 8, the rest: every fp32 value is
 // their exact sum, and a product with a bf16 value is exact in fp32), so that nothing is lost against the fp32 MFMA:
-// 3 x 16 cycles per 16 x 16 x 32 block instead of 8 x 32.  LDS holds the r rows of a term only (a lane beyond r reads row
+// 3 x 16 cycles per 16 x 16 x 32 block instead of 8 x 32.  That holds for finite values: an infinite entry of X meets terms
+// that are zero (Inf x 0 is NaN where Inf x m is Inf), an infinite entry of the matrix has no terms.  A result that is not
+// finite is therefore computed again from the entries themselves, one multiply-add after the other.  LDS holds the r rows of a term only (a lane beyond r reads row
 // r - 1, its outputs are dropped), Ms[term][q][i], pitch KP + 8 (16-byte reads of 16 rows then meet every bank once).
 // KW of the 8 waves share a span; a wave has two K steps in flight, i.e. its whole share of a mode of up to 512.
 // The fp32 form needed 10 us of MFMA time for the (8, 512, 5632) grad_out of a language model's widest layer, after its
@@ -451,6 +453,21 @@ __global__ __launch_bounds__(TSB_NT, NBR <= 2 ? 4 : 2) void k_ttm_stream_bf16(Ba
             v4f out = *reinterpret_cast<const v4f*>(red + ((sp * HK * QP + q) * TS_RP + 4 * pc));
 #pragma unroll
             for (int k = 1; k < HK; ++k) out += *reinterpret_cast<const v4f*>(red + (((sp * HK + k) * QP + q) * TS_RP + 4 * pc));
+            const bool fin[4] = {fabsf(out[0]) < INFINITY, fabsf(out[1]) < INFINITY, fabsf(out[2]) < INFINITY, fabsf(out[3]) < INFINITY};
+            if (!(fin[0] && fin[1] && fin[2] && fin[3])) {
+                const bf16_t* __restrict__ xe = X + ((size_t)oe * n * inner + je);
+                v4f again = {0.f, 0.f, 0.f, 0.f};
+                for (int i = 0; i < n; ++i) {
+                    const uint2 w = *reinterpret_cast<const uint2*>(xe + (size_t)i * inner);
+                    const float m = Mp[(long long)i * ms_i + q];
+                    again[0] = fmaf(__uint_as_float(w.x << 16), m, again[0]);
+                    again[1] = fmaf(__uint_as_float(w.x & 0xffff0000u), m, again[1]);
+                    again[2] = fmaf(__uint_as_float(w.y << 16), m, again[2]);
+                    again[3] = fmaf(__uint_as_float(w.y & 0xffff0000u), m, again[3]);
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) out[v] = fin[v] ? out[v] : again[v];
+            }
             v4f* yp = reinterpret_cast<v4f*>(Y + (((size_t)oe * r + q) * inner + je));
             if (beta) out += *yp;
             *yp = out;

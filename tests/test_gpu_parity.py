@@ -289,6 +289,47 @@ def test_streaming_mode_product_bf16(case):
     assert any("k_ttm_stream_bf16<%s>" % variant in s_ for s_ in sites), [s_ for s_ in sites if "ttm" in s_]
 
 
+@pytest.mark.parametrize("n,row", [(130, 3), (130, 129), (300, 7), (512, 511)])
+@pytest.mark.parametrize("where", ["grad_out", "factor"])
+def test_streaming_mode_product_bf16_of_an_infinite_entry(n, row, where):
+    """An Inf in grad_out (a loss scale that was too large) or in a factor: Inf in the outputs that it enters with one sign, as a
+    product entry by entry gives it, and not the NaN of Inf x 0 over the matrix's zero terms or the mode's padding; every
+    other output as without it.  All entries positive, so that no Inf meets another of the opposite sign."""
+    from paper_2505_05086_amd import binding as B
+    rng = np.random.default_rng(n + row)
+    b, din, dout, ranks = 4, 24, 5000, (4, 4, 1)
+    desc = B.make_desc((b, n, din), ranks, "bf16")
+    U = [_dev(rng.uniform(0.5, 1.0, (d, r))) for d, r in zip((b, n, din), ranks)]
+    S = _dev(rng.uniform(0.5, 1.0, ranks))
+    gy = torch.from_numpy(rng.uniform(0.5, 1.0, (b, n, dout)).astype(np.float32)).cuda().to(torch.bfloat16)
+    ws = B.alloc_workspace(desc, None, dout)
+
+    def grad():
+        dW = torch.empty(dout, din, device="cuda")
+        B.asi_weight_grad_linear(desc, S, U, gy, dout, dW, False, ws)
+        return dW
+
+    plain = grad()
+    assert torch.isfinite(plain).all()
+    hit = torch.zeros(dout, dtype=torch.bool, device="cuda")
+    if where == "grad_out":
+        gy[2, row, 37] = float("inf")
+        hit[37] = True
+    else:
+        U[1][row, 2] = float("inf")
+        hit[:] = True
+    B.asi_profile_enable(True)
+    try:
+        dW = grad()
+        torch.cuda.synchronize()
+        sites = list(B.asi_profile_report())
+    finally:
+        B.asi_profile_enable(False)
+    assert any("k_ttm_stream_bf16" in s_ for s_ in sites), sites
+    assert torch.all(torch.isposinf(dW[hit])), dW[hit]
+    assert torch.equal(dW[~hit], plain[~hit])
+
+
 EDGE_LINEAR = [((3, 5, 7), (2, 3, 4), 6), ((4, 9, 30), (4, 9, 30), 3), ((2, 33, 130), (1, 7, 20), 70),
                ((64, 1, 5), (3, 1, 2), 1), ((6, 50, 300), (3, 34, 100), 40),     # a rank above 64
                ((3, 20, 600), (2, 8, 24), 50),                                   # a last mode of 512 or more
