@@ -16,8 +16,8 @@
 // of 64 through two LDS buffers (one barrier per chunk), the next two chunks travelling in registers.
 #include "asi_device.h"
 #include "asi_kernels.h"
+#include "asi_lds.h"
 
-#include <atomic>
 #include <cstdio>
 #include <cstring>
 
@@ -295,14 +295,10 @@ template <int NBN, int WN, int CBW>
 static hipError_t launch_gemm_one(const Batch<GemmBfJob>& b, dim3 grid, hipStream_t st) {
     constexpr size_t lds = GemmShape<NBN, WN, CBW>::lds_bytes;
     static_assert(lds <= 160 * 1024, "LDS of a CU");
-    if (lds > 65536) {                // more than a static array may take: allowed once per kernel
-        static std::atomic<bool> allowed{false};
-        if (!allowed.load()) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_bf16<NBN, WN, CBW>),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return e;
-            allowed.store(true);
-        }
+    if (lds > 65536) {                // more than a static array may take
+        static LdsAllowed allowed;
+        const hipError_t e = allow_lds(reinterpret_cast<const void*>(k_gemm_bf16<NBN, WN, CBW>), lds, allowed);
+        if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL((k_gemm_bf16<NBN, WN, CBW>), grid, BG_NT, lds, st, b);
     return hipGetLastError();

@@ -10,8 +10,8 @@
 // Splits of K write partial T's that a reduction kernel sums in fixed order.
 #include "asi_device.h"
 #include "asi_kernels.h"
+#include "asi_lds.h"
 
-#include <atomic>
 #include <cstdio>
 #include <cstring>
 #include <type_traits>
@@ -722,21 +722,16 @@ hipError_t launch_corr_items(const Item* const* items, int n, hipStream_t st) {
         hipLaunchKernelGGL(k_corr, grid, 256, 0, st, b);
         return hipGetLastError();
     }
-    // LDS is dynamic: the large-chunk instantiations need more than the 64 KB a static array may take,
-    // which has to be allowed once per kernel (the flags are only ever set, so a race between threads is harmless)
+    // LDS is dynamic: most instantiations need more than the 64 KB a static array may take
 #define ASI_CORR_LAUNCH(MAXT, EXACT, BIG)                                                                          \
     do {                                                                                                           \
         constexpr int ZMAX = BIG == 5 ? CR_ZMAX_SHORT : CR_ZMAX_SMALL;                                             \
         constexpr size_t lds = sizeof(float) * (BIG >= 1 && BIG <= 4 ? corr_big_lds_floats()                                        \
                                                     : corr_lds_floats<MAXT>(CR_KC_SMALL, ZMAX));                   \
         if (lds > 65536) {                                                                                         \
-            static std::atomic<bool> allowed{false};                                                               \
-            if (!allowed.load()) {                                                                                 \
-                hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_corr_mfma<MAXT, EXACT, BIG>),   \
-                                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);          \
-                if (e != hipSuccess) return e;                                                                     \
-                allowed.store(true);                                                                               \
-            }                                                                                                      \
+            static LdsAllowed allowed;                                                                             \
+            const hipError_t e = allow_lds(reinterpret_cast<const void*>(k_corr_mfma<MAXT, EXACT, BIG>), lds, allowed); \
+            if (e != hipSuccess) return e;                                                                         \
         }                                                                                                          \
         hipLaunchKernelGGL((k_corr_mfma<MAXT, EXACT, BIG>), grid, CR_NT, lds, st, b);                              \
     } while (0)

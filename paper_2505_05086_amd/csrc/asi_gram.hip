@@ -31,8 +31,8 @@
 // dropped), so each instruction covers S times the columns.
 #include "asi_gram_device.h"
 #include "asi_kernels.h"
+#include "asi_lds.h"
 
-#include <atomic>
 #include <cstdio>
 #include <cstring>
 
@@ -253,13 +253,9 @@ bool make_subspace_gram(DType xt, const void* X, long long outer, int n, long lo
 template <typename T, int NB, bool DMA>
 static hipError_t launch_gram_t(dim3 grid, hipStream_t st, const Batch<GramJob>& b) {
     constexpr int ring = sg_nbuf<NB>() * sg_buf_bytes<NB>(), sums = 4 * gram_blocks<NB>() * 256 * 8, lds = ring > sums ? ring : sums;
-    static std::atomic<bool> allowed{false};
-    if (!allowed.load()) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_subspace_gram<T, NB, DMA>),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (e != hipSuccess) return e;
-        allowed.store(true);
-    }
+    static LdsAllowed allowed;
+    const hipError_t e = allow_lds(reinterpret_cast<const void*>(k_subspace_gram<T, NB, DMA>), lds, allowed);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_subspace_gram<T, NB, DMA>), grid, SG_NT, lds, st, b);
     return hipGetLastError();
 }

@@ -23,8 +23,8 @@
 // partial P (its rows x its columns) that the orthogonalisation sums in fixed order.
 #include "asi_device.h"
 #include "asi_kernels.h"
+#include "asi_lds.h"
 
-#include <atomic>
 #include <cstdio>
 #include <cstring>
 #include <type_traits>
@@ -309,14 +309,10 @@ template <typename T, int NRB, int NCB, int NBQ, bool VEC>
 static hipError_t launch_long_one(const Batch<LongJob>& b, dim3 grid, hipStream_t st) {
     constexpr size_t lds = LongShape<NRB, NCB, NBQ>::lds_bytes;
     static_assert(lds <= 160 * 1024, "LDS of a CU");
-    if (lds > 65536) {                // more than a static array may take: allowed once per kernel
-        static std::atomic<bool> allowed{false};
-        if (!allowed.load()) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_subspace_long<T, NRB, NCB, NBQ, VEC>),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return e;
-            allowed.store(true);
-        }
+    if (lds > 65536) {                // more than a static array may take
+        static LdsAllowed allowed;
+        const hipError_t e = allow_lds(reinterpret_cast<const void*>(k_subspace_long<T, NRB, NCB, NBQ, VEC>), lds, allowed);
+        if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL((k_subspace_long<T, NRB, NCB, NBQ, VEC>), grid, LG_NT, lds, st, b);
     return hipGetLastError();

@@ -29,8 +29,8 @@
 // Slow path (r > 192): one workgroup per mode, everything in global memory.
 #include "asi_device.h"
 #include "asi_kernels.h"
+#include "asi_lds.h"
 
-#include <atomic>
 #include <cstdio>
 #include <cstring>
 #include <type_traits>
@@ -1615,15 +1615,11 @@ hipError_t launch_orth_items(const Item* const* items, int n, hipStream_t st, ch
             break;
         case IT_ORTHW_CHOL: {
             // packed triangle, dinv, rdiag, pivot reciprocals, inverse block factor
-            const size_t nb16 = (size_t)((rmax + 15) / 16) * 16;
-            const size_t lds = sizeof(double) * ((size_t)rmax * (rmax + 1) / 2 + 2 * (size_t)rmax + nb16 + 16 * 17);
-            static std::atomic<size_t> lds_allowed{0};     // the attribute only ever needs to grow
-            if (lds > lds_allowed.load()) {
-                hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_orthw_chol),
-                                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-                if (e != hipSuccess) return e;
-                lds_allowed.store(lds);
-            }
+            const auto bytes = [](size_t r) { return sizeof(double) * (r * (r + 1) / 2 + 2 * r + (r + 15) / 16 * 16 + 16 * 17); };
+            const size_t lds = bytes((size_t)rmax);
+            static LdsAllowed allowed;
+            const hipError_t e = allow_lds(reinterpret_cast<const void*>(k_orthw_chol), bytes(OW_RMAX), allowed);
+            if (e != hipSuccess) return e;
             hipLaunchKernelGGL(k_orthw_chol, grid, OWC_NT, lds, st, b, aux & 1, (aux >> 1) & 1);
             break;
         }

@@ -25,9 +25,9 @@
 // 37.0 -> 35.4, 16384 of 14 x 14 (rank 7) 17.2 -> 11.9, 1079 of 45 x 37 16.4 -> 15.8.
 #include "asi_gram_device.h"
 #include "asi_kernels.h"
+#include "asi_lds.h"
 
 #include <algorithm>
-#include <atomic>
 #include <cstdio>
 #include <cstring>
 #include <type_traits>
@@ -251,13 +251,9 @@ bool make_subspace_planes(DType xt, const void* X, long long planes, int rows, i
 template <typename T, int NB, bool DMA>
 static hipError_t launch_planes_t(const Batch<PlanesJob>& b, dim3 grid, int lds, hipStream_t st) {
     if (lds > 65536) {
-        static std::atomic<int> allowed{65536};        // the attribute only ever needs to grow
-        if (lds > allowed.load()) {
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_subspace_planes<T, NB, DMA>),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-            if (e != hipSuccess) return e;
-            allowed.store(160 * 1024);
-        }
+        static LdsAllowed allowed;
+        const hipError_t e = allow_lds(reinterpret_cast<const void*>(k_subspace_planes<T, NB, DMA>), 160 * 1024, allowed);
+        if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL((k_subspace_planes<T, NB, DMA>), grid, PN_NT, lds, st, b);
     return hipGetLastError();

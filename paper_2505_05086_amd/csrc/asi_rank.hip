@@ -16,7 +16,6 @@
 // asi_weight_grad_* on the truncated eigenvectors).
 #include <hip/hip_runtime.h>
 
-#include <atomic>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
@@ -25,6 +24,7 @@
 
 #include "../../include/asi.h"
 #include "asi_device.h"
+#include "asi_lds.h"
 
 namespace {
 
@@ -645,13 +645,9 @@ template <int NE>
 hipError_t jacobi_sweep(double* W, int n, double tol2, const int32_t* prev, int32_t* cur, hipStream_t st) {
     constexpr size_t lds = sizeof(double) * 2 * RK_JB * (RK_JL * NE + ((RK_JL * NE) % 32 == 0 ? 16 : 0));
     if (lds > 65536) {
-        static std::atomic<bool> allowed{false};
-        if (!allowed.load()) {
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_jacobi_block<NE>),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return e;
-            allowed.store(true);
-        }
+        static LdsAllowed allowed;
+        const hipError_t e = allow_lds(reinterpret_cast<const void*>(k_jacobi_block<NE>), lds, allowed);
+        if (e != hipSuccess) return e;
     }
     const int nblk2 = ((n + RK_JB - 1) / RK_JB + 1) & ~1;
     for (int round = 0; round < nblk2 - 1; ++round)

@@ -24,8 +24,8 @@
 // has nothing but its loads to wait for, and the resident waves are what keeps them in flight.
 #include "asi_device.h"
 #include "asi_kernels.h"
+#include "asi_lds.h"
 
-#include <atomic>
 #include <cstdio>
 #include <cstring>
 #include <type_traits>
@@ -539,14 +539,10 @@ bool make_ttm_stream(DType xt, const void* X, long long outer, int n, long long 
 
 template <typename T, int NBR, int KW>
 static hipError_t launch_stream_one(const Batch<TtmJob>& b, dim3 grid, size_t lds, hipStream_t st) {
-    if (lds > 65536) {                // more than a static array may take: allowed once per kernel
-        static std::atomic<bool> allowed{false};
-        if (!allowed.load()) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_ttm_stream<T, NBR, KW>),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)TS_LDS_MAX);
-            if (e != hipSuccess) return e;
-            allowed.store(true);
-        }
+    if (lds > 65536) {                // more than a static array may take
+        static LdsAllowed allowed;
+        const hipError_t e = allow_lds(reinterpret_cast<const void*>(k_ttm_stream<T, NBR, KW>), TS_LDS_MAX, allowed);
+        if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL((k_ttm_stream<T, NBR, KW>), grid, 256, lds, st, b);
     return hipGetLastError();
@@ -580,13 +576,9 @@ static hipError_t launch_stream_t(int nbr, int kw, const Batch<TtmJob>& b, dim3 
 template <int NBR, int KW>
 static hipError_t launch_stream_bf16_one(const Batch<TtmJob>& b, dim3 grid, size_t lds, hipStream_t st) {
     if (lds > 65536) {
-        static std::atomic<bool> allowed{false};
-        if (!allowed.load()) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_ttm_stream_bf16<NBR, KW>),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)TS_LDS_MAX);
-            if (e != hipSuccess) return e;
-            allowed.store(true);
-        }
+        static LdsAllowed allowed;
+        const hipError_t e = allow_lds(reinterpret_cast<const void*>(k_ttm_stream_bf16<NBR, KW>), TS_LDS_MAX, allowed);
+        if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL((k_ttm_stream_bf16<NBR, KW>), grid, TSB_NT, lds, st, b);
     return hipGetLastError();

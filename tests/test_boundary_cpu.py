@@ -218,3 +218,39 @@ def test_bench_refuses_more_than_one_gpu():
     res = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--gpus", "2"], capture_output=True, text=True, timeout=120)
     assert res.returncode == 2
     assert "one GPU" in res.stderr and res.stdout.strip() == ""
+
+
+LDS_PROBE = r"""
+#include "asi_lds.h"
+#include <cstdio>
+static int dev = 0, calls = 0, fail = 0;
+extern "C" hipError_t hipGetDevice(int* d) { *d = dev; return hipSuccess; }
+extern "C" hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int bytes) {
+    ++calls;
+    return fail || bytes != 90000 ? hipErrorInvalidValue : hipSuccess;
+}
+int main() {
+    static asi::LdsAllowed allowed, other;
+    auto at = [&](int d, asi::LdsAllowed& a) { dev = d; calls = 0; const hipError_t e = asi::allow_lds(nullptr, 90000, a); std::printf("%d%c ", calls, e == hipSuccess ? '+' : '-'); };
+    at(0, allowed); at(0, allowed); at(1, allowed); at(0, allowed); at(1, allowed); at(63, allowed); at(63, allowed); at(64, allowed); at(64, allowed);
+    at(0, other);
+    fail = 1; at(5, allowed); fail = 0; at(5, allowed); at(5, allowed);
+    return 0;
+}
+"""
+
+
+def test_lds_allowance_is_asked_for_on_every_gpu(tmp_path):
+    """A kernel's allowance of more than 64 KB of LDS belongs to one GPU: the second that the process launches on has to ask for it
+    too (the runtime is a stand-in here), and a failure is not remembered as success."""
+    import shutil
+    import subprocess
+    csrc = os.path.join(ROOT, "paper_2505_05086_amd", "csrc")
+    users = [f for f in os.listdir(csrc) if "hipFuncSetAttribute" in open(os.path.join(csrc, f)).read()]
+    assert users == ["asi_lds.h"]
+    src, exe = tmp_path / "probe.cpp", tmp_path / "probe"
+    src.write_text(LDS_PROBE)
+    subprocess.run([shutil.which("g++") or "g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I" + csrc, str(src),
+                    "-o", str(exe)], check=True)
+    out = subprocess.run([str(exe)], check=True, stdout=subprocess.PIPE, text=True).stdout.split()
+    assert out == ["1+", "0+", "1+", "0+", "0+", "1+", "0+", "1+", "1+", "1+", "1-", "1+", "0+"]
