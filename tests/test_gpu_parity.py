@@ -593,6 +593,7 @@ def _graded_tensor(lay, ratio, seed=20250505):
 def _check_orthonormal_basis(lay, A, stream_id, tag):
     st = LayerStream(9, stream_id, lay)
     run = _runner(lay)
+    run.ws.zero_()
     run.set_factors(st.u_prev0())
     U_gpu = run.compress(run.upload(A))
     torch.cuda.synchronize()
@@ -626,6 +627,7 @@ def _check_orthonormal_basis(lay, A, stream_id, tag):
             assert ep <= bound, f"{tag} mode {m}: leading {k} columns, projector err {ep:.2e} > bound {bound:.2e}"
             compared += 1
     assert compared >= len(U_or), f"{tag}: only {compared} nested projectors were comparable"
+    return run.ws, A64, U0
 
 
 @pytest.mark.parametrize("ratio", [1e-1, 1e-2, 3e-3])
@@ -717,16 +719,6 @@ def test_correlation_takes_fewer_rows_per_chunk_where_the_slab_is_large(dims, ra
     assert any("k_corr_mfma" in s_ for s_ in sites), sites
 
 
-@pytest.mark.parametrize("ratio", [0.9, 0.2])
-@pytest.mark.parametrize("dims,ranks", [((15, 192, 193), (15, 16, 17)), ((33, 208, 50), (32, 33, 49)), ((64, 70, 1000), (64, 63, 48))])
-def test_orthogonalisation_at_block_and_slice_edges(dims, ranks, ratio):
-    """Ranks one around every block of 16 up to 64, modes of one ragged slice of 16 rows, of 12 and 13 slices (added directly
-    and in groups) and of 63; graded mildly (the first pass is certified from its factor) and strongly (it is checked and
-    repeated)."""
-    lay = Layer("orth", dims, ranks, "f32", "linear", 12)
-    _check_orthonormal_basis(lay, _graded_tensor(lay, ratio), 13, f"{dims} ratio {ratio}")
-
-
 def _orth_path(ws, A64, U_prev, m):
     """Which path the orthogonalisation of mode m (rank up to 64) took in the compress call that last used the workspace:
     2 = first pass certified from its factor, 1 = measured and found enough, 0 = second pass.  The bookkeeping is found by what
@@ -742,6 +734,43 @@ def _orth_path(ws, A64, U_prev, m):
             and np.all(np.abs(w[i + 1:i + 1 + k] - diag[:k]) <= 1e-2 * diag[:k])]
     assert len(hits) == 1, (m, hits)
     return int(w[hits[0] + 66])
+
+
+def _orth_paths_possible(P):
+    """The paths that the orthogonalisation of P may take by its own rules, with a factor of three or more on either side of each
+    line for what the kernel rounds otherwise: 2 where its bound on |Q^T Q - I| after one pass is below 1e-7 (u = 2^-53, c the
+    column-scaled condition number), 1 where the bound is not but the distance itself is, else 0."""
+    n, r = P.shape
+    G = P.T @ P
+    X = np.linalg.inv(np.linalg.qr(P)[1])
+    c = np.max(np.sum(np.sqrt(np.diag(G))[:, None] * np.abs(X), axis=0))
+    slices = (n + 15) // 16
+    per = slices if slices <= 12 else int(np.ceil(np.sqrt(slices)))
+    bound = 2.0 ** -53 * ((18 + per + -(-slices // per) + 2 * r) * c * c + 4 * r * c)
+    Q = P @ np.linalg.inv(np.linalg.cholesky(G).T)
+    dev = np.max(np.abs(Q.T @ Q - np.eye(r)))
+    paths = set()
+    if bound < 3e-7:
+        paths.add(2)
+    if bound > 3e-8 and dev < 1e-6:
+        paths.add(1)
+    if bound > 3e-8 and dev > 1e-8:
+        paths.add(0)
+    return paths
+
+
+@pytest.mark.parametrize("ratio,reached", [(0.9, 2), (0.2, 2), (0.02, 1), (3e-3, 0)])
+@pytest.mark.parametrize("dims,ranks", [((15, 192, 193), (15, 16, 17)), ((33, 208, 50), (32, 33, 49)), ((64, 70, 1000), (64, 63, 48))])
+def test_orthogonalisation_at_block_and_slice_edges(dims, ranks, ratio, reached):
+    """Ranks one around every block of 16 up to 64, modes of one ragged slice of 16 rows, of 12 and 13 slices (added directly
+    and in groups) and of 63, graded so that the first pass is certified from its factor (0.9 and 0.2, every mode), measured and
+    found enough (0.02), or repeated (3e-3); the path that every mode took is read from the workspace."""
+    lay = Layer("orth", dims, ranks, "f32", "linear", 12)
+    ws, A64, U0 = _check_orthonormal_basis(lay, _graded_tensor(lay, ratio), 13, f"{dims} ratio {ratio}")
+    took = [_orth_path(ws, A64, U0[m], m) for m in range(3)]
+    for m in range(3):
+        assert took[m] in _orth_paths_possible(O.subspace_P(A64, U0[m], m)), (m, took)
+    assert reached in took and (ratio < 0.1 or took == [2, 2, 2]), took
 
 
 def _tensor_with_a_low_direction(rng, dims, m):
