@@ -1430,10 +1430,10 @@ int orth_gram_slices(int n) { return (n + OP_GS - 1) / OP_GS; }
 // slices per group: about the square root, no more than kOrthGroups groups
 int orth_group_size(int n) {
     const int s = orth_gram_slices(n);
+    if (s <= 12) return s;                               // one group: the second level only copies
+    if (s > kOrthGroups * kOrthGroups) return (s + kOrthGroups - 1) / kOrthGroups;
     int g = 1;
     while (g * g < s) ++g;
-    if (s <= 12) g = s;                                  // one group: the second level only copies
-    while ((s + g - 1) / g > kOrthGroups) ++g;
     return g;
 }
 bool orth_wide_supported(int r) { return r > OP_RMAX && r <= OW_RMAX; }

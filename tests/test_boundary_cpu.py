@@ -53,6 +53,21 @@ def test_workspace_query():
     assert asi.asi_workspace_bytes(asi.make_desc((4, 20, 2100), (3, 8, 90)), None, 12) == 0
 
 
+def test_planning_a_very_long_mode_takes_no_time():
+    """The plan of a call is made anew on every call: its host time must not grow with a mode's length."""
+    import time
+    best = {}
+    for n in (1 << 12, 1 << 30):
+        d = asi.make_desc((4, 4, n), (2, 2, 8))
+        times = []
+        for _ in range(5):
+            t = time.perf_counter()
+            assert asi.asi_workspace_bytes(d) > 0
+            times.append(time.perf_counter() - t)
+        best[n] = min(times)
+    assert best[1 << 30] <= 10 * best[1 << 12] + 1e-4, best
+
+
 def test_layers_that_just_fit_the_static_scratch():
     # long modes of rank 64 in few columns: what grows with the 16-row Gram slices must not push them over the limit
     for dims, ranks in (((3, 214, 3423), (1, 64, 64)), ((3, 299, 2618), (2, 64, 64)), ((6, 94, 3614), (1, 58, 64))):
