@@ -26,9 +26,8 @@ constexpr int CR_TO = 64;            // output channels per workgroup
 // leaves the matrix pipe of a large map idle a third of the time (measured with device
 // timestamps: per chunk 1.0-1.3 us of LDS stores and 1.3-2.7 us of load issue in which no wave multiplies,
 // against 6-8 us of products), so large maps take chunks of 128 positions (whole output rows), and both forms use TWO buffers:
-// half of the waves store the next chunk and issue the loads of the one after it BEFORE they multiply the
-// current chunk, the other half AFTER, so that on every SIMD one wave multiplies while the other moves
-// data, and a chunk costs one barrier.
+// every wave stores the next chunk, issues the loads of the one after it and multiplies the current one, and a chunk costs
+// one barrier.
 // Small maps: slabs of up to CR_ZMAX_SHORT floats (7 x 7 with a halo: 16 x 81) have an instantiation of their own, whose
 // loader takes half the loads.
 constexpr int CR_KC_SMALL = 64, CR_ZMAX_SMALL = 4096, CR_ZMAX_SHORT = 2048;
@@ -107,17 +106,23 @@ static bool corr_plan(const CorrGeom& g, CorrPlan* p, bool* cut) {
     p->nchunks = g.r1 * p->nyc;
     const long long base = corr_plan_tiles(g);
     long long target = 256;
-    // A CU holds one workgroup (registers; the large chunks: LDS, too), so a workgroup beyond the 256th waits for a whole
-    // round: the split count is rounded down (960 x 40 x 9 over 24 x 7 x 7: 270 workgroups 46 us, 225 with a fifth chunk each
-    // 29; two workgroups per CU, forced to 128 registers, 34).
+    // Splits for one workgroup per CU, rounded down.  The large chunks and the 25-tap form fit a CU once (LDS; registers), so a
+    // workgroup beyond the 256th waits for a whole round.  The other small-chunk forms fit two or three times, but a workgroup's
+    // first loads and its result, and the partial sums of the next launch, cost more than a second one per CU hides.  Splits
+    // for 256 | 512 workgroups, correlation + expansion: 960 x 40 x 9 over 24 x 7 x 7 29 + 6 | 32 + 6 us, 256 x 32 x 9 over
+    // 16 x 14 x 14 19 + 11 | 21 + 13, 320 x 40 x 1 over 24 x 7 x 7 8.7 + 9.3 | 8.7 + 10.6, 64 x 16 x 9 over 8 x 50 x 50
+    // 19 + 17 | 21 + 26 (768: as 512 or slower).
     long long want = target / base;
     if (want > p->nchunks) want = p->nchunks;
     if (want < 1) want = 1;
     p->cps = (int)((p->nchunks + want - 1) / want);
-    // A chunk is a dependent round of loads, barriers and 9 x 16 products: a workgroup that walks a
-    // thousand output positions or more this way is better cut in three, so that three workgroups
-    // per CU hide each other's rounds (measured on 64 x 64 planes: 252 -> 144 us; below that the extra
-    // partial sums cost more than the overlap gains: 83 -> 96 us on 56 x 56 planes with twice the channels' splits).
+    // A chunk is a dependent round of loads, a barrier and products: a workgroup that walks a thousand output positions or more
+    // this way is cut in three, so that the workgroups of a CU (three with one tap, two with up to nine) hide each other's
+    // rounds.  Correlation + expansion of the partial sums, cut | not cut: 1024 x 64 x 1 over 32 x 14 x 14 36 + 16 | 48 + 14 us;
+    // 512 x 64 x 9 over 16 x 30 x 30 122 + 25 | 129 + 20, 768 over 32 x 13 x 13 86 + 33 | 94 + 27; with more channels still the
+    // partial sums cost more than the overlap gains (1024 over 32 x 14 x 14 117 + 48 | 119 + 35).  The 25-tap form fits a CU
+    // once (222 registers) and is cut for its sums: 512 x 64 x 25 over 16 x 28 x 28 would take 360 + 8 us instead of 413 + 16,
+    // but three times as many of its additions would then be in fp32 (weight gradient off by 5.9e-7 instead of 3.9e-7).
     *cut = p->kc == CR_KC_SMALL && (long long)p->cps * p->ry * g.Wo >= 1024;
     if (*cut) {
         want = (3 * target + base - 1) / base;

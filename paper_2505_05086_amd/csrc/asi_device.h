@@ -29,9 +29,9 @@ __device__ __forceinline__ double ldg_f64(const double* __restrict__ p, long lon
     return ok ? v : 0.0;
 }
 
-// Memory-to-LDS copy without registers: every active lane of the wave moves 16 bytes from src + off (off below `bytes`, the
-// extent of src) to lds + 16 * lane, lds being the same for the whole wave.  Waited for like any load (a workgroup barrier
-// does).  The builtins exist in the device pass only.
+// Memory-to-LDS copy without registers: every active lane of the wave moves 16 bytes from src + off to lds + 16 * lane, lds being
+// the same for the whole wave; at or beyond `bytes`, the extent of src, it writes zeros.  Waited for with
+// wait_copies_and_sync.  The builtins exist in the device pass only.
 __device__ __forceinline__ void copy16_to_lds(const void* src, int bytes, int off, void* lds) {
 #if defined(__HIP_DEVICE_COMPILE__)
     __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(src), 0, bytes, 0x00027000),

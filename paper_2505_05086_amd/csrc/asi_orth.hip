@@ -16,15 +16,18 @@
 //           factors: blocked Cholesky in LDS without a shift, with the shift only if a pivot is lost.
 //           It then inverts R and bounds what one pass leaves of |Q^T Q - I|: with X = R^-1 and
 //           c = max_j sum_i sqrt(G_ii) |X_ij|  (the column-scaled condition number), rounding of G, of the factor and of
-//           the products gives  |Q^T Q - I| <= u ((18 + slices of a group + groups + 2 r) c^2 + 4 r c).  Below OP_DONE_TOL - the steady
-//           state of a warm-started basis, c is 10..300 there and 2000 would do - the first pass is certified.
+//           the products gives  |Q^T Q - I| <= u ((18 + slices of a group + groups + 2 r) c^2 + 4 r c).  Below OP_DONE_TOL
+//           (c up to about 2000) the first pass is certified: always where the basis has settled (c 1..300), and on
+//           activations that move a little every step for most modes, but not for long modes of steep spectra (256 to 960
+//           channels: c 1000 to 9000), although what one pass leaves there is 4e-9.
 //   apply : certified: Q = P X, a wave per 16 x 16 block of Q, all its operands in one round of loads; nothing else.
 //           Otherwise: Q0 = P R^-1 by block forward substitution (fp64 MFMA), written in fp64 and as
 //           the fp32 result, plus the slice Gram of Q0; the last-arriving workgroup measures
 //           |Q0^T Q0 - I| and only if that exceeds OP_DONE_TOL runs the second pass by itself
 // The two launches are a chain of dependent round trips to memory and of pivots; 512 threads keep up to 48 loads each in
-// flight.  960 x 40 (30 slices) and three short modes: gram0 30.9 -> 27.2, apply 21.0 -> 4.7 us; measuring the result instead of
-// certifying it (slice Grams, hand-over, sum, comparison) was half of apply.
+// flight.  960 x 40 (30 slices) and three short modes: gram0 30.9 -> 27.2, apply 21.0 -> 4.7 us certified; measuring the result
+// instead of certifying it (slice Grams, hand-over, sum, comparison) was half of apply, and still is where the certificate is
+// refused (bracketed by events, on activations whose factors move by 2 % a step: 6.2 certified, 22.8 refused, 23.0 before).
 // Wide path (64 < r <= 192): separate Gram / Cholesky / apply launches on the packed triangle.
 // Slow path (r > 192): one workgroup per mode, everything in global memory.
 #include "asi_device.h"
@@ -120,7 +123,7 @@ __device__ __forceinline__ double bcast_lane(double x, int src) {      // src un
     return __hiloint2double(hi, lo);
 }
 
-// e / r for 0 <= e < 2^16 and 1 <= r <= 64 without an integer division: the rounded float quotient
+// e / r for 0 <= e < 2^16 and 1 <= r <= 192 without an integer division: the rounded float quotient
 // of (e + 0.5) is exact in that range (the same device as in the product kernels).
 __device__ __forceinline__ int small_div(int e, float inv_r) { return (int)(((float)e + 0.5f) * inv_r); }
 
@@ -605,7 +608,8 @@ __device__ bool last_arrival(int32_t* ctr, int nblk, int* s_flag) {
 // slices; the slice Grams are then added in two levels, groups of gsz slices by the workgroup of a group that arrives last,
 // the groups by the one of the mode that does, because what one CU can read past its L2 is 25 bytes a cycle (30 slices of
 // 32 rows summed by one workgroup: 8.5 us for the partial sums and 6.8 for the Grams; 60 slices in 8 groups 3.6 and 6.3).
-// RM bounds the ranks of the launch's modes: a slice has at most 16 * RM elements, ITS per thread.
+// RM bounds the ranks of the launch's modes: a slice has at most 16 * RM elements, ITS per thread.  Up to 32 a CU holds two
+// workgroups (128 registers; six of <32> spill, 28 bytes a lane).
 template <int RM>
 __global__ __launch_bounds__(OP_NT, RM <= 32 ? 4 : 2) void k_orth_gram0(OrthBatch a) {
     __shared__ __align__(16) unsigned char raw[sizeof(CholSmem)];
@@ -844,7 +848,7 @@ __global__ __launch_bounds__(OP_NT) void k_orth_apply(OrthBatch a) {
 
 // ---- wide path, 64 < r <= 192 -----------------------------------------------------------------
 // Same two passes.  The Gram matrix no longer fits the statically sized LDS arrays, so
-//   gramw : 128-row blocks read P64 in 32-row sub-slices and keep their block pairs in registers
+//   gramw : 64-row blocks read P64 in 32-row sub-slices and keep their block pairs in registers
 //   cholw : one workgroup per mode, Gram matrix packed (upper triangle) in up to 150 KB of
 //           dynamic LDS, same right-looking factorisation
 //   applyw: 32-row blocks, R's off-diagonal blocks are read straight from global memory

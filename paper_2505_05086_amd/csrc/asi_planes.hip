@@ -12,7 +12,7 @@
 //
 // A tile is a run of whole planes, contiguous in memory, copied to LDS as it is (16 bytes per lane and instruction
 // straight from memory to LDS, no register and no vector instruction on the way) while the previous tile is multiplied:
-// two buffers, one barrier per tile.  Eight waves: wave w < 4 accumulates G_H of planes w, w + 4, .., wave w + 4 the G_W of
+// two buffers, one wait per tile.  Eight waves: wave w < 4 accumulates G_H of planes w, w + 4, .., wave w + 4 the G_W of
 // the same planes, one of each on every SIMD.  Operand of K slot lg: lane (lg, ll) holds element (M = 16 mb + ll, K), for
 // the A and the B side alike; K slot (s, lg) of a block of 16 stands for index 16 kb + 4 lg + s, of a last block of
 // 4 nst or fewer for 16 kb + nst lg + s.  Rows past the plane read what lies behind it and only reach rows and columns of G

@@ -654,7 +654,7 @@ def test_ill_conditioned_wide_rank_stays_orthonormal(ratio):
 
 @pytest.mark.parametrize("ratio", [0.3, 0.05])
 def test_ill_conditioned_wide_rank_many_slices(ratio):
-    """A wide mode long enough (2100 rows: 17 slices of 128) that its slice Gram matrices are added
+    """A wide mode long enough (2100 rows: 33 slices of 64) that its slice Gram matrices are added
     by a tree level before the factorisation; both passes and the shifted retry read the summed ones."""
     lay = Layer("illcond", (8, 20, 2100), (6, 16, 90), "f32", "linear", 12)
     _check_orthonormal_basis(lay, _graded_tensor(lay, ratio), 10, f"wide, many slices, ratio {ratio}")
@@ -717,6 +717,37 @@ def test_correlation_takes_fewer_rows_per_chunk_where_the_slab_is_large(dims, ra
     finally:
         B.asi_profile_enable(False)
     assert any("k_corr_mfma" in s_ for s_ in sites), sites
+
+
+@pytest.mark.parametrize("k", [1, 3, 5])
+def test_correlation_of_a_long_walk(k):
+    """More than a thousand output positions per workgroup: the walk is cut in three (more than 512 workgroups).  Weight gradient
+    against the dense sum in float64 on the reconstruction; fp32 sums of 16 x 26 x 30 products: 1e-5 of the largest entry."""
+    from paper_2505_05086_amd import binding as B
+    rng = np.random.default_rng(k)
+    dims, ranks, cout, pad = (16, 512, 26, 30), (16, 64, 6, 6), 512, (k - 1) // 2
+    desc, conv = B.make_desc(dims, ranks, "f32"), B.make_conv(cout, k, k, (1, 1), (pad, pad), (1, 1), 1)
+    U = [_dev(np.linalg.qr(rng.standard_normal((n, r)))[0]) for n, r in zip(dims, ranks)]
+    S, gy = _dev(rng.standard_normal(ranks)), torch.randn(dims[0], cout, *dims[2:], device="cuda", generator=torch.Generator("cuda").manual_seed(k))
+    dW = torch.empty(cout, dims[1], k, k, device="cuda")
+    B.asi_profile_enable(True)
+    try:
+        B.asi_weight_grad_conv2d(desc, S, U, gy, conv, dW, False, B.alloc_workspace(desc, conv, 0))
+        torch.cuda.synchronize()
+        sites = {s_: v["workgroups"] for s_, v in B.asi_profile_report().items() if "k_corr" in s_}
+    finally:
+        B.asi_profile_enable(False)
+    assert len(sites) == 1 and all("k_corr_mfma" in s_ and w > 512 for s_, w in sites.items()), sites
+    x = S.double()
+    for u in U:
+        x = torch.tensordot(x, u.double().t().contiguous(), dims=([0], [0]))
+    x = torch.nn.functional.pad(x, (pad, pad, pad, pad))
+    g2 = gy.double().transpose(0, 1).reshape(cout, -1).contiguous()
+    for a in range(k):
+        for b in range(k):
+            xs = x[:, :, a:a + dims[2], b:b + dims[3]].transpose(0, 1).reshape(dims[1], -1).contiguous()
+            want = g2 @ xs.t().contiguous()
+            assert float((dW[:, :, a, b] - want).abs().max() / want.abs().max()) <= 1e-5, (a, b)
 
 
 def _orth_path(ws, A64, U_prev, m):
