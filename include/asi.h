@@ -210,6 +210,8 @@ size_t asi_mode_spectrum_workspace_bytes(const asi_tensor_desc* desc, int32_t mo
  *   eigenvectors  out device fp32 (dims[mode] x dims[mode]) row-major, column k = k-th principal component,
  *                 nullable; its first r columns are the factor of a truncated HOSVD of rank r.  A column
  *                 whose eigenvalue is below 1e-12 of the largest is returned as zeros.
+ * A tensor that holds a NaN or an infinity: every eigenvalue is NaN (infinite where the Gram matrix holds no
+ * NaN), every eigenvector zero.
  *   sweeps        out HOST int32 (nullable): Jacobi sweeps used, -1 if 60 sweeps did not converge
  * Unlike every other entry point this one WAITS for the stream: it iterates to convergence and reads
  * the iteration's state after every sweep.  dims[mode] <= 512 (ASI_ERR_UNSUPPORTED beyond);
