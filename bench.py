@@ -37,7 +37,7 @@ KERNEL_UNIT = {"k_subspace_small": "mfma_f32+f64", "k_subspace_tiny": "valu_f32+
                "k_subspace_gram": "mfma_f64", "k_gauss_fill": "valu_f64",
                "k_ttm_mfma": "mfma_f32", "k_ttm_ksplit": "mfma_f32", "k_ttm_stream": "mfma_f32", "k_ttm_stream_short": "mfma_f32", "k_ttm_stream_bf16": "mfma_bf16", "k_ttm_expand": "mfma_f32", "k_ttm_duo": "mfma_f32", "k_ttm_thin": "valu_f32",
                "k_gemm_bf16": "mfma_bf16", "k_split_bf16": "valu_f32", "k_pair": "mfma_f64",
-               "k_corr_mfma": "mfma_f32", "k_corr": "valu_f32",
+               "k_corr_mfma": "mfma_f32", "k_corr_mfma_split": "mfma_bf16", "k_corr": "valu_f32",
                "k_orth_gram0": "mfma_f64", "k_orth_apply": "mfma_f64",
                "k_orthw_gram": "mfma_f64", "k_orthw_apply": "mfma_f64", "k_orthw_chol": "valu_f64",
                "k_orth_big": "valu_f64", "k_orth_presum": "valu_f64", "k_orthw_gsum": "valu_f64", "k_sum_partials": "valu_f64",

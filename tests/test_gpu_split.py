@@ -1,0 +1,94 @@
+"""Kernels that multiply operands cut into terms on a faster matrix unit, at the edges of their tiles, against the plain sums in
+float64."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _sites(call):
+    from paper_2505_05086_amd import binding as B
+    B.asi_profile_enable(True)
+    try:
+        call()
+        torch.cuda.synchronize()
+        return list(B.asi_profile_report())
+    finally:
+        B.asi_profile_enable(False)
+
+
+def _factors(rng, dims, ranks):
+    return [torch.from_numpy(np.linalg.qr(rng.standard_normal((n, r)))[0].astype(np.float32)).cuda() for n, r in zip(dims, ranks)]
+
+
+def _dense_dw(S, U, gy, stride, pad, dil):
+    x = S.double()
+    for u in U:
+        x = torch.tensordot(x, u.double().t().contiguous(), dims=([0], [0]))
+    x = torch.nn.functional.pad(x, (pad[1], pad[1], pad[0], pad[0]))
+    ho, wo = gy.shape[2:]
+    g2 = gy.double().transpose(0, 1).reshape(gy.shape[1], -1).contiguous()
+    out = torch.empty(gy.shape[1], x.shape[1], 3, 3, dtype=torch.float64, device="cuda")
+    for a in range(3):
+        for b in range(3):
+            xs = x[:, :, a * dil[0]:a * dil[0] + (ho - 1) * stride[0] + 1:stride[0], b:b + wo]
+            out[:, :, a, b] = g2 @ xs.transpose(0, 1).reshape(x.shape[1], -1).t().contiguous()
+    return out
+
+
+# Output rows of one position, one short of / just past a group of eight and of the widest map; maps with fewer core channels
+# than a chunk takes and with a ragged last chunk of rows; channels past a tile of 64, core channels past one of 16; strides and
+# dilations along H, paddings other than 1 (0: windows that end at the map's edge; 2: more positions than the map is wide).
+@pytest.mark.parametrize("dims,ranks,cout,stride,pad,dil", [
+    ((5, 20, 3, 3), (3, 17, 2, 2), 65, 1, 0, 1),
+    ((6, 33, 7, 7), (5, 16, 4, 4), 64, 1, 1, 1),
+    ((9, 18, 8, 9), (9, 18, 5, 5), 63, 1, 1, 1),
+    ((4, 24, 17, 18), (3, 9, 6, 6), 130, 1, 0, 1),
+    ((3, 20, 66, 63), (2, 5, 9, 9), 40, 1, 1, 1),
+    ((3, 12, 45, 62), (3, 12, 7, 8), 17, 1, 2, 1),
+    ((4, 16, 41, 24), (4, 16, 6, 6), 32, 2, 1, 1),
+    ((4, 16, 23, 31), (3, 16, 6, 6), 32, 1, 1, 3),
+])
+def test_split_correlation_at_the_edges_of_its_tiles(dims, ranks, cout, stride, pad, dil):
+    """Bound: fp32 sums of K products, K up to 4000, are off by about sqrt(K) 2^-25 of a typical entry; 1e-5 of the largest."""
+    from paper_2505_05086_amd import binding as B
+    rng = np.random.default_rng(sum(dims) + cout)
+    ho = (dims[2] + 2 * pad - 2 * dil - 1) // stride + 1
+    wo = dims[3] + 2 * pad - 2
+    desc, conv = B.make_desc(dims, ranks, "f32"), B.make_conv(cout, 3, 3, (stride, 1), (pad, pad), (dil, 1), 1)
+    U = _factors(rng, dims, ranks)
+    S = torch.from_numpy(rng.standard_normal(ranks).astype(np.float32)).cuda()
+    gy = torch.from_numpy(rng.standard_normal((dims[0], cout, ho, wo)).astype(np.float32)).cuda()
+    dW = torch.empty(cout, dims[1], 3, 3, device="cuda")
+    ws = B.alloc_workspace(desc, conv, 0)
+    ws.fill_(255)                                        # NaN wherever nothing was written
+    sites = _sites(lambda: B.asi_weight_grad_conv2d(desc, S, U, gy, conv, dW, False, ws))
+    assert any("k_corr_mfma_split<9, %s>" % ("true" if wo % 8 else "false") in s for s in sites), sites
+    want = _dense_dw(S, U, gy, (stride, 1), (pad, pad), (dil, 1))
+    assert float((dW - want).abs().max() / want.abs().max()) <= 1e-5
+
+
+@pytest.mark.parametrize("value", [float("inf"), 3.4e38])
+def test_split_correlation_of_an_entry_without_finite_terms(value):
+    """An infinite grad_out entry makes its output channel's gradient Inf or NaN where the plain sums have it, and nowhere else; an
+    entry that rounds to an infinite bf16 value is computed like any other."""
+    from paper_2505_05086_amd import binding as B
+    rng = np.random.default_rng(3)
+    dims, ranks, cout = (4, 16, 10, 12), (4, 8, 5, 5), 70
+    desc, conv = B.make_desc(dims, ranks, "f32"), B.make_conv(cout, 3, 3, (1, 1), (1, 1), (1, 1), 1)
+    U = _factors(rng, dims, ranks)
+    U[0] = torch.eye(4, device="cuda")                   # the batch entries stay apart
+    S = torch.from_numpy((1e-3 * rng.standard_normal(ranks)).astype(np.float32)).cuda()
+    gy = torch.from_numpy(rng.standard_normal((4, cout, 10, 12)).astype(np.float32)).cuda()
+    gy[2, 66, 4, 5] = value
+    dW = torch.empty(cout, 16, 3, 3, device="cuda")
+    B.asi_weight_grad_conv2d(desc, S, U, gy, conv, dW, False, B.alloc_workspace(desc, conv, 0))
+    rest = torch.arange(cout, device="cuda") != 66
+    want = _dense_dw(S, U, gy, (1, 1), (1, 1), (1, 1))
+    assert bool(torch.isfinite(dW[rest]).all())
+    assert float((dW[rest] - want[rest]).abs().max() / want[rest].abs().max()) <= 1e-5
+    if np.isfinite(value):
+        assert float((dW[66] - want[66]).abs().max() / want[66].abs().max()) <= 1e-5
+    else:
+        assert not bool(torch.isfinite(dW[66]).any())
