@@ -16,7 +16,7 @@
  *   - Every data pointer is caller-owned DEVICE memory on the current HIP
  *     device.  The library allocates nothing, keeps no state between calls and
  *     only enqueues kernels on `stream`; it never synchronises with the host
- *     (one exception, stated there: asi_mode_spectrum).
+ *     (one exception, stated there: asi_mode_spectrum and its form for several modes).
  *   - Activation `A` and output gradient `grad_out`: dense row-major, (B,C,H,W)
  *     or (B,N,D); element type given by asi_tensor_desc.dtype (fp32, or bf16
  *     with fp32 accumulation).
@@ -219,6 +219,14 @@ size_t asi_mode_spectrum_workspace_bytes(const asi_tensor_desc* desc, int32_t mo
 asi_status asi_mode_spectrum(const asi_tensor_desc* desc, const void* A, int32_t mode, double* eigenvalues,
                              float* eigenvectors, void* ws, size_t ws_bytes, int32_t* sweeps,
                              asi_stream_t stream);
+
+/* The same for n_modes (1 to 4) modes of one tensor in one call, whose launches serve all of them: entry k of eigenvalues,
+ * eigenvectors (null, or null entries: not wanted) and sweeps (nullable) belongs to mode modes[k].  Each result is the same, bit
+ * for bit, as asi_mode_spectrum's for that mode. */
+size_t asi_mode_spectra_workspace_bytes(const asi_tensor_desc* desc, const int32_t* modes, int32_t n_modes);
+asi_status asi_mode_spectra(const asi_tensor_desc* desc, const void* A, const int32_t* modes, int32_t n_modes,
+                            double* const* eigenvalues, float* const* eigenvectors, void* ws, size_t ws_bytes, int32_t* sweeps,
+                            asi_stream_t stream);
 
 /* Sec. 3.3, Step 1: for each threshold eps[j] (HOST array, 0 < eps <= 1, n_eps <= 16) the smallest
  * r >= 1 with sum_{k <= r} lambda_k >= eps[j] * sum_k lambda_k.

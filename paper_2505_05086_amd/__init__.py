@@ -26,6 +26,8 @@ from .binding import (  # noqa: F401
     asi_core_project_batch,
     asi_explained_variance_ranks,
     asi_frobenius_diff,
+    asi_mode_spectra,
+    asi_mode_spectra_workspace_bytes,
     asi_mode_spectrum,
     asi_mode_spectrum_workspace_bytes,
     asi_profile_enable,

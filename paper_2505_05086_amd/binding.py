@@ -26,7 +26,7 @@ EXPORTS = ["asi_workspace_bytes", "asi_compress", "asi_compress_cold", "asi_cold
            "asi_weight_grad_linear", "asi_compress_batch", "asi_core_project_batch",
            "asi_weight_grad_conv2d_batch", "asi_weight_grad_linear_batch", "asi_status_string", "asi_version",
            "asi_profile_enable", "asi_profile_report", "asi_activation_memory", "asi_mode_spectrum_workspace_bytes",
-           "asi_mode_spectrum", "asi_explained_variance_ranks", "asi_frobenius_diff", "asi_rank_select"]
+           "asi_mode_spectrum", "asi_mode_spectra_workspace_bytes", "asi_mode_spectra", "asi_explained_variance_ranks", "asi_frobenius_diff", "asi_rank_select"]
 FROBENIUS_WS_BYTES = 8192            # ASI_FROBENIUS_WS_BYTES of include/asi.h
 MAX_BATCH = 8
 
@@ -102,6 +102,11 @@ def lib() -> C.CDLL:
         L.asi_activation_memory.argtypes = [C.POINTER(TensorDesc)]
         L.asi_mode_spectrum_workspace_bytes.restype = C.c_size_t
         L.asi_mode_spectrum_workspace_bytes.argtypes = [C.POINTER(TensorDesc), C.c_int32]
+        L.asi_mode_spectra_workspace_bytes.restype = C.c_size_t
+        L.asi_mode_spectra_workspace_bytes.argtypes = [C.POINTER(TensorDesc), C.POINTER(C.c_int32), C.c_int32]
+        L.asi_mode_spectra.restype = C.c_int
+        L.asi_mode_spectra.argtypes = [C.POINTER(TensorDesc), vp, C.POINTER(C.c_int32), C.c_int32, C.POINTER(vp), C.POINTER(vp), vp,
+                                       C.c_size_t, C.POINTER(C.c_int32), vp]
         L.asi_mode_spectrum.restype = C.c_int
         L.asi_mode_spectrum.argtypes = [C.POINTER(TensorDesc), vp, C.c_int32, vp, vp, vp, C.c_size_t,
                                         C.POINTER(C.c_int32), vp]
@@ -342,6 +347,26 @@ def asi_mode_spectrum(desc: TensorDesc, A: torch.Tensor, mode: int, eigenvalues:
     _check(lib().asi_mode_spectrum(C.byref(desc), _ptr(A), int(mode), _ptr(eigenvalues), _ptr(eigenvectors), _ptr(ws),
                                    ws.numel(), C.byref(sweeps), _stream()), "asi_mode_spectrum")
     return int(sweeps.value)
+
+
+def asi_mode_spectra_workspace_bytes(desc: TensorDesc, modes: Sequence[int]) -> int:
+    return int(lib().asi_mode_spectra_workspace_bytes(C.byref(desc), (C.c_int32 * len(modes))(*modes), len(modes)))
+
+
+def asi_mode_spectra(desc: TensorDesc, A: torch.Tensor, modes: Sequence[int], eigenvalues: Sequence[torch.Tensor],
+                     eigenvectors: Sequence[Optional[torch.Tensor]], ws: torch.Tensor) -> List[int]:
+    """asi_mode_spectrum of several modes in one call.  Returns the numbers of Jacobi sweeps."""
+    k = len(modes)
+    if len(eigenvalues) != k or len(eigenvectors) != k:
+        raise ValueError("one tensor of eigenvalues and one of eigenvectors (or None) per mode")
+    _check_dev(A, *eigenvalues, *eigenvectors, ws)
+    if any(e.dtype != torch.float64 for e in eigenvalues) or any(v is not None and v.dtype != torch.float32 for v in eigenvectors):
+        raise ValueError("eigenvalues are fp64, eigenvectors fp32")
+    sweeps = (C.c_int32 * k)()
+    lam, vec = ((C.c_void_p * k)(*[None if t is None else t.data_ptr() for t in ts]) for ts in (eigenvalues, eigenvectors))
+    _check(lib().asi_mode_spectra(C.byref(desc), _ptr(A), (C.c_int32 * k)(*modes), k, lam, vec, _ptr(ws), ws.numel(), sweeps,
+                                  _stream()), "asi_mode_spectra")
+    return list(sweeps)
 
 
 def asi_explained_variance_ranks(eigenvalues: torch.Tensor, eps: Sequence[float], ranks: torch.Tensor) -> None:

@@ -42,24 +42,60 @@ constexpr int RK_FROB_WG = 1024;
 
 inline size_t align_up(size_t x) { return (x + RK_ALIGN - 1) / RK_ALIGN * RK_ALIGN; }
 
-struct GramJob {
+struct CholScale {
+    double scale, shift;                                 // what the factorisation applied: W^T W = scale (G + shift / scale I)
+    double bad;                                          // 0; G not finite: what every eigenvalue is returned as, NaN or Inf
+};
+// One mode of a call.  The modes of a tensor are independent and each is a long chain of small launches, so the launches serve
+// all of them: workgroup b belongs to the mode j with first[j] <= b < first[j + 1].  The rank-selection row of a (128, 160, 7, 7)
+// layer, one mode after the other 3620 us, so 2380: the 128-long mode (84 launches of 11 us) runs beside the 160-long one (108 of 14).
+struct SpecJob {
     const void* X;
     long long outer, inner, ncols;
     int n, tiles, nsplit, nchunks;
     double* part;                       // (nsplit, n, n)
+    double* G;
+    double* W;
+    double* norms;
+    CholScale* sc;
+    int32_t* rot;                       // rotations of every sweep
+    double shift_factor, tol2;
+    double* lam;
+    float* vec;
 };
+constexpr int RK_MODES = 4;
+struct SpecBatch {
+    int njobs;
+    int first[RK_MODES + 1];
+    SpecJob job[RK_MODES];
+};
+__device__ __forceinline__ const SpecJob& find_mode(const SpecBatch& a, int* blk) {
+    int j = 0;
+    const int b = blockIdx.x;
+    while (j + 1 < a.njobs && b >= a.first[j + 1]) ++j;
+    *blk = b - a.first[j];
+    return a.job[j];
+}
+
+// 1 / x for normal x: the hardware's estimate (2^-20 or better) and one step of third order
+__device__ __forceinline__ double recip64(double x) {
+    const double r = __builtin_amdgcn_rcp(x), e = fma(-x, r, 1.0);
+    return fma(r * e, 1.0 + e, r);
+}
 
 // One 64 x 64 tile of G over the column chunks z, z + nsplit, ...  Wave w owns rows 16 w .. 16 w + 15 of the
 // tile.  Both operands come from LDS tiles held row-major (mode index x columns); a 16-byte read gives a lane
 // the columns 4 lg .. 4 lg + 3 of a 16-column block, which stand for K slot lg of four MFMA steps (the same
 // assignment for both operands, and a sum over columns does not care about their order).
 template <typename T>
-__global__ __launch_bounds__(256) void k_mode_gram(GramJob jb) {
+__global__ __launch_bounds__(256) void k_mode_gram(SpecBatch a) {
+    int blk;
+    const SpecJob& jb = find_mode(a, &blk);
     __shared__ __align__(16) float Xi[RK_T * RK_LD];
     __shared__ __align__(16) float Xj[RK_T * RK_LD];
     const T* __restrict__ X = static_cast<const T*>(jb.X);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lg = lane >> 4, ll = lane & 15;
-    const int tile = blockIdx.x % (jb.tiles * jb.tiles), z = blockIdx.x / (jb.tiles * jb.tiles);
+    const int tile = blk % (jb.tiles * jb.tiles), z = blk / (jb.tiles * jb.tiles);
     const int bi = tile / jb.tiles, bj = tile - bi * jb.tiles;
     const int n = jb.n;
     const long long inner = jb.inner, ncols = jb.ncols;
@@ -134,10 +170,13 @@ __global__ __launch_bounds__(256) void k_mode_gram(GramJob jb) {
 }
 
 // G[e] = sum over the column ranges, in their order, 32 of them in flight; the first workgroup clears the iteration's counters
-__global__ __launch_bounds__(256) void k_gram_reduce(const double* __restrict__ part, int nsplit, long long cnt,
-                                                     double* __restrict__ G, int32_t* __restrict__ zero, int nzero) {
-    if (blockIdx.x == 0 && (int)threadIdx.x < nzero) zero[threadIdx.x] = 0;
-    const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
+__global__ __launch_bounds__(256) void k_gram_reduce(SpecBatch a, int nzero) {
+    int blk;
+    const SpecJob& jb = find_mode(a, &blk);
+    if (blk == 0 && (int)threadIdx.x < nzero) jb.rot[threadIdx.x] = 0;
+    const double* __restrict__ part = jb.part;
+    const int nsplit = jb.nsplit;
+    const long long cnt = (long long)jb.n * jb.n, e = (long long)blk * 256 + threadIdx.x;
     if (e >= cnt) return;
     double s = 0.0;
     for (int z0 = 0; z0 < nsplit; z0 += 32) {
@@ -147,7 +186,7 @@ __global__ __launch_bounds__(256) void k_gram_reduce(const double* __restrict__ 
 #pragma unroll
         for (int u = 0; u < 32; ++u) s += z0 + u < nsplit ? t[u] : 0.0;
     }
-    G[e] = s;
+    jb.G[e] = s;
 }
 
 __device__ __forceinline__ double wave_sum(double x) {
@@ -170,12 +209,13 @@ __device__ __forceinline__ double wave_sum(double x) {
 // One launch per panel of 32 rows: workgroup (I, J) factors the 32 x 32 diagonal block (redundantly: 32 dependent steps,
 // 3 us, less than a launch of its own), solves the panel's blocks above I and J and updates the trailing block (I, J).
 constexpr int RK_CB = 32;
-struct CholScale {
-    double scale, shift;                                 // what the factorisation applied: W^T W = scale (G + shift / scale I)
-    double bad;                                          // 0; G not finite: what every eigenvalue is returned as, NaN or Inf
-};
 
-__global__ __launch_bounds__(256) void k_chol_scale(const double* __restrict__ G, int n, double shift_factor, CholScale* out) {
+__global__ __launch_bounds__(256) void k_chol_scale(SpecBatch a) {
+    int blk;
+    const SpecJob& jb = find_mode(a, &blk);
+    const double* __restrict__ G = jb.G;
+    const int n = jb.n;
+    CholScale* out = jb.sc;
     __shared__ double red[4];
     __shared__ int s_nan;
     const int tid = threadIdx.x;
@@ -202,20 +242,25 @@ __global__ __launch_bounds__(256) void k_chol_scale(const double* __restrict__ G
         const bool ok = tr > 0.0 && tr < 1e300;          // (a zero tensor: the factor is sqrt(shift) I)
         if (ok) (void)frexp(tr, &e);
         out->scale = ldexp(1.0, -e);
-        out->shift = ok ? shift_factor * ldexp(tr, -e) : 1.0;
+        out->shift = ok ? jb.shift_factor * ldexp(tr, -e) : 1.0;
         out->bad = finite ? 0.0 : (s_nan ? NAN : INFINITY);
     }
 }
 
-__global__ __launch_bounds__(256) void k_chol_panel(double* __restrict__ G, double* __restrict__ W, int n, int P,
-                                                    const CholScale* __restrict__ sc) {
+__global__ __launch_bounds__(256) void k_chol_panel(SpecBatch a, int P) {
+    int blk;
+    const SpecJob& jb = find_mode(a, &blk);
+    double* __restrict__ G = jb.G;
+    double* __restrict__ W = jb.W;
+    const CholScale* __restrict__ sc = jb.sc;
+    const int n = jb.n;
     constexpr int B = RK_CB, LD = B + 1;
     __shared__ double D[B * LD], Xi[B * LD], Xj[B * LD], dinv[B];
     const int tid = threadIdx.x, nb = (n + B - 1) / B, rest = nb - P - 1;
     // workgroup 0 writes the diagonal block of R; the others are the tiles I <= J of the trailing matrix
     int I = P, J = P;
     if (rest > 0) {
-        int q = blockIdx.x, i = 0;
+        int q = blk, i = 0;
         while (q >= rest - i) { q -= rest - i; ++i; }
         I = P + 1 + i; J = I + q;
     }
@@ -243,7 +288,7 @@ __global__ __launch_bounds__(256) void k_chol_panel(double* __restrict__ G, doub
     // D = R_PP^T R_PP, rows left unscaled (row k holds R_kk R_kj) and the pivots' reciprocals kept: one barrier per step
     const int r0 = tid >> 5, c0 = tid & 31;
     for (int k = 0; k < B; ++k) {
-        const double pk = 1.0 / D[k * LD + k], dk = D[k * LD + c0] * pk;
+        const double pk = recip64(D[k * LD + k]), dk = D[k * LD + c0] * pk;
         double v[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) v[u] = D[(r0 + 8 * u) * LD + c0] - D[k * LD + r0 + 8 * u] * dk;
@@ -289,7 +334,7 @@ __global__ __launch_bounds__(256) void k_chol_panel(double* __restrict__ G, doub
             if (row < n && I * B + c0 < n) W[(long long)row * n + I * B + c0] = Xi[r * LD + c0] * rs;
             if (I * B + r < n && P * B + c0 < n) W[(long long)(I * B + r) * n + P * B + c0] = 0.0;
         }
-        if (blockIdx.x == 0 && row < n && P * B + c0 < n)
+        if (blk == 0 && row < n && P * B + c0 < n)
             W[(long long)row * n + P * B + c0] = c0 >= r ? D[r * LD + c0] * rs : 0.0;
     }
 }
@@ -390,8 +435,10 @@ __device__ __forceinline__ void row_norm2(const double* r, double* out, int lane
 }
 
 // n <= 64: the whole iteration.  32 pairs x 16 lanes; rot[0] = sweeps used if converged, else 0.
-__global__ __launch_bounds__(512) void k_jacobi_small(double* __restrict__ W, int n, double tol2, int max_sweeps,
-                                                      int32_t* __restrict__ rot) {
+__global__ __launch_bounds__(512) void k_jacobi_small(SpecBatch jobs, int max_sweeps) {
+    double* __restrict__ W = jobs.job[blockIdx.x].W;
+    const int n = jobs.job[blockIdx.x].n;
+    const double tol2 = jobs.job[blockIdx.x].tol2;
     constexpr int NE = 4, LD = 64 + 16;                  // pitch 16 mod 32 doubles: two rows on disjoint banks
     __shared__ double w[64 * LD], nrm[64];
     __shared__ int s_rot;
@@ -423,23 +470,23 @@ __global__ __launch_bounds__(512) void k_jacobi_small(double* __restrict__ W, in
         const int i = e / n, j = e - i * n;
         W[e] = w[i * LD + j];
     }
-    if (tid == 0) rot[0] = used;
+    if (tid == 0) jobs.job[blockIdx.x].rot[0] = used;
 }
 
-// One launch of a sweep for n > 64: workgroup q takes the q-th pair of blocks of `round`.  prev / cur: rotations of the
-// sweep before (null in the first; zero there means converged, nothing is done) and of this one.
+// One launch of a sweep for n > 64: workgroup q of a mode takes the q-th pair of blocks of `round`.  Rotations of the sweep before (not
+// in the first; zero there means converged, nothing is done) and of this one are counted in the mode's rot.
 extern __shared__ double jac_dyn[];
 template <int NE>
-__global__ __launch_bounds__(256) void k_jacobi_block(double* __restrict__ W, int n, int nblk2, int round, double tol2,
-                                                      const int32_t* __restrict__ prev, int32_t* __restrict__ cur) {
+__device__ __forceinline__ void jacobi_block(const SpecJob& jb, int blk, int sweep, int round, int& s_rot, double* nrm) {
+    double* __restrict__ W = jb.W;
+    const int n = jb.n, nblk2 = ((n + RK_JB - 1) / RK_JB + 1) & ~1;
+    const double tol2 = jb.tol2;
+    int32_t* cur = jb.rot + sweep;
     constexpr int LD = RK_JL * NE + ((RK_JL * NE) % 32 == 0 ? 16 : 0);
-    if (prev && *prev == 0) return;
-    __shared__ int s_rot;
-    __shared__ double nrm[2 * RK_JB];
     double* w = jac_dyn;                                 // 32 rows of LD
     const int tid = threadIdx.x, lane = tid & (RK_JL - 1), p = tid / RK_JL;
     int bi, bj;
-    round_robin(nblk2 - 1, round, blockIdx.x, &bi, &bj);
+    round_robin(nblk2 - 1, round, blk, &bi, &bj);
     if (tid == 0) s_rot = 0;
     // this thread group's two rows; rows past the end are zeros and never rotate.  All loads are in flight together.
     const int gi = bi * RK_JB + p, gj = bj * RK_JB + p;
@@ -514,14 +561,35 @@ __global__ __launch_bounds__(256) void k_jacobi_block(double* __restrict__ W, in
     __syncthreads();
     if (tid == 0 && s_rot) atomicAdd(cur, s_rot);
 }
+// elements per lane of a row of n: the shapes the rows are held in
+__host__ __device__ constexpr int row_shape(int n) { return n <= 128 ? 8 : (n <= 192 ? 12 : (n <= 256 ? 16 : 32)); }
+template <int NE>                                        // of the longest mode
+__global__ __launch_bounds__(256) void k_jacobi_block(SpecBatch a, int sweep, int round) {
+    __shared__ int s_rot;
+    __shared__ double nrm[2 * RK_JB];
+    int blk;
+    const SpecJob& jb = find_mode(a, &blk);
+    const int nblk2 = ((jb.n + RK_JB - 1) / RK_JB + 1) & ~1;
+    if (round >= nblk2 - 1 || (sweep > 0 && jb.rot[sweep - 1] == 0)) return;         // the same for all threads
+    const int ne = row_shape(jb.n);
+    if (NE == 8 || ne == 8) jacobi_block<8>(jb, blk, sweep, round, s_rot, nrm);
+    else if (NE == 12 || ne == 12) jacobi_block<12>(jb, blk, sweep, round, s_rot, nrm);
+    else if (NE == 16 || ne == 16) jacobi_block<16>(jb, blk, sweep, round, s_rot, nrm);
+    else jacobi_block<32>(jb, blk, sweep, round, s_rot, nrm);
+}
 
 // After convergence row k of W is sqrt(lambda_k) v_k^T, lambda_k an eigenvalue of the scaled and shifted G.  Eigenvalues in descending order (ties by row index),
 // eigenvectors as the columns of an n x n row-major fp32 matrix; a column whose eigenvalue is below
 // 1e-12 of the largest (a null direction, whose row carries no direction any more) is returned as zeros.  A G that is not finite
 // has no spectrum: every eigenvalue is NaN (Inf if no entry of G is NaN), every column zeros.
-__global__ __launch_bounds__(64) void k_row_norms(const double* __restrict__ W, int n, double* __restrict__ norms, const CholScale* __restrict__ sc) {
+__global__ __launch_bounds__(64) void k_row_norms(SpecBatch a) {
+    int k;
+    const SpecJob& jb = find_mode(a, &k);
+    const double* __restrict__ W = jb.W;
+    const CholScale* __restrict__ sc = jb.sc;
+    const int n = jb.n;
     constexpr int NE = RK_NMAX / 64;
-    const int k = blockIdx.x, lane = threadIdx.x;
+    const int lane = threadIdx.x;
     double t[NE];
 #pragma unroll
     for (int u = 0; u < NE; ++u) t[u] = W[(long long)k * n + (lane + 64 * u < n ? lane + 64 * u : 0)];
@@ -529,14 +597,20 @@ __global__ __launch_bounds__(64) void k_row_norms(const double* __restrict__ W, 
 #pragma unroll
     for (int u = 0; u < NE; ++u) s += lane + 64 * u < n ? t[u] * t[u] : 0.0;
     s = wave_sum(s);
-    if (lane == 0) norms[k] = sc->bad != 0.0 ? sc->bad : s > sc->shift ? (s - sc->shift) / sc->scale : 0.0;   // the eigenvalue of G itself
+    if (lane == 0) jb.norms[k] = sc->bad != 0.0 ? sc->bad : s > sc->shift ? (s - sc->shift) / sc->scale : 0.0;   // the eigenvalue of G itself
 }
 // workgroup k places row k: its rank among the eigenvalues by counting, then its column of the eigenvector matrix
-__global__ __launch_bounds__(256) void k_spectrum_finish(const double* __restrict__ W, int n, const double* __restrict__ norms, const CholScale* __restrict__ sc,
-                                                         double* __restrict__ lam_out, float* __restrict__ vec_out) {
+__global__ __launch_bounds__(256) void k_spectrum_finish(SpecBatch a) {
+    int k;
+    const SpecJob& jb = find_mode(a, &k);
+    const double* __restrict__ W = jb.W;
+    const double* __restrict__ norms = jb.norms;
+    const CholScale* __restrict__ sc = jb.sc;
+    float* __restrict__ vec_out = jb.vec;
+    const int n = jb.n;
     __shared__ int s_pos[4];
     __shared__ double s_max[4];
-    const int tid = threadIdx.x, k = blockIdx.x;
+    const int tid = threadIdx.x;
     const double l = norms[k];
     int pos = 0;
     double lmax = 0.0;
@@ -556,7 +630,7 @@ __global__ __launch_bounds__(256) void k_spectrum_finish(const double* __restric
     pos = s_pos[0] + s_pos[1] + s_pos[2] + s_pos[3];
     lmax = fmax(fmax(s_max[0], s_max[1]), fmax(s_max[2], s_max[3]));
     if (sc->bad != 0.0) pos = k;                         // (nothing to order by)
-    if (tid == 0) lam_out[pos] = l;
+    if (tid == 0) jb.lam[pos] = l;
     if (!vec_out) return;
     const bool live = l > 1e-12 * lmax && l > 0.0;
     const double inv = live ? 1.0 / sqrt(l * sc->scale + sc->shift) : 0.0;       // the row's norm
@@ -640,25 +714,46 @@ GramPlan plan_gram(const ModeShape& ms) {
     return p;
 }
 
-// the launches of one sweep for n > 64: every pair of blocks once
+// the modes of a launch: their argument blocks side by side, `blocks` workgroups each (none: the mode takes no part)
+template <typename F>
+int gather_modes(const SpecJob* jobs, int n, F blocks, SpecBatch* b) {
+    int total = 0;
+    b->njobs = 0;
+    for (int j = 0; j < n; ++j) {
+        const int k = blocks(jobs[j]);
+        if (k <= 0) continue;
+        b->first[b->njobs] = total;
+        b->job[b->njobs++] = jobs[j];
+        total += k;
+    }
+    for (int j = b->njobs; j <= RK_MODES; ++j) b->first[j] = total;
+    return total;
+}
+
+// the launches of one sweep for modes of n > 64: every pair of blocks once
 template <int NE>
-hipError_t jacobi_sweep(double* W, int n, double tol2, const int32_t* prev, int32_t* cur, hipStream_t st) {
+hipError_t jacobi_sweep(const SpecBatch& b, int grid, int rounds, int sweep, hipStream_t st) {
     constexpr size_t lds = sizeof(double) * 2 * RK_JB * (RK_JL * NE + ((RK_JL * NE) % 32 == 0 ? 16 : 0));
     if (lds > 65536) {
         static LdsAllowed allowed;
         const hipError_t e = allow_lds(reinterpret_cast<const void*>(k_jacobi_block<NE>), lds, allowed);
         if (e != hipSuccess) return e;
     }
-    const int nblk2 = ((n + RK_JB - 1) / RK_JB + 1) & ~1;
-    for (int round = 0; round < nblk2 - 1; ++round)
-        hipLaunchKernelGGL(k_jacobi_block<NE>, dim3((unsigned)(nblk2 / 2)), 256, lds, st, W, n, nblk2, round, tol2, prev, cur);
+    for (int round = 0; round < rounds; ++round) hipLaunchKernelGGL(k_jacobi_block<NE>, dim3((unsigned)grid), 256, lds, st, b, sweep, round);
     return hipGetLastError();
 }
-hipError_t launch_jacobi_sweep(double* W, int n, double tol2, const int32_t* prev, int32_t* cur, hipStream_t st) {
-    if (n <= 128) return jacobi_sweep<8>(W, n, tol2, prev, cur, st);
-    if (n <= 192) return jacobi_sweep<12>(W, n, tol2, prev, cur, st);
-    if (n <= 256) return jacobi_sweep<16>(W, n, tol2, prev, cur, st);
-    return jacobi_sweep<32>(W, n, tol2, prev, cur, st);
+hipError_t launch_jacobi_sweep(const SpecJob* jobs, int njobs, int sweep, hipStream_t st) {
+    SpecBatch b;
+    int longest = 0;
+    for (int j = 0; j < njobs; ++j) longest = jobs[j].n > longest ? jobs[j].n : longest;
+    const auto blocks = [](int n) { return ((n + RK_JB - 1) / RK_JB + 1) & ~1; };
+    const int grid = gather_modes(jobs, njobs, [&](const SpecJob& j) { return blocks(j.n) / 2; }, &b), rounds = blocks(longest) - 1;
+    switch (row_shape(longest)) {
+        case 8: return jacobi_sweep<8>(b, grid, rounds, sweep, st);
+        case 12: return jacobi_sweep<12>(b, grid, rounds, sweep, st);
+        case 16: return jacobi_sweep<16>(b, grid, rounds, sweep, st);
+        default: return jacobi_sweep<32>(b, grid, rounds, sweep, st);
+    }
 }
 
 struct Search {
@@ -703,83 +798,128 @@ int64_t asi_activation_memory(const asi_tensor_desc* desc) {
     return prod + sum;
 }
 
+size_t asi_mode_spectra_workspace_bytes(const asi_tensor_desc* desc, const int32_t* modes, int32_t n_modes) {
+    if (!modes || n_modes < 1 || n_modes > RK_MODES) return 0;
+    size_t total = 0;
+    for (int k = 0; k < n_modes; ++k) {
+        ModeShape ms;
+        asi_status why;
+        if (!parse_mode(desc, modes[k], &ms, &why)) return 0;
+        total += plan_gram(ms).bytes;
+    }
+    return total;
+}
+
 size_t asi_mode_spectrum_workspace_bytes(const asi_tensor_desc* desc, int32_t mode) {
-    ModeShape ms;
-    asi_status why;
-    if (!parse_mode(desc, mode, &ms, &why)) return 0;
-    return plan_gram(ms).bytes;
+    return asi_mode_spectra_workspace_bytes(desc, &mode, 1);
+}
+
+asi_status asi_mode_spectra(const asi_tensor_desc* desc, const void* A, const int32_t* modes, int32_t n_modes, double* const* eigenvalues,
+                            float* const* eigenvectors, void* ws, size_t ws_bytes, int32_t* sweeps, asi_stream_t stream) {
+    if (!modes || n_modes < 1 || n_modes > RK_MODES || !eigenvalues) return ASI_ERR_INVALID_ARG;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    char* base = static_cast<char*>(ws);
+    SpecJob jobs[RK_MODES];
+    size_t need = 0;
+    for (int k = 0; k < n_modes; ++k) {
+        ModeShape ms;
+        asi_status why;
+        if (!parse_mode(desc, modes[k], &ms, &why)) return why;
+        if (!A || !eigenvalues[k]) return ASI_ERR_INVALID_ARG;
+        const GramPlan p = plan_gram(ms);
+        SpecJob& jb = jobs[k];
+        char* at = base + need;
+        need += p.bytes;
+        jb.X = A; jb.outer = ms.outer; jb.inner = ms.inner; jb.ncols = ms.ncols; jb.n = ms.n;
+        jb.tiles = p.tiles; jb.nsplit = p.nsplit; jb.nchunks = p.nchunks;
+        jb.part = reinterpret_cast<double*>(at); at += p.part_bytes;
+        jb.G = reinterpret_cast<double*>(at); at += p.w_bytes;
+        jb.W = reinterpret_cast<double*>(at); at += p.w_bytes;
+        jb.norms = reinterpret_cast<double*>(at); at += p.norm_bytes;
+        jb.sc = reinterpret_cast<CholScale*>(at); at += align_up(sizeof(CholScale));
+        jb.rot = reinterpret_cast<int32_t*>(at);
+        // additions behind an entry of G: the columns of a range (64 a chunk), then the ranges
+        const double adds = (double)RK_T * ((p.nchunks + p.nsplit - 1) / p.nsplit) + p.nsplit;
+        jb.shift_factor = (4.0 * ms.n + adds) * 1.1102230246251565e-16;
+        const double tol = 4.0 * ms.n * 2.220446049250313e-16;   // two rows count as orthogonal below the rounding of their dot product
+        jb.tol2 = tol * tol;
+        jb.lam = eigenvalues[k];
+        jb.vec = eigenvectors ? eigenvectors[k] : nullptr;
+    }
+    if (!ws || reinterpret_cast<uintptr_t>(ws) % RK_ALIGN != 0 || ws_bytes < need) return ASI_ERR_WORKSPACE;
+
+    SpecBatch b;
+    int grid = gather_modes(jobs, n_modes, [](const SpecJob& j) { return j.tiles * j.tiles * j.nsplit; }, &b);
+    if (desc->dtype == ASI_BF16) hipLaunchKernelGGL(k_mode_gram<bf16_t>, dim3((unsigned)grid), 256, 0, st, b);
+    else hipLaunchKernelGGL(k_mode_gram<float>, dim3((unsigned)grid), 256, 0, st, b);
+    grid = gather_modes(jobs, n_modes, [](const SpecJob& j) { return (j.n * j.n + 255) / 256; }, &b);
+    hipLaunchKernelGGL(k_gram_reduce, dim3((unsigned)grid), 256, 0, st, b, RK_SWEEPS);
+    grid = gather_modes(jobs, n_modes, [](const SpecJob&) { return 1; }, &b);
+    hipLaunchKernelGGL(k_chol_scale, dim3((unsigned)grid), 256, 0, st, b);
+    for (int P = 0; P < (RK_NMAX + RK_CB - 1) / RK_CB; ++P) {
+        grid = gather_modes(jobs, n_modes, [P](const SpecJob& j) {
+            const int rest = (j.n + RK_CB - 1) / RK_CB - P - 1;
+            return rest > 0 ? rest * (rest + 1) / 2 : (rest == 0 ? 1 : 0);
+        }, &b);
+        if (grid == 0) break;
+        hipLaunchKernelGGL(k_chol_panel, dim3((unsigned)grid), 256, 0, st, b, P);
+    }
+    if (hipGetLastError() != hipSuccess) return ASI_ERR_HIP;
+
+    // Sweeps until a whole one rotates nothing; the counts come back to the host (this entry point iterates to convergence and
+    // therefore waits for the stream).  Modes of up to 64 iterate in one launch.  Sweeps are handed over several at a time (one
+    // that follows a converged one returns at once), so that the host's wait does not stand between every two of them.
+    grid = gather_modes(jobs, n_modes, [](const SpecJob& j) { return j.n > 1 && j.n <= 64 ? 1 : 0; }, &b);
+    if (grid) hipLaunchKernelGGL(k_jacobi_small, dim3((unsigned)grid), 512, 0, st, b, RK_SWEEPS);
+    int used[RK_MODES];                                  // sweeps until convergence, -1 before
+    SpecJob open[RK_MODES];                              // the longer modes that have not converged
+    int which[RK_MODES], n_open = 0;
+    for (int k = 0; k < n_modes; ++k) {
+        used[k] = jobs[k].n == 1 ? 0 : -1;
+        if (jobs[k].n > 64) { which[n_open] = k; open[n_open++] = jobs[k]; }
+    }
+    int32_t h[RK_MODES][RK_SWEEPS];
+    for (int done = 0; done == 0 || (n_open > 0 && done < RK_SWEEPS);) {
+        int upto = done + (done == 0 ? 6 : 2);
+        if (upto > RK_SWEEPS) upto = RK_SWEEPS;
+        for (int sweep = done; sweep < upto && n_open; ++sweep)
+            if (launch_jacobi_sweep(open, n_open, sweep, st) != hipSuccess) return ASI_ERR_HIP;
+        bool asked = false;
+        for (int k = 0; k < n_modes; ++k) {
+            const int count = jobs[k].n > 64 ? upto : (done == 0 && jobs[k].n > 1 ? 1 : 0);
+            if (used[k] >= 0 || count == 0) continue;
+            if (hipMemcpyAsync(h[k], jobs[k].rot, sizeof(int32_t) * count, hipMemcpyDeviceToHost, st) != hipSuccess) return ASI_ERR_HIP;
+            asked = true;
+        }
+        if (asked && hipStreamSynchronize(st) != hipSuccess) return ASI_ERR_HIP;
+        for (int k = 0; k < n_modes && done == 0; ++k)
+            if (jobs[k].n > 1 && jobs[k].n <= 64 && h[k][0] > 0) used[k] = h[k][0];
+        int left = 0;
+        for (int q = 0; q < n_open; ++q) {
+            int at = -1;
+            for (int sweep = done; sweep < upto && at < 0; ++sweep)
+                if (h[which[q]][sweep] == 0) at = sweep + 1;
+            used[which[q]] = at;
+            if (at < 0) { which[left] = which[q]; open[left++] = open[q]; }
+        }
+        n_open = left;
+        done = upto;
+    }
+    grid = gather_modes(jobs, n_modes, [](const SpecJob& j) { return j.n; }, &b);
+    hipLaunchKernelGGL(k_row_norms, dim3((unsigned)grid), 64, 0, st, b);
+    hipLaunchKernelGGL(k_spectrum_finish, dim3((unsigned)grid), 256, 0, st, b);
+    if (hipGetLastError() != hipSuccess) return ASI_ERR_HIP;
+    bool converged = true;
+    for (int k = 0; k < n_modes; ++k) {
+        if (sweeps) sweeps[k] = used[k];
+        converged = converged && used[k] >= 0;
+    }
+    return converged ? ASI_OK : ASI_ERR_NUMERIC;
 }
 
 asi_status asi_mode_spectrum(const asi_tensor_desc* desc, const void* A, int32_t mode, double* eigenvalues,
                              float* eigenvectors, void* ws, size_t ws_bytes, int32_t* sweeps, asi_stream_t stream) {
-    ModeShape ms;
-    asi_status why;
-    if (!parse_mode(desc, mode, &ms, &why)) return why;
-    if (!A || !eigenvalues) return ASI_ERR_INVALID_ARG;
-    const GramPlan p = plan_gram(ms);
-    if (!ws || reinterpret_cast<uintptr_t>(ws) % RK_ALIGN != 0 || ws_bytes < p.bytes) return ASI_ERR_WORKSPACE;
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    char* base = static_cast<char*>(ws);
-    double* part = reinterpret_cast<double*>(base);
-    base += p.part_bytes;
-    double* G = reinterpret_cast<double*>(base); base += p.w_bytes;
-    double* W = reinterpret_cast<double*>(base); base += p.w_bytes;
-    double* norms = reinterpret_cast<double*>(base); base += p.norm_bytes;
-    CholScale* sc = reinterpret_cast<CholScale*>(base); base += align_up(sizeof(CholScale));
-    int32_t* rot = reinterpret_cast<int32_t*>(base);
-    const int n = ms.n;
-
-    GramJob jb;
-    jb.X = A; jb.outer = ms.outer; jb.inner = ms.inner; jb.ncols = ms.ncols; jb.n = n;
-    jb.tiles = p.tiles; jb.nsplit = p.nsplit; jb.nchunks = p.nchunks; jb.part = part;
-    const dim3 grid((unsigned)(p.tiles * p.tiles * p.nsplit));
-    if (ms.bf16) hipLaunchKernelGGL(k_mode_gram<bf16_t>, grid, 256, 0, st, jb);
-    else hipLaunchKernelGGL(k_mode_gram<float>, grid, 256, 0, st, jb);
-    const long long cnt = (long long)n * n;
-    hipLaunchKernelGGL(k_gram_reduce, dim3((unsigned)((cnt + 255) / 256)), 256, 0, st, part, p.nsplit, cnt, G, rot, RK_SWEEPS);
-    // additions behind an entry of G: the columns of a range (64 a chunk), then the ranges
-    const double adds = (double)RK_T * ((p.nchunks + p.nsplit - 1) / p.nsplit) + p.nsplit;
-    hipLaunchKernelGGL(k_chol_scale, dim3(1), 256, 0, st, G, n, (4.0 * n + adds) * 1.1102230246251565e-16, sc);
-    for (int P = 0, nb = (n + RK_CB - 1) / RK_CB; P < nb; ++P) {
-        const int rest = nb - P - 1;
-        hipLaunchKernelGGL(k_chol_panel, dim3((unsigned)(rest > 0 ? rest * (rest + 1) / 2 : 1)), 256, 0, st, G, W, n, P, sc);
-    }
-    if (hipGetLastError() != hipSuccess) return ASI_ERR_HIP;
-
-    // sweeps until a whole one rotates nothing; the counts come back to the host (this entry point iterates to
-    // convergence and therefore waits for the stream)
-    const double tol = 4.0 * n * 2.220446049250313e-16;     // two rows count as orthogonal below the rounding of their dot product
-    int used = 0;
-    bool converged = n == 1;
-    int32_t h[RK_SWEEPS];
-    auto read_counts = [&](int count) {
-        return hipMemcpyAsync(h, rot, sizeof(int32_t) * count, hipMemcpyDeviceToHost, st) == hipSuccess &&
-               hipStreamSynchronize(st) == hipSuccess;
-    };
-    if (n > 1 && n <= 64) {
-        hipLaunchKernelGGL(k_jacobi_small, dim3(1), 512, 0, st, W, n, tol * tol, RK_SWEEPS, rot);
-        if (hipGetLastError() != hipSuccess || !read_counts(1)) return ASI_ERR_HIP;
-        used = h[0];
-        converged = used > 0;
-    } else if (n > 64) {
-        // Sweeps are handed over several at a time (a sweep that follows a converged one returns at once), so that the
-        // host's wait for a count does not stand between every two of them.
-        for (int done = 0; done < RK_SWEEPS && !converged;) {
-            int upto = done + (done == 0 ? 6 : 2);
-            if (upto > RK_SWEEPS) upto = RK_SWEEPS;
-            for (int sweep = done; sweep < upto; ++sweep)
-                if (launch_jacobi_sweep(W, n, tol * tol, sweep ? rot + sweep - 1 : nullptr, rot + sweep, st) != hipSuccess) return ASI_ERR_HIP;
-            if (!read_counts(upto)) return ASI_ERR_HIP;
-            for (int sweep = done; sweep < upto && !converged; ++sweep)
-                if (h[sweep] == 0) { converged = true; used = sweep + 1; }
-            done = upto;
-        }
-    }
-    if (sweeps) *sweeps = converged ? used : -1;
-    hipLaunchKernelGGL(k_row_norms, dim3((unsigned)n), 64, 0, st, W, n, norms, sc);
-    hipLaunchKernelGGL(k_spectrum_finish, dim3((unsigned)n), 256, 0, st, W, n, norms, sc, eigenvalues, eigenvectors);
-    if (hipGetLastError() != hipSuccess) return ASI_ERR_HIP;
-    return converged ? ASI_OK : ASI_ERR_NUMERIC;
+    return asi_mode_spectra(desc, A, &mode, 1, &eigenvalues, &eigenvectors, ws, ws_bytes, sweeps, stream);
 }
 
 asi_status asi_explained_variance_ranks(const double* eigenvalues, int32_t n, const double* eps, int32_t n_eps,

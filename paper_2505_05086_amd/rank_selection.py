@@ -35,19 +35,23 @@ class ModeSpectrum:
 
 def mode_spectrum(A: torch.Tensor, mode: int) -> ModeSpectrum:
     """Squared singular values and left singular vectors of the mode's unfolding (App. A.2)."""
+    return mode_spectra(A, (mode,))[0]
+
+
+def mode_spectra(A: torch.Tensor, modes: Sequence[int]) -> List[ModeSpectrum]:
+    """The spectra of several modes in one call: their iterations run side by side."""
     if not A.is_cuda:
         raise RuntimeError("the ASI path runs on the GPU only (no CPU fallback)")
     A = A.detach().contiguous()
     desc = B.make_desc(tuple(A.shape), (1,) * A.dim(), _dtype_name(A))
-    need = B.asi_mode_spectrum_workspace_bytes(desc, mode)
+    need = B.asi_mode_spectra_workspace_bytes(desc, modes)
     if need == 0:
-        raise B.AsiError(2, "asi_mode_spectrum_workspace_bytes")
-    n = A.shape[mode]
+        raise B.AsiError(2, "asi_mode_spectra_workspace_bytes")
     ws = torch.empty(need, dtype=torch.uint8, device=A.device)
-    lam = torch.empty(n, dtype=torch.float64, device=A.device)
-    vec = torch.empty(n, n, dtype=torch.float32, device=A.device)
-    sweeps = B.asi_mode_spectrum(desc, A, mode, lam, vec, ws)
-    return ModeSpectrum(lam, vec, sweeps)
+    lam = [torch.empty(A.shape[m], dtype=torch.float64, device=A.device) for m in modes]
+    vec = [torch.empty(A.shape[m], A.shape[m], dtype=torch.float32, device=A.device) for m in modes]
+    sweeps = B.asi_mode_spectra(desc, A, modes, lam, vec, ws)
+    return [ModeSpectrum(*s) for s in zip(lam, vec, sweeps)]
 
 
 def explained_variance_ranks(spectra: Sequence[ModeSpectrum], eps: Sequence[float]) -> List[Tuple[int, ...]]:
@@ -81,7 +85,7 @@ def perplexity_row(A: torch.Tensor, grad_out: torch.Tensor, dW_exact: torch.Tens
     A = A.detach().contiguous()
     grad_out = grad_out.detach().contiguous().to(A.dtype)
     dW_exact = dW_exact.detach().contiguous().float()
-    spectra = [mode_spectrum(A, m) for m in range(A.dim())]
+    spectra = mode_spectra(A, range(A.dim()))
     rank_rows = explained_variance_ranks(spectra, eps)
     f32 = dict(dtype=torch.float32, device=A.device)
     fws = torch.empty(B.FROBENIUS_WS_BYTES, dtype=torch.uint8, device=A.device)

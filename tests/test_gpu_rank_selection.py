@@ -269,3 +269,19 @@ def test_spectrum_of_a_tensor_that_is_not_finite(n, what):
     assert not torch.any(sp.eigenvectors)
     if what != "inf":
         assert RS.explained_variance_ranks([sp], (0.5, 0.9)) == [(n,), (n,)]
+
+
+@pytest.mark.parametrize("dims", [(3, 70, 5, 40), (200, 129, 3), (65, 5, 300)])
+def test_spectra_of_several_modes_in_one_call_are_those_of_each_alone(dims):
+    """Modes of one workgroup, of one, two and three register shapes side by side, which converge after different numbers of sweeps: the
+    same bits as one call per mode, in any order."""
+    B, RS = _mods()
+    rng = np.random.default_rng(11)
+    A = torch.from_numpy(_planted(rng, dims, 0.9)).cuda()
+    alone = [RS.mode_spectrum(A, m) for m in range(len(dims))]
+    for modes in (tuple(range(len(dims))), tuple(range(len(dims)))[::-1], (1, 0)):
+        for m, sp in zip(modes, RS.mode_spectra(A, modes)):
+            assert torch.equal(sp.eigenvalues, alone[m].eigenvalues) and torch.equal(sp.eigenvectors, alone[m].eigenvectors)
+            assert sp.sweeps == alone[m].sweeps
+    with pytest.raises(B.AsiError):
+        RS.mode_spectra(A, (0, len(dims)))
