@@ -29,12 +29,12 @@ HEADLINE_CONFIG = 4
 HBM_PEAK_GBS = 8000.0
 # published dense peaks of the units each kernel uses (TFLOP/s); "mfma_f32+f64" is the harmonic
 # mean for a kernel whose flops are half fp32 MFMA (V = A_m^T U) and half fp64 MFMA (P = A_m V)
-PEAK_TFLOPS = {"mfma_f32": 157.3, "mfma_f64": 78.6, "mfma_bf16": 2500.0, "valu_f32": 157.3, "valu_f64": 78.6,
+PEAK_TFLOPS = {"mfma_f32": 157.3, "mfma_f64": 78.6, "mfma_bf16": 2500.0, "mfma_i8": 5000.0, "valu_f32": 157.3, "valu_f64": 78.6,
                "mfma_f32+f64": 2.0 / (1.0 / 157.3 + 1.0 / 78.6), "valu_f32+f64": 2.0 / (1.0 / 157.3 + 1.0 / 78.6),
                "mfma_bf16+f64": 2.0 / (1.0 / 2500.0 + 1.0 / 78.6)}
 # which arithmetic unit each kernel symbol runs its contraction on; a symbol that is not listed is an error
 KERNEL_UNIT = {"k_subspace_small": "mfma_f32+f64", "k_subspace_tiny": "valu_f32+f64", "k_subspace_long": "mfma_f32+f64", "k_subspace_planes": "mfma_f64",
-               "k_subspace_gram": "mfma_f64", "k_gauss_fill": "valu_f64",
+               "k_subspace_gram": "mfma_f64", "k_subspace_gram_digits": "mfma_i8", "k_pair_digits": "mfma_i8", "k_v_digits": "valu_f32", "k_v_max": "valu_f32", "k_amax_bf16": "valu_f32", "k_gauss_fill": "valu_f64",
                "k_ttm_mfma": "mfma_f32", "k_ttm_ksplit": "mfma_f32", "k_ttm_stream": "mfma_f32", "k_ttm_stream_short": "mfma_f32", "k_ttm_stream_bf16": "mfma_bf16", "k_ttm_expand": "mfma_f32", "k_ttm_duo": "mfma_f32", "k_ttm_thin": "valu_f32",
                "k_gemm_bf16": "mfma_bf16", "k_split_bf16": "valu_f32", "k_pair": "mfma_f64",
                "k_corr_mfma": "mfma_f32", "k_corr_mfma_split": "mfma_bf16", "k_corr": "valu_f32",

@@ -95,14 +95,46 @@ struct CompressPlan {
     bool paired = false;             // the last two modes of a 4-mode tensor share one kernel
     bool tiny = false;               // ... the vector-ALU kernel for tiny planes
     bool planes = false;             // ... the Gram-matrix kernel for planes of up to 64 x 64 (asi_planes.hip)
+    bool digm[4] = {};               // bf16: the step on the int8 MFMA (asi_digits.hip), through the Gram matrix or, with bfv, as a pair product
+    unsigned* amax = nullptr;        // ... the tensor's largest magnitude, in parts
+    unsigned char* Vd = nullptr;     // ... V as digits
+    unsigned* vmost = nullptr;
+    double* vscale = nullptr;
     bool fast_orth[4] = {};
     bool wide_orth[4] = {};
     size_t bytes = 0;
 };
 
+// Which modes of a bf16 tensor take the int8 MFMA.  It costs a pass over the tensor for its largest magnitude and saves time that
+// grows with the tensor, in us (fitted to the launches of 64 x 197 x 3072 with ranks 32, 64, 192, of 64 x 197 x 768 with 32, 64, 96 and
+// of 32 x 256 x 768 with 32, 48, 64):
+//   largest magnitude                      15 | 5 | 5
+//   64 entries through the Gram matrix     67 -> 51 | 26 -> 25   (32 entries and fewer: the fp64 form is bound by memory already)
+//   197 | 197 | 256 entries                179 -> 118 | 50 -> 63 | 30 -> 64   (G U and its partial sums are 36 us whatever the tensor; a part
+//                                          of G's blocks cuts the whole tensor again)
+//   last mode, V's digits included         336 -> 126 | 63 -> 41 | 30 -> 28
+void choose_digits(const Shape& s, CompressPlan* p) {
+    if (s.dt != BF16 || s.numel % 8 != 0) return;
+    const double numel = (double)s.numel;
+    double gain = 0.0;
+    bool take[4] = {};
+    for (int m = 0; m < s.d; ++m) {
+        const int n = (int)s.n[m], nb = (n + 15) / 16, rb = (s.r[m] + 15) / 16, parts = (nb * (nb + 1) / 2 + 47) / 48;
+        double g;
+        if (p->gramm[m] && n > 32) g = 5e-7 * numel - 3.5;
+        else if (p->longm[m] && n <= 256) g = (1.12e-6 * rb - 1e-6 * parts) * numel - 36.0;
+        else if (p->bfv[m] && pair_digits_splits(s.numel / n, n, s.r[m])) g = 2.9e-8 * numel * s.r[m] - 8.0;
+        else continue;
+        if (!p->bfv[m] && subspace_gram_digits_nwg(s.outer(m), n, s.inner(m)) == 0) continue;
+        if (g > 2.0) { take[m] = true; gain += g; }
+    }
+    if (gain > 1.3 * (3.0 + 3e-7 * numel) + 3.0)
+        for (int m = 0; m < s.d; ++m) p->digm[m] = take[m];
+}
+
 // cold: the first iteration of Alg. 1 (t = 0).  V is generated inside the P kernel of every mode, so no
-// mode takes a fused V/P kernel and no V is stored.
-CompressPlan plan_compress(const Shape& s, void* ws, bool cold = false) {
+// mode takes a fused V/P kernel and no V is stored.  digits: the int8 MFMA may be used (the activation is aligned).
+CompressPlan plan_compress(const Shape& s, void* ws, bool cold = false, bool digits = false) {
     CompressPlan p;
     Carver c(ws);
     size_t vmax = 0;
@@ -119,6 +151,7 @@ CompressPlan plan_compress(const Shape& s, void* ws, bool cold = false) {
                    gemm_bf16_supported(s.numel / s.n[m], (int)s.n[m], s.r[m]);
         if (p.bfv[m]) ubmax = std::max(ubmax, split_bf16_elems((int)s.n[m], s.r[m]));
     }
+    if (digits && !cold) choose_digits(s, &p);
     p.Ub = c.take<unsigned short>(ubmax);
     size_t vpmax = 0;
     for (int m = 0; m < s.d; ++m) {
@@ -128,6 +161,15 @@ CompressPlan plan_compress(const Shape& s, void* ws, bool cold = false) {
     }
     p.Vpart = c.take<float>(vpmax);
     p.ctr8 = c.take<int32_t>(4 * kOrthCtrs);
+    for (int m = 0; m < s.d; ++m) {
+        if (!p.digm[m]) continue;
+        if (!p.amax) p.amax = c.take<unsigned>(kAmaxParts);
+        if (!p.bfv[m]) continue;
+        const int ns = pair_digits_splits(s.numel / s.n[m], (int)s.n[m], s.r[m]);
+        p.Vd = c.take<unsigned char>(v_digits_bytes(s.numel / s.n[m], s.r[m], ns));
+        p.vmost = c.take<unsigned>(v_digits_most(s.numel / s.n[m], s.r[m]));
+        p.vscale = c.take<double>(v_digits_scales(s.r[m], ns));
+    }
     p.tiny = !cold && s.d == 4 && subspace_tiny_supported((int)s.n[2], (int)s.n[3], s.r[2], s.r[3]);
     p.planes = !cold && s.d == 4 && !p.tiny && subspace_planes_supported(s.n[0] * s.n[1], (int)s.n[2], (int)s.n[3], s.r[2], s.r[3]);
     p.paired = p.tiny || p.planes;
@@ -135,6 +177,7 @@ CompressPlan plan_compress(const Shape& s, void* ws, bool cold = false) {
         const size_t n = (size_t)s.n[m], r = (size_t)s.r[m];
         if (p.tiny && m >= 2) p.nsplit[m] = subspace_tiny_nwg(s.n[0] * s.n[1]);
         else if (p.planes && m >= 2) p.nsplit[m] = subspace_planes_nwg(s.dt, s.n[0] * s.n[1], (int)s.n[2], (int)s.n[3]);
+        else if (p.digm[m]) p.nsplit[m] = p.bfv[m] ? pair_digits_splits(s.numel / s.n[m], (int)n, (int)r) : subspace_gram_digits_nwg(s.outer(m), (int)n, s.inner(m));
         else if (p.gramm[m]) p.nsplit[m] = subspace_gram_nwg(s.dt, s.outer(m), (int)n, s.inner(m));
         else if (p.longm[m]) p.nsplit[m] = subspace_long_splits(s.outer(m), (int)n, s.inner(m), (int)r);
         else p.nsplit[m] = p.fused[m] ? subspace_small_nwg(s.outer(m), (int)n, s.inner(m))
@@ -474,7 +517,8 @@ asi_status build_compress(const asi_tensor_desc* desc, const void* A, const floa
     if (!A || (!cold && !U_prev) || !U_out) return ASI_ERR_INVALID_ARG;
     for (int m = 0; m < s.d; ++m)
         if ((!cold && !U_prev[m]) || !U_out[m]) return ASI_ERR_INVALID_ARG;
-    CompressPlan p = plan_compress(s, ws, cold);
+    CompressPlan p = plan_compress(s, ws, cold, reinterpret_cast<uintptr_t>(A) % 16 == 0);
+    if (p.amax && ws_bytes < p.bytes) p = plan_compress(s, ws, cold);        // (what fitted without the digits still does)
     if (!ws_ok(ws, ws_bytes, p.bytes)) return ASI_ERR_WORKSPACE;
 
     OrthArgs fast, wide, slow;
@@ -507,6 +551,10 @@ asi_status build_compress(const asi_tensor_desc* desc, const void* A, const floa
         preneed[m] = true;
     }
     bool zero_given = false;
+    if (p.amax) {
+        ASI_ADD(pg, "", (double)s.numel * 2.0, 0.0, make_amax_bf16(A, s.numel, p.amax, p.ctr8, 4 * kOrthCtrs, it__));
+        zero_given = true;
+    }
     for (int k = 0; k < nord; ++k) {
         const int m = order[k];
         const long long outer = s.outer(m), inner = s.inner(m);
@@ -524,6 +572,11 @@ asi_status build_compress(const asi_tensor_desc* desc, const void* A, const floa
                                            p.part[3], p.nsplit[m], it__));
         } else if (p.paired && m == 3) {
             // done together with mode 3
+        } else if (p.digm[m] && !p.bfv[m]) {
+            // the Gram matrix of the unfolding on the int8 MFMA, then G U_prev
+            const double cols = (double)outer * (double)inner;
+            ASI_ADD(pg, "", cols * n * 2.0 + 4.0 * n * r + 8.0 * n * r * p.nsplit[m], 4.0 * cols * n * r,
+                    make_subspace_gram_digits(A, outer, n, inner, U_prev[m], r, p.part[m], p.nsplit[m], p.amax, it__));
         } else if (p.longm[m]) {
             // long fibres (64 < n <= 512): V and P from one LDS tile of complete fibres, V never stored
             int32_t* zero = zero_given ? nullptr : p.ctr8;
@@ -558,7 +611,12 @@ asi_status build_compress(const asi_tensor_desc* desc, const void* A, const floa
                 const int ks = p.bfks[m];
                 ASI_ADD(pg, "V", cols * n * 2.0 + 2.0 * (double)split_bf16_elems(n, r) + 4.0 * cols * r * ks, 2.0 * cols * n * r,
                         make_gemm_bf16(A, outer, n, p.Ub, r, ks > 1 ? p.Vpart : p.V, ks, nullptr, 0, it__));
-                if (ks > 1)
+                if (p.digm[m]) {
+                    ASI_ADD(pg, "V", 4.0 * cols * r * (ks > 1 ? ks + 1 : 1), cols * r * ks,
+                            make_v_digits(ks > 1 ? p.Vpart : p.V, ks, p.V, outer, r, p.nsplit[m], p.vmost, p.Vd, p.vscale, 0, it__));
+                    ASI_ADD(pg, "V", 4.0 * cols * r + (double)v_digits_bytes(outer, r, p.nsplit[m]), cols * r,
+                            make_v_digits(ks > 1 ? p.Vpart : p.V, ks, p.V, outer, r, p.nsplit[m], p.vmost, p.Vd, p.vscale, 1, it__));
+                } else if (ks > 1)
                     ASI_ADD(pg, "V", 4.0 * cols * r * (ks + 1), cols * r * ks,
                             make_sum_partials(p.Vpart, ks, (long long)outer * r, p.V, 0, it__));
             } else {
@@ -579,6 +637,10 @@ asi_status build_compress(const asi_tensor_desc* desc, const void* A, const floa
             if (cold)
                 ASI_TRYS(add_pair_gauss(pg, "P", s.dt, A, outer, n, inner, *seed, m, r, p.part[m], p.nsplit[m], zero, 4 * kOrthCtrs,
                                         ride.njobs ? &ride : nullptr, ride_b));
+            else if (p.digm[m])
+                ASI_ADD(pg, "P", (double)s.numel * 2.0 + (double)v_digits_bytes(outer, r, p.nsplit[m]) + 8.0 * n * r * p.nsplit[m] + ride_b,
+                        2.0 * (double)s.numel * r,
+                        make_pair_digits(A, outer, n, p.V, p.Vd, p.vscale, r, p.part[m], p.nsplit[m], p.amax, ride.njobs ? &ride : nullptr, it__));
             else
                 ASI_TRYS(add_pair(pg, "P", s.dt, A, outer, n, inner, p.V, r, p.part[m], p.nsplit[m], zero, 4 * kOrthCtrs,
                                   ride.njobs ? &ride : nullptr, ride_b));
@@ -947,7 +1009,7 @@ size_t asi_workspace_bytes(const asi_tensor_desc* desc, const asi_conv2d_desc* c
     asi_status why;
     if (!parse_desc(desc, &s, &why)) return 0;
     size_t need = std::max(plan_compress(s, nullptr).bytes, plan_core(s, nullptr).bytes);
-    need = std::max(need, plan_compress(s, nullptr, true).bytes);
+    need = std::max(need, std::max(plan_compress(s, nullptr, true).bytes, plan_compress(s, nullptr, false, true).bytes));
     if (conv) {
         ConvGeom cg;
         if (!parse_conv(s, conv, &cg)) return 0;

@@ -20,7 +20,7 @@ constexpr int kItemArgMax = 640;     // bytes of the largest per-layer argument 
 enum ItemKind {
     IT_TTM = 1, IT_KSPLIT, IT_PAIR, IT_SMALL, IT_PRESUM, IT_GRAM0, IT_APPLY, IT_ORTHW_GRAM, IT_ORTHW_CHOL,
     IT_ORTHW_APPLY, IT_ORTH_BIG, IT_CORR_MFMA, IT_CORR, IT_SUM_F32, IT_SUM_F64, IT_EXPAND, IT_INIT, IT_TINY, IT_TTM_DUO, IT_TTM_STREAM, IT_TTM_EXPAND,
-    IT_LONG, IT_PLANES, IT_SPLIT_BF16, IT_GEMM_BF16, IT_GAUSS, IT_GRAM_MODE, IT_DW_FOLD, IT_Z_PLANES, IT_CORE_PLANES, IT_ORTHW_GSUM
+    IT_LONG, IT_PLANES, IT_SPLIT_BF16, IT_GEMM_BF16, IT_GAUSS, IT_GRAM_MODE, IT_DW_FOLD, IT_Z_PLANES, IT_CORE_PLANES, IT_ORTHW_GSUM, IT_DIGITS
 };
 
 struct Item {
@@ -221,6 +221,28 @@ int subspace_gram_nwg(DType xt, long long outer, int n, long long inner);
 bool make_subspace_gram(DType xt, const void* X, long long outer, int n, long long inner, const float* U, int r, double* part,
                         int nwg, int32_t* zero, int nzero, Item* out);
 hipError_t launch_gram_items(const Item* const* items, int n, hipStream_t st);
+
+// ---- subspace steps of bf16 tensors on the int8 MFMA (asi_digits.hip) -----------------------------------------
+// All of them read the tensor's largest magnitude, which a pass of its own leaves as kAmaxParts partial maxima (numel a multiple of
+// eight, X 16-byte aligned; the same holds for the Gram form).
+constexpr int kAmaxParts = 512;
+bool make_amax_bf16(const void* X, long long numel, unsigned* out_max, int32_t* zero, int nzero, Item* out);
+// P = (A_m A_m^T) U_prev for modes of 33 to 256 entries over an inner extent that is a multiple of eight: part is (nwg, n, r); 0: not
+// supported
+int subspace_gram_digits_nwg(long long outer, int n, long long inner);
+bool make_subspace_gram_digits(const void* X, long long outer, int n, long long inner, const float* U, int r, double* part, int nwg,
+                               const unsigned* amax, Item* out);
+// P = A_m V along a last mode: V, given as ks partial products, as digits (make_v_digits), then the product; part is (nsplit, n, r);
+// no splits: not supported
+int pair_digits_splits(long long ncols, int n, int r);
+size_t v_digits_bytes(long long ncols, int r, int nsplit);
+size_t v_digits_scales(int r, int nsplit);
+size_t v_digits_most(long long ncols, int r);
+bool make_v_digits(const float* V, int ks, float* sum, long long ncols, int r, int nsplit, unsigned* most, unsigned char* digits, double* scales,
+                   int step, Item* out);        // step 0: sums and largest magnitudes, step 1: the digits
+bool make_pair_digits(const void* X, long long ncols, int n, const float* V, const unsigned char* digits, const double* scales, int r, double* part,
+                      int nsplit, const unsigned* amax, const PresumArgs* pre, Item* out);
+hipError_t launch_digits_items(const Item* const* items, int n, hipStream_t st);
 
 // ---- fused V/P step for modes with n <= 64 (asi_subspace.hip): part is (nwg, n, r) fp64 ---------------
 bool subspace_small_supported(int n, int r);

@@ -92,3 +92,82 @@ def test_split_correlation_of_an_entry_without_finite_terms(value):
         assert float((dW[66] - want[66]).abs().max() / want[66].abs().max()) <= 1e-5
     else:
         assert not bool(torch.isfinite(dW[66]).any())
+
+
+def _exact_factor(A, u, mode):
+    """Q of P = A_m (A_m^T u) in float64, positive diagonal of R."""
+    m = A.double().movedim(mode, 0).reshape(A.shape[mode], -1)
+    P = torch.zeros(u.shape, dtype=torch.float64, device="cuda")
+    for c in range(0, m.shape[1], 1 << 18):
+        a = m[:, c:c + (1 << 18)].contiguous()
+        P += a @ (a.t().contiguous() @ u.double())
+    Q, R = torch.linalg.qr(P.cpu())
+    return (Q * torch.sign(torch.diagonal(R))).cuda()
+
+
+def _low_rank(rng, dims, ranks):
+    x = torch.from_numpy(rng.standard_normal(ranks).astype(np.float32)).cuda()
+    U = _factors(rng, dims, ranks)
+    for u in U:
+        x = torch.tensordot(x, u.t().contiguous(), dims=([0], [0]))
+    return x / x.square().mean().sqrt(), U
+
+
+# 40 batch entries (three row blocks, the last ragged) and 130 tokens (nine, 45 blocks in one part) or 240 (fifteen, 120 blocks in
+# three parts), inner extents that end inside a tile; hidden modes and columns that are no multiple of 64, ranks that fill one, two and
+# three blocks per wave and not.  `small`: nothing below the last digit; scattered values (the list); whole slices of every mode
+# (more than the list holds: the second walk).
+@pytest.mark.parametrize("dims,ranks,kernels", [
+    ((40, 130, 3400), (20, 64, 70), ("gram_digits<4>", "gram_digits<1>", "pair_digits<2>")),
+    ((38, 240, 2504), (12, 60, 60), ("gram_digits<4>", "pair_digits<1>")),
+    ((24, 240, 5000), (12, 64, 34), ("gram_digits<1>", "pair_digits<1>")),
+    ((17, 251, 1000), (9, 20, 150), ("pair_digits<3>",)),
+])
+@pytest.mark.parametrize("small", ["none", "scattered", "slices"])
+def test_steps_on_digits_against_float64(dims, ranks, kernels, small):
+    """Factors of one step from a nearby basis.  fp32 rounding of the result is 3e-8; the hidden mode's V has its factor in two bf16
+    terms (2^-17), which the conditioning of these tensors (all directions of similar weight) hardly amplifies: 1e-5."""
+    from paper_2505_05086_amd import binding as B
+    rng = np.random.default_rng(sum(dims))
+    x, U = _low_rank(rng, dims, ranks)
+    g = torch.Generator("cuda").manual_seed(1)
+    x += 1e-3 * torch.randn(dims, device="cuda", generator=g)
+    if small == "scattered":
+        x[torch.rand(dims, device="cuda", generator=g) < 1e-5] *= 1e-7
+    elif small == "slices":
+        x[:3] *= 1e-7
+        x[:, ::7] *= 1e-8
+        x[:, :, 5::9] *= 3e-8
+    A = x.to(torch.bfloat16).contiguous()
+    prev = [torch.linalg.qr((u + 0.02 / u.shape[0] ** 0.5 * torch.randn(u.shape, device="cuda", generator=g)).cpu())[0].cuda().contiguous() for u in U]
+    desc = B.make_desc(dims, ranks, "bf16")
+    outs, info = [], torch.zeros(1, dtype=torch.int32, device="cuda")
+    ws = B.alloc_workspace(desc, None, 0)
+    for _ in range(2):
+        out = [torch.empty_like(u) for u in prev]
+        ws.fill_(255)
+        sites = _sites(lambda: B.asi_compress(desc, A, prev, out, ws, info))
+        outs.append(out)
+    for k in kernels:
+        assert any(k in s for s in sites), (k, sites)
+    assert int(info.item()) == 0
+    for m in range(3):
+        assert torch.equal(outs[0][m], outs[1][m]), m      # the same sums in every run
+        want = _exact_factor(A, prev[m], m)
+        err = float((outs[0][m] - want).norm() / want.norm())
+        assert err <= (1e-5 if m == 2 else 1e-6), (m, err)
+
+
+def test_steps_on_digits_report_a_tensor_that_is_not_finite():
+    from paper_2505_05086_amd import binding as B
+    dims, ranks = (40, 130, 3400), (20, 64, 70)
+    rng = np.random.default_rng(5)
+    x, U = _low_rank(rng, dims, ranks)
+    A = x.to(torch.bfloat16).contiguous()
+    A[3, 7, 11] = float("inf")
+    desc = B.make_desc(dims, ranks, "bf16")
+    out, info = [torch.empty_like(u) for u in U], torch.zeros(1, dtype=torch.int32, device="cuda")
+    sites = _sites(lambda: B.asi_compress(desc, A, U, out, B.alloc_workspace(desc, None, 0), info))
+    assert any("digits" in s for s in sites), sites
+    assert int(info.item()) != 0
+    assert all(not bool(torch.isfinite(u).any()) for u in out)
