@@ -22,7 +22,7 @@ struct CorrPlan {
     int ni;          // core channels i per chunk
     int ow;          // groups of eight output positions per output row
     int nk;          // K blocks (four such groups) per chunk
-    int px;          // slab row pitch
+    int px;          // slab row pitch (stride two: the even entries, then the odd ones)
     int zj, zi, zt;  // from one core channel j, core channel i, bf16 term to the next
 };
 
@@ -38,7 +38,7 @@ struct CorrJob {
 
 inline long long corr_plan_tiles(const CorrGeom& g) { return (long long)((g.cout + CR_TO - 1) / CR_TO) * ((g.r2 + 15) / 16); }
 
-// split form: chooses the chunk for a geometry that it takes (3 x 3 taps, unit stride and dilation along W)
+// split form: chooses the chunk for a geometry that it takes (3 x 3 taps, a stride of one or two and unit dilation along W)
 bool corr_split_plan(const CorrGeom& g, CorrPlan* p, bool* cut);
 hipError_t launch_corr_split(const Batch<CorrJob>& b, dim3 grid, hipStream_t st);
 

@@ -1,4 +1,4 @@
-// Step 4 of Eq. 14 on fp32 MFMA (3 x 3 taps with unit stride and dilation along W: asi_corr_split.hip):
+// Step 4 of Eq. 14 on fp32 MFMA (3 x 3 taps with a stride of one or two and unit dilation along W: asi_corr_split.hip):
 //     T[o,j,kh,kw] = sum_{i,y,x} G1[i,o,y,x] * Zpad[i,j, y*s - p + kh*d, x*s - p + kw*d]
 // an implicit GEMM with M = cout (o), N = (tap, j), K = (i, y, x).  A workgroup owns 64
 // output channels x 16 core channels j x all taps and walks its share of K in chunks of one
@@ -34,9 +34,9 @@ constexpr int CR_NT = 64 * CR_NW;
 constexpr int CR_KG = CR_NW / 4;     // K-step groups
 
 // instantiation for a plan: low nibble 0 = <1,true,V>, 1 = <9,true,V>, 2 = <9,false,V>, 3 = <25,false,V>, V = the high nibble: 1 for
-// short slabs; 0x100 the split-bf16 form
+// short slabs; 0x100 the split-bf16 form, 0x101 with a stride of two along W
 static unsigned corr_plan_key(const CorrGeom& g, const CorrPlan& p) {
-    if (p.split) return 0x100u;
+    if (p.split) return g.sw == 2 ? 0x101u : 0x100u;
     const int taps = g.kh * g.kw;
     return (taps == 1 ? 0u : (taps == 9 ? 1u : (taps < 9 ? 2u : 3u))) | (p.zld * 16 <= CR_ZMAX_SHORT ? 0x10u : 0u);
 }
@@ -441,7 +441,7 @@ bool make_corr(const float* G1, const float* Z, float* Tpart, const CorrGroup& g
         const int taps = g.kh * g.kw;
         out->kind = IT_CORR_MFMA;
         out->key = corr_plan_key(g, jb.pl);
-        if (jb.pl.split) std::snprintf(out->label, sizeof(out->label), "k_corr_mfma_split<9, %s>", g.Wo % 8 ? "true" : "false");
+        if (jb.pl.split) std::snprintf(out->label, sizeof(out->label), "k_corr_mfma_split<9, %s, %d>", g.Wo % 8 ? "true" : "false", g.sw);
         else std::snprintf(out->label, sizeof(out->label), "k_corr_mfma<%d, %s, %s>", taps == 1 ? 1 : (taps <= 9 ? 9 : 25),
                            (taps == 1 || taps == 9) ? "true" : "false", (out->key >> 4) ? "true" : "false");
     } else {
@@ -466,7 +466,7 @@ hipError_t launch_corr_items(const Item* const* items, int n, hipStream_t st) {
         hipLaunchKernelGGL(k_corr, grid, 256, 0, st, b);
         return hipGetLastError();
     }
-    if (items[0]->key == 0x100u) return launch_corr_split(b, grid, st);
+    if (items[0]->key >= 0x100u) return launch_corr_split(b, grid, st);
     // LDS is dynamic: most instantiations need more than the 64 KB a static array may take
 #define ASI_CORR_LAUNCH(MAXT, EXACT, SHORT)                                                                        \
     do {                                                                                                           \

@@ -1,5 +1,5 @@
-// Step 4 of Eq. 14 for 3 x 3 taps with unit stride and dilation along W, on the bf16 MFMA:
-//     T[o,j,kh,kw] = sum_{i,y,x} G1[i,o,y,x] * Zpad[i,j, y*s - p + kh*d, x - p + kw]
+// Step 4 of Eq. 14 for 3 x 3 taps with a stride of one or two and unit dilation along W, on the bf16 MFMA:
+//     T[o,j,kh,kw] = sum_{i,y,x} G1[i,o,y,x] * Zpad[i,j, y*s - p + kh*d, x*t - p + kw]
 // The same implicit GEMM as asi_corr.hip (M = o, N = (tap, j), K = (i, y, x); a workgroup owns 64 output channels x 16 core
 // channels x 9 taps and walks its share of K in chunks), with every fp32 operand as the exact sum of three bf16 terms
 // (x = h + m + l, eight significant bits each, rounded to nearest): a product is the six term products h h, h m, m h, m m, h l,
@@ -9,15 +9,17 @@
 //
 // A K slot group of a lane is eight consecutive output positions x of one row (rows are padded to a multiple of eight with
 // zeros of G1).  Their B operands for the three taps of a kernel row are three windows of ten consecutive entries of a slab
-// row: one 16-byte and one 4-byte LDS read per term, the middle window by byte alignment.  Z slabs are cut into terms
+// row: one 16-byte and one 4-byte LDS read per term, the middle window by byte alignment.  With a stride of two the even and the
+// odd entries of a slab row are kept apart: the taps 0 and 2 are two windows of the one, tap 1 a window of the other.  Z slabs are cut into terms
 // when they are stored to LDS (each serves 64 output channels); G1 goes from memory to the registers of the one wave
 // that multiplies it and is cut there, one K block ahead of its products.
 //
-// Against the fp32 form, us: 256 x 48 x 9 over 8 x 64 x 64 84 -> 56, 128 x 32 x 9 over 16 x 56 x 56 48 -> 36, three of 512 x 48 x 9
-// over 16 x 7 x 7 31 -> 21, 960 x 40 x 9 over 24 x 7 x 7 28 -> 18.5, 1024 x 64 x 9 over 32 x 14 x 14 120 -> 62; small layers
-// (10 to 15 us, first loads and result) equal or 1 to 2 less.  Bound: a chunk of 256 positions is 3.3 us of products beside
-// 3 us of vector instructions (200 a K block for the cuts, shifts and copies, 45 a pair of Z), which a SIMD issues one
-// after the other.  Error of the weight gradient against 64 bits: 0.94 of the fp32 form's on average, 40 layers.
+// Against the fp32 form, us: 256 x 48 x 9 over 8 x 64 x 64 84 -> 49, 128 x 32 x 9 over 16 x 56 x 56 48 -> 35, three of 512 x 48 x 9
+// over 16 x 7 x 7 31 -> 21, 960 x 40 x 9 over 24 x 7 x 7 28 -> 18.5, 1024 x 64 x 9 over 32 x 14 x 14 118 -> 78, stride two: 512 x 64 x 9
+// over 16 x 14 x 14 44 -> 29; small layers (10 to 15 us, first loads and result) equal or 1 to 2 less.  Bound: a chunk of 256
+// positions is 3.3 us of products beside 3 us of vector instructions (200 a K block for the cuts, shifts and copies, 45 a pair of Z),
+// which a SIMD issues one after the other.  Error of the weight gradient against 64 bits: 0.94 of the fp32 form's on average over
+// 40 layers.
 #include "asi_corr.h"
 #include "asi_device.h"
 #include "asi_lds.h"
@@ -46,7 +48,10 @@ static size_t split_lds(const CorrPlan& p) {
 }
 
 // The chunk (ry rows of a map, or ni whole maps) with the fewest cycles for a workgroup's share of K, `want` splits or fewer: a
-// round of the eight waves is 2 x 108 products on each SIMD; storing 512 pairs of Z and the barrier come on top.
+// round of the eight waves is 2 x 108 products on each SIMD and the vector instructions around them; cutting and storing 512 pairs of
+// Z and the barrier come on top (15.8 thousand cycles for a chunk of 256 positions of 64 x 64 maps).
+constexpr double CS_ROUND = 5500.0;
+static double store_cycles(const CorrGeom& g) { return g.sw == 1 ? 500.0 : 1100.0; }
 static bool choose_chunk(const CorrGeom& g, long long want, CorrPlan* p) {
     const long long map = (long long)g.cout * g.Ho * g.Wo;
     double best = 0.0;
@@ -59,12 +64,12 @@ static bool choose_chunk(const CorrGeom& g, long long want, CorrPlan* p) {
             q.ow = (g.Wo + 7) / 8;
             q.nyc = (g.Ho + ry - 1) / ry;
             q.rows_in = (ry - 1) * g.sh + 2 * g.dh + 1;
-            q.wp = g.Wo + 2;
+            q.wp = (g.Wo - 1) * g.sw + 3;
             const long long oct = (long long)ni * ry * q.ow, pairs = (long long)ni * 16 * q.rows_in * ((q.wp + 1) / 2);
             if (oct > CS_MAX_OCT || pairs > CS_NP * CS_NT || q.rows_in > 255) break;
             if (4 * ni * map >= (1LL << 30)) break;
             q.nk = (int)(oct + 3) / 4;
-            q.px = 8 * q.ow + 8;
+            q.px = g.sw * (8 * q.ow + 8);
             q.zj = q.rows_in * q.px;
             if (q.zj / 8 % 2 == 0) q.zj += 8;            // lanes (j) an odd number of 16-byte pieces apart: no two on one bank
             q.zi = 16 * q.zj;
@@ -74,7 +79,7 @@ static bool choose_chunk(const CorrGeom& g, long long want, CorrPlan* p) {
             const long long w = want < q.nchunks ? want : q.nchunks;
             q.cps = (int)((q.nchunks + w - 1) / w);
             q.nsplit = (q.nchunks + q.cps - 1) / q.cps;
-            const double cost = q.cps * (3700.0 * ((q.nk + CS_KG - 1) / CS_KG) + 220.0 * ((pairs + CS_NT - 1) / CS_NT) + 600.0);
+            const double cost = q.cps * (CS_ROUND * ((q.nk + CS_KG - 1) / CS_KG) + store_cycles(g) * ((pairs + CS_NT - 1) / CS_NT) + 1000.0);
             if (best == 0.0 || cost < best) { best = cost; *p = q; }
         }
     return best > 0.0;
@@ -82,13 +87,15 @@ static bool choose_chunk(const CorrGeom& g, long long want, CorrPlan* p) {
 
 bool corr_split_plan(const CorrGeom& g, CorrPlan* p, bool* cut) {
     *cut = false;
-    if (g.kh != 3 || g.kw != 3 || g.sw != 1 || g.dw != 1 || g.Wo > 64) return false;
+    if (g.kh != 3 || g.kw != 3 || g.sw > 2 || g.dw != 1 || g.Wo > 64) return false;
     if ((long long)g.r1 * g.cout * g.Ho * g.Wo >= (1LL << 31) || (long long)g.r1 * g.r2 * g.H * g.W >= (1LL << 31)) return false;
-    // One workgroup per CU (registers) at most, and no more splits than pay: a split costs its share of the next launch, 100
-    // cycles and a partial tensor written and read at some 2 TB/s (320 workgroups of 24 x 16 x 9 over 7 x 7: the expansion 12 us
-    // instead of 5).
-    const double tbytes = 36.0 * g.cout * g.r2, kblocks = (double)g.r1 * g.Ho * ((g.Wo + 7) / 8) / 4;
-    const long long even = 1 + (long long)sqrt(3700.0 / CS_KG * kblocks / (100.0 + 1e-3 * tbytes));
+    // One workgroup per CU (registers) at most, and no more splits than pay: a split takes its share of the walk, and costs the next
+    // launch 200 cycles (a round of 16 loads is 1.3 us) and a partial tensor written and read at some 2 TB/s.  Correlation +
+    // expansion, splits: 32 x 8 x 9 over 4 x 16 x 16, 16 | 64: 8.7 + 4.0 | 8.5 + 7.2 us; 64 x 16 x 9 over 24 x 7 x 7, 12 | 72: 11.5 + 4.0 |
+    // 10.9 + 8.2; 128 x 32 x 9 over 8 x 23 x 23 at stride 2, 22 | 48: 21.4 + 6.2 | 16.0 + 7.3.
+    const double rounds = (double)g.r1 * g.Ho * ((g.Wo + 7) / 8) / (4.0 * CS_KG);
+    const double stores = (double)g.r1 * g.Ho * g.sh * 16 * (((g.Wo - 1) * g.sw + 4) / 2) / CS_NT;
+    const long long even = 1 + (long long)sqrt((1.3 * CS_ROUND * rounds + store_cycles(g) * stores) / (200.0 + 36e-3 * g.cout * g.r2));
     long long want = 256 / corr_plan_tiles(g);
     if (want > even) want = even;
     if (want < 1) want = 1;
@@ -121,8 +128,8 @@ __device__ __forceinline__ v4f mfma_bf16(v4u a, v4u b, v4f c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
 }
 
-// RAGGED: output rows are no multiple of eight, the positions past a row's end are cleared
-template <int TAPS, bool RAGGED>
+// RAGGED: output rows are no multiple of eight, the positions past a row's end are cleared.  SW: stride along W
+template <int TAPS, bool RAGGED, int SW>
 __global__ __launch_bounds__(CS_NT) void k_corr_mfma_split(Batch<CorrJob> bt) {
     static_assert(TAPS == 9, "written for 3 x 3 taps");
     int lb;
@@ -173,7 +180,7 @@ __global__ __launch_bounds__(CS_NT) void k_corr_mfma_split(Batch<CorrJob> bt) {
             fix1 |= (in && x1 == c1) ? (1u << u) : 0u;
             step1 |= c1 != c0 ? (1u << u) : 0u;
             off_z[u] = e < pairs ? (unsigned)((ii * g.r2 + min(j, g.r2 - 1)) * HW + c0) : 0u;
-            meta_z[u] = e < pairs ? row | (ii << 8) | ((ii * pl.zi + jl * pl.zj + row * pl.px + 2 * m) << 12) : -1;
+            meta_z[u] = e < pairs ? row | (ii << 8) | ((ii * pl.zi + jl * pl.zj + row * pl.px + (SW == 1 ? 2 * m : m)) << 12) : -1;
         }
     }
     float z0[CS_NP], z1[CS_NP];
@@ -200,9 +207,16 @@ __global__ __launch_bounds__(CS_NT) void k_corr_mfma_split(Batch<CorrJob> bt) {
                 unsigned h, m, l;
                 split_pair(((zrow & fix0) >> u) & 1u ? z0[u] : 0.f, ((zrow & fix1) >> u) & 1u ? z1[u] : 0.f, h, m, l);
                 unsigned short* d = b + (meta_z[u] >> 12);
-                *reinterpret_cast<unsigned*>(d) = h;
-                *reinterpret_cast<unsigned*>(d + pl.zt) = m;
-                *reinterpret_cast<unsigned*>(d + 2 * pl.zt) = l;
+                if constexpr (SW == 1) {
+                    *reinterpret_cast<unsigned*>(d) = h;
+                    *reinterpret_cast<unsigned*>(d + pl.zt) = m;
+                    *reinterpret_cast<unsigned*>(d + 2 * pl.zt) = l;
+                } else {                                 // an even and an odd entry
+                    const int odd = pl.px >> 1;
+                    d[0] = (unsigned short)h; d[odd] = (unsigned short)(h >> 16);
+                    d[pl.zt] = (unsigned short)m; d[pl.zt + odd] = (unsigned short)(m >> 16);
+                    d[2 * pl.zt] = (unsigned short)l; d[2 * pl.zt + odd] = (unsigned short)(l >> 16);
+                }
             }
     };
 
@@ -292,14 +306,19 @@ __global__ __launch_bounds__(CS_NT) void k_corr_mfma_split(Batch<CorrJob> bt) {
             const unsigned short* zb = buf + cur * bufsz + a_org + ll * pl.zj;
             if (kb + CS_KG < pl.nk) fetch_a(c_i, c_y, kb + CS_KG);
             else if (more) fetch_a(n_i, n_y, kgrp);
-            unsigned w[2][3][5];
-            auto window = [&](int kh, unsigned (&d)[3][5]) __attribute__((always_inline)) {
+            constexpr int WD = SW == 1 ? 5 : 9;          // dwords of a window; stride two: five even, four odd
+            unsigned w[2][3][WD];
+            auto window = [&](int kh, unsigned (&d)[3][WD]) __attribute__((always_inline)) {
 #pragma unroll
                 for (int t = 0; t < 3; ++t) {
                     const unsigned short* zr = zb + t * pl.zt + kh * khs;
                     const v4u q = *reinterpret_cast<const v4u*>(zr);
                     d[t][0] = q[0]; d[t][1] = q[1]; d[t][2] = q[2]; d[t][3] = q[3];
                     d[t][4] = *reinterpret_cast<const unsigned*>(zr + 8);
+                    if constexpr (SW == 2) {
+                        const v4u o = *reinterpret_cast<const v4u*>(zr + (pl.px >> 1));
+                        d[t][5] = o[0]; d[t][6] = o[1]; d[t][7] = o[2]; d[t][8] = o[3];
+                    }
                 }
             };
             window(0, w[0]);
@@ -307,15 +326,22 @@ __global__ __launch_bounds__(CS_NT) void k_corr_mfma_split(Batch<CorrJob> bt) {
             for (int kh = 0; kh < 3; ++kh) {
                 if (kh < 2) window(kh + 1, w[(kh + 1) & 1]);
                 __builtin_amdgcn_sched_barrier(0);
-                const unsigned (&d)[3][5] = w[kh & 1];
+                const unsigned (&d)[3][WD] = w[kh & 1];
                 v4u b[3][3];                             // [tap of the row][term]
 #pragma unroll
                 for (int t = 0; t < 3; ++t) {
                     b[0][t] = (v4u){d[t][0], d[t][1], d[t][2], d[t][3]};
+                    v4u next;                            // the window one entry on
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) b[1][t][q] = __builtin_amdgcn_alignbit(d[t][q + 1], d[t][q], 16);
+                    for (int q = 0; q < 4; ++q) next[q] = __builtin_amdgcn_alignbit(d[t][q + 1], d[t][q], 16);
+                    if constexpr (SW == 1) {
+                        b[1][t] = next;
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) b[2][t][q] = copy(d[t][q + 1]);
+                        for (int q = 0; q < 4; ++q) b[2][t][q] = copy(d[t][q + 1]);
+                    } else {
+                        b[1][t] = (v4u){d[t][WD - 4], d[t][WD - 3], d[t][WD - 2], d[t][WD - 1]};
+                        b[2][t] = next;
+                    }
                 }
                 // small terms first; six accumulators take turns
                 constexpr int TA[6] = {2, 0, 1, 1, 0, 0}, TB[6] = {0, 2, 1, 0, 1, 0};
@@ -379,7 +405,7 @@ __global__ __launch_bounds__(CS_NT) void k_corr_mfma_split(Batch<CorrJob> bt) {
                         const float* gp = G1 + ((long long)i * g.cout + o) * HoWo + (long long)y * g.Wo;
                         const float* zp = Z + ((long long)i * g.r2 + j0 + jl) * HW + (long long)yy * g.W;
                         for (int x = 0; x < g.Wo; ++x) {
-                            const int xx = x - g.pw + kw;
+                            const int xx = x * SW - g.pw + kw;
                             if (xx >= 0 && xx < g.W) v = fmaf(gp[x], zp[xx], v);
                         }
                     }
@@ -389,14 +415,15 @@ __global__ __launch_bounds__(CS_NT) void k_corr_mfma_split(Batch<CorrJob> bt) {
     }
 }
 
-template <bool RAGGED>
+template <bool RAGGED, int SW>
 static hipError_t launch_split(const Batch<CorrJob>& b, dim3 grid, size_t lds, hipStream_t st) {
     static LdsAllowed allowed;
-    const hipError_t e = allow_lds(reinterpret_cast<const void*>(k_corr_mfma_split<9, RAGGED>), CS_LDS_MAX, allowed);
+    const hipError_t e = allow_lds(reinterpret_cast<const void*>(k_corr_mfma_split<9, RAGGED, SW>), CS_LDS_MAX, allowed);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_corr_mfma_split<9, RAGGED>), grid, CS_NT, lds, st, b);
+    hipLaunchKernelGGL((k_corr_mfma_split<9, RAGGED, SW>), grid, CS_NT, lds, st, b);
     return hipGetLastError();
 }
+// (the layers of a launch have one stride along W)
 hipError_t launch_corr_split(const Batch<CorrJob>& b, dim3 grid, hipStream_t st) {
     size_t lds = 0;
     bool ragged = false;
@@ -404,7 +431,8 @@ hipError_t launch_corr_split(const Batch<CorrJob>& b, dim3 grid, hipStream_t st)
         lds = split_lds(b.job[j].pl) > lds ? split_lds(b.job[j].pl) : lds;
         ragged = ragged || b.job[j].g.Wo % 8 != 0;
     }
-    return ragged ? launch_split<true>(b, grid, lds, st) : launch_split<false>(b, grid, lds, st);
+    if (b.job[0].g.sw == 2) return ragged ? launch_split<true, 2>(b, grid, lds, st) : launch_split<false, 2>(b, grid, lds, st);
+    return ragged ? launch_split<true, 1>(b, grid, lds, st) : launch_split<false, 1>(b, grid, lds, st);
 }
 
 }  // namespace asi

@@ -27,21 +27,27 @@ def _dense_dw(S, U, gy, stride, pad, dil):
     for u in U:
         x = torch.tensordot(x, u.double().t().contiguous(), dims=([0], [0]))
     x = torch.nn.functional.pad(x, (pad[1], pad[1], pad[0], pad[0]))
-    ho, wo = gy.shape[2:]
+    ho, wo = gy.shape[2:]                                # (dilation along H only)
     g2 = gy.double().transpose(0, 1).reshape(gy.shape[1], -1).contiguous()
     out = torch.empty(gy.shape[1], x.shape[1], 3, 3, dtype=torch.float64, device="cuda")
     for a in range(3):
         for b in range(3):
-            xs = x[:, :, a * dil[0]:a * dil[0] + (ho - 1) * stride[0] + 1:stride[0], b:b + wo]
+            xs = x[:, :, a * dil[0]:a * dil[0] + (ho - 1) * stride[0] + 1:stride[0], b:b + (wo - 1) * stride[1] + 1:stride[1]]
             out[:, :, a, b] = g2 @ xs.transpose(0, 1).reshape(x.shape[1], -1).t().contiguous()
     return out
 
 
 # Output rows of one position, one short of / just past a group of eight and of the widest map; maps with fewer core channels
 # than a chunk takes and with a ragged last chunk of rows; channels past a tile of 64, core channels past one of 16; strides and
-# dilations along H, paddings other than 1 (0: windows that end at the map's edge; 2: more positions than the map is wide).
+# dilations along H, paddings other than 1 (0: windows that end at the map's edge; 2: more positions than the map is wide); the same
+# with a stride of two along W over maps of odd and even width.
 @pytest.mark.parametrize("dims,ranks,cout,stride,pad,dil", [
     ((5, 20, 3, 3), (3, 17, 2, 2), 65, 1, 0, 1),
+    ((5, 20, 3, 4), (3, 17, 2, 2), 65, (1, 2), 0, 1),
+    ((6, 18, 17, 15), (6, 18, 5, 5), 66, (2, 2), 1, 1),
+    ((3, 12, 30, 34), (3, 12, 6, 6), 20, (2, 2), 1, 1),
+    ((2, 10, 21, 127), (2, 9, 6, 9), 18, (1, 2), 1, 1),
+    ((2, 10, 20, 61), (2, 9, 6, 9), 18, (2, 2), 2, 2),
     ((6, 33, 7, 7), (5, 16, 4, 4), 64, 1, 1, 1),
     ((9, 18, 8, 9), (9, 18, 5, 5), 63, 1, 1, 1),
     ((4, 24, 17, 18), (3, 9, 6, 6), 130, 1, 0, 1),
@@ -54,9 +60,10 @@ def test_split_correlation_at_the_edges_of_its_tiles(dims, ranks, cout, stride, 
     """Bound: fp32 sums of K products, K up to 4000, are off by about sqrt(K) 2^-25 of a typical entry; 1e-5 of the largest."""
     from paper_2505_05086_amd import binding as B
     rng = np.random.default_rng(sum(dims) + cout)
-    ho = (dims[2] + 2 * pad - 2 * dil - 1) // stride + 1
-    wo = dims[3] + 2 * pad - 2
-    desc, conv = B.make_desc(dims, ranks, "f32"), B.make_conv(cout, 3, 3, (stride, 1), (pad, pad), (dil, 1), 1)
+    stride = stride if isinstance(stride, tuple) else (stride, 1)
+    ho = (dims[2] + 2 * pad - 2 * dil - 1) // stride[0] + 1
+    wo = (dims[3] + 2 * pad - 3) // stride[1] + 1
+    desc, conv = B.make_desc(dims, ranks, "f32"), B.make_conv(cout, 3, 3, stride, (pad, pad), (dil, 1), 1)
     U = _factors(rng, dims, ranks)
     S = torch.from_numpy(rng.standard_normal(ranks).astype(np.float32)).cuda()
     gy = torch.from_numpy(rng.standard_normal((dims[0], cout, ho, wo)).astype(np.float32)).cuda()
@@ -64,8 +71,8 @@ def test_split_correlation_at_the_edges_of_its_tiles(dims, ranks, cout, stride, 
     ws = B.alloc_workspace(desc, conv, 0)
     ws.fill_(255)                                        # NaN wherever nothing was written
     sites = _sites(lambda: B.asi_weight_grad_conv2d(desc, S, U, gy, conv, dW, False, ws))
-    assert any("k_corr_mfma_split<9, %s>" % ("true" if wo % 8 else "false") in s for s in sites), sites
-    want = _dense_dw(S, U, gy, (stride, 1), (pad, pad), (dil, 1))
+    assert any("k_corr_mfma_split<9, %s, %d>" % ("true" if wo % 8 else "false", stride[1]) in s for s in sites), sites
+    want = _dense_dw(S, U, gy, stride, (pad, pad), (dil, 1))
     assert float((dW - want).abs().max() / want.abs().max()) <= 1e-5
 
 
