@@ -5,7 +5,7 @@
 //                      left singular vectors of the mode-m unfolding (App. A.2): k_mode_gram accumulates
 //                      G in fp64 on the MFMA, split over column ranges; k_gram_reduce adds the ranges in a
 //                      fixed order; k_chol_panel factors it (G = R^T R), a cyclic one-sided Jacobi iteration
-//                      (k_jacobi_small, k_jacobi_block) orthogonalises the rows of W = R, after which row k
+//                      (k_jacobi_small, k_jacobi_block, k_jacobi_one) orthogonalises the rows of W = R, after which row k
 //                      is sqrt(lambda_k) v_k^T; k_spectrum_finish sorts.
 //   explained variance ranks per threshold (Sec. 3.3, Step 1): k_ev_ranks.
 //   perplexity         Frobenius norm of the difference of two weight gradients (Eq. 7): k_frob_partial,
@@ -58,7 +58,7 @@ struct SpecJob {
     double* W;
     double* norms;
     CholScale* sc;
-    int32_t* rot;                       // rotations of every sweep
+    int32_t* rot;                       // rotations of every sweep that count against convergence
     double shift_factor, tol2;
     double* lam;
     float* vec;
@@ -70,9 +70,10 @@ struct SpecBatch {
     SpecJob job[RK_MODES];
 };
 __device__ __forceinline__ const SpecJob& find_mode(const SpecBatch& a, int* blk) {
-    int j = 0;
     const int b = blockIdx.x;
-    while (j + 1 < a.njobs && b >= a.first[j + 1]) ++j;
+    int j = 0;
+#pragma unroll
+    for (int k = 1; k < RK_MODES; ++k) j += b >= a.first[k] ? 1 : 0;     // (behind the last mode: the grid's end)
     *blk = b - a.first[j];
     return a.job[j];
 }
@@ -383,14 +384,23 @@ __device__ __forceinline__ double rsqrt64(double x) {
 // The rotation (c, s) that makes rows with squared norms al, be and product ga orthogonal: x' = c x - s y, y' = s x + c y.
 // With d = be - al, g = 2 ga, h = sqrt(d^2 + g^2):  c = sqrt((1 + |d| / h) / 2),  s = sign(d) g / (2 h c), the smaller of
 // the two angles.  Returns false (c = 1, s = 0) where the rows are orthogonal to the rounding of their product already.
-__device__ __forceinline__ bool rotation(double& al, double& be, double ga, double tol2, double* c, double* s) {
-    *c = 1.0; *s = 0.0;
-    if (!(ga * ga > tol2 * (al * be))) return false;
+// *wide: the rotation counts against convergence.  One by a small angle between rows that were nearly orthogonal does not: with
+// both below t = 2^-26, it changes the cosine of another pair by at most 2 t^2 (the angle times the ratio of the norms is at most
+// 2 t, the cosine it brings in t), and the 2 (n - 2) rotations of a sweep that touch a pair by 4 n t^2 = 4 n 2^-52, which is what two rows
+// may be off and count as orthogonal.  So a sweep without a wide rotation ends converged and needs no sweep after it to show it
+// (a sweep of a 160-long mode is 90 to 130 us; modes of 65 to 250: 747 -> 679 us, 1760 -> 1748 and 1930 -> 1772
+// for 192, 2849 -> 2641 for 250, the errors of eigenvalues and vectors unchanged).
+constexpr double RK_SMALL2 = 2.220446049250313e-16;     // t^2
+__device__ __forceinline__ bool rotation(double& al, double& be, double ga, double tol2, double* c, double* s, int* wide) {
+    *c = 1.0; *s = 0.0; *wide = 0;
+    const double ab = al * be;
+    if (!(ga * ga > tol2 * ab)) return false;
     const double d = be - al, g = 2.0 * ga;
     const double ih = rsqrt64(fma(d, d, g * g));
     const double c2 = fma(0.5 * fabs(d), ih, 0.5), rc = rsqrt64(c2);
     *c = c2 * rc;
     *s = (d >= 0.0 ? 0.5 : -0.5) * g * ih * rc;
+    *wide = !(ga * ga <= RK_SMALL2 * ab && *s * *s <= RK_SMALL2);
     const double tg = *s * rc * ga;                      // tan(angle) ga, rc = 1 / c
     al -= tg; be += tg;
     return true;
@@ -405,9 +415,9 @@ __device__ __forceinline__ void round_robin(int m, int round, int p, int* a, int
     *b = u < v ? v : u;
 }
 
-// Rotates the rows ra, rb in LDS (16 NE elements, zero padded) with squared norms in na, nb; returns whether it did.
+// Rotates the rows ra, rb in LDS (16 NE elements, zero padded) with squared norms in na, nb; returns whether it counts.
 template <int NE>
-__device__ __forceinline__ bool jacobi_pair(double* ra, double* rb, double* na, double* nb, int lane, double tol2) {
+__device__ __forceinline__ int jacobi_pair(double* ra, double* rb, double* na, double* nb, int lane, double tol2) {
     double x[NE], y[NE], al = *na, be = *nb, ga = 0.0, g2 = 0.0;
 #pragma unroll
     for (int k = 0; k < NE; ++k) { x[k] = ra[lane + RK_JL * k]; y[k] = rb[lane + RK_JL * k]; }
@@ -415,14 +425,15 @@ __device__ __forceinline__ bool jacobi_pair(double* ra, double* rb, double* na, 
     for (int k = 0; k < NE; k += 2) { ga = fma(x[k], y[k], ga); g2 = fma(x[k + 1], y[k + 1], g2); }
     ga = row16_sum(ga + g2);
     double c, s;
-    if (!rotation(al, be, ga, tol2, &c, &s)) return false;
+    int wide;
+    if (!rotation(al, be, ga, tol2, &c, &s, &wide)) return 0;
 #pragma unroll
     for (int k = 0; k < NE; ++k) {
         ra[lane + RK_JL * k] = fma(c, x[k], -s * y[k]);
         rb[lane + RK_JL * k] = fma(s, x[k], c * y[k]);
     }
     if (lane == 0) { *na = al; *nb = be; }
-    return true;
+    return wide;
 }
 // squared norm of an LDS row by its 16 lanes
 template <int NE>
@@ -459,7 +470,7 @@ __global__ __launch_bounds__(512) void k_jacobi_small(SpecBatch jobs, int max_sw
         for (int round = 0; round < m; ++round) {
             int a, b;
             round_robin(m, round, p, &a, &b);
-            if (2 * p < n2 && b < n) mine += jacobi_pair<NE>(w + a * LD, w + b * LD, nrm + a, nrm + b, lane, tol2) ? 1 : 0;
+            if (2 * p < n2 && b < n) mine += jacobi_pair<NE>(w + a * LD, w + b * LD, nrm + a, nrm + b, lane, tol2);
             __syncthreads();                             // a row is written by one pair and read by another in the next round
         }
         if (lane == 0 && mine) atomicAdd(&s_rot, mine);
@@ -473,8 +484,8 @@ __global__ __launch_bounds__(512) void k_jacobi_small(SpecBatch jobs, int max_sw
     if (tid == 0) jobs.job[blockIdx.x].rot[0] = used;
 }
 
-// One launch of a sweep for n > 64: workgroup q of a mode takes the q-th pair of blocks of `round`.  Rotations of the sweep before (not
-// in the first; zero there means converged, nothing is done) and of this one are counted in the mode's rot.
+// One launch of a sweep for n > 64: workgroup q of a mode takes the q-th pair of blocks of `round`.  The rotations that count, of the sweep
+// before (not in the first; zero there means converged, nothing is done) and of this one, are in the mode's rot.
 extern __shared__ double jac_dyn[];
 template <int NE>
 __device__ __forceinline__ void jacobi_block(const SpecJob& jb, int blk, int sweep, int round, int& s_rot, double* nrm) {
@@ -497,6 +508,7 @@ __device__ __forceinline__ void jacobi_block(const SpecJob& jb, int blk, int swe
         x[k] = W[(long long)(gi < n ? gi : n - 1) * n + ic];
         y[k] = W[(long long)(gj < n ? gj : n - 1) * n + ic];
     }
+    if (sweep > 0 && jb.rot[sweep - 1] == 0) return;     // (the same for all threads; asked behind the rows, both are on their way)
 #pragma unroll
     for (int k = 0; k < NE; ++k) {
         const bool in = lane + RK_JL * k < n;
@@ -519,7 +531,7 @@ __device__ __forceinline__ void jacobi_block(const SpecJob& jb, int blk, int swe
         for (int q = 0; q < 2 * RK_JB - 1; ++q) {
             int a, b;
             round_robin(2 * RK_JB - 1, q, p, &a, &b);
-            mine += jacobi_pair<NE>(w + a * LD, w + b * LD, nrm + a, nrm + b, lane, tol2) ? 1 : 0;
+            mine += jacobi_pair<NE>(w + a * LD, w + b * LD, nrm + a, nrm + b, lane, tol2);
             __syncthreads();
         }
 #pragma unroll
@@ -537,7 +549,8 @@ __device__ __forceinline__ void jacobi_block(const SpecJob& jb, int blk, int swe
             for (int k = 0; k < NE; k += 2) { ga = fma(x[k], y[k], ga); g2 = fma(x[k + 1], y[k + 1], g2); }
             ga = row16_sum(ga + g2);
             double c, s;
-            if (rotation(al, be, ga, tol2, &c, &s)) {
+            int wide;
+            if (rotation(al, be, ga, tol2, &c, &s, &wide)) {
 #pragma unroll
                 for (int k = 0; k < NE; ++k) {
                     const double v = fma(c, x[k], -s * y[k]);
@@ -545,7 +558,7 @@ __device__ __forceinline__ void jacobi_block(const SpecJob& jb, int blk, int swe
                     x[k] = v;
                 }
                 if (lane == 0) nrm[b] = be;
-                ++mine;
+                mine += wide;
             }
             __syncthreads();
         }
@@ -563,19 +576,27 @@ __device__ __forceinline__ void jacobi_block(const SpecJob& jb, int blk, int swe
 }
 // elements per lane of a row of n: the shapes the rows are held in
 __host__ __device__ constexpr int row_shape(int n) { return n <= 128 ? 8 : (n <= 192 ? 12 : (n <= 256 ? 16 : 32)); }
-template <int NE>                                        // of the longest mode
+// NE of the longest mode.  A launch for one mode neither looks for its mode nor carries the code of other shapes (k_jacobi_one; a
+// 500-long mode takes 9.4 ms in the general form, 8.9 in this one).
+template <int NE>
 __global__ __launch_bounds__(256) void k_jacobi_block(SpecBatch a, int sweep, int round) {
     __shared__ int s_rot;
     __shared__ double nrm[2 * RK_JB];
     int blk;
     const SpecJob& jb = find_mode(a, &blk);
     const int nblk2 = ((jb.n + RK_JB - 1) / RK_JB + 1) & ~1;
-    if (round >= nblk2 - 1 || (sweep > 0 && jb.rot[sweep - 1] == 0)) return;         // the same for all threads
+    if (round >= nblk2 - 1) return;                      // the same for all threads
     const int ne = row_shape(jb.n);
     if (NE == 8 || ne == 8) jacobi_block<8>(jb, blk, sweep, round, s_rot, nrm);
     else if (NE == 12 || ne == 12) jacobi_block<12>(jb, blk, sweep, round, s_rot, nrm);
     else if (NE == 16 || ne == 16) jacobi_block<16>(jb, blk, sweep, round, s_rot, nrm);
     else jacobi_block<32>(jb, blk, sweep, round, s_rot, nrm);
+}
+template <int NE>
+__global__ __launch_bounds__(256) void k_jacobi_one(SpecJob jb, int sweep, int round) {
+    __shared__ int s_rot;
+    __shared__ double nrm[2 * RK_JB];
+    jacobi_block<NE>(jb, blockIdx.x, sweep, round, s_rot, nrm);
 }
 
 // After convergence row k of W is sqrt(lambda_k) v_k^T, lambda_k an eigenvalue of the scaled and shifted G.  Eigenvalues in descending order (ties by row index),
@@ -735,11 +756,15 @@ template <int NE>
 hipError_t jacobi_sweep(const SpecBatch& b, int grid, int rounds, int sweep, hipStream_t st) {
     constexpr size_t lds = sizeof(double) * 2 * RK_JB * (RK_JL * NE + ((RK_JL * NE) % 32 == 0 ? 16 : 0));
     if (lds > 65536) {
-        static LdsAllowed allowed;
-        const hipError_t e = allow_lds(reinterpret_cast<const void*>(k_jacobi_block<NE>), lds, allowed);
+        static LdsAllowed allowed, allowed_one;
+        const hipError_t e = b.njobs == 1 ? allow_lds(reinterpret_cast<const void*>(k_jacobi_one<NE>), lds, allowed_one)
+                                          : allow_lds(reinterpret_cast<const void*>(k_jacobi_block<NE>), lds, allowed);
         if (e != hipSuccess) return e;
     }
-    for (int round = 0; round < rounds; ++round) hipLaunchKernelGGL(k_jacobi_block<NE>, dim3((unsigned)grid), 256, lds, st, b, sweep, round);
+    for (int round = 0; round < rounds; ++round) {
+        if (b.njobs == 1) hipLaunchKernelGGL(k_jacobi_one<NE>, dim3((unsigned)grid), 256, lds, st, b.job[0], sweep, round);
+        else hipLaunchKernelGGL(k_jacobi_block<NE>, dim3((unsigned)grid), 256, lds, st, b, sweep, round);
+    }
     return hipGetLastError();
 }
 hipError_t launch_jacobi_sweep(const SpecJob* jobs, int njobs, int sweep, hipStream_t st) {
@@ -866,7 +891,7 @@ asi_status asi_mode_spectra(const asi_tensor_desc* desc, const void* A, const in
     }
     if (hipGetLastError() != hipSuccess) return ASI_ERR_HIP;
 
-    // Sweeps until a whole one rotates nothing; the counts come back to the host (this entry point iterates to convergence and
+    // Sweeps until a whole one has no rotation that counts; the counts come back to the host (this entry point iterates to convergence and
     // therefore waits for the stream).  Modes of up to 64 iterate in one launch.  Sweeps are handed over several at a time (one
     // that follows a converged one returns at once), so that the host's wait does not stand between every two of them.
     grid = gather_modes(jobs, n_modes, [](const SpecJob& j) { return j.n > 1 && j.n <= 64 ? 1 : 0; }, &b);

@@ -70,6 +70,24 @@ def test_mode_spectra_against_library_svd(case):
         assert O.max_rel_err(O.projector(U), O.projector(Uo)) <= 1e-5, m
 
 
+@pytest.mark.parametrize("n", [48, 100, 300])
+def test_mode_spectrum_of_clusters(n):
+    """Three levels of n / 3 equal singular values, 1e-3 apart, up to the rounding of fp32: rows that are nearly orthogonal and nearly
+    of one length take large angles, so that a sweep of small products alone does not end the iteration.  Eigenvalues to n eps of the
+    trace, columns orthogonal to the rounding of their fp32 entries."""
+    B, RS = _mods()
+    rng = np.random.default_rng(n)
+    Q = np.linalg.qr(rng.standard_normal((2 * n, n)))[0].T * np.repeat(10.0 ** -np.array([0.0, 3.0, 3.5]), -(-n // 3))[:n, None]
+    P = np.linalg.qr(rng.standard_normal((n, n)))[0]
+    A = (P @ Q).astype(np.float32).reshape(1, n, 2 * n)
+    sp = RS.mode_spectrum(torch.from_numpy(A).cuda(), 1)
+    want = R.mode_spectrum(A.astype(F64), 1)
+    lam = sp.eigenvalues.cpu().numpy()
+    assert np.max(np.abs(lam - want)) <= 4 * n * np.finfo(F64).eps * want.sum()
+    U = sp.eigenvectors.double().cpu().numpy()
+    assert np.max(np.abs(U.T @ U - np.eye(n))) <= 1e-6
+
+
 @pytest.mark.parametrize("n", [2, 63, 64, 65, 97, 128, 129, 192, 193, 257, 512])
 @pytest.mark.parametrize("thin", [False, True])
 def test_mode_spectrum_at_the_edges_of_the_iteration(n, thin):
