@@ -1009,7 +1009,8 @@ size_t asi_workspace_bytes(const asi_tensor_desc* desc, const asi_conv2d_desc* c
     asi_status why;
     if (!parse_desc(desc, &s, &why)) return 0;
     size_t need = std::max(plan_compress(s, nullptr).bytes, plan_core(s, nullptr).bytes);
-    need = std::max(need, std::max(plan_compress(s, nullptr, true).bytes, plan_compress(s, nullptr, false, true).bytes));
+    need = std::max(need, plan_compress(s, nullptr, true).bytes);
+    if (s.dt == BF16) need = std::max(need, plan_compress(s, nullptr, false, true).bytes);
     if (conv) {
         ConvGeom cg;
         if (!parse_conv(s, conv, &cg)) return 0;

@@ -716,6 +716,8 @@ bool parse_mode(const asi_tensor_desc* desc, int mode, ModeShape* ms, asi_status
     return true;
 }
 constexpr int RK_SWEEPS = 60;
+constexpr size_t RK_COUNTS = RK_ALIGN;                   // bytes of a mode's counters
+static_assert(sizeof(int32_t) * RK_SWEEPS <= RK_COUNTS, "a counter per sweep");
 struct GramPlan { int tiles, nchunks, nsplit; size_t part_bytes, w_bytes, norm_bytes, bytes; };
 GramPlan plan_gram(const ModeShape& ms) {
     GramPlan p;
@@ -731,7 +733,7 @@ GramPlan plan_gram(const ModeShape& ms) {
     p.w_bytes = align_up(sizeof(double) * (size_t)ms.n * ms.n);
     p.norm_bytes = align_up(sizeof(double) * (size_t)ms.n);
     // partial Gram matrices, G, W, the eigenvalues in row order, scale and shift, a rotation counter per sweep
-    p.bytes = p.part_bytes + 2 * p.w_bytes + p.norm_bytes + align_up(sizeof(CholScale)) + align_up(sizeof(int32_t) * RK_SWEEPS);
+    p.bytes = p.part_bytes + 2 * p.w_bytes + p.norm_bytes + align_up(sizeof(CholScale)) + RK_COUNTS;
     return p;
 }
 
@@ -854,7 +856,7 @@ asi_status asi_mode_spectra(const asi_tensor_desc* desc, const void* A, const in
         const GramPlan p = plan_gram(ms);
         SpecJob& jb = jobs[k];
         char* at = base + need;
-        need += p.bytes;
+        need += p.bytes - RK_COUNTS;
         jb.X = A; jb.outer = ms.outer; jb.inner = ms.inner; jb.ncols = ms.ncols; jb.n = ms.n;
         jb.tiles = p.tiles; jb.nsplit = p.nsplit; jb.nchunks = p.nchunks;
         jb.part = reinterpret_cast<double*>(at); at += p.part_bytes;
@@ -862,7 +864,6 @@ asi_status asi_mode_spectra(const asi_tensor_desc* desc, const void* A, const in
         jb.W = reinterpret_cast<double*>(at); at += p.w_bytes;
         jb.norms = reinterpret_cast<double*>(at); at += p.norm_bytes;
         jb.sc = reinterpret_cast<CholScale*>(at); at += align_up(sizeof(CholScale));
-        jb.rot = reinterpret_cast<int32_t*>(at);
         // additions behind an entry of G: the columns of a range (64 a chunk), then the ranges
         const double adds = (double)RK_T * ((p.nchunks + p.nsplit - 1) / p.nsplit) + p.nsplit;
         jb.shift_factor = (4.0 * ms.n + adds) * 1.1102230246251565e-16;
@@ -871,6 +872,8 @@ asi_status asi_mode_spectra(const asi_tensor_desc* desc, const void* A, const in
         jb.lam = eigenvalues[k];
         jb.vec = eigenvectors ? eigenvectors[k] : nullptr;
     }
+    // the counters of all modes stand side by side behind the last mode
+    for (int k = 0; k < n_modes; ++k, need += RK_COUNTS) jobs[k].rot = reinterpret_cast<int32_t*>(base + need);
     if (!ws || reinterpret_cast<uintptr_t>(ws) % RK_ALIGN != 0 || ws_bytes < need) return ASI_ERR_WORKSPACE;
 
     SpecBatch b;
@@ -903,20 +906,17 @@ asi_status asi_mode_spectra(const asi_tensor_desc* desc, const void* A, const in
         used[k] = jobs[k].n == 1 ? 0 : -1;
         if (jobs[k].n > 64) { which[n_open] = k; open[n_open++] = jobs[k]; }
     }
-    int32_t h[RK_MODES][RK_SWEEPS];
+    // one copy brings the counters of all modes: a copy is a wait of some 30 us
+    int32_t h[RK_MODES][RK_COUNTS / sizeof(int32_t)];
     for (int done = 0; done == 0 || (n_open > 0 && done < RK_SWEEPS);) {
-        int upto = done + (done == 0 ? 6 : 2);
+        int upto = done + (done == 0 ? 8 : 2);
         if (upto > RK_SWEEPS) upto = RK_SWEEPS;
         for (int sweep = done; sweep < upto && n_open; ++sweep)
             if (launch_jacobi_sweep(open, n_open, sweep, st) != hipSuccess) return ASI_ERR_HIP;
-        bool asked = false;
-        for (int k = 0; k < n_modes; ++k) {
-            const int count = jobs[k].n > 64 ? upto : (done == 0 && jobs[k].n > 1 ? 1 : 0);
-            if (used[k] >= 0 || count == 0) continue;
-            if (hipMemcpyAsync(h[k], jobs[k].rot, sizeof(int32_t) * count, hipMemcpyDeviceToHost, st) != hipSuccess) return ASI_ERR_HIP;
-            asked = true;
+        if (n_open || (done == 0 && grid)) {
+            if (hipMemcpyAsync(h, jobs[0].rot, RK_COUNTS * n_modes, hipMemcpyDeviceToHost, st) != hipSuccess) return ASI_ERR_HIP;
+            if (hipStreamSynchronize(st) != hipSuccess) return ASI_ERR_HIP;
         }
-        if (asked && hipStreamSynchronize(st) != hipSuccess) return ASI_ERR_HIP;
         for (int k = 0; k < n_modes && done == 0; ++k)
             if (jobs[k].n > 1 && jobs[k].n <= 64 && h[k][0] > 0) used[k] = h[k][0];
         int left = 0;

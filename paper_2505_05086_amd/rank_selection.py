@@ -56,12 +56,13 @@ def mode_spectra(A: torch.Tensor, modes: Sequence[int]) -> List[ModeSpectrum]:
 
 def explained_variance_ranks(spectra: Sequence[ModeSpectrum], eps: Sequence[float]) -> List[Tuple[int, ...]]:
     """One tuple of ranks (one per mode) per threshold: the layer's rows of the rank tensor R."""
-    per_mode = []
-    for sp in spectra:
-        r = torch.empty(len(eps), dtype=torch.int32, device=sp.eigenvalues.device)
+    if len({sp.eigenvalues.device for sp in spectra}) == 1:      # one copy to the host for all modes
+        per_mode = torch.empty((len(spectra), len(eps)), dtype=torch.int32, device=spectra[0].eigenvalues.device)
+    else:
+        per_mode = [torch.empty(len(eps), dtype=torch.int32, device=sp.eigenvalues.device) for sp in spectra]
+    for sp, r in zip(spectra, per_mode):
         B.asi_explained_variance_ranks(sp.eigenvalues, eps, r)
-        per_mode.append(r)
-    host = [r.cpu().tolist() for r in per_mode]
+    host = per_mode.tolist() if isinstance(per_mode, torch.Tensor) else [r.tolist() for r in per_mode]
     return [tuple(int(h[j]) for h in host) for j in range(len(eps))]
 
 
