@@ -48,7 +48,8 @@ struct CholScale {
 };
 // One mode of a call.  The modes of a tensor are independent and each is a long chain of small launches, so the launches serve
 // all of them: workgroup b belongs to the mode j with first[j] <= b < first[j + 1].  The rank-selection row of a (128, 160, 7, 7)
-// layer, one mode after the other 3620 us, so 2380: the 128-long mode (84 launches of 11 us) runs beside the 160-long one (108 of 14).
+// layer, one mode after the other 3620 us, so 2380 (2030 with one copy for all counters): the 128-long mode (84 launches of 11 us)
+// runs beside the 160-long one (108 of 14).
 struct SpecJob {
     const void* X;
     long long outer, inner, ncols;
@@ -344,8 +345,8 @@ __global__ __launch_bounds__(256) void k_chol_panel(SpecBatch a, int P) {
 // A rotation of two rows makes them orthogonal; a sweep visits every pair once.  The iteration is a chain of n - 1
 // dependent rounds of disjoint pairs per sweep and some ten sweeps: what bounds it is the length of a round, not
 // arithmetic.  One launch per round cost ~5 us a round (32 ms for a 512-long mode, 7 ms for 160); here the rounds of a
-// launch run inside workgroups that hold their rows in LDS, 16 lanes to a pair (1.8 ms for 160, 8.9 ms for 512, factor and
-// all; a round of cross pairs is 0.6 us, of which the LDS traffic of the rows is about a third).
+// launch run inside workgroups that hold their rows in LDS, 16 lanes to a pair (1.4 ms for 160, 8.9 ms for 500, factor and
+// all; a round of cross pairs is 0.54 us, half of it the rotation, and a launch has 5 us outside its rounds).
 //   n <= 64: one workgroup holds all rows and runs the whole iteration to convergence in one launch.
 //   n > 64:  rows in blocks of 16.  A launch pairs the blocks (round-robin over blocks), a workgroup takes two blocks and
 //            visits their 16 x 16 cross pairs in 16 rounds; the first launch of a sweep also visits the pairs inside the
