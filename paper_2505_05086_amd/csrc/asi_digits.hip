@@ -6,15 +6,14 @@
 // v_mfma_i32_16x16x64_i8 sums products of digits without rounding (19 cycles for 16 x 16 x 64 multiply-adds, 1080 on the fp64
 // MFMA).  Products of digits whose positions add up to the same power share an int32 accumulator; the few sums of a result are put
 // together in fp64, once.  The sums are exact, where fp64 rounds after every four products.
-// 64 x 197 x 3072, ranks 32, 64, 192: batch mode 67 -> 51 us, token mode 179 -> 118, hidden mode 336 -> 126 (105 and V's digits), largest
+// 64 x 197 x 3072, ranks 32, 64, 192: batch mode 67 -> 51 us, token mode 179 -> 118, hidden mode 336 -> 148 (121 and V's digits), largest
 // magnitude 15.  Bound: a tile's cutting (300 vector instructions a thread), its products and LDS traffic one after the other,
 // 2.4 + 3.6 + 2.8 thousand cycles for 197 rows; the fp64 forms were bound by the fp64 MFMA.
 //   k_amax_bf16            largest magnitude of the tensor (the scale), one pass per call
 //   k_subspace_gram_digits P = (A_m A_m^T) U_prev for short modes and for long fibres of up to 256: the digits of a tile are both
 //                          operands, 4 x 4 digit products a block of G
-//   k_pair_digits          P = A_m V along a last mode: V (fp32, from the bf16 MFMA product) is cut into three digits by
-//                          k_v_digits, relative to the largest entry of its column in a range of rows (2^-22 of it; what V
-//                          itself is off by is 2^-18), 4 x 3 digit products
+//   k_pair_digits          P = A_m V along a last mode: V (fp32, from the bf16 MFMA product) is cut into four digits by
+//                          k_v_digits, relative to the largest entry of its column in a range of rows; 4 x 4 digit products
 // A value below 2^-22 of the largest (one in 10^5 or 10^6 in ordinary data) may have bits below the last digit.  The thread that
 // cuts it puts what is left on a list of its workgroup, and at the end the products of the listed rests are added in fp64, in the
 // order of their places.  A workgroup that meets more of them than the list holds (parts of a tensor that are small throughout)
@@ -441,15 +440,20 @@ __global__ __launch_bounds__(DG_NT, 2) void k_subspace_gram_digits(Batch<GramDig
 }
 
 // ---- V as digits ------------------------------------------------------------------------------
-// V (columns x r, the sum of ks partial products) in three digits relative to the largest entry of an output in a range of columns,
+// V (columns x r, the sum of ks partial products) in four digits relative to the largest entry of an output in a range of columns,
 // stored as k_pair_digits copies it to LDS: 1 KB per (chunk of 64 columns, block of 16 outputs, digit), 16 columns per lane.  A
 // workgroup per chunk, twice: sums and largest magnitudes, then the digits.  (A workgroup per range and block of outputs that does
-// both has 60 workgroups for 12608 x 192 and took 78 us; 8 + 13 so.)
+// both has 60 workgroups for 12608 x 192 and took 78 us; 8 + 13 so, with three digits.)
+// Why four digits: a digit is off by at most half of 2^-29 max |V_q|.  V itself is off by what the two bf16 terms of its factor leave out,
+// 2^-18.6 (rms) of the root mean square of a column x_c of X.  Over N columns the digits add 2^-29 max |V_q| |X|_F / sqrt(12) to P_q,
+// that adds 2^-18.6 sqrt(sum |x_c|^4 / n); with |V_q| <= |x_c| and |X|_F^2 <= sqrt(N sum |x_c|^4) the first is at most 2^-12.2 sqrt(n) N^(1/4) of
+// the second whatever the values, 0.09 for 3072 x 2560 and 0.5 at VD_MAX_N.  (Three digits: up to 256 times as much.)
+constexpr int VD_MAX_N = 1 << 16;
 struct VDigitsJob {
     const float* V;                      // (ks, ncols, r)
     float* sum;                          // (ncols, r); V itself if there is nothing to add up
     unsigned* most;                      // (chunks, 16 nqb) bit patterns of the largest magnitudes
-    unsigned char* out;                  // (nsplit, cps, nqb, 3, 1024)
+    unsigned char* out;                  // (nsplit, cps, nqb, 4, 1024)
     double* vscale;                      // (nsplit, 16 nqb): what a unit of an output's digits is worth
     long long ncols;
     int ks, r, nqb, nsplit, cps;         // cps: chunks per split
@@ -503,11 +507,11 @@ __global__ __launch_bounds__(VD_NT) void k_v_digits(Batch<VDigitsJob> bt) {
         for (int k = z * jb.cps; k < k1; ++k) m = max(m, jb.most[(long long)k * rp + tid]);
         int e = 0;
         if (m != 0 && m < 0x7f800000u) (void)frexpf(__uint_as_float(m), &e);             // below 2^e
-        shift[tid] = m < 0x7f800000u ? 22 - e : 1 << 20;
-        if (lb == z * jb.cps) jb.vscale[(long long)z * rp + tid] = m < 0x7f800000u ? ldexp(1.0, e - 22) : __builtin_nan("");
+        shift[tid] = m < 0x7f800000u ? 30 - e : 1 << 20;
+        if (lb == z * jb.cps) jb.vscale[(long long)z * rp + tid] = m < 0x7f800000u ? ldexp(1.0, e - 30) : __builtin_nan("");
     }
     __syncthreads();
-    unsigned char* out = jb.out + (long long)lb * jb.nqb * 3072;
+    unsigned char* out = jb.out + (long long)lb * jb.nqb * 4096;
     for (int t = tid; t < 16 * (rp / 4); t += VD_NT) {   // four columns of four outputs
         const int cq = t / (rp / 4), q0 = 4 * (t - cq * (rp / 4));
         float v[4][4];
@@ -525,17 +529,17 @@ __global__ __launch_bounds__(VD_NT) void k_v_digits(Batch<VDigitsJob> bt) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) v[c][q] = 4 * cq + c < cols && q0 + q < r ? v[c][q] : 0.f;
         }
-        unsigned char* to = out + (q0 >> 4) * 3072 + ((cq >> 2) * 16 + (q0 & 15)) * 16 + 4 * (cq & 3);
+        unsigned char* to = out + (q0 >> 4) * 4096 + ((cq >> 2) * 16 + (q0 & 15)) * 16 + 4 * (cq & 3);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int sh = shift[q0 + q];
             int k[4];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) k[c] = sh < 1 << 20 ? (int)rintf(ldexpf(v[c][q], sh)) : 0;
+            for (int c = 0; c < 4; ++c) k[c] = sh < 1 << 20 ? (int)rintf(ldexpf(v[c][q], sh)) : 0;      // (2^30 at most)
             unsigned d[4];
             digits4(k[0], k[1], k[2], k[3], d);
 #pragma unroll
-            for (int g = 0; g < 3; ++g) *reinterpret_cast<unsigned*>(to + g * 1024 + q * 16) = d[g];
+            for (int g = 0; g < 4; ++g) *reinterpret_cast<unsigned*>(to + g * 1024 + q * 16) = d[g];
         }
     }
 }
@@ -545,8 +549,8 @@ __global__ __launch_bounds__(VD_NT) void k_v_digits(Batch<VDigitsJob> bt) {
 // 192), so that X is read and cut once.  Chunks of 64 columns: X through registers (a wave eight columns, a lane one row: bytes of
 // consecutive columns are what a lane multiplies, so the cut also transposes), the digits of V copied to LDS as they are.  Two
 // buffers each, one barrier a chunk.  Wave w: row blocks 2 (w % 2) and the next, output blocks QB (w / 2) to QB (w / 2) + QB - 1;
-// six int32 accumulators a block.
-constexpr int PD_MAX_CPS = 128;          // chunks per range: 3 digit products of 2^14, 64 columns, twice that where there are rests
+// seven int32 accumulators a block.
+constexpr int PD_MAX_CPS = 128;          // chunks per range: 4 digit products of 2^14, 64 columns: 2^29, and twice that where there are rests
 struct PairDigitsJob {
     const void* X;                       // (ncols, n) bf16
     const float* V;                      // (ncols, r)
@@ -579,7 +583,7 @@ __global__ __launch_bounds__(DG_NT, 2) void k_pair_digits(Batch<PairDigitsJob> b
     const int cols = (int)(left < (long long)jb.cps * 64 ? left : (long long)jb.cps * 64), chunks = (cols + 63) >> 6;
     const Scale sc = tensor_scale(jb.amax, red);         // (not finite: neither is V, and its scales are NaN)
     if (tid == 0) list.count = 0;
-    const int vb = nqb * 3072;                           // bytes of a chunk of V
+    const int vb = nqb * 4096;                           // bytes of a chunk of V
     unsigned char* const xbuf = dg_dyn;
     unsigned char* const vbuf = dg_dyn + 2 * XB;
     const unsigned char* const vsrc = jb.Vd + (long long)z * jb.cps * vb;
@@ -615,9 +619,9 @@ __global__ __launch_bounds__(DG_NT, 2) void k_pair_digits(Batch<PairDigitsJob> b
         if (any_below(small, sc.low)) list_rests(list, ch, pk, sc.f, sc.low, lane, 8 * wave);
     };
     auto copy_v = [&](int ch, unsigned char* buf) __attribute__((always_inline)) {
-        for (int pc = wave; pc < 3 * nqb; pc += DG_NT / 64) copy16_to_lds(vsrc + (long long)ch * vb, vb, pc * 1024 + lane * 16, buf + pc * 1024);
+        for (int pc = wave; pc < 4 * nqb; pc += DG_NT / 64) copy16_to_lds(vsrc + (long long)ch * vb, vb, pc * 1024 + lane * 16, buf + pc * 1024);
     };
-    constexpr int G = 6;
+    constexpr int G = 7;
     v4i acc[2][QB][G];
 #pragma unroll
     for (int b = 0; b < 2; ++b)
@@ -636,13 +640,13 @@ __global__ __launch_bounds__(DG_NT, 2) void k_pair_digits(Batch<PairDigitsJob> b
 #pragma unroll
         for (int k = 0; k < QB; ++k)
             if (qb0 + k < nqb) {                         // uniform
-                v4i v[3];
+                v4i v[4];
 #pragma unroll
-                for (int d = 0; d < 3; ++d) v[d] = *reinterpret_cast<const v4i*>(bv + ((qb0 + k) * 3 + d) * 1024 + lane * 16);
+                for (int d = 0; d < 4; ++d) v[d] = *reinterpret_cast<const v4i*>(bv + ((qb0 + k) * 4 + d) * 1024 + lane * 16);
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
 #pragma unroll
-                    for (int j = 0; j < 3; ++j)
+                    for (int j = 0; j < 4; ++j)
                         if (i + j >= LOW)
 #pragma unroll
                             for (int b = 0; b < 2; ++b) acc[b][k][i + j - LOW] = mfma_i8(a[b][i], v[j], acc[b][k][i + j - LOW]);
@@ -794,7 +798,7 @@ static int pair_digits_cps(long long ncols, int nsplit) {
     return (int)((chunks + nsplit - 1) / nsplit);
 }
 int pair_digits_splits(long long ncols, int n, int r) {
-    if (ncols < 1024 || ncols >= (1LL << 31) || n < 64 || r < 1 || r > 192) return 0;
+    if (ncols < 1024 || ncols >= (1LL << 31) || n < 64 || n > VD_MAX_N || r < 1 || r > 192) return 0;
     const long long gx = (n + 63) / 64, chunks = (ncols + 63) / 64;
     long long ns = gx >= 256 ? 1 : 256 / gx;                     // one workgroup per CU (LDS)
     if (ns > 32) ns = 32;                                        // (a tree level for the partial sums beyond)
@@ -805,7 +809,7 @@ int pair_digits_splits(long long ncols, int n, int r) {
     return (int)((chunks + cps - 1) / cps);
 }
 size_t v_digits_bytes(long long ncols, int r, int nsplit) {
-    return (size_t)nsplit * pair_digits_cps(ncols, nsplit) * ((r + 15) / 16) * 3072;
+    return (size_t)nsplit * pair_digits_cps(ncols, nsplit) * ((r + 15) / 16) * 4096;
 }
 size_t v_digits_most(long long ncols, int r) { return (size_t)((ncols + 63) / 64) * 16 * ((r + 15) / 16); }
 size_t v_digits_scales(int r, int nsplit) { return (size_t)nsplit * 16 * ((r + 15) / 16); }
@@ -852,7 +856,7 @@ static hipError_t launch_pair_digits(const Item* const* items, int n, hipStream_
     Batch<PairDigitsJob> b;
     dim3 grid;
     if (!gather(items, n, &b, &grid)) return hipErrorInvalidValue;
-    constexpr size_t most = 2 * 16384 + 2 * 4 * QB * 3072;
+    constexpr size_t most = 2 * 16384 + 2 * 4 * QB * 4096;
     static LdsAllowed allowed;
     const hipError_t e = allow_lds(reinterpret_cast<const void*>(k_pair_digits<QB>), most, allowed);
     if (e != hipSuccess) return e;

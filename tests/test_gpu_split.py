@@ -122,47 +122,58 @@ def _low_rank(rng, dims, ranks):
 
 # 40 batch entries (three row blocks, the last ragged) and 130 tokens (nine, 45 blocks in one part) or 240 (fifteen, 120 blocks in
 # three parts), inner extents that end inside a tile; hidden modes and columns that are no multiple of 64, ranks that fill one, two and
-# three blocks per wave and not.  `small`: nothing below the last digit; scattered values (the list); whole slices of every mode
-# (more than the list holds: the second walk).
-@pytest.mark.parametrize("dims,ranks,kernels", [
+# three blocks per wave and not.
+_DIGITS = [
     ((40, 130, 3400), (20, 64, 70), ("gram_digits<4>", "gram_digits<1>", "pair_digits<2>")),
     ((38, 240, 2504), (12, 60, 60), ("gram_digits<4>", "pair_digits<1>")),
     ((24, 240, 5000), (12, 64, 34), ("gram_digits<1>", "pair_digits<1>")),
     ((17, 251, 1000), (9, 20, 150), ("pair_digits<3>",)),
-])
-@pytest.mark.parametrize("small", ["none", "scattered", "slices"])
-def test_steps_on_digits_against_float64(dims, ranks, kernels, small):
-    """Factors of one step from a nearby basis.  fp32 rounding of the result is 3e-8; the hidden mode's V has its factor in two bf16
-    terms (2^-17), which the conditioning of these tensors (all directions of similar weight) hardly amplifies: 1e-5."""
+]
+
+
+def _step(A, dims, ranks, prev, kernels):
     from paper_2505_05086_amd import binding as B
-    rng = np.random.default_rng(sum(dims))
-    x, U = _low_rank(rng, dims, ranks)
-    g = torch.Generator("cuda").manual_seed(1)
-    x += 1e-3 * torch.randn(dims, device="cuda", generator=g)
-    if small == "scattered":
-        x[torch.rand(dims, device="cuda", generator=g) < 1e-5] *= 1e-7
-    elif small == "slices":
-        x[:3] *= 1e-7
-        x[:, ::7] *= 1e-8
-        x[:, :, 5::9] *= 3e-8
-    A = x.to(torch.bfloat16).contiguous()
-    prev = [torch.linalg.qr((u + 0.02 / u.shape[0] ** 0.5 * torch.randn(u.shape, device="cuda", generator=g)).cpu())[0].cuda().contiguous() for u in U]
     desc = B.make_desc(dims, ranks, "bf16")
-    outs, info = [], torch.zeros(1, dtype=torch.int32, device="cuda")
-    ws = B.alloc_workspace(desc, None, 0)
-    for _ in range(2):
-        out = [torch.empty_like(u) for u in prev]
-        ws.fill_(255)
-        sites = _sites(lambda: B.asi_compress(desc, A, prev, out, ws, info))
-        outs.append(out)
-    for k in kernels:
-        assert any(k in s for s in sites), (k, sites)
+    info, ws = torch.zeros(1, dtype=torch.int32, device="cuda"), B.alloc_workspace(desc, None, 0)
+    out = [torch.empty_like(u) for u in prev]
+    ws.fill_(255)                                        # NaN wherever nothing was written
+    sites = _sites(lambda: B.asi_compress(desc, A, prev, out, ws, info))
+    if kernels is None:
+        assert not any("digits" in s for s in sites), sites
+    else:
+        assert all(any(k in s for s in sites) for k in kernels), sites
     assert int(info.item()) == 0
+    return out
+
+
+# Ordinary values; some small ones in every tile; token norms that spread over five decades.
+@pytest.mark.parametrize("dims,ranks,kernels", _DIGITS)
+@pytest.mark.parametrize("data", ["ordinary", "gelu", "tokens"])
+def test_steps_on_digits_against_float64(dims, ranks, kernels, data):
+    """Factors of one step from a nearby basis.  fp32 rounding of the result is 3e-8; the hidden
+    mode's V has its factor in two bf16 terms (2^-18), which ordinary values hardly amplify: 1e-5.  And no further off than the same step on
+    the fp64 MFMA (an activation that is not 16-byte aligned takes that), but for the rounding of the result."""
+    rng = np.random.default_rng(sum(dims))
+    g = torch.Generator("cuda").manual_seed(1)
+    x, U = _low_rank(rng, dims, ranks)
+    x += 1e-3 * torch.randn(dims, device="cuda", generator=g)
+    if data == "gelu":
+        x = torch.nn.functional.gelu(2 * x)
+    elif data == "tokens":
+        x *= torch.exp(2 * torch.randn(dims[0], dims[1], 1, device="cuda", generator=g))
+    prev = [torch.linalg.qr((u + 0.02 / u.shape[0] ** 0.5 * torch.randn(u.shape, device="cuda", generator=g)).cpu())[0].cuda().contiguous() for u in U]
+    A = x.to(torch.bfloat16).contiguous()
+    apart = torch.empty(A.numel() + 1, dtype=A.dtype, device="cuda")[1:].view(dims).copy_(A)
+    outs = [_step(A, dims, ranks, prev, kernels) for _ in range(2)]
+    wide = _step(apart, dims, ranks, prev, None)
     for m in range(3):
         assert torch.equal(outs[0][m], outs[1][m]), m      # the same sums in every run
         want = _exact_factor(A, prev[m], m)
-        err = float((outs[0][m] - want).norm() / want.norm())
-        assert err <= (1e-5 if m == 2 else 1e-6), (m, err)
+        got, ref = (float((o - want).norm() / want.norm()) for o in (outs[0][m], wide[m]))
+        print(f"{data} {dims} mode {m}: {got:.2e}, on fp64 {ref:.2e}")
+        assert got <= max(1.2 * ref, 1e-7), (m, got, ref)
+        if m < 2 or data == "ordinary":
+            assert got <= (1e-5 if m == 2 else 1e-6), (m, got)
 
 
 def test_steps_on_digits_report_a_tensor_that_is_not_finite():
