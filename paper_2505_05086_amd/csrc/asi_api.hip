@@ -108,11 +108,14 @@ struct CompressPlan {
 // Which modes of a bf16 tensor take the int8 MFMA.  It costs a pass over the tensor for its largest magnitude and saves time that
 // grows with the tensor, in us (fitted to the launches of 64 x 197 x 3072 with ranks 32, 64, 192, of 64 x 197 x 768 with 32, 64, 96 and
 // of 32 x 256 x 768 with 32, 48, 64):
-//   largest magnitude                      15 | 5 | 5
-//   64 entries through the Gram matrix     67 -> 51 | 26 -> 25   (32 entries and fewer: the fp64 form is bound by memory already)
-//   197 | 197 | 256 entries                179 -> 118 | 50 -> 63 | 30 -> 64   (G U and its partial sums are 36 us whatever the tensor; a part
-//                                          of G's blocks cuts the whole tensor again)
-//   last mode, V's digits included         336 -> 126 | 63 -> 41 | 30 -> 28
+//   largest magnitude                      17 | 6 | 5
+//   64 entries through the Gram matrix     70 -> 50 | 26 -> 25   (32 entries and fewer: the fp64 form is bound by memory already)
+//   197 | 197 | 256 entries                173 -> 119 | 50 -> 66 | 30 -> 67   (G U and its partial sums are 36 us whatever the tensor, the launch
+//                                          that does nothing is 3; a part of G's blocks cuts the whole tensor again)
+//   last mode, V's digits included         330 -> 148 | 67 -> 48 | 32 -> 32
+// Where the values have many bits below the digits (behind a GELU), which no rule on sizes can tell, the fp64 products are made all the same,
+// and the first two layer-steps take 1090 us (763 with digits, 1005 without) and 410 (371, 385).  The factor 1.3 and the 3 us keep
+// layers out whose gain is within what the fits are off by, which would then only have the loss.
 void choose_digits(const Shape& s, CompressPlan* p) {
     if (s.dt != BF16 || s.numel % 8 != 0) return;
     const double numel = (double)s.numel;
@@ -122,8 +125,8 @@ void choose_digits(const Shape& s, CompressPlan* p) {
         const int n = (int)s.n[m], nb = (n + 15) / 16, rb = (s.r[m] + 15) / 16, parts = (nb * (nb + 1) / 2 + 47) / 48;
         double g;
         if (p->gramm[m] && n > 32) g = 5e-7 * numel - 3.5;
-        else if (p->longm[m] && n <= 256) g = (1.12e-6 * rb - 1e-6 * parts) * numel - 36.0;
-        else if (p->bfv[m] && pair_digits_splits(s.numel / n, n, s.r[m])) g = 2.9e-8 * numel * s.r[m] - 8.0;
+        else if (p->longm[m] && n <= 256) g = (1.12e-6 * rb - 1e-6 * parts) * numel - 40.0;
+        else if (p->bfv[m] && pair_digits_splits(s.numel / n, n, s.r[m])) g = 2.6e-8 * numel * s.r[m] - 8.0;
         else continue;
         if (!p->bfv[m] && subspace_gram_digits_nwg(s.outer(m), n, s.inner(m)) == 0) continue;
         if (g > 2.0) { take[m] = true; gain += g; }
@@ -160,7 +163,7 @@ CompressPlan plan_compress(const Shape& s, void* ws, bool cold = false, bool dig
         if (p.bfks[m] > 1) vpmax = std::max(vpmax, (size_t)p.bfks[m] * (size_t)(s.numel / s.n[m]) * s.r[m]);
     }
     p.Vpart = c.take<float>(vpmax);
-    p.ctr8 = c.take<int32_t>(4 * kOrthCtrs);
+    p.ctr8 = c.take<int32_t>(4 * kOrthCtrs + 4);     // (and a word per mode: its digits did not suit)
     for (int m = 0; m < s.d; ++m) {
         if (!p.digm[m]) continue;
         if (!p.amax) p.amax = c.take<unsigned>(kAmaxParts);
@@ -177,7 +180,11 @@ CompressPlan plan_compress(const Shape& s, void* ws, bool cold = false, bool dig
         const size_t n = (size_t)s.n[m], r = (size_t)s.r[m];
         if (p.tiny && m >= 2) p.nsplit[m] = subspace_tiny_nwg(s.n[0] * s.n[1]);
         else if (p.planes && m >= 2) p.nsplit[m] = subspace_planes_nwg(s.dt, s.n[0] * s.n[1], (int)s.n[2], (int)s.n[3]);
-        else if (p.digm[m]) p.nsplit[m] = p.bfv[m] ? pair_digits_splits(s.numel / s.n[m], (int)n, (int)r) : subspace_gram_digits_nwg(s.outer(m), (int)n, s.inner(m));
+        else if (p.digm[m] && p.bfv[m]) p.nsplit[m] = pair_digits_splits(s.numel / s.n[m], (int)n, (int)r);
+        else if (p.digm[m]) {
+            p.nsplit[m] = subspace_gram_digits_nwg(s.outer(m), (int)n, s.inner(m));
+            if (p.longm[m]) p.nsplit[m] = std::max(p.nsplit[m], subspace_long_splits(s.outer(m), (int)n, s.inner(m), (int)r));
+        }
         else if (p.gramm[m]) p.nsplit[m] = subspace_gram_nwg(s.dt, s.outer(m), (int)n, s.inner(m));
         else if (p.longm[m]) p.nsplit[m] = subspace_long_splits(s.outer(m), (int)n, s.inner(m), (int)r);
         else p.nsplit[m] = p.fused[m] ? subspace_small_nwg(s.outer(m), (int)n, s.inner(m))
@@ -552,7 +559,7 @@ asi_status build_compress(const asi_tensor_desc* desc, const void* A, const floa
     }
     bool zero_given = false;
     if (p.amax) {
-        ASI_ADD(pg, "", (double)s.numel * 2.0, 0.0, make_amax_bf16(A, s.numel, p.amax, p.ctr8, 4 * kOrthCtrs, it__));
+        ASI_ADD(pg, "", (double)s.numel * 2.0, 0.0, make_amax_bf16(A, s.numel, p.amax, p.ctr8, 4 * kOrthCtrs + 4, it__));
         zero_given = true;
     }
     for (int k = 0; k < nord; ++k) {
@@ -576,7 +583,11 @@ asi_status build_compress(const asi_tensor_desc* desc, const void* A, const floa
             // the Gram matrix of the unfolding on the int8 MFMA, then G U_prev
             const double cols = (double)outer * (double)inner;
             ASI_ADD(pg, "", cols * n * 2.0 + 4.0 * n * r + 8.0 * n * r * p.nsplit[m], 4.0 * cols * n * r,
-                    make_subspace_gram_digits(A, outer, n, inner, U_prev[m], r, p.part[m], p.nsplit[m], p.amax, it__));
+                    make_subspace_gram_digits(A, outer, n, inner, U_prev[m], r, p.part[m], p.nsplit[m], p.amax,
+                                              p.longm[m] ? p.ctr8 + 4 * kOrthCtrs + m : nullptr, it__));
+            if (p.longm[m])
+                ASI_ADD(pg, "", 0.0, 0.0, make_subspace_long(s.dt, A, outer, n, inner, U_prev[m], r, p.part[m], p.nsplit[m], nullptr, 0, it__,
+                                                             p.ctr8 + 4 * kOrthCtrs + m));
         } else if (p.longm[m]) {
             // long fibres (64 < n <= 512): V and P from one LDS tile of complete fibres, V never stored
             int32_t* zero = zero_given ? nullptr : p.ctr8;

@@ -6,19 +6,22 @@
 // v_mfma_i32_16x16x64_i8 sums products of digits without rounding (19 cycles for 16 x 16 x 64 multiply-adds, 1080 on the fp64
 // MFMA).  Products of digits whose positions add up to the same power share an int32 accumulator; the few sums of a result are put
 // together in fp64, once.  The sums are exact, where fp64 rounds after every four products.
-// 64 x 197 x 3072, ranks 32, 64, 192: batch mode 67 -> 51 us, token mode 179 -> 118, hidden mode 336 -> 148 (121 and V's digits), largest
-// magnitude 15.  Bound: a tile's cutting (300 vector instructions a thread), its products and LDS traffic one after the other,
-// 2.4 + 3.6 + 2.8 thousand cycles for 197 rows; the fp64 forms were bound by the fp64 MFMA.
 //   k_amax_bf16            largest magnitude of the tensor (the scale), one pass per call
 //   k_subspace_gram_digits P = (A_m A_m^T) U_prev for short modes and for long fibres of up to 256: the digits of a tile are both
 //                          operands, 4 x 4 digit products a block of G
 //   k_pair_digits          P = A_m V along a last mode: V (fp32, from the bf16 MFMA product) is cut into four digits by
 //                          k_v_digits, relative to the largest entry of its column in a range of rows; 4 x 4 digit products
-// A value below 2^-22 of the largest (one in 10^5 or 10^6 in ordinary data) may have bits below the last digit.  The thread that
-// cuts it puts what is left on a list of its workgroup, and at the end the products of the listed rests are added in fp64, in the
-// order of their places.  A workgroup that meets more of them than the list holds (parts of a tensor that are small throughout)
-// walks its tiles once more and multiplies the rests of all values, as further digits in the same accumulators; what is left out
-// then is below 2^-52 of the product of the largest values.
+// A value below 2^-22 of the largest may have bits below the last digit, a rest: 2e-6 of the values of the layer below, 6e-4 to 1e-2
+// behind a GELU.  The thread that cuts it puts the rest on a list of its workgroup, and at the end the products of the listed rests are
+// added in fp64, in the order of their places.  From the first tile on whose rests do not fit, a workgroup multiplies its tiles on the fp64 MFMA;
+// the Gram matrix of a long mode, which would take longer there than V and P do, gives up instead, and k_subspace_long, which the host
+// launches behind it, does the step.  So nothing is left out whatever the values: all entries of G and all products of X are those of
+// the fp64 forms, and the sums are rounded less often.
+// 64 x 197 x 3072, ranks 32, 64, 192, fp64 forms | digits | digits where every tile has more rests than the list takes, us:
+//   batch mode 70 | 50 | 103, token mode 173 | 116 + 3 | 26 + 180, hidden mode 320 | 121 and V's digits (18; 11 with three) | 305,
+//   largest magnitude 17, the layer-step 1005 | 763 | 1090.
+// Bound: a tile's cutting (300 vector instructions a thread), its products and LDS traffic one after the other,
+// 2.4 + 3.6 + 2.8 thousand cycles for 197 rows; the fp64 forms were bound by the fp64 MFMA.
 #include "asi_device.h"
 #include "asi_kernels.h"
 #include "asi_lds.h"
@@ -111,11 +114,6 @@ __device__ __forceinline__ void to_int8(v4u raw, float f, int (&q)[8], unsigned&
         small = __builtin_bit_cast(unsigned, __builtin_elementwise_min(__builtin_bit_cast(v2us, small), __builtin_bit_cast(v2us, less)));
     }
 }
-// what to_int8 cut off, in units of 2^-24
-__device__ __forceinline__ int rest_of(float x, float f) {
-    const float t = f * x;
-    return (int)((t - (float)(int)t) * 0x1p24f);
-}
 // the four digits of four integers: byte k of out[d] is digit d of q[k]
 __device__ __forceinline__ void digits4(int q0, int q1, int q2, int q3, unsigned (&out)[4]) {
     const unsigned a = ((unsigned)q0 + 0x80808080u) ^ 0x80808080u, b = ((unsigned)q1 + 0x80808080u) ^ 0x80808080u;
@@ -127,42 +125,76 @@ __device__ __forceinline__ void digits4(int q0, int q1, int q2, int q3, unsigned
     out[2] = __builtin_amdgcn_perm(cd1, ab1, 0x05040100u);
     out[3] = __builtin_amdgcn_perm(cd1, ab1, 0x07060302u);
 }
-// The rests that a workgroup has met
-constexpr int DG_LIST = 256;
+// The values with a rest that a workgroup has met
+constexpr int DG_LIST = DG_NT;
+constexpr int DG_AHEAD = 16;             // entries whose values are on their way together
+constexpr unsigned long long DG_NO_PLACE = ~0ull;
 struct RestList {
     int count;
-    int tile[DG_LIST], at[DG_LIST];      // at: row << 16 | column in the tile
-    int rest[DG_LIST];                   // in units of 2^-24
-    unsigned char order[DG_LIST];        // the k-th by (tile, at)
+    int full[2];                         // a tile of this parity has brought more than there is room for
+    unsigned long long place[DG_LIST];   // tile << 32 | row << 16 | column in the tile
+    float rest[DG_LIST];                 // what to_int8 cut off
+    __device__ __forceinline__ int tile(int e) const { return (int)(place[e] >> 32); }
+    __device__ __forceinline__ int row(int e) const { return (int)(place[e] >> 16) & 0xffff; }
+    __device__ __forceinline__ int col(int e) const { return (int)place[e] & 0xffff; }
 };
 __device__ __forceinline__ bool any_below(unsigned small, unsigned low) {
     const unsigned a = small & 0xffffu, b = small >> 16;
     return min(a, b) + 1u < low;
 }
-// the values of one piece (eight columns of a row) that have a rest
-__device__ __forceinline__ void list_rests(RestList& l, int tile, v4u raw, float f, unsigned low, int row, int col) {
-#pragma unroll 1
+// How many entries there may be after `tiles` tiles of a workgroup.  An entry costs 0.2 to 0.4 us at the end (a read of a column or row, and its
+// updates), a tile on the fp64 MFMA 4 to 5 us more than its digits: a dozen entries a tile would pay.  Eight, so that a tensor with
+// somewhat more is found out in the first tiles (with twelve, the long mode of a GELU output met 12.5 a tile and was given up after 225 us).
+__device__ __forceinline__ int list_room(int tiles) { return min(16 + 8 * tiles, DG_LIST); }
+// the values of one piece (eight columns of a row) that have a rest; room: entries that there may be so far, DG_LIST at most
+__device__ __forceinline__ void list_rests(RestList& l, int tile, int parity, int room, v4u raw, float f, unsigned low, int row, int col) {
+    unsigned has = 0;                    // the values to look at: mostly one, and none in most lanes
+#pragma unroll
     for (int k = 0; k < 8; ++k) {
-        const unsigned w = k < 2 ? raw[0] : (k < 4 ? raw[1] : (k < 6 ? raw[2] : raw[3]));
-        const unsigned b = k & 1 ? w >> 16 : w & 0xffffu;
-        if ((b & 0x7fffu) == 0 || (b & 0x7fffu) >= low) continue;
-        const int rest = rest_of(__uint_as_float(b << 16), f);
-        if (rest == 0) continue;
+        const unsigned b = (k & 1 ? raw[k >> 1] >> 16 : raw[k >> 1]) & 0x7fffu;
+        has |= b != 0 && b < low ? 1u << k : 0u;
+    }
+    while (has) {
+        const int k = __builtin_ctz(has);
+        has &= has - 1;
+        const unsigned w = k < 4 ? (k < 2 ? raw[0] : raw[1]) : (k < 6 ? raw[2] : raw[3]);
+        const float t = f * __uint_as_float(k & 1 ? w & 0xffff0000u : w << 16), rest = t - (float)(int)t;
+        if (rest == 0.f) continue;
         const int e = atomicAdd(&l.count, 1);
-        if (e < DG_LIST) { l.tile[e] = tile; l.at[e] = row << 16 | (col + k); l.rest[e] = rest; }
+        if (e >= room) {
+            if (e < DG_LIST) l.place[e] = DG_NO_PLACE;   // (counted, so it has to hold something: the last in order, and of no tile)
+            l.full[parity] = 1;
+            return;
+        }
+        l.place[e] = (unsigned long long)(unsigned)tile << 32 | (unsigned)(row << 16 | (col + k));
+        l.rest[e] = rest;
     }
 }
-// (the order in which threads append to the list is not the same in every run; that of the sums is)
-__device__ __forceinline__ void sort_rests(RestList& l) {
+// Puts the list in the order of the places, whichever thread came first; returns how many there are of the tiles before `end`
+__device__ __forceinline__ int sort_rests(RestList& l, int end) {
+    static_assert(DG_LIST <= DG_NT && DG_LIST % 8 == 0, "an entry per thread");
     __syncthreads();
-    const int n = l.count, t = threadIdx.x;
-    if (n <= DG_LIST && t < n) {
-        int before = 0;
-        for (int e = 0; e < n; ++e) before += l.tile[e] < l.tile[t] || (l.tile[e] == l.tile[t] && l.at[e] < l.at[t]) ? 1 : 0;
-        l.order[before] = (unsigned char)t;
+    const int n = l.count < DG_LIST ? l.count : DG_LIST, t = threadIdx.x;        // (every slot below n holds a place)
+    const unsigned long long mine = t < n ? l.place[t] : DG_NO_PLACE;
+    const float rest = t < n ? l.rest[t] : 0.f;
+    int listed = 0, before = 0;
+    for (int e0 = 0; e0 < n; e0 += 8) {
+        unsigned long long p[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) p[u] = l.place[e0 + u];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (e0 + u < n) {
+                before += p[u] < mine ? 1 : 0;
+                listed += (unsigned)(p[u] >> 32) < (unsigned)end ? 1 : 0;
+            }
     }
     __syncthreads();
+    if (mine != DG_NO_PLACE) { l.place[before] = mine; l.rest[before] = rest; }
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(listed);
 }
+__device__ __forceinline__ v4d mfma_f64(float a, float b, v4d c) { return __builtin_amdgcn_mfma_f64_16x16x4f64((double)a, (double)b, c, 0, 0, 0); }
 __device__ __forceinline__ v4i mfma_i8(v4i a, v4i b, v4i c) { return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0); }
 
 extern __shared__ __align__(16) unsigned char dg_dyn[];
@@ -172,8 +204,9 @@ extern __shared__ __align__(16) unsigned char dg_dyn[];
 // 1 KB per (column block, digit, row block), 16 bytes = 16 consecutive columns of one row per lane.  G's blocks on and above the
 // diagonal are dealt out: KK = 4 (n <= 64): wave w takes column block w % 4 and half of the blocks; KK = 1 (n <= 256): the blocks go
 // to `parts` workgroups, each of which cuts the whole tile into digits, and there to the eight waves.  Seven int32 accumulators a
-// block hold |sum| < 2^31 for 2^13 columns of a wave (digit products reach 2^14, four share an accumulator, and the rests of
-// every tile may add twice that).
+// block hold |sum| < 2^30 for 2^13 columns of a wave (digit products reach 2^14, four share an accumulator).
+// KK = 4: from the first tile whose rests find no room on the list, tiles are multiplied on the fp64 MFMA, as wide values in the place of
+// their digits: [four columns][row] 16 bytes.  Its result has row lg + 4 v where the int8 one has 4 lg + v, so A's rows are read in that order.
 template <int KK> constexpr int gd_pw() { return KK == 4 ? 5 : 6; }      // blocks per wave, at most
 constexpr int GD_G = 7;                  // powers of 256 in a product of two values
 constexpr int GD_MAX_COLS = 1 << 13;     // columns per wave
@@ -185,8 +218,7 @@ struct GramDigitsJob {
     long long outer, inner;
     int tiles_per_o, ntiles;
     int n, r, slices, parts, per_part;   // blocks of G per part
-    int32_t* zero;
-    int nzero;
+    int32_t* refused;                    // KK = 1: set by a workgroup that has too many rests for its list
 };
 
 template <int KK>
@@ -203,14 +235,17 @@ __global__ __launch_bounds__(DG_NT, 2) void k_subspace_gram_digits(Batch<GramDig
     const int n = jb.n, r = jb.r, NB = (n + 15) >> 4;
     const long long inner = jb.inner;
     const int slice = lb / jb.parts, part = lb - slice * jb.parts;
-    if (jb.zero && lb == 0 && tid < jb.nzero) jb.zero[tid] = 0;
     double* __restrict__ out = jb.part + (long long)lb * n * r;
     const Scale sc = tensor_scale(jb.amax, red);
+    if (slice >= jb.slices) {                            // (a partial sum that only the fp64 form has)
+        for (int e = tid; e < n * r; e += DG_NT) out[e] = 0.0;
+        return;
+    }
     if (!sc.finite) {                                    // an infinite or NaN entry: no finite sum to be had
         for (int e = tid; e < n * r; e += DG_NT) out[e] = __builtin_nan("");
         return;
     }
-    if (tid == 0) list.count = 0;
+    if (tid == 0) list.count = list.full[0] = list.full[1] = 0;
 
     // this wave's blocks: p0 .. p0 + np - 1 of the row-wise enumeration of the upper triangle
     const int npairs = NB * (NB + 1) / 2, first = part * jb.per_part;
@@ -250,7 +285,7 @@ __global__ __launch_bounds__(DG_NT, 2) void k_subspace_gram_digits(Batch<GramDig
             raw[u] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)(pcol < vc && prow + u * RU < n ? goff + u * gstep : FAR), 0, 0);
 #endif
     };
-    auto store = [&](unsigned char* buf, int tile) __attribute__((always_inline)) {
+    auto store = [&](unsigned char* buf, int tile, int it) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < NL; ++u) {
             unsigned small = 0xffffffffu;
@@ -261,7 +296,7 @@ __global__ __launch_bounds__(DG_NT, 2) void k_subspace_gram_digits(Batch<GramDig
             digits4(q[4], q[5], q[6], q[7], b);
 #pragma unroll
             for (int d = 0; d < 4; ++d) *reinterpret_cast<v2u*>(buf + dst + (d * NBX + u * (RU / 16)) * 1024) = (v2u){a[d], b[d]};
-            if (any_below(small, sc.low)) list_rests(list, tile, raw[u], sc.f, sc.low, prow + u * RU, pcol);
+            if (any_below(small, sc.low)) list_rests(list, tile, it & 1, list_room(it + 1), raw[u], sc.f, sc.low, prow + u * RU, pcol);
         }
     };
     v4i acc[GD_PW][GD_G];
@@ -273,67 +308,111 @@ __global__ __launch_bounds__(DG_NT, 2) void k_subspace_gram_digits(Batch<GramDig
 #pragma unroll
         for (int k = 0; k < 4; ++k) d[k] = *reinterpret_cast<const v4i*>(buf + ((kk * 4 + k) * NBX + block) * 1024 + lane * 16);
     };
-    // acc += rows of A times rows of B; LOW = 3: the digits of one side stand three positions lower (products below the last digit are left out)
-    auto multiply = [&](const unsigned char* bufa, const unsigned char* bufb, auto rest) __attribute__((always_inline)) {
-        constexpr int LOW = decltype(rest)::value;
+    auto multiply = [&](const unsigned char* buf) __attribute__((always_inline)) {
         v4i a[4];
 #pragma unroll
         for (int p = 0; p < GD_PW; ++p)
             if (p < np) {                                // uniform
                 v4i b[4];
-                operand(bufb, bj[p], b);
-                if (p == 0 || bi[p] != bi[p ? p - 1 : 0]) operand(bufa, bi[p], a);
+                operand(buf, bj[p], b);
+                if (p == 0 || bi[p] != bi[p ? p - 1 : 0]) operand(buf, bi[p], a);
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
 #pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        if (i + j >= LOW) acc[p][i + j - LOW] = mfma_i8(a[i], b[j], acc[p][i + j - LOW]);
+                    for (int j = 0; j < 4; ++j) acc[p][i + j] = mfma_i8(a[i], b[j], acc[p][i + j]);
             }
     };
 
     if (slice < jb.ntiles) fetch(slice);
     __syncthreads();                                     // the list is empty
-    if (slice < jb.ntiles) store(dg_dyn, slice);
+    if (slice < jb.ntiles) store(dg_dyn, slice, 0);
     if (slice + jb.slices < jb.ntiles) fetch(slice + jb.slices);
-    int it = 0;
+    int it = 0, tile = slice;
 #pragma unroll 1
-    for (int tile = slice; tile < jb.ntiles; tile += jb.slices, ++it) {
+    for (; tile < jb.ntiles; tile += jb.slices, ++it) {
         unsigned char* cur = dg_dyn + (it & 1) * BUF;
         __syncthreads();                                 // this tile's digits are there, the other buffer is no longer read
-        if (tile + jb.slices < jb.ntiles) store(dg_dyn + ((it & 1) ^ 1) * BUF, tile + jb.slices);
+        // (the flag of this parity is written again behind the next barrier only: the same for all waves)
+        if (__builtin_amdgcn_readfirstlane(list.full[it & 1])) break;
+        int others = 0;                                  // another workgroup has given up: so does this one, behind the next barrier
+        if (KK == 1 && tid == 0) others = __hip_atomic_load(jb.refused, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tile + jb.slices < jb.ntiles) store(dg_dyn + ((it & 1) ^ 1) * BUF, tile + jb.slices, it + 1);
         if (tile + 2 * jb.slices < jb.ntiles) fetch(tile + 2 * jb.slices);
-        multiply(cur, cur, std::integral_constant<int, 0>());
+        multiply(cur);
+        if (others) list.full[(it & 1) ^ 1] = 1;
     }
-    sort_rests(list);
-    const int rests = __builtin_amdgcn_readfirstlane(list.count);
-    if (rests > DG_LIST) {
-        // G += R H^T + H R^T over all tiles, H the digits of before, R those of the rests
-#pragma unroll 1
-        for (int tile = slice; tile < jb.ntiles; tile += jb.slices) {
-            fetch(tile);
-#pragma unroll 1
-            for (int h = 0; h < 2; ++h)
+    if (KK == 1 && tile < jb.ntiles) {                   // uniform
+        if (tid == 0) __hip_atomic_store(jb.refused, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return;
+    }
+    const int listed = sort_rests(list, tile);
+    if (KK == 1 && __builtin_amdgcn_readfirstlane(list.full[it & 1])) return;        // (others, in the last tile)
+    // this wave's sums in fp64
+    const double unit = ldexp(1.0, -2 * sc.s);
+    v4d sum[GD_PW];
 #pragma unroll
-                for (int u = 0; u < NL; ++u) {
-                    int q[8];
+    for (int p = 0; p < GD_PW; ++p)
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) {
-                        const float x = __uint_as_float(k & 1 ? raw[u][k >> 1] & 0xffff0000u : raw[u][k >> 1] << 16);
-                        q[k] = h ? rest_of(x, sc.f) : (int)(sc.f * x);
+        for (int v = 0; v < 4; ++v) {
+            double s = 0.0;
+#pragma unroll
+            for (int g = GD_G - 1; g >= 0; --g) s = fma(s, 256.0, (double)acc[p][g][v]);
+            sum[p][v] = s * unit;
+        }
+    if constexpr (KK == 4) if (tile < jb.ntiles) {       // uniform
+        constexpr int ROWS = 16 * NBX;
+        static_assert(4 * ROWS * TC == BUF, "a wide tile takes the place of its digits");
+        auto store_wide = [&](unsigned char* buf) __attribute__((always_inline)) {
+            // row ^ piece: a wave's pieces of one row would all start at one bank
+            v4f* to = reinterpret_cast<v4f*>(buf) + (pcol >> 2) * ROWS + (prow ^ ((pcol >> 3) & 15));
+#pragma unroll
+            for (int u = 0; u < NL; ++u) {
+                float x[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) x[k] = __uint_as_float(k & 1 ? raw[u][k >> 1] & 0xffff0000u : raw[u][k >> 1] << 16);
+                to[u * RU] = (v4f){x[0], x[1], x[2], x[3]};
+                to[u * RU + ROWS] = (v4f){x[4], x[5], x[6], x[7]};
+            }
+        };
+        const int arow = 4 * (ll & 3) + (ll >> 2);
+        // four steps of sixteen columns, of which a lane group has four; the next step's operands are read under the products of this one
+        auto multiply_wide = [&](const v4f* w4, auto full) __attribute__((always_inline)) {
+            v4f a[2][GD_PW], b[2][GD_PW];
+            auto operands = [&](int q) __attribute__((always_inline)) {
+#pragma unroll
+                for (int p = 0; p < GD_PW; ++p)
+                    if (full() || p < np) {              // uniform
+                        a[q & 1][p] = w4[4 * q * ROWS + 16 * bi[p] + (arow ^ (8 * kk + 2 * q + (lg >> 1) & 15))];
+                        b[q & 1][p] = w4[4 * q * ROWS + 16 * bj[p] + (ll ^ (8 * kk + 2 * q + (lg >> 1) & 15))];
                     }
-                    unsigned a[4], b[4];
-                    digits4(q[0], q[1], q[2], q[3], a);
-                    digits4(q[4], q[5], q[6], q[7], b);
+            };
+            operands(0);
 #pragma unroll
-                    for (int d = 0; d < 4; ++d) *reinterpret_cast<v2u*>(dg_dyn + h * BUF + dst + (d * NBX + u * (RU / 16)) * 1024) = (v2u){a[d], b[d]};
-                }
+            for (int q = 0; q < 4; ++q) {
+                if (q < 3) operands(q + 1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+#pragma unroll
+                    for (int p = 0; p < GD_PW; ++p)
+                        if (full() || p < np) sum[p] = mfma_f64(a[q & 1][p][s], b[q & 1][p][s], sum[p]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        fetch(tile);
+        store_wide(dg_dyn);
+        if (tile + jb.slices < jb.ntiles) fetch(tile + jb.slices);
+#pragma unroll 1
+        for (int k = 0; tile < jb.ntiles; tile += jb.slices, k ^= 1) {
             __syncthreads();
-            multiply(dg_dyn + BUF, dg_dyn, std::integral_constant<int, 3>());
-            multiply(dg_dyn, dg_dyn + BUF, std::integral_constant<int, 3>());
-            __syncthreads();
+            if (tile + jb.slices < jb.ntiles) store_wide(dg_dyn + (k ^ 1) * BUF);
+            if (tile + 2 * jb.slices < jb.ntiles) fetch(tile + 2 * jb.slices);
+            const v4f* w4 = reinterpret_cast<const v4f*>(dg_dyn + k * BUF) + (16 * kk + lg) * ROWS;
+            if (np == GD_PW) multiply_wide(w4, std::true_type());
+            else multiply_wide(w4, std::false_type());
         }
     }
-    // G in fp64 (units of 2^-2s): block p at p GB, element (i, j) of a block at 17 i + j (a block is read along rows and columns: with
+    // G: block p at p GB, element (i, j) of a block at 17 i + j (a block is read along rows and columns: with
     // 16 doubles a row the second cost 22 us for 197 rows)
     constexpr int GB = 16 * 17;
     __syncthreads();
@@ -346,45 +425,45 @@ __global__ __launch_bounds__(DG_NT, 2) void k_subspace_gram_digits(Batch<GramDig
                 if (p < np)
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        double s = 0.0;
-#pragma unroll
-                        for (int g = GD_G - 1; g >= 0; --g) s = fma(s, 256.0, (double)acc[p][g][v]);
                         double* d = G + (p0 + p) * GB + (4 * lg + v) * 17 + ll;
-                        *d = round == 0 ? s : *d + s;
+                        *d = round == 0 ? sum[p][v] : *d + sum[p][v];
                     }
         }
         __syncthreads();
     }
-    // the listed rests: row and column i of G gain rest x_j, the diagonal element rest (2 x_i - rest); eight columns of X on their way
-    const int listed = rests > DG_LIST ? 0 : rests;
-    for (int e0 = 0; e0 < listed; e0 += 8) {
-        unsigned short w[8];
+    // The listed rests R of digits H: row and column i of G gain R_i x_j, the diagonal element R_i (2 x_i - R_i).  Where both values of a
+    // product have one, R_i (H_j + R_j) + H_i R_j is what is missing: the lower row meets the upper one without its rest.  DG_AHEAD columns
+    // of X on their way
+    // (element (lo, hi) of G belongs to thread hi while the entries of rows lo are added, and to thread lo for those of rows hi)
+    for (int e0 = 0; e0 < listed; e0 += DG_AHEAD) {
+        unsigned short w[DG_AHEAD];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int id = list.order[e0 + k < listed ? e0 + k : e0], tile = list.tile[id], c = list.at[id] & 0xffff;
-            const int o = (unsigned)tile / (unsigned)jb.tiles_per_o;
-            w[k] = X[((long long)o * n + (tid < n ? tid : 0)) * inner + (long long)(tile - o * jb.tiles_per_o) * TC + c];
+        for (int k = 0; k < DG_AHEAD; ++k) {
+            const int e = e0 + k < listed ? e0 + k : 0, t = list.tile(e), o = (unsigned)t / (unsigned)jb.tiles_per_o;
+            w[k] = X[((long long)o * n + (tid < n ? tid : 0)) * inner + (long long)(t - o * jb.tiles_per_o) * TC + list.col(e)];
         }
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            if (e0 + k >= listed) break;                 // uniform
-            const int id = list.order[e0 + k], i = list.at[id] >> 16;
-            const int lo = tid < i ? tid : i, hi = tid < i ? i : tid, bl = lo >> 4, bh = hi >> 4;
-            const int at = bl * NB - (bl * (bl - 1)) / 2 + bh - bl - first;
-            if (tid < n && at >= 0 && at < mine) {
-                const double rest = (double)list.rest[id] * 0x1p-24, x = (double)(sc.f * __uint_as_float((unsigned)w[k] << 16));
-                const double add = rest * (tid == i ? 2.0 * x - rest : x);
-                double* g = G + at * GB;
-                const int a = lo & 15, b = hi & 15;
-                g[17 * a + b] += add;
-                if (bl == bh && a != b) g[17 * b + a] += add;            // (a diagonal block is held in full)
-            }
+        for (int below = 0; below < 2; ++below) {
+            if (tid < n)
+#pragma unroll
+                for (int k = 0; k < DG_AHEAD; ++k) {
+                    if (e0 + k >= listed) break;         // uniform
+                    const int i = __builtin_amdgcn_readfirstlane(list.row(e0 + k));
+                    const int lo = below ? tid : i, hi = below ? i : tid, bl = lo >> 4, bh = hi >> 4;
+                    const int at = bl * NB - (bl * (bl - 1)) / 2 + bh - bl - first;
+                    if (hi < lo || (below && hi == lo) || at < 0 || at >= mine) continue;
+                    const float x = sc.f * __uint_as_float((unsigned)w[k] << 16), rest = list.rest[e0 + k];
+                    const double add = (double)rest * unit * (tid == i ? 2.0 * (double)x - (double)rest : (double)(below ? x : (float)(int)x));
+                    double* g = G + at * GB;
+                    const int a = lo & 15, b = hi & 15;
+                    g[17 * a + b] += add;
+                    if (bl == bh && a != b) g[17 * b + a] += add;        // (a diagonal block is held in full)
+                }
             __syncthreads();
         }
     }
     // P = G U, this workgroup's blocks of G: a wave takes a block of 16 outputs, requests all of U for it at once, and walks its
     // share of the row blocks
-    const double unit = ldexp(1.0, -2 * sc.s);
     const int nqb = (r + 15) >> 4;
     for (int qb = wave % nqb; qb < nqb; qb += DG_NT / 64) {
         const int q = 16 * qb + ll;
@@ -422,7 +501,7 @@ __global__ __launch_bounds__(DG_NT, 2) void k_subspace_gram_digits(Batch<GramDig
                 if (at >= 0) {                                         // uniform
 #pragma unroll
                     for (int s = 0; s < 4; ++s) {
-                        const double uu = 16 * kb + 4 * s + lg < n && q < r ? (double)u[kb][s] * unit : 0.0;
+                        const double uu = 16 * kb + 4 * s + lg < n && q < r ? (double)u[kb][s] : 0.0;
                         if (s & 1) o1 = __builtin_amdgcn_mfma_f64_16x16x4f64(x[kb & 1][s], uu, o1, 0, 0, 0);
                         else o = __builtin_amdgcn_mfma_f64_16x16x4f64(x[kb & 1][s], uu, o, 0, 0, 0);
                     }
@@ -549,8 +628,9 @@ __global__ __launch_bounds__(VD_NT) void k_v_digits(Batch<VDigitsJob> bt) {
 // 192), so that X is read and cut once.  Chunks of 64 columns: X through registers (a wave eight columns, a lane one row: bytes of
 // consecutive columns are what a lane multiplies, so the cut also transposes), the digits of V copied to LDS as they are.  Two
 // buffers each, one barrier a chunk.  Wave w: row blocks 2 (w % 2) and the next, output blocks QB (w / 2) to QB (w / 2) + QB - 1;
-// seven int32 accumulators a block.
-constexpr int PD_MAX_CPS = 128;          // chunks per range: 4 digit products of 2^14, 64 columns: 2^29, and twice that where there are rests
+// seven int32 accumulators a block.  Chunks from the first one on whose rests find no room on the list are multiplied on the fp64 MFMA, V as
+// it is and X wide ([four columns][row] 16 bytes) in the place of their digits.
+constexpr int PD_MAX_CPS = 128;          // chunks per range: 4 digit products of 2^14, 64 columns: 2^29
 struct PairDigitsJob {
     const void* X;                       // (ncols, n) bf16
     const float* V;                      // (ncols, r)
@@ -582,7 +662,7 @@ __global__ __launch_bounds__(DG_NT, 2) void k_pair_digits(Batch<PairDigitsJob> b
     const long long c_beg = (long long)z * jb.cps * 64, left = jb.ncols - c_beg;
     const int cols = (int)(left < (long long)jb.cps * 64 ? left : (long long)jb.cps * 64), chunks = (cols + 63) >> 6;
     const Scale sc = tensor_scale(jb.amax, red);         // (not finite: neither is V, and its scales are NaN)
-    if (tid == 0) list.count = 0;
+    if (tid == 0) list.count = list.full[0] = list.full[1] = 0;
     const int vb = nqb * 4096;                           // bytes of a chunk of V
     unsigned char* const xbuf = dg_dyn;
     unsigned char* const vbuf = dg_dyn + 2 * XB;
@@ -616,7 +696,7 @@ __global__ __launch_bounds__(DG_NT, 2) void k_pair_digits(Batch<PairDigitsJob> b
         digits4(q[4], q[5], q[6], q[7], b);
 #pragma unroll
         for (int d = 0; d < 4; ++d) *reinterpret_cast<v2u*>(buf + xdst + d * 4096) = (v2u){a[d], b[d]};
-        if (any_below(small, sc.low)) list_rests(list, ch, pk, sc.f, sc.low, lane, 8 * wave);
+        if (any_below(small, sc.low)) list_rests(list, ch, ch & 1, list_room(ch + 1), pk, sc.f, sc.low, lane, 8 * wave);
     };
     auto copy_v = [&](int ch, unsigned char* buf) __attribute__((always_inline)) {
         for (int pc = wave; pc < 4 * nqb; pc += DG_NT / 64) copy16_to_lds(vsrc + (long long)ch * vb, vb, pc * 1024 + lane * 16, buf + pc * 1024);
@@ -630,8 +710,7 @@ __global__ __launch_bounds__(DG_NT, 2) void k_pair_digits(Batch<PairDigitsJob> b
 #pragma unroll
             for (int g = 0; g < G; ++g) acc[b][k][g] = (v4i){0, 0, 0, 0};
     const int rb = 2 * (wave & 1), qb0 = QB * (wave >> 1);
-    auto multiply = [&](const unsigned char* bx, const unsigned char* bv, auto rest) __attribute__((always_inline)) {
-        constexpr int LOW = decltype(rest)::value;       // 3: digits of X three positions lower
+    auto multiply = [&](const unsigned char* bx, const unsigned char* bv) __attribute__((always_inline)) {
         v4i a[2][4];
 #pragma unroll
         for (int b = 0; b < 2; ++b)
@@ -647,9 +726,8 @@ __global__ __launch_bounds__(DG_NT, 2) void k_pair_digits(Batch<PairDigitsJob> b
                 for (int i = 0; i < 4; ++i)
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
-                        if (i + j >= LOW)
 #pragma unroll
-                            for (int b = 0; b < 2; ++b) acc[b][k][i + j - LOW] = mfma_i8(a[b][i], v[j], acc[b][k][i + j - LOW]);
+                        for (int b = 0; b < 2; ++b) acc[b][k][i + j] = mfma_i8(a[b][i], v[j], acc[b][k][i + j]);
             }
     };
     copy_v(0, vbuf);
@@ -657,42 +735,24 @@ __global__ __launch_bounds__(DG_NT, 2) void k_pair_digits(Batch<PairDigitsJob> b
     __syncthreads();                                     // the list is empty
     store(0, xbuf);
     if (chunks > 1) fetch(1);
+    int ch = 0;
 #pragma unroll 1
-    for (int ch = 0; ch < chunks; ++ch) {
+    for (; ch < chunks; ++ch) {
         const int cur = ch & 1;
         wait_copies_and_sync<0>();                       // this chunk's digits are there, the other buffers are no longer read
+        // (the flag of this parity is written again behind the next barrier only: the same for all waves)
+        if (__builtin_amdgcn_readfirstlane(list.full[cur])) break;
         if (ch + 1 < chunks) {
             copy_v(ch + 1, vbuf + (cur ^ 1) * vb);
             store(ch + 1, xbuf + (cur ^ 1) * XB);
         }
         if (ch + 2 < chunks) fetch(ch + 2);
-        multiply(xbuf + cur * XB, vbuf + cur * vb, std::integral_constant<int, 0>());
+        multiply(xbuf + cur * XB, vbuf + cur * vb);
     }
-    sort_rests(list);
-    const int rests = __builtin_amdgcn_readfirstlane(list.count);
-    if (rests > DG_LIST) {
-        // the rests of all values
-#pragma unroll 1
-        for (int ch = 0; ch < chunks; ++ch) {
-            copy_v(ch, vbuf);
-            fetch(ch);
-            const int c0 = 64 * ch + 8 * wave;
-            int q[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) q[k] = rest_of(iin && c0 + k < cols ? __uint_as_float((unsigned)raw[k] << 16) : 0.f, sc.f);
-            unsigned a[4], b[4];
-            digits4(q[0], q[1], q[2], q[3], a);
-            digits4(q[4], q[5], q[6], q[7], b);
-#pragma unroll
-            for (int d = 0; d < 4; ++d) *reinterpret_cast<v2u*>(xbuf + xdst + d * 4096) = (v2u){a[d], b[d]};
-            wait_copies_and_sync<0>();
-            multiply(xbuf, vbuf, std::integral_constant<int, 3>());
-            __syncthreads();
-        }
-    }
+    const int listed = sort_rests(list, ch);
     double* __restrict__ out = jb.part + (long long)z * n * r;
     const double unit = ldexp(1.0, -sc.s);
-    double sum[2][QB][4];
+    v4d sum[2][QB];
 #pragma unroll
     for (int k = 0; k < QB; ++k) {
         const int q = 16 * (qb0 + k) + ll;
@@ -707,29 +767,93 @@ __global__ __launch_bounds__(DG_NT, 2) void k_pair_digits(Batch<PairDigitsJob> b
                 sum[b][k][v] = s * vs;
             }
     }
-    // the listed rests: row i gains rest V[c]; four rows of V on their way
-    const int listed = rests > DG_LIST ? 0 : rests;
-    for (int e0 = 0; e0 < listed; e0 += 4) {
-        float vv[4][QB];
+    if (ch < chunks) {                                   // uniform
+        auto store_wide = [&](int ch, unsigned char* buf) __attribute__((always_inline)) {
+            const int c0 = 64 * ch + 8 * wave;
+            float x[8];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int id = list.order[e0 + e < listed ? e0 + e : e0];
-            const float* row = jb.V + (c_beg + 64LL * list.tile[id] + (list.at[id] & 0xffff)) * r;
+            for (int k = 0; k < 8; ++k) x[k] = iin && c0 + k < cols ? __uint_as_float((unsigned)raw[k] << 16) : 0.f;
+            v4f* to = reinterpret_cast<v4f*>(buf) + 2 * wave * 64 + lane;
+            to[0] = (v4f){x[0], x[1], x[2], x[3]};
+            to[64] = (v4f){x[4], x[5], x[6], x[7]};
+        };
+        auto copy_wide = [&](int ch, unsigned char* buf) __attribute__((always_inline)) {        // 64 rows of r floats
+            const int here = cols - 64 * ch < 64 ? cols - 64 * ch : 64;
+            for (int pc = wave; 4 * pc < r; pc += DG_NT / 64)
+                copy16_to_lds(jb.V + (c_beg + 64LL * ch) * r, (4 * here * r + 15) & ~15, pc * 1024 + lane * 16, buf + pc * 1024);
+        };
+        const int arow = 4 * (ll & 3) + (ll >> 2);
+        // four steps of sixteen columns, of which a lane group has four; the next step's operands are read under the products of this one
+        auto multiply_wide = [&](const v4f* xw, const float* vw, int here, auto full) __attribute__((always_inline)) {
+            v4f a[2][2];
+            float y[2][QB][4];
+            auto operands = [&](int q4) __attribute__((always_inline)) {
+                a[q4 & 1][0] = xw[4 * 64 * q4];
+                a[q4 & 1][1] = xw[4 * 64 * q4 + 16];
+#pragma unroll
+                for (int k = 0; k < QB; ++k)
+                    if (full() || qb0 + k < nqb)         // uniform
+#pragma unroll
+                        for (int s = 0; s < 4; ++s) y[q4 & 1][k][s] = vw[(16 * q4 + s) * r + 16 * k];
+            };
+            operands(0);
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                if (q4 < 3) operands(q4 + 1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+#pragma unroll
+                    for (int k = 0; k < QB; ++k)
+                        if (full() || qb0 + k < nqb) {
+                            const float v = full() || 16 * q4 + s < here ? y[q4 & 1][k][s] : 0.f;        // (what lies behind V's end)
+                            sum[0][k] = mfma_f64(a[q4 & 1][0][s], v, sum[0][k]);
+                            sum[1][k] = mfma_f64(a[q4 & 1][1][s], v, sum[1][k]);
+                        }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        fetch(ch);
+        copy_wide(ch, vbuf);
+        store_wide(ch, xbuf);
+        if (ch + 1 < chunks) fetch(ch + 1);
+#pragma unroll 1
+        for (int k2 = 0; ch < chunks; ++ch, k2 ^= 1) {
+            wait_copies_and_sync<0>();
+            if (ch + 1 < chunks) {
+                copy_wide(ch + 1, vbuf + (k2 ^ 1) * vb);
+                store_wide(ch + 1, xbuf + (k2 ^ 1) * XB);
+            }
+            if (ch + 2 < chunks) fetch(ch + 2);
+            const v4f* xw = reinterpret_cast<const v4f*>(xbuf + k2 * XB) + lg * 64 + 16 * rb + arow;
+            const float* vw = reinterpret_cast<const float*>(vbuf + k2 * vb) + 4 * lg * r + 16 * qb0 + ll;
+            const int here = cols - 64 * ch;
+            if (here >= 64 && qb0 + QB <= nqb) multiply_wide(xw, vw, 64, std::true_type());
+            else multiply_wide(xw, vw, here - 4 * lg, std::false_type());
+        }
+    }
+    // the listed rests: row i gains rest V[c]; DG_AHEAD rows of V on their way
+    for (int e0 = 0; e0 < listed; e0 += DG_AHEAD) {
+        float vv[DG_AHEAD][QB];
+#pragma unroll
+        for (int e = 0; e < DG_AHEAD; ++e) {
+            const int id = e0 + e < listed ? e0 + e : 0;
+            const float* row = jb.V + (c_beg + 64LL * list.tile(id) + list.col(id)) * r;
 #pragma unroll
             for (int k = 0; k < QB; ++k) vv[e][k] = row[16 * (qb0 + k) + ll < r ? 16 * (qb0 + k) + ll : 0];
         }
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
+        for (int e = 0; e < DG_AHEAD; ++e) {
             if (e0 + e >= listed) break;                 // uniform
-            const int id = list.order[e0 + e], row = list.at[id] >> 16;
-            const double rest = (double)list.rest[id] * 0x1p-24 * unit;
+            const int row = __builtin_amdgcn_readfirstlane(list.row(e0 + e));
+            const double rest = ((row >> 2) & 3) == lg ? (double)list.rest[e0 + e] * unit : 0.0;
 #pragma unroll
             for (int b = 0; b < 2; ++b)
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
-                    if (row == 16 * (rb + b) + 4 * lg + v)
+                    if (row >> 4 == rb + b && (row & 3) == v)            // uniform
 #pragma unroll
-                        for (int k = 0; k < QB; ++k) sum[b][k][v] = fma(rest, (double)vv[e][k], sum[b][k][v]);
+                        for (int k = 0; k < QB; ++k) sum[b][k][v] = rest != 0.0 ? fma(rest, (double)vv[e][k], sum[b][k][v]) : sum[b][k][v];
         }
     }
 #pragma unroll
@@ -777,12 +901,12 @@ int subspace_gram_digits_nwg(long long outer, int n, long long inner) {
     return gram_digits_shape(outer, n, inner, &jb) ? jb.slices * jb.parts : 0;
 }
 bool make_subspace_gram_digits(const void* X, long long outer, int n, long long inner, const float* U, int r, double* part, int nwg,
-                               const unsigned* amax, Item* out) {
+                               const unsigned* amax, int32_t* refused, Item* out) {
     GramDigitsJob jb;
     std::memset(&jb, 0, sizeof(jb));
-    if (!gram_digits_shape(outer, n, inner, &jb) || jb.slices * jb.parts != nwg) return false;
+    if (!gram_digits_shape(outer, n, inner, &jb) || jb.slices * jb.parts > nwg || (n > 64 && !refused)) return false;
     if (!X || !U || !part || !amax || r < 1 || reinterpret_cast<uintptr_t>(X) % 16 != 0) return false;
-    jb.X = X; jb.U = U; jb.part = part; jb.amax = amax; jb.outer = outer; jb.inner = inner; jb.n = n; jb.r = r;
+    jb.X = X; jb.U = U; jb.part = part; jb.amax = amax; jb.outer = outer; jb.inner = inner; jb.n = n; jb.r = r; jb.refused = refused;
     *out = Item();
     out->kind = IT_DIGITS;
     out->key = n <= 64 ? 1 : 2;

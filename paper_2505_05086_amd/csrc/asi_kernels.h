@@ -227,11 +227,11 @@ hipError_t launch_gram_items(const Item* const* items, int n, hipStream_t st);
 // eight, X 16-byte aligned; the same holds for the Gram form).
 constexpr int kAmaxParts = 512;
 bool make_amax_bf16(const void* X, long long numel, unsigned* out_max, int32_t* zero, int nzero, Item* out);
-// P = (A_m A_m^T) U_prev for modes of 33 to 256 entries over an inner extent that is a multiple of eight: part is (nwg, n, r); 0: not
-// supported
+// P = (A_m A_m^T) U_prev for modes of 33 to 256 entries over an inner extent that is a multiple of eight: part is (nwg, n, r), nwg the
+// number below (0: not supported) or more; for n > 64, *refused (zero before) is set where the values don't suit, and part left undefined
 int subspace_gram_digits_nwg(long long outer, int n, long long inner);
 bool make_subspace_gram_digits(const void* X, long long outer, int n, long long inner, const float* U, int r, double* part, int nwg,
-                               const unsigned* amax, Item* out);
+                               const unsigned* amax, int32_t* refused, Item* out);
 // P = A_m V along a last mode: V, given as ks partial products, as digits (make_v_digits), then the product; part is (nsplit, n, r);
 // no splits: not supported
 int pair_digits_splits(long long ncols, int n, int r);
@@ -250,10 +250,11 @@ int subspace_small_nwg(long long outer, int n, long long inner);
 bool make_subspace_small(DType xt, const void* X, long long outer, int n, long long inner, const float* U, int r,
                          double* part, int nwg, int32_t* zero, int nzero, Item* out);
 // ---- fused V/P step for modes with 64 < n <= 512 and r <= 64 (asi_long.hip): part is (nsplit, n, r) fp64 -------
+// only_if: nothing is done where *only_if is zero when the kernel starts, and nsplit may be larger (partial sums of zeros then)
 bool subspace_long_supported(long long outer, int n, long long inner, int r);
 int subspace_long_splits(long long outer, int n, long long inner, int r);
 bool make_subspace_long(DType xt, const void* X, long long outer, int n, long long inner, const float* U, int r,
-                        double* part, int nsplit, int32_t* zero, int nzero, Item* out);
+                        double* part, int nsplit, int32_t* zero, int nzero, Item* out, const int32_t* only_if = nullptr);
 
 // The last two modes of X seen as (planes, rows, cols), planes of up to 64 x 64, both from one read of X (asi_planes.hip):
 // part_rows is (nwg, rows, r_rows), part_cols (nwg, cols, r_cols).

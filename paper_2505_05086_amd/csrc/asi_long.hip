@@ -46,6 +46,7 @@ struct LongJob {
     int ncg, gy;             // column groups (= partial sums) x column blocks of U
     int32_t* zero;           // nullable: `nzero` int32 the kernel clears (arrival counters of later launches)
     int nzero;
+    const int32_t* only_if;  // nullable: nothing is done where it is zero
 };
 
 extern __shared__ __align__(16) float lg_dyn[];
@@ -100,6 +101,7 @@ __global__ __launch_bounds__(LG_NT) void k_subspace_long(Batch<LongJob> bt) {
     double* Vd = reinterpret_cast<double*>(lg_dyn + SH::XS + SH::VP);
     int lb;
     const LongJob& jb = bt.job[locate(bt, &lb)];
+    if (jb.only_if && *jb.only_if == 0) return;
     const T* __restrict__ X = static_cast<const T*>(jb.X);
     const int n = jb.n, r = jb.r;
     const long long inner = jb.inner, ncols = jb.ncols;
@@ -282,14 +284,15 @@ int subspace_long_splits(long long outer, int n, long long inner, int r) {
 
 // key: [0] bf16, [1] 16-byte pieces, [4..7] NRB, [8..11] NCB, [12..15] NBQ
 bool make_subspace_long(DType xt, const void* X, long long outer, int n, long long inner, const float* U, int r,
-                        double* part, int nsplit, int32_t* zero, int nzero, Item* out) {
+                        double* part, int nsplit, int32_t* zero, int nzero, Item* out, const int32_t* only_if) {
     if (!subspace_long_supported(outer, n, inner, r) || !X || !U || !part || nzero < 0 || nzero > 256) return false;
     LongJob jb;
     std::memset(&jb, 0, sizeof(jb));
     jb.X = X; jb.U = U; jb.part = part; jb.outer = outer; jb.inner = inner; jb.n = n; jb.r = r;
-    jb.zero = zero; jb.nzero = zero ? nzero : 0;
+    jb.zero = zero; jb.nzero = zero ? nzero : 0; jb.only_if = only_if;
     long_geometry(outer, n, inner, r, &jb);
-    if (jb.ncg != nsplit) return false;
+    if (jb.ncg > nsplit || (jb.ncg < nsplit && !only_if)) return false;
+    jb.ncg = nsplit;                     // (groups past the last tile leave zeros)
     int nrb, ncb, nbq;
     long_shape(n, r, &nrb, &ncb, &nbq);
     *out = Item();
