@@ -3,9 +3,9 @@
 // The same implicit GEMM as asi_corr.hip (M = o, N = (tap, j), K = (i, y, x); a workgroup owns 64 output channels x 16 core
 // channels x 9 taps and walks its share of K in chunks), with every fp32 operand as the exact sum of three bf16 terms
 // (x = h + m + l, eight significant bits each, rounded to nearest): a product is the six term products h h, h m, m h, m m, h l,
-// l h, each exact in fp32 and summed in fp32; the three left out are below 2^-25 of it, an eighth of what one rounding of
-// the sum costs.  16 x 16 x 32 multiply-adds are 6 x 16 cycles so, 8 x 32 on the fp32 MFMA, and a sum of 32 products is rounded
-// once per term product instead of eight times.
+// l h, each exact in fp32 and summed in fp32; the three left out are below 2^-24 of it, 2^-27.4 (rms) on normal data, where one
+// rounding of the sum is up to 2^-24 of the sum so far.  16 x 16 x 32 multiply-adds are 6 x 16 cycles so, 8 x 32 on the fp32 MFMA, and a
+// sum of 32 products is rounded once per term product instead of eight times.
 //
 // A K slot group of a lane is eight consecutive output positions x of one row (rows are padded to a multiple of eight with
 // zeros of G1).  Their B operands for the three taps of a kernel row are three windows of ten consecutive entries of a slab
@@ -26,6 +26,7 @@
 
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 
 namespace asi {
 
@@ -43,7 +44,7 @@ constexpr int CS_TS_LD = 16 * 9 + 1;             // result tile: 64 rows of (j, 
 constexpr size_t CS_LDS_MAX = 160 * 1024;
 
 static size_t split_lds(const CorrPlan& p) {
-    const size_t work = 2 * 3 * 2 * (size_t)p.zt + 16 * 4 * (size_t)p.nk, result = sizeof(float) * 2 * CR_TO * CS_TS_LD;
+    const size_t work = 2 * 3 * 2 * (size_t)p.zt + 16 * 4 * (size_t)p.nk, result = sizeof(float) * 2 * CR_TO * CS_TS_LD + 16;
     return work > result ? work : result;
 }
 
@@ -117,6 +118,13 @@ __device__ __forceinline__ void split_pair(float a, float b, unsigned& h, unsign
     const float sa = ra - __uint_as_float(m << 16), sb = rb - __uint_as_float(m & 0xffff0000u);
     l = __builtin_bit_cast(unsigned, __builtin_convertvector((v2f){sa, sb}, v2bf));
 }
+// What two fp32 values are, as a dword of two bf16: +-1, 0, +-Inf or NaN.  *huge: one is finite and its first term is not.
+__device__ __forceinline__ unsigned sign_or_special(float x, bool* huge) {
+    const unsigned u = __float_as_uint(x), e = u & 0x7fffffffu;
+    if (e >= 0x7f7f8000u && e < 0x7f800000u) *huge = true;
+    return e == 0 ? 0u : (u >> 16 & 0x8000u) | (e < 0x7f800000u ? 0x3f80u : (e == 0x7f800000u ? 0x7f80u : 0x7fc0u));
+}
+__device__ __forceinline__ unsigned class_pair(float a, float b, bool* huge) { return sign_or_special(a, huge) | sign_or_special(b, huge) << 16; }
 // a register's copy (left to itself the compiler reads an operand that starts at an odd register from LDS once more, dword by dword
 // and with four lanes to a bank, which costs the LDS as long as the products take)
 __device__ __forceinline__ unsigned copy(unsigned x) {
@@ -148,15 +156,6 @@ __global__ __launch_bounds__(CS_NT) void k_corr_mfma_split(Batch<CorrJob> bt) {
     const int bufsz = 3 * pl.zt;                         // elements of one buffer
     unsigned short* const buf = reinterpret_cast<unsigned short*>(cs_dyn);
     int4* const tab = reinterpret_cast<int4*>(cs_dyn + 4 * (size_t)bufsz);
-
-    // entry of a position group: slab offset of its window origin, byte offset of its G1 values, (core channel, row), positions
-    for (int e = tid; e < 4 * pl.nk; e += CS_NT) {
-        const int per = pl.ry * pl.ow, ii = e / per, rem = e - ii * per, yl = rem / pl.ow, ox = rem - yl * pl.ow;
-        const bool in = ii < pl.ni;
-        const int left = g.Wo - 8 * ox;
-        tab[e] = in ? make_int4(ii * pl.zi + yl * g.sh * pl.px + 8 * ox, 4 * (ii * g.cout * HoWo + yl * g.Wo + 8 * ox), (ii << 16) | yl, left < 8 ? left : 8)
-                    : make_int4(0, 0, 0xffff, 0);
-    }
 
     // What a thread's loads of Z depend on, whatever the chunk: pair (core channel ii, core channel j, slab row, two columns)
     const int npr = (pl.wp + 1) >> 1, pairs = pl.ni * 16 * pl.rows_in * npr;
@@ -200,12 +199,19 @@ __global__ __launch_bounds__(CS_NT) void k_corr_mfma_split(Batch<CorrJob> bt) {
                 zrow |= (row == rowc && iin) ? (1u << u) : 0u;
             }
     };
-    auto store_z = [&](unsigned short* b) __attribute__((always_inline)) {
+    bool huge = false, z_special = false;                // what the second walk has met
+    auto store_z = [&](unsigned short* b, auto plain) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < CS_NP; ++u)
             if (u < nzu && meta_z[u] >= 0) {
-                unsigned h, m, l;
-                split_pair(((zrow & fix0) >> u) & 1u ? z0[u] : 0.f, ((zrow & fix1) >> u) & 1u ? z1[u] : 0.f, h, m, l);
+                const float x0 = ((zrow & fix0) >> u) & 1u ? z0[u] : 0.f, x1 = ((zrow & fix1) >> u) & 1u ? z1[u] : 0.f;
+                unsigned h, m = 0, l = 0;
+                if constexpr (plain()) {
+                    h = class_pair(x0, x1, &huge);
+                    z_special = z_special || !(fabsf(x0) < INFINITY) || !(fabsf(x1) < INFINITY);
+                } else {
+                    split_pair(x0, x1, h, m, l);
+                }
                 unsigned short* d = b + (meta_z[u] >> 12);
                 if constexpr (SW == 1) {
                     *reinterpret_cast<unsigned*>(d) = h;
@@ -249,170 +255,208 @@ __global__ __launch_bounds__(CS_NT) void k_corr_mfma_split(Batch<CorrJob> bt) {
     };
 
     v4f acc[CS_OB][9];
-#pragma unroll
-    for (int ob = 0; ob < CS_OB; ++ob)
-#pragma unroll
-        for (int t = 0; t < 9; ++t) acc[ob][t] = (v4f){0.f, 0.f, 0.f, 0.f};
-
-    // the chunk being multiplied (c), the next (n): group of core channels and chunk of rows
-    const int ig0 = ch_beg / pl.nyc;
-    int c_i = ig0 * pl.ni, c_y = ch_beg - ig0 * pl.nyc;
-    auto advance = [&](int& i, int& y) __attribute__((always_inline)) {
-        if (++y == pl.nyc) { y = 0; i += pl.ni; }
-    };
-    int n_i = c_i, n_y = c_y;
-    // the first loads of Z, then (the table is complete) of G1; the buffers are cleared while they are on their way
-    if (ch_beg < ch_end) fetch_z(c_i, c_y);
-    __syncthreads();
-    if (ch_beg < ch_end && kgrp < pl.nk) fetch_a(c_i, c_y, kgrp);
-    for (int e = tid; e < bufsz / 4; e += CS_NT) reinterpret_cast<uint4*>(buf)[e] = make_uint4(0u, 0u, 0u, 0u);   // both buffers
-    __syncthreads();
-    if (ch_beg < ch_end) {
-        store_z(buf);
-        advance(n_i, n_y);
-    }
-    if (ch_beg + 1 < ch_end) fetch_z(n_i, n_y);
-    __syncthreads();
-    const int khs = g.dh * pl.px;
-#pragma unroll 1
-    for (int ch = ch_beg; ch < ch_end; ++ch) {
-        const int cur = (ch - ch_beg) & 1;
-        const bool more = ch + 1 < ch_end;
-        int f_i = n_i, f_y = n_y;
-        if (more) {
-            store_z(buf + (cur ^ 1) * bufsz);
-            if (ch + 2 < ch_end) {
-                advance(f_i, f_y);
-                fetch_z(f_i, f_y);
-            }
-        }
-#pragma unroll 1
-        for (int kb = kgrp; kb < pl.nk; kb += CS_KG) {
-            // this K block's G1 as bf16 terms; the next one's is requested
-            v4u a[CS_OB][3];
-#pragma unroll
-            for (int ob = 0; ob < CS_OB; ++ob)
-#pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    float x = __uint_as_float(araw[ob][d >> 1][2 * (d & 1)]), y = __uint_as_float(araw[ob][d >> 1][2 * (d & 1) + 1]);
-                    if (RAGGED) {
-                        x = 2 * d < a_left ? x : 0.f;
-                        y = 2 * d + 1 < a_left ? y : 0.f;
-                    }
-                    unsigned h, m, l;
-                    split_pair(x, y, h, m, l);
-                    a[ob][0][d] = h; a[ob][1][d] = m; a[ob][2][d] = l;
-                }
-            const unsigned short* zb = buf + cur * bufsz + a_org + ll * pl.zj;
-            if (kb + CS_KG < pl.nk) fetch_a(c_i, c_y, kb + CS_KG);
-            else if (more) fetch_a(n_i, n_y, kgrp);
-            constexpr int WD = SW == 1 ? 5 : 9;          // dwords of a window; stride two: five even, four odd
-            unsigned w[2][3][WD];
-            auto window = [&](int kh, unsigned (&d)[3][WD]) __attribute__((always_inline)) {
-#pragma unroll
-                for (int t = 0; t < 3; ++t) {
-                    const unsigned short* zr = zb + t * pl.zt + kh * khs;
-                    const v4u q = *reinterpret_cast<const v4u*>(zr);
-                    d[t][0] = q[0]; d[t][1] = q[1]; d[t][2] = q[2]; d[t][3] = q[3];
-                    d[t][4] = *reinterpret_cast<const unsigned*>(zr + 8);
-                    if constexpr (SW == 2) {
-                        const v4u o = *reinterpret_cast<const v4u*>(zr + (pl.px >> 1));
-                        d[t][5] = o[0]; d[t][6] = o[1]; d[t][7] = o[2]; d[t][8] = o[3];
-                    }
-                }
-            };
-            window(0, w[0]);
-#pragma unroll
-            for (int kh = 0; kh < 3; ++kh) {
-                if (kh < 2) window(kh + 1, w[(kh + 1) & 1]);
-                __builtin_amdgcn_sched_barrier(0);
-                const unsigned (&d)[3][WD] = w[kh & 1];
-                v4u b[3][3];                             // [tap of the row][term]
-#pragma unroll
-                for (int t = 0; t < 3; ++t) {
-                    b[0][t] = (v4u){d[t][0], d[t][1], d[t][2], d[t][3]};
-                    v4u next;                            // the window one entry on
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) next[q] = __builtin_amdgcn_alignbit(d[t][q + 1], d[t][q], 16);
-                    if constexpr (SW == 1) {
-                        b[1][t] = next;
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) b[2][t][q] = copy(d[t][q + 1]);
-                    } else {
-                        b[1][t] = (v4u){d[t][WD - 4], d[t][WD - 3], d[t][WD - 2], d[t][WD - 1]};
-                        b[2][t] = next;
-                    }
-                }
-                // small terms first; six accumulators take turns
-                constexpr int TA[6] = {2, 0, 1, 1, 0, 0}, TB[6] = {0, 2, 1, 0, 1, 0};
-#pragma unroll
-                for (int p = 0; p < 6; ++p)
-#pragma unroll
-                    for (int dx = 0; dx < 3; ++dx)
-#pragma unroll
-                        for (int ob = 0; ob < CS_OB; ++ob) acc[ob][3 * kh + dx] = mfma_bf16(a[ob][TA[p]], b[dx][TB[p]], acc[ob][3 * kh + dx]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-        c_i = n_i; c_y = n_y;
-        n_i = f_i; n_y = f_y;
-        __syncthreads();
-    }
-
-    // lane holds o = o0 + 16 (2 wo + ob) + 4 lg + v, j = j0 + ll.  The K groups add their tiles in LDS in a fixed order (groups 2
-    // and 3 write two tiles, 0 and 1 add to them, the store adds the two), and for one output channel the (j, tap) values of
-    // this workgroup are then one contiguous run of T.
-    const long long total = (long long)g.cout * g.r2 * 9;
-    const int nj = (g.r2 - j0 < 16) ? g.r2 - j0 : 16;
     float* Ts = reinterpret_cast<float*>(cs_dyn);
     constexpr int TS_SZ = CR_TO * CS_TS_LD;
+    volatile int* const met = reinterpret_cast<int*>(Ts + 2 * TS_SZ);    // behind the tiles: what any thread has met
+    // This workgroup's share of K, summed into the tiles Ts.  plain: of the operands' signs (Inf and NaN as they are) instead
+    auto walk = [&](auto plain) __attribute__((always_inline)) {
 #pragma unroll
-    for (int round = 0; round < 2; ++round) {
-        if (kgrp >> 1 == 1 - round) {
-            float* Tg = Ts + (kgrp & 1) * TS_SZ;
+        for (int ob = 0; ob < CS_OB; ++ob)
 #pragma unroll
-            for (int ob = 0; ob < CS_OB; ++ob)
-#pragma unroll
-                for (int t = 0; t < 9; ++t)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        float* p = &Tg[(16 * (CS_OB * wo + ob) + 4 * lg + v) * CS_TS_LD + ll * 9 + t];
-                        *p = round == 0 ? acc[ob][t][v] : *p + acc[ob][t][v];
-                    }
+            for (int t = 0; t < 9; ++t) acc[ob][t] = (v4f){0.f, 0.f, 0.f, 0.f};
+
+        // the chunk being multiplied (c), the next (n): group of core channels and chunk of rows
+        const int ig0 = ch_beg / pl.nyc;
+        int c_i = ig0 * pl.ni, c_y = ch_beg - ig0 * pl.nyc;
+        auto advance = [&](int& i, int& y) __attribute__((always_inline)) {
+            if (++y == pl.nyc) { y = 0; i += pl.ni; }
+        };
+        int n_i = c_i, n_y = c_y;
+        // the first loads of Z, then (the table is complete) of G1; the buffers are cleared while they are on their way
+        if (ch_beg < ch_end) fetch_z(c_i, c_y);
+        // entry of a position group: slab offset of its window origin, byte offset of its G1 values, (core channel, row), positions
+        for (int e = tid; e < 4 * pl.nk; e += CS_NT) {
+            const int per = pl.ry * pl.ow, ii = e / per, rem = e - ii * per, yl = rem / pl.ow, ox = rem - yl * pl.ow;
+            const bool in = ii < pl.ni;
+            const int left = g.Wo - 8 * ox;
+            tab[e] = in ? make_int4(ii * pl.zi + yl * g.sh * pl.px + 8 * ox, 4 * (ii * g.cout * HoWo + yl * g.Wo + 8 * ox), (ii << 16) | yl, left < 8 ? left : 8)
+                        : make_int4(0, 0, 0xffff, 0);
         }
         __syncthreads();
-    }
+        if (ch_beg < ch_end && kgrp < pl.nk) fetch_a(c_i, c_y, kgrp);
+        for (int e = tid; e < bufsz / 4; e += CS_NT) reinterpret_cast<uint4*>(buf)[e] = make_uint4(0u, 0u, 0u, 0u);   // both buffers
+        __syncthreads();
+        if (ch_beg < ch_end) {
+            store_z(buf, plain);
+            advance(n_i, n_y);
+        }
+        if (ch_beg + 1 < ch_end) fetch_z(n_i, n_y);
+        __syncthreads();
+        const int khs = g.dh * pl.px;
+#pragma unroll 1
+        for (int ch = ch_beg; ch < ch_end; ++ch) {
+            const int cur = (ch - ch_beg) & 1;
+            const bool more = ch + 1 < ch_end;
+            int f_i = n_i, f_y = n_y;
+            if (more) {
+                store_z(buf + (cur ^ 1) * bufsz, plain);
+                if (ch + 2 < ch_end) {
+                    advance(f_i, f_y);
+                    fetch_z(f_i, f_y);
+                }
+            }
+#pragma unroll 1
+            for (int kb = kgrp; kb < pl.nk; kb += CS_KG) {
+                // this K block's G1 as bf16 terms; the next one's is requested
+                v4u a[CS_OB][3];
+#pragma unroll
+                for (int ob = 0; ob < CS_OB; ++ob)
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) {
+                        float x = __uint_as_float(araw[ob][d >> 1][2 * (d & 1)]), y = __uint_as_float(araw[ob][d >> 1][2 * (d & 1) + 1]);
+                        if (RAGGED) {
+                            x = 2 * d < a_left ? x : 0.f;
+                            y = 2 * d + 1 < a_left ? y : 0.f;
+                        }
+                        unsigned h, m = 0, l = 0;
+                        if constexpr (plain()) h = class_pair(x, y, &huge);
+                        else split_pair(x, y, h, m, l);
+                        a[ob][0][d] = h; a[ob][1][d] = m; a[ob][2][d] = l;
+                    }
+                const unsigned short* zb = buf + cur * bufsz + a_org + ll * pl.zj;
+                if (kb + CS_KG < pl.nk) fetch_a(c_i, c_y, kb + CS_KG);
+                else if (more) fetch_a(n_i, n_y, kgrp);
+                constexpr int WD = SW == 1 ? 5 : 9;          // dwords of a window; stride two: five even, four odd
+                unsigned w[2][3][WD];
+                auto window = [&](int kh, unsigned (&d)[3][WD]) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int t = 0; t < 3; ++t) {
+                        const unsigned short* zr = zb + t * pl.zt + kh * khs;
+                        const v4u q = *reinterpret_cast<const v4u*>(zr);
+                        d[t][0] = q[0]; d[t][1] = q[1]; d[t][2] = q[2]; d[t][3] = q[3];
+                        d[t][4] = *reinterpret_cast<const unsigned*>(zr + 8);
+                        if constexpr (SW == 2) {
+                            const v4u o = *reinterpret_cast<const v4u*>(zr + (pl.px >> 1));
+                            d[t][5] = o[0]; d[t][6] = o[1]; d[t][7] = o[2]; d[t][8] = o[3];
+                        }
+                    }
+                };
+                window(0, w[0]);
+#pragma unroll
+                for (int kh = 0; kh < 3; ++kh) {
+                    if (kh < 2) window(kh + 1, w[(kh + 1) & 1]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    const unsigned (&d)[3][WD] = w[kh & 1];
+                    v4u b[3][3];                             // [tap of the row][term]
+#pragma unroll
+                    for (int t = 0; t < 3; ++t) {
+                        b[0][t] = (v4u){d[t][0], d[t][1], d[t][2], d[t][3]};
+                        v4u next;                            // the window one entry on
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) next[q] = __builtin_amdgcn_alignbit(d[t][q + 1], d[t][q], 16);
+                        if constexpr (SW == 1) {
+                            b[1][t] = next;
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) b[2][t][q] = copy(d[t][q + 1]);
+                        } else {
+                            b[1][t] = (v4u){d[t][WD - 4], d[t][WD - 3], d[t][WD - 2], d[t][WD - 1]};
+                            b[2][t] = next;
+                        }
+                    }
+                    // small terms first; six accumulators take turns
+                    constexpr int TA[6] = {2, 0, 1, 1, 0, 0}, TB[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+                    for (int p = plain() ? 5 : 0; p < 6; ++p)
+#pragma unroll
+                        for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+                            for (int ob = 0; ob < CS_OB; ++ob) acc[ob][3 * kh + dx] = mfma_bf16(a[ob][TA[p]], b[dx][TB[p]], acc[ob][3 * kh + dx]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            c_i = n_i; c_y = n_y;
+            n_i = f_i; n_y = f_y;
+            __syncthreads();
+        }
+
+        // lane holds o = o0 + 16 (2 wo + ob) + 4 lg + v, j = j0 + ll.  The K groups add their tiles in LDS in a fixed order (groups 2
+        // and 3 write two tiles, 0 and 1 add to them, the store adds the two), and for one output channel the (j, tap) values of
+        // this workgroup are then one contiguous run of T.
+        if (tid < 2) met[tid] = 0;
+#pragma unroll
+        for (int round = 0; round < 2; ++round) {
+            if (kgrp >> 1 == 1 - round) {
+                float* Tg = Ts + (kgrp & 1) * TS_SZ;
+#pragma unroll
+                for (int ob = 0; ob < CS_OB; ++ob)
+#pragma unroll
+                    for (int t = 0; t < 9; ++t)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            float* p = &Tg[(16 * (CS_OB * wo + ob) + 4 * lg + v) * CS_TS_LD + ll * 9 + t];
+                            *p = round == 0 ? acc[ob][t][v] : *p + acc[ob][t][v];
+                        }
+            }
+            __syncthreads();
+        }
+    };
+    const long long total = (long long)g.cout * g.r2 * 9;
+    const int nj = (g.r2 - j0 < 16) ? g.r2 - j0 : 16;
     const int rowlen = nj * 9;
     const float inv_rowlen = 1.0f / (float)rowlen;
     float* __restrict__ out = jb.Tpart + (long long)bz * total;
-    for (int e = tid; e < CR_TO * rowlen; e += CS_NT) {  // e < 9216: the rounded float quotients are exact
-        const int ol = (int)(((float)e + 0.5f) * inv_rowlen), c = e - ol * rowlen;
-        const int o = o0 + ol;
-        if (o >= g.cout) continue;
-        float v = Ts[ol * CS_TS_LD + c] + Ts[TS_SZ + ol * CS_TS_LD + c];
-        if (!(fabsf(v) < INFINITY)) {
-            // An infinite (or huge) operand has no finite terms and a term product of Inf and 0 is NaN: the entry again as
-            // plain fp32 sums.
-            const int jl = (int)(((float)c + 0.5f) * (1.0f / 9.0f)), t = c - 9 * jl, kh = t / 3, kw = t - 3 * kh;
-            v = 0.f;
-            for (int ch = ch_beg; ch < ch_end; ++ch) {
-                const int ig = ch / pl.nyc, y0 = (ch - ig * pl.nyc) * pl.ry, y1 = min(y0 + pl.ry, g.Ho);
-                const int i1 = min((ig + 1) * pl.ni, g.r1);
-                for (int i = ig * pl.ni; i < i1; ++i)
-                    for (int y = y0; y < y1; ++y) {
-                        const int yy = y * g.sh - g.ph + kh * g.dh;
-                        if (yy < 0 || yy >= g.H) continue;
-                        const float* gp = G1 + ((long long)i * g.cout + o) * HoWo + (long long)y * g.Wo;
-                        const float* zp = Z + ((long long)i * g.r2 + j0 + jl) * HW + (long long)yy * g.W;
-                        for (int x = 0; x < g.Wo; ++x) {
-                            const int xx = x * SW - g.pw + kw;
-                            if (xx >= 0 && xx < g.W) v = fmaf(gp[x], zp[xx], v);
-                        }
-                    }
-            }
+    // f(where in T, output channel, (j, tap), value of the tiles) for the entries that this thread stores
+    auto entries = [&](auto f) __attribute__((always_inline)) {
+        for (int e = tid; e < CR_TO * rowlen; e += CS_NT) {              // e < 9216: the rounded float quotients are exact
+            const int ol = (int)(((float)e + 0.5f) * inv_rowlen), c = e - ol * rowlen, o = o0 + ol;
+            if (o < g.cout) f(out + ((long long)o * g.r2 + j0) * 9 + c, o, c, Ts[ol * CS_TS_LD + c] + Ts[TS_SZ + ol * CS_TS_LD + c]);
         }
-        out[((long long)o * g.r2 + j0) * 9 + c] = v;
-    }
+    };
+    walk(std::false_type());
+    bool special = false;
+    entries([&](float* t, int, int, float v) __attribute__((always_inline)) {
+        *t = v;
+        special = special || !(fabsf(v) < INFINITY);
+    });
+    if (special) met[0] = 1;
+    wait_copies_and_sync<32>();                          // (for the flags, not for the stores)
+    if (met[0] == 0) return;                             // (the same for all threads)
+    __syncthreads();
+    // Entries that are not finite: a term product of Inf and 0 is NaN, also where the product of the values is Inf, and an infinite value
+    // has no further terms.  A second walk over signs tells what plain sums would be, NaN, Inf or finite, in the time of the first (a gradient
+    // that is NaN throughout is what loss scaling makes now and then; the weight gradient of 256 x 48 x 9 over 8 x 64 x 64, finite 74 us, took
+    // 4.8 ms entry by entry, 110 us so).
+    walk(std::true_type());
+    if (huge) met[0] = 1;
+    if (z_special) met[1] = 1;
+    __syncthreads();
+    const bool any_huge = met[0] != 0, any_z = met[1] != 0;
+    entries([&](float* t, int o, int c, float what) __attribute__((always_inline)) {
+        if (fabsf(*t) < INFINITY) return;
+        const bool finite = fabsf(what) < INFINITY;
+        if (!finite) *t = what;
+        // left: sums of finite values that overflow; a value that rounds to an infinite bf16 one; and zeros in the place of positions that
+        // there are not, times an infinite entry of Z.  The latter two again as plain sums.
+        if (finite ? !any_huge : !any_z) return;
+        const int jl = (int)(((float)c + 0.5f) * (1.0f / 9.0f)), tap = c - 9 * jl, kh = tap / 3, kw = tap - 3 * kh;
+        float v = 0.f;
+        for (int ch = ch_beg; ch < ch_end; ++ch) {
+            const int ig = ch / pl.nyc, y0 = (ch - ig * pl.nyc) * pl.ry, y1 = min(y0 + pl.ry, g.Ho);
+            const int i1 = min((ig + 1) * pl.ni, g.r1);
+            for (int i = ig * pl.ni; i < i1; ++i)
+                for (int y = y0; y < y1; ++y) {
+                    const int yy = y * g.sh - g.ph + kh * g.dh;
+                    if (yy < 0 || yy >= g.H || isnan(v)) continue;
+                    const float* gp = G1 + ((long long)i * g.cout + o) * HoWo + (long long)y * g.Wo;
+                    const float* zp = Z + ((long long)i * g.r2 + j0 + jl) * HW + (long long)yy * g.W;
+                    for (int x = 0; x < g.Wo; ++x) {
+                        const int xx = x * SW - g.pw + kw;
+                        if (xx >= 0 && xx < g.W) v = fmaf(gp[x], zp[xx], v);
+                    }
+                }
+        }
+        *t = v;
+    });
 }
 
 template <bool RAGGED, int SW>

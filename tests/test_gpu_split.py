@@ -101,6 +101,75 @@ def test_split_correlation_of_an_entry_without_finite_terms(value):
         assert not bool(torch.isfinite(dW[66]).any())
 
 
+# A single batch entry and core channel, so that a gradient entry meets one value of Z: infinite, NaN or too large for a bf16 term,
+# inside the map and where windows hang over its edge (zeros times Inf); several that cancel; finite sums that overflow; maps that are no
+# multiple of eight positions, strides of one and two.
+@pytest.mark.parametrize("hw,stride", [((10, 12), 1), ((9, 16), 1), ((11, 14), 2)])
+@pytest.mark.parametrize("entries", [{(4, 5): "inf"}, {(4, 5): "-inf"}, {(0, 0): "inf", (3, 2): "nan"}, {(0, 0): "inf"}, {(1, 2): "inf", (3, 4): "-inf"},
+                                     {(2, 3): "3.4e38"}, {(2, 3): "3.4e38", (0, 0): "inf"}, {}, "all nan", "all inf", "overflow"])
+def test_split_correlation_of_special_values(hw, stride, entries):
+    from paper_2505_05086_amd import binding as B
+    rng = np.random.default_rng(7)
+    dims, ranks, cout = (1, 16, *hw), (1, 1, 5, 5), 70
+    ho, wo = ((x - 1) // stride + 1 for x in hw)
+    desc, conv = B.make_desc(dims, ranks, "f32"), B.make_conv(cout, 3, 3, (stride, stride), (1, 1), (1, 1), 1)
+    U = _factors(rng, dims, ranks)
+    U[0] = torch.ones(1, 1, device="cuda")
+    S = torch.from_numpy((1e-3 * rng.standard_normal(ranks)).astype(np.float32)).cuda()
+    gy = torch.from_numpy(rng.standard_normal((1, cout, ho, wo)).astype(np.float32)).cuda()
+    if isinstance(entries, dict):
+        for (y, x), v in entries.items():
+            gy[0, 66, y, x] = float(v)
+    elif entries == "overflow":
+        gy[0, 66] = 1e38
+        S = S.abs() * 1e6
+    else:
+        gy.fill_(float(entries.split()[1]))
+    dW = torch.empty(cout, 16, 3, 3, device="cuda")
+    sites = _sites(lambda: B.asi_weight_grad_conv2d(desc, S, U, gy, conv, dW, False, B.alloc_workspace(desc, conv, 0)))
+    assert any("k_corr_mfma_split" in s for s in sites), sites
+    want = _dense_dw(S, U, gy, (stride, stride), (1, 1), (1, 1))
+    if entries == "overflow":                            # (infinite or NaN, by the order of the sums, where fp32 has no number)
+        over = want.abs() > 3.5e38
+        assert bool(over.any()) and not bool(torch.isfinite(dW[over]).any())
+    else:
+        assert torch.equal(torch.isnan(dW), torch.isnan(want))
+        assert torch.equal(torch.isposinf(dW), torch.isposinf(want)) and torch.equal(torch.isneginf(dW), torch.isneginf(want))
+    rest, row = torch.isfinite(want), torch.arange(cout, device="cuda") == 66
+    for rows in (~row, row)[:1 if entries == "overflow" else 2]:
+        part = rest & rows[:, None, None, None]
+        if bool(part.any()):
+            assert float((dW - want)[part].abs().max() / want[part].abs().max()) <= 1e-5
+
+
+def test_split_correlation_of_a_nan_gradient_is_not_summed_entry_by_entry():
+    """Twice the finite time, with room for the noise of a measurement (entry by entry it took 65 times as long)."""
+    from paper_2505_05086_amd import binding as B
+    rng = np.random.default_rng(8)
+    dims, ranks, cout = (8, 256, 64, 64), (8, 48, 32, 32), 256
+    desc, conv = B.make_desc(dims, ranks, "f32"), B.make_conv(cout, 3, 3, (1, 1), (1, 1), (1, 1), 1)
+    U = _factors(rng, dims, ranks)
+    S = torch.from_numpy(rng.standard_normal(ranks).astype(np.float32)).cuda()
+    gy = torch.randn(dims[0], cout, 64, 64, device="cuda")
+    dW, ws = torch.empty(cout, dims[1], 3, 3, device="cuda"), B.alloc_workspace(desc, conv, 0)
+
+    def time(g):
+        best = float("inf")
+        for _ in range(4):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(5):
+                B.asi_weight_grad_conv2d(desc, S, U, g, conv, dW, False, ws)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+
+    finite = time(gy)
+    for value in ("nan", "inf"):
+        assert time(torch.full_like(gy, float(value))) <= 4 * finite
+
+
 def _exact_factor(A, u, mode):
     """Q of P = A_m (A_m^T u) in float64, positive diagonal of R."""
     m = A.double().movedim(mode, 0).reshape(A.shape[mode], -1)
