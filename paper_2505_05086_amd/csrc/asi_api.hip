@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "../../include/asi.h"
+#include "asi_corr.h"
 #include "asi_kernels.h"
 
 namespace {
@@ -348,6 +349,7 @@ struct ConvPlan {
     float *G1 = nullptr, *Z1 = nullptr, *Z = nullptr, *Tpart = nullptr, *T = nullptr;
     float* S1 = nullptr;             // r1 = B: the core expanded along the batch mode (see build_conv)
     int nsplit = 1;
+    CorrPlan corr = {};
     size_t bytes = 0;
 };
 
@@ -363,7 +365,7 @@ ConvPlan plan_conv(const Shape& s, const ConvGeom& cg, void* ws) {
     p.Z = c.take<float>((size_t)g.r1 * g.r2 * g.H * g.W);
     CorrGroup alone;
     alone.n = 1; alone.g[0] = &g;
-    p.nsplit = corr_splits(alone, 0);
+    p.nsplit = corr_splits(alone, 0, &p.corr);
     const size_t tsz = (size_t)g.cout * g.r2 * g.kh * g.kw;
     p.T = c.take<float>(tsz);
     p.Tpart = p.nsplit > 1 ? c.take<float>(tsz * p.nsplit) : p.T;
@@ -866,13 +868,13 @@ asi_status build_conv_grad(const ConvBuild& cb, const float* const* U, float* dW
     const CorrGeom& g = cg.g;
     const int taps = g.kh * g.kw;
     ConvPlan p = cb.p;
-    p.nsplit = corr_splits(grp, self);
+    if (grp.n > 1) p.nsplit = corr_splits(grp, self, &p.corr);     // (alone: as planned)
     if (p.nsplit > cb.p.nsplit) return ASI_ERR_UNSUPPORTED;        // (cannot be: the workspace holds those of the layer alone)
     if (p.nsplit == 1) p.Tpart = p.T;
     // 4. T = correlation of Zpad with G1 over (r1, Ho, Wo)        (cout, r2, kh, kw)
     const double tsz = (double)g.cout * g.r2 * taps;
     ASI_ADD(pg, "", 4.0 * ((double)g.r1 * g.cout * g.Ho * g.Wo + (double)g.r1 * g.r2 * g.H * g.W + tsz * p.nsplit),
-            2.0 * g.r1 * g.Ho * g.Wo * tsz, make_corr(cb.G1, p.Z, p.Tpart, grp, self, p.nsplit, it__));
+            2.0 * g.r1 * g.Ho * g.Wo * tsz, make_corr(cb.G1, p.Z, p.Tpart, g, p.corr, p.nsplit, it__));
     // 5. dW = T x_(r2) U2, per group                              (cout, C/groups, kh, kw)
     // An ungrouped convolution with 1 or 9 taps and r2 <= 64 sums the partial T's and expands the result in one
     // launch (T itself is then never written); anything else sums first and multiplies in a second launch.

@@ -413,10 +413,10 @@ bool corr_shares(const CorrGeom& a, const CorrGeom& b) {
     return corr_plan(a, &pa, &cut) && corr_plan(b, &pb, &cut) && corr_plan_key(a, pa) == corr_plan_key(b, pb);
 }
 
-int corr_splits(const CorrGroup& grp, int self) {
+int corr_splits(const CorrGroup& grp, int self, CorrPlan* plan) {
     const CorrGeom& g = *grp.g[self];
-    CorrPlan pl;
-    if (corr_plan_shared(grp, self, &pl)) return pl.nsplit;
+    if (corr_plan_shared(grp, self, plan)) return plan->nsplit;
+    plan->nsplit = 0;
     const long long total = (long long)g.cout * g.r2 * g.kh * g.kw;
     const long long blocks = (total + 255) / 256;
     long long want = (2048 + blocks - 1) / blocks;
@@ -427,16 +427,16 @@ int corr_splits(const CorrGroup& grp, int self) {
 }
 
 // key: see corr_plan_key; the fallback kernel has kind IT_CORR
-bool make_corr(const float* G1, const float* Z, float* Tpart, const CorrGroup& grp, int self, int nsplit, Item* out) {
-    const CorrGeom& g = *grp.g[self];
+bool make_corr(const float* G1, const float* Z, float* Tpart, const CorrGeom& g, const CorrPlan& plan, int nsplit, Item* out) {
     const long long total = (long long)g.cout * g.r2 * g.kh * g.kw;
     if (total <= 0 || nsplit <= 0 || !G1 || !Z || !Tpart) return false;
     CorrJob jb;
     std::memset(&jb, 0, sizeof(jb));
     jb.G1 = G1; jb.Z = Z; jb.Tpart = Tpart; jb.g = g;
     *out = Item();
-    if (corr_plan_shared(grp, self, &jb.pl)) {
-        if (nsplit != jb.pl.nsplit) return false;
+    if (plan.nsplit > 0) {
+        if (nsplit != plan.nsplit) return false;
+        jb.pl = plan;
         jb.gx = (g.cout + CR_TO - 1) / CR_TO; jb.gy = (g.r2 + 15) / 16; jb.gz = jb.pl.nsplit;
         const int taps = g.kh * g.kw;
         out->kind = IT_CORR_MFMA;

@@ -343,8 +343,10 @@ struct CorrGroup {       // the correlations of one launch; how far each is spli
     const CorrGeom* g[kMaxBatch] = {};
 };
 bool corr_shares(const CorrGeom& a, const CorrGeom& b);
-int corr_splits(const CorrGroup& grp, int self);
-bool make_corr(const float* G1, const float* Z, float* Tpart, const CorrGroup& grp, int self, int nsplit, Item* out);
+struct CorrPlan;         // asi_corr.h
+// the splits of a layer of the group and its plan (without splits: the plain kernel's)
+int corr_splits(const CorrGroup& grp, int self, CorrPlan* plan);
+bool make_corr(const float* G1, const float* Z, float* Tpart, const CorrGeom& g, const CorrPlan& plan, int nsplit, Item* out);
 
 // ---- step 5 of Eq. 14 with groups: dW[o,c,t] (+)= sum_j T[o,j,t] * U2[(o/og)*cg + c, j] -----------------------
 struct ExpandJob {
