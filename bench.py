@@ -3,9 +3,9 @@
 
 One "step" = the whole path (asi_compress -> asi_core_project -> asi_weight_grad_*)
 for every layer of a workload on one batch of synthetic activations that are
-already resident in HBM.  Prints ONE JSON line.
+already resident in HBM.  Prints ONE JSON line of a few kilobytes; --details writes every launch's figures to a file.
 
-    python bench.py [--gpus 1] [--steps K] [--warmup W] [--config N] [--no-cpu-baseline]
+    python bench.py [--gpus 1] [--steps K] [--warmup W] [--config N] [--no-cpu-baseline] [--details FILE]
 
 Without --config the headline (`value`, `ms_per_step`, `roofline`, `cpu_baseline`) is the largest
 fp32 workload, config 4, and `per_config` carries the same figures for every workload (1-5: the headline set, 6: the language-model shape).
@@ -147,6 +147,7 @@ def parse_args():
     ap.add_argument("--cpu-seconds", type=float, default=15.0, help="oracle time budget for the headline workload")
     ap.add_argument("--cpu-seconds-other", type=float, default=3.0,
                     help="oracle time budget for each further workload of per_config (at least one layer-step is timed)")
+    ap.add_argument("--details", default="", help="also write the whole record, with the figures of every launch, to this JSON file")
     return ap.parse_args()
 
 
@@ -580,6 +581,34 @@ def measure(cfg, args, cpu_seconds):
     return out
 
 
+LINE_MAX = 6000                  # characters: the line is read from the end of an output that is kept to some 8000
+
+
+def headline(out: dict) -> dict:
+    """The record without what belongs to single launches, numbers to five digits: one line that a log keeps whole."""
+    def short(x):
+        if isinstance(x, float):
+            return float(f"{x:.5g}")
+        if isinstance(x, dict):
+            return {k: short(v) for k, v in x.items()}
+        return [short(v) for v in x] if isinstance(x, (list, tuple)) else x
+
+    roof = ("kernel", "bound", "achieved", "peak", "unit", "frac", "avg_launch_us", "launches_per_step", "kernel_time_share", "traffic")
+    whole = ("algorithmic_bytes_per_step", "hbm_us_at_peak", "hbm_frac", "flop_frac", "counter_traffic_over_algorithmic")
+    line = {k: v for k, v in out.items() if k not in ("roofline", "kernel_breakdown", "per_config")}
+    line["roofline"] = dict({k: out["roofline"][k] for k in roof}, whole_step={k: out["roofline"]["whole_step"][k] for k in whole})
+    if "per_config" in out:
+        line["per_config"] = [dict({k: c[k] for k in ("config", "dtype", "value", "ms_per_step", "host_enqueue_ms_per_step")},
+                                   roofline={k: c["roofline"][k] for k in ("kernel", "bound", "achieved", "unit", "frac")},
+                                   hbm_frac=c["roofline"]["whole_step"]["hbm_frac"]) for c in out["per_config"]]
+    line = short(line)
+    for key in ("phases_eager_single_stream", "cpu_baseline", "per_config"):     # (what a longer workload list would push out first)
+        if len(json.dumps(line, separators=(",", ":"))) <= LINE_MAX:
+            break
+        line.pop(key, None)
+    return line
+
+
 def main():
     args = parse_args()
     if args.gpus != 1:
@@ -621,7 +650,10 @@ def main():
                         "passes": m["kernel_breakdown"],
                         "cpu_baseline": m.get("cpu_baseline")})
         out["per_config"] = per
-    print(json.dumps(out))
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump(out, f, indent=1)
+    print(json.dumps(headline(out), separators=(",", ":")))
 
 
 if __name__ == "__main__":

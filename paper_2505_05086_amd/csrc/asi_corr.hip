@@ -98,8 +98,11 @@ static bool corr_plan(const CorrGeom& g, CorrPlan* p, bool* cut) {
 
 // The plan of layer `self` of a launch.  The layers share the CUs, and a workgroup costs about four chunks beside its own (first
 // loads, result through LDS): every layer takes as many chunks per workgroup as give the fewest rounds x (chunks + 4) over
-// the whole launch, never more splits than alone (three layers of 512 x 48 x 9 over 16 x 7 x 7: 576 workgroups of two chunks
-// 46 us, 216 of six 32; one of them beside 256 x 32 x 9 over 16 x 14 x 14: 448 workgroups of two chunks 34, 224 of four 26).
+// the whole launch, never more splits than alone (three layers of 512 x 48 x 9 over 16 x 7 x 7 in the fp32 form, which they had then: 576
+// workgroups of two chunks 46 us, 216 of six 32).  The split form's chunks hold up to 256 groups of positions and differ by layer, but a layer
+// has few of them alone (eight of the 7 x 7 one) and the rule leaves little to choose: with one or twelve chunks in the place of the
+// four, nine mixes of 7 x 7 to 64 x 64 layers took the same times (three 7 x 7 21.8 to 21.9 us, 7 x 7 beside 14 x 14 23.2 to 23.3, with
+// 28 x 28 40.5 to 41.0, four 14 x 14 24.0 to 24.2).
 static bool corr_plan_shared(const CorrGroup& grp, int self, CorrPlan* p) {
     bool cut;
     if (!corr_plan(*grp.g[self], p, &cut)) return false;

@@ -235,6 +235,35 @@ def test_bench_refuses_more_than_one_gpu():
     assert "one GPU" in res.stderr and res.stdout.strip() == ""
 
 
+def test_bench_line_is_short_enough_to_be_kept_whole():
+    """The line leaves out the figures of single launches (60 KB of them came to nothing where a log keeps the last 8000 characters)."""
+    import importlib.util
+    import json
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    spec = importlib.util.spec_from_file_location("bench", os.path.join(root, "bench.py"))
+    bench = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(bench)
+    x = 1234.56789012345
+    whole = {k: x for k in ("algorithmic_bytes_per_step", "hbm_us_at_peak", "hbm_frac", "flop_frac", "counter_traffic_over_algorithmic", "other")}
+    roof = dict({k: x for k in ("achieved", "peak", "frac", "avg_launch_us", "launches_per_step", "kernel_time_share", "traffic", "more")},
+                kernel="k_subspace_planes<float, 4, true>", bound="mfma", unit="TFLOP/s", whole_step=whole)
+    passes = {f"compress|k_some_kernel<{i}, true>:P": {str(j): x for j in range(11)} for i in range(40)}
+    phases = {p: {"us_per_step": x, "launches_per_step": x} for p in ("compress", "core", "weight_grad")}
+    cpu = {"seconds_per_step": x, "variants": {f"variant {i}": {str(j): x for j in range(6)} for i in range(3)}}
+    config = {"workload": "a workload of two layers " * 6, **{f"key {i}": x for i in range(9)}, "queue_probe": {str(i): x for i in range(12)}}
+    one = dict(value=x, ms_per_step=x, host_enqueue_ms_per_step=x, dtype="bf16", roofline=roof, phases_eager_single_stream=phases)
+    out = dict({k: "some text" for k in ("metric", "unit", "scaling", "data")}, **one, n_gpus=1, steps=20, warmup=5, higher_is_better=True,
+               vs_baseline=None, config=config, cpu_baseline=cpu, kernel_breakdown=passes, gpu_ms_per_step_events=x,
+               per_config=[dict(one, config=i, workload="w" * 150, passes=passes, cpu_baseline=cpu) for i in range(1, 7)])
+    assert len(json.dumps(out)) > 60000
+    line = bench.headline(out)
+    text = json.dumps(line, separators=(",", ":"))
+    assert len(text) <= bench.LINE_MAX < 8000 and "\n" not in text
+    assert line["value"] == 1234.6 and len(line["per_config"]) == 6 and line["cpu_baseline"] and "kernel_breakdown" not in line
+    out["per_config"] *= 8                               # a longer list goes rather than the line
+    assert len(json.dumps(bench.headline(out), separators=(",", ":"))) <= bench.LINE_MAX
+
+
 LDS_PROBE = r"""
 #include "asi_lds.h"
 #include <cstdio>
