@@ -222,7 +222,8 @@ asi_status asi_mode_spectrum(const asi_tensor_desc* desc, const void* A, int32_t
 
 /* The same for n_modes (1 to 4) modes of one tensor in one call, whose launches serve all of them: entry k of eigenvalues,
  * eigenvectors (null, or null entries: not wanted) and sweeps (nullable) belongs to mode modes[k].  Each result is the same, bit
- * for bit, as asi_mode_spectrum's for that mode. */
+ * for bit, as asi_mode_spectrum's for that mode.  The workspace is the sum of what the modes take alone (a mode of 512 entries up to 73
+ * MB), since they are worked on side by side; where that is too much, fewer modes a call. */
 size_t asi_mode_spectra_workspace_bytes(const asi_tensor_desc* desc, const int32_t* modes, int32_t n_modes);
 asi_status asi_mode_spectra(const asi_tensor_desc* desc, const void* A, const int32_t* modes, int32_t n_modes,
                             double* const* eigenvalues, float* const* eigenvectors, void* ws, size_t ws_bytes, int32_t* sweeps,
