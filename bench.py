@@ -63,6 +63,16 @@ def source_digest() -> str:
     return h.hexdigest()[:16]
 
 
+def counters_of(kernels: dict, symbol: str):
+    """The record of a launch site's kernel.  A label may leave out the last template arguments: then those of all such kernels, by launches."""
+    name = symbol.replace("asi::", "")
+    if name in kernels:
+        return kernels[name]
+    same = [r for k, r in kernels.items() if name.endswith(">") and k.startswith(name[:-1] + ",")]
+    n = sum(r["launches"] for r in same)
+    return {k: sum(r[k] * r["launches"] for r in same) / n for k in ("fetch_bytes_per_launch", "write_bytes_per_launch")} if n else None
+
+
 def stored_traffic(cfg_index: int):
     """The committed rocprofv3 --pmc summary of this workload (FETCH_SIZE / WRITE_SIZE per launch), or None.
     Returns (kernels, meta): meta says which build the counters were read on and whether that is this one."""
@@ -506,7 +516,7 @@ def measure(cfg, args, cpu_seconds):
     kernels, meta = stored_traffic(cfg.index)
     roof["traffic"] = None
     if kernels is not None and meta["same_build"]:
-        rec = kernels.get(dom) or kernels.get(dom.replace("asi::", ""))
+        rec = counters_of(kernels, dom)
         if rec is not None:
             roof["traffic"] = float(rec["fetch_bytes_per_launch"]) + float(rec["write_bytes_per_launch"])
     roof["traffic_source"] = meta
@@ -532,7 +542,7 @@ def measure(cfg, args, cpu_seconds):
         tot = 0.0
         ok = True
         for sym, v in per_kernel.items():
-            rec = kernels.get(sym) or kernels.get(sym.replace("asi::", ""))
+            rec = counters_of(kernels, sym)
             if rec is None:
                 ok = False
                 break
