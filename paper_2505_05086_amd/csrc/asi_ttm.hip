@@ -11,15 +11,15 @@
 // M2(i%n2, q%r2), which contracts two adjacent modes (H and W) in one pass.
 //
 // k_ttm_ksplit serves long fibres with few unfolding columns (the channel mode of a late conv
-// layer): a workgroup owns only 16 columns, its four waves split the mode index between them,
-// every operand goes from global memory straight into the MFMA registers (all loads of a round
-// are in flight together) and the four partial tiles are added through LDS.
+// layer): a workgroup owns 16 or 32 columns, its eight waves split the mode index between them, every operand goes from
+// global memory straight into the MFMA registers, and the partial tiles are added through LDS.
 //
 // k_ttm_thin serves modes of at most 16 entries over very many columns on the vector ALU (further down).
 //
 // All kernels take the argument blocks of several layers side by side (Batch<TtmJob>).
 #include "asi_device.h"
 #include "asi_kernels.h"
+#include "asi_lds.h"
 
 #include <cstdio>
 #include <cstring>
@@ -295,78 +295,148 @@ __global__ __launch_bounds__(256) void k_ttm_duo(Batch<TtmDuoJob> bt) {
 }
 
 // ---- long fibres, few columns ------------------------------------------------------------------
-// A workgroup owns 16*CB columns.  Round = 16*KS mode indices: wave w, step s multiplies rows
-// k0 + 16s + 4w .. +3.  A operands (16 columns x 4 i, one per column block) and B operands
-// (4 i x 16 q) are loaded by the lanes that use them; CB column blocks share each B operand.
-template <typename T, int NBR, int KS, int CB>
-__global__ __launch_bounds__(256) void k_ttm_ksplit(Batch<TtmJob> bt) {
-    __shared__ float red[4][NBR * 16][16 * CB + 1];
+// A workgroup owns 16 CB columns (CB: one or two); its eight waves deal the K steps (four mode indices each) of the whole mode among
+// themselves, and every operand goes from memory straight into the registers of the lanes that multiply it:
+//   A operand (16 columns x 4 i)  = X at row 4 s + lane / 16 of column 16 cb + lane % 16
+//   B operand (4 i x 16 outputs)  = M at row 4 s + lane / 16; lane ll of a row holds the NBR CONSECUTIVE outputs NBR ll + nb, one
+//                                   load of 4 NBR bytes for NBR blocks of interleaved outputs
+// What bounds it is the number of loads between a workgroup's start and its end, not the products: R steps are requested while
+// the R before them are multiplied.  With four waves, 16 columns, a dword per operand and no step requested ahead a 960-long
+// mode took 180 + 60 loads a wave in four dependent rounds, here 30 x (1 + CB): 960 x 40 over 6272 columns (24 MB) 17.9 -> 13.6 us,
+// 512 x 48 over 3 x 3136 (19 MB) 19.7 -> 13.5, 256 x 32 over 12544 (13 MB) 10.0 -> 6.7.  At 960 the products are 4.8 us of it (196
+// workgroups, 180 of them a SIMD and wave).  M is read through a buffer
+// descriptor: what lies beyond its last element arrives as zero (a row beyond the mode, or the next row's entries in outputs that
+// are dropped anyway), so neither needs a test in the loop; a last step that is not whole is masked by itself.
+template <int N> struct LoadB;
+template <> struct LoadB<1> { typedef unsigned type; };
+template <> struct LoadB<2> { typedef unsigned type __attribute__((ext_vector_type(2))); };
+template <> struct LoadB<3> { typedef unsigned type __attribute__((ext_vector_type(3))); };
+template <> struct LoadB<4> { typedef unsigned type __attribute__((ext_vector_type(4))); };
+
+constexpr int KS_NT = 512, KS_NW = KS_NT / 64;
+
+template <typename T, int NBR, int CB, bool CONTIG>
+__global__ __launch_bounds__(KS_NT, 4) void k_ttm_ksplit(Batch<TtmJob> bt) {
+    constexpr int R = NBR + CB <= 4 ? 8 : 36 / (NBR + CB);      // steps in flight beside those being multiplied (128 registers)
+    constexpr int LD = 16 * CB + 4;                  // pitch of a partial tile's row: 16-byte pieces stay aligned
+    extern __shared__ __align__(16) float ks_red[];  // [KS_NW][16 NBR][LD]
     int lb;
     const TtmJob& jb = bt.job[locate_xcd(bt, &lb)];
     const T* __restrict__ X = static_cast<const T*>(jb.X);
-    const float* __restrict__ Mp = jb.Mp;
     float* __restrict__ Y = jb.Y;
-    const long long outer = jb.outer, inner = jb.inner, ms_i = jb.ms_i, ms_q = jb.ms_q;
+    const long long outer = jb.outer, inner = jb.inner;
     const int n = jb.n, r = jb.r, beta = jb.beta;
+    const unsigned ms_i = (unsigned)jb.ms_i, ms_q = (unsigned)jb.ms_q;        // the matrix is below 2 GB (host check)
     const int bx = lb / jb.gy, by = lb - bx * jb.gy;      // output tiles of the same columns are neighbours (one L2)
     const long long ncols = outer * inner;
     const long long c0 = (long long)bx * (16 * CB);
     const int q0 = by * (NBR * 16);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lg = lane >> 4, ll = lane & 15;
+    const int tid = threadIdx.x, lane = tid & 63, lg = lane >> 4, ll = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (jb.zero && lb == 0 && tid < jb.nzero) jb.zero[tid] = 0;
-    long long xbase[CB];
-    bool cok[CB];
+    // this lane's columns, as 32-bit offsets from the workgroup's first slab (host check)
+    const long long o0 = c0 / inner;
+    const T* __restrict__ Xw = X + o0 * (long long)n * inner;
+    unsigned xoff[CB];
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) {
-        const long long c = c0 + 16 * cb + ll;
-        cok[cb] = c < ncols;
-        const long long cc = cok[cb] ? c : 0;
+        const long long c = c0 + 16 * cb + ll, cc = c < ncols ? c : c0;       // past the end: the first column, dropped at the store
         const long long o = cc / inner, j = cc - o * inner;
-        xbase[cb] = o * (long long)n * inner + j;
+        xoff[cb] = (unsigned)((o - o0) * (long long)n * inner + j);
     }
+    const unsigned row = (unsigned)inner;
+    const unsigned qoff = (unsigned)(q0 + NBR * ll) * ms_q;
+    const int steps = (n + 3) >> 2;
+    const int mine = wave < steps ? (steps - 1 - wave) / KS_NW + 1 : 0;       // steps wave, wave + 8, ..
+    const bool ragged = (n & 3) != 0;
+#if defined(__HIP_DEVICE_COMPILE__)
+    const auto mrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(jb.Mp), 0, (int)(4u * ((unsigned)(n - 1) * ms_i + (unsigned)(r - 1) * ms_q + 1u)), 0x00027000);
+#endif
+    typedef typename LoadB<NBR>::type MV;
+    struct Stage { T x[R][CB]; MV m[R]; };
+    auto fetch = [&](int t0, Stage& g) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            const int t = t0 + u < mine ? t0 + u : mine - 1;                  // uniform; a repeated step is not multiplied
+            const int i0 = 4 * (wave + KS_NW * t), i = i0 + lg;
+            const unsigned xr = (unsigned)(i < n ? i : n - 1) * row;
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) g.x[u][cb] = Xw[xoff[cb] + xr];
+#if defined(__HIP_DEVICE_COMPILE__)
+            const int mo = (int)(4u * ((unsigned)i * ms_i + qoff));
+            if (CONTIG) {
+                if constexpr (NBR == 1) g.m[u] = __builtin_amdgcn_raw_buffer_load_b32(mrsrc, mo, 0, 0);
+                if constexpr (NBR == 2) g.m[u] = __builtin_amdgcn_raw_buffer_load_b64(mrsrc, mo, 0, 0);
+                if constexpr (NBR == 3) g.m[u] = __builtin_amdgcn_raw_buffer_load_b96(mrsrc, mo, 0, 0);
+                if constexpr (NBR == 4) g.m[u] = __builtin_amdgcn_raw_buffer_load_b128(mrsrc, mo, 0, 0);
+            } else {
+                unsigned e[NBR];
+#pragma unroll
+                for (int nb = 0; nb < NBR; ++nb) e[nb] = __builtin_amdgcn_raw_buffer_load_b32(mrsrc, mo + (int)(4u * nb * ms_q), 0, 0);
+                __builtin_memcpy(&g.m[u], e, sizeof(e));
+            }
+#endif
+        }
+    };
     v4f acc[CB][NBR];
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
         for (int nb = 0; nb < NBR; ++nb) acc[cb][nb] = (v4f){0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < n; k0 += 16 * KS) {
-        float xr[CB][KS], mr[NBR][KS];
+    auto multiply = [&](int t0, Stage& g) __attribute__((always_inline)) {
 #pragma unroll
-        for (int s = 0; s < KS; ++s) {
-            const int i = k0 + 16 * s + 4 * wave + lg;
+        for (int u = 0; u < R; ++u)
+            if (t0 + u < mine) {                     // uniform
+                const int s = wave + KS_NW * (t0 + u);
+                float x[CB], m[NBR];
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb) xr[cb][s] = ldg_f32(X, xbase[cb] + (long long)i * inner, cok[cb] && i < n);
+                for (int cb = 0; cb < CB; ++cb) x[cb] = to_f32(g.x[u][cb]);
+                __builtin_memcpy(m, &g.m[u], sizeof(m));
+                if (ragged && s == steps - 1) {      // uniform
+                    const bool in = 4 * s + lg < n;
 #pragma unroll
-            for (int nb = 0; nb < NBR; ++nb) {
-                const int q = q0 + 16 * nb + ll;
-                mr[nb][s] = ldg_f32(Mp, (long long)i * ms_i + (long long)q * ms_q, i < n && q < r);
+                    for (int cb = 0; cb < CB; ++cb) x[cb] = in ? x[cb] : 0.f;
+#pragma unroll
+                    for (int nb = 0; nb < NBR; ++nb) m[nb] = in ? m[nb] : 0.f;
+                }
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                    for (int nb = 0; nb < NBR; ++nb)
+                        acc[cb][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[cb], m[nb], acc[cb][nb], 0, 0, 0);
+            }
+    };
+    if (mine > 0) {
+        Stage a, b;
+        fetch(0, a);
+        for (int t = 0; t < mine; t += 2 * R) {
+            if (t + R < mine) fetch(t + R, b);
+            multiply(t, a);
+            if (t + R < mine) {
+                if (t + 2 * R < mine) fetch(t + 2 * R, a);
+                multiply(t + R, b);
             }
         }
-#pragma unroll
-        for (int s = 0; s < KS; ++s)
-#pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-                for (int nb = 0; nb < NBR; ++nb)
-                    acc[cb][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(xr[cb][s], mr[nb][s], acc[cb][nb], 0, 0, 0);
     }
-    // lane holds column 16cb + 4*lg + v, output 16nb + ll
+    // lane holds columns 16 cb + 4 lg .. + 3, output NBR ll + nb
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
         for (int nb = 0; nb < NBR; ++nb)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) red[wave][16 * nb + ll][16 * cb + 4 * lg + v] = acc[cb][nb][v];
+            *reinterpret_cast<v4f*>(ks_red + (wave * 16 * NBR + NBR * ll + nb) * LD + 16 * cb + 4 * lg) = acc[cb][nb];
     __syncthreads();
     constexpr int W = 16 * CB;
     const int cl = tid % W;
     const long long cc = c0 + cl;
     if (cc < ncols) {
         const long long o = cc / inner, j = cc - o * inner;
-        for (int ql = tid / W; ql < NBR * 16; ql += 256 / W) {
+        for (int ql = tid / W; ql < NBR * 16; ql += KS_NT / W) {
             const int q = q0 + ql;
             if (q < r) {
-                const float v = (red[0][ql][cl] + red[1][ql][cl]) + (red[2][ql][cl] + red[3][ql][cl]);
+                float p[KS_NW];
+#pragma unroll
+                for (int w = 0; w < KS_NW; ++w) p[w] = ks_red[(w * 16 * NBR + ql) * LD + cl];
+                const float v = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
                 const long long idx = (o * r + q) * inner + j;
                 Y[idx] = beta ? Y[idx] + v : v;
             }
@@ -561,20 +631,31 @@ static bool ttm_expand_supported(DType xt, long long inner, int n, int r, const 
 }
 
 // ---- host side -----------------------------------------------------------------------------------
-// key bits: [0] bf16 input, [1] LASTMODE, [2] KRON, [3] split kernel, [4..6] NBR-1, [8..12] KS,
-// [13] split kernel with several column blocks per workgroup (4 up to NBR = 3, else 2),
-// [14] K chunks of 64 (tiled kernel along the last mode), [15] the vector-ALU kernel for very short modes.
-// Bits 4..12 only bound sizes.
-static unsigned ttm_key(bool bf16, bool last, bool kron, bool ksplit, int nbr, int ks, bool wide, bool kc64) {
-    return (bf16 ? 1u : 0u) | (last ? 2u : 0u) | (kron ? 4u : 0u) | (ksplit ? 8u : 0u) | ((unsigned)(nbr - 1) << 4) |
-           ((unsigned)ks << 8) | (wide ? 0x2000u : 0u) | (kc64 ? 0x4000u : 0u);
+// key bits: [0] bf16 input, [1] LASTMODE, [2] KRON, [3] split kernel, [4..6] NBR-1,
+// [14] K chunks of 64 (tiled kernel along the last mode), [15] the vector-ALU kernel for very short modes,
+// [16] split kernel: two column blocks per workgroup, [18] split kernel: rows of the matrix contiguous.
+// Bits 4..6 only bound sizes.
+static unsigned ttm_key(bool bf16, bool last, bool kron, bool ksplit, int nbr, bool kc64) {
+    return (bf16 ? 1u : 0u) | (last ? 2u : 0u) | (kron ? 4u : 0u) | (ksplit ? 8u : 0u) | ((unsigned)(nbr - 1) << 4) | (kc64 ? 0x4000u : 0u);
 }
-static int ksplit_cb(int nbr, bool wide) { return !wide ? 1 : (nbr <= 3 ? 4 : 2); }
 
 // The tiled kernel walks the mode index in n/32 dependent steps with ncols/64 workgroups; when that
 // leaves most of the chip idle the split kernel is the faster one.
 static bool prefer_ksplit(long long ncols, int n, long long inner) {
     return inner > 1 && n > 64 && (ncols + TM_TC - 1) / TM_TC < 512;
+}
+
+// its offsets have 32 bits, relative to the first slab of a workgroup's columns and to the matrix
+static bool ksplit_reaches(long long outer, int n, long long inner, long long ms_i, long long ms_q, int r) {
+    const long long slabs = 64 / inner + 2 < outer ? 64 / inner + 2 : outer;
+    return ms_i > 0 && ms_q > 0 && slabs * n * inner < (1LL << 30) && (n + 3) * ms_i + (r + 63) * ms_q < (1LL << 29);
+}
+// Column blocks per workgroup: the fewest column blocks that a CU multiplies one after the other, two a workgroup on a tie (they share the
+// loads of the matrix).  One | two: 512 x 48 over 3 x 3136 columns (588 | 294 workgroups) 13.5 | 15.0 us, 960 x 40 over 6272 (392 |
+// 196) 14.8 | 13.6, 256 x 32 over 12544 (784 | 392) 8.9 | 6.7; four: 9.2 there.
+static int ksplit_cb(long long ncols) {
+    const long long one = ((ncols + 15) / 16 + 255) / 256, two = ((ncols + 31) / 32 + 255) / 256 * 2;
+    return one < two ? 1 : 2;
 }
 
 static bool fill_ttm(DType xt, const void* X, long long outer, int n, long long inner, const float* Mp, long long ms_i,
@@ -601,20 +682,17 @@ static bool fill_ttm(DType xt, const void* X, long long outer, int n, long long 
         const long long gx = (ncols + TH_COLS - 1) / TH_COLS;
         if (gx > 0x3fffffffLL) return false;
         jb.gx = (int)gx; jb.gy = 1;
-        out->kind = IT_TTM; out->key = ttm_key(xt == BF16, false, false, false, 1, 0, false, false) | 0x8000u;
+        out->kind = IT_TTM; out->key = ttm_key(xt == BF16, false, false, false, 1, false) | 0x8000u;
         std::snprintf(out->label, sizeof(out->label), "k_ttm_thin<%s, %d>", tn, n <= 8 ? 8 : 16);
-    } else if (!kron && prefer_ksplit(ncols, n, inner)) {
+    } else if (!kron && prefer_ksplit(ncols, n, inner) && ksplit_reaches(outer, n, inner, ms_i, ms_q, r)) {
         const int nbr = r >= 64 ? 4 : (r + 15) / 16;
-        // several column blocks per workgroup share the matrix operand; worth it once that still
-        // leaves a workgroup for every other CU
-        const bool wide = ncols / (16 * ksplit_cb(nbr, true)) >= 128;
-        const int ks = n <= 64 ? 4 : (wide ? 8 : (n <= 128 ? 8 : 16));
-        const int wcols = 16 * ksplit_cb(nbr, wide);
-        const long long gx = (ncols + wcols - 1) / wcols;
+        const int cb = ksplit_cb(ncols);
+        const long long gx = (ncols + 16 * cb - 1) / (16 * cb);
         jb.gx = (int)gx; jb.gy = (r + nbr * 16 - 1) / (nbr * 16);
         if (gx * jb.gy > 0x3fffffffLL) return false;
-        out->kind = IT_KSPLIT; out->key = ttm_key(xt == BF16, false, false, true, nbr, ks, wide, false);
-        std::snprintf(out->label, sizeof(out->label), "k_ttm_ksplit<%s, %d, %d, %d>", tn, nbr, ks, ksplit_cb(nbr, wide));
+        const bool contig = ms_q == 1;
+        out->kind = IT_KSPLIT; out->key = ttm_key(xt == BF16, false, false, true, nbr, false) | ((unsigned)(cb - 1) << 16) | (contig ? 0x40000u : 0u);
+        std::snprintf(out->label, sizeof(out->label), "k_ttm_ksplit<%s, %d, %d, %s>", tn, nbr, cb, contig ? "true" : "false");
     } else {
         // short inner extents: tiles of whole outer indices (stores then run contiguously)
         jb.tile_cols = (!last && inner < TM_TC) ? (int)(TM_TC / inner * inner) : TM_TC;
@@ -625,7 +703,7 @@ static bool fill_ttm(DType xt, const void* X, long long outer, int n, long long 
         jb.gx = (int)gx; jb.gy = (r + TM_TQ - 1) / TM_TQ;
         if (gx * jb.gy > 0x3fffffffLL) return false;
         const bool kc64 = kron ? n > 64 : (last && n >= 256 && gx * jb.gy <= 256);   // (at most one workgroup per CU)
-        out->kind = IT_TTM; out->key = ttm_key(xt == BF16, last, kron, false, nbr, 0, false, kc64);
+        out->kind = IT_TTM; out->key = ttm_key(xt == BF16, last, kron, false, nbr, kc64);
         std::snprintf(out->label, sizeof(out->label), "k_ttm_mfma<%s, %s, %d, %d>", tn, last ? "true" : "false", nbr,
                       kron ? (kc64 ? 2 : 1) : (kc64 ? 3 : 0));
     }
@@ -665,17 +743,22 @@ static void launch_tiled(int nbr, const Batch<TtmJob>& b, dim3 grid, hipStream_t
         default: hipLaunchKernelGGL((k_ttm_mfma<T, LAST, 4, KM>), grid, 256, 0, st, b); break;
     }
 }
-template <typename T, int NBR>
-static void launch_split(int ks, bool wide, const Batch<TtmJob>& b, dim3 grid, hipStream_t st) {
-    constexpr int CB = NBR <= 3 ? 4 : 2;
-    if (wide) {
-        if (ks == 4) hipLaunchKernelGGL((k_ttm_ksplit<T, NBR, 4, CB>), grid, 256, 0, st, b);
-        else hipLaunchKernelGGL((k_ttm_ksplit<T, NBR, 8, CB>), grid, 256, 0, st, b);
-    } else {
-        if (ks == 4) hipLaunchKernelGGL((k_ttm_ksplit<T, NBR, 4, 1>), grid, 256, 0, st, b);
-        else if (ks == 8) hipLaunchKernelGGL((k_ttm_ksplit<T, NBR, 8, 1>), grid, 256, 0, st, b);
-        else hipLaunchKernelGGL((k_ttm_ksplit<T, NBR, 16, 1>), grid, 256, 0, st, b);
+template <typename T, int NBR, int CB, bool CONTIG>
+static hipError_t launch_split_one(const Batch<TtmJob>& b, dim3 grid, hipStream_t st) {
+    constexpr size_t lds = sizeof(float) * KS_NW * 16 * NBR * (16 * CB + 4);
+    if (lds > 64 * 1024) {
+        static LdsAllowed allowed;
+        const hipError_t e = allow_lds(reinterpret_cast<const void*>(k_ttm_ksplit<T, NBR, CB, CONTIG>), lds, allowed);
+        if (e != hipSuccess) return e;
     }
+    hipLaunchKernelGGL((k_ttm_ksplit<T, NBR, CB, CONTIG>), grid, KS_NT, lds, st, b);
+    return hipGetLastError();
+}
+template <typename T, int NBR>
+static hipError_t launch_split(int cb, bool contig, const Batch<TtmJob>& b, dim3 grid, hipStream_t st) {
+    if (cb == 2) return contig ? launch_split_one<T, NBR, 2, true>(b, grid, st) : launch_split_one<T, NBR, 2, false>(b, grid, st);
+    if (cb == 1) return contig ? launch_split_one<T, NBR, 1, true>(b, grid, st) : launch_split_one<T, NBR, 1, false>(b, grid, st);
+    return hipErrorInvalidValue;
 }
 
 // a: a tiled plain product that is not along the last mode; z: a Kronecker product with short K.
@@ -740,7 +823,8 @@ hipError_t launch_ttm_items(const Item* const* items, int n, hipStream_t st, cha
     if (!gather(items, n, &b, &grid)) return hipErrorInvalidValue;
     const unsigned key = items[0]->key;
     const bool bf16 = key & 1u, last = key & 2u, kron = key & 4u, ksplit = key & 8u;
-    const bool wide = key & 0x2000u, kc64 = key & 0x4000u;
+    const bool kc64 = key & 0x4000u, contig = key & 0x40000u;
+    const int cb = 1 + (int)((key >> 16) & 1u);
     if (key & 0x8000u) {             // very short mode: one instantiation per bound on n
         int nmax = 8;
         for (int j = 0; j < n; ++j) {
@@ -753,32 +837,31 @@ hipError_t launch_ttm_items(const Item* const* items, int n, hipStream_t st, cha
         else { if (nmax == 8) hipLaunchKernelGGL((k_ttm_thin<bf16_t, 8>), grid, 256, 0, st, b); else hipLaunchKernelGGL((k_ttm_thin<bf16_t, 16>), grid, 256, 0, st, b); }
         return hipGetLastError();
     }
-    // the instantiation with the most column blocks / steps serves every item
-    int nbr = 1, ks = 0;
+    // the instantiation with the most output blocks serves every item
+    int nbr = 1;
     for (int j = 0; j < n; ++j) {
-        const int nj = (int)((items[j]->key >> 4) & 7u) + 1, kj = (int)((items[j]->key >> 8) & 31u);
+        const int nj = (int)((items[j]->key >> 4) & 7u) + 1;
         nbr = nj > nbr ? nj : nbr;
-        ks = kj > ks ? kj : ks;
     }
     if (label_out) {
         const char* tn = bf16 ? "asi::bf16_t" : "float";
-        if (ksplit) std::snprintf(label_out, 96, "k_ttm_ksplit<%s, %d, %d, %d>", tn, nbr, ks, ksplit_cb(nbr, wide));
+        if (ksplit) std::snprintf(label_out, 96, "k_ttm_ksplit<%s, %d, %d, %s>", tn, nbr, cb, contig ? "true" : "false");
         else std::snprintf(label_out, 96, "k_ttm_mfma<%s, %s, %d, %d>", tn, last ? "true" : "false", nbr, kron ? (kc64 ? 2 : 1) : (kc64 ? 3 : 0));
     }
     if (ksplit) {
         if (!bf16) {
             switch (nbr) {
-                case 1: launch_split<float, 1>(ks, wide, b, grid, st); break;
-                case 2: launch_split<float, 2>(ks, wide, b, grid, st); break;
-                case 3: launch_split<float, 3>(ks, wide, b, grid, st); break;
-                default: launch_split<float, 4>(ks, wide, b, grid, st); break;
+                case 1: return launch_split<float, 1>(cb, contig, b, grid, st);
+                case 2: return launch_split<float, 2>(cb, contig, b, grid, st);
+                case 3: return launch_split<float, 3>(cb, contig, b, grid, st);
+                default: return launch_split<float, 4>(cb, contig, b, grid, st);
             }
         } else {
             switch (nbr) {
-                case 1: launch_split<bf16_t, 1>(ks, wide, b, grid, st); break;
-                case 2: launch_split<bf16_t, 2>(ks, wide, b, grid, st); break;
-                case 3: launch_split<bf16_t, 3>(ks, wide, b, grid, st); break;
-                default: launch_split<bf16_t, 4>(ks, wide, b, grid, st); break;
+                case 1: return launch_split<bf16_t, 1>(cb, contig, b, grid, st);
+                case 2: return launch_split<bf16_t, 2>(cb, contig, b, grid, st);
+                case 3: return launch_split<bf16_t, 3>(cb, contig, b, grid, st);
+                default: return launch_split<bf16_t, 4>(cb, contig, b, grid, st);
             }
         }
     } else if (kron) {           // always LASTMODE

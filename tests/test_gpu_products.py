@@ -1,0 +1,72 @@
+"""Mode products and pair products at the edges of their tiles, against the plain sums in float64."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _sites(call):
+    from paper_2505_05086_amd import binding as B
+    B.asi_profile_enable(True)
+    try:
+        call()
+        torch.cuda.synchronize()
+        return list(B.asi_profile_report())
+    finally:
+        B.asi_profile_enable(False)
+
+
+def _dev(x, dtype="f32"):
+    return torch.from_numpy(x.astype(np.float32)).cuda().to(torch.float32 if dtype == "f32" else torch.bfloat16)
+
+
+def _modes(x, mats):
+    """x multiplied along every mode by mats[m] (n_m x r_m), in float64."""
+    x = x.double()
+    for m in mats:
+        x = torch.tensordot(x, m.double(), dims=([0], [0]))
+    return x
+
+
+# The channel mode (not a multiple of the four entries of a step; fewer steps than waves times the steps in flight, and more), 15 to 65
+# outputs (one to four blocks, two tiles), columns short of and past one, two and many blocks, an inner extent of 1 x 2 to 9 x 11.
+@pytest.mark.parametrize("dims,ranks", [
+    ((3, 65, 1, 2), (3, 6, 1, 2)), ((2, 97, 5, 7), (2, 16, 2, 7)), ((70, 100, 7, 7), (40, 17, 3, 5)), ((5, 131, 9, 11), (5, 47, 4, 3)),
+    ((300, 66, 3, 5), (60, 33, 2, 5)), ((9, 515, 7, 7), (9, 63, 5, 5)), ((4, 1029, 5, 7), (4, 65, 5, 7)), ((170, 258, 7, 7), (10, 20, 2, 2))])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_product_along_a_long_mode_with_few_columns(dims, ranks, dtype):
+    """Bound: fp32 sums of at most 1029 products, off by about sqrt(K) 2^-25 of a typical entry; 2e-6 of the largest."""
+    from paper_2505_05086_amd import binding as B
+    rng = np.random.default_rng(sum(dims) + sum(ranks))
+    x = _dev(rng.standard_normal(dims), dtype)
+    U = [_dev(np.linalg.qr(rng.standard_normal((n, r)))[0]) for n, r in zip(dims, ranks)]
+    desc = B.make_desc(dims, ranks, dtype)
+    S = torch.empty(ranks, device="cuda")
+    ws = B.alloc_workspace(desc, None, 0)
+    ws.fill_(255)                                        # NaN wherever nothing was written
+    sites = _sites(lambda: B.asi_core_project(desc, x, U, S, ws))
+    assert any("k_ttm_ksplit" in s for s in sites), sites
+    want = _modes(x, U)
+    assert float((S - want).abs().max() / want.abs().max()) <= 2e-6
+
+
+@pytest.mark.parametrize("r2,cout", [(65, 30), (130, 7)])
+def test_product_with_a_transposed_matrix_along_a_long_mode(r2, cout):
+    """The last step of a 3 x 3 weight gradient with more than 64 core channels; bound as above, over two chained sums."""
+    from paper_2505_05086_amd import binding as B
+    rng = np.random.default_rng(r2)
+    dims, ranks = (4, 150, 9, 9), (4, r2, 9, 9)
+    x = _dev(rng.standard_normal(dims))
+    U = [_dev(np.linalg.qr(rng.standard_normal((n, r)))[0]) for n, r in zip(dims, ranks)]
+    S = _modes(x, U).float()
+    gy = _dev(rng.standard_normal((4, cout, 9, 9)))
+    desc, conv = B.make_desc(dims, ranks, "f32"), B.make_conv(cout, 3, 3, (1, 1), (1, 1), (1, 1), 1)
+    dW = torch.empty(cout, 150, 3, 3, device="cuda")
+    ws = B.alloc_workspace(desc, conv, 0)
+    ws.fill_(255)
+    sites = _sites(lambda: B.asi_weight_grad_conv2d(desc, S, U, gy, conv, dW, False, ws))
+    assert any("k_ttm_ksplit" in s and "false>" in s for s in sites), sites
+    xr = _modes(S, [u.t().contiguous() for u in U])
+    want = torch.nn.grad.conv2d_weight(xr.cpu(), dW.shape, gy.double().cpu(), padding=1).cuda()
+    assert float((dW - want).abs().max() / want.abs().max()) <= 5e-6
