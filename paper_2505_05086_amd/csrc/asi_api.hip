@@ -138,7 +138,8 @@ void choose_digits(const Shape& s, CompressPlan* p) {
 
 // cold: the first iteration of Alg. 1 (t = 0).  V is generated inside the P kernel of every mode, so no
 // mode takes a fused V/P kernel and no V is stored.  digits: the int8 MFMA may be used (the activation is aligned).
-CompressPlan plan_compress(const Shape& s, void* ws, bool cold = false, bool digits = false) {
+// coarse: fewer splits of the pair products (pair_splits).
+CompressPlan plan_with(const Shape& s, void* ws, bool cold, bool digits, bool coarse) {
     CompressPlan p;
     Carver c(ws);
     size_t vmax = 0;
@@ -189,7 +190,7 @@ CompressPlan plan_compress(const Shape& s, void* ws, bool cold = false, bool dig
         else if (p.gramm[m]) p.nsplit[m] = subspace_gram_nwg(s.dt, s.outer(m), (int)n, s.inner(m));
         else if (p.longm[m]) p.nsplit[m] = subspace_long_splits(s.outer(m), (int)n, s.inner(m), (int)r);
         else p.nsplit[m] = p.fused[m] ? subspace_small_nwg(s.outer(m), (int)n, s.inner(m))
-                                      : pair_splits(s.outer(m), (int)n, s.inner(m), (int)r);
+                                      : pair_splits(s.outer(m), (int)n, s.inner(m), (int)r, coarse);
         p.part[m] = c.take<double>((size_t)p.nsplit[m] * n * r);
         if (p.nsplit[m] > 32) {
             p.nsplit2[m] = (p.nsplit[m] + 31) / 32;
@@ -225,6 +226,16 @@ CompressPlan plan_compress(const Shape& s, void* ws, bool cold = false, bool dig
         }
     }
     p.bytes = c.off;
+    return p;
+}
+
+// The plan of a call.  Where only the partial sums of the pair products keep a layer out of the static scratch, they are fewer.
+CompressPlan plan_compress(const Shape& s, void* ws, bool cold = false, bool digits = false) {
+    CompressPlan p = plan_with(s, ws, cold, digits, false);
+    if (p.bytes > (size_t)ASI_STATIC_SCRATCH_BYTES) {
+        const CompressPlan q = plan_with(s, ws, cold, digits, true);
+        if (q.bytes <= (size_t)ASI_STATIC_SCRATCH_BYTES) return q;
+    }
     return p;
 }
 
@@ -382,13 +393,13 @@ struct LinPlan {
     size_t bytes = 0;
 };
 
-LinPlan plan_linear(const Shape& s, long long dout, void* ws) {
+LinPlan plan_linear(const Shape& s, long long dout, void* ws, bool coarse = false) {
     LinPlan p;
     Carver c(ws);
     p.G1 = c.take<float>((size_t)s.r[0] * s.n[1] * dout);
     p.G2 = c.take<float>((size_t)s.r[0] * s.r[1] * dout);
     if (s.r[0] == s.n[0]) p.S1 = c.take<float>((size_t)s.n[0] * s.r[1] * s.r[2]);
-    p.nsplit = pair_splits((long long)s.r[0] * s.r[1], (int)dout, 1, s.r[2]);
+    p.nsplit = pair_splits((long long)s.r[0] * s.r[1], (int)dout, 1, s.r[2], coarse);
     p.T = c.take<float>((size_t)dout * s.r[2]);
     p.Tpart = c.take<double>((size_t)p.nsplit * dout * s.r[2]);
     p.bytes = c.off;
@@ -527,7 +538,9 @@ asi_status build_compress(const asi_tensor_desc* desc, const void* A, const floa
     for (int m = 0; m < s.d; ++m)
         if ((!cold && !U_prev[m]) || !U_out[m]) return ASI_ERR_INVALID_ARG;
     CompressPlan p = plan_compress(s, ws, cold, reinterpret_cast<uintptr_t>(A) % 16 == 0);
-    if (p.amax && ws_bytes < p.bytes) p = plan_compress(s, ws, cold);        // (what fitted without the digits still does)
+    // scratch of another size than asi_workspace_bytes asks for: without the digits, then with fewer splits
+    if (p.amax && ws_bytes < p.bytes) p = plan_compress(s, ws, cold);
+    if (ws_bytes < p.bytes) p = plan_with(s, ws, cold, false, true);
     if (!ws_ok(ws, ws_bytes, p.bytes)) return ASI_ERR_WORKSPACE;
 
     OrthArgs fast, wide, slow;
@@ -911,6 +924,7 @@ asi_status build_linear(const asi_tensor_desc* desc, const float* S, const float
     for (int m = 0; m < 3; ++m)
         if (!U[m]) return ASI_ERR_INVALID_ARG;
     LinPlan p = plan_linear(s, dout, ws);
+    if (ws_bytes < p.bytes) p = plan_linear(s, dout, ws, true);              // (as in build_compress)
     if (!ws_ok(ws, ws_bytes, p.bytes)) return ASI_ERR_WORKSPACE;
     const int B = (int)s.n[0], N = (int)s.n[1], D = (int)s.n[2];
     const int r1 = s.r[0], r2 = s.r[1], r3 = s.r[2];

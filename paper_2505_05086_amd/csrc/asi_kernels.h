@@ -194,7 +194,8 @@ struct PairJob {
     int pre_blocks;
     PresumArgs pre;
 };
-int pair_splits(long long outer, int n, long long inner, int r);
+// coarse: never more than 256 columns a split leave, nor than fill the chip twice (for scratch that has no room for more)
+int pair_splits(long long outer, int n, long long inner, int r, bool coarse = false);
 bool make_pair(DType xt, const void* X, long long outer, int n, long long inner, const float* Y, int r, double* part,
                int nsplit, int32_t* zero, int nzero, const PresumArgs* pre, Item* out);
 // the same with Y = the generated standard-normal V of mode `mode` (Alg. 1, t = 0)

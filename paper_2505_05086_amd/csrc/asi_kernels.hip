@@ -8,6 +8,7 @@
 #include "asi_kernels.h"
 #include "asi_lds.h"
 
+#include <algorithm>
 #include <cstdio>
 #include <cstring>
 #include <type_traits>
@@ -15,42 +16,94 @@
 namespace asi {
 
 // ---------------------------------------------------------------------------
-// pair: P[i,q] = sum_c X[i,c] Y[q,c] on fp64 MFMA.  A workgroup owns 64 rows i x 32 outputs q
-// over one split of the unfolding columns; chunks of 64 columns are prefetched into registers
-// while the previous chunk is multiplied.  Wave w multiplies rows 16w..16w+15:
-//   A operand (16 i x 4 c) = Xs[4ks + lane/16][16w + lane%16],  B operand (4 c x 16 q) = Ys[4ks + lane/16][16nb + lane%16]
+// pair: P[i,q] = sum_c X[i,c] Y[q,c] on fp64 MFMA.  A workgroup owns 64 rows i x TQ = 16 NBQ outputs q over one split of the
+// unfolding columns, in chunks of 64 columns through two LDS buffers (one barrier a chunk); a chunk is requested two before it
+// is multiplied and stored one before.  Both tiles lie in LDS with the columns contiguous, pitch 68
+// (rows of four banks: 16-byte reads of 16 rows meet every bank once): one 16-byte read gives a lane its operand of four K steps,
+// K slot (s, lg) being column 16 b + 4 lg + s on both sides.  Four waves own 16 rows each, the other four take every other block
+// of 16 columns on accumulators of their own, added through LDS at the end.
+//   A operand (16 i x 4 c) = Xs[16 w + lane % 16][..],  B operand (4 c x 16 q) = Ys[16 nb + lane % 16][..]
 // fp32 values are widened to fp64, so every product is exact and the sums are carried in fp64.
+// Bound: fp64 MFMA (64 cycles for 16 x 16 x 4) and the vector instructions beside it, which a SIMD issues one after the other:
+// per 16 columns and 48 outputs a wave has 12 MFMAs, 4 LDS reads and 16 widenings, and its share of the staging, which ranks up
+// to 64 pay once.  Tiles of 64 x 32 outputs (a rank of 40 or 48 then took two of them, and half as many products again in
+// padding) with the columns apart in LDS had three reads and three widenings for every two MFMAs: 960 x 40 over 6272 columns 25.0 ->
+// 20.6 us, 512 x 48 over 3 x 3136 26.8 -> 20.9, 256 x 32 over 12544 16.4 -> 15.0, 768 x 192 over 2048 21.8 -> 19.4.  A chunk of 64 x 48
+// takes 4600 cycles, 3072 of them MFMA; requesting a chunk earlier, two workgroups a CU, or dword copies from memory to LDS
+// without registers (22.8) change nothing or lose.
 // ---------------------------------------------------------------------------
-constexpr int PR_TI = 64, PR_TQ = 32, PR_TK = 64;
-// Waves per workgroup: 4 own 16 rows of the tile each; the second four take every other K step of
-// a chunk on accumulators of their own, added through LDS at the end.  One wave per SIMD pays its
-// operand reads and conversions on top of its products; two waves per SIMD overlap them.
-constexpr int PR_NW = 8, PR_NT = 64 * PR_NW, PR_KG = PR_NW / 4;
+constexpr int PR_TI = 64, PR_TK = 64, PR_LD = PR_TK + 4, PR_NW = 8, PR_NT = 64 * PR_NW;
 typedef double v4d __attribute__((ext_vector_type(4)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 
-// GEN: Y is not read; its tile is the standard-normal V of Alg. 1's first iteration, generated by the
-// thread that stores it (64 columns x 8 groups of four outputs = one generator call per thread and chunk).
-// TQ: outputs per workgroup, 32 or 64.  64 along the last mode when the rank exceeds 32 (the hidden mode of a
-// transformer activation): a chunk's X tile then feeds twice the products, and the vector work of staging it,
-// which costs this kernel as much as its MFMAs, is paid half as often.
-extern __shared__ __align__(16) unsigned char pr_dyn[];
-template <typename T, bool LASTMODE, bool GEN, int TQ>
-__global__ __launch_bounds__(PR_NT) void k_pair(Batch<PairJob> bt) {
-    // Along the last mode the tiles are held widened (a Y element is an operand of four waves, so widening
-    // once at the store saves most of the conversions); otherwise the stores run down the columns of the
-    // tiles, where 8-byte elements would collide in the LDS banks.
-    using S = std::conditional_t<LASTMODE, double, float>;
-    static_assert(TQ == 32 || (TQ == 64 && LASTMODE && !GEN), "wide tiles along the last mode only");
-    constexpr size_t XS_BYTES = sizeof(S) * PR_TK * (PR_TI + 1);
-    static_assert(XS_BYTES % 16 == 0, "Ys starts aligned");
-    S (*Xs)[PR_TI + 1] = reinterpret_cast<S (*)[PR_TI + 1]>(pr_dyn);
-    S (*Ys)[TQ + 1] = reinterpret_cast<S (*)[TQ + 1]>(pr_dyn + XS_BYTES);
-    int lb;
-    const PairJob& jb = bt.job[locate(bt, &lb)];
+template <int TQ>
+constexpr size_t pair_lds() { return 2 * sizeof(float) * PR_LD * (PR_TI + TQ); }
+
+template <typename T> struct Four;                   // four consecutive elements as they lie in memory
+template <> struct Four<float> { typedef v4f type; };
+template <> struct Four<bf16_t> { typedef uint2 type; };
+__device__ __forceinline__ v4f widen4(const v4f& p) { return p; }
+__device__ __forceinline__ v4f widen4(const uint2& p) {
+    return (v4f){__uint_as_float(p.x << 16), __uint_as_float(p.x & 0xffff0000u), __uint_as_float(p.y << 16), __uint_as_float(p.y & 0xffff0000u)};
+}
+
+// one chunk: `left` columns of the split from its first on, tiles in buf
+template <int NBQ>
+__device__ __forceinline__ void pair_multiply(const float* buf, long long left, int wr, int kgrp, int lg, int ll, v4d (&acc)[NBQ]) {
+    const int nkb = (int)((left < PR_TK ? left : PR_TK) + 15) >> 4;
+#pragma unroll
+    for (int h = 0; h < PR_TK / 32; ++h) {
+        const int kb = 2 * h + kgrp;
+        if (kb < nkb) {                            // uniform
+            const v4f a = *reinterpret_cast<const v4f*>(buf + (16 * wr + ll) * PR_LD + 16 * kb + 4 * lg);
+            v4f b[NBQ];
+#pragma unroll
+            for (int nb = 0; nb < NBQ; ++nb) b[nb] = *reinterpret_cast<const v4f*>(buf + PR_LD * PR_TI + (16 * nb + ll) * PR_LD + 16 * kb + 4 * lg);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const double av = (double)a[u];
+#pragma unroll
+                for (int nb = 0; nb < NBQ; ++nb) acc[nb] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, (double)b[nb][u], acc[nb], 0, 0, 0);
+            }
+        }
+    }
+}
+// the K groups add their accumulators through LDS (the tiles are no longer read), then the first stores; out: the split's (n, r)
+extern __shared__ __align__(16) float pr_dyn[];
+template <int NBQ>
+__device__ __forceinline__ void pair_store(double* __restrict__ out, int n, int r, int i0, int q0, int wr, int kgrp, int lg, int ll, const v4d (&acc)[NBQ]) {
+    constexpr int TQ = 16 * NBQ;
+    double* red = reinterpret_cast<double*>(pr_dyn);              // PR_TI x TQ doubles
+    static_assert(pair_lds<TQ>() >= sizeof(double) * PR_TI * TQ, "reduction buffer fits the tiles");
+    __syncthreads();
+    if (kgrp == 1)
+#pragma unroll
+        for (int nb = 0; nb < NBQ; ++nb)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) red[(16 * wr + lg + 4 * v) * TQ + 16 * nb + ll] = acc[nb][v];
+    __syncthreads();
+    if (kgrp == 0)
+#pragma unroll
+        for (int nb = 0; nb < NBQ; ++nb)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int il = 16 * wr + lg + 4 * v, i = i0 + il, q = q0 + 16 * nb + ll;    // fp64 MFMA result layout
+                const double sum = acc[nb][v] + red[il * TQ + 16 * nb + ll];
+                if (i < n && q < r) out[(long long)i * r + q] = sum;
+            }
+}
+
+// FORM: how X (outer, n, inner) lies in memory.  PAIR_LAST: inner = 1, a thread takes four columns of one row.  PAIR_VEC: inner a
+// multiple of four and everything aligned, pieces of four columns.  PAIR_ANY: element by element.
+// GEN: Y is not read; its tile is the standard-normal V of Alg. 1's first iteration, generated by the thread that stores it.
+enum { PAIR_ANY = 0, PAIR_VEC = 1, PAIR_LAST = 2 };
+template <typename T, int FORM, bool GEN, int TQ>
+__device__ __forceinline__ void pair_tile(const PairJob& jb, int lb) {
+    constexpr int TI = PR_TI, NBQ = TQ / 16, BUF = PR_LD * (TI + TQ);
     const T* __restrict__ X = static_cast<const T*>(jb.X);
     const float* __restrict__ Y = jb.Y;
     double* __restrict__ part = jb.part;
-    const long long outer = jb.outer, inner = jb.inner, cols_per_split = jb.cols_per_split;
+    const long long outer = jb.outer, inner = jb.inner;
     const int n = jb.n, r = jb.r;
     if (lb >= jb.gx * jb.gy * jb.gz) {             // extra workgroups: another mode's partial-sum tree
         if (threadIdx.x < 256) presum_block(jb.pre.job, jb.pre.njobs, lb - jb.gx * jb.gy * jb.gz);
@@ -59,186 +112,245 @@ __global__ __launch_bounds__(PR_NT) void k_pair(Batch<PairJob> bt) {
     // Neighbouring blocks (one XCD after the renumbering) are the output tiles of the same rows of X,
     // then the row tiles of the same split: the large operand is fetched from memory once.
     lb = xcd_order(lb, jb.gx * jb.gy * jb.gz);
-    const int bz = lb / (jb.gx * jb.gy), rem = lb - bz * (jb.gx * jb.gy), bx = rem / jb.gy, by = rem - bx * jb.gy;
+    const int s = lb / (jb.gx * jb.gy), rem = lb - s * (jb.gx * jb.gy), bx = rem / jb.gy, by = rem - bx * jb.gy;
     const long long ncols = outer * inner;
-    const int i0 = bx * PR_TI, q0 = by * TQ, s = bz;
-    const long long cbeg = (long long)s * cols_per_split;
-    const long long cend = (cbeg + cols_per_split < ncols) ? cbeg + cols_per_split : ncols;
-    const int tid = threadIdx.x, lane = tid & 63, wave = (tid >> 6) & 3, kgrp = tid >> 8, lg = lane >> 4, ll = lane & 15;
+    const int i0 = bx * TI, q0 = by * TQ;
+    const long long cbeg = (long long)s * jb.cols_per_split;
+    const long long cend = (cbeg + jb.cols_per_split < ncols) ? cbeg + jb.cols_per_split : ncols;
+    const int tid = threadIdx.x, lane = tid & 63, lg = lane >> 4, ll = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wr = wave & 3, kgrp = wave >> 2;
     if (jb.zero && lb == 0 && tid < jb.nzero) jb.zero[tid] = 0;   // arrival counters of later launches
 
-    constexpr int NX = PR_TI * PR_TK / PR_NT, NY = TQ * PR_TK / PR_NT, RS = PR_NT / PR_TK;   // loads per thread, row step
-    constexpr int YCS = PR_NT / TQ;                // last mode: columns of the Y tile per pass of the workgroup
-    // A chunk's loads go to addresses that are always valid (a lane outside the tile, the split or the
-    // tensor reads a clamped position instead) and what they return stays untouched in registers until
-    // stash() masks and widens it after the previous chunk's MFMAs: the loads are one straight run of
-    // instructions, all in flight together, and nothing waits for one of them before the multiply.
-    T xr[NX];
-    float yr[NY];
-    static_assert(!GEN || (NY == 4 && RS * 4 == TQ), "one generator call (four outputs) per thread and chunk");
-    const int cl = tid & (PR_TK - 1), rl = tid / PR_TK;
-    // not the last mode: column c = (o, j) of this lane in the chunk to fetch next, carried from chunk
-    // to chunk by additions (PR_TK = so * inner + sj with sj < inner, so at most one carry into o)
-    // (a lane whose column lies beyond the tensor keeps base 0: with a row offset it still reads inside X)
-    long long lc = cbeg + cl, lj = 0, xbase = 0, ybase = 0;
-    const int so = LASTMODE || inner > PR_TK ? 0 : PR_TK / (int)inner;
-    const long long sj = LASTMODE ? 0 : PR_TK - so * inner;
-    const long long xplane = (long long)n * inner, yplane = (long long)r * inner;
-    if (!LASTMODE && lc < ncols) {
-        // quotient by a double division (exact below 2^52) with one correction step
-        long long o = (long long)((double)lc / (double)inner);
-        lj = lc - o * inner;
-        if (lj < 0) { --o; lj += inner; } else if (lj >= inner) { ++o; lj -= inner; }
-        xbase = o * xplane + lj;
-        ybase = o * yplane + lj;
-    }
-    // last mode: offsets of this lane's elements from the chunk's first element (PR_TK * n < 2^32: host check);
-    // a column past the split's end reads column 0 instead, a row or output past the end the tile's first
-    unsigned xoff[LASTMODE ? NX : 1], yoff[LASTMODE ? NY : 1];
-    const unsigned xoff0 = (i0 + (tid & 63) < n) ? (tid & 63) : 0, yoff0 = (q0 + (tid & (TQ - 1)) < r) ? (tid & (TQ - 1)) : 0;
-    if (LASTMODE) {
-#pragma unroll
-        for (int t = 0; t < NX; ++t) xoff[t] = (unsigned)((tid >> 6) + PR_NW * t) * (unsigned)n + xoff0;
-#pragma unroll
-        for (int t = 0; t < NY; ++t) yoff[t] = (unsigned)(tid / TQ + YCS * t) * (unsigned)r + yoff0;
-    }
-    auto fetch = [&](long long c0) {
-        if (!LASTMODE) {
-#pragma unroll
-            for (int t = 0; t < NX; ++t) {
-                const int i = i0 + rl + RS * t;
-                xr[t] = X[xbase + (long long)(i < n ? i : i0) * inner];
-            }
-            if (GEN) gauss4(jb.seed_lo, jb.seed_hi, jb.mode, c0 + cl, (uint32_t)(q0 / 4 + rl), yr);
-#pragma unroll
-            for (int t = 0; t < (GEN ? 0 : NY); ++t) {
-                const int q = q0 + rl + RS * t;
-                yr[t] = Y[ybase + (long long)(q < r ? q : q0) * inner];
-            }
-            lc += PR_TK; lj += sj; xbase += so * xplane + sj; ybase += so * yplane + sj;
-            if (lj >= inner) { lj -= inner; xbase += xplane - inner; ybase += yplane - inner; }
-            if (lc >= ncols) { xbase = 0; ybase = 0; }
-        } else {  // inner == 1: one 64-bit base per chunk (uniform) and 32-bit lane offsets, fixed for the whole split
-            const T* __restrict__ xb = X + (c0 * (long long)n + i0);
-            const float* __restrict__ yb = GEN ? nullptr : Y + (c0 * (long long)r + q0);
-            const int lim = (int)(cend - c0 < PR_TK ? cend - c0 : PR_TK);     // columns of the chunk inside the split
-#pragma unroll
-            for (int t = 0; t < NX; ++t) xr[t] = xb[(tid >> 6) + PR_NW * t < lim ? xoff[t] : xoff0];
-            if (GEN) gauss4(jb.seed_lo, jb.seed_hi, jb.mode, c0 + cl, (uint32_t)(q0 / 4 + rl), yr);
-#pragma unroll
-            for (int t = 0; t < (GEN ? 0 : NY); ++t) yr[t] = yb[tid / TQ + YCS * t < lim ? yoff[t] : yoff0];
-        }
+    // Loads go to addresses that are always valid and what they return stays untouched in registers until stash(): they are one
+    // straight run of instructions, all in flight together.  A row or an output past the end reads the last one (its results are
+    // dropped); a column past the split's end reads a column inside the tensor and is masked on both sides.  An address is a
+    // base that is the same for the wave (scalar unit) plus a lane offset that is worked out once per chunk or per split: the 64-bit
+    // arithmetic of a row times inner per load and chunk cost as much as the products.
+    constexpr int NXA = TI / 8, NYA = TQ / 8;                // PAIR_ANY: column tid & 63, rows wave + 8 t
+    constexpr int NXV = TI / 32, NYV = (TQ + 31) / 32;       // PAIR_VEC: piece tid & 15, rows tid / 16 + 32 t
+    constexpr int NXL = TI / 32, NYL = (TQ + 31) / 32;       // PAIR_LAST: (row, group of four columns) e = tid + 512 t
+    constexpr int NG = (NBQ + 1) / 2;                        // GEN: (column e & 63, group of four outputs e / 64)
+    typedef typename Four<T>::type X4;
+    struct Stage {
+        T xa[FORM == PAIR_ANY ? NXA : (FORM == PAIR_LAST ? 4 * NXL : 1)];
+        X4 xv[FORM == PAIR_VEC ? NXV : 1];
+        float ya[GEN ? 4 * NG : (FORM == PAIR_ANY ? NYA : (FORM == PAIR_LAST ? 4 * NYL : 1))];
+        v4f yv[!GEN && FORM == PAIR_VEC ? NYV : 1];
     };
-    auto stash = [&](long long c0) {
-        if (!LASTMODE) {
-            const bool valid = c0 + cl < cend;
+    const int cl = FORM == PAIR_VEC ? 4 * (tid & 15) : lane, rl = FORM == PAIR_VEC ? tid >> 4 : wave;
+    const long long xplane = (long long)n * inner, yplane = (long long)r * inner;
+    // not the last mode: slab and place in it of the chunk to fetch next (uniform)
+    long long co = 0, cj = 0;
+    if (FORM != PAIR_LAST) { co = cbeg / inner; cj = cbeg - co * inner; }
+    const float inv_inner = 1.0f / (float)inner;
+    // lane offsets that hold for the whole split
+    long long xro[FORM == PAIR_VEC ? NXV : 1], yro[!GEN && FORM == PAIR_VEC ? NYV : 1];
+    unsigned xrl = 0, yrl[!GEN && FORM == PAIR_LAST ? NYL : 1];
+    if constexpr (FORM == PAIR_VEC) {
 #pragma unroll
-            for (int t = 0; t < NX; ++t) Xs[cl][rl + RS * t] = (valid && i0 + rl + RS * t < n) ? to_f32(xr[t]) : 0.f;
+        for (int t = 0; t < NXV; ++t) { const int i = i0 + rl + 32 * t; xro[t] = (i < n ? i : n - 1) * inner; }
+        if constexpr (!GEN)
 #pragma unroll
-            for (int t = 0; t < NY; ++t) {
-                const int ql = GEN ? 4 * rl + t : rl + RS * t;
-                Ys[cl][ql] = (valid && q0 + ql < r) ? yr[t] : 0.f;
+            for (int t = 0; t < NYV; ++t) { const int q = q0 + rl + 32 * t; yro[t] = (q < r ? q : r - 1) * inner; }
+    }
+    if constexpr (FORM == PAIR_LAST) {
+        xrl = (unsigned)(i0 + lane < n ? i0 + lane : n - 1);
+        if constexpr (!GEN)
+#pragma unroll
+            for (int t = 0; t < NYL; ++t) {
+                const int q = q0 + (tid + PR_NT * t) % TQ;
+                yrl[t] = (unsigned)(q < r ? q : r - 1);
             }
-        } else {
-            const bool iv = i0 + (tid & 63) < n, qv = q0 + (tid & (TQ - 1)) < r;
+    }
+    auto fetch = [&](long long c0, Stage& st) __attribute__((always_inline)) {
+        const int lim = (int)(cend - c0 < PR_TK ? cend - c0 : PR_TK);     // columns of the chunk inside the split
+        if constexpr (FORM != PAIR_LAST) {
+            // this lane's column: slab co + o, place j; a column past the tensor's end reads the chunk's first
+            const int in = c0 + cl < ncols ? cl : 0;
+            const long long j0 = cj + in;
+            const int o = inner < PR_TK ? (int)(((float)(int)j0 + 0.5f) * inv_inner) : (j0 >= inner ? 1 : 0);      // (j0 < 128: exact)
+            const long long j = j0 - (inner < PR_TK ? (long long)(o * (int)inner) : (o ? inner : 0));
+            const long long xo = o * xplane + j, yo = o * yplane + j;
+            const T* __restrict__ xb = X + co * xplane;
+            const float* __restrict__ yb = GEN ? nullptr : Y + co * yplane;
+            if constexpr (FORM == PAIR_ANY) {
 #pragma unroll
-            for (int t = 0; t < NX; ++t)
-                Xs[(tid >> 6) + PR_NW * t][tid & 63] = (iv && c0 + (tid >> 6) + PR_NW * t < cend) ? (S)to_f32(xr[t]) : (S)0;
-            if (GEN) {
+                for (int t = 0; t < NXA; ++t) { const int i = i0 + rl + 8 * t; st.xa[t] = (xb + (i < n ? i : n - 1) * inner)[xo]; }
+                if constexpr (!GEN)
 #pragma unroll
-                for (int t = 0; t < NY; ++t) Ys[cl][4 * rl + t] = (c0 + cl < cend && q0 + 4 * rl + t < r) ? (S)yr[t] : (S)0;
+                    for (int t = 0; t < NYA; ++t) { const int q = q0 + rl + 8 * t; st.ya[t] = (yb + (q < r ? q : r - 1) * inner)[yo]; }
             } else {
 #pragma unroll
-                for (int t = 0; t < NY; ++t)
-                    Ys[tid / TQ + YCS * t][tid & (TQ - 1)] = (qv && c0 + tid / TQ + YCS * t < cend) ? (S)yr[t] : (S)0;
+                for (int t = 0; t < NXV; ++t) st.xv[t] = *reinterpret_cast<const X4*>(xb + (xo + xro[t]));
+                if constexpr (!GEN)
+#pragma unroll
+                    for (int t = 0; t < NYV; ++t) st.yv[t] = *reinterpret_cast<const v4f*>(yb + (yo + yro[t]));
+            }
+            cj += PR_TK;
+            if (inner < PR_TK) { const int d = (int)(((float)(int)cj + 0.5f) * inv_inner); co += d; cj -= d * inner; }
+            else if (cj >= inner) { ++co; cj -= inner; }
+        } else {
+            // (64 n and 64 r below 2^30: host check)
+            const T* __restrict__ xb = X + c0 * (long long)n;
+#pragma unroll
+            for (int t = 0; t < NXL; ++t)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int c = 4 * (wave + PR_NW * t) + u;             // uniform
+                    st.xa[4 * t + u] = (xb + (c < lim ? c : 0) * (long long)n)[xrl];
+                }
+            if constexpr (!GEN) {
+                const float* __restrict__ yb = Y + c0 * (long long)r;
+#pragma unroll
+                for (int t = 0; t < NYL; ++t) {
+                    const int c = 4 * ((tid + PR_NT * t) / TQ);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) st.ya[4 * t + u] = yb[(unsigned)(c + u < lim ? c + u : 0) * (unsigned)r + yrl[t]];
+                }
             }
         }
+        if constexpr (GEN)
+#pragma unroll
+            for (int t = 0; t < NG; ++t) {
+                const int e = tid + PR_NT * t, c = e & 63, g = e >> 6;
+                if (g < 4 * NBQ && q0 + 4 * g < r) gauss4(jb.seed_lo, jb.seed_hi, jb.mode, c0 + c, (uint32_t)(q0 / 4 + g), st.ya + 4 * t);
+            }
+    };
+    // FULL: every column of the chunk belongs to the split
+    auto stash_as = [&](auto full, int lim, float* buf, const Stage& st) __attribute__((always_inline)) {
+        constexpr bool FULL = decltype(full)::value;
+        float* xs = buf;
+        float* ys = buf + PR_LD * TI;
+        auto mask4 = [&](v4f v, int c) __attribute__((always_inline)) {
+            if constexpr (!FULL)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) v[u] = c + u < lim ? v[u] : 0.f;
+            return v;
+        };
+        if constexpr (FORM == PAIR_ANY) {
+            const bool in = FULL || cl < lim;
+#pragma unroll
+            for (int t = 0; t < NXA; ++t) xs[(rl + 8 * t) * PR_LD + cl] = in ? to_f32(st.xa[t]) : 0.f;
+            if constexpr (!GEN)
+#pragma unroll
+                for (int t = 0; t < NYA; ++t) ys[(rl + 8 * t) * PR_LD + cl] = in ? st.ya[t] : 0.f;
+        } else if constexpr (FORM == PAIR_VEC) {
+#pragma unroll
+            for (int t = 0; t < NXV; ++t) *reinterpret_cast<v4f*>(xs + (rl + 32 * t) * PR_LD + cl) = mask4(widen4(st.xv[t]), cl);
+            if constexpr (!GEN)
+#pragma unroll
+                for (int t = 0; t < NYV; ++t)
+                    if (TQ % 32 == 0 || rl + 32 * t < TQ) *reinterpret_cast<v4f*>(ys + (rl + 32 * t) * PR_LD + cl) = mask4(st.yv[t], cl);
+        } else {
+#pragma unroll
+            for (int t = 0; t < NXL; ++t) {
+                const int g = wave + PR_NW * t;
+                const v4f v = {to_f32(st.xa[4 * t]), to_f32(st.xa[4 * t + 1]), to_f32(st.xa[4 * t + 2]), to_f32(st.xa[4 * t + 3])};
+                *reinterpret_cast<v4f*>(xs + lane * PR_LD + 4 * g) = mask4(v, 4 * g);
+            }
+            if constexpr (!GEN)
+#pragma unroll
+                for (int t = 0; t < NYL; ++t) {
+                    const int e = tid + PR_NT * t, g = e / TQ, q = e - g * TQ;
+                    const v4f v = {st.ya[4 * t], st.ya[4 * t + 1], st.ya[4 * t + 2], st.ya[4 * t + 3]};
+                    if (TQ % 32 == 0 || g < PR_TK / 4) *reinterpret_cast<v4f*>(ys + q * PR_LD + 4 * g) = mask4(v, 4 * g);
+                }
+        }
+        if constexpr (GEN)
+#pragma unroll
+            for (int t = 0; t < NG; ++t) {
+                const int e = tid + PR_NT * t, c = e & 63, g = e >> 6;
+                if (g < 4 * NBQ)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) ys[(4 * g + u) * PR_LD + c] = ((FULL || c < lim) && q0 + 4 * g < r) ? st.ya[4 * t + u] : 0.f;
+            }
+    };
+    auto stash = [&](long long c0, float* buf, const Stage& g) __attribute__((always_inline)) {
+        if (cend - c0 >= PR_TK) stash_as(std::true_type{}, PR_TK, buf, g);
+        else stash_as(std::false_type{}, (int)(cend - c0), buf, g);
     };
 
-    constexpr int NBQ = TQ / 16;
     v4d acc[NBQ];
 #pragma unroll
     for (int nb = 0; nb < NBQ; ++nb) acc[nb] = (v4d){0.0, 0.0, 0.0, 0.0};
-    if (cbeg < cend) fetch(cbeg);
+    // chunk c is multiplied while chunk c + 1 is stored and chunk c + 2 is on its way
+    Stage g;
+    float* cur = pr_dyn;
+    float* nxt = pr_dyn + BUF;
+    if (cbeg < cend) {
+        fetch(cbeg, g);
+        stash(cbeg, cur, g);
+        if (cbeg + PR_TK < cend) fetch(cbeg + PR_TK, g);
+    }
     for (long long c0 = cbeg; c0 < cend; c0 += PR_TK) {
-        __syncthreads();
-        stash(c0);
-        __syncthreads();
-        if (c0 + PR_TK < cend) fetch(c0 + PR_TK);
-#pragma unroll
-        for (int ks = kgrp; ks < PR_TK / 4; ks += PR_KG) {
-            const double a = (double)Xs[4 * ks + lg][16 * wave + ll];
-            double bq[NBQ];
-#pragma unroll
-            for (int nb = 0; nb < NBQ; ++nb) bq[nb] = (double)Ys[4 * ks + lg][16 * nb + ll];
-#pragma unroll
-            for (int nb = 0; nb < NBQ; ++nb) acc[nb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, bq[nb], acc[nb], 0, 0, 0);
-        }
+        __syncthreads();                           // this chunk is stored, and the other buffer has been read
+        if (c0 + PR_TK < cend) stash(c0 + PR_TK, nxt, g);
+        if (c0 + 2 * PR_TK < cend) fetch(c0 + 2 * PR_TK, g);
+        pair_multiply<NBQ>(cur, cend - c0, wr, kgrp, lg, ll, acc);
+        float* t = cur; cur = nxt; nxt = t;
     }
-    // the K groups add their accumulators through LDS (the tiles are no longer read), then group 0 stores
-    double* red = reinterpret_cast<double*>(&Xs[0][0]);           // 64 x TQ doubles in the space of the X tile
-    static_assert(XS_BYTES >= sizeof(double) * PR_TI * TQ, "reduction buffer fits the X tile");
-#pragma unroll
-    for (int kg = PR_KG - 1; kg >= 1; --kg) {
-        __syncthreads();
-        if (kgrp == kg) {
-#pragma unroll
-            for (int nb = 0; nb < NBQ; ++nb)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    double* p = red + (16 * wave + lg + 4 * v) * TQ + 16 * nb + ll;
-                    *p = (kg == PR_KG - 1) ? acc[nb][v] : *p + acc[nb][v];
-                }
-        }
-    }
-    __syncthreads();
-    if (kgrp == 0) {
-#pragma unroll
-        for (int nb = 0; nb < NBQ; ++nb)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int i = i0 + 16 * wave + lg + 4 * v, q = q0 + 16 * nb + ll;    // fp64 MFMA result layout
-                const double sum = PR_KG > 1 ? acc[nb][v] + red[(16 * wave + lg + 4 * v) * TQ + 16 * nb + ll] : acc[nb][v];
-                if (i < n && q < r) part[((long long)s * n + i) * r + q] = sum;
-            }
-    }
+    pair_store<NBQ>(part + (long long)s * n * r, n, r, i0, q0, wr, kgrp, lg, ll, acc);
+}
+template <typename T, bool LAST, bool GEN, int TQ>
+__global__ __launch_bounds__(PR_NT, 4) void k_pair(Batch<PairJob> bt) {
+    int lb;
+    const PairJob& jb = bt.job[locate(bt, &lb)];
+    pair_tile<T, LAST ? PAIR_LAST : PAIR_ANY, GEN, TQ>(jb, lb);
+}
+template <typename T, int TQ>
+__global__ __launch_bounds__(PR_NT, 4) void k_pair_vec(Batch<PairJob> bt) {
+    int lb;
+    const PairJob& jb = bt.job[locate(bt, &lb)];
+    pair_tile<T, PAIR_VEC, false, TQ>(jb, lb);
 }
 
+// Outputs per workgroup and splits of the columns.  Splits for the least modelled time, in cycles: a CU's workgroups, each 256 NBQ
+// cycles of MFMA per 16 columns and 88 + 52 NBQ of staging, reads and widenings; 8000 for what lies before the first and after
+// the last product; then the partial sums, written and read once at some 1.6 KB a cycle, a round trip for every 16 (32 up to rank
+// 32) that gram0 adds up together, and beyond 32 of them a level of the partial-sum tree (one more launch on the chain).
+// Three 512 x 48 layers of 3136 columns: 10 | 13 | 17 | 25 | 32 splits 26.8 | 23.4 | 19.8 | 23.7 | 27.1 us, gram0 25.2 up to 16, then 27.4.
+struct PairPlan { int tq, ns; };
 static long long pair_cols_per_split(long long ncols, int nsplit) {
-    long long cps = (ncols + nsplit - 1) / nsplit;
-    cps = (cps + PR_TK - 1) / PR_TK * PR_TK;
-    return cps;
+    const long long cps = (ncols + nsplit - 1) / nsplit;
+    return (cps + 15) / 16 * 16;
 }
-
-// outputs per workgroup: 64 along the last mode for ranks above 32 over a long contraction (with a few thousand
-// columns the launch is short of workgroups rather than of MFMA rate: T of the linear layers of a ViT block,
-// 2048 columns, takes 38 us with 64 outputs against 33 with 32); not for the generating variant
-static int pair_tq(long long ncols, long long inner, int r, bool gen) {
-    return (inner == 1 && r > 32 && ncols >= 4096 && !gen) ? 64 : PR_TQ;
-}
-
-int pair_splits(long long outer, int n, long long inner, int r) {
-    const long long ncols = outer * inner;
-    const int tq = pair_tq(ncols, inner, r, false);
-    const long long tiles = (long long)((n + PR_TI - 1) / PR_TI) * ((r + tq - 1) / tq);
-    long long maxs = (ncols + 255) / 256;                     // at least 256 columns per split
-    if (maxs > 64) maxs = 64;
-    if (maxs < 1) maxs = 1;
-    // The chip holds two workgroups per CU at full rate (512 slots; a single workgroup per CU leaves the
-    // MFMA pipe idle while it loads and stores tiles).  Workgroups beyond that run in further rounds, so
-    // the time goes as rounds x (columns of a split + a fixed cost per workgroup, worth ~128 columns);
-    // the number of splits minimises it.  Few tiles: as many splits as allowed (one round anyway); many
-    // tiles (a 3072 x 192 result is 288): a count that fills whole rounds, not one workgroup per CU.
+static PairPlan pair_plan(long long ncols, long long inner, int n, int r, int most) {
+    const int blocks = (r + 15) / 16, gy = (blocks + 3) / 4;
+    int nbq = (blocks + gy - 1) / gy;
+    if (inner == 1 && gy == 1 && nbq == 3) nbq = 4;
+    const long long tiles = (long long)((n + PR_TI - 1) / PR_TI) * gy;
+    long long maxs = (ncols + 127) / 128;                     // at least 128 columns per split
+    maxs = maxs > most ? most : (maxs < 1 ? 1 : maxs);
+    const int lot = r > 32 ? 16 : 32;
     int best = 1;
-    long long best_cost = -1;
+    double best_cost = -1.0;
     for (int ns = 1; ns <= (int)maxs; ++ns) {
         const long long cps = pair_cols_per_split(ncols, ns);
-        if (ns > 1 && cps * (ns - 1) >= ncols) continue;     // the last split would be empty
-        const long long rounds = (tiles * ns + 511) / 512;
-        // beyond 32 splits the partial sums need a tree level: one more launch on the chain (~600 columns' worth)
-        const long long cost = rounds * (cps + 128) + (ns > 32 ? 600 : 0);
+        if (ns > 1 && cps * (ns - 1) >= ncols) continue;      // the last split would be empty
+        const double per_cu = (double)((tiles * ns + 255) / 256);
+        const double cost = per_cu * cps / 16.0 * (308.0 * nbq + 88.0) + (per_cu > 1.0 ? 2.0 : 1.0) * 8000.0 + ns * (double)n * r * 16.0 / 1600.0 +
+                            (ns + lot - 1) / lot * 4800.0 + (ns > 32 ? 10000.0 : 0.0);
+        if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = ns; }
+    }
+    return {16 * nbq, best};
+}
+int pair_splits(long long outer, int n, long long inner, int r, bool coarse) {
+    const long long ncols = outer * inner;
+    if (!coarse) return pair_plan(ncols, inner, n, r, 64).ns;
+    // the least rounds x (columns of a split, in chunks, + 128) of 512 workgroups of 64 x 32 (64 along the last mode), 256 columns or more a split
+    const int tq = (inner == 1 && r > 32 && ncols >= 4096) ? 64 : 32;
+    const long long tiles = (long long)((n + PR_TI - 1) / PR_TI) * ((r + tq - 1) / tq);
+    const int maxs = (int)std::max(1LL, std::min(64LL, (ncols + 255) / 256));
+    int best = 1;
+    long long best_cost = -1;
+    for (int ns = 1; ns <= maxs; ++ns) {
+        const long long cps = ((ncols + ns - 1) / ns + PR_TK - 1) / PR_TK * PR_TK;
+        if (ns > 1 && cps * (ns - 1) >= ncols) continue;
+        const long long cost = (tiles * ns + 511) / 512 * (cps + 128) + (ns > 32 ? 600 : 0);
         if (best_cost < 0 || cost < best_cost) { best = ns; best_cost = cost; }
     }
+    // (no split may be empty with 16 columns as the unit either)
+    while (best > 1 && pair_cols_per_split(ncols, best) * (best - 1) >= ncols) --best;
     return best;
 }
 
@@ -265,7 +377,7 @@ static bool make_pair_any(DType xt, const void* X, long long outer, int n, long 
     jb.X = X; jb.outer = outer; jb.inner = inner; jb.cols_per_split = pair_cols_per_split(ncols, nsplit);
     jb.Y = gen ? nullptr : Y; jb.part = part; jb.n = n; jb.r = r;
     jb.seed_lo = (uint32_t)(seed & 0xffffffffu); jb.seed_hi = (uint32_t)(seed >> 32); jb.mode = mode;
-    const int tq = pair_tq(ncols, inner, r, gen);
+    const int tq = pair_plan(ncols, inner, n, r, nsplit).tq;
     jb.gx = (n + PR_TI - 1) / PR_TI; jb.gy = (r + tq - 1) / tq; jb.gz = nsplit;
     jb.zero = zero; jb.nzero = zero ? nzero : 0;
     if (pre) {
@@ -273,12 +385,16 @@ static bool make_pair_any(DType xt, const void* X, long long outer, int n, long 
         if (jb.pre_blocks < 0) return false;
         jb.pre = *pre;
     }
-    const bool last = (inner == 1);
+    const bool vec = inner % 4 == 0 && reinterpret_cast<uintptr_t>(X) % (xt == F32 ? 16 : 8) == 0 && reinterpret_cast<uintptr_t>(Y) % 16 == 0;
+    // (generating takes an order longer: one form of it is enough)
+    const int form = inner == 1 ? PAIR_LAST : (vec && !gen ? PAIR_VEC : PAIR_ANY);
     *out = Item();
-    out->kind = IT_PAIR; out->key = (xt == BF16 ? 1u : 0u) | (last ? 2u : 0u) | (gen ? 4u : 0u) | (tq == 64 ? 8u : 0u);
+    out->kind = IT_PAIR;
+    out->key = (xt == BF16 ? 1u : 0u) | ((unsigned)form << 1) | (gen ? 8u : 0u) | ((unsigned)(tq / 16 - 1) << 4);
+    const char* tn = xt == F32 ? "float" : "asi::bf16_t";
+    if (form == PAIR_VEC) std::snprintf(out->label, sizeof(out->label), "k_pair_vec<%s, %d>", tn, tq);
+    else std::snprintf(out->label, sizeof(out->label), "k_pair<%s, %s, %s, %d>", tn, form == PAIR_LAST ? "true" : "false", gen ? "true" : "false", tq);
     out->nblocks = jb.gx * jb.gy * jb.gz + jb.pre_blocks;
-    std::snprintf(out->label, sizeof(out->label), "k_pair<%s, %s, %s, %d>", xt == F32 ? "float" : "asi::bf16_t",
-                  last ? "true" : "false", gen ? "true" : "false", tq);
     static_assert(sizeof(PairJob) <= kItemArgMax, "argument block");
     std::memcpy(out->arg, &jb, sizeof(jb));
     return true;
@@ -293,38 +409,48 @@ bool make_pair_gauss(DType xt, const void* X, long long outer, int n, long long 
     return make_pair_any(xt, X, outer, n, inner, nullptr, true, seed, mode, r, part, nsplit, zero, nzero, pre, out);
 }
 
+template <typename T, int FORM, bool GEN, int TQ>
+static hipError_t launch_pair_one(const Batch<PairJob>& b, dim3 grid, hipStream_t st) {
+    constexpr size_t lds = pair_lds<TQ>();
+    void (*fn)(Batch<PairJob>);
+    if constexpr (FORM == PAIR_VEC) fn = k_pair_vec<T, TQ>;
+    else fn = k_pair<T, FORM == PAIR_LAST, GEN, TQ>;
+    if (lds > 64 * 1024) {
+        static LdsAllowed allowed;
+        const hipError_t e = allow_lds(reinterpret_cast<const void*>(fn), lds, allowed);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(fn, grid, PR_NT, lds, st, b);
+    return hipGetLastError();
+}
+template <typename T, int FORM, bool GEN>
+static hipError_t launch_pair_size(int tq, const Batch<PairJob>& b, dim3 grid, hipStream_t st) {
+    switch (tq) {
+        case 16: return launch_pair_one<T, FORM, GEN, 16>(b, grid, st);
+        case 32: return launch_pair_one<T, FORM, GEN, 32>(b, grid, st);
+        case 48: return launch_pair_one<T, FORM, GEN, 48>(b, grid, st);
+        default: return launch_pair_one<T, FORM, GEN, 64>(b, grid, st);
+    }
+}
 hipError_t launch_pair_items(const Item* const* items, int n, hipStream_t st) {
     Batch<PairJob> b;
     dim3 grid;
     if (!gather(items, n, &b, &grid)) return hipErrorInvalidValue;
-    // tiles: PR_TK x (PR_TI + 1) of X and PR_TK x (TQ + 1) of Y, as doubles along the last mode, else floats
-    const size_t lds_f = sizeof(float) * PR_TK * ((PR_TI + 1) + (PR_TQ + 1));
-    const size_t lds_d = sizeof(double) * PR_TK * ((PR_TI + 1) + (PR_TQ + 1));
-    const size_t lds_w = sizeof(double) * PR_TK * ((PR_TI + 1) + (64 + 1));
-    const unsigned key = items[0]->key & 15u;
-    if (key & 8u) {                    // 64 outputs per workgroup: more LDS than a static array may take
-        if (key != 10u && key != 11u) return hipErrorInvalidValue;
-        static LdsAllowed allowed[2];
-        const int bi = key & 1u;
-        const void* fn = bi ? reinterpret_cast<const void*>(k_pair<bf16_t, true, false, 64>)
-                            : reinterpret_cast<const void*>(k_pair<float, true, false, 64>);
-        const hipError_t e = allow_lds(fn, lds_w, allowed[bi]);
-        if (e != hipSuccess) return e;
-        if (bi) hipLaunchKernelGGL((k_pair<bf16_t, true, false, 64>), grid, PR_NT, lds_w, st, b);
-        else hipLaunchKernelGGL((k_pair<float, true, false, 64>), grid, PR_NT, lds_w, st, b);
-        return hipGetLastError();
+    const unsigned key = items[0]->key;
+    const int tq = 16 * (1 + (int)((key >> 4) & 3u));
+    switch (key & 15u) {
+        case 0: return launch_pair_size<float, PAIR_ANY, false>(tq, b, grid, st);
+        case 1: return launch_pair_size<bf16_t, PAIR_ANY, false>(tq, b, grid, st);
+        case 2: return launch_pair_size<float, PAIR_VEC, false>(tq, b, grid, st);
+        case 3: return launch_pair_size<bf16_t, PAIR_VEC, false>(tq, b, grid, st);
+        case 4: return launch_pair_size<float, PAIR_LAST, false>(tq, b, grid, st);
+        case 5: return launch_pair_size<bf16_t, PAIR_LAST, false>(tq, b, grid, st);
+        case 8: return launch_pair_size<float, PAIR_ANY, true>(tq, b, grid, st);
+        case 9: return launch_pair_size<bf16_t, PAIR_ANY, true>(tq, b, grid, st);
+        case 12: return launch_pair_size<float, PAIR_LAST, true>(tq, b, grid, st);
+        case 13: return launch_pair_size<bf16_t, PAIR_LAST, true>(tq, b, grid, st);
+        default: return hipErrorInvalidValue;
     }
-    switch (key) {
-        case 0: hipLaunchKernelGGL((k_pair<float, false, false, PR_TQ>), grid, PR_NT, lds_f, st, b); break;
-        case 1: hipLaunchKernelGGL((k_pair<bf16_t, false, false, PR_TQ>), grid, PR_NT, lds_f, st, b); break;
-        case 2: hipLaunchKernelGGL((k_pair<float, true, false, PR_TQ>), grid, PR_NT, lds_d, st, b); break;
-        case 3: hipLaunchKernelGGL((k_pair<bf16_t, true, false, PR_TQ>), grid, PR_NT, lds_d, st, b); break;
-        case 4: hipLaunchKernelGGL((k_pair<float, false, true, PR_TQ>), grid, PR_NT, lds_f, st, b); break;
-        case 5: hipLaunchKernelGGL((k_pair<bf16_t, false, true, PR_TQ>), grid, PR_NT, lds_f, st, b); break;
-        case 6: hipLaunchKernelGGL((k_pair<float, true, true, PR_TQ>), grid, PR_NT, lds_d, st, b); break;
-        default: hipLaunchKernelGGL((k_pair<bf16_t, true, true, PR_TQ>), grid, PR_NT, lds_d, st, b); break;
-    }
-    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------

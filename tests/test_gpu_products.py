@@ -70,3 +70,38 @@ def test_product_with_a_transposed_matrix_along_a_long_mode(r2, cout):
     xr = _modes(S, [u.t().contiguous() for u in U])
     want = torch.nn.grad.conv2d_weight(xr.cpu(), dW.shape, gy.double().cpu(), padding=1).cuda()
     assert float((dW - want).abs().max() / want.abs().max()) <= 5e-6
+
+
+# (mode): rows short of and past a tile of 64, ranks of one to four blocks of 16 and of two tiles, columns short of a block of 16, of a
+# chunk of 64 and past several, inner extents of 1, odd, a multiple of four above and below a chunk; the activation one element off.
+@pytest.mark.parametrize("dims,ranks,mode", [
+    ((3, 65, 1, 7), (3, 15, 1, 7), 1), ((9, 127, 3, 5), (9, 16, 3, 5), 1), ((40, 130, 7, 7), (20, 33, 5, 5), 1), ((5, 513, 9, 11), (5, 48, 5, 5), 1),
+    ((6, 515, 2, 2), (6, 24, 2, 2), 1), ((4, 640, 4, 8), (4, 49, 4, 4), 1), ((3, 600, 6, 12), (3, 70, 6, 12), 1), ((2, 100, 9, 80), (2, 17, 5, 9), 1),
+    ((3, 35, 514), (3, 20, 50), 2), ((2, 33, 577), (2, 33, 17), 2), ((4, 1100, 66), (4, 64, 31), 1)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_pair_product_at_the_edges_of_its_tiles(dims, ranks, mode, dtype, shift):
+    """The factor of a mode that goes through V and P, against float64.  P's condition is that of random data, 5 to 340; V is fp32,
+    2^-24 of its entries, which the condition (below 500) takes to 3e-5 of the factor's largest entry.  bf16 last modes cut U_prev in two bf16 terms: 2^-17 of its
+    entries, 2e-4."""
+    from paper_2505_05086_amd import binding as B
+    rng = np.random.default_rng(sum(dims) + sum(ranks) + shift)
+    numel = int(np.prod(dims))
+    flat = _dev(rng.standard_normal(numel + 1), dtype)
+    x = flat[shift:shift + numel].view(dims)
+    U = [_dev(np.linalg.qr(rng.standard_normal((n, r)))[0]) for n, r in zip(dims, ranks)]
+    out = [torch.full_like(u, float("nan")) for u in U]
+    desc = B.make_desc(dims, ranks, dtype)
+    info = torch.full((1,), 7, dtype=torch.int32, device="cuda")
+    ws = B.alloc_workspace(desc, None, 0)
+    ws.fill_(255)
+    sites = _sites(lambda: B.asi_compress(desc, x, U, out, ws, info))
+    assert any("k_pair" in s for s in sites), sites
+    assert int(info) == 0
+    a = x.double().movedim(mode, 0).reshape(dims[mode], -1)
+    p = a @ (a.t().contiguous() @ U[mode].double())
+    q, r = torch.linalg.qr(p)
+    want = q * torch.sign(torch.diagonal(r))
+    assert float(torch.linalg.cond(p)) < 500
+    err = float((out[mode] - want).abs().max() / want.abs().max())
+    assert err <= (2e-4 if dtype == "bf16" and mode == len(dims) - 1 else 3e-5), err
