@@ -84,7 +84,6 @@ struct CompressPlan {
     double* Gsum[4] = {};           // wide path, many slices: the slice Grams added up by a tree level
     int ngsum[4] = {};
     double* R[4] = {};
-    double* Rinv[4] = {};
     double* Dinv[4] = {};
     double* scal[4] = {};
     int32_t* ctr8 = nullptr;         // arrival counters, kOrthCtrs per mode
@@ -103,7 +102,7 @@ struct CompressPlan {
     double* vscale = nullptr;
     bool fast_orth[4] = {};
     bool wide_orth[4] = {};
-    size_t bytes = 0;
+    size_t bytes = 0, pair_bytes = 0;    // ... of the partial sums of pair products
 };
 
 // Which modes of a bf16 tensor take the int8 MFMA.  It costs a pass over the tensor for its largest magnitude and saves time that
@@ -191,22 +190,21 @@ CompressPlan plan_with(const Shape& s, void* ws, bool cold, bool digits, bool co
         else if (p.longm[m]) p.nsplit[m] = subspace_long_splits(s.outer(m), (int)n, s.inner(m), (int)r);
         else p.nsplit[m] = p.fused[m] ? subspace_small_nwg(s.outer(m), (int)n, s.inner(m))
                                       : pair_splits(s.outer(m), (int)n, s.inner(m), (int)r, coarse);
+        const size_t before = c.off;
         p.part[m] = c.take<double>((size_t)p.nsplit[m] * n * r);
         if (p.nsplit[m] > 32) {
             p.nsplit2[m] = (p.nsplit[m] + 31) / 32;
             p.part2[m] = c.take<double>((size_t)p.nsplit2[m] * n * r);
         }
+        if (!p.fused[m] && !p.longm[m] && !(p.paired && m >= 2)) p.pair_bytes += c.off - before;
         p.fast_orth[m] = orth_fast_supported((int)r);
         // gram0 leaves the sum in the place of the first of the partial sums that it adds up: a workgroup has read all of its
         // rows before it writes them, and no other reads those rows.  Pays for the Gram matrices of 16-row slices, so that no
         // layer needs more scratch for them.
         p.P64[m] = !p.fast_orth[m] ? c.take<double>(n * r) : p.part2[m] ? p.part2[m] : p.part[m];
         if (p.fast_orth[m]) {
-            p.nblk[m] = orth_slices((int)n);
-            p.Gpart[m] = c.take<double>((size_t)(orth_gram_slices((int)n) + orth_groups((int)n)) * r * (r + 1) / 2);
-            p.R[m] = c.take<double>(r * r);
-            p.Rinv[m] = c.take<double>(orth_rinv_elems((int)r));
-            p.Dinv[m] = c.take<double>(((r + 15) / 16) * 256);
+            p.nblk[m] = orth_apply_wgs((int)n);
+            p.Gpart[m] = c.take<double>((size_t)orth_gram_mats((int)n) * r * (r + 1) / 2);
             p.scal[m] = c.take<double>(68);
         } else if (orth_wide_supported((int)r)) {
             p.wide_orth[m] = true;
@@ -232,7 +230,7 @@ CompressPlan plan_with(const Shape& s, void* ws, bool cold, bool digits, bool co
 // The plan of a call.  Where only the partial sums of the pair products keep a layer out of the static scratch, they are fewer.
 CompressPlan plan_compress(const Shape& s, void* ws, bool cold = false, bool digits = false) {
     CompressPlan p = plan_with(s, ws, cold, digits, false);
-    if (p.bytes > (size_t)ASI_STATIC_SCRATCH_BYTES) {
+    if (p.bytes > (size_t)ASI_STATIC_SCRATCH_BYTES && p.bytes - p.pair_bytes < (size_t)ASI_STATIC_SCRATCH_BYTES) {
         const CompressPlan q = plan_with(s, ws, cold, digits, true);
         if (q.bytes <= (size_t)ASI_STATIC_SCRATCH_BYTES) return q;
     }
@@ -684,9 +682,9 @@ asi_status build_compress(const asi_tensor_desc* desc, const void* A, const floa
         j.part = p.part[m]; j.nsplit = p.nsplit[m]; j.n = n; j.r = r;
         if (p.part2[m]) { j.part = p.part2[m]; j.nsplit = p.nsplit2[m]; }     // the tree's first level has run
         j.P64 = p.P64[m]; j.Uout = U_out[m]; j.mode1 = m + 1; j.info = info;
-        j.nblk = p.nblk[m]; j.Gpart = p.Gpart[m]; j.R = p.R[m]; j.Rinv = p.Rinv[m]; j.Dinv = p.Dinv[m]; j.scal = p.scal[m];
+        j.nblk = p.nblk[m]; j.Gpart = p.Gpart[m]; j.R = p.R[m]; j.Dinv = p.Dinv[m]; j.scal = p.scal[m];
         j.ctr = p.ctr8 + kOrthCtrs * m;
-        if (p.fast_orth[m]) j.gsz = orth_group_size(n);
+        if (p.fast_orth[m]) { j.gsz = orth_group_size(n); j.spw = orth_apply_slices(n); }
         if (p.wide_orth[m] && p.Gsum[m]) {
             GsumJob& gj = gsum.job[gsum.njobs++];
             gj.in = p.Gpart[m]; gj.out = p.Gsum[m]; gj.nblk = p.nblk[m]; gj.r = r;
@@ -714,8 +712,8 @@ asi_status build_compress(const asi_tensor_desc* desc, const void* A, const floa
     if (fast.njobs) {
         // Orthogonalize: Cholesky-QR (with a diagonal shift if the plain factorisation loses a pivot),
         // then a second Cholesky-QR pass unless the first result is orthonormal to 1e-7 already.
-        // Each launch ends with the factorisation of its Gram matrices in the last workgroup of a
-        // mode; the second pass, when needed, is carried out by that workgroup too.
+        // Every workgroup of the second launch factors its mode's Gram matrix for itself; the second pass, when needed, is
+        // carried out by the one that finishes the mode's last slice.
         ASI_ADD(pg, "", fast_b + chol_b, fast_f + chol_f, make_orth_gram0(fast, it__));
         ASI_ADD(pg, "", 2.5 * fast_b + chol_b, 2 * fast_f + chol_f, make_orth_apply(fast, it__));
     }

@@ -280,17 +280,17 @@ struct OrthJob {
     float* Uout;         // (n, r)
     int32_t* info;       // nullable
     // fast path (r <= 64) and wide path
-    double* Gpart;       // fast path: (orth_gram_slices(n) + groups of them, r (r+1) / 2) packed Gram matrices; slow path: (r, r)
-    double* R;           // (r, r)
-    double* Rinv;        // fast path: blocks of R^-1 on and above the diagonal, orth_rinv_elems(r) elements
-    double* Dinv;        // (ceil(r/16), 16, 16) inverses of R's diagonal blocks
+    double* Gpart;       // fast path: (orth_gram_mats(n), r (r+1) / 2) packed Gram matrices; slow path: (r, r)
+    double* R;           // wide path: (r, r)
+    double* Dinv;        // wide path: (ceil(r/16), 16, 16) inverses of R's diagonal blocks
     double* scal;        // 68 doubles of bookkeeping (wide path: 2 + 192)
     int32_t* ctr;        // 2 + kOrthGroups arrival counters, zero before the first orth launch of a call
     int nsplit;
     int n, r;
     int mode1;           // 1-based mode number for *info
-    int nblk;            // row slices = orth_slices(n) (wide path: orth_wide_gram_blocks(n))
+    int nblk;            // fast path: workgroups of apply = orth_apply_wgs(n); wide path: orth_wide_gram_blocks(n)
     int gsz;             // fast path: slices of gram0 per group
+    int spw;             // fast path: slices of apply per workgroup
     unsigned long long* devbits;   // wide path with a summed Gram matrix (make_orthw_gsum): bits of max |G - I|; else null
 };
 struct OrthArgs {        // the modes of one tensor that share a path
@@ -313,14 +313,17 @@ struct GsumArgs {
 };
 bool make_orthw_gsum(const GsumArgs& a, Item* out);
 bool orth_fast_supported(int r);
-inline size_t orth_rinv_elems(int r) { const size_t nb = (size_t)(r + 15) / 16; return nb * (nb + 1) / 2 * 256; }
 int orth_slices(int n);
 int orth_gram_slices(int n);
 int orth_group_size(int n);
 inline int orth_groups(int n) { return (orth_gram_slices(n) + orth_group_size(n) - 1) / orth_group_size(n); }
-// gram0: sums the partial sums of P, slice Grams; the last workgroup of a mode factors (shifted if need be), inverts the
-//        factor, certifies the first pass where it can, and clears *info.
-// apply: U = P R^-1; where the first pass is not certified, slice Grams of the result and, if they say so, a second pass.
+int orth_apply_slices(int n);
+inline int orth_apply_wgs(int n) { return (orth_slices(n) + orth_apply_slices(n) - 1) / orth_apply_slices(n); }
+// gram0's slices, then their groups, or for a single group the second pass's
+inline int orth_gram_mats(int n) { return orth_gram_slices(n) + (orth_groups(n) > 1 ? orth_groups(n) : orth_apply_wgs(n)); }
+// gram0: sums the partial sums of P, slice Grams, groups of them; clears *info.
+// apply: every workgroup factors (shifted if need be), inverts the factor and certifies the first pass where it can; U = P R^-1; where
+//        it is not certified, slice Grams of the result and, if they say so, a second pass.
 bool make_orth_gram0(const OrthArgs& a, Item* out);
 bool make_orth_apply(const OrthArgs& a, Item* out);
 // wide path, 64 < r <= 192: nblk = orth_wide_gram_blocks(n), scal holds 2 + 192 doubles,

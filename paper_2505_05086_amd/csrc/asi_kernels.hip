@@ -309,34 +309,35 @@ __global__ __launch_bounds__(PR_NT, 4) void k_pair_vec(Batch<PairJob> bt) {
 // the last product; then the partial sums, written and read once at some 1.6 KB a cycle, a round trip for every 16 (32 up to rank
 // 32) that gram0 adds up together, and beyond 32 of them a level of the partial-sum tree (one more launch on the chain).
 // Three 512 x 48 layers of 3136 columns: 10 | 13 | 17 | 25 | 32 splits 26.8 | 23.4 | 19.8 | 23.7 | 27.1 us, gram0 25.2 up to 16, then 27.4.
-struct PairPlan { int tq, ns; };
 static long long pair_cols_per_split(long long ncols, int nsplit) {
     const long long cps = (ncols + nsplit - 1) / nsplit;
     return (cps + 15) / 16 * 16;
 }
-static PairPlan pair_plan(long long ncols, long long inner, int n, int r, int most) {
-    const int blocks = (r + 15) / 16, gy = (blocks + 3) / 4;
-    int nbq = (blocks + gy - 1) / gy;
-    if (inner == 1 && gy == 1 && nbq == 3) nbq = 4;
-    const long long tiles = (long long)((n + PR_TI - 1) / PR_TI) * gy;
+static int pair_tq(long long inner, int r) {
+    const int blocks = (r + 15) / 16, gy = (blocks + 3) / 4, nbq = (blocks + gy - 1) / gy;
+    return inner == 1 && gy == 1 && nbq == 3 ? 64 : 16 * nbq;
+}
+static int pair_best_splits(long long ncols, long long inner, int n, int r) {
+    const int tq = pair_tq(inner, r), lot = r > 32 ? 16 : 32;
+    const long long tiles = (long long)((n + PR_TI - 1) / PR_TI) * ((r + tq - 1) / tq);
+    const double block = 308.0 * (tq / 16) + 88.0, partial = (double)n * r * (16.0 / 1600.0);
     long long maxs = (ncols + 127) / 128;                     // at least 128 columns per split
-    maxs = maxs > most ? most : (maxs < 1 ? 1 : maxs);
-    const int lot = r > 32 ? 16 : 32;
+    maxs = maxs > 64 ? 64 : (maxs < 1 ? 1 : maxs);
     int best = 1;
     double best_cost = -1.0;
-    for (int ns = 1; ns <= (int)maxs; ++ns) {
+    for (int ns = 1; ns <= (int)maxs; ns += ns < 16 ? 1 : 2) {
         const long long cps = pair_cols_per_split(ncols, ns);
         if (ns > 1 && cps * (ns - 1) >= ncols) continue;      // the last split would be empty
-        const double per_cu = (double)((tiles * ns + 255) / 256);
-        const double cost = per_cu * cps / 16.0 * (308.0 * nbq + 88.0) + (per_cu > 1.0 ? 2.0 : 1.0) * 8000.0 + ns * (double)n * r * 16.0 / 1600.0 +
-                            (ns + lot - 1) / lot * 4800.0 + (ns > 32 ? 10000.0 : 0.0);
+        const long long per_cu = (tiles * ns + 255) >> 8;
+        const double cost = (double)(per_cu * (cps >> 4)) * block + (per_cu > 1 ? 16000.0 : 8000.0) + ns * partial +
+                            (ns <= lot ? 4800.0 : (ns <= 2 * lot ? 9600.0 : 19200.0)) + (ns > 32 ? 10000.0 : 0.0);
         if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = ns; }
     }
-    return {16 * nbq, best};
+    return best;
 }
 int pair_splits(long long outer, int n, long long inner, int r, bool coarse) {
     const long long ncols = outer * inner;
-    if (!coarse) return pair_plan(ncols, inner, n, r, 64).ns;
+    if (!coarse) return pair_best_splits(ncols, inner, n, r);
     // the least rounds x (columns of a split, in chunks, + 128) of 512 workgroups of 64 x 32 (64 along the last mode), 256 columns or more a split
     const int tq = (inner == 1 && r > 32 && ncols >= 4096) ? 64 : 32;
     const long long tiles = (long long)((n + PR_TI - 1) / PR_TI) * ((r + tq - 1) / tq);
@@ -377,7 +378,7 @@ static bool make_pair_any(DType xt, const void* X, long long outer, int n, long 
     jb.X = X; jb.outer = outer; jb.inner = inner; jb.cols_per_split = pair_cols_per_split(ncols, nsplit);
     jb.Y = gen ? nullptr : Y; jb.part = part; jb.n = n; jb.r = r;
     jb.seed_lo = (uint32_t)(seed & 0xffffffffu); jb.seed_hi = (uint32_t)(seed >> 32); jb.mode = mode;
-    const int tq = pair_plan(ncols, inner, n, r, nsplit).tq;
+    const int tq = pair_tq(inner, r);
     jb.gx = (n + PR_TI - 1) / PR_TI; jb.gy = (r + tq - 1) / tq; jb.gz = nsplit;
     jb.zero = zero; jb.nzero = zero ? nzero : 0;
     if (pre) {

@@ -11,23 +11,22 @@
 // are projected out; a column keeping less than 1e-12 ||P||_F is reported through *info.
 //
 // Fast path (r <= 64), two launches that serve all modes of a tensor at once:
-//   gram0 : row slices of 32 rows sum the split partial sums of P -> P64 and write their slice Gram
-//           (fp64 MFMA); the workgroup that arrives last at the mode's counter sums the slice Grams and
-//           factors: blocked Cholesky in LDS without a shift, with the shift only if a pivot is lost.
-//           It then inverts R and bounds what one pass leaves of |Q^T Q - I|: with X = R^-1 and
+//   gram0 : row slices of 16 rows sum the split partial sums of P -> P64 and write their slice Gram (fp64 MFMA); of a mode of more than
+//           12 slices, groups of them are added by the workgroup of the group that arrives last.
+//   apply : EVERY workgroup adds the matrices up and factors the sum: Cholesky in the registers of one wave without a shift,
+//           with the shift only if a pivot is lost.  It then inverts R and bounds what one pass leaves of |Q^T Q - I|: with X = R^-1 and
 //           c = max_j sum_i sqrt(G_ii) |X_ij|  (the column-scaled condition number), rounding of G, of the factor and of
 //           the products gives  |Q^T Q - I| <= u ((18 + slices of a group + groups + 2 r) c^2 + 4 r c).  Below OP_DONE_TOL
 //           (c up to about 2000) the first pass is certified: always where the basis has settled (c 1..300), and on
 //           activations that move a little every step for most modes, but not for long modes of steep spectra (256 to 960
 //           channels: c 1000 to 9000), although what one pass leaves there is 4e-9.
-//   apply : certified: Q = P X, a wave per 16 x 16 block of Q, all its operands in one round of loads; nothing else.
-//           Otherwise: Q0 = P R^-1 by block forward substitution (fp64 MFMA), written in fp64 and as
-//           the fp32 result, plus the slice Gram of Q0; the last-arriving workgroup measures
-//           |Q0^T Q0 - I| and only if that exceeds OP_DONE_TOL runs the second pass by itself
-// The two launches are a chain of dependent round trips to memory and of pivots; 512 threads keep up to 48 loads each in
-// flight.  960 x 40 (30 slices) and three short modes: gram0 30.9 -> 27.2, apply 21.0 -> 4.7 us certified; measuring the result
-// instead of certifying it (slice Grams, hand-over, sum, comparison) was half of apply, and still is where the certificate is
-// refused (bracketed by events, on activations whose factors move by 2 % a step: 6.2 certified, 22.8 refused, 23.0 before).
+//           Certified: Q = P X, X still in registers.  Otherwise: Q0 = P R^-1 by block forward substitution (fp64 MFMA), written in
+//           fp64 and as the fp32 result, plus the slice Gram of Q0; the last-arriving workgroup measures |Q0^T Q0 - I| and only if
+//           that exceeds OP_DONE_TOL runs the second pass by itself.
+// The two launches are a chain of dependent round trips to memory and of pivots.  960 x 40 (60 slices) and three short modes: 24.6 + 4.8
+// us with the factorisation in the workgroup of gram0 that arrived last, 8.6 + 16.0 so; 256 x 32 21.8 + 3.9 -> 8.5 + 12.3, 32 x 8
+// 14.1 + 4.0 -> 6.0 + 7.2.  Of the 14.6 us inside apply for 960 x 40: 1.7 kernel start and arguments, 1.5 the matrices, 0.8 to LDS, 6.0
+// factor (ten panels of four pivots), 2.5 inverse, 1.4 product and the rest.
 // Wide path (64 < r <= 192): separate Gram / Cholesky / apply launches on the packed triangle.
 // Slow path (r > 192): one workgroup per mode, everything in global memory.
 #include "asi_device.h"
@@ -45,6 +44,7 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 constexpr int OP_RS = 32;              // rows per slice of apply
 constexpr int OP_GS = 16;              // rows per slice of gram0
 constexpr int OP_RMAX = 64;
+constexpr int OP_ONE_GROUP = 12;       // slices of gram0 that apply adds up itself (16: 3 us dearer there, 2.7 cheaper in gram0)
 constexpr int OP_LD = OP_RMAX + 1;
 constexpr double OP_EPS = 1.1102230246251565e-16;
 constexpr int OP_NT = 512, OP_NW = OP_NT / 64;
@@ -88,26 +88,42 @@ __device__ __forceinline__ double published(const double* p, long long idx, bool
     return ok ? v : 0.0;
 }
 
-// Gram of the ROWS rows held in Ps (zero padded to 64 columns) -> packed upper triangle Gout (r (r+1) / 2)
+// Gram of the ROWS rows held in Ps (zero padded to 64 columns), added to the wave's block pairs in acc: pair `wave` and, beyond eight
+// of them, pair `wave + 8` of the blocks on and above the diagonal, row by row
+constexpr int OP_PAIRS = 2;
+__device__ __forceinline__ void wave_pair(int nb, int pr, int* ab, int* bb) {
+    int i = 0, rem = pr;
+    while (i < nb && rem >= nb - i) { rem -= nb - i; ++i; }
+    *ab = i; *bb = i + rem;                                  // ab == nb: no such pair
+}
 template <int ROWS>
-__device__ void gram_from_lds(const double (*Ps)[OP_LD], int r, double* Gout) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lg = lane >> 4, ll = lane & 15;
-    const int nb = (r + 15) / 16, npairs = nb * (nb + 1) / 2;
-    const int nwaves = blockDim.x >> 6;
-    for (int pr = wave; pr < npairs; pr += nwaves) {
-        int ab = 0, rem = pr;
-        while (rem >= nb - ab) { rem -= nb - ab; ++ab; }
-        const int bb = ab + rem;
-        v4d acc = {0.0, 0.0, 0.0, 0.0};
+__device__ __forceinline__ void gram_add(const double (*Ps)[OP_LD], int r, v4d (&acc)[OP_PAIRS]) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lg = lane >> 4, ll = lane & 15;
+    const int nb = (r + 15) / 16;
 #pragma unroll
-        for (int ks = 0; ks < ROWS / 4; ++ks)
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(Ps[4 * ks + lg][16 * ab + ll], Ps[4 * ks + lg][16 * bb + ll], acc,
-                                                       0, 0, 0);
+    for (int s = 0; s < OP_PAIRS; ++s) {
+        int ab, bb;
+        wave_pair(nb, wave + OP_NW * s, &ab, &bb);
+        if (ab < nb)                                         // uniform
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int ga = 16 * ab + lg + 4 * v, gb = 16 * bb + ll;
-            if (ga < r && gb < r && ga <= gb) publish(Gout + tri_idx(r, ga, gb), acc[v]);
-        }
+            for (int ks = 0; ks < ROWS / 4; ++ks)
+                acc[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(Ps[4 * ks + lg][16 * ab + ll], Ps[4 * ks + lg][16 * bb + ll], acc[s], 0, 0, 0);
+    }
+}
+// -> packed upper triangle Gout (r (r+1) / 2)
+__device__ __forceinline__ void gram_publish(const v4d (&acc)[OP_PAIRS], int r, double* Gout) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lg = lane >> 4, ll = lane & 15;
+    const int nb = (r + 15) / 16;
+#pragma unroll
+    for (int s = 0; s < OP_PAIRS; ++s) {
+        int ab, bb;
+        wave_pair(nb, wave + OP_NW * s, &ab, &bb);
+        if (ab < nb)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int ga = 16 * ab + lg + 4 * v, gb = 16 * bb + ll;
+                if (ga < r && gb < r && ga <= gb) publish(Gout + tri_idx(r, ga, gb), acc[s][v]);
+            }
     }
 }
 
@@ -156,7 +172,7 @@ struct GramPacked {                      // row-wise packed upper triangle of an
 // Rows are left unscaled: row k holds R[k][j] * R[k][k], the diagonal the pivots R[k][k]^2.
 // A non-positive pivot is replaced (by a number in [1, 2)) and reported through `bad` (1-based index, first one wins).
 struct Panel4 {
-    double li;           // lane (lg, ll): element [ll][lg] of L4^-1 (zero for ll > 3)
+    double li;           // lane (lg, ll): element [ll mod 4][lg] of L4^-1
     double pl;           // 1 / q of row lg of the panel
 };
 // g: the panel's register of the diagonal block; p: the panel's number in the block; col1: 1-based index of its first pivot
@@ -192,18 +208,21 @@ __device__ __forceinline__ Panel4 factor_panel(double g, int p, int col1, int lg
     // (pinned: left alone the compiler turns the selects into a ladder of branches around the arithmetic)
     asm volatile("" : "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(pi[0]), "+v"(pi[1]), "+v"(pi[2]), "+v"(pi[3]));
     Panel4 o;
-    o.li = ll == 0 ? x[0] : (ll == 1 ? x[1] : (ll == 2 ? x[2] : (ll == 3 ? x[3] : 0.0)));
-    o.pl = lg == 0 ? pi[0] : (lg == 1 ? pi[1] : (lg == 2 ? pi[2] : pi[3]));
+    o.li = (ll & 2) ? ((ll & 1) ? x[3] : x[2]) : ((ll & 1) ? x[1] : x[0]);
+    o.pl = (lg & 2) ? ((lg & 1) ? pi[3] : pi[2]) : ((lg & 1) ? pi[1] : pi[0]);
     return o;
 }
 __device__ __forceinline__ v4d mfma64(double a, double b, v4d c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+// L4^-1 times four rows of 16: four 4 x 4 x 4 blocks in one instruction, operands and result in the layout of a panel (lane 16 k + 4 block
+// + i holds element [i][k] of the left operand).  A dependent one takes 33 cycles where the 16 x 16 x 4 form, three quarters of
+// it zeros, takes 80.
+__device__ __forceinline__ double panel_rows(double li, double g) { return __builtin_amdgcn_mfma_f64_4x4x4f64(li, g, 0.0, 0, 0, 0); }
 
 // One diagonal block of a matrix in LDS behind an accessor (wide ranks): U in place, pinvs[base+k] the pivots' reciprocals,
 // Xb[i][j] = (L^-1)[j][i].
 template <class GA>
 __device__ void chol_block16(const GA G, double (*Xb)[17], double* pinvs, int base, int* bad_io) {
     const int lane = threadIdx.x & 63, lg = lane >> 4, ll = lane & 15;
-    const v4d zero = {0.0, 0.0, 0.0, 0.0};
     v4d g, x;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
@@ -215,7 +234,7 @@ __device__ void chol_block16(const GA G, double (*Xb)[17], double* pinvs, int ba
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
         const Panel4 f = factor_panel(g[p], p, base + 4 * p + 1, lg, ll, &bad);
-        const double w = mfma64(f.li, g[p], zero)[0], wx = mfma64(f.li, x[p], zero)[0];
+        const double w = panel_rows(f.li, g[p]), wx = panel_rows(f.li, x[p]);
         if (p < 3) {
             const v4d gn = mfma64(-w, w * f.pl, g), xn = mfma64(-w, wx * f.pl, x);
 #pragma unroll
@@ -236,12 +255,14 @@ __device__ void chol_block16(const GA G, double (*Xb)[17], double* pinvs, int ba
 
 // A matrix of nb <= NB blocks a side (r <= 64), whole, in the registers of the wave: no LDS round trip and no barrier between
 // panels.  In: Gs (symmetric, identity beyond r); out: U in the upper blocks of Gs, Xs[b][i][j] = (L_bb^-1)[j][i].
-// Per panel the chain is fetch, four reciprocals, two products (~700 cycles); the products of the other blocks fill its gaps.
-// 48 columns: 9.5 us as blocks of 16 with the block row and the trailing blocks dealt to all waves behind barriers, 7.6 so.
+// Per panel the chain is fetch, four reciprocals, two products; pivots left unchecked (the test and the replacement out of the chain)
+// change nothing.
+// 48 columns: 9.5 us as blocks of 16 with the block row and the trailing blocks dealt to all waves behind barriers, 7.6 so, 6.8 with the
+// panel's rows multiplied in 4 x 4 blocks.  Panels wholly beyond r are rows of the identity and are skipped (40 columns: 6.0).
 template <int NB>
-__device__ __forceinline__ void chol_wave(double (*Gs)[OP_LD], double (*Xs)[16][17], int nb, int* bad_io) {
+__device__ __forceinline__ void chol_wave(double (*Gs)[OP_LD], double (*Xs)[16][17], int r, int* bad_io) {
     const int lane = threadIdx.x & 63, lg = lane >> 4, ll = lane & 15;
-    const v4d zero = {0.0, 0.0, 0.0, 0.0};
+    const int nb = (r + 15) / 16;
     v4d g[NB][NB];
 #pragma unroll
     for (int I = 0; I < NB; ++I)
@@ -258,9 +279,10 @@ __device__ __forceinline__ void chol_wave(double (*Gs)[OP_LD], double (*Xs)[16][
             for (int v = 0; v < 4; ++v) x[v] = 4 * v + lg == ll ? 1.0 : 0.0;
 #pragma unroll
             for (int p = 0; p < 4; ++p) {
+                if (p > 0 && 16 * b + 4 * p >= r) continue;      // uniform: rows of the identity
                 const Panel4 f = factor_panel(g[b][b][p], p, 16 * b + 4 * p + 1, lg, ll, &bad);
                 double w[NB], mw[NB];
-                w[b] = mfma64(f.li, g[b][b][p], zero)[0];
+                w[b] = panel_rows(f.li, g[b][b][p]);
                 mw[b] = w[b] * f.pl;
                 if (p < 3) {
                     const v4d gn = mfma64(-w[b], mw[b], g[b][b]);
@@ -268,7 +290,7 @@ __device__ __forceinline__ void chol_wave(double (*Gs)[OP_LD], double (*Xs)[16][
                     for (int v = p + 1; v < 4; ++v) g[b][b][v] = gn[v];
                 }
                 g[b][b][p] = w[b];
-                const double wx = mfma64(f.li, x[p], zero)[0];
+                const double wx = panel_rows(f.li, x[p]);
                 if (p < 3) {
                     const v4d xn = mfma64(-w[b], wx * f.pl, x);
 #pragma unroll
@@ -277,7 +299,7 @@ __device__ __forceinline__ void chol_wave(double (*Gs)[OP_LD], double (*Xs)[16][
                 x[p] = wx;
 #pragma unroll
                 for (int J = b + 1; J < NB; ++J) {
-                    w[J] = mfma64(f.li, g[b][J][p], zero)[0];
+                    w[J] = panel_rows(f.li, g[b][J][p]);
                     mw[J] = w[J] * f.pl;
                     if (p < 3) {
                         const v4d gn = mfma64(-w[b], mw[J], g[b][J]);
@@ -303,32 +325,30 @@ __device__ __forceinline__ void chol_wave(double (*Gs)[OP_LD], double (*Xs)[16][
     *bad_io = bad;
 }
 
-// One workgroup: sums the slice Grams of a mode, adds the shift (first pass) and
-// factors the matrix, identity padded to a multiple of 16 (wave 0).  Writes R, the inverses of R's diagonal blocks and the
-// bookkeeping in scal; the first pass also inverts R and certifies itself where it can (see above); with `last` it reports a
-// rank-deficient P through *info.  The first pass never does: its launch clears *info, which the modes of a layer share, and
-// nothing orders one workgroup's report after another's clearing.  scal[0] = trace(P^T P), scal[1 + k] = running product of
-// the R diagonals, scal[65] = first bad pivot (certified: first column at the noise floor), scal[66] = 1 when the first
-// pass needed no second (apply's check), 2 when it is certified.
+// One workgroup: sums the Gram matrices of a mode, adds the shift (first pass) and factors the sum, identity padded to a multiple
+// of 16 (wave 0).  scal (written by the mode's workgroup that leads): [0] = trace(P^T P), [1 + k] = running product of the R
+// diagonals, [65] = first bad pivot (certified: first column at the noise floor), [66] = 2 where the first pass is certified, 1
+// where it was measured and found enough, else 0.
 struct CholSmem {
-    double Gs[OP_RMAX][OP_LD];
+    double Gs[OP_RMAX][OP_LD];       // the sum, then its factor (rows unscaled), then R
     double dinv[OP_RMAX];
     double rdiag[OP_RMAX];
     double pinvs[OP_RMAX];
     double gsq[OP_RMAX];
-    double Xs[OP_RMAX / 16][16][17];
+    double Xs[OP_RMAX / 16][16][17]; // inverses of L's diagonal blocks, then of R's
     double colmax[OP_NW];
     double s_trace;
     int s_bad;
 };
 
 // Sum of `count` packed matrices of T elements, in their order: element tid + OP_NT it in sum[it].  A round keeps up to 48
-// loads per thread in flight (a round is one dependent trip to memory).
+// loads per thread in flight (a round is one dependent trip to memory); up to eight matrices take a round of their own size, since
+// what is asked for beyond the last costs as much as the matrices themselves.  PUBLISHED: by workgroups of this launch.
 template <int RM>
 constexpr int packed_its() { return (RM * (RM + 1) / 2 + OP_NT - 1) / OP_NT; }
-template <int RM>
-__device__ __forceinline__ void sum_packed(const double* src, int count, int T, double (&sum)[packed_its<RM>()]) {
-    constexpr int ITS = packed_its<RM>(), SB = 48 / ITS > 24 ? 24 : 48 / ITS;
+template <int RM, bool PUBLISHED, int SB>
+__device__ __forceinline__ void sum_packed_by(const double* src, int count, int T, double (&sum)[packed_its<RM>()]) {
+    constexpr int ITS = packed_its<RM>();
     const int tid = threadIdx.x;
 #pragma unroll
     for (int it = 0; it < ITS; ++it) sum[it] = 0.0;
@@ -339,8 +359,10 @@ __device__ __forceinline__ void sum_packed(const double* src, int count, int T, 
         for (int u = 0; u < SB; ++u) {
             const double* m = src + (long long)(b0 + u < count ? b0 + u : count - 1) * T;       // uniform
 #pragma unroll
-            for (int it = 0; it < ITS; ++it)
-                t[u][it] = published(m, (unsigned)(tid + OP_NT * it < T ? tid + OP_NT * it : 0), true);
+            for (int it = 0; it < ITS; ++it) {
+                const unsigned e = tid + OP_NT * it < T ? tid + OP_NT * it : 0;
+                t[u][it] = PUBLISHED ? published(m, e, true) : m[e];
+            }
         }
 #pragma unroll
         for (int u = 0; u < SB; ++u)
@@ -348,57 +370,61 @@ __device__ __forceinline__ void sum_packed(const double* src, int count, int T, 
             for (int it = 0; it < ITS; ++it) sum[it] += b0 + u < count ? t[u][it] : 0.0;
     }
 }
+template <int RM, bool PUBLISHED>
+__device__ __forceinline__ void sum_packed(const double* src, int count, int T, double (&sum)[packed_its<RM>()]) {
+    constexpr int ITS = packed_its<RM>(), SB = 48 / ITS > 24 ? 24 : 48 / ITS;
+    if (SB > 8 && count <= 8) sum_packed_by<RM, PUBLISHED, 8>(src, count, T, sum);
+    else sum_packed_by<RM, PUBLISHED, SB>(src, count, T, sum);
+}
 
-// slices, nslices: the packed matrices whose sum is factored (groups of slices in the first pass, slices in the second)
-template <int RM>
-__device__ bool chol_job(const OrthJob& jb, int pass, int last, const double* slices, int nslices, int32_t* info, CholSmem& sm) {
+// Factors the sum of the nslices matrices.  First pass: PASS 0; lead: writes scal.  Second pass (one workgroup of the mode): false
+// where the first was enough.  Leaves in sm: the factor in Gs, 1 / R_kk in dinv, R_kk in pinvs, the running products in rdiag, the square
+// roots of the diagonal before elimination in gsq.
+template <int RM, int PASS>
+__device__ __forceinline__ bool chol_factor(const OrthJob& jb, bool lead, const double* slices, int nslices, int32_t* info, CholSmem& sm, bool* shifted_out) {
     double (*Gs)[OP_LD] = sm.Gs;
-    double* dinv = sm.dinv;
     double* rdiag = sm.rdiag;
-    double* pinvs = sm.pinvs;
-    double* gsq = sm.gsq;
-    double (*Xs)[16][17] = sm.Xs;
-    double& s_trace = sm.s_trace;
-    int& s_bad = sm.s_bad;
     const int n = jb.n, r = jb.r, tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6, lg = lane >> 4, ll = lane & 15;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nb = (r + 15) / 16;
-    // sum of the slice Grams (packed upper triangles); IA elements per thread
     constexpr int ITS = packed_its<RM>();
     const int T = (r * (r + 1)) / 2;
     double sum[ITS];
     // where the thread's elements lie in the matrix (worked out while the loads are on their way): row ga of the packed
     // triangle is the largest with tri_idx(r, ga, ga) <= e; the square root is off by one at most
-    int gpos[ITS];
-    auto decode = [&](int e) __attribute__((always_inline)) {
+    int grow[ITS], gcol[ITS];
+#pragma unroll
+    for (int it = 0; it < ITS; ++it) {
+        const int e = tid + OP_NT * it < T ? tid + OP_NT * it : 0;
         const float d = (float)(2 * r + 1);
         int ga = (int)((d - sqrtf(d * d - 8.0f * (float)e)) * 0.5f);
         ga = ga < 0 ? 0 : (ga > r - 1 ? r - 1 : ga);
         ga += (ga + 1 < r && tri_idx(r, ga + 1, ga + 1) <= e) ? 1 : 0;
         ga -= tri_idx(r, ga, ga) > e ? 1 : 0;
-        return ga * OP_LD + ga + (e - tri_idx(r, ga, ga));
-    };
-#pragma unroll
-    for (int it = 0; it < ITS; ++it) gpos[it] = tid + OP_NT * it < T ? decode(tid + OP_NT * it) : 0;
-    sum_packed<RM>(slices, nslices, T, sum);
+        grow[it] = ga; gcol[it] = ga + (e - tri_idx(r, ga, ga));
+    }
+    sum_packed<RM, PASS == 1>(slices, nslices, T, sum);
     // Gs = the summed Gram matrix, padded with the identity up to a multiple of 16
-    auto scatter = [&]() {
+    auto scatter = [&]() __attribute__((always_inline)) {
         __syncthreads();
-        for (int e = tid; e < OP_RMAX * 64; e += OP_NT) Gs[e >> 6][e & 63] = ((e >> 6) == (e & 63)) ? 1.0 : 0.0;
-        __syncthreads();
+        const int pad = 16 * nb - r;                          // rows and columns r .. 16 nb - 1
+        for (int e = tid; e < pad * 16 * nb; e += OP_NT) {
+            const int k = r + e / (16 * nb), o = e % (16 * nb);
+            Gs[k][o] = o == k ? 1.0 : 0.0;
+            Gs[o][k] = o == k ? 1.0 : 0.0;
+        }
 #pragma unroll
         for (int it = 0; it < ITS; ++it)
             if (tid + OP_NT * it < T) {
-                const int row = gpos[it] / OP_LD, col = gpos[it] - row * OP_LD;
-                Gs[row][col] = sum[it];
-                Gs[col][row] = sum[it];
+                Gs[grow[it]][gcol[it]] = sum[it];
+                Gs[gcol[it]][grow[it]] = sum[it];
             }
         __syncthreads();
     };
     scatter();
     int bad = 0;
     bool shifted = false;
-    if (pass == 1) {
+    if (PASS == 1) {
         // Q0 may already be orthonormal to working accuracy (a warm-started, well-conditioned P): then
         // the second pass would only reproduce the identity, and the fp32 copy of Q0 that the solve
         // has written is the result.
@@ -423,7 +449,7 @@ __device__ bool chol_job(const OrthJob& jb, int pass, int last, const double* sl
                 const double floor_ = 1e-12 * sqrt(jb.scal[0]);
                 const bool low = tid < r && !(jb.scal[1 + tid] > floor_);
                 const unsigned long long mask = __ballot(low);
-                if (tid == 0 && last && info) {
+                if (tid == 0 && info) {
                     const double badv = jb.scal[65];
                     if (badv != 0.0) flag_info(info, jb.mode1, (int)badv);
                     if (mask) flag_info(info, jb.mode1, __ffsll((long long)mask));
@@ -431,155 +457,139 @@ __device__ bool chol_job(const OrthJob& jb, int pass, int last, const double* sl
             }
             return false;
         }
-        if (tid == 0) s_trace = jb.scal[0];
-    } else if (wave == 0) {
+        if (tid == 0) sm.s_trace = jb.scal[0];
+    } else if (wave == 1) {                                   // (beside the factorisation, which is wave 0's)
         const double g = (lane < r) ? Gs[lane][lane] : 0.0;
         double tr = g;
 #pragma unroll
         for (int m = 32; m >= 1; m >>= 1) tr += __shfl_xor(tr, m);
-        if (lane == 0) { s_trace = tr; jb.scal[0] = tr; }
-        if (lane < r) rdiag[lane] = g;                      // the diagonal before elimination
+        if (lane == 0) { sm.s_trace = tr; if (lead) jb.scal[0] = tr; }
     }
     // First pass: plain Cholesky first; if a pivot is lost (non-positive, or below 1e-12 of its
     // diagonal entry: cond(P) beyond ~1e6) the factorisation is redone with the diagonal shift
     // that makes it safe up to cond(P) ~ 1e9.  The second pass factors once.
+    double gdiag = 0.0;                                       // wave 0: the diagonal before elimination (unshifted)
+    if (wave == 0) gdiag = lane < r ? Gs[lane][lane] : 0.0;
     for (int attempt = 0;; ++attempt) {
+        if (PASS == 0) __syncthreads();                       // (the trace's reads come before the factor's writes)
         if (wave == 0) {
-            chol_wave<RM / 16>(Gs, Xs, nb, &bad);
-            const bool lost = pass == 0 && lane < r && !(Gs[lane][lane] > 1e-12 * rdiag[lane]);
+            chol_wave<RM / 16>(Gs, sm.Xs, r, &bad);
+            const bool lost = PASS == 0 && lane < r && !(Gs[lane][lane] > 1e-12 * gdiag);
             const unsigned long long mask = __ballot(lost);
-            if (lane == 0) s_bad = (bad != 0 || mask != 0) ? 1 : 0;
+            if (lane == 0) sm.s_bad = (bad != 0 || mask != 0) ? 1 : 0;
         }
         __syncthreads();
-        if (pass != 0 || attempt != 0 || !s_bad) break;
+        if (PASS != 0 || attempt != 0 || !sm.s_bad) break;
         shifted = true;
         scatter();
-        if (tid < r) Gs[tid][tid] += 11.0 * ((double)n * r + (double)r * (r + 1)) * OP_EPS * s_trace;
-        __syncthreads();
+        if (tid < r) Gs[tid][tid] += 11.0 * ((double)n * r + (double)r * (r + 1)) * OP_EPS * sm.s_trace;
     }
     __syncthreads();
-    if (tid == 0) s_bad = bad;
-    double gdiag = 0.0;                      // the column's diagonal before elimination
+    if (tid == 0) sm.s_bad = bad;
     if (tid < r) {
         double p = Gs[tid][tid];
         if (!(p > 0.0)) p = 1.0;
         const double d = sqrt(p);
-        dinv[tid] = 1.0 / d;
-        pinvs[tid] = d;
-        gdiag = rdiag[tid];
-        const double rd = (pass == 0 ? 1.0 : jb.scal[1 + tid]) * d;
+        sm.dinv[tid] = 1.0 / d;
+        sm.pinvs[tid] = d;
+        const double rd = (PASS == 0 ? 1.0 : jb.scal[1 + tid]) * d;
         rdiag[tid] = rd;
-        jb.scal[1 + tid] = rd;
+        if (lead) jb.scal[1 + tid] = rd;
     } else if (tid < OP_RMAX) {
-        dinv[tid] = 1.0; pinvs[tid] = 1.0;
+        sm.dinv[tid] = 1.0; sm.pinvs[tid] = 1.0;
     }
-    if (tid < OP_RMAX) gsq[tid] = tid < r ? sqrt(gdiag) : 0.0;
+    if (tid < OP_RMAX) sm.gsq[tid] = tid < r ? sqrt(gdiag) : 0.0;
     __syncthreads();
-    if (pass == 0 && !shifted) {
-        // X = R^-1, wave J its block column J from the diagonal block up:  X_IJ = -X_II sum_{I < K <= J} R_IK X_KJ.  A result
-        // block (lane: rows lg + 4 v, column ll) is the B operand of the next product as it is, K slot (v, lg) being row
-        // lg + 4 v, so the chain stays in registers.  Stored in that order for apply: block (I, J) of the upper triangle at
-        // J (J + 1) / 2 + I, element [v][lane].
-        double cs = 0.0;                     // this lane's share of its column's sum_i sqrt(G_ii) |X_ij|
-        if (wave < nb) {
-            const int J = wave;
-            v4d X[RM / 16];
+    *shifted_out = shifted;
+    return true;
+}
+
+// X = R^-1, a wave its block column J = wave mod 4 from the diagonal block up:  X_IJ = -X_II sum_{I < K <= J} R_IK X_KJ.  A result
+// block (lane: rows lg + 4 v, column ll) is the B operand of the next product as it is, K slot (v, lg) being row lg + 4 v, so
+// the chain stays in registers, and so does X for the product with P.  Returns the bound on |Q^T Q - I| after one pass.
+template <int RM>
+__device__ __forceinline__ double invert(int r, int per_group, int nslices, CholSmem& sm, v4d (&X)[RM / 16]) {
+    const int tid = threadIdx.x, nb = (r + 15) / 16;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lg = lane >> 4, ll = lane & 15, J = wave & 3;
+    double cs = 0.0;                         // this lane's share of its column's sum_i sqrt(G_ii) |X_ij|
 #pragma unroll
-            for (int I = RM / 16 - 1; I >= 0; --I) {
-                if (I > J) continue;         // uniform
-                if (I == J) {
+    for (int I = 0; I < RM / 16; ++I) X[I] = (v4d){0.0, 0.0, 0.0, 0.0};
+    if (J < nb) {
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int i = lg + 4 * v;
-                        X[I][v] = (ll >= i && 16 * J + ll < r) ? Xs[I][i][ll] * dinv[16 * J + ll] : 0.0;
-                    }
-                } else {
-                    v4d acc = {0.0, 0.0, 0.0, 0.0};
-                    const double di = dinv[16 * I + ll];
-#pragma unroll
-                    for (int K = I + 1; K < RM / 16; ++K)
-                        if (K <= J)          // uniform
-#pragma unroll
-                            for (int v = 0; v < 4; ++v)
-                                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(Gs[16 * I + ll][16 * K + lg + 4 * v] * di, X[K][v], acc, 0, 0, 0);
-                    v4d o = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int k = lg + 4 * v;
-                        o = __builtin_amdgcn_mfma_f64_16x16x4f64(k >= ll ? -Xs[I][ll][k] * dinv[16 * I + k] : 0.0, acc[v], o, 0, 0, 0);
-                    }
-                    X[I] = o;
-                }
-                double* xo = jb.Rinv + (J * (J + 1) / 2 + I) * 256 + lane;
+        for (int I = RM / 16 - 1; I >= 0; --I) {
+            if (I > J) continue;             // uniform
+            if (I == J) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    xo[64 * v] = X[I][v];
-                    cs += gsq[16 * I + lg + 4 * v] * fabs(X[I][v]);
+                    const int i = lg + 4 * v;
+                    X[I][v] = (ll >= i && 16 * J + ll < r) ? sm.Xs[I][i][ll] * sm.dinv[16 * J + ll] : 0.0;
                 }
-            }
-            cs += __shfl_xor(cs, 16);
-            cs += __shfl_xor(cs, 32);
+            } else {
+                v4d acc = {0.0, 0.0, 0.0, 0.0};
+                const double di = sm.dinv[16 * I + ll];
 #pragma unroll
-            for (int m = 8; m >= 1; m >>= 1) cs = fmax(cs, __shfl_xor(cs, m));
-        }
-        if (lane == 0) sm.colmax[wave] = cs;
-        __syncthreads();
-        double c = 0.0;
+                for (int K = I + 1; K < RM / 16; ++K)
+                    if (K <= J)              // uniform
 #pragma unroll
-        for (int w = 0; w < OP_NW; ++w) c = fmax(c, sm.colmax[w]);
-        // (16 products in a chain per slice, the slices of a group, the groups; then factor, inverse and product)
-        const double bound = OP_EPS * ((18.0 + jb.gsz + nslices + 2.0 * r) * c * c + 4.0 * r * c);
-        if (s_bad == 0 && bound <= OP_DONE_TOL) {            // (false for NaN)
-            if (tid < 64) {
-                // a column at the noise floor is left for apply to report: this launch is the one that clears *info
-                const unsigned long long mask = __ballot(tid < r && !(rdiag[tid] > 1e-12 * sqrt(s_trace)));
-                if (tid == 0) {
-                    jb.scal[65] = mask ? (double)__ffsll((long long)mask) : 0.0;
-                    jb.scal[66] = 2.0;
+                        for (int v = 0; v < 4; ++v)
+                            acc = mfma64(sm.Gs[16 * I + ll][16 * K + lg + 4 * v] * di, X[K][v], acc);
+                v4d o = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int k = lg + 4 * v;
+                    o = mfma64(k >= ll ? -sm.Xs[I][ll][k] * sm.dinv[16 * I + k] : 0.0, acc[v], o);
                 }
+                X[I] = o;
             }
-            return false;
-        }
-    }
-    if (pass == 0 && tid == 0) jb.scal[66] = 0.0;
-    {   // R = rows scaled by 1 / R[k][k], zeros below the diagonal (reads first, selects after)
-        const int gb = tid & 63;
-        double gv[RM / OP_NW], dv[RM / OP_NW], iv[RM / OP_NW];
 #pragma unroll
-        for (int it = 0; it < RM / OP_NW; ++it) {
-            const int ga = (tid >> 6) + OP_NW * it;
-            gv[it] = Gs[ga][gb]; dv[it] = pinvs[ga]; iv[it] = dinv[ga];
+            for (int v = 0; v < 4; ++v) cs += sm.gsq[16 * I + lg + 4 * v] * fabs(X[I][v]);
         }
+        cs += __shfl_xor(cs, 16);
+        cs += __shfl_xor(cs, 32);
 #pragma unroll
-        for (int it = 0; it < RM / OP_NW; ++it) asm volatile("" : "+v"(gv[it]), "+v"(dv[it]), "+v"(iv[it]));
+        for (int m = 8; m >= 1; m >>= 1) cs = fmax(cs, __shfl_xor(cs, m));
+    }
+    if (lane == 0) sm.colmax[wave] = cs;
+    __syncthreads();
+    double c = 0.0;
 #pragma unroll
-        for (int it = 0; it < RM / OP_NW; ++it) {
-            const int ga = (tid >> 6) + OP_NW * it;
-            if (ga < r && gb < r) jb.R[ga * r + gb] = (ga < gb) ? gv[it] * iv[it] : (ga == gb ? dv[it] : 0.0);
-        }
+    for (int w = 0; w < OP_NW; ++w) {
+        const double m = sm.colmax[w];
+        c = m > c || m != m ? m : c;         // (a NaN stays)
     }
-    // inverse of each 16x16 diagonal block of R:  (R_bb^-1)[i][j] = (L_bb^-1)[j][i] / R[j][j]
-    for (int e = tid; e < nb * 256; e += OP_NT) {
-        const int b = e >> 8, i = (e >> 4) & 15, jj = e & 15, base = 16 * b;
-        const bool in = base + i < r && base + jj < r && jj >= i;
-        jb.Dinv[e] = in ? Xs[b][i][jj] * dinv[base + jj] : 0.0;
+    // (16 products in a chain per slice, the slices of a group, the groups; then factor, inverse and product)
+    return OP_EPS * ((18.0 + per_group + nslices + 2.0 * r) * c * c + 4.0 * r * c);
+}
+
+// For the solve: R in the place of its factor (rows scaled by 1 / R[k][k], zeros below the diagonal and beyond r), and the inverses
+// of its diagonal blocks, (R_bb^-1)[i][j] = (L_bb^-1)[j][i] / R[j][j]
+template <int RM>
+__device__ __forceinline__ void finish_r(int r, CholSmem& sm) {
+    const int tid = threadIdx.x, gb = tid & 63, nb = (r + 15) / 16;
+    double gv[RM / OP_NW];
+    constexpr int DI = (RM * 16 + OP_NT - 1) / OP_NT;
+    double dv[DI];
+#pragma unroll
+    for (int it = 0; it < RM / OP_NW; ++it) {
+        const int ga = (tid >> 6) + OP_NW * it;
+        const double g = sm.Gs[ga][gb] * sm.dinv[ga];
+        gv[it] = (ga < r && gb < r) ? (ga < gb ? g : (ga == gb ? sm.pinvs[ga] : 0.0)) : 0.0;
     }
-    if (tid < 64) {
-        // first column (if any) whose accumulated R diagonal fell to the noise floor
-        const double floor_ = 1e-12 * sqrt(s_trace);
-        const bool low = tid < r && !(rdiag[tid] > floor_);
-        const unsigned long long mask = __ballot(low);
-        if (tid == 0) {
-            double badv = (pass == 0) ? 0.0 : jb.scal[65];
-            if (badv == 0.0 && s_bad) badv = (double)s_bad;
-            jb.scal[65] = badv;
-            if (last && info) {
-                if (badv != 0.0) flag_info(info, jb.mode1, (int)badv);
-                if (mask) flag_info(info, jb.mode1, __ffsll((long long)mask));
-            }
-        }
+#pragma unroll
+    for (int u = 0; u < DI; ++u) {
+        const int e = tid + OP_NT * u, b = e >> 8, i = (e >> 4) & 15, jj = e & 15, base = 16 * b;
+        const bool in = b < nb && base + i < r && base + jj < r && jj >= i;
+        dv[u] = in ? sm.Xs[b][i][jj] * sm.dinv[base + jj] : 0.0;
     }
-    return true;
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < RM / OP_NW; ++it) sm.Gs[(tid >> 6) + OP_NW * it][gb] = gv[it];
+#pragma unroll
+    for (int u = 0; u < DI; ++u) {
+        const int e = tid + OP_NT * u;
+        if (e < nb * 256) sm.Xs[e >> 8][(e >> 4) & 15][e & 15] = dv[u];
+    }
+    __syncthreads();
 }
 
 // ---- hand-over from the slices of a mode to its factorisation ------------------------------
@@ -604,18 +614,16 @@ __device__ bool last_arrival(int32_t* ctr, int nblk, int* s_flag) {
 }
 
 // ---- gram0 ----------------------------------------------------------------------------------
-// A slice is 16 rows, so that the partial sums of P (10 MB for 32 splits of 960 x 40) are read by as many CUs as there are
-// slices; the slice Grams are then added in two levels, groups of gsz slices by the workgroup of a group that arrives last,
-// the groups by the one of the mode that does, because what one CU can read past its L2 is 25 bytes a cycle (30 slices of
-// 32 rows summed by one workgroup: 8.5 us for the partial sums and 6.8 for the Grams; 60 slices in 8 groups 3.6 and 6.3).
+// A slice is 16 rows, so that the partial sums of P (5 MB for 16 splits of 960 x 40) are read by as many CUs as there are
+// slices, because what one CU can read past its L2 is 25 bytes a cycle; beyond 12 slices the Grams of about sqrt(slices) of them are
+// added up by the workgroup of the group that arrives last, so that the next launch finds a dozen matrices at most (sixty: 390 KB
+// for each of its workgroups).
 // RM bounds the ranks of the launch's modes: a slice has at most 16 * RM elements, ITS per thread.  Up to 32 a CU holds two
-// workgroups (128 registers; six of <32> spill, 28 bytes a lane).
+// workgroups (128 registers).
 template <int RM>
 __global__ __launch_bounds__(OP_NT, RM <= 32 ? 4 : 2) void k_orth_gram0(OrthBatch a) {
-    __shared__ __align__(16) unsigned char raw[sizeof(CholSmem)];
+    __shared__ double Ps[OP_GS][OP_LD];
     __shared__ int s_last;
-    double (*Ps)[OP_LD] = reinterpret_cast<double (*)[OP_LD]>(raw);                 // [OP_GS][OP_LD]
-    static_assert(sizeof(CholSmem) >= OP_GS * OP_LD * sizeof(double), "the slice fits");
     int ji, blk;
     find_job(a, &ji, &blk);
     const OrthJob& jb = a.job[ji];
@@ -657,86 +665,51 @@ __global__ __launch_bounds__(OP_NT, RM <= 32 ? 4 : 2) void k_orth_gram0(OrthBatc
     }
     __syncthreads();
     const int T = (r * (r + 1)) / 2, nsl = (n + OP_GS - 1) / OP_GS, gsz = jb.gsz, ngrp = (nsl + gsz - 1) / gsz;
-    const int grp = blk / gsz, in_grp = nsl - grp * gsz < gsz ? nsl - grp * gsz : gsz;
-    gram_from_lds<OP_GS>(Ps, r, jb.Gpart + (long long)blk * T);
-    // the workgroup that finishes a group's last slice adds the group up, the one that finishes the last group factors
-    if (!last_arrival<false>(jb.ctr + 2 + grp, in_grp, &s_last)) return;
-    double* sums = jb.Gpart;
-    if (ngrp > 1) {
-        sums += (long long)nsl * T;
-        double gs[packed_its<RM>()];
-        sum_packed<RM>(jb.Gpart + (long long)grp * gsz * T, in_grp, T, gs);
+    v4d acc[OP_PAIRS];
 #pragma unroll
-        for (int it = 0; it < packed_its<RM>(); ++it)
-            if (tid + OP_NT * it < T) publish(sums + (long long)grp * T + tid + OP_NT * it, gs[it]);
-        if (!last_arrival<false>(jb.ctr + 0, ngrp, &s_last)) return;
-    }
-    chol_job<RM>(jb, 0, 0, sums, ngrp > 1 ? ngrp : nsl, jb.info, *reinterpret_cast<CholSmem*>(raw));
+    for (int u = 0; u < OP_PAIRS; ++u) acc[u] = (v4d){0.0, 0.0, 0.0, 0.0};
+    gram_add<OP_GS>(Ps, r, acc);
+    gram_publish(acc, r, jb.Gpart + (long long)blk * T);
+    if (ngrp == 1) return;
+    // the workgroup that finishes a group's last slice adds the group up
+    const int grp = blk / gsz, in_grp = nsl - grp * gsz < gsz ? nsl - grp * gsz : gsz;
+    if (!last_arrival<false>(jb.ctr + 2 + grp, in_grp, &s_last)) return;
+    double gs[packed_its<RM>()];
+    sum_packed<RM, true>(jb.Gpart + (long long)grp * gsz * T, in_grp, T, gs);
+#pragma unroll
+    for (int it = 0; it < packed_its<RM>(); ++it)
+        if (tid + OP_NT * it < T) jb.Gpart[(long long)(nsl + grp) * T + tid + OP_NT * it] = gs[it];
 }
 
 // ---- apply ----------------------------------------------------------------------------------
-// Not certified: all threads load the slice, R and the diagonal-block inverses in one round of loads; waves 0 and 1
-// then solve 16 rows each.
-struct ApplySmem {
-    double Ps[OP_RS][OP_LD];
-    double Rs[OP_RMAX][OP_LD];
-    double Ds[OP_RMAX / 16][16][17];
-};
-union ApplyOrChol {                      // the factorisation reuses the memory of the finished solve
-    ApplySmem ap;
-    CholSmem ch;
-};
-
-// One 32-row slice: P64[slice] <- P64[slice] R^-1.  The first pass stores the result in fp64 for
-// the second pass, its fp32 copy in Uout (the result if the first pass turns out to be enough) and
-// the slice's Gram matrix; the final pass stores fp32 only.
+// One 32-row slice: P64[slice] <- P64[slice] R^-1, R and the inverses of its diagonal blocks in sm; waves 0 and 1 solve 16 rows each.
+// The first pass stores the result in fp64 for the second pass and its fp32 copy in Uout (the result if the first pass turns
+// out to be enough) and leaves it in Ps; the final pass stores fp32 only.
 template <int RM>
-__device__ void apply_slice(const OrthJob& jb, int blk, int final_pass, ApplySmem& ap) {
-    double (*Ps)[OP_LD] = ap.Ps;
-    double (*Rs)[OP_LD] = ap.Rs;
-    double (*Ds)[16][17] = ap.Ds;
+__device__ void apply_slice(const OrthJob& jb, int slice, int final_pass, double (*Ps)[OP_LD], const CholSmem& sm) {
+    const double (*Rs)[OP_LD] = sm.Gs;
+    const double (*Ds)[16][17] = sm.Xs;
     const int n = jb.n, r = jb.r, tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6, lg = lane >> 4, ll = lane & 15;
     const int nb = (r + 15) / 16;
-    const int i0 = blk * OP_RS;
+    const int i0 = slice * OP_RS;
     const int nrows = (n - i0 < OP_RS) ? n - i0 : OP_RS;
-    constexpr int PI = OP_RS * RM / OP_NT, RI = (RM * RM + OP_NT - 1) / OP_NT, DI = (RM * 16 + OP_NT - 1) / OP_NT;
+    constexpr int PI = OP_RS * RM / OP_NT;
     const float inv_r = 1.0f / (float)r;
-    double tp[PI], tr[RI], td[DI];
+    double tp[PI];
 #pragma unroll
     for (int u = 0; u < PI; ++u) {
         const int idx = u * OP_NT + tid;
         tp[u] = ldg_f64(jb.P64, (long long)i0 * r + idx, idx < nrows * r);
     }
-#pragma unroll
-    for (int u = 0; u < RI; ++u) {
-        const int e = u * OP_NT + tid;
-        tr[u] = ldg_f64(jb.R, e, e < r * r);
-    }
-#pragma unroll
-    for (int u = 0; u < DI; ++u) {
-        const int e = u * OP_NT + tid;
-        td[u] = ldg_f64(jb.Dinv, e, e < nb * 256);
-    }
+    __syncthreads();                                      // (the last slice has been read)
     for (int e = tid; e < OP_RS * OP_LD; e += OP_NT) (&Ps[0][0])[e] = 0.0;
-    for (int e = tid; e < OP_RMAX * OP_LD; e += OP_NT) (&Rs[0][0])[e] = 0.0;
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < PI; ++u) {
         const int idx = u * OP_NT + tid;
         const int pi = small_div(idx, inv_r);
         if (idx < nrows * r) Ps[pi][idx - pi * r] = tp[u];
-    }
-#pragma unroll
-    for (int u = 0; u < RI; ++u) {
-        const int e = u * OP_NT + tid;
-        const int ri = small_div(e, inv_r);
-        if (e < r * r) Rs[ri][e - ri * r] = tr[u];
-    }
-#pragma unroll
-    for (int u = 0; u < DI; ++u) {
-        const int e = u * OP_NT + tid;
-        if (e < nb * 256) Ds[e >> 8][(e >> 4) & 15][e & 15] = td[u];
     }
     __syncthreads();
     // wave w < 2 owns rows 16w..16w+15 of the slice; block columns are solved left to right
@@ -768,81 +741,112 @@ __device__ void apply_slice(const OrthJob& jb, int blk, int final_pass, ApplySme
         }
         __syncthreads();
     }
-    if (final_pass) {
-        for (int idx = tid; idx < nrows * r; idx += OP_NT) {
-            const int pi = small_div(idx, inv_r);
-            jb.Uout[(long long)i0 * r + idx] = (float)Ps[pi][idx - pi * r];
-        }
-    } else {
-        for (int idx = tid; idx < nrows * r; idx += OP_NT) {
-            const int pi = small_div(idx, inv_r);
-            const double q0 = Ps[pi][idx - pi * r];
-            jb.P64[(long long)i0 * r + idx] = q0;
-            jb.Uout[(long long)i0 * r + idx] = (float)q0;
-        }
-        gram_from_lds<OP_RS>(Ps, r, jb.Gpart + (long long)blk * ((r * (r + 1)) / 2));
+    for (int idx = tid; idx < nrows * r; idx += OP_NT) {
+        const int pi = small_div(idx, inv_r);
+        const double q0 = Ps[pi][idx - pi * r];
+        if (!final_pass) jb.P64[(long long)i0 * r + idx] = q0;
+        jb.Uout[(long long)i0 * r + idx] = (float)q0;
     }
 }
 
-// Second half of the orthonormalisation in one launch: every workgroup solves its slice with the
-// first-pass factor; the one that finishes a mode's last slice checks Q0^T Q0 against the identity
-// and, only if that fails, factors it and solves all slices of the mode once more by itself (a
-// rare, slow path: it trades a launch per call for serial work on ill-conditioned inputs).
+// The rest of the orthonormalisation in one launch.  EVERY workgroup of a mode adds up the mode's Gram matrices, factors the sum and
+// inverts the factor for itself (the same bits in all of them), then takes its slices of 32 rows: a dozen microseconds of one wave's
+// dependent pivots cost nothing on a chip that has nothing else to do, and no workgroup waits for another.  One workgroup that
+// arrived last did it before, inside gram0: a second level of hand-over, loads past the L2, and the factor's way through memory.
+// Certified: Q = P X, wave (half h, block column J) 16 rows times its block column of X, the rows requested when the kernel starts.
+// Otherwise: solve, slice Gram; the workgroup that finishes a mode's last slice checks Q0^T Q0 against the identity and, only
+// if that fails, factors it and solves all slices of the mode once more by itself (a rare, slow path: it trades a launch per
+// call for serial work on ill-conditioned inputs).  Its Grams lie where nothing of this launch is read: over gram0's slice
+// Grams where those have been added up by groups, behind them otherwise.
 template <int RM>
 __global__ __launch_bounds__(OP_NT) void k_orth_apply(OrthBatch a) {
-    __shared__ __align__(16) unsigned char raw[sizeof(ApplyOrChol)];
+    __shared__ CholSmem sm;
+    __shared__ double Ps[OP_RS][OP_LD];
     __shared__ int s_last;
-    ApplySmem& ap = *reinterpret_cast<ApplySmem*>(raw);
     int ji, blk;
     find_job(a, &ji, &blk);
-    const OrthJob jb = a.job[ji];
-    {
-        // Certified: wave (half h, block column J) multiplies 16 rows by the block column of X, operands straight from memory
-        // (K slot (v, lg) of a block is index lg + 4 v for both sides); they are requested together with the flag that says
-        // whether they are of use.
-        const int n = jb.n, r = jb.r, nb = (r + 15) / 16;
-        const int lane = threadIdx.x & 63, lg = lane >> 4, ll = lane & 15;
-        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        const int h = wave & 1, J = wave >> 1;
-        const int row = blk * OP_RS + 16 * h + ll;
-        double av[RM / 16][4], bv[RM / 16][4];
+    const OrthJob& jb = a.job[ji];
+    const int n = jb.n, r = jb.r, nb = (r + 15) / 16, tid = threadIdx.x;
+    const int T = (r * (r + 1)) / 2, nsl = (n + OP_GS - 1) / OP_GS, ngrp = (nsl + jb.gsz - 1) / jb.gsz;
+    const int first = blk * jb.spw, nall = (n + OP_RS - 1) / OP_RS, end = first + jb.spw < nall ? first + jb.spw : nall;
+    const int lane = tid & 63, lg = lane >> 4, ll = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), J = wave & 3, h = wave >> 2;
+    double av[RM / 16][4];
+    auto rows = [&](int slice) __attribute__((always_inline)) {
+        const int row = slice * OP_RS + 16 * h + ll;
 #pragma unroll
         for (int I = 0; I < RM / 16; ++I)
-            if (I <= J && J < nb) {          // uniform
+            if (I <= J && J < nb)            // uniform
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const int k = 16 * I + lg + 4 * v;
                     av[I][v] = jb.P64[(row < n && k < r) ? (long long)row * r + k : 0];
-                    bv[I][v] = jb.Rinv[(J * (J + 1) / 2 + I) * 256 + 64 * v + lane];
+                }
+    };
+    if (RM < 64) rows(first);                // (at 64 the factorisation needs the registers)
+    const bool lead = blk == 0;
+    bool shifted;
+    chol_factor<RM, 0>(jb, lead, jb.Gpart + (ngrp > 1 ? (long long)nsl * T : 0), ngrp > 1 ? ngrp : nsl, jb.info, sm, &shifted);
+    if (!shifted) {
+        v4d X[RM / 16];
+        const double bound = invert<RM>(r, ngrp > 1 ? jb.gsz : 1, ngrp > 1 ? ngrp : nsl, sm, X);
+        if (sm.s_bad == 0 && bound <= OP_DONE_TOL) {             // (false for NaN)
+            if (lead && wave == 0) {
+                const unsigned long long mask = __ballot(lane < r && !(sm.rdiag[lane] > 1e-12 * sqrt(sm.s_trace)));
+                if (lane == 0) {
+                    const int low = mask ? __ffsll((long long)mask) : 0;
+                    jb.scal[65] = (double)low;
+                    jb.scal[66] = 2.0;
+                    if (low) flag_info(jb.info, jb.mode1, low);
                 }
             }
-        const double state = jb.scal[66], low = jb.scal[65];
-        if (state == 2.0) {
-            if (blk == 0 && threadIdx.x == 0 && low != 0.0) flag_info(jb.info, jb.mode1, (int)low);
             if (J >= nb) return;
-            v4d q = {0.0, 0.0, 0.0, 0.0};
+            for (int s = first; s < end; ++s) {
+                if (s != first || RM == 64) rows(s);
+                const int row = s * OP_RS + 16 * h + ll;
+                v4d q = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-            for (int I = 0; I < RM / 16; ++I)
-                if (I <= J)                  // uniform
+                for (int I = 0; I < RM / 16; ++I)
+                    if (I <= J)              // uniform
 #pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        q = __builtin_amdgcn_mfma_f64_16x16x4f64((row < n && 16 * I + lg + 4 * v < r) ? av[I][v] : 0.0, bv[I][v], q, 0, 0, 0);
+                        for (int v = 0; v < 4; ++v) q = mfma64((row < n && 16 * I + lg + 4 * v < r) ? av[I][v] : 0.0, X[I][v], q);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int i = blk * OP_RS + 16 * h + lg + 4 * v, c = 16 * J + ll;
-                if (i < n && c < r) jb.Uout[(long long)i * r + c] = (float)q[v];
+                for (int v = 0; v < 4; ++v) {
+                    const int i = s * OP_RS + 16 * h + lg + 4 * v, c = 16 * J + ll;
+                    if (i < n && c < r) jb.Uout[(long long)i * r + c] = (float)q[v];
+                }
             }
             return;
         }
     }
-    apply_slice<RM>(jb, blk, 0, ap);
+    if (lead && tid == 0) { jb.scal[65] = (double)sm.s_bad; jb.scal[66] = 0.0; }
+    finish_r<RM>(r, sm);
+    v4d acc[OP_PAIRS];
+#pragma unroll
+    for (int u = 0; u < OP_PAIRS; ++u) acc[u] = (v4d){0.0, 0.0, 0.0, 0.0};
+    for (int s = first; s < end; ++s) {
+        apply_slice<RM>(jb, s, 0, Ps, sm);
+        gram_add<OP_RS>(Ps, r, acc);
+    }
+    double* second = jb.Gpart + (ngrp > 1 ? 0 : (long long)nsl * T);
+    gram_publish(acc, r, second + (long long)blk * T);
     if (!last_arrival<true>(jb.ctr + 1, jb.nblk, &s_last)) return;
-    const bool again = chol_job<RM>(jb, 1, 1, jb.Gpart, jb.nblk, jb.info, *reinterpret_cast<CholSmem*>(raw));
-    if (!again) return;
-    for (int b2 = 0; b2 < jb.nblk; ++b2) {
-        __threadfence();                   // R, Dinv (and every slice of Q0) are read back from memory
-        __syncthreads();
-        apply_slice<RM>(jb, b2, 1, ap);
+    if (!chol_factor<RM, 1>(jb, true, second, jb.nblk, jb.info, sm, &shifted)) return;
+    if (tid < 64) {
+        // first column (if any) whose accumulated R diagonal fell to the noise floor
+        const unsigned long long mask = __ballot(tid < r && !(sm.rdiag[tid] > 1e-12 * sqrt(sm.s_trace)));
+        if (tid == 0) {
+            double badv = jb.scal[65];
+            if (badv == 0.0 && sm.s_bad) badv = (double)sm.s_bad;
+            jb.scal[65] = badv;
+            if (badv != 0.0) flag_info(jb.info, jb.mode1, (int)badv);
+            if (mask) flag_info(jb.info, jb.mode1, __ffsll((long long)mask));
+        }
+    }
+    finish_r<RM>(r, sm);
+    for (int s = 0; s < nall; ++s) {
+        __threadfence();                   // every slice of Q0 is read back from memory
+        apply_slice<RM>(jb, s, 1, Ps, sm);
     }
 }
 
@@ -1434,11 +1438,18 @@ int orth_gram_slices(int n) { return (n + OP_GS - 1) / OP_GS; }
 // slices per group: about the square root, no more than kOrthGroups groups
 int orth_group_size(int n) {
     const int s = orth_gram_slices(n);
-    if (s <= 12) return s;                               // one group: the second level only copies
+    if (s <= OP_ONE_GROUP) return s;                     // one group: apply adds the slices up itself
     if (s > kOrthGroups * kOrthGroups) return (s + kOrthGroups - 1) / kOrthGroups;
     int g = 1;
     while (g * g < s) ++g;
     return g;
+}
+// Slices of 32 rows that a workgroup of apply takes: one, more where that makes more than 128 workgroups.  A mode of one group keeps
+// the Grams of a second pass, one per workgroup, behind those of the slices: four at most, so that no layer needs more scratch
+// than with the first pass's factor in memory.
+int orth_apply_slices(int n) {
+    const int s = orth_slices(n), most = orth_groups(n) == 1 ? 4 : 128;
+    return (s + most - 1) / most;
 }
 bool orth_wide_supported(int r) { return r > OP_RMAX && r <= OW_RMAX; }
 int orth_wide_gram_blocks(int n) { return (n + OW_ROWS - 1) / OW_ROWS; }
@@ -1461,9 +1472,9 @@ static bool fast_args_ok(const OrthArgs& a) {
     if (a.njobs <= 0 || a.njobs > 4) return false;
     for (int j = 0; j < a.njobs; ++j) {
         const OrthJob& jb = a.job[j];
-        if (jb.n <= 0 || jb.r <= 0 || jb.r > OP_RMAX || jb.nblk != orth_slices(jb.n)) return false;
+        if (jb.n <= 0 || jb.r <= 0 || jb.r > OP_RMAX || jb.nblk != orth_apply_wgs(jb.n) || jb.spw != orth_apply_slices(jb.n)) return false;
         if (jb.gsz != orth_group_size(jb.n) || orth_groups(jb.n) > kOrthGroups) return false;
-        if (!jb.Gpart || !jb.R || !jb.Rinv || !jb.Dinv || !jb.scal || !jb.P64 || !jb.Uout || !jb.part || !jb.ctr) return false;
+        if (!jb.Gpart || !jb.scal || !jb.P64 || !jb.Uout || !jb.part || !jb.ctr) return false;
     }
     return true;
 }
