@@ -446,10 +446,10 @@ inline void tag(Program& pg, const char* role, double bytes, double flops) {
 
 // mode product with its accounting: reads X and M once, writes (or updates) Y once
 asi_status add_ttm(Program& pg, const char* role, DType xt, const void* X, long long outer, int n, long long inner,
-                   const float* Mp, long long ms_i, long long ms_q, int r, float* Y, int beta, bool stream_ok = true) {
+                   const float* Mp, long long ms_i, long long ms_q, int r, float* Y, int beta) {
     const double cols = (double)outer * (double)inner;
     ASI_ADD(pg, role, cols * n * esize(xt) + 4.0 * n * r + 4.0 * cols * r * (beta ? 2 : 1), 2.0 * cols * n * r,
-            make_ttm(xt, X, outer, n, inner, Mp, ms_i, ms_q, r, Y, beta, it__, stream_ok));
+            make_ttm(xt, X, outer, n, inner, Mp, ms_i, ms_q, r, Y, beta, it__));
     return ASI_OK;
 }
 // two trailing modes at once (Kronecker product of their matrices)
@@ -788,6 +788,13 @@ asi_status build_core(const asi_tensor_desc* desc, const void* A, const float* c
             if (ks > 1)
                 ASI_ADD(pg, "core", 4.0 * cols * r * (ks + 1), cols * r * ks,
                         make_sum_partials(p.part, ks, (long long)outer * r, dst, 0, it__));
+        } else if (p.kron && m == 2 && sdt == F32 && k >= 1 &&
+                   (pg.items.emplace_back(), make_core_planes(static_cast<const float*>(src), outer, (int)s.n[2], (int)s.n[3], U[2], s.r[2],
+                                                              U[3], s.r[3], dst, &pg.items.back()) || (pg.items.pop_back(), false))) {
+            // the same plane by plane where the tensor has shrunk already
+            const double H = (double)s.n[2], W = (double)s.n[3], planes = (double)outer;
+            tag(pg, "core", 4.0 * (planes * (H * W + (double)s.r[2] * s.r[3]) + H * s.r[2] + W * s.r[3]),
+                2.0 * planes * (H * W * s.r[3] + H * s.r[2] * s.r[3]));
         } else if (p.kron && m == 2) {
             // (.., H, W) -> (.., r3, r4):  M(h*W + w, a*r4 + b) = U3[h,a] * U4[w,b]
             ASI_TRYS(add_ttm_kron(pg, "core", sdt, src, outer, (int)s.n[2], (int)s.n[3], U[2], s.r[2], 1, s.r[2], U[3],
@@ -842,28 +849,26 @@ asi_status build_conv_maps(const asi_tensor_desc* desc, const float* S, const fl
         cb->G1 = static_cast<const float*>(grad_out);
     } else {
         // 1. G1 = grad_out x_1 U1^T                                   (r1, cout, Ho, Wo)
-        // (where Z comes from one merged product it can share G1's launch: G1 then stays on the tiled kernel)
-        ASI_TRYS(add_ttm(pg, "G1", s.dt, grad_out, 1, cg.B, (long long)g.cout * g.Ho * g.Wo, U[0], g.r1, 1, g.r1, p.G1, 0,
-                         p.Z1 != nullptr));
+        ASI_TRYS(add_ttm(pg, "G1", s.dt, grad_out, 1, cg.B, (long long)g.cout * g.Ho * g.Wo, U[0], g.r1, 1, g.r1, p.G1, 0));
     }
-    if (!p.Z1) {
-        // 2+3. Z = S x_3 U3 x_4 U4 in one pass:  M(a*r4 + b, h*W + w) = U3[h,a] * U4[w,b]   (r1, r2, H, W)
-        ASI_TRYS(add_ttm_kron(pg, "Z", F32, Sz, (long long)g.r1 * g.r2, r3, r4, U[2], 1, r3, g.H, U[3], 1, r4, g.W, p.Z));
-        // G1 and Z do not depend on each other: one launch for both when their kernels allow it
-        Item duo;
-        const size_t ni = pg.items.size();
-        if (!expand_core && make_ttm_duo(pg.items[ni - 2], pg.items[ni - 1], &duo)) {
-            pg.items.pop_back();
-            pg.items.back() = duo;
-        }
-    } else if (pg.items.emplace_back(),
-               make_z_planes(Sz, (long long)g.r1 * g.r2, r3, r4, U[2], g.H, U[3], g.W, p.Z, &pg.items.back())) {
+    pg.items.emplace_back();
+    if (make_z_planes(Sz, (long long)g.r1 * g.r2, r3, r4, U[2], g.H, U[3], g.W, p.Z, &pg.items.back())) {
         // 2+3. Z[p] = U3 S[p] U4^T plane by plane, both products in one launch (planes of up to 64 x 64, ranks up to 32)
         const double planes = (double)g.r1 * g.r2;
         tag(pg, "Z", 4.0 * (planes * ((double)r3 * r4 + (double)g.H * g.W) + (double)g.H * r3 + (double)g.W * r4),
             2.0 * planes * ((double)g.H * r3 * r4 + (double)g.H * g.W * r4));
+        // G1 and Z do not depend on each other: one launch for both where G1's kernel allows it (a tiled G1 beside planes of more than
+        // 256 entries: the planes are the longer of the two and its workgroups' LDS keeps them few)
+        Item duo;
+        const size_t ni = pg.items.size();
+        if (!expand_core && (!p.Z1 || pg.items[ni - 2].kind == IT_TTM_STREAM) && make_ttm_duo(pg.items[ni - 2], pg.items[ni - 1], &duo)) {
+            pg.items.pop_back();
+            pg.items.back() = duo;
+        }
+    } else if (pg.items.pop_back(), !p.Z1) {
+        // 2+3. Z = S x_3 U3 x_4 U4 in one pass:  M(a*r4 + b, h*W + w) = U3[h,a] * U4[w,b]   (r1, r2, H, W)
+        ASI_TRYS(add_ttm_kron(pg, "Z", F32, Sz, (long long)g.r1 * g.r2, r3, r4, U[2], 1, r3, g.H, U[3], 1, r4, g.W, p.Z));
     } else {
-        pg.items.pop_back();
         // 2. Z1 = S x_3 U3                                        (r1, r2, H, r4)
         ASI_TRYS(add_ttm(pg, "Z1", F32, Sz, (long long)g.r1 * g.r2, r3, r4, U[2], 1, r3, g.H, p.Z1, 0));
         // 3. Z = Z1 x_4 U4                                        (r1, r2, H, W)

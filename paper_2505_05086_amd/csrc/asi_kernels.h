@@ -113,10 +113,9 @@ struct TtmJob {
     int32_t* zero;         // nullable: `nzero` int32 the kernel clears (arrival counters of later launches)
     int nzero;
 };
-// stream_ok = false keeps the product on the tiled kernels (which can share a launch with a second product, make_ttm_duo)
 constexpr long long kStreamMinElems = 1LL << 20;
 bool make_ttm(DType xt, const void* X, long long outer, int n, long long inner, const float* Mp, long long ms_i,
-              long long ms_q, int r, float* Y, int beta, Item* out, bool stream_ok = true);
+              long long ms_q, int r, float* Y, int beta, Item* out);
 // the same product by the streaming kernel (asi_ttm_stream.hip); make_ttm picks it where it is supported and faster
 bool ttm_stream_supported(DType xt, const void* X, long long outer, int n, long long inner, const float* Mp,
                           long long ms_i, long long ms_q, int r, const float* Y);
@@ -158,10 +157,10 @@ __device__ __forceinline__ void presum_block(const PresumJob* jobs, int njobs, i
     jb.out[(long long)g * jb.cnt + e] = s;
 }
 
-// One launch for two independent products made by make_ttm / make_ttm_kron (tagged with role, bytes, flops):
-// a plain tiled product not along the last mode, and a small merged (Kronecker) product.  Returns false
-// if the items do not have these forms.
+// One launch for two independent items (tagged with role, bytes, flops): a plain product by make_ttm, tiled or streaming, not along
+// the last mode, and the planes of make_z_planes.  Returns false if the items do not have these forms.
 bool make_ttm_duo(const Item& a, const Item& z, Item* out);
+bool make_ttm_stream_duo(const Item& a, const Item& z, Item* out);
 
 // ---- product along the last mode of a bf16 tensor on the bf16 MFMA (asi_bf16.hip) -----------------------------
 // Y[c,q] = sum_i X[c,i] M[i,q]: X (ncols, n) bf16, Y (ncols, r) fp32.  The fp32 matrix is first split into two bf16
@@ -379,17 +378,16 @@ bool make_dw_fold(const float* Tpart, int nsplit, const float* U2, float* dW, in
                   Item* out);
 hipError_t launch_dw_fold_items(const Item* const* items, int n, hipStream_t st);
 
-// ---- steps 2 and 3 of Eq. 14 for large planes in one launch (asi_kernels.hip) ----------------------------------
+// ---- steps 2 and 3 of Eq. 14 in one launch (asi_kernels.hip, asi_zplanes.h) ----------------------------------
 // Z[p] = U3 S[p] U4^T for every plane p of the core: S (planes, r3, r4), U3 (H, r3), U4 (W, r4), Z (planes, H, W);
-// H, W <= 64, r3, r4 <= 32 and multiples of 4, W a multiple of 4, 16-byte aligned pointers.  False otherwise (the
-// caller then takes the two mode products one after the other).
+// H, W <= 64, r3, r4 <= 32.  False otherwise (the caller then takes the two mode products one after the other).
 bool make_z_planes(const float* S, long long planes, int r3, int r4, const float* U3, int H, const float* U4, int W, float* Z,
                    Item* out);
 hipError_t launch_z_planes_items(const Item* const* items, int n, hipStream_t st);
 
 // ---- the H and W products of the core projection for large planes in one launch (asi_kernels.hip) -----------
 // Y[p] = U3^T X[p] U4 for every plane p: X (planes, H, W) fp32, U3 (H, r3), U4 (W, r4), Y (planes, r3, r4); H, W <= 64,
-// r3, r4 <= 32, W a multiple of 4, X 16-byte aligned.  False otherwise (the caller takes the two mode products).
+// r3, r4 <= 32.  False otherwise (the caller takes the two mode products).
 bool make_core_planes(const float* X, long long planes, int H, int W, const float* U3, int r3, const float* U4, int r4, float* Y,
                       Item* out);
 hipError_t launch_core_planes_items(const Item* const* items, int n, hipStream_t st);

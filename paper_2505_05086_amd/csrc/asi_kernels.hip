@@ -7,6 +7,7 @@
 #include "asi_device.h"
 #include "asi_kernels.h"
 #include "asi_lds.h"
+#include "asi_zplanes.h"
 
 #include <algorithm>
 #include <cstdio>
@@ -859,133 +860,37 @@ hipError_t launch_dw_fold_items(const Item* const* items, int n, hipStream_t st)
 }
 
 // ---------------------------------------------------------------------------
-// Steps 2 and 3 of Eq. 14 for large planes: Z[p] = U3 S[p] U4^T, one workgroup per plane of the core
+// Steps 2 and 3 of Eq. 14, plane by plane (asi_zplanes.h): planes of up to 16 rows share a workgroup, a wave each
 // ---------------------------------------------------------------------------
-// Both products of a plane are a few thousand multiply-adds on operands that fit a wave's registers; as two mode
-// products over the whole core they were two launches of 10 us each, bound by their round trips.  Here wave w of a
-// plane's workgroup takes rows h = 16 w .. 16 w + 15: it loads the plane of S, its rows of U3 and the whole of U4 once
-// and multiplies twice on the fp32 MFMA:
-//   Z1^T[q, h] = sum_k S[k, q] U3[h, k]        A = S^T (row q = ll), B = U3^T (column h = ll)
-//   Z^T[w, h]  = sum_q U4[w, q] Z1^T[q, h]     A = U4 (row w = ll),  B = Z1^T
-// K slot lg of step s of a 16-block stands for index 16 block + 4 lg + s: a lane's B operand of the second product
-// is then register s of the first product's result (row 4 lg + s of the block, column ll), so Z1 never leaves the
-// registers, and the A operands are 16-byte loads of four consecutive indices.  The result registers hold four
-// consecutive w of one row h: 16-byte stores, 64 contiguous bytes per row and instruction.
-struct ZPlanesJob {
-    const float* S;
-    const float* U3;
-    const float* U4;
-    float* Z;
-    long long planes;
-    int H, W, r3, r4;
-};
-
-template <int WB>
+template <int WB, bool VEC>
 __global__ __launch_bounds__(256) void k_z_planes(Batch<ZPlanesJob> bt) {
-    typedef float v4f __attribute__((ext_vector_type(4)));
     int lb;
     const ZPlanesJob& jb = bt.job[locate(bt, &lb)];
-    const int tid = threadIdx.x, lane = tid & 63, lg = lane >> 4, ll = lane & 15;
-    const int hb = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave w takes rows 16 w .. 16 w + 15 of the plane
-    const long long plane = lb;
-    const int H = jb.H, W = jb.W, r3 = jb.r3, r4 = jb.r4;
-    if (16 * hb >= H) return;                            // (no barrier in this kernel)
-    const float* __restrict__ Sp = jb.S + plane * r3 * r4;
-
-    // operands: all loads first, from addresses valid for every lane; masked afterwards
-    v4f u3[2], u4[WB][2];
-    float sa[2][2][4];
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int qb = 0; qb < 2; ++qb)
-#pragma unroll
-            for (int s_ = 0; s_ < 4; ++s_) {
-                const int k = 16 * kb + 4 * lg + s_, q = 16 * qb + ll;
-                sa[kb][qb][s_] = Sp[(k < r3 && q < r4) ? k * r4 + q : 0];
-            }
-    const int h = 16 * hb + ll;
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-        const int k0 = 16 * kb + 4 * lg;
-        u3[kb] = *reinterpret_cast<const v4f*>(jb.U3 + ((h < H && k0 < r3) ? h * r3 + k0 : 0));
-    }
-#pragma unroll
-    for (int wb = 0; wb < WB; ++wb)
-#pragma unroll
-        for (int qb = 0; qb < 2; ++qb) {
-            const int w = 16 * wb + ll, q0 = 16 * qb + 4 * lg;
-            u4[wb][qb] = *reinterpret_cast<const v4f*>(jb.U4 + ((w < W && q0 < r4) ? w * r4 + q0 : 0));
-        }
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int qb = 0; qb < 2; ++qb)
-#pragma unroll
-            for (int s_ = 0; s_ < 4; ++s_) {
-                const int k = 16 * kb + 4 * lg + s_, q = 16 * qb + ll;
-                sa[kb][qb][s_] = (k < r3 && q < r4) ? sa[kb][qb][s_] : 0.f;
-            }
-    const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) u3[kb] = (h < H && 16 * kb + 4 * lg < r3) ? u3[kb] : zero4;
-#pragma unroll
-    for (int wb = 0; wb < WB; ++wb)
-#pragma unroll
-        for (int qb = 0; qb < 2; ++qb) u4[wb][qb] = (16 * wb + ll < W && 16 * qb + 4 * lg < r4) ? u4[wb][qb] : zero4;
-
-    // Z1^T: z1[qb][e] = Z1^T[16 qb + 4 lg + e][16 hb + ll]
-    v4f z1[2] = {zero4, zero4};
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-        if (16 * kb < r3) {                                // (uniform: a rank of at most 16 has one block)
-#pragma unroll
-            for (int s_ = 0; s_ < 4; ++s_)
-#pragma unroll
-                for (int qb = 0; qb < 2; ++qb)
-                    z1[qb] = __builtin_amdgcn_mfma_f32_16x16x4f32(sa[kb][qb][s_], u3[kb][s_], z1[qb], 0, 0, 0);
-        }
-    }
-    // Z^T: zt[wb][e] = Z[16 hb + ll][16 wb + 4 lg + e]
-    v4f zt[WB];
-#pragma unroll
-    for (int wb = 0; wb < WB; ++wb) zt[wb] = zero4;
-#pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
-        if (16 * qb < r4) {
-#pragma unroll
-            for (int s_ = 0; s_ < 4; ++s_)
-#pragma unroll
-                for (int wb = 0; wb < WB; ++wb)
-                    zt[wb] = __builtin_amdgcn_mfma_f32_16x16x4f32(u4[wb][qb][s_], z1[qb][s_], zt[wb], 0, 0, 0);
-        }
-    }
-    float* __restrict__ Zp = jb.Z + plane * H * W;
-#pragma unroll
-    for (int wb = 0; wb < WB; ++wb) {
-        const int w0 = 16 * wb + 4 * lg;
-        if (h < H && w0 < W) *reinterpret_cast<v4f*>(Zp + h * W + w0) = zt[wb];      // W is a multiple of 4
-    }
+    z_planes_block<WB, VEC>(jb, lb);
 }
 
+// key: [0..3] blocks of 16 columns, [4] VEC
 bool make_z_planes(const float* S, long long planes, int r3, int r4, const float* U3, int H, const float* U4, int W, float* Z,
                    Item* out) {
     if (!S || !U3 || !U4 || !Z || planes <= 0) return false;
     if (H < 1 || W < 1 || H > 64 || W > 64 || r3 < 1 || r4 < 1 || r3 > 32 || r4 > 32) return false;
-    if (r3 % 4 != 0 || r4 % 4 != 0 || W % 4 != 0) return false;
-    if (reinterpret_cast<uintptr_t>(U3) % 16 != 0 || reinterpret_cast<uintptr_t>(U4) % 16 != 0 || reinterpret_cast<uintptr_t>(Z) % 16 != 0)
-        return false;
+    const bool vec = r3 % 4 == 0 && r4 % 4 == 0 && W % 4 == 0 && reinterpret_cast<uintptr_t>(U3) % 16 == 0 &&
+                     reinterpret_cast<uintptr_t>(U4) % 16 == 0 && reinterpret_cast<uintptr_t>(Z) % 16 == 0;
+    // (a dozen planes element by element are no shorter a launch than two mode products, which spread them further)
+    if (!vec && planes < 16) return false;
     if (planes > 0x3fffffffLL) return false;
     ZPlanesJob jb;
     std::memset(&jb, 0, sizeof(jb));
     jb.S = S; jb.U3 = U3; jb.U4 = U4; jb.Z = Z; jb.planes = planes; jb.H = H; jb.W = W; jb.r3 = r3; jb.r4 = r4;
-    const int hb = (H + 15) / 16, wb = (W + 15) / 16;
+    jb.hbs = H <= 16 ? 1 : (H <= 32 ? 2 : 4);
+    const long long per = 4 / jb.hbs;
+    jb.blocks = (int)((planes + per - 1) / per);
+    const int wb = (W + 15) / 16;
     *out = Item();
     out->kind = IT_Z_PLANES;
-    out->key = (unsigned)wb;
-    out->nblocks = (int)planes;
-    (void)hb;
-    std::snprintf(out->label, sizeof(out->label), "k_z_planes<%d>", wb);
+    out->key = (unsigned)wb | (vec ? 16u : 0u);
+    out->nblocks = jb.blocks;
+    std::snprintf(out->label, sizeof(out->label), vec ? "k_z_planes<%d>" : "k_z_planes<%d, false>", wb);
     static_assert(sizeof(ZPlanesJob) <= kItemArgMax, "argument block");
     std::memcpy(out->arg, &jb, sizeof(jb));
     return true;
@@ -1002,11 +907,15 @@ hipError_t launch_z_planes_items(const Item* const* items, int n, hipStream_t st
         std::memcpy(&zj, items[j]->arg, sizeof(zj));
         if (zj.H > 64 || zj.W > 16 * wb || zj.r3 > 32 || zj.r4 > 32) return hipErrorInvalidValue;
     }
-    switch (wb) {
-        case 1: hipLaunchKernelGGL((k_z_planes<1>), grid, 256, 0, st, b); return hipGetLastError();
-        case 2: hipLaunchKernelGGL((k_z_planes<2>), grid, 256, 0, st, b); return hipGetLastError();
-        case 3: hipLaunchKernelGGL((k_z_planes<3>), grid, 256, 0, st, b); return hipGetLastError();
-        case 4: hipLaunchKernelGGL((k_z_planes<4>), grid, 256, 0, st, b); return hipGetLastError();
+    switch (key) {
+        case 1: hipLaunchKernelGGL((k_z_planes<1, false>), grid, 256, 0, st, b); return hipGetLastError();
+        case 2: hipLaunchKernelGGL((k_z_planes<2, false>), grid, 256, 0, st, b); return hipGetLastError();
+        case 3: hipLaunchKernelGGL((k_z_planes<3, false>), grid, 256, 0, st, b); return hipGetLastError();
+        case 4: hipLaunchKernelGGL((k_z_planes<4, false>), grid, 256, 0, st, b); return hipGetLastError();
+        case 17: hipLaunchKernelGGL((k_z_planes<1, true>), grid, 256, 0, st, b); return hipGetLastError();
+        case 18: hipLaunchKernelGGL((k_z_planes<2, true>), grid, 256, 0, st, b); return hipGetLastError();
+        case 19: hipLaunchKernelGGL((k_z_planes<3, true>), grid, 256, 0, st, b); return hipGetLastError();
+        case 20: hipLaunchKernelGGL((k_z_planes<4, true>), grid, 256, 0, st, b); return hipGetLastError();
         default: break;
     }
     return hipErrorInvalidValue;
@@ -1018,7 +927,8 @@ hipError_t launch_z_planes_items(const Item* const* items, int n, hipStream_t st
 // The mirror image of k_z_planes.  Wave w takes rows h = 16 w .. 16 w + 15 of the plane:
 //   T1[h, q]  = sum_w X[h, w] U4[w, q]           A = X (row h = ll, 16-byte loads of four w), B = U4
 //   Yw[a, q]  = sum_{h of the wave} U3[h, a] T1[h, q]     A = U3^T (row a = ll), B = T1: register s of the first result
-// and the four partial Y's are added through LDS in the order of the waves.
+// and the partial Y's of a plane's waves are added through LDS in their order.  A plane of up to 16 rows has one wave, four of them a
+// workgroup.  VEC: W is a multiple of four and X aligned.
 struct CorePlanesJob {
     const float* X;
     const float* U3;
@@ -1026,18 +936,20 @@ struct CorePlanesJob {
     float* Y;
     long long planes;
     int H, W, r3, r4;
+    int hbs;             // waves of a plane: 1, 2 or 4
 };
 
-template <int WB>
+template <int WB, bool VEC>
 __global__ __launch_bounds__(256) void k_core_planes(Batch<CorePlanesJob> bt) {
     typedef float v4f __attribute__((ext_vector_type(4)));
     __shared__ float red[4][32][33];
     int lb;
     const CorePlanesJob& jb = bt.job[locate(bt, &lb)];
     const int tid = threadIdx.x, lane = tid & 63, lg = lane >> 4, ll = lane & 15;
-    const int hb = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), hbs = jb.hbs, hb = wave & (hbs - 1), per = 4 / hbs;
     const int H = jb.H, W = jb.W, r3 = jb.r3, r4 = jb.r4;
-    const float* __restrict__ Xp = jb.X + (long long)lb * H * W;
+    const long long plane0 = (long long)lb * per, plane = plane0 + wave / hbs;
+    const float* __restrict__ Xp = jb.X + (plane < jb.planes ? plane : plane0) * H * W;      // (past the end: dropped)
     const int h = 16 * hb + ll;
 
     // operands: all loads first, from addresses valid for every lane; masked afterwards
@@ -1047,7 +959,10 @@ __global__ __launch_bounds__(256) void k_core_planes(Batch<CorePlanesJob> bt) {
 #pragma unroll
     for (int wb = 0; wb < WB; ++wb) {
         const int w0 = 16 * wb + 4 * lg;
-        xa[wb] = *reinterpret_cast<const v4f*>(Xp + ((h < H && w0 < W) ? h * W + w0 : 0));
+        if (VEC) xa[wb] = *reinterpret_cast<const v4f*>(Xp + ((h < H && w0 < W) ? h * W + w0 : 0));
+        else
+#pragma unroll
+            for (int s_ = 0; s_ < 4; ++s_) xa[wb][s_] = Xp[(h < H && w0 + s_ < W) ? h * W + w0 + s_ : 0];
     }
 #pragma unroll
     for (int wb = 0; wb < WB; ++wb)
@@ -1067,7 +982,12 @@ __global__ __launch_bounds__(256) void k_core_planes(Batch<CorePlanesJob> bt) {
         }
     const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int wb = 0; wb < WB; ++wb) xa[wb] = (h < H && 16 * wb + 4 * lg < W) ? xa[wb] : zero4;      // W is a multiple of 4
+    for (int wb = 0; wb < WB; ++wb) {
+        if (VEC) xa[wb] = (h < H && 16 * wb + 4 * lg < W) ? xa[wb] : zero4;
+        else
+#pragma unroll
+            for (int s_ = 0; s_ < 4; ++s_) xa[wb][s_] = (h < H && 16 * wb + 4 * lg + s_ < W) ? xa[wb][s_] : 0.f;
+    }
 #pragma unroll
     for (int wb = 0; wb < WB; ++wb)
 #pragma unroll
@@ -1103,12 +1023,23 @@ __global__ __launch_bounds__(256) void k_core_planes(Batch<CorePlanesJob> bt) {
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) red[hb][16 * ab + 4 * lg + e][16 * qb + ll] = y[ab][qb][e];
+            for (int e = 0; e < 4; ++e) red[wave][16 * ab + 4 * lg + e][16 * qb + ll] = y[ab][qb][e];
     __syncthreads();
-    float* __restrict__ Yp = jb.Y + (long long)lb * r3 * r4;
-    for (int e = tid; e < r3 * r4; e += 256) {
-        const int a = e / r4, q = e - a * r4;
-        Yp[e] = ((red[0][a][q] + red[1][a][q]) + red[2][a][q]) + red[3][a][q];
+    const int sz = r3 * r4;
+    float* __restrict__ Yp = jb.Y + plane0 * sz;
+    if (hbs == 4) {                                        // uniform
+        for (int e = tid; e < sz; e += 256) {
+            const int a = e / r4, q = e - a * r4;
+            Yp[e] = ((red[0][a][q] + red[1][a][q]) + red[2][a][q]) + red[3][a][q];
+        }
+        return;
+    }
+    const int left = (int)(jb.planes - plane0 < per ? jb.planes - plane0 : per);
+    for (int e = tid; e < left * sz; e += 256) {
+        const int pl = e / sz, a = (e - pl * sz) / r4, q = e - pl * sz - a * r4;
+        float v = red[pl * hbs][a][q];
+        for (int w = 1; w < hbs; ++w) v += red[pl * hbs + w][a][q];
+        Yp[e] = v;
     }
 }
 
@@ -1116,16 +1047,18 @@ bool make_core_planes(const float* X, long long planes, int H, int W, const floa
                       Item* out) {
     if (!X || !U3 || !U4 || !Y || planes <= 0 || planes > 0x3fffffffLL) return false;
     if (H < 1 || W < 1 || H > 64 || W > 64 || r3 < 1 || r4 < 1 || r3 > 32 || r4 > 32) return false;
-    if (W % 4 != 0 || reinterpret_cast<uintptr_t>(X) % 16 != 0) return false;
+    const bool vec = W % 4 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0;
     CorePlanesJob jb;
     std::memset(&jb, 0, sizeof(jb));
     jb.X = X; jb.U3 = U3; jb.U4 = U4; jb.Y = Y; jb.planes = planes; jb.H = H; jb.W = W; jb.r3 = r3; jb.r4 = r4;
+    jb.hbs = H <= 16 ? 1 : (H <= 32 ? 2 : 4);
+    const long long per = 4 / jb.hbs;
     const int wb = (W + 15) / 16;
     *out = Item();
     out->kind = IT_CORE_PLANES;
-    out->key = (unsigned)wb;
-    out->nblocks = (int)planes;
-    std::snprintf(out->label, sizeof(out->label), "k_core_planes<%d>", wb);
+    out->key = (unsigned)wb | (vec ? 16u : 0u);
+    out->nblocks = (int)((planes + per - 1) / per);
+    std::snprintf(out->label, sizeof(out->label), vec ? "k_core_planes<%d>" : "k_core_planes<%d, false>", wb);
     static_assert(sizeof(CorePlanesJob) <= kItemArgMax, "argument block");
     std::memcpy(out->arg, &jb, sizeof(jb));
     return true;
@@ -1141,11 +1074,15 @@ hipError_t launch_core_planes_items(const Item* const* items, int n, hipStream_t
         std::memcpy(&cj, items[j]->arg, sizeof(cj));
         if (cj.H > 64 || cj.W > 16 * wb || cj.r3 > 32 || cj.r4 > 32) return hipErrorInvalidValue;
     }
-    switch (wb) {
-        case 1: hipLaunchKernelGGL((k_core_planes<1>), grid, 256, 0, st, b); return hipGetLastError();
-        case 2: hipLaunchKernelGGL((k_core_planes<2>), grid, 256, 0, st, b); return hipGetLastError();
-        case 3: hipLaunchKernelGGL((k_core_planes<3>), grid, 256, 0, st, b); return hipGetLastError();
-        case 4: hipLaunchKernelGGL((k_core_planes<4>), grid, 256, 0, st, b); return hipGetLastError();
+    switch (items[0]->key) {
+        case 1: hipLaunchKernelGGL((k_core_planes<1, false>), grid, 256, 0, st, b); return hipGetLastError();
+        case 2: hipLaunchKernelGGL((k_core_planes<2, false>), grid, 256, 0, st, b); return hipGetLastError();
+        case 3: hipLaunchKernelGGL((k_core_planes<3, false>), grid, 256, 0, st, b); return hipGetLastError();
+        case 4: hipLaunchKernelGGL((k_core_planes<4, false>), grid, 256, 0, st, b); return hipGetLastError();
+        case 17: hipLaunchKernelGGL((k_core_planes<1, true>), grid, 256, 0, st, b); return hipGetLastError();
+        case 18: hipLaunchKernelGGL((k_core_planes<2, true>), grid, 256, 0, st, b); return hipGetLastError();
+        case 19: hipLaunchKernelGGL((k_core_planes<3, true>), grid, 256, 0, st, b); return hipGetLastError();
+        case 20: hipLaunchKernelGGL((k_core_planes<4, true>), grid, 256, 0, st, b); return hipGetLastError();
         default: break;
     }
     return hipErrorInvalidValue;

@@ -20,6 +20,7 @@
 #include "asi_device.h"
 #include "asi_kernels.h"
 #include "asi_lds.h"
+#include "asi_zplanes.h"
 
 #include <cstdio>
 #include <cstring>
@@ -279,10 +280,10 @@ __global__ __launch_bounds__(256) void k_ttm_mfma(Batch<TtmJob> bt) {
 }
 
 // Two independent products in one launch: a plain product along a leading mode (G1 = grad_out x_1 U1^T
-// of Eq. 14) and, in extra workgroups, a small merged product of fp32 data (Z = S x_3 U3 x_4 U4).
+// of Eq. 14) and, in extra workgroups, Z = S x_3 U3 x_4 U4 plane by plane.
 struct TtmDuoJob {
     TtmJob a;        // dtype T, not the last mode, plain matrix, NBR column blocks
-    TtmJob z;        // fp32, trailing modes merged by a Kronecker product, K chunks of 32
+    ZPlanesJob z;
     int a_blocks;
 };
 template <typename T, int NBR>
@@ -291,7 +292,7 @@ __global__ __launch_bounds__(256) void k_ttm_duo(Batch<TtmDuoJob> bt) {
     int lb;
     const TtmDuoJob& jb = bt.job[locate(bt, &lb)];
     if (lb < jb.a_blocks) ttm_tile<T, false, NBR, 0>(jb.a, xcd_order(lb, jb.a_blocks), smem);
-    else ttm_tile<float, true, 4, 1>(jb.z, lb - jb.a_blocks, smem);
+    else z_planes_block<0, false>(jb.z, lb - jb.a_blocks);
 }
 
 // ---- long fibres, few columns ------------------------------------------------------------------
@@ -714,13 +715,13 @@ static bool fill_ttm(DType xt, const void* X, long long outer, int n, long long 
 }
 
 bool make_ttm(DType xt, const void* X, long long outer, int n, long long inner, const float* Mp, long long ms_i,
-              long long ms_q, int r, float* Y, int beta, Item* out, bool stream_ok) {
+              long long ms_q, int r, float* Y, int beta, Item* out) {
     const KronSpec none = {nullptr, 0, 0, 1, 1};
     const long long ncols = outer * inner;
     const bool thin = n <= 16 && r <= 16 && ncols >= (1LL << 18);
     // the streaming kernel pays once the tensor is large enough to keep the chip busy with its loads
     // (the split kernel's 16-column workgroups spread few columns further: it keeps the products below 256 spans)
-    if (stream_ok && inner > 1 && !thin && ncols * n >= kStreamMinElems && (ncols >= 256 * 64 || !prefer_ksplit(ncols, n, inner)) &&
+    if (inner > 1 && !thin && ncols * n >= kStreamMinElems && (ncols >= 256 * 64 || !prefer_ksplit(ncols, n, inner)) &&
         ttm_stream_supported(xt, X, outer, n, inner, Mp, ms_i, ms_q, r, Y))
         return make_ttm_stream(xt, X, outer, n, inner, Mp, ms_i, ms_q, r, Y, beta, out);
     return fill_ttm(xt, X, outer, n, inner, Mp, ms_i, ms_q, r, Y, beta, none, out);
@@ -761,15 +762,15 @@ static hipError_t launch_split(int cb, bool contig, const Batch<TtmJob>& b, dim3
     return hipErrorInvalidValue;
 }
 
-// a: a tiled plain product that is not along the last mode; z: a Kronecker product with short K.
-// Fails (and leaves *out alone) if the two do not have these forms; the caller then launches them apart.
+// a: a tiled plain product that is not along the last mode, or a streaming one; z: planes (make_z_planes).  Fails (and leaves *out
+// alone) if they do not have these forms; the caller then launches them apart.
 bool make_ttm_duo(const Item& a, const Item& z, Item* out) {
-    if (a.kind != IT_TTM || z.kind != IT_TTM) return false;
-    if ((a.key & 0xe00eu) != 0u) return false;                 // not last mode, plain, tiled, chunks of 32
-    if ((z.key & 0x600fu) != (2u | 4u)) return false;          // fp32, last mode, Kronecker, tiled, chunks of 32
+    if (z.kind != IT_Z_PLANES) return false;
+    if (a.kind == IT_TTM_STREAM) return make_ttm_stream_duo(a, z, out);
+    if (a.kind != IT_TTM || (a.key & 0xc00eu) != 0u) return false;       // not last mode, plain, tiled, chunks of 32
     TtmDuoJob jb;
     std::memcpy(&jb.a, a.arg, sizeof(TtmJob));
-    std::memcpy(&jb.z, z.arg, sizeof(TtmJob));
+    std::memcpy(&jb.z, z.arg, sizeof(ZPlanesJob));
     jb.a_blocks = a.nblocks;
     if ((long long)a.nblocks + z.nblocks > 0x3fffffffLL) return false;
     const int nbr = (int)((a.key >> 4) & 7u) + 1;

@@ -25,7 +25,9 @@
 #include "asi_device.h"
 #include "asi_kernels.h"
 #include "asi_lds.h"
+#include "asi_zplanes.h"
 
+#include <cstddef>
 #include <cstdio>
 #include <cstring>
 #include <type_traits>
@@ -39,6 +41,14 @@ constexpr size_t TS_LDS_MAX = 96 * 1024;     // of the CU's 160 KB: a 512-long m
 
 extern __shared__ __align__(16) float ts_dyn[];
 
+// A streaming product and, in extra workgroups (none: z.blocks = 0), Z of Eq. 14 plane by plane, which G1 does not depend on.  They
+// come first, so that none of them starts when the product is nearly done.  G1 and Z of 14 x 14 15.9 -> 9.0 us, of three 7 x 7 layers
+// 16.0 -> 14.2, of 960 x 7 x 7 at batch 128 14.1 -> 13.9 (tiled, with Z as one product with the factors' Kronecker product, before).
+struct TtmStreamJob {
+    TtmJob a;
+    ZPlanesJob z;
+};
+
 template <typename T> struct StreamPiece { typedef v4f type; };
 template <> struct StreamPiece<bf16_t> { typedef uint2 type; };
 __device__ __forceinline__ v4f stream_widen(const v4f& p) { return p; }
@@ -50,12 +60,15 @@ __device__ __forceinline__ v4f stream_widen(const uint2& p) {
 }
 
 template <typename T, int NBR, int KW>
-__global__ __launch_bounds__(256, 2) void k_ttm_stream(Batch<TtmJob> bt) {
+__global__ __launch_bounds__(256, 2) void k_ttm_stream(Batch<TtmStreamJob> bt) {
     typedef typename StreamPiece<T>::type P;
     constexpr int SPANS = 4 / KW, QP = 16 * NBR;
     constexpr int RB = NBR <= 3 ? 4 : 2;                // rounds (of 16 rows) whose loads are in flight together
     int lb;
-    const TtmJob& jb = bt.job[locate_xcd(bt, &lb)];
+    const TtmStreamJob& sj = bt.job[locate(bt, &lb)];
+    if (lb < sj.z.blocks) { z_planes_block<0, false>(sj.z, lb); return; }
+    const TtmJob& jb = sj.a;
+    lb = xcd_order(lb - sj.z.blocks, jb.gx);
     const T* __restrict__ X = static_cast<const T*>(jb.X);
     const float* __restrict__ Mp = jb.Mp;
     float* __restrict__ Y = jb.Y;
@@ -532,13 +545,27 @@ bool make_ttm_stream(DType xt, const void* X, long long outer, int n, long long 
     if (wide) std::snprintf(out->label, sizeof(out->label), "k_ttm_stream_bf16<%d, %d>", nbr, kw);
     else if (shrt) std::snprintf(out->label, sizeof(out->label), "k_ttm_stream_short<%s, %d>", xt == F32 ? "float" : "asi::bf16_t", nbr);
     else std::snprintf(out->label, sizeof(out->label), "k_ttm_stream<%s, %d, %d>", xt == F32 ? "float" : "asi::bf16_t", nbr, kw);
-    static_assert(sizeof(TtmJob) <= kItemArgMax, "argument block");
+    static_assert(sizeof(TtmStreamJob) <= kItemArgMax, "argument block");
+    std::memset(out->arg, 0, sizeof(TtmStreamJob));
     std::memcpy(out->arg, &jb, sizeof(jb));
     return true;
 }
 
+bool make_ttm_stream_duo(const Item& a, const Item& z, Item* out) {
+    if (a.kind != IT_TTM_STREAM || z.kind != IT_Z_PLANES || ((a.key >> 12) & 3u) != 0u) return false;
+    // (not the bf16 form, and not the short one, whose workgroups are shorter than a plane takes: 17.0 + 6.1 us apart, 24.2 together)
+    if ((long long)a.nblocks + z.nblocks > 0x3fffffffLL) return false;
+    Item it = a;
+    std::memcpy(it.arg + offsetof(TtmStreamJob, z), z.arg, sizeof(ZPlanesJob));
+    it.nblocks = a.nblocks + z.nblocks;
+    std::snprintf(it.role, sizeof(it.role), "%s+%s", a.role, z.role);
+    it.bytes = a.bytes + z.bytes; it.flops = a.flops + z.flops;
+    *out = it;
+    return true;
+}
+
 template <typename T, int NBR, int KW>
-static hipError_t launch_stream_one(const Batch<TtmJob>& b, dim3 grid, size_t lds, hipStream_t st) {
+static hipError_t launch_stream_one(const Batch<TtmStreamJob>& b, dim3 grid, size_t lds, hipStream_t st) {
     if (lds > 65536) {                // more than a static array may take
         static LdsAllowed allowed;
         const hipError_t e = allow_lds(reinterpret_cast<const void*>(k_ttm_stream<T, NBR, KW>), TS_LDS_MAX, allowed);
@@ -548,7 +575,7 @@ static hipError_t launch_stream_one(const Batch<TtmJob>& b, dim3 grid, size_t ld
     return hipGetLastError();
 }
 template <typename T, int NBR>
-static hipError_t launch_stream_kw(int kw, const Batch<TtmJob>& b, dim3 grid, size_t lds, hipStream_t st) {
+static hipError_t launch_stream_kw(int kw, const Batch<TtmStreamJob>& b, dim3 grid, size_t lds, hipStream_t st) {
     if (kw == 1) return launch_stream_one<T, NBR, 1>(b, grid, lds, st);
     if (kw == 2) return launch_stream_one<T, NBR, 2>(b, grid, lds, st);
     return launch_stream_one<T, NBR, 4>(b, grid, lds, st);
@@ -564,7 +591,7 @@ static hipError_t launch_stream_short_t(int nbr, const Batch<TtmJob>& b, dim3 gr
     return hipGetLastError();
 }
 template <typename T>
-static hipError_t launch_stream_t(int nbr, int kw, const Batch<TtmJob>& b, dim3 grid, size_t lds, hipStream_t st) {
+static hipError_t launch_stream_t(int nbr, int kw, const Batch<TtmStreamJob>& b, dim3 grid, size_t lds, hipStream_t st) {
     switch (nbr) {
         case 1: return launch_stream_kw<T, 1>(kw, b, grid, lds, st);
         case 2: return launch_stream_kw<T, 2>(kw, b, grid, lds, st);
@@ -588,38 +615,52 @@ static hipError_t launch_stream_bf16(int kw, const Batch<TtmJob>& b, dim3 grid, 
     return kw == 4 ? launch_stream_bf16_one<NBR, 4>(b, grid, lds, st) : launch_stream_bf16_one<NBR, 8>(b, grid, lds, st);
 }
 
-hipError_t launch_ttm_stream_items(const Item* const* items, int n, hipStream_t st) {
+static hipError_t launch_stream_short_items(const Item* const* items, int n, hipStream_t st) {
+    Batch<TtmJob> b;
+    dim3 grid;
+    if (!gather(items, n, &b, &grid)) return hipErrorInvalidValue;
+    const unsigned key = items[0]->key;
+    const int nbr = (int)((key >> 4) & 7u) + 1;
+    // the short form holds exactly two rounds of a mode
+    for (int j = 0; j < n; ++j) {
+        TtmJob tj;
+        std::memcpy(&tj, items[j]->arg, sizeof(tj));
+        if (tj.n <= 16 || tj.n > 32 || tj.ms_i >= (1LL << 25)) return hipErrorInvalidValue;
+    }
+    if (key & 1u) return launch_stream_short_t<bf16_t>(nbr, b, grid, st);
+    return launch_stream_short_t<float>(nbr, b, grid, st);
+}
+static hipError_t launch_stream_bf16_items(const Item* const* items, int n, hipStream_t st) {
     Batch<TtmJob> b;
     dim3 grid;
     if (!gather(items, n, &b, &grid)) return hipErrorInvalidValue;
     const unsigned key = items[0]->key;
     const int nbr = (int)((key >> 4) & 7u) + 1, kw = (int)((key >> 8) & 15u);
-    if ((key >> 12) & 1u) {                             // the short form holds exactly two rounds of a mode
-        for (int j = 0; j < n; ++j) {
-            TtmJob tj;
-            std::memcpy(&tj, items[j]->arg, sizeof(tj));
-            if (tj.n <= 16 || tj.n > 32 || tj.ms_i >= (1LL << 25)) return hipErrorInvalidValue;
-        }
-        if (key & 1u) return launch_stream_short_t<bf16_t>(nbr, b, grid, st);
-        return launch_stream_short_t<float>(nbr, b, grid, st);
+    size_t lds = 0;
+    for (int j = 0; j < n; ++j) {
+        TtmJob tj;
+        std::memcpy(&tj, items[j]->arg, sizeof(tj));
+        if (tj.r > 16 * nbr) return hipErrorInvalidValue;
+        const size_t l = stream_bf16_lds(tj.n, tj.r);
+        lds = l > lds ? l : lds;
     }
-    if ((key >> 13) & 1u) {
-        size_t lds = 0;
-        for (int j = 0; j < n; ++j) {
-            TtmJob tj;
-            std::memcpy(&tj, items[j]->arg, sizeof(tj));
-            if (tj.r > 16 * nbr) return hipErrorInvalidValue;
-            const size_t l = stream_bf16_lds(tj.n, tj.r);
-            lds = l > lds ? l : lds;
-        }
-        if (lds > TS_LDS_MAX) return hipErrorInvalidValue;
-        switch (nbr) {
-            case 1: return launch_stream_bf16<1>(kw, b, grid, lds, st);
-            case 2: return launch_stream_bf16<2>(kw, b, grid, lds, st);
-            case 3: return launch_stream_bf16<3>(kw, b, grid, lds, st);
-            default: return launch_stream_bf16<4>(kw, b, grid, lds, st);
-        }
+    if (lds > TS_LDS_MAX) return hipErrorInvalidValue;
+    switch (nbr) {
+        case 1: return launch_stream_bf16<1>(kw, b, grid, lds, st);
+        case 2: return launch_stream_bf16<2>(kw, b, grid, lds, st);
+        case 3: return launch_stream_bf16<3>(kw, b, grid, lds, st);
+        default: return launch_stream_bf16<4>(kw, b, grid, lds, st);
     }
+}
+
+hipError_t launch_ttm_stream_items(const Item* const* items, int n, hipStream_t st) {
+    const unsigned key = items[0]->key;
+    if ((key >> 13) & 1u) return launch_stream_bf16_items(items, n, st);
+    if ((key >> 12) & 1u) return launch_stream_short_items(items, n, st);
+    Batch<TtmStreamJob> b;
+    dim3 grid;
+    if (!gather(items, n, &b, &grid)) return hipErrorInvalidValue;
+    const int nbr = (int)((key >> 4) & 7u) + 1, kw = (int)((key >> 8) & 15u);
     size_t lds = 0;
     for (int j = 0; j < n; ++j) {                       // items of one launch share the instantiation; the largest matrix sizes the LDS
         TtmJob tj;

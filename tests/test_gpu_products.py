@@ -105,3 +105,33 @@ def test_pair_product_at_the_edges_of_its_tiles(dims, ranks, mode, dtype, shift)
     assert float(torch.linalg.cond(p)) < 500
     err = float((out[mode] - want).abs().max() / want.abs().max())
     assert err <= (2e-4 if dtype == "bf16" and mode == len(dims) - 1 else 3e-5), err
+
+
+# Planes of one to four blocks of 16 rows and columns (one, two and four waves a plane; the last workgroup of planes not full), ranks of
+# one and two blocks that are no multiple of four; G1 streamed (a million entries of grad_out), tiled, and grad_out itself (r1 = B).
+@pytest.mark.parametrize("dims,ranks,cout", [
+    ((40, 9, 7, 7), (8, 5, 5, 5), 520), ((20, 6, 13, 17), (12, 5, 9, 17), 240), ((18, 7, 31, 18), (8, 5, 13, 6), 112), ((6, 8, 33, 50), (5, 7, 19, 31), 30),
+    ((64, 11, 14, 14), (16, 7, 7, 7), 100), ((5, 9, 64, 63), (5, 5, 29, 32), 11), ((9, 10, 2, 16), (5, 9, 2, 9), 33), ((33, 6, 49, 8), (4, 6, 6, 5), 90)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_plane_products_of_any_size(dims, ranks, cout, dtype):
+    """Core and 1 x 1 weight gradient against float64: chains of fp32 sums of at most 500 terms, 2e-6 of the largest entry per product."""
+    from paper_2505_05086_amd import binding as B
+    rng = np.random.default_rng(sum(dims) + sum(ranks))
+    x = _dev(rng.standard_normal(dims), dtype)
+    U = [_dev(np.linalg.qr(rng.standard_normal((n, r)))[0]) for n, r in zip(dims, ranks)]
+    desc, conv = B.make_desc(dims, ranks, dtype), B.make_conv(cout, 1, 1, (1, 1), (0, 0), (1, 1), 1)
+    S = torch.empty(ranks, device="cuda")
+    ws = B.alloc_workspace(desc, conv, 0)
+    ws.fill_(255)                                        # NaN wherever nothing was written
+    sites = _sites(lambda: B.asi_core_project(desc, x, U, S, ws))
+    want = _modes(x, U)
+    assert float((S - want).abs().max() / want.abs().max()) <= 5e-6
+    gy = _dev(rng.standard_normal((dims[0], cout) + dims[2:]), dtype)
+    dW = torch.empty(cout, dims[1], 1, 1, device="cuda")
+    ws.fill_(255)
+    sites = _sites(lambda: B.asi_weight_grad_conv2d(desc, S, U, gy, conv, dW, False, ws))
+    assert any("k_z_planes" in s or "+Z" in s for s in sites), sites
+    assert not any(s.endswith(":Z1") for s in sites), sites
+    xr = _modes(S, [u.t().contiguous() for u in U])
+    ref = gy.double().transpose(0, 1).reshape(cout, -1).contiguous() @ xr.transpose(0, 1).reshape(dims[1], -1).t().contiguous()
+    assert float((dW.view(cout, -1) - ref).abs().max() / ref.abs().max()) <= 1e-5
