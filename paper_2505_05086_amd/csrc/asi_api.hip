@@ -93,7 +93,7 @@ struct CompressPlan {
     bool gramm[4] = {};              // short mode, long inner extent: P = (A_m A_m^T) U_prev (asi_gram.hip)
     bool longm[4] = {};              // long fibres: V and P from one LDS tile of complete fibres (asi_long.hip)
     bool paired = false;             // the last two modes of a 4-mode tensor share one kernel
-    bool tiny = false;               // ... the vector-ALU kernel for tiny planes
+    bool tiny = false;               // ... the kernel for planes of up to 8 x 8
     bool planes = false;             // ... the Gram-matrix kernel for planes of up to 64 x 64 (asi_planes.hip)
     bool digm[4] = {};               // bf16: the step on the int8 MFMA (asi_digits.hip), through the Gram matrix or, with bfv, as a pair product
     unsigned* amax = nullptr;        // ... the tensor's largest magnitude, in parts
@@ -179,7 +179,7 @@ CompressPlan plan_with(const Shape& s, void* ws, bool cold, bool digits, bool co
     p.paired = p.tiny || p.planes;
     for (int m = 0; m < s.d; ++m) {
         const size_t n = (size_t)s.n[m], r = (size_t)s.r[m];
-        if (p.tiny && m >= 2) p.nsplit[m] = subspace_tiny_nwg(s.n[0] * s.n[1]);
+        if (p.tiny && m >= 2) p.nsplit[m] = subspace_tiny_nwg(s.dt, s.n[0] * s.n[1], (int)s.n[2], (int)s.n[3]);
         else if (p.planes && m >= 2) p.nsplit[m] = subspace_planes_nwg(s.dt, s.n[0] * s.n[1], (int)s.n[2], (int)s.n[3]);
         else if (p.digm[m] && p.bfv[m]) p.nsplit[m] = pair_digits_splits(s.numel / s.n[m], (int)n, (int)r);
         else if (p.digm[m]) {

@@ -194,6 +194,184 @@ __global__ __launch_bounds__(PN_NT, NB <= 2 ? 4 : 2) void k_subspace_planes(Batc
     gram_times_u<NB, 4>(red + 2 * role * NP * 256, U, n, r, jb.part[role] + (long long)lb * n * r, slot, lane, u);
 }
 
+// ---- planes of up to 8 x 8 (7 x 7 maps) --------------------------------------------------------------------
+// The same Gram matrices with TWO planes stacked in the 16 rows of an operand: the two 8 x 8 blocks on the diagonal of the 16 x 16
+// result are theirs, what lies off it is dropped, and a mode of a pair of planes costs two MFMAs (K slot (s, lg) is index 2 lg + s), a
+// quarter of what one plane a block of 16 x 16 x 16 takes.  Tiles of 16 KB go through a ring of four buffers, three of them on their
+// way; what a tile does not fill arrives as zeros, so that an odd last plane has a partner of zeros.
+// 122880 planes of 7 x 7 at rank 6 (24 MB): 128 cycles of MFMA a plane, 6.5 us; 19.8 -> 17.0 us against a thread per plane and mode on the
+// vector ALU, three batched layers of 32768 planes 21.8 -> 17.2.
+constexpr int TY_BUF = 16384, TY_RING = 4, TY_COPIES = TY_BUF / (16 * PN_NT);
+struct TinyJob {
+    const void* X;
+    long long planes, ntiles;
+    const float* U[2];    // (rows, r[0]) and (cols, r[1])
+    double* part[2];      // (nwg, rows, r[0]) and (nwg, cols, r[1])
+    int rows, cols, r[2];
+    int pt;               // planes per tile, a multiple of eight
+    int nwg;
+};
+
+template <typename T, bool DMA>
+__global__ __launch_bounds__(PN_NT, 4) void k_subspace_tiny(Batch<TinyJob> bt) {
+    int lb;
+    const TinyJob& jb = bt.job[locate(bt, &lb)];
+    const T* __restrict__ X = static_cast<const T*>(jb.X);
+    const int rows = jb.rows, cols = jb.cols, pe = rows * cols, pt = jb.pt;
+    const int tid = threadIdx.x, lane = tid & 63, lg = lane >> 4, ll = lane & 15;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int role = wv >> 2, slot = wv & 3;           // role 0: mode H (rows), role 1: mode W (cols)
+    auto elems_of = [&](long long t) __attribute__((always_inline)) {
+        const long long left = jb.planes - t * pt;
+        return left <= 0 ? 0 : (int)(left < pt ? left : pt) * pe;
+    };
+    auto fetch = [&](long long t, int b) __attribute__((always_inline)) {
+        const int elems = elems_of(t);
+        const T* src = X + (elems ? t * pt * pe : 0);
+        unsigned char* dst = pn_raw + b * TY_BUF;
+        if constexpr (DMA) {
+            const int whole = elems * (int)sizeof(T) & ~15;
+#pragma unroll
+            for (int u = 0; u < TY_COPIES; ++u)
+                copy16_to_lds(src, whole, (u * PN_NT + tid) * 16, dst + (u * PN_NT + 64 * wv) * 16);
+        } else {
+            constexpr int PER = TY_BUF / (int)sizeof(T) / PN_NT;
+            for (int u0 = 0; u0 < PER; u0 += 8) {      // element by element: a tensor aligned to its element only
+                T v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int e = (u0 + u) * PN_NT + tid;
+                    v[u] = src[e < elems ? e : 0];
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int e = (u0 + u) * PN_NT + tid;
+                    reinterpret_cast<T*>(dst)[e] = e < elems ? v[u] : T();
+                }
+            }
+        }
+    };
+    // this lane's two elements of a pair of planes: plane ll / 8, index ll % 8 of the mode, indices 2 lg and 2 lg + 1 of the other
+    const int k = role == 0 ? cols : rows, ks = role == 0 ? 1 : cols, ms = role == 0 ? cols : 1;
+    const bool in0 = 2 * lg < k, in1 = 2 * lg + 1 < k;
+    const int o0 = (ll >> 3) * pe + (ll & 7) * ms + (in0 ? 2 * lg : 0) * ks, o1 = (ll >> 3) * pe + (ll & 7) * ms + (in1 ? 2 * lg + 1 : 0) * ks;
+    v4d acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+
+    constexpr int AHEAD = DMA ? TY_RING - 1 : 1;       // tiles on their way
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) fetch(lb + (long long)u * jb.nwg, u);
+    int b = 0;
+    for (long long t = lb; t < jb.ntiles; t += jb.nwg) {
+        if constexpr (DMA) wait_copies_and_sync<(TY_RING - 2) * TY_COPIES>();
+        else __syncthreads();                          // tile t is in LDS; the buffer of the tile before is no longer read
+        fetch(t + (long long)AHEAD * jb.nwg, (b + AHEAD) & (TY_RING - 1));
+        const int elems = elems_of(t), np = elems / pe;
+        T* xb = reinterpret_cast<T*>(pn_raw + b * TY_BUF);
+        if (DMA && ((elems * (int)sizeof(T)) & 15)) {  // uniform: the end of the tensor, under 16 bytes past the last whole piece
+            const int e = (elems * (int)sizeof(T) & ~15) / (int)sizeof(T) + tid;
+            if (e < elems) xb[e] = X[t * pt * pe + e];
+            __syncthreads();
+        }
+        const T* q = xb + 2 * slot * pe;
+        const int pairs = ((np + 1) / 2 - slot + 3) / 4;        // of this wave: pairs slot, slot + 4, ..
+        int i = 0;
+        for (; i + 1 < pairs; i += 2) {
+            float x[4];
+            x[0] = to_f32(q[o0]); x[1] = to_f32(q[o1]); x[2] = to_f32(q[8 * pe + o0]); x[3] = to_f32(q[8 * pe + o1]);
+            const double d0 = in0 ? (double)x[0] : 0.0, d1 = in1 ? (double)x[1] : 0.0, d2 = in0 ? (double)x[2] : 0.0, d3 = in1 ? (double)x[3] : 0.0;
+            acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(d0, d0, acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(d2, d2, acc[1], 0, 0, 0);
+            acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(d1, d1, acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(d3, d3, acc[1], 0, 0, 0);
+            q += 16 * pe;
+        }
+        if (i < pairs) {
+            const float x0 = to_f32(q[o0]), x1 = to_f32(q[o1]);
+            const double d0 = in0 ? (double)x0 : 0.0, d1 = in1 ? (double)x1 : 0.0;
+            acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(d0, d0, acc[0], 0, 0, 0);
+            acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(d1, d1, acc[0], 0, 0, 0);
+        }
+        b = (b + 1) & (TY_RING - 1);
+    }
+    acc[0] += acc[1];
+    if constexpr (DMA) wait_copies_and_sync<0>();      // (the last copies write zeros into buffers that the sums take over)
+
+    // the four waves of a mode, both modes at once, as in k_subspace_planes; then the two diagonal blocks
+    double* red = reinterpret_cast<double*>(pn_raw);   // [2 modes][2][256]
+    const int n = role ? cols : rows, r = jb.r[role];
+    const float* __restrict__ U = jb.U[role];
+    float u[1][4];
+    gram_load_u<1>(U, n, r, slot, lane, u);
+    double* mine = red + (2 * role + (slot & 1)) * 256;
+    __syncthreads();                                   // the tiles are no longer read
+    if (slot >= 2) gram_put<1>(&acc[0], mine, lane);
+    __syncthreads();
+    if (slot < 2) gram_add<1>(&acc[0], mine, lane);
+    if (slot == 1) gram_put<1>(&acc[0], mine, lane);
+    __syncthreads();
+    if (slot == 0) {
+        gram_add<1>(&acc[0], mine + 256, lane);
+        gram_put<1>(&acc[0], mine, lane);
+    }
+    __syncthreads();
+    if (tid < 128) {
+        const int i = (tid >> 3) & 7, j = tid & 7;     // element (i, j) at (i / 4) 64 + (i % 4) 16 + j
+        double* g = red + 2 * (tid >> 6) * 256 + (i >> 2) * 64 + (i & 3) * 16 + j;
+        *g += g[128 + 8];
+    }
+    __syncthreads();
+    gram_times_u<1, 4>(red + 2 * role * 256, U, n, r, jb.part[role] + (long long)lb * n * r, slot, lane, u);
+}
+
+bool subspace_tiny_supported(int rows, int cols, int r_rows, int r_cols) {
+    return rows <= 8 && cols <= 8 && r_rows <= rows && r_cols <= cols;
+}
+static int tiny_pt(DType xt, int rows, int cols) {
+    // (an operand's rows past a plane reach up to 63 elements past the last one: they stay in the buffer)
+    const int pt = (TY_BUF - 256) / (rows * cols * (xt == F32 ? 4 : 2)) / 8 * 8;
+    return pt > 512 ? 512 : pt;
+}
+// two workgroups per CU are resident, and every one walks the same number of tiles
+int subspace_tiny_nwg(DType xt, long long planes, int rows, int cols) {
+    const long long pt = tiny_pt(xt, rows, cols), ntiles = (planes + pt - 1) / pt, per = (ntiles + 511) / 512;
+    return (int)((ntiles + per - 1) / per);
+}
+// key: [0] bf16, [1] memory-to-LDS copies
+bool make_subspace_tiny(DType xt, const void* X, long long planes, int rows, int cols, const float* U_rows, int r_rows,
+                        double* part_rows, const float* U_cols, int r_cols, double* part_cols, int nwg, Item* out) {
+    if (!subspace_tiny_supported(rows, cols, r_rows, r_cols) || !X || !U_rows || !U_cols || !part_rows || !part_cols)
+        return false;
+    if (planes < 1 || rows < 1 || cols < 1 || nwg != subspace_tiny_nwg(xt, planes, rows, cols)) return false;
+    TinyJob jb;
+    std::memset(&jb, 0, sizeof(jb));
+    jb.X = X; jb.planes = planes; jb.pt = tiny_pt(xt, rows, cols); jb.ntiles = (planes + jb.pt - 1) / jb.pt;
+    jb.U[0] = U_rows; jb.U[1] = U_cols; jb.part[0] = part_rows; jb.part[1] = part_cols;
+    jb.rows = rows; jb.cols = cols; jb.r[0] = r_rows; jb.r[1] = r_cols; jb.nwg = nwg;
+    *out = Item();
+    out->kind = IT_TINY;
+    const bool dma = reinterpret_cast<uintptr_t>(X) % 16 == 0;       // (a tile of a multiple of eight planes is a multiple of 16 bytes)
+    out->key = (xt == BF16 ? 1u : 0u) | (dma ? 2u : 0u);
+    out->nblocks = nwg;
+    std::snprintf(out->label, sizeof(out->label), "k_subspace_tiny<%s, %s>", xt == F32 ? "float" : "asi::bf16_t", dma ? "true" : "false");
+    static_assert(sizeof(TinyJob) <= kItemArgMax, "argument block");
+    std::memcpy(out->arg, &jb, sizeof(jb));
+    return true;
+}
+hipError_t launch_tiny_items(const Item* const* items, int n, hipStream_t st) {
+    Batch<TinyJob> b;
+    dim3 grid;
+    if (!gather(items, n, &b, &grid)) return hipErrorInvalidValue;
+    constexpr size_t lds = TY_RING * TY_BUF;
+    switch (items[0]->key) {
+        case 0: hipLaunchKernelGGL((k_subspace_tiny<float, false>), grid, PN_NT, lds, st, b); break;
+        case 1: hipLaunchKernelGGL((k_subspace_tiny<bf16_t, false>), grid, PN_NT, lds, st, b); break;
+        case 2: hipLaunchKernelGGL((k_subspace_tiny<float, true>), grid, PN_NT, lds, st, b); break;
+        case 3: hipLaunchKernelGGL((k_subspace_tiny<bf16_t, true>), grid, PN_NT, lds, st, b); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
 // ---- host side ---------------------------------------------------------------------------------
 bool subspace_planes_supported(long long planes, int rows, int cols, int r_rows, int r_cols) {
     if (planes < 1 || rows < 1 || rows > 64 || cols < 1 || cols > 64) return false;

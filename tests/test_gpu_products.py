@@ -135,3 +135,42 @@ def test_plane_products_of_any_size(dims, ranks, cout, dtype):
     xr = _modes(S, [u.t().contiguous() for u in U])
     ref = gy.double().transpose(0, 1).reshape(cout, -1).contiguous() @ xr.transpose(0, 1).reshape(dims[1], -1).t().contiguous()
     assert float((dW.view(cout, -1) - ref).abs().max() / ref.abs().max()) <= 1e-5
+
+
+def _check_factors(dims, ranks, modes, dtype, shift, label, tol):
+    from paper_2505_05086_amd import binding as B
+    rng = np.random.default_rng(sum(dims) + sum(ranks) + shift)
+    numel = int(np.prod(dims))
+    flat = _dev(rng.standard_normal(numel + 1), dtype)
+    x = flat[shift:shift + numel].view(dims)
+    U = [_dev(np.linalg.qr(rng.standard_normal((n, r)))[0]) for n, r in zip(dims, ranks)]
+    out = [torch.full_like(u, float("nan")) for u in U]
+    desc = B.make_desc(dims, ranks, dtype)
+    info = torch.full((1,), 7, dtype=torch.int32, device="cuda")
+    ws = B.alloc_workspace(desc, None, 0)
+    ws.fill_(255)
+    sites = _sites(lambda: B.asi_compress(desc, x, U, out, ws, info))
+    assert any(label in s for s in sites), sites
+    assert int(info) == 0
+    for m in modes:
+        a = x.double().movedim(m, 0).reshape(dims[m], -1)
+        p = a @ (a.t().contiguous() @ U[m].double())
+        q, r = torch.linalg.qr(p)
+        want = q * torch.sign(torch.diagonal(r))
+        assert float(torch.linalg.cond(p)) < 500
+        err = float((out[m] - want).abs().max() / want.abs().max())
+        assert err <= tol, (m, err)
+
+
+# Odd numbers of planes (two share an operand), a last tile that is not full, tiles whose bytes are no multiple of a copy's 16, one
+# plane, one row, one column, planes of 64 and of one element, the last rows of an operand past the planes; one element off.
+@pytest.mark.parametrize("dims,ranks", [
+    ((9, 9, 7, 7), (4, 5, 5, 5)), ((1, 163, 5, 5), (1, 9, 5, 3)), ((1, 1, 8, 8), (1, 1, 1, 1)), ((3, 701, 1, 8), (3, 7, 1, 8)), ((5, 103, 8, 3), (3, 4, 8, 3)),
+    ((67, 65, 6, 7), (9, 8, 1, 7)), ((1, 4099, 1, 1), (1, 1, 1, 1)), ((700, 31, 8, 8), (6, 5, 8, 8)), ((257, 129, 4, 2), (5, 6, 3, 2))])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_tiny_planes_at_the_edges_of_their_tiles(dims, ranks, dtype, shift):
+    """Sums in fp64 from the activation on: the factor is rounded to fp32 once, 1e-6 of its largest entry with a condition below 500
+    (2^-53 of P's entries times the condition's square, as the factorisation is of P's Gram matrix, is below 1e-10)."""
+    want = "k_subspace_tiny<%s, %s>" % ("float" if dtype == "f32" else "asi::bf16_t", "false" if shift else "true")
+    _check_factors(dims, ranks, (2, 3), dtype, shift, want, 1e-6)
