@@ -143,7 +143,7 @@ CompressPlan plan_with(const Shape& s, void* ws, bool cold, bool digits, bool co
     Carver c(ws);
     size_t vmax = 0;
     for (int m = 0; m < s.d; ++m) {
-        p.fused[m] = !cold && subspace_small_supported((int)s.n[m], s.r[m]);
+        p.fused[m] = !cold && subspace_small_supported(s.outer(m), (int)s.n[m], s.inner(m), s.r[m]);
         p.gramm[m] = p.fused[m] && subspace_gram_supported(s.outer(m), (int)s.n[m], s.inner(m), s.r[m]);
         p.longm[m] = !cold && !p.fused[m] && subspace_long_supported(s.outer(m), (int)s.n[m], s.inner(m), s.r[m]);
         if (!cold && !p.fused[m] && !p.longm[m]) vmax = std::max(vmax, (size_t)(s.numel / s.n[m]) * s.r[m]);
@@ -188,7 +188,7 @@ CompressPlan plan_with(const Shape& s, void* ws, bool cold, bool digits, bool co
         }
         else if (p.gramm[m]) p.nsplit[m] = subspace_gram_nwg(s.dt, s.outer(m), (int)n, s.inner(m));
         else if (p.longm[m]) p.nsplit[m] = subspace_long_splits(s.outer(m), (int)n, s.inner(m), (int)r);
-        else p.nsplit[m] = p.fused[m] ? subspace_small_nwg(s.outer(m), (int)n, s.inner(m))
+        else p.nsplit[m] = p.fused[m] ? subspace_small_nwg(s.outer(m), (int)n, s.inner(m), (int)r)
                                       : pair_splits(s.outer(m), (int)n, s.inner(m), (int)r, coarse);
         const size_t before = c.off;
         p.part[m] = c.take<double>((size_t)p.nsplit[m] * n * r);

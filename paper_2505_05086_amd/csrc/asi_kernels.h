@@ -245,8 +245,8 @@ bool make_pair_digits(const void* X, long long ncols, int n, const float* V, con
 hipError_t launch_digits_items(const Item* const* items, int n, hipStream_t st);
 
 // ---- fused V/P step for modes with n <= 64 (asi_subspace.hip): part is (nwg, n, r) fp64 ---------------
-bool subspace_small_supported(int n, int r);
-int subspace_small_nwg(long long outer, int n, long long inner);
+bool subspace_small_supported(long long outer, int n, long long inner, int r);
+int subspace_small_nwg(long long outer, int n, long long inner, int r);
 bool make_subspace_small(DType xt, const void* X, long long outer, int n, long long inner, const float* U, int r,
                          double* part, int nwg, int32_t* zero, int nzero, Item* out);
 // ---- fused V/P step for modes with 64 < n <= 512 and r <= 64 (asi_long.hip): part is (nsplit, n, r) fp64 -------

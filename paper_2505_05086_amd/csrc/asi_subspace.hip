@@ -41,15 +41,13 @@ struct SmallView {
     int sI;              // LDS stride between consecutive mode indices
     int div, mulA, mulB; // LDS offset of fibre c at mode index 0: (c / div) * mulA + (c % div) * mulB
     float inv_div;       // 1 / div: c stays below 2^14, so the rounded float quotient is exact
-    int cols_per_o;      // fibres one outer slice contributes (whole_o tiles)
+    int cols_per_o;      // fibres one outer slice contributes
 };
 struct SmallJob {
     const void* X;
-    long long outer;     // outer slices (whole_o) / rows of tiles
+    long long outer;     // outer slices
     long long o_elems;   // elements per outer slice
-    long long inner;     // whole_o == 0: row length; tile = To groups of (n rows x 128 columns), stacked in LDS
-    int whole_o, To;     // To: outer slices per tile (whole_o), else column groups per tile
-    long long tiles_per_o;
+    int To;              // outer slices per tile
     long long ntiles;
     int nwg;             // workgroups of this job; each walks tiles nwg apart
     int32_t* zero;       // nullable: `nzero` int32 to clear (arrival counters of the orth launches that follow)
@@ -58,7 +56,7 @@ struct SmallJob {
 };
 
 
-template <typename T, int NBM, int NBR, bool WHOLE_O, bool STACK = false>   // STACK: several column groups per tile
+template <typename T, int NBM, int NBR>
 __global__ __launch_bounds__(256, 2) void k_subspace_small(Batch<SmallJob> bt) {
     int lb;
     const SmallJob& jb = bt.job[locate(bt, &lb)];
@@ -96,89 +94,29 @@ __global__ __launch_bounds__(256, 2) void k_subspace_small(Batch<SmallJob> bt) {
 #pragma unroll
             for (int nb = 0; nb < NBR; ++nb) pacc[mb][nb] = (v4d){0.0, 0.0, 0.0, 0.0};
 
-    const int n0 = jb.v.n;
-    const int rowI = SS_TC + SS_PAD;
-    // Tiles of a long inner extent (!WHOLE_O): a short mode leaves most of the 64 LDS rows empty, so a tile
-    // takes To groups of 128 columns and stacks them: LDS row g * n + i holds mode index i of columns
-    // 128 g .. 128 g + 127.  The loads of a tile are issued (clamped, not branched, so that all stay in
-    // flight) while the previous tile is multiplied and stored to LDS when that is done.
-    T pre[WHOLE_O ? 1 : 32];
-    const float inv_n0 = 1.0f / (float)n0;
-    auto tile_origin = [&](long long tile, const T** src, int* vc) {
-        const int tcols = SS_TC * jb.To;
-        const long long o = tile / jb.tiles_per_o;
-        const long long j0 = (tile - o * jb.tiles_per_o) * tcols;
-        *vc = (int)((jb.inner - j0 < tcols) ? jb.inner - j0 : tcols);
-        *src = X + o * n0 * jb.inner + j0;
-    };
-    auto issue = [&](long long tile) {
-        const T* src;
-        int vc;
-        tile_origin(tile, &src, &vc);
-        const int c = tid & (SS_TC - 1);
-#pragma unroll
-        for (int u = 0; u < 32; ++u) {
-            const int row = (tid >> 7) + 2 * u;
-            if constexpr (!STACK) {      // one group: LDS row = mode index
-                pre[u] = src[(c < vc && row < n0) ? (long long)row * jb.inner + c : 0];
-            } else {
-                const int g = (int)(((float)row + 0.5f) * inv_n0), i = row - g * n0, col = g * SS_TC + c;
-                pre[u] = src[(g < jb.To && col < vc) ? (long long)i * jb.inner + col : 0];
-            }
-        }
-    };
-    auto commit = [&](long long tile) -> int {
-        const T* src;
-        int vc;
-        tile_origin(tile, &src, &vc);
-        const int c = tid & (SS_TC - 1);
-#pragma unroll
-        for (int u = 0; u < 32; ++u) {
-            const int row = (tid >> 7) + 2 * u;
-            if constexpr (!STACK) {
-                if (row < n0) smem[row * rowI + c] = (c < vc) ? to_f32(pre[u]) : 0.f;
-            } else {
-                const int g = (int)(((float)row + 0.5f) * inv_n0), col = g * SS_TC + c;
-                if (g < jb.To) smem[row * rowI + c] = (col < vc) ? to_f32(pre[u]) : 0.f;
-            }
-        }
-        return vc;
-    };
-    if constexpr (!WHOLE_O) {
-        if (lb < jb.ntiles) issue(lb);
-    }
     for (long long tile = lb; tile < jb.ntiles; tile += jb.nwg) {
         __syncthreads();   // everyone is done with the previous tile (and Us is written)
-        int no_or_vc;
-        if constexpr (WHOLE_O) {
-            // the whole tile is requested before any of it is stored: one memory latency per tile
-            const long long o0 = tile * jb.To;
-            const int no = (int)((jb.outer - o0 < jb.To) ? jb.outer - o0 : jb.To);
-            const int count = no * (int)jb.o_elems;
-            const T* src = X + o0 * jb.o_elems;
-            T prw[SS_PRE];
+        // the whole tile is requested before any of it is stored: one memory latency per tile
+        const long long o0 = tile * jb.To;
+        const int no = (int)((jb.outer - o0 < jb.To) ? jb.outer - o0 : jb.To);
+        const int count = no * (int)jb.o_elems;
+        const T* src = X + o0 * jb.o_elems;
+        T prw[SS_PRE];
 #pragma unroll
-            for (int u = 0; u < SS_PRE; ++u) {
-                const int e = u * 256 + tid;
-                prw[u] = src[e < count ? e : 0];          // clamped, not branched: all loads stay in flight
-            }
+        for (int u = 0; u < SS_PRE; ++u) {
+            const int e = u * 256 + tid;
+            prw[u] = src[e < count ? e : 0];          // clamped, not branched: all loads stay in flight
+        }
 #pragma unroll
-            for (int u = 0; u < SS_PRE; ++u) {
-                const int e = u * 256 + tid;
-                if (e < count) smem[e] = to_f32(prw[u]);
-            }
-            no_or_vc = no;
-        } else {
-            no_or_vc = commit(tile);
+        for (int u = 0; u < SS_PRE; ++u) {
+            const int e = u * 256 + tid;
+            if (e < count) smem[e] = to_f32(prw[u]);
         }
         __syncthreads();
-        if constexpr (!WHOLE_O) {
-            if (tile + jb.nwg < jb.ntiles) issue(tile + jb.nwg);
-        }
         {
             const SmallView& sv = jb.v;
             const int n = sv.n, sI = sv.sI;
-            const int valid_cols = WHOLE_O ? no_or_vc * sv.cols_per_o : no_or_vc;
+            const int valid_cols = no * sv.cols_per_o;
             // The loop body is free of branches and every group of LDS reads is issued before the
             // products that consume it, so that a fibre block pays LDS latency twice, not once per product.
             // B operands of step A do not depend on the fibre block (rows i >= n of Us are zero)
@@ -265,7 +203,11 @@ __global__ __launch_bounds__(256, 2) void k_subspace_small(Batch<SmallJob> bt) {
 }
 
 // ---- host side ---------------------------------------------------------------------
-bool subspace_small_supported(int n, int r) { return n <= 64 && r <= 64 && r <= n; }
+static bool cols_form(int n, long long inner, int r) { return n > 48 && r <= 16 && inner >= SS_TC; }
+bool subspace_small_supported(long long outer, int n, long long inner, int r) {
+    if (n > 64 || r > 64 || r > n) return false;
+    return inner < SS_TC || subspace_gram_supported(outer, n, inner, r) || cols_form(n, inner, r);
+}
 
 // Outer slices per tile when a tile is a run of whole slices: as many as the LDS buffer holds, but
 // no fewer than ~SS_MAX_WG tiles in all: the MFMA chains of a tile are latency bound, and only
@@ -277,82 +219,180 @@ static long long whole_To(long long outer, long long o_elems) {
     return To < 1 ? 1 : To;
 }
 
-// tile geometry of one mode seen as (outer, n, inner)
-static void single_geometry(long long outer, int n, long long inner, SmallJob* jb) {
-    jb->outer = outer; jb->inner = inner; jb->o_elems = (long long)n * inner;
-    if (inner < SS_TC && (long long)n * inner <= SS_LDS_FLOATS) {
-        long long To = whole_To(outer, (long long)n * inner);
-        jb->whole_o = 1; jb->To = (int)To; jb->tiles_per_o = 0;
-        jb->ntiles = (outer + To - 1) / To;
-    } else {
-        // groups of 128 columns per tile: as many as the 64 LDS rows hold, while ~SS_MAX_WG tiles remain
-        int G = 64 / n;
-        while (G > 1 && outer * ((inner + (long long)SS_TC * G - 1) / ((long long)SS_TC * G)) < SS_MAX_WG) --G;
-        if (G < 1) G = 1;
-        jb->whole_o = 0; jb->To = G;
-        jb->tiles_per_o = (inner + (long long)SS_TC * G - 1) / ((long long)SS_TC * G);
-        jb->ntiles = outer * jb->tiles_per_o;
+// ---- modes of 49 to 64 entries and up to 16 ranks over a long inner extent (asi_gram.hip takes the others) -----------------
+// Nothing goes through LDS: a wave takes 16 consecutive columns and loads them twice, in the two layouts that its products want:
+//   V (fp32 MFMA)  A operand (16 columns x 4 i):  row 4 s + lane / 16, column lane % 16           16 dwords
+//   P (fp64 MFMA)  A operand (16 i x 4 columns):  row 16 mb + lane % 16, columns 4 (lane / 16) + v   4 pieces of four columns
+// K slot (v, lane group) of the second product is column 4 lg + v, which is where the first product leaves V in register v.  The
+// second set of loads meets the lines of the first in the L1.  U_prev is in registers, no wave waits for another before the
+// sums at the end.  The form with a tile in LDS was bound by its loads, stores, reads and barriers (its products are 3 us):
+// three 64 x 512 x 7 x 7 layers at rank 8 in one launch 23.0 -> 14.5 us, 64 x 256 x 14 x 14 at rank 16 14.6 -> 10.4
+constexpr int SC_NT = 512, SC_NW = SC_NT / 64, SC_NB = 4;
+struct ColsJob {
+    const void* X;           // (outer, n, inner)
+    const float* U;          // (n, r)
+    double* part;            // (nwg, n, r)
+    long long outer, inner, nblk;    // blocks of 16 columns
+    int bpo;                 // blocks per outer slice
+    int n, r, nwg;
+    int32_t* zero;           // nullable: `nzero` int32 to clear
+    int nzero;
+};
+template <typename T> struct ColsPiece { typedef v4f type; };
+template <> struct ColsPiece<bf16_t> { typedef uint2 type; };
+__device__ __forceinline__ v4f cols_widen(const v4f& p) { return p; }
+__device__ __forceinline__ v4f cols_widen(const uint2& p) {
+    return (v4f){__uint_as_float(p.x << 16), __uint_as_float(p.x & 0xffff0000u), __uint_as_float(p.y << 16), __uint_as_float(p.y & 0xffff0000u)};
+}
+
+// VEC: the inner extent is a multiple of four and X is aligned to four elements
+template <typename T, bool VEC>
+__global__ __launch_bounds__(SC_NT, VEC ? 4 : 2) void k_subspace_cols(Batch<ColsJob> bt) {
+    __shared__ double red[SC_NW][SC_NB * 256];
+    int lb;
+    const ColsJob& jb = bt.job[locate_xcd(bt, &lb)];
+    const T* __restrict__ X = static_cast<const T*>(jb.X);
+    const int n = jb.n, r = jb.r, tid = threadIdx.x, lane = tid & 63, lg = lane >> 4, ll = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const long long inner = jb.inner, nblk = jb.nblk;
+    if (jb.zero && lb == 0 && tid < jb.nzero) jb.zero[tid] = 0;
+    const bool r_in = ll < r;
+    // B operand of the first product: U[4 s + lg][ll]
+    float u[4 * SC_NB];
+#pragma unroll
+    for (int s = 0; s < 4 * SC_NB; ++s) { const int i = 4 * s + lg; u[s] = jb.U[(i < n && r_in) ? i * r + ll : 0]; }
+    v4d acc[SC_NB];
+#pragma unroll
+    for (int mb = 0; mb < SC_NB; ++mb) acc[mb] = (v4d){0.0, 0.0, 0.0, 0.0};
+    // rows past the mode read the last one: masked in the first product, dropped in the second
+    const long long lastrow = (long long)(n - 1) * inner;
+    for (long long blk = (long long)lb * SC_NW + wave; blk < nblk; blk += (long long)jb.nwg * SC_NW) {
+        const long long o = blk / jb.bpo, j0 = (blk - o * jb.bpo) * 16;
+        const int left = (int)(inner - j0 < 16 ? inner - j0 : 16);           // columns of the block
+        const T* __restrict__ xb = X + o * (long long)n * inner + j0;
+        T xa[4 * SC_NB];
+        typename ColsPiece<T>::type xv[SC_NB];
+        T xs[VEC ? 1 : SC_NB][4];
+        const long long ca = (long long)lg * inner + (ll < left ? ll : 0);
+        const int c4 = 4 * lg < left ? 4 * lg : 0;
+#pragma unroll
+        for (int s = 0; s < 4 * SC_NB; ++s) xa[s] = 4 * s + 3 < 49 || 4 * s + lg < n ? xb[(long long)(4 * s) * inner + ca] : xb[lastrow + (ll < left ? ll : 0)];
+#pragma unroll
+        for (int mb = 0; mb < SC_NB; ++mb) {
+            const long long row = 16 * mb + ll < n ? (long long)(16 * mb + ll) * inner : lastrow;
+            if constexpr (VEC) xv[mb] = *reinterpret_cast<const typename ColsPiece<T>::type*>(xb + (row + c4));
+            else
+#pragma unroll
+                for (int v = 0; v < 4; ++v) xs[mb][v] = xb[row + (4 * lg + v < left ? 4 * lg + v : 0)];
+        }
+        v4f vacc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < 4 * SC_NB; ++s) {
+            const bool in = (4 * s + 3 < 49 || 4 * s + lg < n) && ll < left;
+            const float a = in ? to_f32(xa[s]) : 0.f;
+            const float b = (4 * s + 3 < 49 || 4 * s + lg < n) && r_in ? u[s] : 0.f;
+            vacc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, vacc, 0, 0, 0);
+        }
+        v4f x[SC_NB];
+#pragma unroll
+        for (int mb = 0; mb < SC_NB; ++mb) {
+            if constexpr (VEC) {
+                x[mb] = cols_widen(xv[mb]);
+                if (4 * lg >= left) x[mb] = (v4f){0.f, 0.f, 0.f, 0.f};
+            } else {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) x[mb][v] = 4 * lg + v < left ? to_f32(xs[mb][v]) : 0.f;
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const double b = (double)vacc[v];
+#pragma unroll
+            for (int mb = 0; mb < SC_NB; ++mb) acc[mb] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)x[mb][v], b, acc[mb], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int mb = 0; mb < SC_NB; ++mb)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) red[wave][mb * 256 + 64 * v + lane] = acc[mb][v];
+    __syncthreads();
+    double* out = jb.part + (long long)lb * n * r;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int e = tid + SC_NT * h, i = 16 * (e >> 8) + ((e >> 4) & 3) + 4 * ((e >> 6) & 3), q = e & 15;      // fp64 MFMA result layout
+        double s = red[0][e];
+#pragma unroll
+        for (int w = 1; w < SC_NW; ++w) s += red[w][e];
+        if (i < n && q < r) out[i * r + q] = s;
     }
 }
 
-int subspace_small_nwg(long long outer, int n, long long inner) {
-    SmallJob jb;
-    single_geometry(outer, n, inner, &jb);
-    // tiles of a long inner extent are prefetched behind the previous tile's products: two resident
-    // workgroups per CU, each walking several tiles, instead of further rounds of workgroups
-    const int cap = jb.whole_o ? SS_MAX_WG : SS_MAX_WG / 2;
-    return (int)(jb.ntiles < cap ? jb.ntiles : cap);
+static long long cols_blocks(long long outer, long long inner) { return outer * ((inner + 15) / 16); }
+
+// tile geometry of one mode seen as (outer, n, inner): runs of whole outer slices
+static void single_geometry(long long outer, int n, long long inner, SmallJob* jb) {
+    jb->outer = outer; jb->o_elems = (long long)n * inner;
+    const long long To = whole_To(outer, (long long)n * inner);
+    jb->To = (int)To;
+    jb->ntiles = (outer + To - 1) / To;
 }
 
-static bool finish_small(DType xt, SmallJob& jb, int nbm, int nbr, int nwg, Item* out) {
-    if (nbm < 1 || nbm > 4 || nbr < 1 || nbr > nbm || nwg <= 0 || nwg > jb.ntiles) return false;
-    jb.nwg = nwg;
+int subspace_small_nwg(long long outer, int n, long long inner, int r) {
+    if (cols_form(n, inner, r)) {
+        // a block per wave up to one workgroup a CU, beyond that every wave walks as many: 392 workgroups instead of 196 11.4 us
+        // against 10.4 (64 x 256 x 14 x 14), 98 15.6
+        const long long wgs = (cols_blocks(outer, inner) + SC_NW - 1) / SC_NW, per = (wgs + 255) / 256;
+        return (int)((wgs + per - 1) / per);
+    }
+    SmallJob jb;
+    single_geometry(outer, n, inner, &jb);
+    return (int)(jb.ntiles < SS_MAX_WG ? jb.ntiles : SS_MAX_WG);
+}
+
+// key: [0] bf16, [1] VEC (columns), [2] columns, [4..6] NBM, [8..10] NBR
+bool make_subspace_small(DType xt, const void* X, long long outer, int n, long long inner, const float* U, int r,
+                         double* part, int nwg, int32_t* zero, int nzero, Item* out) {
+    if (!subspace_small_supported(outer, n, inner, r) || !X || !U || !part || nzero < 0 || nzero > 256) return false;
+    if (nwg != subspace_small_nwg(outer, n, inner, r)) return false;
+    const char* tn = xt == F32 ? "float" : "asi::bf16_t";
     *out = Item();
     out->kind = IT_SMALL;
-    const bool stack = !jb.whole_o && jb.To > 1;
-    out->key = (xt == BF16 ? 1u : 0u) | (jb.whole_o ? 4u : 0u) | (stack ? 8u : 0u) |
-               ((unsigned)nbm << 4) | ((unsigned)nbr << 8);
     out->nblocks = nwg;
-    std::snprintf(out->label, sizeof(out->label), "k_subspace_small<%s, %d, %d, %s, %s>", xt == F32 ? "float" : "asi::bf16_t",
-                  nbm, nbr, jb.whole_o ? "true" : "false", stack ? "true" : "false");
+    if (cols_form(n, inner, r)) {
+        ColsJob jb;
+        std::memset(&jb, 0, sizeof(jb));
+        jb.X = X; jb.U = U; jb.part = part; jb.outer = outer; jb.inner = inner; jb.nblk = cols_blocks(outer, inner);
+        jb.bpo = (int)((inner + 15) / 16); jb.n = n; jb.r = r; jb.nwg = nwg; jb.zero = zero; jb.nzero = zero ? nzero : 0;
+        const bool vec = inner % 4 == 0 && reinterpret_cast<uintptr_t>(X) % (xt == F32 ? 16 : 8) == 0;
+        out->key = (xt == BF16 ? 1u : 0u) | (vec ? 2u : 0u) | 4u;
+        std::snprintf(out->label, sizeof(out->label), "k_subspace_cols<%s, %s>", tn, vec ? "true" : "false");
+        static_assert(sizeof(ColsJob) <= kItemArgMax, "argument block");
+        std::memcpy(out->arg, &jb, sizeof(jb));
+        return true;
+    }
+    SmallJob jb;
+    std::memset(&jb, 0, sizeof(jb));
+    jb.X = X; jb.zero = zero; jb.nzero = zero ? nzero : 0;
+    single_geometry(outer, n, inner, &jb);
+    jb.nwg = nwg;
+    SmallView& v = jb.v;
+    v.U = U; v.part = part; v.n = n; v.r = r;
+    v.sI = (int)inner; v.div = (int)inner; v.mulA = n * (int)inner; v.mulB = 1; v.cols_per_o = (int)inner;
+    v.inv_div = 1.0f / (float)v.div;
+    const int nbm = (n + 15) / 16, nbr = (r + 15) / 16;
+    out->key = (xt == BF16 ? 1u : 0u) | ((unsigned)nbm << 4) | ((unsigned)nbr << 8);
+    std::snprintf(out->label, sizeof(out->label), "k_subspace_small<%s, %d, %d>", tn, nbm, nbr);
     static_assert(sizeof(SmallJob) <= kItemArgMax, "argument block");
     std::memcpy(out->arg, &jb, sizeof(jb));
     return true;
 }
 
-bool make_subspace_small(DType xt, const void* X, long long outer, int n, long long inner, const float* U, int r,
-                         double* part, int nwg, int32_t* zero, int nzero, Item* out) {
-    if (!subspace_small_supported(n, r) || !X || !U || !part || nzero < 0 || nzero > 256) return false;
-    SmallJob jb;
-    std::memset(&jb, 0, sizeof(jb));
-    jb.X = X; jb.zero = zero; jb.nzero = zero ? nzero : 0;
-    single_geometry(outer, n, inner, &jb);
-    SmallView& v = jb.v;
-    v.U = U; v.part = part; v.n = n; v.r = r;
-    if (jb.whole_o) {
-        v.sI = (int)inner; v.div = (int)inner; v.mulA = n * (int)inner; v.mulB = 1; v.cols_per_o = (int)inner;
-    } else {
-        v.sI = SS_TC + SS_PAD; v.div = SS_TC; v.mulA = n * (SS_TC + SS_PAD); v.mulB = 1; v.cols_per_o = 0;   // group g starts n rows further down
-    }
-    v.inv_div = 1.0f / (float)v.div;
-    return finish_small(xt, jb, (n + 15) / 16, (r + 15) / 16, nwg, out);
-}
-
 template <typename T>
-static bool launch_small_t(const Batch<SmallJob>& b, dim3 grid, int nbm, int nbr, bool whole_o, bool stack, hipStream_t st) {
-    if (stack) {
-        if (whole_o || nbm > 2) return false;
-        if (nbm == 1 && nbr == 1) hipLaunchKernelGGL((k_subspace_small<T, 1, 1, false, true>), grid, 256, 0, st, b);
-        else if (nbm == 2 && nbr == 1) hipLaunchKernelGGL((k_subspace_small<T, 2, 1, false, true>), grid, 256, 0, st, b);
-        else if (nbm == 2 && nbr == 2) hipLaunchKernelGGL((k_subspace_small<T, 2, 2, false, true>), grid, 256, 0, st, b);
-        else return false;
-        return true;
-    }
-#define ASI_SS_CASE(M, R)                                                                                \
-    if (nbm == M && nbr == R) {                                                                          \
-        if (whole_o) hipLaunchKernelGGL((k_subspace_small<T, M, R, true>), grid, 256, 0, st, b);         \
-        else hipLaunchKernelGGL((k_subspace_small<T, M, R, false>), grid, 256, 0, st, b);                \
-        return true;                                                                                     \
+static bool launch_small_t(const Batch<SmallJob>& b, dim3 grid, int nbm, int nbr, hipStream_t st) {
+#define ASI_SS_CASE(M, R)                                                                      \
+    if (nbm == M && nbr == R) {                                                                \
+        hipLaunchKernelGGL((k_subspace_small<T, M, R>), grid, 256, 0, st, b);                  \
+        return true;                                                                           \
     }
     ASI_SS_CASE(1, 1) ASI_SS_CASE(2, 1) ASI_SS_CASE(2, 2) ASI_SS_CASE(3, 1) ASI_SS_CASE(3, 2)
     ASI_SS_CASE(3, 3) ASI_SS_CASE(4, 1) ASI_SS_CASE(4, 2) ASI_SS_CASE(4, 3) ASI_SS_CASE(4, 4)
@@ -361,13 +401,23 @@ static bool launch_small_t(const Batch<SmallJob>& b, dim3 grid, int nbm, int nbr
 }
 
 hipError_t launch_small_items(const Item* const* items, int n, hipStream_t st) {
-    Batch<SmallJob> b;
-    dim3 grid;
-    if (!gather(items, n, &b, &grid)) return hipErrorInvalidValue;
     const unsigned key = items[0]->key;
-    const bool bf16 = key & 1u, whole_o = key & 4u, stack = key & 8u;
+    dim3 grid;
+    if (key & 4u) {
+        Batch<ColsJob> b;
+        if (!gather(items, n, &b, &grid)) return hipErrorInvalidValue;
+        switch (key & 3u) {
+            case 0: hipLaunchKernelGGL((k_subspace_cols<float, false>), grid, SC_NT, 0, st, b); break;
+            case 1: hipLaunchKernelGGL((k_subspace_cols<bf16_t, false>), grid, SC_NT, 0, st, b); break;
+            case 2: hipLaunchKernelGGL((k_subspace_cols<float, true>), grid, SC_NT, 0, st, b); break;
+            default: hipLaunchKernelGGL((k_subspace_cols<bf16_t, true>), grid, SC_NT, 0, st, b); break;
+        }
+        return hipGetLastError();
+    }
+    Batch<SmallJob> b;
+    if (!gather(items, n, &b, &grid)) return hipErrorInvalidValue;
     const int nbm = (int)((key >> 4) & 7u), nbr = (int)((key >> 8) & 7u);
-    const bool ok = bf16 ? launch_small_t<bf16_t>(b, grid, nbm, nbr, whole_o, stack, st) : launch_small_t<float>(b, grid, nbm, nbr, whole_o, stack, st);
+    const bool ok = (key & 1u) ? launch_small_t<bf16_t>(b, grid, nbm, nbr, st) : launch_small_t<float>(b, grid, nbm, nbr, st);
     return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
 

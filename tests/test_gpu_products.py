@@ -174,3 +174,17 @@ def test_tiny_planes_at_the_edges_of_their_tiles(dims, ranks, dtype, shift):
     (2^-53 of P's entries times the condition's square, as the factorisation is of P's Gram matrix, is below 1e-10)."""
     want = "k_subspace_tiny<%s, %s>" % ("float" if dtype == "f32" else "asi::bf16_t", "false" if shift else "true")
     _check_factors(dims, ranks, (2, 3), dtype, shift, want, 1e-6)
+
+
+# Modes of 49 to 64 entries over a long inner extent: columns that are no multiple of four, of a block of 16, exactly whole blocks; one
+# block and more blocks than waves, several outer slices; ranks of one to a whole block; one element off.
+@pytest.mark.parametrize("dims,ranks,mode", [
+    ((49, 1, 1, 128), (1, 1, 1, 16), 0), ((64, 5, 3, 11), (16, 3, 3, 7), 0), ((50, 33, 7, 7), (9, 7, 5, 5), 0), ((64, 65, 14, 14), (16, 7, 5, 5), 0),
+    ((57, 700, 7, 7), (12, 6, 5, 5), 0), ((3, 63, 9, 17), (3, 13, 9, 7), 1), ((70, 53, 16, 16), (8, 16, 7, 7), 1), ((51, 1031, 129), (7, 9, 11), 0)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_subspace_step_of_49_to_64_entries(dims, ranks, mode, dtype, shift):
+    """V is fp32: 2^-24 of its entries, which the condition (below 500) takes to 3e-5 of the factor's largest entry."""
+    inner = int(np.prod(dims[mode + 1:]))
+    want = "k_subspace_cols<%s, %s>" % ("float" if dtype == "f32" else "asi::bf16_t", "false" if shift or inner % 4 else "true")
+    _check_factors(dims, ranks, (mode,), dtype, shift, want, 3e-5)
