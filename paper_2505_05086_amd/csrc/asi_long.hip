@@ -19,6 +19,12 @@
 // The matrix pipe and the vector ALU of a SIMD do not run side by side on this chip, so the loops hold
 // nothing but reads at immediate offsets, the widening of the A operand and the products.
 //
+// What bounds it: the products (20 us of MFMA cycles for 128 entries, rank 32 over 100352 columns), behind them a start in which a
+// workgroup waits for its first tile (64 KB per CU of 256 entries).  The first tile is requested before U_prev, only the rows past n
+// are cleared, partial V's lie 4 floats apart from a multiple of 16 and are added up in fours: 128 x 32 over 100352 columns 35.1 -> 33.6
+// us, 256 x 48 over 32768 33.3 -> 31.5, 83 x 21 over 21645 13.2 -> 12.0, 512 x 20 over 16384 in bf16 25.8 -> 24.5.  Tiles of half the
+// columns, two of them in LDS and V of the next made beside P of this one, with two barriers a tile instead of four: 33.8, 31.1, 11.7.
+//
 // A workgroup owns a run of consecutive tiles and a block of 16 NBQ columns of U; it writes one fp64
 // partial P (its rows x its columns) that the orthogonalisation sums in fixed order.
 #include "asi_device.h"
@@ -33,6 +39,7 @@ namespace asi {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef double v4d __attribute__((ext_vector_type(4)));
+typedef double v2d __attribute__((ext_vector_type(2)));
 
 constexpr int LG_NT = 512;                 // eight waves
 
@@ -58,8 +65,9 @@ struct LongShape {
     static constexpr int NROW = 128 * NRB;
     static constexpr int VQ = 16 * NBQ;
     static constexpr int XS = NROW * LD;              // floats
-    static constexpr int VP = 4 * TC * VQ;            // floats: four partial V
-    static constexpr int VD = 2 * TC * VQ;            // floats: V as doubles
+    static constexpr int VL = VQ + 4;                 // row pitch of a partial V: the four lane groups of a store on different banks
+    static constexpr int VP = 4 * TC * VL;            // floats: four partial V
+    static constexpr int VD = 2 * (TC * VQ + 3 * 16); // floats: V as doubles, 16 apart between quarters of the columns (lane groups again)
     static constexpr size_t lds_bytes = sizeof(float) * (size_t)(XS + VP + VD);
 };
 
@@ -89,7 +97,7 @@ __device__ __forceinline__ void long_store(float* dst, const P& v, bool ok) {
 template <typename T, int NRB, int NCB, int NBQ, bool VEC>
 __global__ __launch_bounds__(LG_NT) void k_subspace_long(Batch<LongJob> bt) {
     using SH = LongShape<NRB, NCB, NBQ>;
-    constexpr int TC = SH::TC, LD = SH::LD, VQ = SH::VQ, NROW = SH::NROW;
+    constexpr int TC = SH::TC, LD = SH::LD, VQ = SH::VQ, VL = SH::VL, NROW = SH::NROW;
     constexpr int HC = NCB / 2;                       // column blocks of a wave in step A
     constexpr int KSA = 8 * NRB;                      // K steps of a wave in step A (32 NRB rows)
     constexpr int W = VEC ? 4 : 1;                    // columns per piece
@@ -114,25 +122,11 @@ __global__ __launch_bounds__(LG_NT) void k_subspace_long(Batch<LongJob> bt) {
     const int t_beg = cg * jb.tpw;
     const int t_end = (t_beg + jb.tpw < jb.ntiles) ? t_beg + jb.tpw : jb.ntiles;
 
-    // rows of U this wave multiplies in step A: B operand (4 i x 16 q) of K step ks = U[32 NRB kq + 4 ks + lg][q0 + 16 nb + ll]
-    float ureg[KSA][NBQ];
-#pragma unroll
-    for (int ks = 0; ks < KSA; ++ks)
-#pragma unroll
-        for (int nb = 0; nb < NBQ; ++nb) {
-            const int i = 32 * NRB * kq + 4 * ks + lg, q = q0 + 16 * nb + ll;
-            const bool ok = (i < n) & (q < r);
-            const float u = jb.U[ok ? (long long)i * r + q : 0];
-            ureg[ks][nb] = ok ? u : 0.f;
-        }
     v4d pacc[NRB][NBQ];
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb)
 #pragma unroll
         for (int nb = 0; nb < NBQ; ++nb) pacc[rb][nb] = (v4d){0.0, 0.0, 0.0, 0.0};
-    // rows n .. NROW - 1 of the tile stay zero for the whole kernel
-    for (int e = tid; e < SH::XS; e += LG_NT) Xs[e] = 0.f;
-
     // loader: this thread's column of the tile and its first row; element offsets are 32-bit (host check)
     const int cl = W * (tid & (TC / W - 1)), r0 = tid / (TC / W);
     typename LongVec<T, VEC>::type pre[NLD];
@@ -153,7 +147,20 @@ __global__ __launch_bounds__(LG_NT) void k_subspace_long(Batch<LongJob> bt) {
             pre[u] = *reinterpret_cast<const typename LongVec<T, VEC>::type*>(X + (base + (unsigned)(i < n ? i : n - 1) * istep));   // clamped, not branched: all loads stay in flight
         }
     };
-    if (t_beg < t_end) fetch(t_beg);
+    if (t_beg < t_end) fetch(t_beg);                   // (before U_prev is asked for: the first tile is what a workgroup waits for)
+    // rows of U this wave multiplies in step A: B operand (4 i x 16 q) of K step ks = U[32 NRB kq + 4 ks + lg][q0 + 16 nb + ll]
+    float ureg[KSA][NBQ];
+#pragma unroll
+    for (int ks = 0; ks < KSA; ++ks)
+#pragma unroll
+        for (int nb = 0; nb < NBQ; ++nb) {
+            const int i = 32 * NRB * kq + 4 * ks + lg, q = q0 + 16 * nb + ll;
+            const bool ok = (i < n) & (q < r);
+            const float u = jb.U[ok ? (long long)i * r + q : 0];
+            ureg[ks][nb] = ok ? u : 0.f;
+        }
+    // rows n .. NROW - 1 of the tile stay zero for the whole kernel
+    for (int e = n * LD + tid; e < SH::XS; e += LG_NT) Xs[e] = 0.f;
     for (int t = t_beg; t < t_end; ++t) {
         __syncthreads();                               // the previous tile is no longer read
 #pragma unroll
@@ -184,25 +191,33 @@ __global__ __launch_bounds__(LG_NT) void k_subspace_long(Batch<LongJob> bt) {
                         vacc[cb][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[cb], ureg[ks][nb], vacc[cb][nb], 0, 0, 0);
             }
             // result layout: lane holds column 16 cb + 4 lg + v, output 16 nb + ll
-            float* vp = Vp + kq * (TC * VQ) + (16 * HC * ch + 4 * lg) * VQ + ll;
+            float* vp = Vp + kq * (TC * VL) + (16 * HC * ch + 4 * lg) * VL + ll;
 #pragma unroll
             for (int cb = 0; cb < HC; ++cb)
 #pragma unroll
                 for (int nb = 0; nb < NBQ; ++nb)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) vp[(16 * cb + v) * VQ + 16 * nb] = vacc[cb][nb][v];
+                    for (int v = 0; v < 4; ++v) vp[(16 * cb + v) * VL + 16 * nb] = vacc[cb][nb][v];
         }
         __syncthreads();
         // ---- V = sum of the four partial V's (fixed order), rounded to fp32 like a stored V, kept as doubles
-        for (int e = tid; e < TC * VQ; e += LG_NT) {
-            const float v = ((Vp[e] + Vp[TC * VQ + e]) + Vp[2 * TC * VQ + e]) + Vp[3 * TC * VQ + e];
-            Vd[e] = (double)v;
+#pragma unroll
+        for (int e0 = 0; e0 < TC * VQ / 4; e0 += LG_NT) {
+            const int e = e0 + tid, c = e / (VQ / 4), q = 4 * (e - c * (VQ / 4));
+            if (TC * VQ / 4 % LG_NT == 0 || e < TC * VQ / 4) {
+                const float* p = Vp + c * VL + q;
+                const v4f v = ((*reinterpret_cast<const v4f*>(p) + *reinterpret_cast<const v4f*>(p + TC * VL)) +
+                               *reinterpret_cast<const v4f*>(p + 2 * TC * VL)) + *reinterpret_cast<const v4f*>(p + 3 * TC * VL);
+                v2d* d = reinterpret_cast<v2d*>(Vd + c * VQ + 16 * (c / (TC / 4)) + q);
+                d[0] = (v2d){(double)v[0], (double)v[1]};
+                d[1] = (v2d){(double)v[2], (double)v[3]};
+            }
         }
         __syncthreads();
         // ---- step B: P[rows of this wave] += X V.  K slot (s, lg) is column lg TC/4 + s.
         {
             const float* xp = Xs + (16 * NRB * wv + ll) * LD + lg * (TC / 4);
-            const double* vd = Vd + (lg * (TC / 4)) * VQ + ll;
+            const double* vd = Vd + lg * (TC / 4 * VQ + 16) + ll;
 #pragma unroll
             for (int s4 = 0; s4 < TC / 16; ++s4) {
                 v4f xa[NRB];
