@@ -33,7 +33,7 @@ PEAK_TFLOPS = {"mfma_f32": 157.3, "mfma_f64": 78.6, "mfma_bf16": 2500.0, "mfma_i
                "mfma_f32+f64": 2.0 / (1.0 / 157.3 + 1.0 / 78.6), "valu_f32+f64": 2.0 / (1.0 / 157.3 + 1.0 / 78.6),
                "mfma_bf16+f64": 2.0 / (1.0 / 2500.0 + 1.0 / 78.6)}
 # which arithmetic unit each kernel symbol runs its contraction on; a symbol that is not listed is an error
-KERNEL_UNIT = {"k_subspace_small": "mfma_f32+f64", "k_subspace_tiny": "mfma_f64", "k_subspace_long": "mfma_f32+f64", "k_subspace_planes": "mfma_f64",
+KERNEL_UNIT = {"k_subspace_small": "mfma_f32+f64", "k_subspace_tiny": "mfma_f64", "k_subspace_cols": "mfma_f32+f64", "k_subspace_steps": "mfma_f64", "k_subspace_long": "mfma_f32+f64", "k_subspace_planes": "mfma_f64",
                "k_subspace_gram": "mfma_f64", "k_subspace_gram_digits": "mfma_i8", "k_pair_digits": "mfma_i8", "k_v_digits": "valu_f32", "k_v_max": "valu_f32", "k_amax_bf16": "valu_f32", "k_gauss_fill": "valu_f64",
                "k_ttm_mfma": "mfma_f32", "k_ttm_ksplit": "mfma_f32", "k_ttm_stream": "mfma_f32", "k_ttm_stream_short": "mfma_f32", "k_ttm_stream_bf16": "mfma_bf16", "k_ttm_expand": "mfma_f32", "k_ttm_duo": "mfma_f32", "k_ttm_thin": "valu_f32",
                "k_gemm_bf16": "mfma_bf16", "k_split_bf16": "valu_f32", "k_pair": "mfma_f64", "k_pair_vec": "mfma_f64",

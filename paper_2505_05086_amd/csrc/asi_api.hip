@@ -507,7 +507,7 @@ asi_status flush(std::vector<Program>& progs, hipStream_t st, const char* phase)
                 if (hipEventCreate(&rec.e0) != hipSuccess || hipEventCreate(&rec.e1) != hipSuccess) return ASI_ERR_HIP;
                 (void)hipEventRecord(rec.e0, st);
             }
-            char label[96];
+            char label[sizeof(Item::label)];
             if (launch_items(group, n, st, label) != hipSuccess) return ASI_ERR_HIP;
             if (prof) {
                 (void)hipEventRecord(rec.e1, st);
@@ -575,7 +575,18 @@ asi_status build_compress(const asi_tensor_desc* desc, const void* A, const floa
         ASI_ADD(pg, "", (double)s.numel * 2.0, 0.0, make_amax_bf16(A, s.numel, p.amax, p.ctr8, 4 * kOrthCtrs + 4, it__));
         zero_given = true;
     }
-    for (int k = 0; k < nord; ++k) {
+    const size_t steps_at = pg.items.size();
+    auto join = [&]() {                  // the step added last joins one before it where the two may share a launch
+        for (size_t i = steps_at; i + 1 < pg.items.size(); ++i) {
+            Item joined;
+            if (!join_steps(pg.items[i], pg.items.back(), &joined)) continue;
+            pg.items[i] = joined;
+            pg.items.pop_back();
+        }
+    };
+    for (int k = 0; k <= nord; ++k) {
+        join();
+        if (k == nord) break;
         const int m = order[k];
         const long long outer = s.outer(m), inner = s.inner(m);
         const int n = (int)s.n[m], r = s.r[m];

@@ -19,7 +19,7 @@ constexpr int kItemArgMax = 640;     // bytes of the largest per-layer argument 
 
 enum ItemKind {
     IT_TTM = 1, IT_KSPLIT, IT_PAIR, IT_SMALL, IT_PRESUM, IT_GRAM0, IT_APPLY, IT_ORTHW_GRAM, IT_ORTHW_CHOL,
-    IT_ORTHW_APPLY, IT_ORTH_BIG, IT_CORR_MFMA, IT_CORR, IT_SUM_F32, IT_SUM_F64, IT_EXPAND, IT_INIT, IT_TINY, IT_TTM_DUO, IT_TTM_STREAM, IT_TTM_EXPAND,
+    IT_ORTHW_APPLY, IT_ORTH_BIG, IT_CORR_MFMA, IT_CORR, IT_SUM_F32, IT_SUM_F64, IT_EXPAND, IT_INIT, IT_TINY, IT_STEPS, IT_TTM_DUO, IT_TTM_STREAM, IT_TTM_EXPAND,
     IT_LONG, IT_PLANES, IT_SPLIT_BF16, IT_GEMM_BF16, IT_GAUSS, IT_GRAM_MODE, IT_DW_FOLD, IT_Z_PLANES, IT_CORE_PLANES, IT_ORTHW_GSUM, IT_DIGITS
 };
 
@@ -28,14 +28,14 @@ struct Item {
     unsigned key = 0;        // instantiation within the kind
     int nblocks = 0;         // workgroups of this layer
     int aux = 0;             // kind specific (orth: final pass / pass number)
-    char label[96];          // kernel instantiation the way a profiler prints it
+    char label[160];         // kernel instantiation the way a profiler prints it
     char role[16];           // what the launch computes ("V", "core", "dW", ...), for timing reports
     double bytes = 0, flops = 0;   // what this launch must move / compute by its definition
     alignas(16) unsigned char arg[kItemArgMax];
 };
 
 // Launches items[0..n) as ONE kernel launch, n <= kMaxBatch; they must be mergeable (same_launch).
-// label_out (nullable, 96 bytes) receives the name of the instantiation that ran.
+// label_out (nullable, 160 bytes) receives the name of the instantiation that ran.
 hipError_t launch_items(const Item* const* items, int n, hipStream_t st, char* label_out);
 // Items of the same kernel whose instantiations differ only in size bounds (column blocks, steps)
 // share the launch of the largest.
@@ -243,6 +243,10 @@ bool make_v_digits(const float* V, int ks, float* sum, long long ncols, int r, i
 bool make_pair_digits(const void* X, long long ncols, int n, const float* V, const unsigned char* digits, const double* scales, int r, double* part,
                       int nsplit, const unsigned* amax, const PresumArgs* pre, Item* out);
 hipError_t launch_digits_items(const Item* const* items, int n, hipStream_t st);
+
+// Subspace steps of one layer that can share a launch (asi_steps.hip): b joins a, which may be several already; false: it does not.
+bool join_steps(const Item& a, const Item& b, Item* out);
+hipError_t launch_steps_items(const Item* const* items, int n, hipStream_t st);
 
 // ---- fused V/P step for modes with n <= 64 (asi_subspace.hip): part is (nwg, n, r) fp64 ---------------
 bool subspace_small_supported(long long outer, int n, long long inner, int r);

@@ -1105,7 +1105,7 @@ hipError_t launch_items(const Item* const* items, int n, hipStream_t st, char* l
     if (n <= 0 || n > kMaxBatch) return hipErrorInvalidValue;
     for (int j = 1; j < n; ++j)
         if (!same_launch(*items[0], *items[j])) return hipErrorInvalidValue;
-    if (label_out) std::snprintf(label_out, 96, "%s", items[0]->label);
+    if (label_out) std::snprintf(label_out, sizeof(items[0]->label), "%s", items[0]->label);
     switch (items[0]->kind) {
         case IT_TTM: case IT_KSPLIT: return launch_ttm_items(items, n, st, label_out);
         case IT_TTM_DUO: return launch_ttm_duo_items(items, n, st, label_out);
@@ -1122,6 +1122,7 @@ hipError_t launch_items(const Item* const* items, int n, hipStream_t st, char* l
         case IT_DIGITS: return launch_digits_items(items, n, st);
         case IT_SMALL: return launch_small_items(items, n, st);
         case IT_TINY: return launch_tiny_items(items, n, st);
+        case IT_STEPS: return launch_steps_items(items, n, st);
         case IT_LONG: return launch_long_items(items, n, st);
         case IT_PLANES: return launch_planes_items(items, n, st);
         case IT_SPLIT_BF16: case IT_GEMM_BF16: return launch_bf16_items(items, n, st);

@@ -188,3 +188,17 @@ def test_subspace_step_of_49_to_64_entries(dims, ranks, mode, dtype, shift):
     inner = int(np.prod(dims[mode + 1:]))
     want = "k_subspace_cols<%s, %s>" % ("float" if dtype == "f32" else "asi::bf16_t", "false" if shift or inner % 4 else "true")
     _check_factors(dims, ranks, (mode,), dtype, shift, want, 3e-5)
+
+
+# Two and three modes' steps in one launch: both Gram forms and planes of one block; columns beside tiny planes (another mode's step, on its
+# own, between them) and beside planes of two blocks.
+@pytest.mark.parametrize("dims,ranks,modes,names", [
+    ((8, 32, 16, 16), (4, 8, 6, 6), (0, 1, 2, 3), ("gram", "gram", "planes")), ((64, 40, 7, 8), (16, 9, 5, 5), (0, 2, 3), ("cols", "tiny")),
+    ((50, 5, 20, 28), (7, 5, 6, 9), (0, 2, 3), ("cols", "planes")), ((4, 3, 12, 12), (2, 3, 4, 5), (0, 1, 2, 3), ("gram", "gram", "planes")),
+    ((130, 9, 6, 8), (8, 5, 3, 5), (2, 3), ("tiny",))])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_subspace_steps_of_several_modes(dims, ranks, modes, names, dtype):
+    """As for the steps alone: V in fp32 (columns), 3e-5; sums in fp64, 1e-6."""
+    tn = "float" if dtype == "f32" else "asi::bf16_t"
+    label = "k_subspace_%s<%s" % (("steps" if len(names) > 1 else names[0]), tn)
+    _check_factors(dims, ranks, modes, dtype, 0, label, 3e-5 if "cols" in names else 1e-6)
