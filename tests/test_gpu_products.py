@@ -195,7 +195,7 @@ def test_subspace_step_of_49_to_64_entries(dims, ranks, mode, dtype, shift):
 @pytest.mark.parametrize("dims,ranks,modes,names", [
     ((8, 32, 16, 16), (4, 8, 6, 6), (0, 1, 2, 3), ("gram", "gram", "planes")), ((64, 40, 7, 8), (16, 9, 5, 5), (0, 2, 3), ("cols", "tiny")),
     ((50, 5, 20, 28), (7, 5, 6, 9), (0, 2, 3), ("cols", "planes")), ((4, 3, 12, 12), (2, 3, 4, 5), (0, 1, 2, 3), ("gram", "gram", "planes")),
-    ((130, 9, 6, 8), (8, 5, 3, 5), (2, 3), ("tiny",))])
+    ((130, 9, 6, 8), (8, 5, 3, 5), (2, 3), ("tiny",)), ((7, 19, 9, 16), (3, 8, 4, 5), (0, 1, 2, 3), ("gram", "gram", "planes"))])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_subspace_steps_of_several_modes(dims, ranks, modes, names, dtype):
     """As for the steps alone: V in fp32 (columns), 3e-5; sums in fp64, 1e-6."""
