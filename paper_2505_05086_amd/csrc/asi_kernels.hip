@@ -660,10 +660,11 @@ struct DwFoldJob {
 
 // CO: output channels per workgroup at most (1..3 with nine taps, 16 or 32 with one); NS: partial tensors whose loads are in
 // flight together (4 where there are no more: with 16 a batch of 7 x 7 layers, three splits each, issued 96 loads per thread
-// for 18 words).  The result tiles take the place of T's: five workgroups stay resident per CU instead of four, and the
-// 1026 of three 512 x 512 x 9 layers fit the chip at once: 27.0 -> 21.2 us.
+// for 18 words).  The result tiles take the place of T's, so that five workgroups fit the LDS of a CU; the launch bounds make them
+// fit its registers too (135 kept three, with accumulators apart; 96 now), and the 1026 of three 512 x 512 x 9 layers run at once:
+// 20.7 -> 19.4 us (products 6 us a SIMD).  B operands requested before T's: 12 registers spilled, 21.0.
 template <int TAPS, int RP, int CO, int NS>
-__global__ __launch_bounds__(256) void k_dw_fold(Batch<DwFoldJob> bt) {
+__global__ __launch_bounds__(256, NS == 4 ? (RP <= 48 ? 5 : 4) : 1) void k_dw_fold(Batch<DwFoldJob> bt) {
     typedef float v4f __attribute__((ext_vector_type(4)));
     constexpr int MB = (CO * TAPS + 15) / 16;              // 16-row blocks of the tile of T
     static_assert(MB == 1 || MB == 2, "at most 32 rows");

@@ -12,10 +12,10 @@
 // P is summed in fp64: the columns of U_prev need not be aligned with singular vectors, so
 // P holds components (sigma_r/sigma_1)^2 below its largest ones that fp32 sums would lose.
 //
-// A tile is either a run of complete outer slices (contiguous memory) or, for a long inner
-// extent, n rows of 128 consecutive elements.  All loads of a tile are issued before the
-// first is stored (one memory latency per tile); two or more workgroups per CU overlap one
-// tile's loads with another's MFMAs.
+// A tile is a run of complete outer slices (contiguous memory).  All loads of a tile are issued
+// before the first is stored (one memory latency per tile); two or more workgroups per CU overlap
+// one tile's loads with another's MFMAs.  A long inner extent of 49 to 64 entries takes no tile
+// (asi_subspace_cols.h).
 #include "asi_device.h"
 #include "asi_kernels.h"
 #include "asi_subspace_cols.h"
@@ -25,7 +25,6 @@
 #include <type_traits>
 
 namespace asi {
-
 
 constexpr int SS_TC = 128;                 // fibres (unfolding columns) per tile
 constexpr int SS_PAD = 4;
@@ -53,7 +52,6 @@ struct SmallJob {
     int nzero;
     SmallView v;
 };
-
 
 template <typename T, int NBM, int NBR>
 __global__ __launch_bounds__(256, 2) void k_subspace_small(Batch<SmallJob> bt) {
@@ -84,14 +82,14 @@ __global__ __launch_bounds__(256, 2) void k_subspace_small(Batch<SmallJob> bt) {
             }
         }
 #pragma unroll
-            for (int u = 0; u < NU; ++u) (&Us[0][0])[tid + 256 * u] = uok[u] ? ut[u] : 0.f;
+        for (int u = 0; u < NU; ++u) (&Us[0][0])[tid + 256 * u] = uok[u] ? ut[u] : 0.f;
     }
 
     v4d pacc[NBM][NBR];
 #pragma unroll
-        for (int mb = 0; mb < NBM; ++mb)
+    for (int mb = 0; mb < NBM; ++mb)
 #pragma unroll
-            for (int nb = 0; nb < NBR; ++nb) pacc[mb][nb] = (v4d){0.0, 0.0, 0.0, 0.0};
+        for (int nb = 0; nb < NBR; ++nb) pacc[mb][nb] = (v4d){0.0, 0.0, 0.0, 0.0};
 
     for (long long tile = lb; tile < jb.ntiles; tile += jb.nwg) {
         __syncthreads();   // everyone is done with the previous tile (and Us is written)
