@@ -477,11 +477,12 @@ def test_conv_weight_gradient_sums_the_partial_products_in_its_last_launch():
 
 
 def test_large_planes_take_steps_2_and_3_in_one_launch():
-    """Z = S x_3 U3 x_4 U4 for planes beyond 16 x 16 with ranks that are multiples of four: one launch, a wave per plane
-    of the core (48 x 52 planes, ranks 16 and 24); with a rank that is not a multiple of four, the two mode products."""
+    """Z = S x_3 U3 x_4 U4 for a dozen planes beyond 16 x 16: one launch, in 16-byte pieces where ranks and width are multiples of
+    four (48 x 52 planes, ranks 16 and 24), element by element where a rank is not (22); a row longer than 64, the two mode products."""
     from paper_2505_05086_amd import binding as B
-    for ranks, fused in (((3, 4, 16, 24), True), ((3, 4, 16, 22), False)):
-        lay = Layer("edge", (4, 6, 48, 52), ranks, "f32", "conv2d", 7, k=3, stride=1, pad=1, dil=1, groups=1, alpha=0.7, noise=1e-2)
+    for ranks, w, site in (((3, 4, 16, 24), 52, "k_z_planes<4>"), ((3, 4, 16, 22), 52, "k_z_planes<4, false>"), ((3, 4, 16, 24), 68, None)):
+        fused = site is not None
+        lay = Layer("edge", (4, 6, 48, w), ranks, "f32", "conv2d", 7, k=3, stride=1, pad=1, dil=1, groups=1, alpha=0.7, noise=1e-2)
         st = LayerStream(9, 8, lay)
         run = _runner(lay)
         A_t, A64, U_or = check_compress(run, lay, st.activation(0), st.u_prev0(), TOL["f32"], f"z planes {ranks}")
@@ -491,7 +492,7 @@ def test_large_planes_take_steps_2_and_3_in_one_launch():
             sites = list(B.asi_profile_report())
         finally:
             B.asi_profile_enable(False)
-        assert any("k_z_planes<4>" in s_ for s_ in sites) == fused, sites
+        assert any((site or "k_z_planes") in s_ for s_ in sites) == fused, sites
         assert any(s_.endswith(":Z1") for s_ in sites) == (not fused), sites
 
 

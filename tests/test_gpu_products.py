@@ -137,6 +137,30 @@ def test_plane_products_of_any_size(dims, ranks, cout, dtype):
     assert float((dW.view(cout, -1) - ref).abs().max() / ref.abs().max()) <= 1e-5
 
 
+# Cores of one to fifteen planes with ranks that are no multiple of four, and the first of sixteen: Z rides in the launch of G1, tiled or
+# (the last two: a million entries of grad_out) streaming, where planes have up to 256 entries.
+@pytest.mark.parametrize("dims,ranks,cout,k", [
+    ((8, 6, 5, 5), (1, 1, 3, 3), 9, 3), ((64, 32, 7, 7), (2, 5, 5, 5), 32, 3), ((9, 6, 13, 9), (3, 5, 5, 6), 20, 1), ((5, 7, 16, 15), (3, 5, 1, 2), 3, 1),
+    ((11, 9, 6, 7), (2, 8, 5, 3), 17, 3), ((64, 8, 14, 14), (4, 3, 7, 7), 100, 1), ((64, 5, 7, 8), (16, 1, 5, 7), 520, 1)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_small_cores_keep_g1_and_z_in_one_launch(dims, ranks, cout, k, dtype):
+    """The weight gradient against float64: chains of fp32 sums of at most 1100 terms, 2e-6 of the largest entry per product."""
+    from paper_2505_05086_amd import binding as B
+    rng = np.random.default_rng(sum(dims) + sum(ranks))
+    U = [_dev(np.linalg.qr(rng.standard_normal((n, r)))[0]) for n, r in zip(dims, ranks)]
+    S = _dev(rng.standard_normal(ranks))
+    gy = _dev(rng.standard_normal((dims[0], cout) + dims[2:]), dtype)
+    desc, conv = B.make_desc(dims, ranks, dtype), B.make_conv(cout, k, k, (1, 1), (k // 2, k // 2), (1, 1), 1)
+    dW = torch.empty(cout, dims[1], k, k, device="cuda")
+    ws = B.alloc_workspace(desc, conv, 0)
+    ws.fill_(255)                                        # NaN wherever nothing was written
+    sites = _sites(lambda: B.asi_weight_grad_conv2d(desc, S, U, gy, conv, dW, False, ws))
+    assert any(s.endswith(":G1+Z") for s in sites), sites
+    xr = _modes(S, [u.t().contiguous() for u in U])
+    want = torch.nn.grad.conv2d_weight(xr.cpu(), dW.shape, gy.double().cpu(), padding=k // 2).cuda()
+    assert float((dW - want).abs().max() / want.abs().max()) <= 1e-5
+
+
 def _check_factors(dims, ranks, modes, dtype, shift, label, tol):
     from paper_2505_05086_amd import binding as B
     rng = np.random.default_rng(sum(dims) + sum(ranks) + shift)
