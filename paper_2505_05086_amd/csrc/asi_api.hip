@@ -446,10 +446,10 @@ inline void tag(Program& pg, const char* role, double bytes, double flops) {
 
 // mode product with its accounting: reads X and M once, writes (or updates) Y once
 asi_status add_ttm(Program& pg, const char* role, DType xt, const void* X, long long outer, int n, long long inner,
-                   const float* Mp, long long ms_i, long long ms_q, int r, float* Y, int beta) {
+                   const float* Mp, long long ms_i, long long ms_q, int r, float* Y, int beta, bool stream_ok = true) {
     const double cols = (double)outer * (double)inner;
     ASI_ADD(pg, role, cols * n * esize(xt) + 4.0 * n * r + 4.0 * cols * r * (beta ? 2 : 1), 2.0 * cols * n * r,
-            make_ttm(xt, X, outer, n, inner, Mp, ms_i, ms_q, r, Y, beta, it__));
+            make_ttm(xt, X, outer, n, inner, Mp, ms_i, ms_q, r, Y, beta, it__, stream_ok));
     return ASI_OK;
 }
 // two trailing modes at once (Kronecker product of their matrices)
@@ -851,24 +851,32 @@ asi_status build_conv_maps(const asi_tensor_desc* desc, const float* S, const fl
     //     T = sum_i (sum_b U1[b,i] dY[b]) * Z[i] = sum_b dY[b] * Z'[b],   Z' from S1 = S x_1 U1   (B, r2, r3, r4),
     // and the correlation reads grad_out itself (fp32 data, aligned for its 16-byte loads).
     const bool expand_core = p.S1 && s.dt == F32 && reinterpret_cast<uintptr_t>(grad_out) % 16 == 0;
-    const float* Sz = S;
-    cb->G1 = p.G1;
+    const float* Sz = expand_core ? p.S1 : S;
+    cb->G1 = expand_core ? static_cast<const float*>(grad_out) : p.G1;
+    Item planes;
+    const bool by_planes = make_z_planes(Sz, (long long)g.r1 * g.r2, r3, r4, U[2], g.H, U[3], g.W, p.Z, &planes);
     if (expand_core) {
         // 1'. S1[b,...] = sum_i U1[b,i] S[i,...]
         ASI_TRYS(add_ttm(pg, "S1", F32, S, 1, g.r1, (long long)g.r2 * r3 * r4, U[0], 1, g.r1, cg.B, p.S1, 0));
-        Sz = p.S1;
-        cb->G1 = static_cast<const float*>(grad_out);
     } else {
         // 1. G1 = grad_out x_1 U1^T                                   (r1, cout, Ho, Wo)
-        ASI_TRYS(add_ttm(pg, "G1", s.dt, grad_out, 1, cg.B, (long long)g.cout * g.Ho * g.Wo, U[0], g.r1, 1, g.r1, p.G1, 0));
+        // (tiled where Z is one merged product: the two then share a launch; 64 x 128 x 1 x 200 at rank 16 of 128 channels 45.5 us for the weight
+        // gradient, 48.6 with a streaming G1 and Z after it)
+        ASI_TRYS(add_ttm(pg, "G1", s.dt, grad_out, 1, cg.B, (long long)g.cout * g.Ho * g.Wo, U[0], g.r1, 1, g.r1, p.G1, 0,
+                         by_planes || p.Z1));
     }
-    pg.items.emplace_back();
-    if (make_z_planes(Sz, (long long)g.r1 * g.r2, r3, r4, U[2], g.H, U[3], g.W, p.Z, &pg.items.back())) {
-        // 2+3. Z[p] = U3 S[p] U4^T plane by plane, both products in one launch (planes of up to 64 x 64, ranks up to 32)
-        const double planes = (double)g.r1 * g.r2;
-        tag(pg, "Z", 4.0 * (planes * ((double)r3 * r4 + (double)g.H * g.W) + (double)g.H * r3 + (double)g.W * r4),
-            2.0 * planes * ((double)g.H * r3 * r4 + (double)g.H * g.W * r4));
-        // G1 and Z do not depend on each other: one launch for both where G1's kernel allows it (a tiled G1 beside planes of more than
+    if (by_planes || !p.Z1) {
+        const double cnt = (double)g.r1 * g.r2;
+        if (by_planes) {
+            // 2+3. Z[p] = U3 S[p] U4^T plane by plane, both products in one launch (planes of up to 64 x 64, ranks up to 32)
+            pg.items.push_back(planes);
+            tag(pg, "Z", 4.0 * (cnt * ((double)r3 * r4 + (double)g.H * g.W) + (double)g.H * r3 + (double)g.W * r4),
+                2.0 * cnt * ((double)g.H * r3 * r4 + (double)g.H * g.W * r4));
+        } else {
+            // 2+3. Z = S x_3 U3 x_4 U4 in one pass:  M(a*r4 + b, h*W + w) = U3[h,a] * U4[w,b]   (r1, r2, H, W)
+            ASI_TRYS(add_ttm_kron(pg, "Z", F32, Sz, (long long)g.r1 * g.r2, r3, r4, U[2], 1, r3, g.H, U[3], 1, r4, g.W, p.Z));
+        }
+        // G1 and Z do not depend on each other: one launch for both where G1's kernel allows it (not a tiled G1 beside planes of more than
         // 256 entries: the planes are the longer of the two and its workgroups' LDS keeps them few)
         Item duo;
         const size_t ni = pg.items.size();
@@ -876,9 +884,6 @@ asi_status build_conv_maps(const asi_tensor_desc* desc, const float* S, const fl
             pg.items.pop_back();
             pg.items.back() = duo;
         }
-    } else if (pg.items.pop_back(), !p.Z1) {
-        // 2+3. Z = S x_3 U3 x_4 U4 in one pass:  M(a*r4 + b, h*W + w) = U3[h,a] * U4[w,b]   (r1, r2, H, W)
-        ASI_TRYS(add_ttm_kron(pg, "Z", F32, Sz, (long long)g.r1 * g.r2, r3, r4, U[2], 1, r3, g.H, U[3], 1, r4, g.W, p.Z));
     } else {
         // 2. Z1 = S x_3 U3                                        (r1, r2, H, r4)
         ASI_TRYS(add_ttm(pg, "Z1", F32, Sz, (long long)g.r1 * g.r2, r3, r4, U[2], 1, r3, g.H, p.Z1, 0));

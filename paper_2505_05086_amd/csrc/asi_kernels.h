@@ -113,9 +113,10 @@ struct TtmJob {
     int32_t* zero;         // nullable: `nzero` int32 the kernel clears (arrival counters of later launches)
     int nzero;
 };
+// stream_ok = false keeps the product on the tiled kernels (the ones that can share a launch with a Kronecker product, make_ttm_duo)
 constexpr long long kStreamMinElems = 1LL << 20;
 bool make_ttm(DType xt, const void* X, long long outer, int n, long long inner, const float* Mp, long long ms_i,
-              long long ms_q, int r, float* Y, int beta, Item* out);
+              long long ms_q, int r, float* Y, int beta, Item* out, bool stream_ok = true);
 // the same product by the streaming kernel (asi_ttm_stream.hip); make_ttm picks it where it is supported and faster
 bool ttm_stream_supported(DType xt, const void* X, long long outer, int n, long long inner, const float* Mp,
                           long long ms_i, long long ms_q, int r, const float* Y);
@@ -158,7 +159,8 @@ __device__ __forceinline__ void presum_block(const PresumJob* jobs, int njobs, i
 }
 
 // One launch for two independent items (tagged with role, bytes, flops): a plain product by make_ttm, tiled or streaming, not along
-// the last mode, and the planes of make_z_planes.  Returns false if the items do not have these forms.
+// the last mode, and the planes of make_z_planes; or a tiled one and a small merged (Kronecker) product of fp32 data.  Returns false if
+// the items do not have these forms.
 bool make_ttm_duo(const Item& a, const Item& z, Item* out);
 bool make_ttm_stream_duo(const Item& a, const Item& z, Item* out);
 

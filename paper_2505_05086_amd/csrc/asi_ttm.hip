@@ -280,18 +280,21 @@ __global__ __launch_bounds__(256) void k_ttm_mfma(Batch<TtmJob> bt) {
 }
 
 // Two independent products in one launch: a plain product along a leading mode (G1 = grad_out x_1 U1^T
-// of Eq. 14) and, in extra workgroups, Z = S x_3 U3 x_4 U4 plane by plane.
+// of Eq. 14) and, in extra workgroups, Z = S x_3 U3 x_4 U4 plane by plane or, KRON, as one merged product (a row or a column longer
+// than 64, a rank above 32: signals of 1 x 200, apart 3 us longer).
+template <bool KRON>
 struct TtmDuoJob {
     TtmJob a;        // dtype T, not the last mode, plain matrix, NBR column blocks
-    ZPlanesJob z;
+    std::conditional_t<KRON, TtmJob, ZPlanesJob> z;      // (KRON: fp32, trailing modes merged by a Kronecker product, K chunks of 32)
     int a_blocks;
 };
-template <typename T, int NBR>
-__global__ __launch_bounds__(256) void k_ttm_duo(Batch<TtmDuoJob> bt) {
+template <typename T, int NBR, bool KRON>
+__global__ __launch_bounds__(256) void k_ttm_duo(Batch<TtmDuoJob<KRON>> bt) {
     __shared__ float smem[TM_SMEM];
     int lb;
-    const TtmDuoJob& jb = bt.job[locate(bt, &lb)];
+    const TtmDuoJob<KRON>& jb = bt.job[locate(bt, &lb)];
     if (lb < jb.a_blocks) ttm_tile<T, false, NBR, 0>(jb.a, xcd_order(lb, jb.a_blocks), smem);
+    else if constexpr (KRON) ttm_tile<float, true, 4, 1>(jb.z, lb - jb.a_blocks, smem);
     else z_planes_block<0, false>(jb.z, lb - jb.a_blocks);
 }
 
@@ -715,13 +718,13 @@ static bool fill_ttm(DType xt, const void* X, long long outer, int n, long long 
 }
 
 bool make_ttm(DType xt, const void* X, long long outer, int n, long long inner, const float* Mp, long long ms_i,
-              long long ms_q, int r, float* Y, int beta, Item* out) {
+              long long ms_q, int r, float* Y, int beta, Item* out, bool stream_ok) {
     const KronSpec none = {nullptr, 0, 0, 1, 1};
     const long long ncols = outer * inner;
     const bool thin = n <= 16 && r <= 16 && ncols >= (1LL << 18);
     // the streaming kernel pays once the tensor is large enough to keep the chip busy with its loads
     // (the split kernel's 16-column workgroups spread few columns further: it keeps the products below 256 spans)
-    if (inner > 1 && !thin && ncols * n >= kStreamMinElems && (ncols >= 256 * 64 || !prefer_ksplit(ncols, n, inner)) &&
+    if (stream_ok && inner > 1 && !thin && ncols * n >= kStreamMinElems && (ncols >= 256 * 64 || !prefer_ksplit(ncols, n, inner)) &&
         ttm_stream_supported(xt, X, outer, n, inner, Mp, ms_i, ms_q, r, Y))
         return make_ttm_stream(xt, X, outer, n, inner, Mp, ms_i, ms_q, r, Y, beta, out);
     return fill_ttm(xt, X, outer, n, inner, Mp, ms_i, ms_q, r, Y, beta, none, out);
@@ -762,52 +765,62 @@ static hipError_t launch_split(int cb, bool contig, const Batch<TtmJob>& b, dim3
     return hipErrorInvalidValue;
 }
 
-// a: a tiled plain product that is not along the last mode, or a streaming one; z: planes (make_z_planes).  Fails (and leaves *out
-// alone) if they do not have these forms; the caller then launches them apart.
-bool make_ttm_duo(const Item& a, const Item& z, Item* out) {
-    if (z.kind != IT_Z_PLANES) return false;
-    if (a.kind == IT_TTM_STREAM) return make_ttm_stream_duo(a, z, out);
-    if (a.kind != IT_TTM || (a.key & 0xc00eu) != 0u) return false;       // not last mode, plain, tiled, chunks of 32
-    TtmDuoJob jb;
-    std::memcpy(&jb.a, a.arg, sizeof(TtmJob));
-    std::memcpy(&jb.z, z.arg, sizeof(ZPlanesJob));
+// a: a tiled plain product that is not along the last mode, with planes (make_z_planes) or a Kronecker product with short K as z, or a
+// streaming one with planes.  Fails (and leaves *out alone) if they do not have these forms; the caller then launches them apart.
+// key: [0] bf16, [1] KRON, [4..6] NBR-1
+template <bool KRON>
+static bool put_ttm_duo(const Item& a, const Item& z, Item* out) {
+    typedef TtmDuoJob<KRON> J;
+    J jb;
+    std::memset(&jb, 0, sizeof(jb));
+    std::memcpy(&jb.a, a.arg, sizeof(jb.a));
+    std::memcpy(&jb.z, z.arg, sizeof(jb.z));
     jb.a_blocks = a.nblocks;
     if ((long long)a.nblocks + z.nblocks > 0x3fffffffLL) return false;
     const int nbr = (int)((a.key >> 4) & 7u) + 1;
     Item it;
     it.kind = IT_TTM_DUO;
-    it.key = (a.key & 1u) | ((unsigned)(nbr - 1) << 4);
+    it.key = (a.key & 1u) | (KRON ? 2u : 0u) | ((unsigned)(nbr - 1) << 4);
     it.nblocks = a.nblocks + z.nblocks;
-    std::snprintf(it.label, sizeof(it.label), "k_ttm_duo<%s, %d>", (a.key & 1u) ? "asi::bf16_t" : "float", nbr);
+    std::snprintf(it.label, sizeof(it.label), "k_ttm_duo<%s, %d, %s>", (a.key & 1u) ? "asi::bf16_t" : "float", nbr, KRON ? "true" : "false");
     std::snprintf(it.role, sizeof(it.role), "%s+%s", a.role, z.role);
     it.bytes = a.bytes + z.bytes; it.flops = a.flops + z.flops;
-    static_assert(sizeof(TtmDuoJob) <= kItemArgMax, "argument block");
+    static_assert(sizeof(J) <= kItemArgMax, "argument block");
     std::memcpy(it.arg, &jb, sizeof(jb));
     *out = it;
     return true;
 }
+bool make_ttm_duo(const Item& a, const Item& z, Item* out) {
+    const bool kron = z.kind == IT_TTM && (z.key & 0x600fu) == (2u | 4u);     // fp32, last mode, Kronecker, tiled, chunks of 32
+    if (!kron && z.kind != IT_Z_PLANES) return false;
+    if (a.kind == IT_TTM_STREAM) return !kron && make_ttm_stream_duo(a, z, out);
+    if (a.kind != IT_TTM || (a.key & 0xc00eu) != 0u) return false;       // not last mode, plain, tiled, chunks of 32
+    return kron ? put_ttm_duo<true>(a, z, out) : put_ttm_duo<false>(a, z, out);
+}
 
-hipError_t launch_ttm_duo_items(const Item* const* items, int n, hipStream_t st, char* label_out) {
-    Batch<TtmDuoJob> b;
+template <typename T, bool KRON>
+static hipError_t launch_duo(const Item* const* items, int n, int nbr, hipStream_t st) {
+    Batch<TtmDuoJob<KRON>> b;
     dim3 grid;
     if (!gather(items, n, &b, &grid)) return hipErrorInvalidValue;
-    const bool bf16 = items[0]->key & 1u;
+    switch (nbr) {
+        case 1: hipLaunchKernelGGL((k_ttm_duo<T, 1, KRON>), grid, 256, 0, st, b); break;
+        case 2: hipLaunchKernelGGL((k_ttm_duo<T, 2, KRON>), grid, 256, 0, st, b); break;
+        case 3: hipLaunchKernelGGL((k_ttm_duo<T, 3, KRON>), grid, 256, 0, st, b); break;
+        default: hipLaunchKernelGGL((k_ttm_duo<T, 4, KRON>), grid, 256, 0, st, b); break;
+    }
+    return hipGetLastError();
+}
+hipError_t launch_ttm_duo_items(const Item* const* items, int n, hipStream_t st, char* label_out) {
+    const bool bf16 = items[0]->key & 1u, kron = items[0]->key & 2u;
     int nbr = 1;
     for (int j = 0; j < n; ++j) {
         const int nj = (int)((items[j]->key >> 4) & 7u) + 1;
         nbr = nj > nbr ? nj : nbr;
     }
-    if (label_out) std::snprintf(label_out, 96, "k_ttm_duo<%s, %d>", bf16 ? "asi::bf16_t" : "float", nbr);
-#define ASI_DUO(TT)                                                                              \
-    switch (nbr) {                                                                               \
-        case 1: hipLaunchKernelGGL((k_ttm_duo<TT, 1>), grid, 256, 0, st, b); break;              \
-        case 2: hipLaunchKernelGGL((k_ttm_duo<TT, 2>), grid, 256, 0, st, b); break;              \
-        case 3: hipLaunchKernelGGL((k_ttm_duo<TT, 3>), grid, 256, 0, st, b); break;              \
-        default: hipLaunchKernelGGL((k_ttm_duo<TT, 4>), grid, 256, 0, st, b); break;             \
-    }
-    if (!bf16) { ASI_DUO(float) } else { ASI_DUO(bf16_t) }
-#undef ASI_DUO
-    return hipGetLastError();
+    if (label_out) std::snprintf(label_out, 96, "k_ttm_duo<%s, %d, %s>", bf16 ? "asi::bf16_t" : "float", nbr, kron ? "true" : "false");
+    if (kron) return bf16 ? launch_duo<bf16_t, true>(items, n, nbr, st) : launch_duo<float, true>(items, n, nbr, st);
+    return bf16 ? launch_duo<bf16_t, false>(items, n, nbr, st) : launch_duo<float, false>(items, n, nbr, st);
 }
 
 hipError_t launch_ttm_expand_items(const Item* const* items, int n, hipStream_t st) {

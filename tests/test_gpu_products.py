@@ -138,10 +138,12 @@ def test_plane_products_of_any_size(dims, ranks, cout, dtype):
 
 
 # Cores of one to fifteen planes with ranks that are no multiple of four, and the first of sixteen: Z rides in the launch of G1, tiled or
-# (the last two: a million entries of grad_out) streaming, where planes have up to 256 entries.
+# (the two after: a million entries of grad_out) streaming, where planes have up to 256 entries; last, planes that the plane kernels do not
+# take (a row or a column longer than 64, a rank above 32), beside a G1 of few and of a million entries.
 @pytest.mark.parametrize("dims,ranks,cout,k", [
     ((8, 6, 5, 5), (1, 1, 3, 3), 9, 3), ((64, 32, 7, 7), (2, 5, 5, 5), 32, 3), ((9, 6, 13, 9), (3, 5, 5, 6), 20, 1), ((5, 7, 16, 15), (3, 5, 1, 2), 3, 1),
-    ((11, 9, 6, 7), (2, 8, 5, 3), 17, 3), ((64, 8, 14, 14), (4, 3, 7, 7), 100, 1), ((64, 5, 7, 8), (16, 1, 5, 7), 520, 1)])
+    ((11, 9, 6, 7), (2, 8, 5, 3), 17, 3), ((64, 8, 14, 14), (4, 3, 7, 7), 100, 1), ((64, 5, 7, 8), (16, 1, 5, 7), 520, 1),
+    ((16, 20, 1, 100), (4, 8, 1, 20), 30, 1), ((64, 9, 1, 200), (8, 5, 1, 40), 128, 1), ((32, 7, 128, 1), (4, 3, 30, 1), 64, 3), ((7, 9, 3, 80), (3, 4, 2, 29), 11, 3)])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_small_cores_keep_g1_and_z_in_one_launch(dims, ranks, cout, k, dtype):
     """The weight gradient against float64: chains of fp32 sums of at most 1100 terms, 2e-6 of the largest entry per product."""
