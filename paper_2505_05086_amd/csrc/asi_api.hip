@@ -525,9 +525,9 @@ asi_status flush(std::vector<Program>& progs, hipStream_t st, const char* phase)
 }
 
 // ---- builders: validate one layer's arguments and append its launches -----------------------------
-// seed: null for the warm-start branch (U_prev given); else the first iteration, V drawn from *seed
+// seed: null for the warm-start branch (U_prev given); else the first iteration, V drawn from *seed; layers: of the batch
 asi_status build_compress(const asi_tensor_desc* desc, const void* A, const float* const* U_prev, float* const* U_out,
-                          void* ws, size_t ws_bytes, int32_t* info, const unsigned long long* seed, Program& pg) {
+                          void* ws, size_t ws_bytes, int32_t* info, const unsigned long long* seed, int layers, Program& pg) {
     Shape s;
     asi_status why;
     if (!parse_desc(desc, &s, &why)) return why;
@@ -579,7 +579,7 @@ asi_status build_compress(const asi_tensor_desc* desc, const void* A, const floa
     auto join = [&]() {                  // the step added last joins one before it where the two may share a launch
         for (size_t i = steps_at; i + 1 < pg.items.size(); ++i) {
             Item joined;
-            if (!join_steps(pg.items[i], pg.items.back(), &joined)) continue;
+            if (!join_steps(pg.items[i], pg.items.back(), layers, &joined)) continue;
             pg.items[i] = joined;
             pg.items.pop_back();
         }
@@ -1077,7 +1077,7 @@ asi_status asi_compress_batch(int32_t count, const asi_tensor_desc* descs, const
     std::vector<Program> progs(count);
     for (int l = 0; l < count; ++l)
         ASI_TRYS(build_compress(&descs[l], A[l], U_prev[l], U_out[l], ws[l], ws_bytes[l], info ? info[l] : nullptr, nullptr,
-                                progs[l]));
+                                count, progs[l]));
     return flush(progs, static_cast<hipStream_t>(stream), "compress");
 }
 
@@ -1085,7 +1085,7 @@ asi_status asi_compress_cold(const asi_tensor_desc* desc, const void* A, uint64_
                              size_t ws_bytes, int32_t* info, asi_stream_t stream) {
     std::vector<Program> progs(1);
     const unsigned long long sd = seed;
-    ASI_TRYS(build_compress(desc, A, nullptr, U_out, ws, ws_bytes, info, &sd, progs[0]));
+    ASI_TRYS(build_compress(desc, A, nullptr, U_out, ws, ws_bytes, info, &sd, 1, progs[0]));
     return flush(progs, static_cast<hipStream_t>(stream), "cold");
 }
 

@@ -247,7 +247,8 @@ bool make_pair_digits(const void* X, long long ncols, int n, const float* V, con
 hipError_t launch_digits_items(const Item* const* items, int n, hipStream_t st);
 
 // Subspace steps of one layer that can share a launch (asi_steps.hip): b joins a, which may be several already; false: it does not.
-bool join_steps(const Item& a, const Item& b, Item* out);
+// layers: of the batch, whose launches they are then in.
+bool join_steps(const Item& a, const Item& b, int layers, Item* out);
 hipError_t launch_steps_items(const Item* const* items, int n, hipStream_t st);
 
 // ---- fused V/P step for modes with n <= 64 (asi_subspace.hip): part is (nwg, n, r) fp64 ---------------

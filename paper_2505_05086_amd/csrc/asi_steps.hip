@@ -77,9 +77,20 @@ static bool step_form(const Item& it, int* kind, size_t* bytes, int* lds) {
     return false;
 }
 
+// times that the chip is filled by this many workgroups
+static long long fillings(long long blocks, int lds) {
+    const long long resident = lds > 80 * 1024 ? 256 : 512;
+    return (blocks + resident - 1) / resident;
+}
+
 // Appends `b` to the steps of `a`.  Where the Gram form of a mode is one of them its ring of buffers (96 KB) leaves room for one
-// workgroup per CU, so it joins only where all workgroups are resident at once.
-bool join_steps(const Item& a, const Item& b, Item* out) {
+// workgroup per CU, so it joins only where all workgroups of the layer are resident at once, and in a batch, whose layers' steps share the
+// launch, where together they fill the chip no more often than apart (the columns and the planes fill it half as often there).
+// Compress of 2 | 3 | 4 | 8 layers, apart -> all steps joined (fillings apart, joined): 16 x 32 x 20 x 20 (50 + 64 Gram, 128 planes) 31.7 -> 27.7 us (3, 2) |
+// 35.5 -> 33.8 (3, 3) | 37.0 -> 39.5 (3, 4) | 56.8 -> 63.5 (6, 8); 8 x 32 x 32 x 32 (64 + 64, 64) 33.0 -> 27.6 | 34.5 -> 33.0 | 36.1 -> 36.3 (3, 3) |
+// 55.5 -> 58.5 (5, 6); 32 x 64 x 14 x 14 (98 Gram, 52 columns) 34.6 -> 34.0 | 42.0 -> 37.6 | 46.0 -> 46.0 (3, 3) | 74.2 -> 72.2 (5, 5).  By the rule
+// four and eight of the first take 37.0 and 57.7, eight of the second 57.6 (their Gram forms join).
+bool join_steps(const Item& a, const Item& b, int layers, Item* out) {
     StepsJob jb;
     std::memset(&jb, 0, sizeof(jb));
     Item it = a;
@@ -95,10 +106,11 @@ bool join_steps(const Item& a, const Item& b, Item* out) {
         std::snprintf(it.label, sizeof(it.label), "k_subspace_steps<%s> = %s", (a.key & 1u) ? "asi::bf16_t" : "float", a.label);
     }
     if (jb.n >= ST_MAX || !step_form(b, &kind, &bytes, &lds) || (b.key & 1u) != (it.key & 1u)) return false;
-    if (lds < jb.lds) lds = jb.lds;
-    const long long blocks = (long long)a.nblocks + b.nblocks;
-    if (blocks > 0x3fffffffLL || (lds > 80 * 1024 && blocks > 256)) return false;
-    jb.lds = lds;
+    const int both = lds > jb.lds ? lds : jb.lds;
+    const long long blocks = (long long)a.nblocks + b.nblocks, n = layers;
+    if (blocks > 0x3fffffffLL || (both > 80 * 1024 && blocks > 256)) return false;
+    if (fillings(n * blocks, both) > fillings(n * a.nblocks, jb.lds) + fillings(n * b.nblocks, lds)) return false;
+    jb.lds = both;
     jb.kind[jb.n] = kind;
     std::memcpy(jb.arg[jb.n], b.arg, bytes);
     jb.first[++jb.n] = (int)blocks;

@@ -111,3 +111,29 @@ def test_correlations_that_share_no_launch_are_split_like_layers_alone():
     pair = [s for s in alone if "<9, " in s][0]
     assert {s: w for s, w in four.items() if s != pair} == {s: w for s, w in alone.items() if s != pair}
     assert alone[pair] <= four[pair] <= 2 * alone[pair]
+
+
+@pytest.mark.parametrize("count,parts", [(1, 3), (2, 3), (4, 2), (8, 2)])
+def test_steps_of_a_batch_share_a_launch_while_it_fills_the_chip_no_more_often(count, parts):
+    """16 x 32 x 20 x 20: 50 and 64 workgroups of two Gram forms, one resident per CU as in a joined launch, and 128 of the planes, of which
+    two are.  Two layers fill 256 CUs twice joined (484) and three times apart; four layers' Gram forms join (456: twice either way) and their
+    planes do not (968: four times instead of three); eight layers' Gram forms would be 912 workgroups, four fillings like apart: joined."""
+    from paper_2505_05086_amd import binding as B
+    lay = Layer("steps", (16, 32, 20, 20), (4, 8, 6, 6), "f32", "conv2d", 9, k=1, alpha=0.7, noise=1e-2)
+    streams = [LayerStream(9, 61 + i, lay) for i in range(count)]
+    _run_layers(9, [61 + i for i in range(count)], [lay] * count, streams, 1)
+    batch = BatchRunner([lay] * count)
+    for r, st in zip(batch.runs, streams):
+        r.set_factors(st.u_prev0())
+    A = [r.upload(st.activation(0)) for r, st in zip(batch.runs, streams)]
+    torch.cuda.synchronize()
+    B.asi_profile_enable(True)
+    try:
+        batch.compress(A)
+        torch.cuda.synchronize()
+        sites = [s.split("|")[1] for s in B.asi_profile_report()]
+    finally:
+        B.asi_profile_enable(False)
+    steps = [s for s in sites if s.startswith("k_subspace_steps")]
+    assert [s.count("k_subspace_") - 1 for s in steps] == [parts], sites
+    assert any(s.startswith("k_subspace_planes") for s in sites) == (parts < 3), sites
