@@ -663,8 +663,15 @@ struct DwFoldJob {
 // for 18 words).  The result tiles take the place of T's, so that five workgroups fit the LDS of a CU; the launch bounds make them
 // fit its registers too (135 kept three, with accumulators apart; 96 now), and the 1026 of three 512 x 512 x 9 layers run at once:
 // 20.7 -> 19.4 us (products 6 us a SIMD).  B operands requested before T's: 12 registers spilled, 21.0.
+// Workgroups per CU that an instantiation's registers are kept to where there are four partial tensors at most: five up to 48 ranks, four
+// beyond, one fewer where that many would spill one or two registers (weight gradients of 1280 x 320 at rank 64 40.8 -> 40.1 us, of 1280 x 960
+// at rank 48 39.2 -> 38.8, of 256 x 256 x 9 the same; 40.7, 38.5 and the same without bounds).
+constexpr int dw_fold_wgs(int rp, int co, int ns) {
+    if (ns != 4) return 1;
+    return (rp <= 48 ? 5 : 4) - ((co == 2 && rp == 48) || (co == 32 && rp >= 48) ? 1 : 0);
+}
 template <int TAPS, int RP, int CO, int NS>
-__global__ __launch_bounds__(256, NS == 4 ? (RP <= 48 ? 5 : 4) : 1) void k_dw_fold(Batch<DwFoldJob> bt) {
+__global__ __launch_bounds__(256, dw_fold_wgs(RP, CO, NS)) void k_dw_fold(Batch<DwFoldJob> bt) {
     typedef float v4f __attribute__((ext_vector_type(4)));
     constexpr int MB = (CO * TAPS + 15) / 16;              // 16-row blocks of the tile of T
     static_assert(MB == 1 || MB == 2, "at most 32 rows");
