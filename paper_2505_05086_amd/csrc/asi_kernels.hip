@@ -314,12 +314,15 @@ static long long pair_cols_per_split(long long ncols, int nsplit) {
     const long long cps = (ncols + nsplit - 1) / nsplit;
     return (cps + 15) / 16 * 16;
 }
-static int pair_tq(long long inner, int r) {
-    const int blocks = (r + 15) / 16, gy = (blocks + 3) / 4, nbq = (blocks + gy - 1) / gy;
-    return inner == 1 && gy == 1 && nbq == 3 ? 64 : 16 * nbq;
+// The fewest tiles of up to four blocks of outputs, all of them as small as that allows.  Along the last mode as elsewhere: tiles of 64 for three
+// blocks cost 1 to 5 us more there (ranks 33 to 48 of modes of 640 to 2048, fp32 and bf16: compress 173.5 against 169.2 us, 105.3 against 101.0;
+// two or three tiles of 48, ranks 66 to 144, 264.0 against 271.5, 327.7 against 338.9).
+static int pair_tq(int r) {
+    const int blocks = (r + 15) / 16, gy = (blocks + 3) / 4;
+    return 16 * ((blocks + gy - 1) / gy);
 }
-static int pair_best_splits(long long ncols, long long inner, int n, int r) {
-    const int tq = pair_tq(inner, r), lot = r > 32 ? 16 : 32;
+static int pair_best_splits(long long ncols, int n, int r) {
+    const int tq = pair_tq(r), lot = r > 32 ? 16 : 32;
     const long long tiles = (long long)((n + PR_TI - 1) / PR_TI) * ((r + tq - 1) / tq);
     const double block = 308.0 * (tq / 16) + 88.0, partial = (double)n * r * (16.0 / 1600.0);
     long long maxs = (ncols + 127) / 128;                     // at least 128 columns per split
@@ -338,7 +341,7 @@ static int pair_best_splits(long long ncols, long long inner, int n, int r) {
 }
 int pair_splits(long long outer, int n, long long inner, int r, bool coarse) {
     const long long ncols = outer * inner;
-    if (!coarse) return pair_best_splits(ncols, inner, n, r);
+    if (!coarse) return pair_best_splits(ncols, n, r);
     // the least rounds x (columns of a split, in chunks, + 128) of 512 workgroups of 64 x 32 (64 along the last mode), 256 columns or more a split
     const int tq = (inner == 1 && r > 32 && ncols >= 4096) ? 64 : 32;
     const long long tiles = (long long)((n + PR_TI - 1) / PR_TI) * ((r + tq - 1) / tq);
@@ -379,7 +382,7 @@ static bool make_pair_any(DType xt, const void* X, long long outer, int n, long 
     jb.X = X; jb.outer = outer; jb.inner = inner; jb.cols_per_split = pair_cols_per_split(ncols, nsplit);
     jb.Y = gen ? nullptr : Y; jb.part = part; jb.n = n; jb.r = r;
     jb.seed_lo = (uint32_t)(seed & 0xffffffffu); jb.seed_hi = (uint32_t)(seed >> 32); jb.mode = mode;
-    const int tq = pair_tq(inner, r);
+    const int tq = pair_tq(r);
     jb.gx = (n + PR_TI - 1) / PR_TI; jb.gy = (r + tq - 1) / tq; jb.gz = nsplit;
     jb.zero = zero; jb.nzero = zero ? nzero : 0;
     if (pre) {

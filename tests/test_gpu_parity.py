@@ -398,13 +398,14 @@ def test_full_rank_batch_mode_and_the_expansion_kernel_are_taken():
     assert any(s_.endswith(":S1") for s_ in sites) and not any(s_.endswith(":G1") for s_ in sites), sites
 
 
+@pytest.mark.parametrize("ranks,tile", [((4, 6, 40), 48), ((7, 10, 56), 64)])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_wide_output_tiles_of_the_last_mode_pair_product(dtype):
+def test_wide_output_tiles_of_the_last_mode_pair_product(dtype, ranks, tile):
     """P = A_m V along a last mode longer than 512 with a rank above 32 over 4096 columns: the pair product
-    takes 64 outputs per workgroup (rank 40: the second block of 16 is half empty, the fourth empty; 520 rows:
+    takes the whole rank per workgroup (ranks 40 and 56: the last block of 16 is half empty; 520 rows:
     nine row tiles, the last one ragged).  Parity as everywhere, and the launch record shows the instantiation."""
     from paper_2505_05086_amd import binding as B
-    lay = Layer("edge", (16, 256, 520), (4, 6, 40), dtype, "linear", 8, alpha=0.7, noise=1e-2)
+    lay = Layer("edge", (16, 256, 520), ranks, dtype, "linear", 8, alpha=0.7, noise=1e-2)
     st = LayerStream(9, 5, lay)
     run = _runner(lay)
     B.asi_profile_enable(True)
@@ -414,7 +415,7 @@ def test_wide_output_tiles_of_the_last_mode_pair_product(dtype):
     finally:
         B.asi_profile_enable(False)
     xt = "float" if dtype == "f32" else "asi::bf16_t"
-    assert any("k_pair<%s, true, false, 64>" % xt in s_ for s_ in sites), sites
+    assert any("k_pair<%s, true, false, %d>" % (xt, tile) in s_ for s_ in sites), sites
     check_core_and_dw(run, lay, A_t, A64, U_or, st.grad_out(0), TOL[dtype], "wide pair")
 
 

@@ -77,7 +77,8 @@ def test_product_with_a_transposed_matrix_along_a_long_mode(r2, cout):
 @pytest.mark.parametrize("dims,ranks,mode", [
     ((3, 65, 1, 7), (3, 15, 1, 7), 1), ((9, 127, 3, 5), (9, 16, 3, 5), 1), ((40, 130, 7, 7), (20, 33, 5, 5), 1), ((5, 513, 9, 11), (5, 48, 5, 5), 1),
     ((6, 515, 2, 2), (6, 24, 2, 2), 1), ((4, 640, 4, 8), (4, 49, 4, 4), 1), ((3, 600, 6, 12), (3, 70, 6, 12), 1), ((2, 100, 9, 80), (2, 17, 5, 9), 1),
-    ((3, 35, 514), (3, 20, 50), 2), ((2, 33, 577), (2, 33, 17), 2), ((4, 1100, 66), (4, 64, 31), 1)])
+    ((3, 35, 514), (3, 20, 50), 2), ((2, 33, 577), (2, 33, 17), 2), ((4, 1100, 66), (4, 64, 31), 1),
+    ((3, 70, 335), (3, 20, 40), 2), ((2, 130, 402), (2, 50, 70), 2)])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("shift", [0, 1])
 def test_pair_product_at_the_edges_of_its_tiles(dims, ranks, mode, dtype, shift):
