@@ -102,7 +102,7 @@ struct CompressPlan {
     double* vscale = nullptr;
     bool fast_orth[4] = {};
     bool wide_orth[4] = {};
-    size_t bytes = 0, pair_bytes = 0;    // ... of the partial sums of pair products
+    size_t bytes = 0, split_bytes = 0;   // ... of the partial sums that a coarse plan has fewer of
 };
 
 // Which modes of a bf16 tensor take the int8 MFMA.  It costs a pass over the tensor for its largest magnitude and saves time that
@@ -137,7 +137,7 @@ void choose_digits(const Shape& s, CompressPlan* p) {
 
 // cold: the first iteration of Alg. 1 (t = 0).  V is generated inside the P kernel of every mode, so no
 // mode takes a fused V/P kernel and no V is stored.  digits: the int8 MFMA may be used (the activation is aligned).
-// coarse: fewer splits of the pair products (pair_splits).
+// coarse: fewer splits of the pair products and of the smallest planes (pair_splits, subspace_tiny_nwg), for scratch that has no room for more.
 CompressPlan plan_with(const Shape& s, void* ws, bool cold, bool digits, bool coarse) {
     CompressPlan p;
     Carver c(ws);
@@ -179,7 +179,7 @@ CompressPlan plan_with(const Shape& s, void* ws, bool cold, bool digits, bool co
     p.paired = p.tiny || p.planes;
     for (int m = 0; m < s.d; ++m) {
         const size_t n = (size_t)s.n[m], r = (size_t)s.r[m];
-        if (p.tiny && m >= 2) p.nsplit[m] = subspace_tiny_nwg(s.dt, s.n[0] * s.n[1], (int)s.n[2], (int)s.n[3]);
+        if (p.tiny && m >= 2) p.nsplit[m] = subspace_tiny_nwg(s.dt, s.n[0] * s.n[1], (int)s.n[2], (int)s.n[3], coarse);
         else if (p.planes && m >= 2) p.nsplit[m] = subspace_planes_nwg(s.dt, s.n[0] * s.n[1], (int)s.n[2], (int)s.n[3]);
         else if (p.digm[m] && p.bfv[m]) p.nsplit[m] = pair_digits_splits(s.numel / s.n[m], (int)n, (int)r);
         else if (p.digm[m]) {
@@ -196,7 +196,7 @@ CompressPlan plan_with(const Shape& s, void* ws, bool cold, bool digits, bool co
             p.nsplit2[m] = (p.nsplit[m] + 31) / 32;
             p.part2[m] = c.take<double>((size_t)p.nsplit2[m] * n * r);
         }
-        if (!p.fused[m] && !p.longm[m] && !(p.paired && m >= 2)) p.pair_bytes += c.off - before;
+        if (m >= 2 && p.paired ? p.tiny : !p.fused[m] && !p.longm[m]) p.split_bytes += c.off - before;
         p.fast_orth[m] = orth_fast_supported((int)r);
         // gram0 leaves the sum in the place of the first of the partial sums that it adds up: a workgroup has read all of its
         // rows before it writes them, and no other reads those rows.  Pays for the Gram matrices of 16-row slices, so that no
@@ -227,10 +227,11 @@ CompressPlan plan_with(const Shape& s, void* ws, bool cold, bool digits, bool co
     return p;
 }
 
-// The plan of a call.  Where only the partial sums of the pair products keep a layer out of the static scratch, they are fewer.
+// The plan of a call.  Where only partial sums keep a layer out of the static scratch, they are fewer: whether a layer has room there is what a
+// caller reads from asi_workspace_bytes, so the plan is the same whoever owns the scratch.
 CompressPlan plan_compress(const Shape& s, void* ws, bool cold = false, bool digits = false) {
     CompressPlan p = plan_with(s, ws, cold, digits, false);
-    if (p.bytes > (size_t)ASI_STATIC_SCRATCH_BYTES && p.bytes - p.pair_bytes < (size_t)ASI_STATIC_SCRATCH_BYTES) {
+    if (p.bytes > (size_t)ASI_STATIC_SCRATCH_BYTES && p.bytes - p.split_bytes < (size_t)ASI_STATIC_SCRATCH_BYTES) {
         const CompressPlan q = plan_with(s, ws, cold, digits, true);
         if (q.bytes <= (size_t)ASI_STATIC_SCRATCH_BYTES) return q;
     }

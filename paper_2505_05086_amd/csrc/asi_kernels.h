@@ -273,7 +273,8 @@ bool make_subspace_planes(DType xt, const void* X, long long planes, int rows, i
 
 // The same for planes of up to 8 x 8, two of them in a block of the matrix unit (asi_planes.hip).
 bool subspace_tiny_supported(int rows, int cols, int r_rows, int r_cols);
-int subspace_tiny_nwg(DType xt, long long planes, int rows, int cols);
+// coarse: no more than one per 128 planes (for scratch that has no room for more); make_subspace_tiny takes any number up to the other
+int subspace_tiny_nwg(DType xt, long long planes, int rows, int cols, bool coarse = false);
 bool make_subspace_tiny(DType xt, const void* X, long long planes, int rows, int cols, const float* U_rows, int r_rows,
                         double* part_rows, const float* U_cols, int r_cols, double* part_cols, int nwg, Item* out);
 

@@ -342,7 +342,8 @@ static int pair_best_splits(long long ncols, int n, int r) {
 int pair_splits(long long outer, int n, long long inner, int r, bool coarse) {
     const long long ncols = outer * inner;
     if (!coarse) return pair_best_splits(ncols, n, r);
-    // the least rounds x (columns of a split, in chunks, + 128) of 512 workgroups of 64 x 32 (64 along the last mode), 256 columns or more a split
+    // A count and no model of the tiles above: scratch that holds this many partial sums has always been accepted.  The least rounds x (columns of
+    // a split, in chunks, + 128) of 512 workgroups of 64 x 32 (64 along the last mode), 256 columns or more a split.
     const int tq = (inner == 1 && r > 32 && ncols >= 4096) ? 64 : 32;
     const long long tiles = (long long)((n + PR_TI - 1) / PR_TI) * ((r + tq - 1) / tq);
     const int maxs = (int)std::max(1LL, std::min(64LL, (ncols + 255) / 256));

@@ -54,16 +54,20 @@ static int tiny_pt(DType xt, int rows, int cols) {
     return pt > 512 ? 512 : pt;
 }
 // two workgroups per CU are resident, and every one walks the same number of tiles
-int subspace_tiny_nwg(DType xt, long long planes, int rows, int cols) {
-    const long long pt = tiny_pt(xt, rows, cols), ntiles = (planes + pt - 1) / pt, per = (ntiles + 511) / 512;
-    return (int)((ntiles + per - 1) / per);
+static long long tiny_even(long long tiles) {
+    const long long per = (tiles + 511) / 512;
+    return (tiles + per - 1) / per;
+}
+int subspace_tiny_nwg(DType xt, long long planes, int rows, int cols, bool coarse) {
+    const long long pt = tiny_pt(xt, rows, cols), fine = tiny_even((planes + pt - 1) / pt);
+    return (int)(coarse ? std::min(fine, tiny_even((planes + 127) / 128)) : fine);
 }
 // key: [0] bf16, [1] memory-to-LDS copies
 bool make_subspace_tiny(DType xt, const void* X, long long planes, int rows, int cols, const float* U_rows, int r_rows,
                         double* part_rows, const float* U_cols, int r_cols, double* part_cols, int nwg, Item* out) {
     if (!subspace_tiny_supported(rows, cols, r_rows, r_cols) || !X || !U_rows || !U_cols || !part_rows || !part_cols)
         return false;
-    if (planes < 1 || rows < 1 || cols < 1 || nwg != subspace_tiny_nwg(xt, planes, rows, cols)) return false;
+    if (planes < 1 || rows < 1 || cols < 1 || nwg < 1 || nwg > subspace_tiny_nwg(xt, planes, rows, cols)) return false;
     TinyJob jb;
     std::memset(&jb, 0, sizeof(jb));
     jb.X = X; jb.planes = planes; jb.pt = tiny_pt(xt, rows, cols); jb.ntiles = (planes + jb.pt - 1) / jb.pt;

@@ -164,7 +164,7 @@ def test_small_cores_keep_g1_and_z_in_one_launch(dims, ranks, cout, k, dtype):
     assert float((dW - want).abs().max() / want.abs().max()) <= 1e-5
 
 
-def _check_factors(dims, ranks, modes, dtype, shift, label, tol):
+def _check_factors(dims, ranks, modes, dtype, shift, label, tol, ws_bytes=None):
     from paper_2505_05086_amd import binding as B
     rng = np.random.default_rng(sum(dims) + sum(ranks) + shift)
     numel = int(np.prod(dims))
@@ -176,9 +176,12 @@ def _check_factors(dims, ranks, modes, dtype, shift, label, tol):
     info = torch.full((1,), 7, dtype=torch.int32, device="cuda")
     ws = B.alloc_workspace(desc, None, 0)
     ws.fill_(255)
+    assert ws_bytes is None or ws_bytes < ws.numel()
+    ws, past = ws[:ws_bytes], ws[ws_bytes:] if ws_bytes else None
     sites = _sites(lambda: B.asi_compress(desc, x, U, out, ws, info))
     assert any(label in s for s in sites), sites
     assert int(info) == 0
+    assert past is None or bool((past == 255).all())     # (nothing is written behind the scratch)
     for m in modes:
         a = x.double().movedim(m, 0).reshape(dims[m], -1)
         p = a @ (a.t().contiguous() @ U[m].double())
@@ -229,3 +232,32 @@ def test_subspace_steps_of_several_modes(dims, ranks, modes, names, dtype):
     tn = "float" if dtype == "f32" else "asi::bf16_t"
     label = "k_subspace_%s<%s" % (("steps" if len(names) > 1 else names[0]), tn)
     _check_factors(dims, ranks, modes, dtype, 0, label, 3e-5 if "cols" in names else 1e-6)
+
+
+# Scratch that holds a partial sum for every 256 columns of a pair product and for every 128 planes of up to 8 x 8, but not the more and
+# smaller splits that the library asks room for: the same calls, with fewer splits.
+@pytest.mark.parametrize("dims,ranks,ws_bytes", [
+    ((84, 172, 7, 7), (84, 37, 7, 6), 5658112), ((6, 1182, 8, 8), (6, 124, 8, 8), 6432768), ((10, 156, 8, 8), (10, 98, 8, 8), 1130496),
+    ((3, 70, 335), (3, 20, 40), 467968), ((2, 130, 402), (2, 50, 70), 1530624)])
+def test_compress_with_scratch_for_fewer_partial_sums(dims, ranks, ws_bytes):
+    """V is fp32 (pair products): 3e-5 of the factor's largest entry, as above."""
+    _check_factors(dims, ranks, range(len(dims)), "f32", 0, "k_orth", 3e-5, ws_bytes)
+
+
+@pytest.mark.parametrize("dims,ranks,dout,ws_bytes", [((11, 297, 200), (6, 34, 60), 904, 7832576), ((5, 352, 66), (3, 44, 55), 1623, 8784128)])
+def test_linear_gradient_with_scratch_for_fewer_partial_sums(dims, ranks, dout, ws_bytes):
+    """Against float64: four chained fp32 sums of at most 352 terms, 2e-6 of the largest entry each."""
+    from paper_2505_05086_amd import binding as B
+    rng = np.random.default_rng(dout)
+    U = [_dev(np.linalg.qr(rng.standard_normal((n, r)))[0]) for n, r in zip(dims, ranks)]
+    S, gy = _dev(rng.standard_normal(ranks)), _dev(rng.standard_normal(dims[:2] + (dout,)))
+    desc = B.make_desc(dims, ranks, "f32")
+    ws = B.alloc_workspace(desc, None, dout)
+    assert ws_bytes < ws.numel()
+    ws.fill_(255)
+    dW = torch.empty(dout, dims[2], device="cuda")
+    B.asi_weight_grad_linear(desc, S, U, gy, dout, dW, False, ws[:ws_bytes])
+    assert bool((ws[ws_bytes:] == 255).all())            # (nothing is written behind the scratch)
+    xr = _modes(S, [u.t().contiguous() for u in U])
+    want = gy.double().reshape(-1, dout).t().contiguous() @ xr.reshape(-1, dims[2])
+    assert float((dW - want).abs().max() / want.abs().max()) <= 1e-5
