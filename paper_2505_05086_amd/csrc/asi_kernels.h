@@ -295,9 +295,10 @@ struct OrthJob {
     int nsplit;
     int n, r;
     int mode1;           // 1-based mode number for *info
-    int nblk;            // fast path: workgroups of apply = orth_apply_wgs(n); wide path: orth_wide_gram_blocks(n)
+    int nblk;            // fast path: runs of slices of apply = orth_apply_wgs(n); wide path: orth_wide_gram_blocks(n)
     int gsz;             // fast path: slices of gram0 per group
-    int spw;             // fast path: slices of apply per workgroup
+    int spw;             // fast path: slices of apply per run
+    int rpw;             // fast path: runs per workgroup of apply (set at the launch, which knows the whole batch)
     unsigned long long* devbits;   // wide path with a summed Gram matrix (make_orthw_gsum): bits of max |G - I|; else null
 };
 struct OrthArgs {        // the modes of one tensor that share a path

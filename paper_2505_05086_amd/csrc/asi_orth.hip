@@ -768,7 +768,7 @@ __global__ __launch_bounds__(OP_NT) void k_orth_apply(OrthBatch a) {
     const OrthJob& jb = a.job[ji];
     const int n = jb.n, r = jb.r, nb = (r + 15) / 16, tid = threadIdx.x;
     const int T = (r * (r + 1)) / 2, nsl = (n + OP_GS - 1) / OP_GS, ngrp = (nsl + jb.gsz - 1) / jb.gsz;
-    const int first = blk * jb.spw, nall = (n + OP_RS - 1) / OP_RS, end = first + jb.spw < nall ? first + jb.spw : nall;
+    const int mine = jb.spw * jb.rpw, first = blk * mine, nall = (n + OP_RS - 1) / OP_RS, end = first + mine < nall ? first + mine : nall;
     const int lane = tid & 63, lg = lane >> 4, ll = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), J = wave & 3, h = wave >> 2;
     double av[RM / 16][4];
@@ -821,16 +821,18 @@ __global__ __launch_bounds__(OP_NT) void k_orth_apply(OrthBatch a) {
     }
     if (lead && tid == 0) { jb.scal[65] = (double)sm.s_bad; jb.scal[66] = 0.0; }
     finish_r<RM>(r, sm);
-    v4d acc[OP_PAIRS];
-#pragma unroll
-    for (int u = 0; u < OP_PAIRS; ++u) acc[u] = (v4d){0.0, 0.0, 0.0, 0.0};
-    for (int s = first; s < end; ++s) {
-        apply_slice<RM>(jb, s, 0, Ps, sm);
-        gram_add<OP_RS>(Ps, r, acc);
-    }
     double* second = jb.Gpart + (ngrp > 1 ? 0 : (long long)nsl * T);
-    gram_publish(acc, r, second + (long long)blk * T);
-    if (!last_arrival<true>(jb.ctr + 1, jb.nblk, &s_last)) return;
+    for (int run = blk * jb.rpw, s = first; s < end; ++run) {     // (a Gram matrix per run, whoever makes it: a batch gives the bits of its layers alone)
+        v4d acc[OP_PAIRS];
+#pragma unroll
+        for (int u = 0; u < OP_PAIRS; ++u) acc[u] = (v4d){0.0, 0.0, 0.0, 0.0};
+        for (int left = jb.spw; left > 0 && s < end; --left, ++s) {
+            apply_slice<RM>(jb, s, 0, Ps, sm);
+            gram_add<OP_RS>(Ps, r, acc);
+        }
+        gram_publish(acc, r, second + (long long)run * T);
+    }
+    if (!last_arrival<true>(jb.ctr + 1, (jb.nblk + jb.rpw - 1) / jb.rpw, &s_last)) return;
     if (!chol_factor<RM, 1>(jb, true, second, jb.nblk, jb.info, sm, &shifted)) return;
     if (tid < 64) {
         // first column (if any) whose accumulated R diagonal fell to the noise floor
@@ -1444,8 +1446,8 @@ int orth_group_size(int n) {
     while (g * g < s) ++g;
     return g;
 }
-// Slices of 32 rows that a workgroup of apply takes: one, more where that makes more than 128 workgroups.  A mode of one group keeps
-// the Grams of a second pass, one per workgroup, behind those of the slices: four at most, so that no layer needs more scratch
+// Slices of 32 rows in a run of apply: one, more where that makes more than 128 runs.  A mode of one group keeps
+// the Grams of a second pass, one per run, behind those of the slices: four at most, so that no layer needs more scratch
 // than with the first pass's factor in memory.
 int orth_apply_slices(int n) {
     const int s = orth_slices(n), most = orth_groups(n) == 1 ? 4 : 128;
@@ -1573,7 +1575,7 @@ hipError_t launch_orth_items(const Item* const* items, int n, hipStream_t st, ch
     long long blocks = 0;
     for (int j = 0; j < n; ++j) blocks += items[j]->nblocks;
     if (blocks <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)blocks);
+    dim3 grid((unsigned)blocks);
     if (kind == IT_PRESUM) {
         PresumBatch b;
         b.njobs = 0;
@@ -1609,6 +1611,24 @@ hipError_t launch_orth_items(const Item* const* items, int n, hipStream_t st, ch
     }
     b.first[0] = 0;
     for (int j = 0; j < b.njobs; ++j) b.first[j + 1] = b.first[j] + (kind == IT_GRAM0 ? orth_gram_slices(b.job[j].n) : b.job[j].nblk);
+    if (kind == IT_APPLY) {
+        // A workgroup takes a run; more where not all would be resident at once (two a CU up to rank 16, else one, for their registers): a second
+        // filling of the chip factors everything once more.  Compress of four | eight layers of 8 x 512 x 2048 at rank 20 (324, 648 runs), apply
+        // 25.3 -> 16.1 | 37.6 -> 18.3 us, all 263.0 -> 251.6 | 484.5 -> 464.0.
+        const int resident = rmax <= 16 ? 512 : 256;
+        int most = 1, rpw = 0, wgs;
+        for (int j = 0; j < b.njobs; ++j) most = b.job[j].nblk > most ? b.job[j].nblk : most;
+        do {
+            ++rpw;
+            wgs = 0;
+            for (int j = 0; j < b.njobs; ++j) wgs += (b.job[j].nblk + rpw - 1) / rpw;
+        } while (wgs > resident && rpw < most);
+        for (int j = 0; j < b.njobs; ++j) {
+            b.job[j].rpw = rpw;
+            b.first[j + 1] = b.first[j] + (b.job[j].nblk + rpw - 1) / rpw;
+        }
+        grid = dim3((unsigned)wgs);
+    }
     const int rm = rmax <= 16 ? 16 : (rmax <= 32 ? 32 : (rmax <= 48 ? 48 : 64));   // register shape of the fast kernels
     if (label_out && (kind == IT_GRAM0 || kind == IT_APPLY))
         std::snprintf(label_out, 96, "%s<%d>", kind == IT_GRAM0 ? "k_orth_gram0" : "k_orth_apply", rm);

@@ -137,3 +137,36 @@ def test_steps_of_a_batch_share_a_launch_while_it_fills_the_chip_no_more_often(c
     steps = [s for s in sites if s.startswith("k_subspace_steps")]
     assert [s.count("k_subspace_") - 1 for s in steps] == [parts], sites
     assert any(s.startswith("k_subspace_planes") for s in sites) == (parts < 3), sites
+
+
+@pytest.mark.parametrize("ratio", [0.9, 0.02])
+def test_batch_with_more_runs_of_slices_than_workgroups_of_the_orthogonalisation(ratio):
+    """Eight layers of 3, 700 and 620 rows: 344 runs of 32 rows, two a workgroup where the chip holds 256; the first pass certified (0.9) and, in the
+    two long modes, measured and repeated (0.02).  Bit for bit the factors of single layers, whose workgroups take a run each."""
+    from paper_2505_05086_amd import binding as B
+    dims, ranks = (3, 700, 620), (3, 20, 18)
+    desc = B.make_desc(dims, ranks, "f32")
+    A, U, one, many, ws, info = [], [], [], [], [], []
+    for i in range(8):
+        rng = np.random.default_rng(900 + i)
+        x = rng.standard_normal(ranks)
+        for m, (n, r) in enumerate(zip(dims, ranks)):
+            q = np.linalg.qr(rng.standard_normal((n, r)))[0] * (ratio ** (np.arange(r) / (r - 1)))
+            x = np.moveaxis(np.tensordot(q, x, axes=(1, m)), 0, m)
+        A.append(torch.from_numpy(np.ascontiguousarray(x / np.abs(x).max(), dtype=np.float32)).cuda())
+        U.append([torch.from_numpy(np.ascontiguousarray(np.linalg.qr(rng.standard_normal((n, r)))[0], dtype=np.float32)).cuda() for n, r in zip(dims, ranks)])
+        one.append([torch.full_like(u, float("nan")) for u in U[-1]])
+        many.append([torch.full_like(u, float("nan")) for u in U[-1]])
+        ws.append(B.alloc_workspace(desc, None, 0))
+        info.append(torch.full((1,), 7, dtype=torch.int32, device="cuda"))
+    for i in range(8):
+        B.asi_compress(desc, A[i], U[i], one[i], ws[i], info[i])
+        assert int(info[i]) == 0
+    for w in ws:
+        w.fill_(255)
+    B.asi_compress_batch([desc] * 8, A, U, many, ws, info)
+    for i in range(8):
+        assert int(info[i]) == 0
+        for a, b in zip(one[i], many[i]):
+            assert torch.equal(a, b), i
+            assert float((b.double().t() @ b.double() - torch.eye(b.shape[1], device="cuda", dtype=torch.float64)).abs().max()) < 1e-5

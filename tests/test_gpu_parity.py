@@ -806,6 +806,15 @@ def test_orthogonalisation_at_block_and_slice_edges(dims, ranks, ratio, reached)
     assert reached in took and (ratio < 0.1 or took == [2, 2, 2]), took
 
 
+@pytest.mark.parametrize("ratio,may", [(0.02, {0, 1}), (3e-3, {0})])
+def test_orthogonalisation_of_a_long_mode_that_is_not_certified(ratio, may):
+    """4130 rows: 259 slices of the first Gram matrix in groups, 130 of the solve in runs of two, the last of two rows; graded so that the first
+    pass is measured, and found enough or repeated by one workgroup."""
+    lay = Layer("orth", (5, 4130, 30), (5, 12, 17), "f32", "linear", 12)
+    ws, A64, U0 = _check_orthonormal_basis(lay, _graded_tensor(lay, ratio), 13, f"ratio {ratio}")
+    assert _orth_path(ws, A64, U0[1], 1) in may & _orth_paths_possible(O.subspace_P(A64, U0[1], 1))
+
+
 def _tensor_with_a_low_direction(rng, dims, m):
     """Mode m: orthogonal directions of singular values 0.95^i, the last at 6e-7, so that P = A A^T U has orthogonal columns
     (any factor of it is well conditioned column by column) of which the last keeps 3.6e-13 < 1e-12 ||P||."""
