@@ -137,7 +137,8 @@ void choose_digits(const Shape& s, CompressPlan* p) {
 
 // cold: the first iteration of Alg. 1 (t = 0).  V is generated inside the P kernel of every mode, so no
 // mode takes a fused V/P kernel and no V is stored.  digits: the int8 MFMA may be used (the activation is aligned).
-// coarse: fewer splits of the pair products and of the smallest planes (pair_splits, subspace_tiny_nwg), for scratch that has no room for more.
+// coarse: fewer splits of the pair products and of small planes (pair_splits, subspace_tiny_nwg, subspace_planes_nwg), for scratch that has
+// no room for more.
 CompressPlan plan_with(const Shape& s, void* ws, bool cold, bool digits, bool coarse) {
     CompressPlan p;
     Carver c(ws);
@@ -177,10 +178,11 @@ CompressPlan plan_with(const Shape& s, void* ws, bool cold, bool digits, bool co
     p.tiny = !cold && s.d == 4 && subspace_tiny_supported((int)s.n[2], (int)s.n[3], s.r[2], s.r[3]);
     p.planes = !cold && s.d == 4 && !p.tiny && subspace_planes_supported(s.n[0] * s.n[1], (int)s.n[2], (int)s.n[3], s.r[2], s.r[3]);
     p.paired = p.tiny || p.planes;
+    bool lone = true;                    // the planes' partial sums alone would need the summing tree
     for (int m = 0; m < s.d; ++m) {
         const size_t n = (size_t)s.n[m], r = (size_t)s.r[m];
         if (p.tiny && m >= 2) p.nsplit[m] = subspace_tiny_nwg(s.dt, s.n[0] * s.n[1], (int)s.n[2], (int)s.n[3], coarse);
-        else if (p.planes && m >= 2) p.nsplit[m] = subspace_planes_nwg(s.dt, s.n[0] * s.n[1], (int)s.n[2], (int)s.n[3]);
+        else if (p.planes && m >= 2) p.nsplit[m] = subspace_planes_nwg(s.dt, s.n[0] * s.n[1], (int)s.n[2], (int)s.n[3], lone || coarse);
         else if (p.digm[m] && p.bfv[m]) p.nsplit[m] = pair_digits_splits(s.numel / s.n[m], (int)n, (int)r);
         else if (p.digm[m]) {
             p.nsplit[m] = subspace_gram_digits_nwg(s.outer(m), (int)n, s.inner(m));
@@ -190,13 +192,14 @@ CompressPlan plan_with(const Shape& s, void* ws, bool cold, bool digits, bool co
         else if (p.longm[m]) p.nsplit[m] = subspace_long_splits(s.outer(m), (int)n, s.inner(m), (int)r);
         else p.nsplit[m] = p.fused[m] ? subspace_small_nwg(s.outer(m), (int)n, s.inner(m), (int)r)
                                       : pair_splits(s.outer(m), (int)n, s.inner(m), (int)r, coarse);
+        lone = lone && (p.fused[m] || p.longm[m]) && p.nsplit[m] <= 32;
         const size_t before = c.off;
         p.part[m] = c.take<double>((size_t)p.nsplit[m] * n * r);
         if (p.nsplit[m] > 32) {
             p.nsplit2[m] = (p.nsplit[m] + 31) / 32;
             p.part2[m] = c.take<double>((size_t)p.nsplit2[m] * n * r);
         }
-        if (m >= 2 && p.paired ? p.tiny : !p.fused[m] && !p.longm[m]) p.split_bytes += c.off - before;
+        if ((p.paired && m >= 2) || (!p.fused[m] && !p.longm[m])) p.split_bytes += c.off - before;
         p.fast_orth[m] = orth_fast_supported((int)r);
         // gram0 leaves the sum in the place of the first of the partial sums that it adds up: a workgroup has read all of its
         // rows before it writes them, and no other reads those rows.  Pays for the Gram matrices of 16-row slices, so that no

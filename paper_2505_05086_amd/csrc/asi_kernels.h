@@ -266,7 +266,9 @@ bool make_subspace_long(DType xt, const void* X, long long outer, int n, long lo
 // The last two modes of X seen as (planes, rows, cols), planes of up to 64 x 64, both from one read of X (asi_planes.hip):
 // part_rows is (nwg, rows, r_rows), part_cols (nwg, cols, r_cols).
 bool subspace_planes_supported(long long planes, int rows, int cols, int r_rows, int r_cols);
-int subspace_planes_nwg(DType xt, long long planes, int rows, int cols);
+// lone: no other mode's partial sums need the summing tree, and no pair product would carry it; make_subspace_planes takes any number up to
+// the one without
+int subspace_planes_nwg(DType xt, long long planes, int rows, int cols, bool lone);
 bool make_subspace_planes(DType xt, const void* X, long long planes, int rows, int cols, const float* U_rows, int r_rows,
                           double* part_rows, const float* U_cols, int r_cols, double* part_cols, int nwg, int32_t* zero,
                           int nzero, Item* out);

@@ -113,12 +113,14 @@ static int planes_pt(DType xt, long long planes, int rows, int cols) {
     while (2 * pt * pb <= 32768 && planes >= 256LL * 2 * pt) pt *= 2;
     return pt;
 }
-int subspace_planes_nwg(DType xt, long long planes, int rows, int cols) {
+int subspace_planes_nwg(DType xt, long long planes, int rows, int cols, bool lone) {
     const int pt = planes_pt(xt, planes, rows, cols);
     const long long ntiles = (planes + pt - 1) / pt;
-    // planes up to 16 x 16 (a tile is 4 KB or less): two tiles a workgroup rather than more partial sums than the orthogonalisation
-    // adds up without a launch of its own (8 x 32 x 16 x 16: a launch of 3.1 us and its gap fewer, the steps 6.6 -> 6.5 us)
-    if (planes_nb(rows, cols) == 1 && ntiles > 32 && ntiles <= 64) return (int)((ntiles + 1) / 2);
+    // Two tiles a workgroup rather than more partial sums than the orthogonalisation adds up without a launch of the summing tree, where these
+    // alone would need it.  Compress, a tile a workgroup -> two: 8 x 32 x 16 x 16 20.4 -> 17.6 us, 8 x 32 x 20 x 20 21.5 -> 20.4, 4 x 38 x 28 x 28 28.9 -> 28.4,
+    // in bf16 21.3 -> 18.6, 21.4 -> 20.0, 30.6 -> 30.0; beyond 32 x 32 a tile is dearer than the launch (8 x 32 x 40 x 40 31.5 -> 35.8), and where the
+    // launch stays, or a pair product carries the tree, nothing is saved (6 x 32 x 28 x 28 22.3 -> 24.7, 3 x 70 x 16 x 16 24.9 -> 25.5).
+    if (lone && planes_nb(rows, cols) <= 2 && ntiles > 32 && ntiles <= 64) return (int)((ntiles + 1) / 2);
     // resident workgroups: one per CU beyond 32 x 32 (accumulators), else two; every one walks the same number of tiles
     const long long most = planes_nb(rows, cols) > 2 ? 256 : 512, per = (ntiles + most - 1) / most;
     return (int)((ntiles + per - 1) / per);
@@ -130,7 +132,7 @@ bool make_subspace_planes(DType xt, const void* X, long long planes, int rows, i
                           int nzero, Item* out) {
     if (!subspace_planes_supported(planes, rows, cols, r_rows, r_cols) || !X || !U_rows || !U_cols || !part_rows || !part_cols)
         return false;
-    if (nzero < 0 || nzero > 256 || nwg != subspace_planes_nwg(xt, planes, rows, cols)) return false;
+    if (nzero < 0 || nzero > 256 || nwg < 1 || nwg > subspace_planes_nwg(xt, planes, rows, cols, false)) return false;
     PlanesJob jb;
     std::memset(&jb, 0, sizeof(jb));
     jb.X = X; jb.planes = planes; jb.pt = planes_pt(xt, planes, rows, cols); jb.ntiles = (planes + jb.pt - 1) / jb.pt;

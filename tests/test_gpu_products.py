@@ -12,7 +12,7 @@ def _sites(call):
     try:
         call()
         torch.cuda.synchronize()
-        return list(B.asi_profile_report())
+        return {site: v["workgroups"] for site, v in B.asi_profile_report().items()}
     finally:
         B.asi_profile_enable(False)
 
@@ -190,6 +190,7 @@ def _check_factors(dims, ranks, modes, dtype, shift, label, tol, ws_bytes=None):
         assert float(torch.linalg.cond(p)) < 500
         err = float((out[m] - want).abs().max() / want.abs().max())
         assert err <= tol, (m, err)
+    return sites
 
 
 # Odd numbers of planes (two share an operand), a last tile that is not full, tiles whose bytes are no multiple of a copy's 16, one
@@ -261,3 +262,16 @@ def test_linear_gradient_with_scratch_for_fewer_partial_sums(dims, ranks, dout, 
     xr = _modes(S, [u.t().contiguous() for u in U])
     want = gy.double().reshape(-1, dout).t().contiguous() @ xr.reshape(-1, dims[2])
     assert float((dW - want).abs().max() / want.abs().max()) <= 1e-5
+
+
+# Planes in 33 to 64 tiles: half as many workgroups where their partial sums alone would need a launch of the summing tree (up to 32 x 32),
+# not where another mode's do (a Gram form of 36 splits) or a pair product carries it (70 entries over 3 x 256 columns).
+# wgs: of the launch that the planes share with the Gram forms before them.
+@pytest.mark.parametrize("dims,ranks,wgs,tree", [
+    ((8, 32, 16, 16), (4, 4, 5, 5), 16 + 16 + 32, False), ((4, 38, 20, 23), (2, 4, 6, 7), 18 + 19, False), ((1, 133, 16, 3), (1, 9, 5, 2), 7 + 34, False),
+    ((6, 32, 28, 28), (3, 4, 9, 9), 49 + 42 + 48, True), ((3, 70, 16, 16), (2, 4, 5, 5), 18 + 53, False), ((4, 40, 33, 20), (2, 4, 9, 6), 40, True)])
+def test_workgroups_of_planes_in_33_to_64_tiles(dims, ranks, wgs, tree):
+    """Sums in fp64 from the activation on: 1e-6, as above."""
+    sites = _check_factors(dims, ranks, (2, 3), "f32", 0, "k_subspace_planes", 1e-6)
+    assert [w for s, w in sites.items() if "k_subspace_planes" in s] == [wgs], sites
+    assert any("presum" in s for s in sites) == tree, sites
