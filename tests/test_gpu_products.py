@@ -138,6 +138,29 @@ def test_plane_products_of_any_size(dims, ranks, cout, dtype):
     assert float((dW.view(cout, -1) - ref).abs().max() / ref.abs().max()) <= 1e-5
 
 
+# The H and W products of the core on an intermediate in fp32, rows in 16-byte pieces and element by element: one, two and four waves a
+# plane (up to 16, 32 and 64 rows), one to four blocks of columns, planes that take one product with the factors' Kronecker product where they
+# come first (7 x 7, 8 x 8) and here do not, the last workgroup of planes not full.
+@pytest.mark.parametrize("dims,ranks,form", [
+    ((40, 90, 7, 7), (7, 9, 5, 5), "1, false"), ((6, 90, 8, 8), (3, 9, 8, 5), "1"), ((9, 60, 2, 16), (3, 5, 2, 9), "1"), ((33, 60, 49, 8), (4, 6, 6, 5), "1"),
+    ((20, 60, 13, 17), (5, 6, 9, 11), "2, false"), ((18, 40, 31, 20), (4, 5, 13, 6), "2"), ((6, 80, 20, 45), (3, 7, 17, 31), "3, false"),
+    ((8, 90, 29, 48), (3, 5, 9, 13), "3"), ((6, 80, 33, 50), (3, 7, 19, 31), "4, false"), ((5, 90, 64, 63), (2, 5, 29, 32), "4, false"), ((6, 80, 40, 52), (3, 7, 19, 31), "4")])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_core_by_planes_of_any_size(dims, ranks, form, dtype):
+    """Against float64: chains of fp32 sums of at most 90 terms a mode, 2e-6 of the largest entry per product."""
+    from paper_2505_05086_amd import binding as B
+    rng = np.random.default_rng(sum(dims) + sum(ranks))
+    x = _dev(rng.standard_normal(dims), dtype)
+    U = [_dev(np.linalg.qr(rng.standard_normal((n, r)))[0]) for n, r in zip(dims, ranks)]
+    desc, S = B.make_desc(dims, ranks, dtype), torch.empty(ranks, device="cuda")
+    ws = B.alloc_workspace(desc, None, 0)
+    ws.fill_(255)                                        # NaN wherever nothing was written
+    sites = _sites(lambda: B.asi_core_project(desc, x, U, S, ws))
+    assert any("k_core_planes<%s>" % form in s for s in sites), sites
+    want = _modes(x, U)
+    assert float((S - want).abs().max() / want.abs().max()) <= 5e-6
+
+
 # Cores of one to fifteen planes with ranks that are no multiple of four, and the first of sixteen: Z rides in the launch of G1, tiled or
 # (the two after: a million entries of grad_out) streaming, where planes have up to 256 entries; last, planes that the plane kernels do not
 # take (a row or a column longer than 64, a rank above 32), beside a G1 of few and of a million entries.
@@ -222,17 +245,23 @@ def test_subspace_step_of_49_to_64_entries(dims, ranks, mode, dtype, shift):
 
 
 # Two and three modes' steps in one launch: both Gram forms and planes of one block; columns beside tiny planes (another mode's step, on its
-# own, between them) and beside planes of two blocks.
+# own, between them), beside a Gram form and planes of two blocks.
 @pytest.mark.parametrize("dims,ranks,modes,names", [
     ((8, 32, 16, 16), (4, 8, 6, 6), (0, 1, 2, 3), ("gram", "gram", "planes")), ((64, 40, 7, 8), (16, 9, 5, 5), (0, 2, 3), ("cols", "tiny")),
-    ((50, 5, 20, 28), (7, 5, 6, 9), (0, 2, 3), ("cols", "planes")), ((4, 3, 12, 12), (2, 3, 4, 5), (0, 1, 2, 3), ("gram", "gram", "planes")),
+    ((50, 5, 20, 28), (7, 5, 6, 9), (0, 1, 2, 3), ("cols", "gram", "planes")), ((4, 3, 12, 12), (2, 3, 4, 5), (0, 1, 2, 3), ("gram", "gram", "planes")),
     ((130, 9, 6, 8), (8, 5, 3, 5), (2, 3), ("tiny",)), ((7, 19, 9, 16), (3, 8, 4, 5), (0, 1, 2, 3), ("gram", "gram", "planes"))])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_subspace_steps_of_several_modes(dims, ranks, modes, names, dtype):
     """As for the steps alone: V in fp32 (columns), 3e-5; sums in fp64, 1e-6."""
     tn = "float" if dtype == "f32" else "asi::bf16_t"
     label = "k_subspace_%s<%s" % (("steps" if len(names) > 1 else names[0]), tn)
-    _check_factors(dims, ranks, modes, dtype, 0, label, 3e-5 if "cols" in names else 1e-6)
+    sites = [s.split("|")[1] for s in _check_factors(dims, ranks, modes, dtype, 0, label, 3e-5 if "cols" in names else 1e-6)]
+    steps = [s.split(" = ")[1].split(" + ") for s in sites if s.startswith("k_subspace_steps")]
+    if len(names) > 1:                                   # the parts in their order, and none of them on its own
+        assert [tuple(p[len("k_subspace_"):p.index("<")] for p in parts) for parts in steps] == [names], sites
+        assert not any(s in parts for parts in steps for s in sites), sites
+    else:
+        assert steps == [], sites
 
 
 # Scratch that holds a partial sum for every 256 columns of a pair product and for every 128 planes of up to 8 x 8, but not the more and
