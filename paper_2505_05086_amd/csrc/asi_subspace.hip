@@ -173,29 +173,27 @@ __global__ __launch_bounds__(256, 2) void k_subspace_small(Batch<SmallJob> bt) {
     }
     // sum the four waves' accumulators through LDS, wave after wave (fixed order)
     double* red = reinterpret_cast<double*>(smem);   // (NBM*16) x (NBR*16) doubles <= 32 KB
-        {
+    __syncthreads();
+    for (int w = 0; w < 4; ++w) {
+        if (wave == w) {
+#pragma unroll
+            for (int mb = 0; mb < NBM; ++mb)
+#pragma unroll
+                for (int nb = 0; nb < NBR; ++nb)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int i = 16 * mb + lg + 4 * v, q = 16 * nb + ll;   // fp64 MFMA result layout
+                        double* p = red + i * (NBR * 16) + q;
+                        *p = (w == 0) ? pacc[mb][nb][v] : *p + pacc[mb][nb][v];
+                    }
+        }
         __syncthreads();
-        for (int w = 0; w < 4; ++w) {
-            if (wave == w) {
-#pragma unroll
-                for (int mb = 0; mb < NBM; ++mb)
-#pragma unroll
-                    for (int nb = 0; nb < NBR; ++nb)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            const int i = 16 * mb + lg + 4 * v, q = 16 * nb + ll;   // fp64 MFMA result layout
-                            double* p = red + i * (NBR * 16) + q;
-                            *p = (w == 0) ? pacc[mb][nb][v] : *p + pacc[mb][nb][v];
-                        }
-            }
-            __syncthreads();
-        }
-        const int n = jb.v.n, r = jb.v.r;
-        double* out = jb.v.part + (long long)lb * n * r;
-        for (int e = tid; e < n * r; e += 256) {
-            const int i = e / r, q = e - i * r;
-            out[e] = red[i * (NBR * 16) + q];
-        }
+    }
+    const int n = jb.v.n, r = jb.v.r;
+    double* out = jb.v.part + (long long)lb * n * r;
+    for (int e = tid; e < n * r; e += 256) {
+        const int i = e / r, q = e - i * r;
+        out[e] = red[i * (NBR * 16) + q];
     }
 }
 
