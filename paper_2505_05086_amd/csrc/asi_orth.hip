@@ -750,7 +750,7 @@ __device__ void apply_slice(const OrthJob& jb, int slice, int final_pass, double
 }
 
 // The rest of the orthonormalisation in one launch.  EVERY workgroup of a mode adds up the mode's Gram matrices, factors the sum and
-// inverts the factor for itself (the same bits in all of them), then takes its slices of 32 rows: a dozen microseconds of one wave's
+// inverts the factor for itself (the same bits in all of them), then takes its runs of slices of 32 rows: a dozen microseconds of one wave's
 // dependent pivots cost nothing on a chip that has nothing else to do, and no workgroup waits for another.  One workgroup that
 // arrived last did it before, inside gram0: a second level of hand-over, loads past the L2, and the factor's way through memory.
 // Certified: Q = P X, wave (half h, block column J) 16 rows times its block column of X, the rows requested when the kernel starts.
