@@ -1105,7 +1105,7 @@ hipError_t launch_core_planes_items(const Item* const* items, int n, hipStream_t
 // ---------------------------------------------------------------------------
 // key bits of the mode-product kernels that only bound sizes (see asi_ttm.hip): NBR
 static unsigned launch_class(const Item& it) {
-    if (it.kind == IT_TTM || it.kind == IT_KSPLIT) return it.key & 0x5e00fu;
+    if (it.kind == IT_TTM || it.kind == IT_KSPLIT) return it.key & 0x7e00fu;
     if (it.kind == IT_TTM_DUO) return it.key & 0xfu;
     return it.key;
 }

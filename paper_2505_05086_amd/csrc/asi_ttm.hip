@@ -299,11 +299,14 @@ __global__ __launch_bounds__(256) void k_ttm_duo(Batch<TtmDuoJob<KRON>> bt) {
 }
 
 // ---- long fibres, few columns ------------------------------------------------------------------
-// A workgroup owns 16 CB columns (CB: one or two); its eight waves deal the K steps (four mode indices each) of the whole mode among
+// A workgroup owns 16 CB columns (CB: one or two); its NW waves (eight or four) deal the K steps (four mode indices each) of the whole mode among
 // themselves, and every operand goes from memory straight into the registers of the lanes that multiply it:
 //   A operand (16 columns x 4 i)  = X at row 4 s + lane / 16 of column 16 cb + lane % 16
 //   B operand (4 i x 16 outputs)  = M at row 4 s + lane / 16; lane ll of a row holds the NBR CONSECUTIVE outputs NBR ll + nb, one
-//                                   load of 4 NBR bytes for NBR blocks of interleaved outputs
+//                                   load of 4 NBR bytes for NBR blocks of interleaved outputs.  CONTIG = false, the matrix stored the other
+//                                   way round: outputs 16 nb + ll, so that the 16 rows of a load follow each other in memory, and no load
+//                                   for steps past the wave's last (the loads are the bound: 130 x 400 over 2304 columns 33.4 -> 16.7 us,
+//                                   the order of outputs alone 22.4 -> 16.7)
 // What bounds it is the number of loads between a workgroup's start and its end, not the products: R steps are requested while
 // the R before them are multiplied.  With four waves, 16 columns, a dword per operand and no step requested ahead a 960-long
 // mode took 180 + 60 loads a wave in four dependent rounds, here 30 x (1 + CB): 960 x 40 over 6272 columns (24 MB) 17.9 -> 13.6 us,
@@ -317,13 +320,12 @@ template <> struct LoadB<2> { typedef unsigned type __attribute__((ext_vector_ty
 template <> struct LoadB<3> { typedef unsigned type __attribute__((ext_vector_type(3))); };
 template <> struct LoadB<4> { typedef unsigned type __attribute__((ext_vector_type(4))); };
 
-constexpr int KS_NT = 512, KS_NW = KS_NT / 64;
-
-template <typename T, int NBR, int CB, bool CONTIG>
-__global__ __launch_bounds__(KS_NT, 4) void k_ttm_ksplit(Batch<TtmJob> bt) {
-    constexpr int R = NBR + CB <= 4 ? 8 : 36 / (NBR + CB);      // steps in flight beside those being multiplied (128 registers)
+template <typename T, int NBR, int CB, bool CONTIG, int NW>
+__global__ __launch_bounds__(64 * NW, 4) void k_ttm_ksplit(Batch<TtmJob> bt) {
+    // steps in flight beside those being multiplied (128 registers); a matrix stored the other way round is bound by the loads themselves
+    constexpr int R = !CONTIG ? 2 : NBR + CB <= 4 ? 8 : 36 / (NBR + CB);
     constexpr int LD = 16 * CB + 4;                  // pitch of a partial tile's row: 16-byte pieces stay aligned
-    extern __shared__ __align__(16) float ks_red[];  // [KS_NW][16 NBR][LD]
+    extern __shared__ __align__(16) float ks_red[];  // [NW][16 NBR][LD]
     int lb;
     const TtmJob& jb = bt.job[locate_xcd(bt, &lb)];
     const T* __restrict__ X = static_cast<const T*>(jb.X);
@@ -349,9 +351,9 @@ __global__ __launch_bounds__(KS_NT, 4) void k_ttm_ksplit(Batch<TtmJob> bt) {
         xoff[cb] = (unsigned)((o - o0) * (long long)n * inner + j);
     }
     const unsigned row = (unsigned)inner;
-    const unsigned qoff = (unsigned)(q0 + NBR * ll) * ms_q;
+    const unsigned qoff = (unsigned)(q0 + (CONTIG ? NBR * ll : ll)) * ms_q;
     const int steps = (n + 3) >> 2;
-    const int mine = wave < steps ? (steps - 1 - wave) / KS_NW + 1 : 0;       // steps wave, wave + 8, ..
+    const int mine = wave < steps ? (steps - 1 - wave) / NW + 1 : 0;       // steps wave, wave + 8, ..
     const bool ragged = (n & 3) != 0;
 #if defined(__HIP_DEVICE_COMPILE__)
     const auto mrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(jb.Mp), 0, (int)(4u * ((unsigned)(n - 1) * ms_i + (unsigned)(r - 1) * ms_q + 1u)), 0x00027000);
@@ -361,8 +363,9 @@ __global__ __launch_bounds__(KS_NT, 4) void k_ttm_ksplit(Batch<TtmJob> bt) {
     auto fetch = [&](int t0, Stage& g) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < R; ++u) {
+            if (!CONTIG && t0 + u >= mine) continue;
             const int t = t0 + u < mine ? t0 + u : mine - 1;                  // uniform; a repeated step is not multiplied
-            const int i0 = 4 * (wave + KS_NW * t), i = i0 + lg;
+            const int i0 = 4 * (wave + NW * t), i = i0 + lg;
             const unsigned xr = (unsigned)(i < n ? i : n - 1) * row;
 #pragma unroll
             for (int cb = 0; cb < CB; ++cb) g.x[u][cb] = Xw[xoff[cb] + xr];
@@ -376,7 +379,7 @@ __global__ __launch_bounds__(KS_NT, 4) void k_ttm_ksplit(Batch<TtmJob> bt) {
             } else {
                 unsigned e[NBR];
 #pragma unroll
-                for (int nb = 0; nb < NBR; ++nb) e[nb] = __builtin_amdgcn_raw_buffer_load_b32(mrsrc, mo + (int)(4u * nb * ms_q), 0, 0);
+                for (int nb = 0; nb < NBR; ++nb) e[nb] = __builtin_amdgcn_raw_buffer_load_b32(mrsrc, mo + (int)(64u * nb * ms_q), 0, 0);
                 __builtin_memcpy(&g.m[u], e, sizeof(e));
             }
 #endif
@@ -391,7 +394,7 @@ __global__ __launch_bounds__(KS_NT, 4) void k_ttm_ksplit(Batch<TtmJob> bt) {
 #pragma unroll
         for (int u = 0; u < R; ++u)
             if (t0 + u < mine) {                     // uniform
-                const int s = wave + KS_NW * (t0 + u);
+                const int s = wave + NW * (t0 + u);
                 float x[CB], m[NBR];
 #pragma unroll
                 for (int cb = 0; cb < CB; ++cb) x[cb] = to_f32(g.x[u][cb]);
@@ -427,20 +430,21 @@ __global__ __launch_bounds__(KS_NT, 4) void k_ttm_ksplit(Batch<TtmJob> bt) {
     for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
         for (int nb = 0; nb < NBR; ++nb)
-            *reinterpret_cast<v4f*>(ks_red + (wave * 16 * NBR + NBR * ll + nb) * LD + 16 * cb + 4 * lg) = acc[cb][nb];
+            *reinterpret_cast<v4f*>(ks_red + (wave * 16 * NBR + (CONTIG ? NBR * ll + nb : 16 * nb + ll)) * LD + 16 * cb + 4 * lg) = acc[cb][nb];
     __syncthreads();
     constexpr int W = 16 * CB;
     const int cl = tid % W;
     const long long cc = c0 + cl;
     if (cc < ncols) {
         const long long o = cc / inner, j = cc - o * inner;
-        for (int ql = tid / W; ql < NBR * 16; ql += KS_NT / W) {
+        for (int ql = tid / W; ql < NBR * 16; ql += 64 * NW / W) {
             const int q = q0 + ql;
             if (q < r) {
-                float p[KS_NW];
+                float p[8] = {};
 #pragma unroll
-                for (int w = 0; w < KS_NW; ++w) p[w] = ks_red[(w * 16 * NBR + ql) * LD + cl];
-                const float v = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+                for (int w = 0; w < NW; ++w) p[w] = ks_red[(w * 16 * NBR + ql) * LD + cl];
+                float v = (p[0] + p[1]) + (p[2] + p[3]);
+                if (NW == 8) v += (p[4] + p[5]) + (p[6] + p[7]);
                 const long long idx = (o * r + q) * inner + j;
                 Y[idx] = beta ? Y[idx] + v : v;
             }
@@ -637,7 +641,7 @@ static bool ttm_expand_supported(DType xt, long long inner, int n, int r, const 
 // ---- host side -----------------------------------------------------------------------------------
 // key bits: [0] bf16 input, [1] LASTMODE, [2] KRON, [3] split kernel, [4..6] NBR-1,
 // [14] K chunks of 64 (tiled kernel along the last mode), [15] the vector-ALU kernel for very short modes,
-// [16] split kernel: two column blocks per workgroup, [18] split kernel: rows of the matrix contiguous.
+// [16] split kernel: two column blocks per workgroup, [17] four waves, [18] rows of the matrix contiguous.
 // Bits 4..6 only bound sizes.
 static unsigned ttm_key(bool bf16, bool last, bool kron, bool ksplit, int nbr, bool kc64) {
     return (bf16 ? 1u : 0u) | (last ? 2u : 0u) | (kron ? 4u : 0u) | (ksplit ? 8u : 0u) | ((unsigned)(nbr - 1) << 4) | (kc64 ? 0x4000u : 0u);
@@ -654,10 +658,17 @@ static bool ksplit_reaches(long long outer, int n, long long inner, long long ms
     const long long slabs = 64 / inner + 2 < outer ? 64 / inner + 2 : outer;
     return ms_i > 0 && ms_q > 0 && slabs * n * inner < (1LL << 30) && (n + 3) * ms_i + (r + 63) * ms_q < (1LL << 29);
 }
-// Column blocks per workgroup: the fewest column blocks that a CU multiplies one after the other, two a workgroup on a tie (they share the
-// loads of the matrix).  One | two: 512 x 48 over 3 x 3136 columns (588 | 294 workgroups) 13.5 | 15.0 us, 960 x 40 over 6272 (392 |
-// 196) 14.8 | 13.6, 256 x 32 over 12544 (784 | 392) 8.9 | 6.7; four: 9.2 there.
-static int ksplit_cb(long long ncols) {
+// Waves: eight for long modes, whose chain of steps is what a launch waits for; four up to 160 entries, of which eight waves would get two to
+// five steps each and pay the sum of eight partial tiles for them (one layer of 77 x 3 over 11280 columns 7.6 -> 6.4 us, eight 28.4 -> 13.9 with the two
+// column blocks below, G1 of 100 x 20 over 9800 columns eight times 32.6 -> 16.3; 200 entries 17.4 -> 14.9 in eight layers but 6.8 -> 8.3 in one),
+// and for a matrix stored the other way round, whose loads of a row per lane are the bound (190 entries 25.5 -> 18.7).
+static int ksplit_waves(int n, bool contig) { return n <= 160 || !contig ? 4 : 8; }
+// Column blocks per workgroup.  Eight waves: the fewest column blocks that a CU multiplies one after the other, two a workgroup on a tie (they
+// share the loads of the matrix).  One | two: 512 x 48 over 3 x 3136 columns (588 | 294 workgroups) 13.5 | 15.0 us, 960 x 40 over 6272 (392 |
+// 196) 14.8 | 13.6, 256 x 32 over 12544 (784 | 392) 8.9 | 6.7; four: 9.2 there.  Four waves, of which a CU holds several workgroups: two as well where
+// that leaves every CU one (130 x 400 over 9000 columns 46.5 -> 33.5 us, 77 x 3 over 3 x 11280 9.4 -> 8.7; with 256 it changes nothing).
+static int ksplit_cb(long long ncols, int nw) {
+    if (nw == 4 && (ncols + 15) / 16 >= 512) return 2;
     const long long one = ((ncols + 15) / 16 + 255) / 256, two = ((ncols + 31) / 32 + 255) / 256 * 2;
     return one < two ? 1 : 2;
 }
@@ -689,14 +700,14 @@ static bool fill_ttm(DType xt, const void* X, long long outer, int n, long long 
         out->kind = IT_TTM; out->key = ttm_key(xt == BF16, false, false, false, 1, false) | 0x8000u;
         std::snprintf(out->label, sizeof(out->label), "k_ttm_thin<%s, %d>", tn, n <= 8 ? 8 : 16);
     } else if (!kron && prefer_ksplit(ncols, n, inner) && ksplit_reaches(outer, n, inner, ms_i, ms_q, r)) {
+        const bool contig = ms_q == 1;
+        const int nw = ksplit_waves(n, contig), cb = ksplit_cb(ncols, nw);
         const int nbr = r >= 64 ? 4 : (r + 15) / 16;
-        const int cb = ksplit_cb(ncols);
         const long long gx = (ncols + 16 * cb - 1) / (16 * cb);
         jb.gx = (int)gx; jb.gy = (r + nbr * 16 - 1) / (nbr * 16);
         if (gx * jb.gy > 0x3fffffffLL) return false;
-        const bool contig = ms_q == 1;
-        out->kind = IT_KSPLIT; out->key = ttm_key(xt == BF16, false, false, true, nbr, false) | ((unsigned)(cb - 1) << 16) | (contig ? 0x40000u : 0u);
-        std::snprintf(out->label, sizeof(out->label), "k_ttm_ksplit<%s, %d, %d, %s>", tn, nbr, cb, contig ? "true" : "false");
+        out->kind = IT_KSPLIT; out->key = ttm_key(xt == BF16, false, false, true, nbr, false) | ((unsigned)(cb - 1) << 16) | (nw == 4 ? 0x20000u : 0u) | (contig ? 0x40000u : 0u);
+        std::snprintf(out->label, sizeof(out->label), "k_ttm_ksplit<%s, %d, %d, %s, %d>", tn, nbr, cb, contig ? "true" : "false", nw);
     } else {
         // short inner extents: tiles of whole outer indices (stores then run contiguously)
         jb.tile_cols = (!last && inner < TM_TC) ? (int)(TM_TC / inner * inner) : TM_TC;
@@ -747,21 +758,26 @@ static void launch_tiled(int nbr, const Batch<TtmJob>& b, dim3 grid, hipStream_t
         default: hipLaunchKernelGGL((k_ttm_mfma<T, LAST, 4, KM>), grid, 256, 0, st, b); break;
     }
 }
-template <typename T, int NBR, int CB, bool CONTIG>
+template <typename T, int NBR, int CB, bool CONTIG, int NW>
 static hipError_t launch_split_one(const Batch<TtmJob>& b, dim3 grid, hipStream_t st) {
-    constexpr size_t lds = sizeof(float) * KS_NW * 16 * NBR * (16 * CB + 4);
+    constexpr size_t lds = sizeof(float) * NW * 16 * NBR * (16 * CB + 4);
     if (lds > 64 * 1024) {
         static LdsAllowed allowed;
-        const hipError_t e = allow_lds(reinterpret_cast<const void*>(k_ttm_ksplit<T, NBR, CB, CONTIG>), lds, allowed);
+        const hipError_t e = allow_lds(reinterpret_cast<const void*>(k_ttm_ksplit<T, NBR, CB, CONTIG, NW>), lds, allowed);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((k_ttm_ksplit<T, NBR, CB, CONTIG>), grid, KS_NT, lds, st, b);
+    hipLaunchKernelGGL((k_ttm_ksplit<T, NBR, CB, CONTIG, NW>), grid, 64 * NW, lds, st, b);
     return hipGetLastError();
 }
+template <typename T, int NBR, int CB>
+static hipError_t launch_split_cb(int nw, bool contig, const Batch<TtmJob>& b, dim3 grid, hipStream_t st) {
+    if (!contig) return nw == 4 ? launch_split_one<T, NBR, CB, false, 4>(b, grid, st) : hipErrorInvalidValue;
+    return nw == 8 ? launch_split_one<T, NBR, CB, true, 8>(b, grid, st) : launch_split_one<T, NBR, CB, true, 4>(b, grid, st);
+}
 template <typename T, int NBR>
-static hipError_t launch_split(int cb, bool contig, const Batch<TtmJob>& b, dim3 grid, hipStream_t st) {
-    if (cb == 2) return contig ? launch_split_one<T, NBR, 2, true>(b, grid, st) : launch_split_one<T, NBR, 2, false>(b, grid, st);
-    if (cb == 1) return contig ? launch_split_one<T, NBR, 1, true>(b, grid, st) : launch_split_one<T, NBR, 1, false>(b, grid, st);
+static hipError_t launch_split(int cb, int nw, bool contig, const Batch<TtmJob>& b, dim3 grid, hipStream_t st) {
+    if (cb == 2) return launch_split_cb<T, NBR, 2>(nw, contig, b, grid, st);
+    if (cb == 1) return launch_split_cb<T, NBR, 1>(nw, contig, b, grid, st);
     return hipErrorInvalidValue;
 }
 
@@ -838,7 +854,7 @@ hipError_t launch_ttm_items(const Item* const* items, int n, hipStream_t st, cha
     const unsigned key = items[0]->key;
     const bool bf16 = key & 1u, last = key & 2u, kron = key & 4u, ksplit = key & 8u;
     const bool kc64 = key & 0x4000u, contig = key & 0x40000u;
-    const int cb = 1 + (int)((key >> 16) & 1u);
+    const int cb = 1 + (int)((key >> 16) & 1u), nw = (key >> 17) & 1u ? 4 : 8;
     if (key & 0x8000u) {             // very short mode: one instantiation per bound on n
         int nmax = 8;
         for (int j = 0; j < n; ++j) {
@@ -859,23 +875,23 @@ hipError_t launch_ttm_items(const Item* const* items, int n, hipStream_t st, cha
     }
     if (label_out) {
         const char* tn = bf16 ? "asi::bf16_t" : "float";
-        if (ksplit) std::snprintf(label_out, 96, "k_ttm_ksplit<%s, %d, %d, %s>", tn, nbr, cb, contig ? "true" : "false");
+        if (ksplit) std::snprintf(label_out, 96, "k_ttm_ksplit<%s, %d, %d, %s, %d>", tn, nbr, cb, contig ? "true" : "false", nw);
         else std::snprintf(label_out, 96, "k_ttm_mfma<%s, %s, %d, %d>", tn, last ? "true" : "false", nbr, kron ? (kc64 ? 2 : 1) : (kc64 ? 3 : 0));
     }
     if (ksplit) {
         if (!bf16) {
             switch (nbr) {
-                case 1: return launch_split<float, 1>(cb, contig, b, grid, st);
-                case 2: return launch_split<float, 2>(cb, contig, b, grid, st);
-                case 3: return launch_split<float, 3>(cb, contig, b, grid, st);
-                default: return launch_split<float, 4>(cb, contig, b, grid, st);
+                case 1: return launch_split<float, 1>(cb, nw, contig, b, grid, st);
+                case 2: return launch_split<float, 2>(cb, nw, contig, b, grid, st);
+                case 3: return launch_split<float, 3>(cb, nw, contig, b, grid, st);
+                default: return launch_split<float, 4>(cb, nw, contig, b, grid, st);
             }
         } else {
             switch (nbr) {
-                case 1: return launch_split<bf16_t, 1>(cb, contig, b, grid, st);
-                case 2: return launch_split<bf16_t, 2>(cb, contig, b, grid, st);
-                case 3: return launch_split<bf16_t, 3>(cb, contig, b, grid, st);
-                default: return launch_split<bf16_t, 4>(cb, contig, b, grid, st);
+                case 1: return launch_split<bf16_t, 1>(cb, nw, contig, b, grid, st);
+                case 2: return launch_split<bf16_t, 2>(cb, nw, contig, b, grid, st);
+                case 3: return launch_split<bf16_t, 3>(cb, nw, contig, b, grid, st);
+                default: return launch_split<bf16_t, 4>(cb, nw, contig, b, grid, st);
             }
         }
     } else if (kron) {           // always LASTMODE
