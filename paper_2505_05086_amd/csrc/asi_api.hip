@@ -832,9 +832,19 @@ struct ConvBuild {
     const float* G1 = nullptr;       // what the correlation reads: p.G1 or grad_out itself
 };
 
-// validation and steps 1 to 3
+// Z plane by plane or as one product with the Kronecker product of the factors, where there is one (planes of up to 256 entries).  Planes take 7
+// to 9 us beside G1, whatever their size, until their waves (16 rows each, the layers' together) fill the chip, and 3.5 us for every filling
+// beyond; the product takes 7 to 13 us and grows with the entries.  Planes | product, with G1: 2048 waves of 7 x 7 8.4 | 10.2 us, of 4 x 4 8.1 |
+// 8.0, 4096 of 41 x 6 8.8 | 9.8; 6144 of 5 x 5 11.9 | 8.7, of 10 x 10 13.6 | 12.8, of 14 x 14 14.8 | 17.4; 16384 of 4 x 4 20.5 | 9.5, of 7 x 7 21.6 | 12.8, of
+// 14 x 14 25.9 | 26.7; 12288 of 20 x 12 20.8 | 17.3.
+bool z_by_planes(const CorrGeom& g, int layers) {
+    const long long waves = (long long)g.r1 * g.r2 * (g.H <= 16 ? 1 : (g.H <= 32 ? 2 : 4)), entries = (long long)g.r1 * g.r2 * g.H * g.W;
+    return waves * layers <= 4096 || entries >= 160 * waves;
+}
+
+// validation and steps 1 to 3; layers: of the batch
 asi_status build_conv_maps(const asi_tensor_desc* desc, const float* S, const float* const* U, const void* grad_out,
-                           const asi_conv2d_desc* conv, const float* dW, void* ws, size_t ws_bytes, ConvBuild* cb, Program& pg) {
+                           const asi_conv2d_desc* conv, const float* dW, void* ws, size_t ws_bytes, int layers, ConvBuild* cb, Program& pg) {
     Shape s;
     asi_status why;
     if (!parse_desc(desc, &s, &why)) return why;
@@ -858,7 +868,7 @@ asi_status build_conv_maps(const asi_tensor_desc* desc, const float* S, const fl
     const float* Sz = expand_core ? p.S1 : S;
     cb->G1 = expand_core ? static_cast<const float*>(grad_out) : p.G1;
     Item planes;
-    const bool by_planes = make_z_planes(Sz, (long long)g.r1 * g.r2, r3, r4, U[2], g.H, U[3], g.W, p.Z, &planes);
+    const bool by_planes = (p.Z1 || z_by_planes(g, layers)) && make_z_planes(Sz, (long long)g.r1 * g.r2, r3, r4, U[2], g.H, U[3], g.W, p.Z, &planes);
     if (expand_core) {
         // 1'. S1[b,...] = sum_i U1[b,i] S[i,...]
         ASI_TRYS(add_ttm(pg, "S1", F32, S, 1, g.r1, (long long)g.r2 * r3 * r4, U[0], 1, g.r1, cg.B, p.S1, 0));
@@ -1146,7 +1156,7 @@ asi_status asi_weight_grad_conv2d_batch(int32_t count, const asi_tensor_desc* de
     std::vector<Program> progs(count);
     std::vector<ConvBuild> cb(count);
     for (int l = 0; l < count; ++l)
-        ASI_TRYS(build_conv_maps(&descs[l], S[l], U[l], grad_out[l], &convs[l], dW[l], ws[l], ws_bytes[l], &cb[l], progs[l]));
+        ASI_TRYS(build_conv_maps(&descs[l], S[l], U[l], grad_out[l], &convs[l], dW[l], ws[l], ws_bytes[l], count, &cb[l], progs[l]));
     // Correlations at the same place of their programs and on the same kernel go out together and share the CUs; the others of a
     // batch run by themselves, one after the other, and are split like layers alone (a 3x3, a 1x1, a 5x5 and a 14x14
     // layer in one batch, all split as if they shared one launch: 174 us for the weight gradients instead of 137).

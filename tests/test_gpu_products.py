@@ -190,6 +190,32 @@ def test_small_cores_keep_g1_and_z_in_one_launch(dims, ranks, cout, k, dtype):
     assert float((dW - want).abs().max() / want.abs().max()) <= 1e-5
 
 
+# Planes whose waves fill the chip once (4096) and no longer, of few entries (one product with the factors' Kronecker product beyond the line) and
+# of 160 entries a wave and more; the layers of a batch together.
+@pytest.mark.parametrize("dims,ranks,layers,planes", [
+    ((64, 64, 4, 5), (64, 64, 1, 2), 1, True), ((65, 64, 4, 5), (65, 64, 1, 2), 1, False), ((64, 70, 7, 7), (16, 64, 2, 3), 4, True), ((64, 70, 7, 7), (16, 64, 2, 3), 5, False),
+    ((64, 64, 41, 6), (16, 64, 5, 1), 1, True), ((64, 66, 41, 6), (16, 65, 5, 1), 1, False), ((70, 64, 16, 10), (65, 64, 3, 2), 1, True)])
+def test_z_by_planes_or_by_the_kronecker_product(dims, ranks, layers, planes):
+    """A 1 x 1 gradient against float64: chains of fp32 sums of at most 500 terms, 2e-6 of the largest entry per product."""
+    from paper_2505_05086_amd import binding as B
+    rng = np.random.default_rng(sum(dims) + layers)
+    cout = 3
+    U = [_dev(np.linalg.qr(rng.standard_normal((n, r)))[0]) for n, r in zip(dims, ranks)]
+    S, gy = _dev(rng.standard_normal(ranks)), _dev(rng.standard_normal((dims[0], cout) + dims[2:]))
+    desc, conv = B.make_desc(dims, ranks, "f32"), B.make_conv(cout, 1, 1, (1, 1), (0, 0), (1, 1), 1)
+    ws = [B.alloc_workspace(desc, conv, 0) for _ in range(layers)]
+    for w in ws:
+        w.fill_(255)
+    dW = [torch.empty(cout, dims[1], 1, 1, device="cuda") for _ in range(layers)]
+    sites = _sites(lambda: B.asi_weight_grad_conv2d_batch([desc] * layers, [S] * layers, [U] * layers, [gy] * layers, [conv] * layers, dW, [False] * layers, ws))
+    z = [s.split("|")[1] for s in sites if s.endswith("Z")]
+    assert len(z) == 1 and (", true>" not in z[0] and "k_ttm_mfma" not in z[0]) == planes, sites
+    xr = _modes(S, [u.t().contiguous() for u in U])
+    want = gy.double().transpose(0, 1).reshape(cout, -1).contiguous() @ xr.transpose(0, 1).reshape(dims[1], -1).t().contiguous()
+    for d in dW:
+        assert float((d.view(cout, -1) - want).abs().max() / want.abs().max()) <= 1e-5
+
+
 def _check_factors(dims, ranks, modes, dtype, shift, label, tol, ws_bytes=None):
     from paper_2505_05086_amd import binding as B
     rng = np.random.default_rng(sum(dims) + sum(ranks) + shift)
