@@ -752,8 +752,18 @@ asi_status build_compress(const asi_tensor_desc* desc, const void* A, const floa
     return ASI_OK;
 }
 
+// The H and W products of a core whose planes have up to 64 entries, after another mode's product: plane by plane, or as one product with the
+// Kronecker product of the factors.  Planes take 6.5 us until their waves (16 rows each, the layers' together) fill the chip and 0.7 us for
+// every 1024 beyond; the product takes 6.6 us (4 x 4 at ranks 2, 2) to 10 (8 x 8 at 6, 6) whatever their number here.  Planes | product: 1536
+// waves of 7 x 7 6.3 | 9.0 us; 3840 of 8 x 8 7.6 to 7.9 | 8.2 to 10.1; 4096 of 4 x 4 7.9 | 6.6, of 8 x 8 7.8 to 8.3 | 8.2 to 10.1; 8192 of 7 x 7
+// 11.2 | 9.6; 24576 of 8 x 8 22.0 | 9.7.
+bool core_by_planes(long long planes, long long H, long long W, int layers) {
+    return planes * (H <= 16 ? 1 : (H <= 32 ? 2 : 4)) * layers <= (H * W <= 16 ? 2048 : 4096);
+}
+
+// layers: of the batch
 asi_status build_core(const asi_tensor_desc* desc, const void* A, const float* const* U, float* S, void* ws,
-                      size_t ws_bytes, const int* order, Program& pg) {
+                      size_t ws_bytes, const int* order, int layers, Program& pg) {
     Shape s;
     asi_status why;
     if (!parse_desc(desc, &s, &why)) return why;
@@ -803,7 +813,7 @@ asi_status build_core(const asi_tensor_desc* desc, const void* A, const float* c
             if (ks > 1)
                 ASI_ADD(pg, "core", 4.0 * cols * r * (ks + 1), cols * r * ks,
                         make_sum_partials(p.part, ks, (long long)outer * r, dst, 0, it__));
-        } else if (p.kron && m == 2 && sdt == F32 && k >= 1 &&
+        } else if (p.kron && m == 2 && sdt == F32 && k >= 1 && core_by_planes(outer, s.n[2], s.n[3], layers) &&
                    (pg.items.emplace_back(), make_core_planes(static_cast<const float*>(src), outer, (int)s.n[2], (int)s.n[3], U[2], s.r[2],
                                                               U[3], s.r[3], dst, &pg.items.back()) || (pg.items.pop_back(), false))) {
             // the same plane by plane where the tensor has shrunk already
@@ -1143,7 +1153,7 @@ asi_status asi_core_project_batch(int32_t count, const asi_tensor_desc* descs, c
     }
     std::vector<Program> progs(count);
     for (int l = 0; l < count; ++l)
-        ASI_TRYS(build_core(&descs[l], A[l], U[l], S[l], ws[l], ws_bytes[l], have_common ? common : nullptr, progs[l]));
+        ASI_TRYS(build_core(&descs[l], A[l], U[l], S[l], ws[l], ws_bytes[l], have_common ? common : nullptr, count, progs[l]));
     return flush(progs, static_cast<hipStream_t>(stream), "core");
 }
 

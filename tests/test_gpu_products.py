@@ -164,6 +164,30 @@ def test_core_by_planes_of_any_size(dims, ranks, form, dtype):
     assert float((S - want).abs().max() / want.abs().max()) <= 5e-6
 
 
+# The same on planes of up to 64 entries whose waves (the layers' together) fill the chip once and no longer, and one more plane than that: one
+# product with the factors' Kronecker product.
+@pytest.mark.parametrize("dims,ranks,layers,planes", [
+    ((150, 256, 7, 7), (16, 40, 3, 3), 1, True), ((150, 257, 7, 7), (16, 40, 3, 3), 1, False), ((90, 128, 8, 8), (8, 80, 4, 5), 4, True),
+    ((90, 129, 8, 8), (8, 80, 4, 5), 4, False), ((60, 128, 60, 1), (8, 24, 9, 1), 1, True), ((60, 129, 60, 1), (8, 24, 9, 1), 1, False),
+    ((90, 256, 4, 4), (8, 60, 2, 2), 1, True), ((90, 257, 4, 4), (8, 60, 2, 2), 1, False)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_core_by_planes_or_by_the_kronecker_product(dims, ranks, layers, planes, dtype):
+    """Against float64: chains of fp32 sums of at most 257 terms a mode, 2e-6 of the largest entry per product."""
+    from paper_2505_05086_amd import binding as B
+    rng = np.random.default_rng(sum(dims) + layers)
+    xs = [_dev(rng.standard_normal(dims), dtype) for _ in range(layers)]
+    U = [_dev(np.linalg.qr(rng.standard_normal((n, r)))[0]) for n, r in zip(dims, ranks)]
+    desc, S = B.make_desc(dims, ranks, dtype), [torch.empty(ranks, device="cuda") for _ in xs]
+    ws = [B.alloc_workspace(desc, None, 0) for _ in xs]
+    for w in ws:
+        w.fill_(255)                                     # NaN wherever nothing was written
+    sites = _sites(lambda: B.asi_core_project_batch([desc] * layers, xs, [U] * layers, S, ws))
+    assert any("k_core_planes" in s for s in sites) == planes, sites
+    for s, x in zip(S, xs):
+        want = _modes(x, U)
+        assert float((s - want).abs().max() / want.abs().max()) <= 5e-6
+
+
 # Cores of one to fifteen planes with ranks that are no multiple of four, and the first of sixteen: Z rides in the launch of G1, tiled or
 # (the two after: a million entries of grad_out) streaming, where planes have up to 256 entries; last, planes that the plane kernels do not
 # take (a row or a column longer than 64, a rank above 32), beside a G1 of few and of a million entries.
