@@ -341,7 +341,8 @@ static int pair_best_splits(long long ncols, int n, int r) {
 }
 int pair_splits(long long outer, int n, long long inner, int r, bool coarse) {
     const long long ncols = outer * inner;
-    if (!coarse) return pair_best_splits(ncols, n, r);
+    const int fine = pair_best_splits(ncols, n, r);
+    if (!coarse) return fine;
     // A count and no model of the tiles above: scratch that holds this many partial sums has always been accepted.  The least rounds x (columns of
     // a split, in chunks, + 128) of 512 workgroups of 64 x 32 (64 along the last mode), 256 columns or more a split.
     const int tq = (inner == 1 && r > 32 && ncols >= 4096) ? 64 : 32;
@@ -357,7 +358,7 @@ int pair_splits(long long outer, int n, long long inner, int r, bool coarse) {
     }
     // (no split may be empty with 16 columns as the unit either)
     while (best > 1 && pair_cols_per_split(ncols, best) * (best - 1) >= ncols) --best;
-    return best;
+    return std::min(best, fine);
 }
 
 int presum_blocks(const PresumArgs& a) {

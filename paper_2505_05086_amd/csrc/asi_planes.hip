@@ -48,19 +48,27 @@ __global__ __launch_bounds__(PN_NT, 4) void k_subspace_tiny(Batch<TinyJob> bt) {
 bool subspace_tiny_supported(int rows, int cols, int r_rows, int r_cols) {
     return rows <= 8 && cols <= 8 && r_rows <= rows && r_cols <= cols;
 }
-static int tiny_pt(DType xt, int rows, int cols) {
-    // (an operand's rows past a plane reach up to 63 elements past the last one: they stay in the buffer)
-    const int pt = (TY_BUF - 256) / (rows * cols * (xt == F32 ? 4 : 2)) / 8 * 8;
-    return pt > 512 ? 512 : pt;
+// Planes that a buffer holds (an operand's rows past a plane reach up to 63 elements past the last one: they stay in the buffer).
+static int tiny_fit(DType xt, int rows, int cols) { return std::min(512, (TY_BUF - 256) / (rows * cols * (xt == F32 ? 4 : 2)) / 8 * 8); }
+// Planes per tile: 128, a workgroup's four waves each a chain of 16 pairs of planes (64 at 512: 10 of a launch's 17 us
+// where there are few tiles); twice that and four times while every CU still gets a tile, for fewer partial sums.  Compress, tiles of 512 or as
+// many as fit | this: 590 planes of 7 x 1 60.0 -> 51.9 us, 2048 43.6 -> 36.5, 16384 in bf16 60.1 -> 51.6, 65536 83.9 -> 78.2; 2048 of 2 x 2 44.0 -> 35.8,
+// 65536 of 4 x 4 84.1 -> 80.9; tiles of 64 take 51.3 and 35.8, but 53.3 for the 16384 and 79.8 for the 65536.
+static int tiny_pt(DType xt, long long planes, int rows, int cols) {
+    const int fit = tiny_fit(xt, rows, cols);
+    int pt = std::min(128, fit);
+    while (2 * pt <= fit && planes >= 256LL * 2 * pt) pt *= 2;
+    return pt;
 }
 // two workgroups per CU are resident, and every one walks the same number of tiles
 static long long tiny_even(long long tiles) {
     const long long per = (tiles + 511) / 512;
     return (tiles + per - 1) / per;
 }
+// coarse: no more than one for 128 planes and one for a full buffer
 int subspace_tiny_nwg(DType xt, long long planes, int rows, int cols, bool coarse) {
-    const long long pt = tiny_pt(xt, rows, cols), fine = tiny_even((planes + pt - 1) / pt);
-    return (int)(coarse ? std::min(fine, tiny_even((planes + 127) / 128)) : fine);
+    const long long pt = tiny_pt(xt, planes, rows, cols), fit = tiny_fit(xt, rows, cols), fine = tiny_even((planes + pt - 1) / pt);
+    return (int)(coarse ? std::min({fine, tiny_even((planes + 127) / 128), tiny_even((planes + fit - 1) / fit)}) : fine);
 }
 // key: [0] bf16, [1] memory-to-LDS copies
 bool make_subspace_tiny(DType xt, const void* X, long long planes, int rows, int cols, const float* U_rows, int r_rows,
@@ -70,7 +78,7 @@ bool make_subspace_tiny(DType xt, const void* X, long long planes, int rows, int
     if (planes < 1 || rows < 1 || cols < 1 || nwg < 1 || nwg > subspace_tiny_nwg(xt, planes, rows, cols)) return false;
     TinyJob jb;
     std::memset(&jb, 0, sizeof(jb));
-    jb.X = X; jb.planes = planes; jb.pt = tiny_pt(xt, rows, cols); jb.ntiles = (planes + jb.pt - 1) / jb.pt;
+    jb.X = X; jb.planes = planes; jb.pt = tiny_pt(xt, planes, rows, cols); jb.ntiles = (planes + jb.pt - 1) / jb.pt;
     jb.U[0] = U_rows; jb.U[1] = U_cols; jb.part[0] = part_rows; jb.part[1] = part_cols;
     jb.rows = rows; jb.cols = cols; jb.r[0] = r_rows; jb.r[1] = r_cols; jb.nwg = nwg;
     *out = Item();

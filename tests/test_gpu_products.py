@@ -270,10 +270,13 @@ def _check_factors(dims, ranks, modes, dtype, shift, label, tol, ws_bytes=None):
 
 
 # Odd numbers of planes (two share an operand), a last tile that is not full, tiles whose bytes are no multiple of a copy's 16, one
-# plane, one row, one column, planes of 64 and of one element, the last rows of an operand past the planes; one element off.
+# plane, one row, one column, planes of 64 and of one element, the last rows of an operand past the planes; one element off.  Tiles of 128 planes, whole and one over, of 256
+# from 65536 planes on and of 512 (elements of up to 2 x 2 and 3 x 2 in bf16) from 131072 on.
 @pytest.mark.parametrize("dims,ranks", [
     ((9, 9, 7, 7), (4, 5, 5, 5)), ((1, 163, 5, 5), (1, 9, 5, 3)), ((1, 1, 8, 8), (1, 1, 1, 1)), ((3, 701, 1, 8), (3, 7, 1, 8)), ((5, 103, 8, 3), (3, 4, 8, 3)),
-    ((67, 65, 6, 7), (9, 8, 1, 7)), ((1, 4099, 1, 1), (1, 1, 1, 1)), ((700, 31, 8, 8), (6, 5, 8, 8)), ((257, 129, 4, 2), (5, 6, 3, 2))])
+    ((67, 65, 6, 7), (9, 8, 1, 7)), ((1, 4099, 1, 1), (1, 1, 1, 1)), ((700, 31, 8, 8), (6, 5, 8, 8)), ((257, 129, 4, 2), (5, 6, 3, 2)),
+    ((16, 8, 3, 5), (5, 4, 2, 3)), ((43, 3, 2, 4), (5, 2, 2, 3)), ((257, 255, 3, 2), (7, 6, 2, 1)), ((256, 256, 2, 3), (7, 6, 2, 2)), ((512, 256, 2, 2), (6, 5, 1, 2)),
+    ((521, 257, 3, 2), (6, 5, 2, 1))])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("shift", [0, 1])
 def test_tiny_planes_at_the_edges_of_their_tiles(dims, ranks, dtype, shift):
@@ -317,11 +320,11 @@ def test_subspace_steps_of_several_modes(dims, ranks, modes, names, dtype):
         assert steps == [], sites
 
 
-# Scratch that holds a partial sum for every 256 columns of a pair product and for every 128 planes of up to 8 x 8, but not the more and
+# Scratch that holds a partial sum for every 256 columns of a pair product and for every 128 planes (or 16 KB of them) of up to 8 x 8, but not the more and
 # smaller splits that the library asks room for: the same calls, with fewer splits.
 @pytest.mark.parametrize("dims,ranks,ws_bytes", [
     ((84, 172, 7, 7), (84, 37, 7, 6), 5658112), ((6, 1182, 8, 8), (6, 124, 8, 8), 6432768), ((10, 156, 8, 8), (10, 98, 8, 8), 1130496),
-    ((3, 70, 335), (3, 20, 40), 467968), ((2, 130, 402), (2, 50, 70), 1530624)])
+    ((3, 70, 335), (3, 20, 40), 467968), ((2, 130, 402), (2, 50, 70), 1530624), ((172, 360, 5, 5), (2, 128, 5, 5), 9788160)])
 def test_compress_with_scratch_for_fewer_partial_sums(dims, ranks, ws_bytes):
     """V is fp32 (pair products): 3e-5 of the factor's largest entry, as above."""
     _check_factors(dims, ranks, range(len(dims)), "f32", 0, "k_orth", 3e-5, ws_bytes)
