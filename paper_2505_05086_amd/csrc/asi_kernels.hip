@@ -316,13 +316,16 @@ static long long pair_cols_per_split(long long ncols, int nsplit) {
 }
 // The fewest tiles of up to four blocks of outputs, all of them as small as that allows.  Along the last mode as elsewhere: tiles of 64 for three
 // blocks cost 1 to 5 us more there (ranks 33 to 48 of modes of 640 to 2048, fp32 and bf16: compress 173.5 against 169.2 us, 105.3 against 101.0;
-// two or three tiles of 48, ranks 66 to 144, 264.0 against 271.5, 327.7 against 338.9).
-static int pair_tq(int r) {
+// two or three tiles of 48, ranks 66 to 144, 264.0 against 271.5, 327.7 against 338.9).  But tiles of 32 where the columns are too few for a
+// split (128) and every tile has a CU: the launch is one workgroup's chain, and half as long (512 x 64, 54 columns 9.3 -> 7.8 us, 100 11.6 -> 8.9,
+// 128 12.0 -> 9.2; rank 40 8.5 -> 7.7, 10.4 -> 8.9, 11.0 -> 9.0; four layers together 9.7 -> 7.8 and 12.3 -> 9.6).
+static int pair_tq(long long ncols, int n, int r) {
     const int blocks = (r + 15) / 16, gy = (blocks + 3) / 4;
+    if (blocks > 2 && ncols <= 128 && (long long)((n + PR_TI - 1) / PR_TI) * ((blocks + 1) / 2) <= 256) return 32;
     return 16 * ((blocks + gy - 1) / gy);
 }
 static int pair_best_splits(long long ncols, int n, int r) {
-    const int tq = pair_tq(r), lot = r > 32 ? 16 : 32;
+    const int tq = pair_tq(ncols, n, r), lot = r > 32 ? 16 : 32;
     const long long tiles = (long long)((n + PR_TI - 1) / PR_TI) * ((r + tq - 1) / tq);
     const double block = 308.0 * (tq / 16) + 88.0, partial = (double)n * r * (16.0 / 1600.0);
     long long maxs = (ncols + 127) / 128;                     // at least 128 columns per split
@@ -384,7 +387,7 @@ static bool make_pair_any(DType xt, const void* X, long long outer, int n, long 
     jb.X = X; jb.outer = outer; jb.inner = inner; jb.cols_per_split = pair_cols_per_split(ncols, nsplit);
     jb.Y = gen ? nullptr : Y; jb.part = part; jb.n = n; jb.r = r;
     jb.seed_lo = (uint32_t)(seed & 0xffffffffu); jb.seed_hi = (uint32_t)(seed >> 32); jb.mode = mode;
-    const int tq = pair_tq(r);
+    const int tq = pair_tq(ncols, n, r);
     jb.gx = (n + PR_TI - 1) / PR_TI; jb.gy = (r + tq - 1) / tq; jb.gz = nsplit;
     jb.zero = zero; jb.nzero = zero ? nzero : 0;
     if (pre) {

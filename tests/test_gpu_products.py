@@ -349,6 +349,29 @@ def test_linear_gradient_with_scratch_for_fewer_partial_sums(dims, ranks, dout, 
     assert float((dW - want).abs().max() / want.abs().max()) <= 1e-5
 
 
+# The pair product of a linear gradient (dout rows of the core's r1 x r2 columns, r3 outputs): tiles of 32 up to 128 columns while every tile
+# has a CU (128 rows of tiles of a rank of four blocks), the widest that the rank fills otherwise; the last
+# block and the last row of tiles not full.
+@pytest.mark.parametrize("dims,ranks,dout,tile", [
+    ((20, 30, 70), (8, 16, 50), 131, 32), ((20, 30, 70), (6, 22, 50), 131, 64), ((20, 50, 90), (3, 42, 33), 64, 32), ((20, 50, 90), (6, 9, 40), 4100, 32),
+    ((9, 30, 150), (2, 9, 100), 70, 32), ((9, 30, 90), (5, 7, 64), 8192, 32), ((9, 30, 90), (5, 7, 64), 8193, 64), ((20, 30, 70), (8, 16, 32), 70, 32),
+    ((20, 30, 70), (8, 16, 15), 70, 16)])
+def test_pair_product_of_few_columns(dims, ranks, dout, tile):
+    """Against float64: four chained fp32 sums of at most 270 terms, 2e-6 of the largest entry each."""
+    from paper_2505_05086_amd import binding as B
+    rng = np.random.default_rng(sum(ranks) + dout)
+    U = [_dev(np.linalg.qr(rng.standard_normal((n, r)))[0]) for n, r in zip(dims, ranks)]
+    S, gy = _dev(rng.standard_normal(ranks)), _dev(rng.standard_normal(dims[:2] + (dout,)))
+    desc, dW = B.make_desc(dims, ranks, "f32"), torch.empty(dout, dims[2], device="cuda")
+    ws = B.alloc_workspace(desc, None, dout)
+    ws.fill_(255)
+    sites = _sites(lambda: B.asi_weight_grad_linear(desc, S, U, gy, dout, dW, False, ws))
+    assert any("k_pair<float, true, false, %d>" % tile in s for s in sites), sites
+    xr = _modes(S, [u.t().contiguous() for u in U])
+    want = gy.double().reshape(-1, dout).t().contiguous() @ xr.reshape(-1, dims[2])
+    assert float((dW - want).abs().max() / want.abs().max()) <= 1e-5
+
+
 # Planes in 33 to 64 tiles: half as many workgroups where their partial sums alone would need a launch of the summing tree (up to 32 x 32),
 # not where another mode's do (a Gram form of 36 splits) or a pair product carries it (70 entries over 3 x 256 columns).
 # wgs: of the launch that the planes share with the Gram forms before them.
