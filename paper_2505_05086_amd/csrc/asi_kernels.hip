@@ -310,6 +310,9 @@ __global__ __launch_bounds__(PR_NT, 4) void k_pair_vec(Batch<PairJob> bt) {
 // the last product; then the partial sums, written and read once at some 1.6 KB a cycle, a round trip for every 16 (32 up to rank
 // 32) that gram0 adds up together, and beyond 32 of them a level of the partial-sum tree (one more launch on the chain).
 // Three 512 x 48 layers of 3136 columns: 10 | 13 | 17 | 25 | 32 splits 26.8 | 23.4 | 19.8 | 23.7 | 27.1 us, gram0 25.2 up to 16, then 27.4.
+// The second round trip is counted a little shorter for ranks of 33 to 48 along the last mode, whose tiles of 48 tie there with more splits:
+// 16 | 26 splits in compress of 14 x 295 x 576 at rank 45 109.1 | 106.1 us, 16 x 202 x 376 at 38 90.0 | 86.1 (three layers 112.3 | 106.8), 64 x 52 x 77 at
+// 37 70.0 | 67.3 (73.1 | 70.4); ranks of 49 to 64 gain 1 to 2 us alone and lose 4 in three layers.
 static long long pair_cols_per_split(long long ncols, int nsplit) {
     const long long cps = (ncols + nsplit - 1) / nsplit;
     return (cps + 15) / 16 * 16;
@@ -324,12 +327,13 @@ static int pair_tq(long long ncols, int n, int r) {
     if (blocks > 2 && ncols <= 128 && (long long)((n + PR_TI - 1) / PR_TI) * ((blocks + 1) / 2) <= 256) return 32;
     return 16 * ((blocks + gy - 1) / gy);
 }
-static int pair_best_splits(long long ncols, int n, int r) {
+static int pair_best_splits(long long ncols, int n, long long inner, int r) {
     const int tq = pair_tq(ncols, n, r), lot = r > 32 ? 16 : 32;
     const long long tiles = (long long)((n + PR_TI - 1) / PR_TI) * ((r + tq - 1) / tq);
     const double block = 308.0 * (tq / 16) + 88.0, partial = (double)n * r * (16.0 / 1600.0);
     long long maxs = (ncols + 127) / 128;                     // at least 128 columns per split
     maxs = maxs > 64 ? 64 : (maxs < 1 ? 1 : maxs);
+    const double second = inner == 1 && r > 32 && r <= 48 ? 8400.0 : 9600.0;
     int best = 1;
     double best_cost = -1.0;
     for (int ns = 1; ns <= (int)maxs; ns += ns < 16 ? 1 : 2) {
@@ -337,14 +341,14 @@ static int pair_best_splits(long long ncols, int n, int r) {
         if (ns > 1 && cps * (ns - 1) >= ncols) continue;      // the last split would be empty
         const long long per_cu = (tiles * ns + 255) >> 8;
         const double cost = (double)(per_cu * (cps >> 4)) * block + (per_cu > 1 ? 16000.0 : 8000.0) + ns * partial +
-                            (ns <= lot ? 4800.0 : (ns <= 2 * lot ? 9600.0 : 19200.0)) + (ns > 32 ? 10000.0 : 0.0);
+                            (ns <= lot ? 4800.0 : (ns <= 2 * lot ? second : 19200.0)) + (ns > 32 ? 10000.0 : 0.0);
         if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = ns; }
     }
     return best;
 }
 int pair_splits(long long outer, int n, long long inner, int r, bool coarse) {
     const long long ncols = outer * inner;
-    const int fine = pair_best_splits(ncols, n, r);
+    const int fine = pair_best_splits(ncols, n, inner, r);
     if (!coarse) return fine;
     // A count and no model of the tiles above: scratch that holds this many partial sums has always been accepted.  The least rounds x (columns of
     // a split, in chunks, + 128) of 512 workgroups of 64 x 32 (64 along the last mode), 256 columns or more a split.

@@ -330,6 +330,26 @@ def test_compress_with_scratch_for_fewer_partial_sums(dims, ranks, ws_bytes):
     _check_factors(dims, ranks, range(len(dims)), "f32", 0, "k_orth", 3e-5, ws_bytes)
 
 
+# The splits of a pair product along the last mode at a rank of three blocks where one round trip of partial sums and two tie: 26 of them
+# over 3232 columns of 376 rows (six tiles) and over 3328 of 77 (two).
+@pytest.mark.parametrize("dims,ranks,least", [((16, 202, 376), (4, 16, 38), 26 * 6), ((64, 52, 77), (4, 16, 37), 26 * 2)])
+def test_splits_of_pair_products_at_ranks_of_three_blocks(dims, ranks, least):
+    """V is fp32: 3e-5 of the factor's largest entry, as above."""
+    from paper_2505_05086_amd import binding as B
+    _check_factors(dims, ranks, (2,), "f32", 0, "k_pair<float, true, false, 48>", 3e-5)
+    rng = np.random.default_rng(3)
+    x, U = _dev(rng.standard_normal(dims)), [_dev(np.linalg.qr(rng.standard_normal((n, r)))[0]) for n, r in zip(dims, ranks)]
+    desc, info = B.make_desc(dims, ranks, "f32"), torch.zeros(1, dtype=torch.int32, device="cuda")
+    ws = B.alloc_workspace(desc, None, 0)
+    B.asi_profile_enable(True)
+    try:
+        B.asi_compress(desc, x, U, [torch.empty_like(u) for u in U], ws, info)
+        wgs = [v["workgroups"] for s, v in B.asi_profile_report().items() if "k_pair<float, true, false, 48>" in s]
+    finally:
+        B.asi_profile_enable(False)
+    assert len(wgs) == 1 and wgs[0] >= least, wgs        # (and those of the partial sums that ride along)
+
+
 @pytest.mark.parametrize("dims,ranks,dout,ws_bytes", [((11, 297, 200), (6, 34, 60), 904, 7832576), ((5, 352, 66), (3, 44, 55), 1623, 8784128)])
 def test_linear_gradient_with_scratch_for_fewer_partial_sums(dims, ranks, dout, ws_bytes):
     """Against float64: four chained fp32 sums of at most 352 terms, 2e-6 of the largest entry each."""
