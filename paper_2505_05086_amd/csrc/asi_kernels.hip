@@ -322,13 +322,18 @@ static long long pair_cols_per_split(long long ncols, int nsplit) {
 // two or three tiles of 48, ranks 66 to 144, 264.0 against 271.5, 327.7 against 338.9).  But tiles of 32 where the columns are too few for a
 // split (128) and every tile has a CU: the launch is one workgroup's chain, and half as long (512 x 64, 54 columns 9.3 -> 7.8 us, 100 11.6 -> 8.9,
 // 128 12.0 -> 9.2; rank 40 8.5 -> 7.7, 10.4 -> 8.9, 11.0 -> 9.0; four layers together 9.7 -> 7.8 and 12.3 -> 9.6).
-static int pair_tq(long long ncols, int n, int r) {
+// And for ranks of 49 to 64 over inner extents that are no multiple of four, whose loads go element by element, where 32 splits of such tiles
+// still have a CU each: 124 x 50 over 2 x 3935 columns 20.5 -> 15.0 us, 174 x 58 over 7 x 2206 29.6 -> 20.9, 128 x 64 over 64 x 49 16.8 -> 12.4 (eight
+// layers 26.9 -> 24.1; the first in eight 33.4 -> 35.8).  Ranks of 33 to 48 gain 2 to 4 us alone and lose as much in batches.
+static int pair_tq(long long ncols, int n, long long inner, int r) {
     const int blocks = (r + 15) / 16, gy = (blocks + 3) / 4;
-    if (blocks > 2 && ncols <= 128 && (long long)((n + PR_TI - 1) / PR_TI) * ((blocks + 1) / 2) <= 256) return 32;
+    const long long narrow = (long long)((n + PR_TI - 1) / PR_TI) * ((blocks + 1) / 2);
+    if (blocks > 2 && ncols <= 128 && narrow <= 256) return 32;
+    if (blocks == 4 && inner > 1 && inner % 4 != 0 && 32 * narrow <= 256) return 32;
     return 16 * ((blocks + gy - 1) / gy);
 }
 static int pair_best_splits(long long ncols, int n, long long inner, int r) {
-    const int tq = pair_tq(ncols, n, r), lot = r > 32 ? 16 : 32;
+    const int tq = pair_tq(ncols, n, inner, r), lot = r > 32 ? 16 : 32;
     const long long tiles = (long long)((n + PR_TI - 1) / PR_TI) * ((r + tq - 1) / tq);
     const double block = 308.0 * (tq / 16) + 88.0, partial = (double)n * r * (16.0 / 1600.0);
     long long maxs = (ncols + 127) / 128;                     // at least 128 columns per split
@@ -391,7 +396,7 @@ static bool make_pair_any(DType xt, const void* X, long long outer, int n, long 
     jb.X = X; jb.outer = outer; jb.inner = inner; jb.cols_per_split = pair_cols_per_split(ncols, nsplit);
     jb.Y = gen ? nullptr : Y; jb.part = part; jb.n = n; jb.r = r;
     jb.seed_lo = (uint32_t)(seed & 0xffffffffu); jb.seed_hi = (uint32_t)(seed >> 32); jb.mode = mode;
-    const int tq = pair_tq(ncols, n, r);
+    const int tq = pair_tq(ncols, n, inner, r);
     jb.gx = (n + PR_TI - 1) / PR_TI; jb.gy = (r + tq - 1) / tq; jb.gz = nsplit;
     jb.zero = zero; jb.nzero = zero ? nzero : 0;
     if (pre) {

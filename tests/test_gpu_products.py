@@ -330,6 +330,18 @@ def test_compress_with_scratch_for_fewer_partial_sums(dims, ranks, ws_bytes):
     _check_factors(dims, ranks, range(len(dims)), "f32", 0, "k_orth", 3e-5, ws_bytes)
 
 
+# Tiles of 32 for ranks of four blocks over inner extents that are no multiple of four while 32 splits of them have a CU each (four tiles of 64
+# rows); one row more, a multiple of four, a rank of three blocks: as wide as the rank.
+@pytest.mark.parametrize("dims,ranks,mode,form", [
+    ((3, 256, 333), (2, 64, 9), 1, "k_pair<%s, false, false, 32>"), ((3, 257, 333), (2, 64, 9), 1, "k_pair<%s, false, false, 64>"),
+    ((3, 100, 332), (2, 49, 9), 1, "k_pair_vec<%s, 64>"), ((5, 100, 331), (2, 49, 9), 1, "k_pair<%s, false, false, 32>"),
+    ((5, 100, 331), (2, 48, 9), 1, "k_pair<%s, false, false, 48>"), ((9, 130, 5, 7), (5, 50, 5, 5), 1, "k_pair<%s, false, false, 32>")])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_pair_tiles_over_inner_extents_that_are_no_multiple_of_four(dims, ranks, mode, form, dtype):
+    """V is fp32: 3e-5 of the factor's largest entry, as above."""
+    _check_factors(dims, ranks, (mode,), dtype, 0, form % ("float" if dtype == "f32" else "asi::bf16_t"), 3e-5)
+
+
 # The splits of a pair product along the last mode at a rank of three blocks where one round trip of partial sums and two tie: 26 of them
 # over 3232 columns of 376 rows (six tiles) and over 3328 of 77 (two).
 @pytest.mark.parametrize("dims,ranks,least", [((16, 202, 376), (4, 16, 38), 26 * 6), ((64, 52, 77), (4, 16, 37), 26 * 2)])
